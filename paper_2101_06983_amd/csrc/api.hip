@@ -554,10 +554,11 @@ int gc_bidirectional_loss_and_rep_grad_bf16(const void* q, const void* p, const 
     if (rc != GC_OK) return rc;
     // dL/df = Eq. 5 of direction 1 + Eq. 6 of direction 2, dL/dg the other two; fixed order
     const size_t ne = (size_t)n * d;
-    { const float* srcs[2] = {g[0], g[3]}; int counts[2] = {1, 1}; size_t strides[2] = {ne, ne};
-      if (launch_partial_reduce(dq, srcs, counts, strides, 2, ne, s) != hipSuccess) return GC_ERR_HIP; }
-    { const float* srcs[2] = {g[1], g[2]}; int counts[2] = {1, 1}; size_t strides[2] = {ne, ne};
-      if (launch_partial_reduce(dp, srcs, counts, strides, 2, ne, s) != hipSuccess) return GC_ERR_HIP; }
+    ReduceJob j[2] = {};
+    j[0].out = dq; j[0].ptr[0] = g[0]; j[0].ptr[1] = g[3];
+    j[1].out = dp; j[1].ptr[0] = g[1]; j[1].ptr[1] = g[2];
+    for (ReduceJob& k : j) { k.n = ne; k.nsrc = 2; k.count[0] = k.count[1] = 1; }
+    if (launch_reduce_jobs(j, 2, s) != hipSuccess) return GC_ERR_HIP;
   }
   return launch_sym_loss_sum(a1, a2, sp.pl, loss) == hipSuccess ? GC_OK : GC_ERR_HIP;
 }

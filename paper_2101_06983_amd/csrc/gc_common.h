@@ -121,10 +121,29 @@ hipError_t launch_sym_loss_sum(const LossArgs& a1, const LossArgs& a2, const Los
 hipError_t launch_stats_merge(const LossArgs& a, const LossPlan& pl);
 void prof_mark_grad_kernel_done(hipStream_t s);  // measurement aid: event after the main gradient kernel(s)
 bool prof_active();  // the measurement events of the loss path are being recorded
-// loss_of / pl: also carry the sum of the row losses of that call (see LossArgs::loss_with_partials)
-hipError_t launch_partial_reduce(float* out, const float* const* srcs, const int* counts, const size_t* strides,
-                                 int nsrc, size_t n, hipStream_t stream, const LossArgs* loss_of = nullptr,
-                                 const LossPlan* pl = nullptr, bool out_bf16 = false, const PosFix* fix = nullptr);
+// One output of a fixed-order sum of partials (partial_reduce_kernel): up to two sources of several equal parts each.  Parts
+// start at multiples of 4 floats and have room for whole vectors.
+struct ReduceJob {
+  void* out;
+  size_t n;                 // elements
+  int nsrc;
+  const float* ptr[2];
+  int count[2];
+  size_t stride[2];         // floats between the parts of a source
+  int out_bf16;             // the sum is stored as bf16 (round to nearest even)
+  PosFix fix;
+  int vec;                  // set by launch_reduce_jobs: `out` takes vector stores
+};
+// one launch for up to two outputs; loss_of / pl: it also carries the sum of the row losses of that call (see
+// LossArgs::loss_with_partials)
+hipError_t launch_reduce_jobs(const ReduceJob* jobs, int njobs, hipStream_t stream, const LossArgs* loss_of = nullptr,
+                              const LossPlan* pl = nullptr);
+// out[n] = the sum of `count` parts, `stride` floats apart
+inline hipError_t launch_partial_sum(float* out, const float* part, int count, size_t stride, size_t n, hipStream_t stream) {
+  ReduceJob j{};
+  j.out = out; j.n = n; j.nsrc = 1; j.ptr[0] = part; j.count[0] = count; j.stride[0] = stride;
+  return launch_reduce_jobs(&j, 1, stream);
+}
 
 // Workgroups are handed to the 8 XCDs round-robin by their id, and each XCD has its own L2.  This
 // turns the hardware id into a task id such that each XCD works on one contiguous range of tasks

@@ -244,16 +244,11 @@ __global__ void __launch_bounds__(256) grad_generic_kernel(const T* __restrict__
   }
 }
 
-// out[e] = sum over sources s, over parts k < counts[s] of srcs[s][k * strides[s] + e], fixed order.
-struct ReduceSrc {
-  const float* ptr[4];
-  int count[4];
-  size_t stride[4];
-  int nsrc;
-  int out_bf16;   // the sum is stored as bf16 (round to nearest even), `out` then points to bf16 elements
-};
-// With a loss sum attached the grid has one more workgroup, the first (so that it runs beside the others), which carries it (it has nothing to do with
-// the partial sums; it only saves a launch on the path that needs both).
+// Fixed-order sums of split partials: out[e] = sum over sources s, over parts k < count[s] of ptr[s][k * stride[s] + e],
+// up to two outputs (dq and dp) in one launch.  With a loss sum attached the grid has one more workgroup, the first (so
+// that it runs beside the others), which carries it (it has nothing to do with the partial sums; it only saves a launch
+// on the path that needs both).
+struct ReduceArgs { ReduceJob job[2]; unsigned blocks0; LossSum ls; };
 // coefficient of the positive of anchor i (target r), see PosFix
 __device__ __forceinline__ float pos_coeff(const PosFix& f, int i, int r) {
   const float t = f.pos_t[i];
@@ -266,46 +261,117 @@ __device__ __forceinline__ void add_row4(f32x4& acc, float c, const unsigned sho
 #pragma unroll
   for (int k = 0; k < 4; k++) acc[k] += c * bf2f((unsigned short)v[k]);
 }
-__global__ void __launch_bounds__(256) partial_reduce_kernel(float* __restrict__ out, ReduceSrc rs, size_t n4, LossSum ls,
-                                                            PosFix fx) {
-  __shared__ float red[1024];
-  if (ls.rowloss && blockIdx.x == 0) {
-    loss_sum_block<256>(ls, red);
-    return;
+// Some target is the positive of several anchors: every anchor that names one of the rows of this workgroup's 1024
+// elements, in index order.  The workgroup looks through the anchors together, 256 at a time, and keeps the matches (in
+// index order: ballot and prefix inside a wave, waves one after the other) in LDS; each thread then adds those of its
+// own row.  (A scan by every thread for itself took 179 of the 253 us of a call with B = 1021, P = 4099, d = 384; the
+// list takes that launch to 8 us.  Rows that no anchor names, the most of them, are skipped.)
+__device__ __forceinline__ void add_shared_positives(f32x4& acc, const PosFix& fx, size_t n4, unsigned block, int row, int col, bool live,
+                                                     int* list /* [256] in LDS */, int* cnt /* [4] */) {
+  const size_t first = (size_t)block * 256, last = first + 255 < n4 ? first + 255 : n4 - 1;
+  const int row0 = (int)(first * 4 / (size_t)fx.d), row1 = (int)((last * 4 + 3) / (size_t)fx.d);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  bool named = false;
+  if (live) {   // the merge records one of the anchors of every named target (whatever the workspace held, if none: checked)
+    const int i = fx.inv[row];
+    named = i >= 0 && i < fx.B && fx.pos[i] == row;
   }
-  size_t e = (size_t)(blockIdx.x - (ls.rowloss ? 1 : 0)) * blockDim.x + threadIdx.x;
-  if (e >= n4) return;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int s = 0; s < rs.nsrc; s++)
-    for (int k = 0; k < rs.count[s]; k++) acc += ((const f32x4*)(rs.ptr[s] + (size_t)k * rs.stride[s]))[e];
-  if (fx.mode) {   // the positive's term, in fp32, after the partials (d is a multiple of 4 here)
-    const int row = (int)((e * 4) / (size_t)fx.d), col = (int)((e * 4) % (size_t)fx.d);
-    if (fx.mode == 1) {
-      const int r = fx.pos[row];
-      if (r >= 0 && r < fx.P) add_row4(acc, pos_coeff(fx, row, r), fx.other + (size_t)r * fx.d, col);
-    } else if (*fx.shared == 0) {
-      const int i = fx.inv[row];   // whatever the workspace held if no anchor names this target: checked
-      if (i >= 0 && i < fx.B && fx.pos[i] == row) add_row4(acc, pos_coeff(fx, i, row), fx.other + (size_t)i * fx.d, col);
-    } else {   // some target is shared: every anchor that names this one, in index order
-      for (int i = 0; i < fx.B; i++)
-        if (fx.pos[i] == row) add_row4(acc, pos_coeff(fx, i, row), fx.other + (size_t)i * fx.d, col);
+  if (!__syncthreads_or(named)) return;
+  for (int i0 = 0; i0 < fx.B; i0 += 256) {
+    const int i = i0 + (int)threadIdx.x;
+    const int r = i < fx.B ? fx.pos[i] : -1;
+    const bool match = r >= row0 && r <= row1;
+    const unsigned long long mask = __builtin_amdgcn_ballot_w64(match);
+    if (lane == 0) cnt[w] = __builtin_popcountll(mask);
+    __syncthreads();
+    int base = 0;
+    for (int k = 0; k < w; k++) base += cnt[k];
+    const int total = cnt[0] + cnt[1] + cnt[2] + cnt[3];
+    if (match) list[base + __builtin_popcountll(mask & ((1ull << lane) - 1ull))] = i;
+    __syncthreads();
+    for (int k = 0; k < total; k++) {
+      const int a = list[k];
+      if (live && fx.pos[a] == row) add_row4(acc, pos_coeff(fx, a, row), fx.other + (size_t)a * fx.d, col);
     }
-  }
-  if (rs.out_bf16) {
-    typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
-    ((bf16x4_t*)out)[e] = __builtin_convertvector(acc, bf16x4_t);
-  } else {
-    ((f32x4*)out)[e] = acc;
+    __syncthreads();   // the list and the counts are free again
   }
 }
-__global__ void __launch_bounds__(256) partial_reduce_tail_kernel(float* __restrict__ out, ReduceSrc rs, size_t beg, size_t n) {
-  size_t e = beg + (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n) return;
-  float acc = 0.f;
-  for (int s = 0; s < rs.nsrc; s++)
-    for (int k = 0; k < rs.count[s]; k++) acc += rs.ptr[s][(size_t)k * rs.stride[s] + e];
-  if (rs.out_bf16) ((__bf16*)out)[e] = (__bf16)acc;
-  else out[e] = acc;
+__global__ void __launch_bounds__(256) partial_reduce_kernel(ReduceArgs a) {
+  __shared__ float red[1024];
+  __shared__ int cnt[4];
+  unsigned block = blockIdx.x;
+  if (a.ls.rowloss) {
+    if (block == 0) {
+      loss_sum_block<256>(a.ls, red);
+      return;
+    }
+    block--;
+  }
+  const bool second = block >= a.blocks0;
+  if (second) block -= a.blocks0;
+  const ReduceJob& j = second ? a.job[1] : a.job[0];
+  const PosFix& fx = j.fix;
+  const size_t e = (size_t)block * 256 + threadIdx.x, n4 = (j.n + 3) / 4;
+  const bool live = e < n4;
+  // The loads of the positive's term depend on each other three deep (anchor, its statistics, its row): they are issued
+  // around those of the first partials, so that a workgroup waits for memory about twice and not five times.
+  int row = 0, col = 0, pi = -1, shared = 0;
+  if (fx.mode && live) {   // (d is a multiple of 4 here)
+    const size_t first = (size_t)block * 1024;   // the same in every thread: the 64-bit division runs on the scalar unit
+    const unsigned row0 = (unsigned)(first / (unsigned)fx.d), off = (unsigned)(first - (size_t)row0 * (unsigned)fx.d) + 4 * threadIdx.x;
+    row = (int)(row0 + off / (unsigned)fx.d);
+    col = (int)(off % (unsigned)fx.d);
+    pi = fx.mode == 1 ? fx.pos[row] : fx.inv[row];   // inv: whatever the workspace held if no anchor names this target
+  }
+  if (fx.mode == 2) shared = *fx.shared;
+  f32x4 v[4];
+#pragma unroll
+  for (int k = 0; k < 4; k++) {
+    v[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (live && k < j.count[0]) v[k] = ((const f32x4*)(j.ptr[0] + (size_t)k * j.stride[0]))[e];
+  }
+  // anchor and target of the positive's term, and whether this element has one
+  int fi = row, fr = pi;
+  bool fix = false;
+  if (fx.mode == 1) {
+    fix = pi >= 0 && pi < fx.P;
+  } else if (fx.mode == 2) {
+    fi = pi; fr = row;
+    fix = shared == 0 && pi >= 0 && pi < fx.B && fx.pos[pi] == row;   // checked
+  }
+  float c = 0.f;
+  s16x4 other = {0, 0, 0, 0};
+  if (fix) {
+    other = *(const s16x4*)(fx.other + (size_t)(fx.mode == 1 ? fr : fi) * fx.d + col);
+    c = pos_coeff(fx, fi, fr);
+  }
+  f32x4 acc = v[0];
+#pragma unroll
+  for (int k = 1; k < 4; k++)
+    if (k < j.count[0]) acc += v[k];
+  if (live) {   // (partials have room for whole vectors)
+    for (int s = 0; s < j.nsrc; s++)
+      for (int k = s == 0 ? 4 : 0; k < j.count[s]; k++) acc += ((const f32x4*)(j.ptr[s] + (size_t)k * j.stride[s]))[e];
+  }
+  if (fix) {   // the positive's term, in fp32, after the partials
+#pragma unroll
+    for (int k = 0; k < 4; k++) acc[k] += c * bf2f((unsigned short)other[k]);
+  }
+  if (shared) add_shared_positives(acc, fx, n4, block, row, col, live, (int*)red, cnt);
+  if (!live) return;
+  if (4 * e + 4 <= j.n && j.vec) {
+    if (j.out_bf16) {
+      typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
+      ((bf16x4_t*)j.out)[e] = __builtin_convertvector(acc, bf16x4_t);
+    } else {
+      ((f32x4*)j.out)[e] = acc;
+    }
+  } else {   // the last elements of an odd count, or an output that is only aligned to its elements
+    for (int k = 0; k < 4 && 4 * e + k < j.n; k++) {
+      if (j.out_bf16) ((__bf16*)j.out)[4 * e + k] = (__bf16)acc[k];
+      else ((float*)j.out)[4 * e + k] = acc[k];
+    }
+  }
 }
 
 // Fused mode: merge of what the splits of the online dQ walk left per anchor (reference, sum 2^(t - reference), and
@@ -415,22 +481,19 @@ static LossSum loss_sum_of(const LossArgs& a, const LossPlan& pl) {
   return ls;
 }
 
-hipError_t launch_partial_reduce(float* out, const float* const* srcs, const int* counts, const size_t* strides,
-                                 int nsrc, size_t n, hipStream_t stream, const LossArgs* loss_of, const LossPlan* pl,
-                                 bool out_bf16, const PosFix* fix) {
-  ReduceSrc rs{};
-  rs.nsrc = nsrc;
-  rs.out_bf16 = out_bf16 ? 1 : 0;
-  for (int s = 0; s < nsrc; s++) { rs.ptr[s] = srcs[s]; rs.count[s] = counts[s]; rs.stride[s] = strides[s]; }
-  LossSum ls{};
-  if (loss_of) ls = loss_sum_of(*loss_of, *pl);
-  PosFix fx{};
-  if (fix) fx = *fix;
-  if (fx.mode && (n % 4 || fx.d % 4)) return hipErrorInvalidValue;   // the term is added by the 4-element kernel only
-  size_t n4 = n / 4;
-  if (n4 || loss_of)
-    partial_reduce_kernel<<<dim3((unsigned)((n4 + 255) / 256 + (loss_of ? 1 : 0))), 256, 0, stream>>>(out, rs, n4, ls, fx);
-  if (n4 * 4 < n) partial_reduce_tail_kernel<<<1, 256, 0, stream>>>(out, rs, n4 * 4, n);
+hipError_t launch_reduce_jobs(const ReduceJob* jobs, int njobs, hipStream_t stream, const LossArgs* loss_of, const LossPlan* pl) {
+  ReduceArgs a{};
+  unsigned blocks[2] = {0, 0};
+  for (int k = 0; k < njobs; k++) {
+    a.job[k] = jobs[k];
+    a.job[k].vec = ((uintptr_t)jobs[k].out & (jobs[k].out_bf16 ? 7 : 15)) == 0;
+    if (jobs[k].fix.mode && (jobs[k].n % 4 || jobs[k].fix.d % 4)) return hipErrorInvalidValue;   // rows of whole vectors only
+    blocks[k] = (unsigned)(((jobs[k].n + 3) / 4 + 255) / 256);
+  }
+  a.blocks0 = blocks[0];
+  if (loss_of) a.ls = loss_sum_of(*loss_of, *pl);
+  const unsigned n = blocks[0] + blocks[1] + (loss_of ? 1 : 0);
+  if (n) partial_reduce_kernel<<<dim3(n), 256, 0, stream>>>(a);
   return hipGetLastError();
 }
 
@@ -507,10 +570,10 @@ static hipError_t grad_generic_t(const LossArgs& a, const LossPlan& pl) {
   if (e != hipSuccess) return e;
   prof_mark_grad_kernel_done(a.stream);
   if (a.dz) {
-    const float* srcs[2] = {dq, dp};
-    int counts[2] = {1, 1};
-    size_t strides[2] = {0, 0};
-    return launch_partial_reduce(a.dz, srcs, counts, strides, 2, (size_t)a.B * a.d, a.stream);
+    ReduceJob j{};
+    j.out = a.dz; j.n = (size_t)a.B * a.d; j.nsrc = 2;
+    j.ptr[0] = dq; j.ptr[1] = dp; j.count[0] = j.count[1] = 1;
+    return launch_reduce_jobs(&j, 1, a.stream);
   }
   return hipSuccess;
 }

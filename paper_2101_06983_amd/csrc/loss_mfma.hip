@@ -1610,32 +1610,27 @@ hipError_t launch_grad_mfma(const LossArgs& a, const LossPlan& pl) {
   }
   if (e != hipSuccess) return e;
   prof_mark_grad_kernel_done(a.stream);
-  // fixed-order sums of the split partials, each with the positive's term of its rows; the first of these
-  // launches also sums the row losses if asked to
+  // fixed-order sums of the split partials, each with the positive's term of its rows: one launch, which also sums the
+  // row losses if asked to
   PosFix fx{};
   fx.pos = ga.pos_pad; fx.pos_t = (const float*)(ws + pl.off_pos); fx.lse2 = ga.lse2; fx.lse2_t = ga.lse2_t;
   fx.B = a.B; fx.P = a.P; fx.d = a.d; fx.scale = ga.out_scale;
-  const LossArgs* loss_of = a.loss_with_partials ? &a : nullptr;
-  if (a.dz) {   // NT-Xent, one walk: rows are anchors, the positive of view i is view i ^ 1
-    fx.mode = 1; fx.other = ga.P;
-    const float* srcs[1] = {ga.dq_out}; int counts[1] = {pl.nsq}; size_t strides[1] = {nq};
-    return launch_partial_reduce(a.dz, srcs, counts, strides, 1, nq, a.stream, loss_of, &pl, false, &fx);
-  }
-  if (want_q) {
-    fx.mode = 1; fx.other = ga.P;
-    const float* srcs[1] = {ga.dq_out}; int counts[1] = {pl.nsq}; size_t strides[1] = {nq};
-    e = launch_partial_reduce(a.dq, srcs, counts, strides, 1, nq, a.stream, loss_of, &pl, cache_bf16, &fx);
-    if (e != hipSuccess) return e;
-    loss_of = nullptr;
+  ReduceJob job[2] = {};
+  int n = 0;
+  if (want_q) {   // rows are anchors (NT-Xent, one walk: the positive of view i is view i ^ 1)
+    ReduceJob& j = job[n++];
+    j.out = a.dz ? (void*)a.dz : (void*)a.dq; j.n = nq; j.nsrc = 1; j.ptr[0] = ga.dq_out; j.count[0] = pl.nsq; j.stride[0] = nq;
+    j.out_bf16 = cache_bf16 && !a.dz;
+    j.fix = fx; j.fix.mode = 1; j.fix.other = ga.P;
   }
   if (want_p) {
-    fx.mode = 2; fx.other = ga.Q;
-    fx.inv = sym_pairs ? a.pos_inv : ga.inv; fx.shared = sym_pairs ? a.zero_word : ga.shared;
-    const float* srcs[1] = {ga.dp_out}; int counts[1] = {pl.nsp}; size_t strides[1] = {np};
-    e = launch_partial_reduce(a.dp, srcs, counts, strides, 1, np, a.stream, loss_of, &pl, cache_bf16, &fx);
-    if (e != hipSuccess) return e;
+    ReduceJob& j = job[n++];
+    j.out = a.dp; j.n = np; j.nsrc = 1; j.ptr[0] = ga.dp_out; j.count[0] = pl.nsp; j.stride[0] = np;
+    j.out_bf16 = cache_bf16;
+    j.fix = fx; j.fix.mode = 2; j.fix.other = ga.Q;
+    j.fix.inv = sym_pairs ? a.pos_inv : ga.inv; j.fix.shared = sym_pairs ? a.zero_word : ga.shared;
   }
-  return hipSuccess;
+  return launch_reduce_jobs(job, n, a.stream, a.loss_with_partials ? &a : nullptr, &pl);
 }
 
 }  // namespace gc

@@ -1416,8 +1416,7 @@ int gc_bilinear_loss_and_grads_bf16(const void* q, const void* p, const int32_t*
     g.A = q; g.lda = d; g.B = A; g.ldb = d; g.M = d; g.N = d; g.K = B; g.C = part; g.ldc = d;
     wgrad_splitk_kernel<false, true><<<(d / 128) * (d / WG_M) * w.slices, 256, 0, s>>>(g, w.rows_per_slice);
     if (hipGetLastError() != hipSuccess) return GC_ERR_HIP;
-    const float* srcs[1] = {part}; int counts[1] = {w.slices}; size_t strides[1] = {(size_t)d * d};
-    if (launch_partial_reduce(domega, srcs, counts, strides, 1, (size_t)d * d, s) != hipSuccess) return GC_ERR_HIP;
+    if (launch_partial_sum(domega, part, w.slices, (size_t)d * d, (size_t)d * d, s) != hipSuccess) return GC_ERR_HIP;
   }
   return GC_OK;
 }
@@ -1493,8 +1492,7 @@ int gc_deepdist_loss_and_grads_bf16(const void* q, const void* p, const int32_t*
   deepdist_walk_kernel<128, DD_DC><<<obC * pw.nsc, 256, 0, s>>>(g);
   if (hipGetLastError() != hipSuccess) return GC_ERR_HIP;
   auto sum_parts = [&](float* out, size_t off_part, int parts, size_t n) {
-    const float* srcs[1] = {(const float*)(ws + off_part)}; int counts[1] = {parts}; size_t strides[1] = {n};
-    return launch_partial_reduce(out, srcs, counts, strides, 1, n, s);
+    return launch_partial_sum(out, (const float*)(ws + off_part), parts, n, n, s);
   };
   if (sum_parts(dc, pw.off_dc_part, pw.nsc, (size_t)P * h) != hipSuccess) return GC_ERR_HIP;
   {  // dL/dw_k = sum_i e_ik: row slices, then their fixed-order sum
