@@ -18,8 +18,8 @@
  *     workspace argument: they use a per-device buffer the library allocates
  *     with hipMalloc on first use and grows on demand (growing frees the old
  *     buffer with hipFree, which waits for the device; while `stream` is being
- *     captured into a graph a call that would have to grow it returns
- *     GC_ERR_UNSUPPORTED instead).  Such calls share the buffer, so the library
+ *     captured into a graph a call that would have to grow it takes the kernels
+ *     that fit, or returns GC_ERR_UNSUPPORTED).  Such calls share the buffer, so the library
  *     puts them in order: a call made on another stream than the previous one
  *     first waits (on the GPU, through an event) for that one's kernels.  Calls
  *     made while their stream is being captured are not ordered this way and
@@ -96,9 +96,12 @@ size_t gc_workspace_bytes(int B, int P, int d, int dt);
  *   loss    [1]    float: (1/B) sum_i (logsumexp_j s_ij - s_{i,r_i})
  *   dq      [B,d]  float: (scale/(temp B)) sum_j (softmax_j(s_i.) - [j = r_i]) p_j
  *   dp      [P,d]  float: (scale/(temp B)) sum_i (softmax_j(s_i.) - [j = r_i]) q_i
- * Any B, P >= 1 and d >= 1 are accepted (ragged sizes are masked); the MFMA
- * kernels serve bf16 with d a multiple of 128 up to 768, other cases take a
- * slower general kernel.  Errors: GC_ERR_NULL, GC_ERR_SHAPE, GC_ERR_HIP.
+ * Any B, P >= 1 and d >= 1 are accepted (ragged sizes are masked).  bf16 with d
+ * a multiple of 128 up to 768 keeps the softmax coefficients in bf16 where they
+ * enter the gradient contractions; fp32 inputs and every other width are computed
+ * in fp32-grade arithmetic throughout (three bf16 numbers per fp32 value on the
+ * matrix cores), from packed copies of the inputs in the workspace.
+ * Errors: GC_ERR_NULL, GC_ERR_SHAPE, GC_ERR_HIP.
  */
 int gc_loss_and_rep_grad_bf16(const void* q, const void* p, const int32_t* pos_idx, int B, int P, int d,
                               float scale, float temp, float* loss, float* dq, float* dp, void* stream);
@@ -112,7 +115,9 @@ int gc_loss_and_rep_grad_f32(const float* q, const float* p, const int32_t* pos_
  * the library's device image, one copy per GPU, held until the process ends: the call makes no hipMalloc, hipFree
  * or other allocating call, and its first use on a device only looks the array's address up.  Shapes with
  * gc_workspace_bytes(B, P, d, GC_BF16) > GC_STATIC_SCRATCH_BYTES are rejected with GC_ERR_TOO_LARGE and nothing is
- * enqueued (the limit covers e.g. B = 512, P = 1024, d = 768).  Every call on a GPU uses that GPU's one array,
+ * enqueued (the limit covers e.g. B = 512, P = 1024, d = 768).  Widths that are no multiple of 128 up to 768 are not
+ * rejected for their packed inputs: where those do not fit beside the statistics, fewer splits or slower kernels without
+ * packed inputs serve the call, and results agree with gc_loss_and_rep_grad_bf16 to fp32 rounding.  Every call on a GPU uses that GPU's one array,
  * which keeps the previous call's contents (the kernels overwrite what they read): two calls that overlap in time
  * on one GPU, on whatever streams, race; calls on one stream are safe.  A pos_idx outside [0, P) shows as
  * loss = NaN, and gc_check_async_error(NULL) also reads this array's error word.

@@ -29,11 +29,14 @@ int num_cu() {
   return cached;
 }
 
-LossPlan make_loss_plan(int B, int P, int d, gc_dtype dt, bool ntxent) {
+static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent, int route, int max_splits) {
   LossPlan pl{};
   const int kNumCU = num_cu();
-  pl.use_mfma = (dt == GC_BF16 && d % 128 == 0 && d >= 128 && d <= 768) ? 1 : 0;
-  if (pl.use_mfma) {
+  pl.route = route;
+  pl.use_mfma = route == ROUTE_MFMA ? 1 : 0;
+  if (route == ROUTE_PLANES) {
+    plan_planes(pl, B, P, d, dt, max_splits);
+  } else if (pl.use_mfma) {
     const int n_ablk = ceil_div(B, 256), tiles = ceil_div(P, 256);
     // d = 128 has a statistics kernel of 256 threads, two workgroups to a CU
     int splits = ceil_div(d == 128 ? 2 * kNumCU : kNumCU, n_ablk);
@@ -102,7 +105,7 @@ LossPlan make_loss_plan(int B, int P, int d, gc_dtype dt, bool ntxent) {
   pl.off_part_l = take((size_t)stat_parts * B * 4);
   pl.off_part_idx = take((size_t)stat_parts * B * 4);
   pl.off_pos = take((size_t)B * 4);
-  pl.b_pad = (B + 63) / 64 * 64;
+  pl.b_pad = route == ROUTE_PLANES ? (B + 127) / 128 * 128 : (B + 63) / 64 * 64;
   pl.off_lse2 = take((size_t)pl.b_pad * 4);
   pl.off_pos_pad = take((size_t)pl.b_pad * 4);
   pl.off_rowloss = take((size_t)B * 4);
@@ -118,12 +121,34 @@ LossPlan make_loss_plan(int B, int P, int d, gc_dtype dt, bool ntxent) {
     if (pl.fz_nsq > dq_parts) dq_parts = pl.fz_nsq;            // the online walk always writes partials
     if (pl.fz_nsp > 1 && pl.fz_nsp > dp_parts) dp_parts = pl.fz_nsp;
   }
-  pl.off_dq_part = take((size_t)dq_parts * B * d * 4);
-  pl.off_dp_part = take((size_t)dp_parts * P * d * 4);
+  pl.px_stride_q = align_up((size_t)B * d, 4);
+  pl.px_stride_p = align_up((size_t)P * d, 4);
+  pl.off_dq_part = take((size_t)dq_parts * (route == ROUTE_PLANES ? pl.px_stride_q : (size_t)B * d) * 4);
+  pl.off_dp_part = take((size_t)dp_parts * (route == ROUTE_PLANES ? pl.px_stride_p : (size_t)P * d) * 4);
+  if (route == ROUTE_PLANES) {
+    const size_t per_row = (size_t)pl.px_KS * 16 * 2 * pl.np;
+    pl.off_qk = take(pl.px_rows_q * per_row);
+    pl.off_qt = take(pl.px_rows_q * per_row);
+    pl.off_pk = take(pl.px_rows_p * per_row);
+    pl.off_pt = take(pl.px_rows_p * per_row);
+  }
   pl.off_on_ref = take((size_t)pl.fz_nsq * B * 4);
   pl.off_pos_idx = take(ntxent ? (size_t)B * 4 : 0);
   pl.total = off;
   return pl;
+}
+// what the packed inputs and partials may take without being asked about (the rest of a 288 GB card is the caller's)
+constexpr size_t kPlanesMaxBytes = (size_t)32 << 30;
+LossPlan make_loss_plan(int B, int P, int d, gc_dtype dt, bool ntxent, size_t limit) {
+  if (dt == GC_BF16 && d % 128 == 0 && d >= 128 && d <= 768) return make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_MFMA, 16);
+  // a handful of scores: the five launches of the planes cost more than the four of the general kernels (30 against 29 us
+  // at 8 x 16 x 64)
+  const bool tiny = (long long)B * P * d <= (1ll << 14);
+  for (int splits = 16; splits >= 1 && !tiny; splits /= 2) {
+    const LossPlan pl = make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_PLANES, splits);
+    if (pl.total <= limit && pl.total <= kPlanesMaxBytes) return pl;
+  }
+  return make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_GENERAL, 1);
 }
 
 static bool shape_ok(int B, int P, int d) {
@@ -137,7 +162,8 @@ static std::mutex g_ws_mutex;
 static void* g_ws_ptr[64];
 static size_t g_ws_bytes[64];
 
-static int own_workspace(size_t need, hipStream_t stream, void** out) {
+// `have` (with *out) also tells what there is when the answer is GC_ERR_UNSUPPORTED
+static int own_workspace(size_t need, hipStream_t stream, void** out, size_t* have) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return GC_ERR_HIP;
   std::lock_guard<std::mutex> lock(g_ws_mutex);
@@ -146,7 +172,11 @@ static int own_workspace(size_t need, hipStream_t stream, void** out) {
     // caller's stream is being captured into a graph
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &cap) != hipSuccess) { (void)hipGetLastError(); cap = hipStreamCaptureStatusNone; }
-    if (cap != hipStreamCaptureStatusNone) return GC_ERR_UNSUPPORTED;
+    if (cap != hipStreamCaptureStatusNone) {
+      *out = g_ws_ptr[dev];
+      *have = g_ws_bytes[dev];
+      return GC_ERR_UNSUPPORTED;
+    }
     if (g_ws_ptr[dev]) (void)hipFree(g_ws_ptr[dev]);  // waits for work that still uses it
     g_ws_ptr[dev] = nullptr;
     g_ws_bytes[dev] = 0;
@@ -155,6 +185,7 @@ static int own_workspace(size_t need, hipStream_t stream, void** out) {
     g_ws_bytes[dev] = sz;
   }
   *out = g_ws_ptr[dev];
+  *have = g_ws_bytes[dev];
   return GC_OK;
 }
 
@@ -226,8 +257,9 @@ bool prof_active() { return g_prof.on; }
 
 static int run_loss(const LossArgs& a_in, const LossPlan& pl) {
   LossArgs a = a_in;
-  // does the gradient pass of this call end in a sum of split partials (launch_grad_mfma)?
-  a.loss_with_partials = pl.use_mfma && !a.lse2_t && (a.dz || a.dq || a.dp);
+  if (!a.ws2) a.ws2 = a.ws;
+  // does the gradient pass of this call end in a sum of split partials that takes the row losses along?
+  a.loss_with_partials = pl.route != ROUTE_GENERAL && !a.lse2_t && !a.defer_loss_sum && (a.dz || a.dq || a.dp);
   const int call = g_prof.calls;
   prof_mark(call, 0, a.stream);
   hipError_t e;
@@ -259,7 +291,7 @@ static int run_loss(const LossArgs& a_in, const LossPlan& pl) {
     return GC_OK;
   }
   if (!a.lse2_t) {
-    e = pl.use_mfma ? launch_stats_mfma(a, pl) : launch_stats_generic(a, pl);
+    e = pl.route == ROUTE_MFMA ? launch_stats_mfma(a, pl) : pl.route == ROUTE_PLANES ? launch_stats_planes(a, pl) : launch_stats_generic(a, pl);
     if (e != hipSuccess) return GC_ERR_HIP;
   }
   prof_mark(call, 1, a.stream);
@@ -269,7 +301,7 @@ static int run_loss(const LossArgs& a_in, const LossPlan& pl) {
   }
   prof_mark(call, 2, a.stream);
   if (a.dq || a.dp || a.dz) {
-    e = pl.use_mfma ? launch_grad_mfma(a, pl) : launch_grad_generic(a, pl);  // records mark 3 after its main kernel(s)
+    e = pl.route == ROUTE_MFMA ? launch_grad_mfma(a, pl) : pl.route == ROUTE_PLANES ? launch_grad_planes(a, pl) : launch_grad_generic(a, pl);  // records mark 3 after its main kernel(s)
     if (e != hipSuccess) return GC_ERR_HIP;
   } else {
     prof_mark(call, 3, a.stream);
@@ -337,14 +369,9 @@ size_t gc_workspace_bytes(int B, int P, int d, int dt) {
   return make_loss_plan(B, P, d, (gc_dtype)dt, false).total;
 }
 
-int gc_loss_and_rep_grad_ex(int dt_int, const void* q, const void* p, const int32_t* pos_idx, int B, int P, int d,
-                            float scale, float temp, unsigned flags, float* loss, float* dq, float* dp, float* lse,
-                            int32_t* argmax, void* workspace, size_t workspace_bytes, void* stream) {
-  int rc = check_loss_args(dt_int, q, p, pos_idx, B, P, d, scale, temp, flags);
-  if (rc != GC_OK) return rc;
-  const gc_dtype dt = (gc_dtype)dt_int;
-  const LossPlan pl = make_loss_plan(B, P, d, dt, false);
-  if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < pl.total) return GC_ERR_WORKSPACE;
+static int loss_with_plan(const LossPlan& pl, gc_dtype dt, const void* q, const void* p, const int32_t* pos_idx, int B, int P, int d,
+                          float scale, float temp, unsigned flags, float* loss, float* dq, float* dp, float* lse,
+                          int32_t* argmax, void* workspace, void* stream) {
   LossArgs a{};
   a.dt = dt; a.q = q; a.p = p; a.pos_idx = pos_idx; a.B = B; a.P = P; a.d = d;
   a.alpha = scale / temp; a.flags = flags;
@@ -353,18 +380,35 @@ int gc_loss_and_rep_grad_ex(int dt_int, const void* q, const void* p, const int3
   return run_loss(a, pl);
 }
 
+int gc_loss_and_rep_grad_ex(int dt_int, const void* q, const void* p, const int32_t* pos_idx, int B, int P, int d,
+                            float scale, float temp, unsigned flags, float* loss, float* dq, float* dp, float* lse,
+                            int32_t* argmax, void* workspace, size_t workspace_bytes, void* stream) {
+  int rc = check_loss_args(dt_int, q, p, pos_idx, B, P, d, scale, temp, flags);
+  if (rc != GC_OK) return rc;
+  const gc_dtype dt = (gc_dtype)dt_int;
+  const LossPlan pl = make_loss_plan(B, P, d, dt, false);
+  if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < pl.total) return GC_ERR_WORKSPACE;
+  return loss_with_plan(pl, dt, q, p, pos_idx, B, P, d, scale, temp, flags, loss, dq, dp, lse, argmax, workspace, stream);
+}
+
 static int simple_loss(gc_dtype dt, const void* q, const void* p, const int32_t* pos_idx, int B, int P, int d,
                        float scale, float temp, float* loss, float* dq, float* dp, void* stream) {
   int rc = check_loss_args(dt, q, p, pos_idx, B, P, d, scale, temp, 0);
   if (rc != GC_OK) return rc;
   if (!loss || !dq || !dp) return GC_ERR_NULL;
-  const size_t need = make_loss_plan(B, P, d, dt, false).total;
+  LossPlan pl = make_loss_plan(B, P, d, dt, false);
   void* ws = nullptr;
-  rc = own_workspace(need, (hipStream_t)stream, &ws);
+  size_t have = 0;
+  rc = own_workspace(pl.total, (hipStream_t)stream, &ws, &have);
+  if (rc == GC_ERR_UNSUPPORTED) {   // a capture cannot grow the buffer: what fits the one there is?
+    pl = make_loss_plan(B, P, d, dt, false, have);
+    if (!ws || pl.total > have) return rc;
+    rc = GC_OK;
+  }
   if (rc != GC_OK) return rc;
   rc = own_workspace_enter((hipStream_t)stream);
   if (rc != GC_OK) return rc;
-  rc = gc_loss_and_rep_grad_ex(dt, q, p, pos_idx, B, P, d, scale, temp, 0, loss, dq, dp, nullptr, nullptr, ws, need, stream);
+  rc = loss_with_plan(pl, dt, q, p, pos_idx, B, P, d, scale, temp, 0, loss, dq, dp, nullptr, nullptr, ws, stream);
   const int rc2 = own_workspace_leave((hipStream_t)stream);   // also after a failed launch: some kernels may be queued
   return rc != GC_OK ? rc : rc2;
 }
@@ -379,15 +423,14 @@ int gc_loss_and_rep_grad_bf16_static(const void* q, const void* p, const int32_t
   int rc = check_loss_args(GC_BF16, q, p, pos_idx, B, P, d, scale, temp, 0);
   if (rc != GC_OK) return rc;
   if (!loss || !dq || !dp) return GC_ERR_NULL;
-  const size_t need = make_loss_plan(B, P, d, GC_BF16, false).total;
-  if (need > (size_t)GC_STATIC_SCRATCH_BYTES) return GC_ERR_TOO_LARGE;
+  const LossPlan pl = make_loss_plan(B, P, d, GC_BF16, false, (size_t)GC_STATIC_SCRATCH_BYTES);
+  if (pl.total > (size_t)GC_STATIC_SCRATCH_BYTES) return GC_ERR_TOO_LARGE;
   void* ws = nullptr;
   rc = static_scratch(&ws);
   if (rc != GC_OK) return rc;
   // every word of the workspace that a kernel of this path reads has been written by an earlier kernel of the same
   // call (statistics, partial sums, the error word): nothing has to start at zero
-  return gc_loss_and_rep_grad_ex(GC_BF16, q, p, pos_idx, B, P, d, scale, temp, 0, loss, dq, dp, nullptr, nullptr, ws,
-                                 need, stream);
+  return loss_with_plan(pl, GC_BF16, q, p, pos_idx, B, P, d, scale, temp, 0, loss, dq, dp, nullptr, nullptr, ws, stream);
 }
 
 int gc_loss_and_rep_grad_f32(const float* q, const float* p, const int32_t* pos_idx, int B, int P, int d, float scale,
@@ -483,13 +526,13 @@ int gc_ntxent_loss_and_grad_bf16(const void* z, int n_views, int d, float temp, 
 
 // Workspace of the symmetric loss: [loss workspace, direction 1][direction 2][r^-1][two losses][4 gradient buffers].
 // With the MFMA kernels one gradient pass serves both directions: the second workspace then holds statistics only
-// and there are no gradient buffers.
+// and there are no gradient buffers.  The general widths share the packed inputs and partials between the directions.
 struct SymPlan { LossPlan pl; size_t off2, off_rinv, off_l, off_g, total; };
 static SymPlan make_sym_plan(int n, int d) {
   SymPlan sp{};
   sp.pl = make_loss_plan(n, n, d, GC_BF16, false);
   size_t off = align_up(sp.pl.total, 256);
-  sp.off2 = off; off = align_up(off + (sp.pl.use_mfma ? sp.pl.off_dq_part : sp.pl.total), 256);
+  sp.off2 = off; off = align_up(off + (sp.pl.route == ROUTE_GENERAL ? sp.pl.total : sp.pl.off_dq_part), 256);
   sp.off_rinv = off; off = align_up(off + (size_t)n * 4, 256);
   sp.off_l = off; off += 256;
   sp.off_g = off; off += sp.pl.use_mfma ? 0 : 4 * align_up((size_t)n * d * 4, 256);
@@ -549,6 +592,7 @@ int gc_bidirectional_loss_and_rep_grad_bf16(const void* q, const void* p, const 
     rc = run_loss(a, sp.pl);
     if (rc != GC_OK) return rc;
     a.q = p; a.p = q; a.pos_idx = rinv; a.loss = l + 1; a.dq = g[2]; a.dp = g[3]; a.ws = ws + sp.off2;
+    a.ws2 = ws;   // its statistics are its own (the row losses of both are summed at the end), the rest is free again
     a2 = a;
     rc = run_loss(a, sp.pl);
     if (rc != GC_OK) return rc;

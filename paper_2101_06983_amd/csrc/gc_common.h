@@ -42,8 +42,14 @@ __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_lo
 // Workspace plan of gc_loss_and_rep_grad_ex: one host function decides the
 // splits and the byte offsets, so gc_workspace_bytes and the launch agree.
 // ---------------------------------------------------------------------------
+enum LossRoute {
+  ROUTE_MFMA = 0,     // loss_mfma.hip: bf16, d a multiple of 128 up to 768
+  ROUTE_PLANES = 1,   // loss_planes.hip: fp32 storage, and bf16 of any other width
+  ROUTE_GENERAL = 2   // loss_generic.hip: the same calls where the workspace is limited and the planes do not fit
+};
 struct LossPlan {
-  int use_mfma;          // 1: bf16 MFMA kernels, 0: general fp32-FMA kernels
+  int route;
+  int use_mfma;          // route == ROUTE_MFMA
   int one_walk;          // NT-Xent on the MFMA kernels: dz from a single walk (no dP role, no dP partials)
   int stat_splits;       // column (target) ranges of the statistics pass
   int stat_cols_per_split;
@@ -53,11 +59,20 @@ struct LossPlan {
   // fused mode (MFMA kernels, d >= 256, dQ wanted): no statistics pass; an online-statistics dQ walk, a kernel that
   // merges its splits into lse2 and dQ, then the dP walk.  Each walk fills the GPU alone, so they have splits of their own
   int fused, fused_auto, fz_nsq, fz_nsp, fz_q_stream_len, fz_p_stream_len;   // can run / is chosen without a flag
+  // ROUTE_PLANES: bf16 planes per stored value; fragments along d (k-steps of 16, column tiles of 32); rows padded to 128;
+  // target tiles per wave of the statistics pass; 32-row blocks a workgroup of the gradient pass owns; column slices;
+  // floats between the partials of an output
+  int np, px_KS, px_CT, px_rows_q, px_rows_p, px_tiles_per_wave, px_no, px_col_slices, px_ct_per_slice;
+  size_t px_stride_q, px_stride_p, off_qk, off_qt, off_pk, off_pt;
+  // (everything below off_dq_part is what a call that only forms statistics touches)
   size_t off_err, off_part_m, off_part_l, off_part_idx, off_pos, off_lse2, off_pos_pad, off_rowloss, off_dq_part,
       off_dp_part, off_pos_idx, off_on_ref, off_inv, total;
 };
 
-LossPlan make_loss_plan(int B, int P, int d, gc_dtype dt, bool ntxent);
+// limit: bytes of workspace there are.  The calls of ROUTE_PLANES take fewer splits, and then ROUTE_GENERAL, to stay below
+// it (the sequence of the other route does not depend on it: the caller compares `total`).
+LossPlan make_loss_plan(int B, int P, int d, gc_dtype dt, bool ntxent, size_t limit = (size_t)-1);
+void plan_planes(LossPlan& pl, int B, int P, int d, gc_dtype dt, int max_splits);
 
 struct LossArgs {
   gc_dtype dt;
@@ -86,6 +101,7 @@ struct LossArgs {
   bool loss_with_partials;
   bool defer_loss_sum;   // the caller sums the row losses itself (the symmetric loss: both directions in one launch)
   char* ws;
+  char* ws2;             // base of the offsets from off_dq_part on (ws; the symmetric loss shares that part between its directions)
   hipStream_t stream;
 };
 
@@ -111,6 +127,8 @@ struct PosFix {
 // kernel-launching halves (one per .hip file)
 hipError_t launch_stats_generic(const LossArgs& a, const LossPlan& pl);
 hipError_t launch_grad_generic(const LossArgs& a, const LossPlan& pl);
+hipError_t launch_stats_planes(const LossArgs& a, const LossPlan& pl);   // packs the inputs first
+hipError_t launch_grad_planes(const LossArgs& a, const LossPlan& pl);
 hipError_t launch_stats_mfma(const LossArgs& a, const LossPlan& pl);
 hipError_t launch_grad_mfma(const LossArgs& a, const LossPlan& pl);
 hipError_t launch_grad_online(const LossArgs& a, const LossPlan& pl);    // fused mode: dQ walk with online statistics

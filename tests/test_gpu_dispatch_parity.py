@@ -24,3 +24,126 @@ def test_targets_shared_by_several_anchors(B, P, d, named):
     check_loss("shared loss", out["loss"].item(), want["loss"], TOL_BF16)
     for k in ("dq", "dp"):
         check("shared %dx%dx%d %s" % (B, P, d, k), relerr(to_np(out[k]), want[k]), TOL_BF16)
+
+
+def run_ex(q, p, r, scale, temp, flags=0):
+    out = gc.gc_loss_and_rep_grad_ex(q, p, r, scale, temp, flags)
+    torch.cuda.synchronize()
+    assert gc.gc_check_async_error(out["workspace"]) == gc.GC_OK
+    return out
+
+
+# fp32 arithmetic whatever the storage: the fp32 tolerance also for bf16 inputs
+def check_fp32_grade(label, out, want, q, p, alpha):
+    check_loss(label + " loss", out["loss"].item(), want["loss"], TOL_F32, 1e-30)
+    for k in ("dq", "dp", "lse"):
+        check(label + " " + k, relerr(to_np(out[k]), want[k]), TOL_F32)
+    assert check_argmax(to_np(out["argmax"]), want, synth.widen(q), synth.widen(p), alpha, 1e-5) <= max(1, len(want["argmax"]) // 500)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("B,P,d", [(31, 33, 65), (129, 127, 63), (128, 256, 64), (5, 700, 130), (700, 5, 97), (300, 260, 1025),
+                                   (70, 90, 1023), (40, 257, 2112), (257, 129, 776), (33, 32, 520), (1, 600, 264), (520, 1, 1024)])
+def test_any_width_in_fp32_grade(B, P, d, dtype):
+    """Edges of the 32-row blocks, the 128-row steps, the 64-column padding, the column slices of 1024; widths whose
+    rows are and are not whole 16-byte vectors; streams of one row."""
+    q, p, _ = synth.dpr_batch(B, P, d, dtype, seed=4200 + B)
+    r = torch.from_numpy(np.random.default_rng(B + P).integers(0, P, size=B).astype(np.int32))
+    want = oracle_loss(q, p, r, 1.0, 0.5)
+    check_fp32_grade("%dx%dx%d %s" % (B, P, d, dtype), run_ex(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.5), want, q, p, 2.0)
+
+
+@pytest.mark.parametrize("B,P,d,dtype", [(4096, 4100, 64, torch.float32), (4100, 4096, 72, torch.bfloat16), (4096, 4096, 200, torch.float32)])
+def test_any_width_large_batch(B, P, d, dtype):
+    # (64 owner rows per workgroup from here on)
+    q, p, r = synth.dpr_batch(B, P, d, dtype, seed=4300 + d, positive_mix=0.3)
+    want = oracle_loss(q, p, r, 1.0, 0.25)
+    check_fp32_grade("%dx%dx%d %s" % (B, P, d, dtype), run_ex(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.25), want, q, p, 4.0)
+
+
+@pytest.mark.parametrize("dtype,shift", [(torch.float32, 1), (torch.bfloat16, 1), (torch.float32, 3), (torch.bfloat16, 5)])
+def test_inputs_and_outputs_aligned_to_their_elements_only(dtype, shift):
+    B, P, d = 70, 130, 136
+    q, p, r = synth.dpr_batch(B, P, d, dtype, seed=4400)
+    want = oracle_loss(q, p, r)
+
+    def off(t):
+        buf = torch.empty(t.numel() + shift, dtype=t.dtype, device=DEV)
+        buf[shift:] = t.reshape(-1).to(DEV)
+        return buf[shift:].view(t.shape)
+
+    out = dict(dq=off(torch.zeros(B, d)), dp=off(torch.zeros(P, d)))
+    got = gc.gc_loss_and_rep_grad_ex(off(q), off(p), r.to(DEV), out=out)
+    torch.cuda.synchronize()
+    check_fp32_grade("shifted by %d %s" % (shift, dtype), got, want, q, p, 1.0)
+
+
+@pytest.mark.parametrize("n,d", [(66, 96), (300, 200)])
+def test_masked_ntxent_and_symmetric_at_any_width(n, d):
+    q, p, _ = synth.dpr_batch(n, n, d, seed=4500 + n, positive_mix=0.2)
+    r = torch.arange(n, dtype=torch.int32) ^ 1
+    want = oracle_loss(q, p, r, 1.0, 0.5, mask_self=True)
+    check_fp32_grade("mask n=%d d=%d" % (n, d), run_ex(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.5, gc.GC_MASK_SELF), want, q, p, 2.0)
+    z = synth.ntxent_views(n, d, seed=4510)
+    want = oracle_loss(z, z, r, 1.0, 0.2, mask_self=True)
+    loss, dz = gc.gc_ntxent_loss_and_grad_bf16(z.to(DEV), 0.2)
+    torch.cuda.synchronize()
+    check_loss("ntxent n=%d d=%d" % (n, d), loss.item(), want["loss"], TOL_F32)
+    check("ntxent n=%d d=%d dz" % (n, d), relerr(to_np(dz), want["dq"] + want["dp"]), TOL_F32)
+    perm = torch.from_numpy(np.random.default_rng(n).permutation(n).astype(np.int32))
+    from oracle import gc_oracle as O
+    want = O.bidirectional(synth.widen(q), synth.widen(p), perm.numpy(), 1.0, 0.5)
+    out = gc.gc_bidirectional_loss_and_rep_grad_bf16(q.to(DEV), p.to(DEV), perm.to(DEV), 1.0, 0.5)
+    torch.cuda.synchronize()
+    check_loss("symmetric n=%d d=%d" % (n, d), out["loss"].item(), want["loss"], TOL_F32)
+    for k in ("dq", "dp"):
+        check("symmetric n=%d d=%d %s" % (n, d, k), relerr(to_np(out[k]), want[k]), TOL_F32)
+
+
+@pytest.mark.parametrize("B,P,d", [(300, 500, 200), (512, 1024, 1000), (2000, 3000, 520)])
+def test_static_scratch_takes_every_width_it_took(B, P, d):
+    """Where the packed inputs do not fit the fixed array beside the partials, fewer splits or the general kernels serve
+    the call; the workspace-less entry point takes the same shapes with the room it wants."""
+    q, p, r = synth.dpr_batch(B, P, d, seed=4600 + d, positive_mix=0.3)
+    want = oracle_loss(q, p, r, 1.0, 0.5)
+    for call in (gc.gc_loss_and_rep_grad_bf16_static, gc.gc_loss_and_rep_grad_bf16):
+        loss, dq, dp = call(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.5)
+        torch.cuda.synchronize()
+        assert gc.gc_check_async_error() == gc.GC_OK
+        check_loss("static %dx%dx%d" % (B, P, d), loss.item(), want["loss"], TOL_F32)
+        check("static %dx%dx%d dq" % (B, P, d), relerr(to_np(dq), want["dq"]), TOL_F32)
+        check("static %dx%dx%d dp" % (B, P, d), relerr(to_np(dp), want["dp"]), TOL_F32)
+
+
+CAPTURE = """
+import sys, torch
+sys.path.insert(0, %r)
+from paper_2101_06983_amd import binding as gc
+g = torch.Generator(device="cuda").manual_seed(1)
+mk = lambda n, d: torch.randn(n, d, generator=g, device="cuda") * d ** -0.5
+gc.gc_loss_and_rep_grad_f32(mk(8, 64), mk(16, 64), torch.arange(8, device="cuda", dtype=torch.int32))   # the library's buffer: 1 MiB
+q, p, r = mk(300, 200), mk(500, 200), torch.arange(300, device="cuda", dtype=torch.int32)
+torch.cuda.synchronize()
+graph = torch.cuda.CUDAGraph()
+with torch.cuda.graph(graph):
+    got = gc.gc_loss_and_rep_grad_f32(q, p, r)
+for k in range(3):
+    q.copy_(mk(300, 200))
+    graph.replay()
+    torch.cuda.synchronize()
+    want = gc.gc_loss_and_rep_grad_ex(q, p, r, want=("loss", "dq", "dp"))
+    torch.cuda.synchronize()
+    for a, b in zip(got, (want["loss"], want["dq"], want["dp"])):
+        assert (a - b).abs().max().item() <= 1e-5 * b.abs().max().item(), k
+print("replays agree")
+"""
+
+
+def test_capture_with_the_library_buffer_too_small_for_the_packed_inputs():
+    """A capture cannot grow the library's buffer: a width that needed little workspace is still served."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", CAPTURE % root], capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "replays agree" in r.stdout, r.stdout + r.stderr
