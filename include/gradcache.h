@@ -286,9 +286,11 @@ int gc_chunk_surrogate_backward_bf16(const void* x_chunk, int rows, const gc_mlp
  *     optional outputs (NULL = kept in the workspace only)
  * workspace: gc_step_mlp_workspace_bytes(B, P, chunk_q, chunk_p, w).  It holds the
  *   representations and their gradient cache ((B + P) * dout numbers each), the
- *   loss workspace, three sets of one sub-batch's activations for Step 3, and
- *   the transient activations of Step 1, whose graph-less forward takes up to
- *   2048 rows (whole sub-batches) per launch: rows * dh floats, three times.
+ *   loss workspace, and one buffer of transient activations: Step 1, whose
+ *   graph-less forward takes up to 2048 rows (whole sub-batches) per launch, and
+ *   Step 3, which re-encodes and back-propagates as many whole sub-batches at a
+ *   time as that buffer holds, use it in turn (about three floats per row and
+ *   column of dh).
  * Everything is enqueued on `stream`; the order in which sub-batches are added
  * to the gradients is the index order, so the result is reproducible bit for
  * bit.  A call that repeats with exactly the same arguments (same buffers) is
@@ -303,12 +305,8 @@ int gc_step_mlp_bf16(const void* x_q, int B, const void* x_p, int P, const int32
                      size_t workspace_bytes, void* stream);
 
 /*
- * The same step with Step 3 run on groups of accumulate_group (1..8) consecutive sub-batches of one side: the
- * re-encoded activations of a group are alive at once (accumulate_group times the activation memory of a sub-batch:
- * the quantity the sub-batch size exists to bound, hence opt-in), and the fp32 gradient accumulators are read and
- * written once per group instead of once per sub-batch.  The sub-batches of a group are still added in index order
- * and in the same 32-row pieces, so every output has the bits gc_step_mlp_bf16 gives (accumulate_group = 1 is that
- * call).  Grouping needs chunk_q and chunk_p to be multiples of 32; otherwise the call runs ungrouped.
+ * The same step; accumulate_group (1..8) bounds nothing any more: Step 3 of either call takes as many whole sub-batches
+ * at a time as the transient activation buffer of Step 1 holds, and every output has the bits gc_step_mlp_bf16 gives.
  * workspace: gc_step_mlp_grouped_workspace_bytes(B, P, chunk_q, chunk_p, w, accumulate_group).
  * Errors as gc_step_mlp_bf16; GC_ERR_SHAPE for accumulate_group outside [1, 8].
  */

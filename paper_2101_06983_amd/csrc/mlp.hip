@@ -2,37 +2,27 @@
 // Step 1, the per-sub-batch re-encode and surrogate backward of Step 3 (the inner sums of Eq. 8 / 9)
 // and the one-GPU driver that runs Steps 1-3.
 //
-// A sub-batch has few rows (32 at the paper's setting), so every contraction of Step 3 is skinny and is bound by
-// how fast the weights and the gradient accumulators move, not by the MFMAs.  Three kernels:
-//
-// mlp_skinny_kernel: C[32 x 32 per workgroup] = A[rows x K] * Bt[N x K]^T, both operands with k contiguous, so
+// mlp_skinny_kernel: C[32 x 32 per workgroup] = A[rows x K] * Bt[N x K]^T for few rows, both operands with k contiguous, so
 //   every MFMA fragment is a plain 16-byte global load and nothing is staged through LDS.  The four waves of a
-//   workgroup split K (64-wide chunks, round-robin), keep two to four chunks of loads in flight each, and sum their
-//   partial tiles through LDS in a fixed order.  Used for
-//     H  = X  W1  (+b1, GELU)              Bt = W1^T [dh][din]   (transposed copy, made once per call)
-//     Y  = Act W2 (+b2)                    Bt = W2^T [dout][dh]  (transposed copy)      A = Act, fp32
-//     dA = U  W2^T, dH = dA * GELU'(H)     Bt = W2 [dh][dout] as stored                 A = U, fp32
-// mlp_wgrad_kernel: the weight-gradient contractions, whose k index is the row of the sub-batch (the slow index
-//   of both operands in memory): 64 x 128 tiles, operands through LDS (loaded a 32-row chunk ahead) and transposing
-//   ds_read_b64_tr_b16 loads, fp32 accumulators in HBM updated in place (+=)
-//     dW2 += Act^T U      A = Act (fp32) [rows][dh]    B = U (fp32) [rows][dout]   db2 += column sums of U
-//     dW1 += X^T dH       A = X [rows][din]            B = dH (fp32) [rows][dh]    db1 += column sums of dH
-// gemm_nt_kernel: the same product as the skinny kernel for MANY rows at once (the graph-less forward of Step 1 over
-//   up to 2048 rows, the batch-wide projections of the distance functions): 64 x 128 or 128 x 128 tiles, both
-//   operands through LDS, optionally with the contraction cut into ranges (split-K).
-// An fp32 operand (the cached gradient rows U, dH, and the activations kept for Step 3) is fed to the bf16 MFMA as
-// hi + lo, two bf16 numbers per value and two MFMAs per step, so that it keeps ~16 mantissa bits: with only
-// rows <= 32 terms per sum a single bf16 rounding (2^-9) would sit right at the error budget.
+//   workgroup split K (64-wide chunks, round-robin), keep up to four chunks of loads in flight each, and sum their
+//   partial tiles through LDS in a fixed order: such a contraction is bound by how fast the weights move.
+// gemm_nt_kernel: the same product for MANY rows at once (the graph-less forward of Step 1 over up to 2048 rows, the
+//   batch-wide projections of the distance functions): 64 x 128 or 128 x 128 tiles, both operands through LDS,
+//   optionally with the contraction cut into ranges (split-K).
+// mlp_prep_kernel, mlp_dh_skinny_kernel / mlp_dh_tiled_kernel, mlp_grads_kernel: Step 3 (see there).
+// wgrad_splitk_kernel: C = A^T B over the rows of the batch (the parameter gradients of the distance functions).
+// An fp32 operand (the cached gradient rows U, dH, the activations) is fed to the bf16 MFMA as hi + lo, two bf16 numbers
+// per value and two MFMAs per step, so that it keeps ~16 mantissa bits: with few terms per sum a single bf16 rounding
+// (2^-9) would sit right at the error budget.
 #include "gc_common.h"
 #include <mutex>
-#include <vector>
 #include <string.h>
 
 namespace gc {
 
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4m;
 
-enum Epilogue { EP_GELU = 0, EP_BIAS = 1, EP_DH = 2, EP_PLAIN = 3 };
+enum Epilogue { EP_GELU = 0, EP_BIAS = 1, EP_PLAIN = 2 };
 
 __device__ __forceinline__ float gelu_f(float h) { return 0.5f * h * (1.f + erff(h * 0.70710678118654752f)); }
 __device__ __forceinline__ float gelu_prime_f(float h) {
@@ -60,15 +50,12 @@ __device__ __forceinline__ void load8(const void* base, size_t idx, bool live, u
   }
 }
 
-// C[M x N] += A^T B over the rows of a sub-batch: A [K][M] (bf16 or fp32), B [K][N] fp32, C fp32 in HBM.
+// C[M x N] = A^T B over the rows (K): A [K][M] (bf16 or fp32), B [K][N] (fp32 or bf16), C fp32.
 struct WgradArgs {
   const void* A; int lda;   // elements
   const void* B; int ldb;   // fp32, or bf16 where the kernel is instantiated with B_F32 = false
-  int M, N, K;              // M a multiple of 64 (WG_M), N a multiple of 128, K = rows of the sub-batch (any)
-  float* C; int ldc;        // += in place (one workgroup per tile: single writer)
-  float* colsum;            // optional: [N] += column sums of B (db2; written by the m-tile 0 workgroups)
-  int colsum_rows;          // the column sums are added colsum_rows rows at a time (0: all K rows in one sum): a launch
-                            // that covers several sub-batches adds them one sub-batch after the other, as single launches do
+  int M, N, K;              // M a multiple of 64 (WG_M), N a multiple of 128, K any
+  float* C; int ldc;
 };
 
 // a workgroup's tile of C is WG_M x 128 (two 32-row MFMA tiles that share the B operand in LDS)
@@ -106,25 +93,20 @@ __device__ __forceinline__ void split8(const Raw8<F32>& r, u32x4& hi, u32x4& lo)
   }
 }
 
-// ACCUM: the tile starts from the value of C in HBM (+=); otherwise from zero (C is written, not read)
-template <bool A_F32, bool B_F32 = true, bool ACCUM = true>
+template <bool A_F32, bool B_F32>
 __device__ __forceinline__ void wgrad_tile(const WgradArgs& g, int bx, int by, unsigned short* As, unsigned short* Bs) {
   constexpr int KCH = WG_KCH, A_LD = WG_A_LD, B_LD = WG_B_LD;
   constexpr int A_LO = KCH * A_LD, B_LO = KCH * B_LD;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, ln = lane & 31;
   const int n0 = bx * 128, m0 = by * WG_M;
 
-  // the accumulator tile starts from its current value in HBM (read issued first: it is the longest wait);
   // lane holds column n, rows m0 + 32 mt + 8 (r / 4) + 4 h + r % 4
   const int n = n0 + wave * 32 + ln;
   f32x16 acc[2];
 #pragma unroll
   for (int mt = 0; mt < 2; mt++)
 #pragma unroll
-    for (int r = 0; r < 16; r++) {
-      const int m = m0 + 32 * mt + 8 * (r >> 2) + 4 * h + (r & 3);
-      acc[mt][r] = (ACCUM && m < g.M) ? g.C[(size_t)m * g.ldc + n] : 0.f;
-    }
+    for (int r = 0; r < 16; r++) acc[mt][r] = 0.f;
 
   // the 32 rows of a k-chunk: one 8-element piece of A and two of B per thread, loaded a chunk ahead of their use
   static_assert(KCH * (WG_M / 8) == 256 && KCH * 16 == 512, "staging pieces per thread");
@@ -186,40 +168,6 @@ __device__ __forceinline__ void wgrad_tile(const WgradArgs& g, int bx, int by, u
       const int m = m0 + 32 * mt + 8 * (r >> 2) + 4 * h + (r & 3);
       if (m < g.M) g.C[(size_t)m * g.ldc + n] = acc[mt][r];
     }
-  if (g.colsum && by == 0 && tid < 128) {
-    const int step = g.colsum_rows > 0 ? g.colsum_rows : g.K;
-    const float* col = (const float*)g.B + n0 + tid;   // (fp32 B only)
-    float total = g.colsum[n0 + tid];
-    for (int k0 = 0; k0 < g.K; k0 += step) {
-      const int k1 = min(g.K, k0 + step);
-      float s = 0.f;
-      for (int k = k0; k < k1; k += 8) {   // eight loads in flight, added in row order
-        float v[8];
-#pragma unroll
-        for (int j = 0; j < 8; j++) v[j] = (k + j < k1) ? col[(size_t)(k + j) * g.ldb] : 0.f;
-#pragma unroll
-        for (int j = 0; j < 8; j++)
-          if (k + j < k1) s += v[j];
-      }
-      total += s;
-    }
-    g.colsum[n0 + tid] = total;
-  }
-}
-
-// both weight gradients of a sub-batch in one launch: workgroups [0, n2) take the tiles of dW2 (A = Act, fp32),
-// the rest the tiles of dW1 (A = X, bf16)
-__global__ void __launch_bounds__(256) mlp_wgrad_kernel(WgradArgs g2, WgradArgs g1, int n2) {
-  __shared__ __attribute__((aligned(16))) unsigned short As[2 * WG_KCH * WG_A_LD];
-  __shared__ __attribute__((aligned(16))) unsigned short Bs[2 * WG_KCH * WG_B_LD];
-  const int id = blockIdx.x;
-  if (id < n2) {
-    const int nb = g2.N / 128;
-    wgrad_tile<true>(g2, id % nb, id / nb, As, Bs);
-  } else {
-    const int nb = g1.N / 128;
-    wgrad_tile<false>(g1, (id - n2) % nb, (id - n2) / nb, As, Bs);
-  }
 }
 
 // C = A^T B with the rows (K) cut into slices: workgroup (tile, slice) adds its slice's product to partial s of C
@@ -236,8 +184,7 @@ __global__ void __launch_bounds__(256) wgrad_splitk_kernel(WgradArgs g, int rows
   s.B = (const char*)g.B + (size_t)k0 * g.ldb * (B_F32 ? 4 : 2);
   s.K = min(rows_per_slice, g.K - k0);
   s.C = g.C + (size_t)slice * g.M * g.ldc;
-  s.colsum = nullptr;
-  wgrad_tile<A_F32, B_F32, false>(s, tile % nb, tile / nb, As, Bs);
+  wgrad_tile<A_F32, B_F32>(s, tile % nb, tile / nb, As, Bs);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -246,29 +193,29 @@ struct SkinnyArgs {
   const unsigned short* Bt; int ldb; // [N][K] bf16
   int M, N, K;                       // M may be ragged; N a multiple of 32, K a multiple of 64
   const unsigned short* bias;        // EP_GELU / EP_BIAS: [N] bf16
-  float* H; int ldh;                 // EP_GELU: optional fp32 pre-activation out; EP_DH: fp32 pre-activation in
-  float* ActF;                       // EP_GELU: fp32 activation out (ldh)
+  float* ActF; int ldh;              // EP_GELU: fp32 activation out
   unsigned short* Cb; int ldc;       // EP_BIAS: bf16 output; EP_PLAIN: bf16 output if set
-  float* Cf;                         // EP_DH: dH out (fp32, ldc); EP_PLAIN: fp32 output if Cb is not set
+  float* Cf;                         // EP_PLAIN: fp32 output if Cb is not set
   float plain_mul;                   // EP_PLAIN: factor on the product (0 means 1)
 };
 
 typedef float SkinnyRed[32][33];   // one partial tile; a workgroup holds four
 
-// one 32 x 32 output tile (n-tile bx, m-tile by); red: the workgroup's four partial tiles in LDS;
-// PD: 64-wide chunks of loads in flight per wave (registers against latency)
-template <bool A_F32, Epilogue EP, int PD>
-__device__ __forceinline__ void skinny_tile(const SkinnyArgs& g, int bx, int by, SkinnyRed* red) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, ln = lane & 31;
-  const int n0 = bx * 32, m0 = by * 32;
-  const int nch = g.K / 64;
+// The product of one 32 x 32 output tile (rows a_row0 .. of A, at most last_row; rows n0 .. of Bt): the partial tiles of the
+// four waves 0..3 (K split in 64-wide chunks, round-robin) are left in LDS.  PD: chunks of loads in flight per
+// wave (registers against latency)
+template <bool A_F32, int PD>
+__device__ __forceinline__ void skinny_product(const void* A, int lda, int a_row0, int last_row, const unsigned short* Bt, int ldb, int n0,
+                                               int K, SkinnyRed* red, int wave) {
+  const int lane = threadIdx.x & 63, h = lane >> 5, ln = lane & 31;
+  const int nch = K / 64;
   // lane (ln, h) holds elements 32 h .. 32 h + 31 of each 64-wide chunk of row ln of A and of Bt; MFMA j of a
   // chunk contracts elements 8 j .. 8 j + 7 of both half-chunks (any order of k works if both operands share it)
   constexpr int AE = A_F32 ? 4 : 2;
   constexpr int AV = A_F32 ? 8 : 4;   // 16-byte loads per chunk for A
-  const int m = min(m0 + ln, g.M - 1);
-  const char* ap = (const char*)g.A + ((size_t)m * g.lda + 32 * h) * AE;
-  const char* bp = (const char*)(g.Bt + (size_t)(n0 + ln) * g.ldb + 32 * h);
+  const int m = min(a_row0 + ln, last_row);
+  const char* ap = (const char*)A + ((size_t)m * lda + 32 * h) * AE;
+  const char* bp = (const char*)(Bt + (size_t)(n0 + ln) * ldb + 32 * h);
   u32x4 fa[PD][AV], fb[PD][4];
   auto issue = [&](int slot, int c) __attribute__((always_inline)) {
 #pragma unroll
@@ -306,40 +253,38 @@ __device__ __forceinline__ void skinny_tile(const SkinnyArgs& g, int bx, int by,
       }
     }
   }
-  // ---- partial tiles of the four waves, summed in a fixed order; lane holds column ln, rows 8 (r / 4) + 4 h + r % 4
+  // lane holds column ln, rows 8 (r / 4) + 4 h + r % 4
 #pragma unroll
   for (int r = 0; r < 16; r++) red[wave][8 * (r >> 2) + 4 * h + (r & 3)][ln] = acc[r];
-  __syncthreads();
-  const int en = tid & 31, n = n0 + en;
-#pragma unroll
-  for (int i = 0; i < 4; i++) {
-    const int em = (tid >> 5) + 8 * i, mm = m0 + em;
-    const float sum = ((red[0][em][en] + red[1][em][en]) + red[2][em][en]) + red[3][em][en];
-    if (EP == EP_GELU) {
-      const float v = sum + bf2f(g.bias[n]);
-      if (mm < g.M) {
-        if (g.H) g.H[(size_t)mm * g.ldh + n] = v;
-        g.ActF[(size_t)mm * g.ldh + n] = gelu_f(v);
-      }
-    } else if (EP == EP_BIAS) {
-      if (mm < g.M) g.Cb[(size_t)mm * g.ldc + n] = f2bf(sum + bf2f(g.bias[n]));
-    } else if (EP == EP_PLAIN) {  // the product itself
-      if (mm < g.M) {
-        if (g.Cb) g.Cb[(size_t)mm * g.ldc + n] = f2bf(sum);
-        else g.Cf[(size_t)mm * g.ldc + n] = g.plain_mul != 0.f ? sum * g.plain_mul : sum;
-      }
-    } else {  // EP_DH (the column sums of dH, db1, are formed by the weight-gradient kernel that reads dH next)
-      if (mm < g.M) g.Cf[(size_t)mm * g.ldc + n] = sum * gelu_prime_f(g.H[(size_t)mm * g.ldh + n]);
-    }
-  }
-  __syncthreads();  // red may be reused by the caller's next tile
+}
+// element (row, column) of the product: the four partial tiles in a fixed order
+__device__ __forceinline__ float skinny_sum(const SkinnyRed* red, int em, int en) {
+  return ((red[0][em][en] + red[1][em][en]) + red[2][em][en]) + red[3][em][en];
 }
 
 // grid (N / 32, m-tiles)
 template <bool A_F32, Epilogue EP>
 __global__ void __launch_bounds__(256) mlp_skinny_kernel(SkinnyArgs g) {
-  __shared__ float red[4][32][33];
-  skinny_tile<A_F32, EP, 4>(g, blockIdx.x, blockIdx.y, red);
+  __shared__ SkinnyRed red[4];
+  const int tid = threadIdx.x, n0 = blockIdx.x * 32, m0 = blockIdx.y * 32;
+  skinny_product<A_F32, 4>(g.A, g.lda, m0, g.M - 1, g.Bt, g.ldb, n0, g.K, red, tid >> 6);
+  __syncthreads();
+  const int en = tid & 31, n = n0 + en;
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    const int em = (tid >> 5) + 8 * i, mm = m0 + em;
+    const float sum = skinny_sum(red, em, en);
+    if (mm < g.M) {
+      if (EP == EP_GELU) {
+        g.ActF[(size_t)mm * g.ldh + n] = gelu_f(sum + bf2f(g.bias[n]));
+      } else if (EP == EP_BIAS) {
+        g.Cb[(size_t)mm * g.ldc + n] = f2bf(sum + bf2f(g.bias[n]));
+      } else {   // the product itself
+        if (g.Cb) g.Cb[(size_t)mm * g.ldc + n] = f2bf(sum);
+        else g.Cf[(size_t)mm * g.ldc + n] = g.plain_mul != 0.f ? sum * g.plain_mul : sum;
+      }
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -358,28 +303,24 @@ struct GemmArgs {
   const unsigned short* bias;         // GO_GELU_F32 / GO_BIAS_BF16: [N] bf16
   int k_split;                        // GO_F32 only: > 1 cuts K into that many equal ranges (each a multiple of 64); range s
   size_t split_stride;                //   writes its partial product to C + s * split_stride (elements)
-  // two row segments (anchors, then targets, in one launch): rows from M1 on are rows 0.. of A2 / C2 when those are set
-  int M1; const void* A2; void* C2;
+  // two row segments (anchors, then targets, in one launch): rows from M1p on are rows 0.. of A2 / C2 when those are set;
+  // rows M1 .. M1p - 1 (there are some only where the segments start at tile boundaries) repeat row M1 - 1
+  int M1, M1p; const void* A2; void* C2;
 };
 // what a tile writes: the product (times mul) as fp32 or bf16, GELU(product + bias) as fp32, product + bias as bf16
 enum GemmOut { GO_F32 = 0, GO_BF16 = 1, GO_GELU_F32 = 2, GO_BIAS_BF16 = 3 };
 constexpr int GM_T = 128, GM_BK = 64, GM_LD = GM_BK + 8;
 template <bool A_F32, int BM>
 constexpr int gemm_lds_bytes() { return 2 * ((A_F32 ? 2 : 1) * BM + GM_T) * GM_LD * 2; }
-template <bool A_F32, GemmOut OUT, int BM>
-__global__ void __launch_bounds__(256) gemm_nt_kernel(GemmArgs g) {
+// acc += the tile's product over k in [kbeg, kbeg + klen); ends with every wave past its last read of LDS
+template <bool A_F32, int BM>
+__device__ __forceinline__ void gemm_mainloop(const GemmArgs& g, int m0, int n0, int kbeg, int klen, unsigned short* gemm_lds,
+                                              f32x16 (&acc)[BM / 64][2]) {
   constexpr int AP = A_F32 ? 2 : 1;   // planes of A
   constexpr int MT = BM / 64;         // 32-row MFMA tiles per wave
   constexpr int NA = BM / 32;         // staging pieces of A per thread (8 elements each); 4 of Bt
   constexpr int A_PLANE = BM * GM_LD, BUF = (AP * BM + GM_T) * GM_LD;   // elements
-  extern __shared__ __attribute__((aligned(16))) unsigned short gemm_lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, ln = lane & 31;
-  const int nbn = g.N / GM_T;
-  const int tiles = ((g.M + BM - 1) / BM) * nbn;
-  const int bid = xcd_task_id();   // consecutive tiles (they share rows of A) on one XCD, behind one L2
-  const int tile = bid % tiles, split = bid / tiles;   // split > 0 only for GO_F32 with k_split > 1
-  const int m0 = (tile / nbn) * BM, n0 = (tile % nbn) * GM_T;
-  const int klen = g.K / (g.k_split > 1 ? g.k_split : 1), kbeg = split * klen;
   const int wm = wave >> 1, wn = wave & 1;
   // staging: piece q = tid + 256 i of a tile is 8 elements: row q / 8, k 8 (q % 8)
   constexpr int AV = A_F32 ? 2 : 1;   // 16-byte loads per piece of A
@@ -391,8 +332,8 @@ __global__ void __launch_bounds__(256) gemm_nt_kernel(GemmArgs g) {
       const int q = tid + 256 * i, row = q >> 3, kc = q & 7;
       if (i < NA) {
         const int am = min(m0 + row, g.M - 1);   // rows past the end repeat the last one; their results are not stored
-        const bool second = g.A2 && am >= g.M1;
-        const size_t ia = (size_t)(second ? am - g.M1 : am) * g.lda + kbeg + k0 + 8 * kc;
+        const bool second = g.A2 && am >= g.M1p;
+        const size_t ia = (size_t)(second ? am - g.M1p : g.A2 ? min(am, g.M1 - 1) : am) * g.lda + kbeg + k0 + 8 * kc;
 #pragma unroll
         for (int v = 0; v < AV; v++) r.a[i][v] = *(const u32x4*)((const char*)(second ? g.A2 : g.A) + ia * (A_F32 ? 4 : 2) + 16 * v);
       }
@@ -421,13 +362,6 @@ __global__ void __launch_bounds__(256) gemm_nt_kernel(GemmArgs g) {
       *(u32x4*)&Bs[row * GM_LD + 8 * kc] = r.b[i];
     }
   };
-  f32x16 acc[MT][2];
-#pragma unroll
-  for (int mt = 0; mt < MT; mt++)
-#pragma unroll
-    for (int nt = 0; nt < 2; nt++)
-#pragma unroll
-      for (int r = 0; r < 16; r++) acc[mt][nt][r] = 0.f;
   const int nk = klen / GM_BK;
   // one k-step: the set that held step kt (already in LDS) takes the loads of step kt + 2, the MFMAs of step kt run,
   // the set of step kt + 1 goes to the other LDS buffer.  (STEADY: steps kt + 1 and kt + 2 exist; without branches
@@ -474,6 +408,31 @@ __global__ void __launch_bounds__(256) gemm_nt_kernel(GemmArgs g) {
     step(kt, rg[0], rg[1], std::false_type{});
     if (kt + 1 < nk) step(kt + 1, rg[1], rg[0], std::false_type{});
   }
+}
+template <int MT>
+__device__ __forceinline__ void gemm_zero(f32x16 (&acc)[MT][2]) {
+#pragma unroll
+  for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+    for (int nt = 0; nt < 2; nt++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) acc[mt][nt][r] = 0.f;
+}
+template <bool A_F32, GemmOut OUT, int BM>
+__global__ void __launch_bounds__(256) gemm_nt_kernel(GemmArgs g) {
+  constexpr int MT = BM / 64;
+  extern __shared__ __attribute__((aligned(16))) unsigned short gemm_lds[];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, ln = lane & 31;
+  const int nbn = g.N / GM_T;
+  const int tiles = ((g.M + BM - 1) / BM) * nbn;
+  const int bid = xcd_task_id();   // consecutive tiles (they share rows of A) on one XCD, behind one L2
+  const int tile = bid % tiles, split = bid / tiles;   // split > 0 only for GO_F32 with k_split > 1
+  const int m0 = (tile / nbn) * BM, n0 = (tile % nbn) * GM_T;
+  const int klen = g.K / (g.k_split > 1 ? g.k_split : 1), kbeg = split * klen;
+  const int wm = wave >> 1, wn = wave & 1;
+  f32x16 acc[MT][2];
+  gemm_zero<MT>(acc);
+  gemm_mainloop<A_F32, BM>(g, m0, n0, kbeg, klen, gemm_lds, acc);
   // lane (ln, h) holds column ln of each MFMA tile, rows 8 (r / 4) + 4 h + r % 4
   const float mul = g.mul != 0.f ? g.mul : 1.f;
 #pragma unroll
@@ -485,9 +444,9 @@ __global__ void __launch_bounds__(256) gemm_nt_kernel(GemmArgs g) {
         const int m = m0 + wm * 32 * MT + mt * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
         const int n = n0 + wn * 64 + nt * 32 + ln;
         if (m < g.M) {
-          const bool second = g.C2 && m >= g.M1;
+          const bool second = g.C2 && m >= g.M1p;   // (M1p == M1 wherever the rows of C are stored by this kernel)
           void* cb = second ? g.C2 : g.C;
-          const size_t at = (size_t)(second ? m - g.M1 : m) * g.ldc + n;
+          const size_t at = (size_t)(second ? m - g.M1p : m) * g.ldc + n;
           if (OUT == GO_F32) ((float*)cb)[(size_t)split * g.split_stride + at] = acc[mt][nt][r] * mul;
           else if (OUT == GO_BF16) ((unsigned short*)cb)[at] = f2bf(acc[mt][nt][r] * mul);
           else if (OUT == GO_GELU_F32) ((float*)cb)[at] = gelu_f(acc[mt][nt][r] + bf2f(g.bias[n]));
@@ -536,44 +495,331 @@ __global__ void __launch_bounds__(256) splitk_bias_bf16_kernel(const float* __re
   else ((s16x4*)out)[e] = o;
 }
 
-// One iteration of Step 3's software pipeline in one launch: the weight gradients of sub-batch c-2, dH and db1 of
-// sub-batch c-1 and the re-encode of sub-batch c are independent of each other (three sets of buffers), and none of
-// them fills the GPU alone.  The first n_dh workgroups take the n-tiles of dH, the next n_enc the tiles of the
-// re-encode, the remaining n_wg the weight-gradient tiles (n_wg2 of them dW2).  A count of 0 switches a part off
-// (pipeline ends).
-struct Step3Args {
-  WgradArgs g2, g1; int n_wg2, n_wg;
-  SkinnyArgs dh; int n_dh;
-  SkinnyArgs enc; int n_enc;
+// ---------------------------------------------------------------------------------------------------
+// Step 3 (Eq. 8 / 9) for a run of rows (one sub-batch, or as many whole sub-batches as the activation buffer holds) in
+// three launches:
+//   mlp_prep_kernel    X and the cached rows U into fragments contiguous along the rows (and the weights transposed where
+//                      the call has not done that yet)
+//   mlp_dh_*_kernel    H = X W1 + b1, Act = GELU(H), dA = U W2^T, dH = dA * GELU'(H) for a tile of rows x dh: both
+//                      contractions in one workgroup, so H and GELU'(H) never leave its registers
+//   mlp_grads_kernel   dW2 += Act^T U, dW1 += X^T dH, and the bias gradients from the column sums the other two left
+// The k index of the last contraction is the row, the slow index of all four operands.  They are therefore kept as
+// fragments: 1 KB blocks [row step of 16][32-column tile][plane], lane l holding column l % 32, rows 4 h + {0..3, 8..11}
+// (h = l / 32) -- which is how an MFMA leaves its results (register r of lane l: row 8 (r / 4) + 4 h + r % 4), so the
+// kernel that forms Act and dH stores them whole lines at a time and the one that contracts them loads MFMA operands
+// straight from L2, without LDS.  fp32 values are two planes (hi + lo), as everywhere in this file.
+// Rows: the rows of a second input (targets behind anchors) start at the next multiple of 32; what lies between and
+// behind repeats a row in Act and dH and is zero in X and U, so it adds nothing.
+struct RowSpan {
+  int n1, n2;                                  // rows of the two inputs (n2 may be 0)
+  int first2;                                  // row at which the second starts: n1 rounded up to 32
+  int rows() const { return n2 ? first2 + n2 : n1; }
+  int blocks() const { return (rows() + 31) / 32; }
 };
-__global__ void __launch_bounds__(256, 3) mlp_step3_kernel(Step3Args a) {
-  constexpr size_t kA = sizeof(unsigned short) * 2 * WG_KCH * WG_A_LD, kB = sizeof(unsigned short) * 2 * WG_KCH * WG_B_LD;
-  constexpr size_t kLds = kA + kB > sizeof(SkinnyRed) * 4 ? kA + kB : sizeof(SkinnyRed) * 4;
-  __shared__ __attribute__((aligned(16))) unsigned char lds[kLds];
+static RowSpan row_span(int n1, int n2) {
+  RowSpan r{};
+  r.n1 = n1; r.n2 = n2; r.first2 = n2 ? (n1 + 31) / 32 * 32 : n1;
+  return r;
+}
+
+__device__ __forceinline__ void store_planes2(unsigned short* base, size_t block, int lane, const float (&v)[8]) {
+  typedef __attribute__((ext_vector_type(8))) float f32x8;
+  const f32x8 x = {v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]};
+  const bf16x8 hi = __builtin_convertvector(x, bf16x8);
+  *(bf16x8*)(base + (block * 2) * 512 + lane * 8) = hi;
+  *(bf16x8*)(base + (block * 2 + 1) * 512 + lane * 8) = __builtin_convertvector(x - __builtin_convertvector(hi, f32x8), bf16x8);
+}
+
+struct TransposeJob { const unsigned short* W; unsigned short* Wt; int K, N; };   // Wt[n][k] = W[k][n], multiples of 64
+struct PrepArgs {
+  TransposeJob tr[2];
+  int n_tr0, n_tr;                             // 64 x 64 tiles of tr[0], of both
+  const unsigned short* x[2]; const float* u[2];
+  int n1, n2, blocks1, blocks;                 // rows; 32-row blocks of the first input, of both
+  int din, dout;
+  unsigned short* xt; unsigned short* ut;      // fragments: one plane, two planes
+  float* usum;                                 // [block][dout]: column sums of U over 32 rows
+};
+// Bound by its loads and stores; one workgroup per 64 x 64 tile of a weight or 32 x 128 block of X or U.
+__global__ void __launch_bounds__(256) mlp_prep_kernel(PrepArgs a) {
+  __shared__ __attribute__((aligned(16))) unsigned char lds[32 * 132 * 4];
+  const int tid = threadIdx.x;
   int id = blockIdx.x;
-  // the long-running workgroups (they stream whole weight rows) come first, the many short weight-gradient tiles
-  // fill in behind them (1.16 -> 1.08 ms per step at config 5 against the other order)
-  SkinnyRed* red = (SkinnyRed*)lds;
-  if (id < a.n_dh) {
-    const int nb = a.dh.N / 32;
-    skinny_tile<true, EP_DH, 2>(a.dh, id % nb, id / nb, red);
+  if (id < a.n_tr) {
+    const bool second = id >= a.n_tr0;
+    const TransposeJob t = second ? a.tr[1] : a.tr[0];
+    if (second) id -= a.n_tr0;
+    const int nb = t.N / 64, n0 = (id % nb) * 64, k0 = (id / nb) * 64;
+    unsigned short (*tile)[72] = (unsigned short (*)[72])lds;
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+      const int q = tid + 256 * i, r = q >> 3, c = (q & 7) * 8;
+      *(u32x4*)&tile[r][c] = *(const u32x4*)(t.W + (size_t)(k0 + r) * t.N + n0 + c);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+      const int q = tid + 256 * i, n = q >> 3, k = (q & 7) * 8;
+      s16x8 v;
+#pragma unroll
+      for (int e = 0; e < 8; e++) v[e] = (short)tile[k + e][n];
+      *(s16x8*)(t.Wt + (size_t)(n0 + n) * t.K + k0 + k) = v;
+    }
     return;
   }
-  id -= a.n_dh;
-  if (id < a.n_enc) {
-    const int nb = a.enc.N / 32;
-    skinny_tile<false, EP_GELU, 2>(a.enc, id % nb, id / nb, red);
-    return;
-  }
-  id -= a.n_enc;
-  unsigned short* As = (unsigned short*)lds;
-  unsigned short* Bs = (unsigned short*)(lds + kA);
-  if (id < a.n_wg2) {
-    const int nb = a.g2.N / 128;
-    wgrad_tile<true>(a.g2, id % nb, id / nb, As, Bs);
+  id -= a.n_tr;
+  float (*tile)[132] = (float (*)[132])lds;
+  const int xb = (a.din + 127) / 128, ub = a.dout / 128;
+  const bool is_u = id >= a.blocks * xb;
+  if (is_u) id -= a.blocks * xb;
+  const int per = is_u ? ub : xb, blk = id / per, c0 = (id % per) * 128;
+  const bool second = blk >= a.blocks1;
+  const int r0 = (second ? blk - a.blocks1 : blk) * 32, rows = second ? a.n2 : a.n1;
+  const int lane = tid & 63, w = tid >> 6, h = lane >> 5, ln = lane & 31;
+  if (is_u) {
+    const float* u = second ? a.u[1] : a.u[0];
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const int q = tid + 256 * i, r = q >> 5, c = (q & 31) * 4;
+      f32x4 v = {0.f, 0.f, 0.f, 0.f};
+      if (r0 + r < rows) v = *(const f32x4*)(u + (size_t)(r0 + r) * a.dout + c0 + c);
+      *(f32x4*)&tile[r][c] = v;
+    }
   } else {
-    const int nb = a.g1.N / 128;
-    wgrad_tile<false>(a.g1, (id - a.n_wg2) % nb, (id - a.n_wg2) / nb, As, Bs);
+    const unsigned short* x = second ? a.x[1] : a.x[0];
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+      const int q = tid + 256 * i, r = q >> 4, c = (q & 15) * 8;
+      s16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
+      if (r0 + r < rows && c0 + c < a.din) v = *(const s16x8*)(x + (size_t)(r0 + r) * a.din + c0 + c);
+#pragma unroll
+      for (int e = 0; e < 8; e++) tile[r][c + e] = bf2f((unsigned short)v[e]);
+    }
+  }
+  __syncthreads();
+  const int ct = c0 / 32 + w, CT = (is_u ? a.dout : a.din) / 32;
+  if (ct < CT) {
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 8; e++) v[e] = tile[16 * i + 4 * h + (e & 3) + 8 * (e >> 2)][32 * w + ln];
+      const size_t block = (size_t)(2 * blk + i) * CT + ct;
+      if (is_u) {
+        store_planes2(a.ut, block, lane, v);
+      } else {
+        s16x8 o;
+#pragma unroll
+        for (int e = 0; e < 8; e++) o[e] = (short)(__builtin_bit_cast(unsigned, v[e]) >> 16);   // stored bf16 values: exact
+        *(s16x8*)(a.xt + block * 512 + lane * 8) = o;
+      }
+    }
+  }
+  if (is_u && tid < 128) {
+    float s = 0.f;
+#pragma unroll
+    for (int r = 0; r < 32; r++) s += tile[r][tid];
+    a.usum[(size_t)blk * a.dout + c0 + tid] = s;
+  }
+}
+
+// Act and dH of a tile.  x: rows of the inputs, W1t [dh][din]; u: cached rows (fp32), W2 [dh][dout] as stored.
+struct DhArgs {
+  const unsigned short* x[2]; const float* u[2];
+  const unsigned short* W1t; const unsigned short* b1; const unsigned short* W2;
+  int n1, n2, first2, rows;                    // see RowSpan
+  int din, dh, dout;
+  unsigned short* act; unsigned short* dhp;    // fragments, two planes each
+  float* hsum;                                 // [32-row block][dh]: column sums of dH
+};
+__device__ __forceinline__ bool row_live(const DhArgs& g, int m) { return m < g.rows && (m < g.n1 || m >= g.first2); }
+
+// Few rows (a sub-batch): 32 x 32 tiles; four waves contract X W1, the other four U W2^T, at the same time.  Bound by the
+// latency of the weights (a wave has all its loads in flight at once) and the 8 KB a wave streams per k-chunk.
+__global__ void __launch_bounds__(512) mlp_dh_skinny_kernel(DhArgs g) {
+  __shared__ SkinnyRed red[8];
+  __shared__ float part[2][32];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, ln = lane & 31;
+  const int n0 = blockIdx.x * 32, blk = blockIdx.y, m0 = blk * 32;
+  const bool second = g.n2 && m0 >= g.first2;
+  const int row0 = second ? m0 - g.first2 : m0, last = (second ? g.n2 : g.n1) - 1;
+  if (wave < 4) skinny_product<false, 4>(second ? g.x[1] : g.x[0], g.din, row0, last, g.W1t, g.din, n0, g.din, red, wave);
+  else skinny_product<true, 4>(second ? g.u[1] : g.u[0], g.dout, row0, last, g.W2, g.dout, n0, g.dout, red + 4, wave - 4);
+  __syncthreads();
+  if (wave < 2) {
+    const float b = bf2f(g.b1[n0 + ln]);
+    float av[8], dv[8], s = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+      const int em = 16 * wave + 4 * h + (e & 3) + 8 * (e >> 2);
+      const float hv = skinny_sum(red, em, ln) + b;
+      av[e] = gelu_f(hv);
+      dv[e] = skinny_sum(red + 4, em, ln) * gelu_prime_f(hv);
+      s += row_live(g, m0 + em) ? dv[e] : 0.f;
+    }
+    const size_t block = (size_t)(2 * blk + wave) * (g.dh / 32) + blockIdx.x;
+    store_planes2(g.act, block, lane, av);
+    store_planes2(g.dhp, block, lane, dv);
+    s += __shfl_xor(s, 32);
+    if (h == 0) part[wave][ln] = s;
+  }
+  __syncthreads();
+  if (tid < 32) g.hsum[(size_t)blk * g.dh + n0 + tid] = part[0][tid] + part[1][tid];
+}
+
+// Many rows: BM x 128 tiles, both contractions through the tiled main loop.
+template <int BM>
+__global__ void __launch_bounds__(256, BM == 64 ? 2 : 1) mlp_dh_tiled_kernel(DhArgs g) {
+  constexpr int MT = BM / 64;
+  extern __shared__ __attribute__((aligned(16))) unsigned short gemm_lds[];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, ln = lane & 31, wm = wave >> 1, wn = wave & 1;
+  const int nbn = g.dh / GM_T, tile = xcd_task_id();
+  const int m0 = (tile / nbn) * BM, n0 = (tile % nbn) * GM_T;
+  const int row0 = m0 + wm * 32 * MT, CT = g.dh / 32;
+  GemmArgs a{};
+  a.M = g.rows; a.M1 = g.n1; a.M1p = g.first2;
+  a.A = g.x[0]; a.A2 = g.n2 ? g.x[1] : nullptr; a.lda = g.din; a.Bt = g.W1t; a.ldb = g.din;
+  f32x16 gp[MT][2];   // H, then GELU'(H)
+  gemm_zero<MT>(gp);
+  gemm_mainloop<false, BM>(a, m0, n0, 0, g.din, gemm_lds, gp);
+#pragma unroll
+  for (int nt = 0; nt < 2; nt++) {
+    const int n = n0 + wn * 64 + nt * 32 + ln;
+    const float b = bf2f(g.b1[n]);
+#pragma unroll
+    for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+      for (int kk = 0; kk < 2; kk++) {
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+          const float hv = gp[mt][nt][8 * kk + e] + b;
+          v[e] = gelu_f(hv);
+          gp[mt][nt][8 * kk + e] = gelu_prime_f(hv);
+        }
+        store_planes2(g.act, (size_t)((row0 / 32 + mt) * 2 + kk) * CT + n / 32, lane, v);
+      }
+  }
+  a.A = g.u[0]; a.A2 = g.n2 ? g.u[1] : nullptr; a.lda = g.dout; a.Bt = g.W2; a.ldb = g.dout;
+  f32x16 acc[MT][2];
+  gemm_zero<MT>(acc);
+  gemm_mainloop<true, BM>(a, m0, n0, 0, g.dout, gemm_lds, acc);
+#pragma unroll
+  for (int nt = 0; nt < 2; nt++) {
+    const int n = n0 + wn * 64 + nt * 32 + ln;
+#pragma unroll
+    for (int mt = 0; mt < MT; mt++) {
+      float s = 0.f;
+#pragma unroll
+      for (int kk = 0; kk < 2; kk++) {
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+          v[e] = acc[mt][nt][8 * kk + e] * gp[mt][nt][8 * kk + e];
+          s += row_live(g, row0 + 32 * mt + 16 * kk + 4 * h + (e & 3) + 8 * (e >> 2)) ? v[e] : 0.f;
+        }
+        store_planes2(g.dhp, (size_t)((row0 / 32 + mt) * 2 + kk) * CT + n / 32, lane, v);
+      }
+      s += __shfl_xor(s, 32);
+      if (h == 0 && row0 + 32 * mt < g.rows) g.hsum[(size_t)(row0 / 32 + mt) * g.dh + n] = s;
+    }
+  }
+}
+
+// The parameter gradients from the fragments.  A workgroup is one wave with a 64 x 128 tile of dW2 or dW1 in registers: it
+// starts from the accumulator's value in HBM, walks the rows 16 at a time and stores it once (single writer, no atomics,
+// rows in index order).  One wave per SIMD is enough: 24 (16) MFMAs per step against 12 (10) loads of 1 KB, issued two
+// steps ahead.  For one 32-row sub-batch the read and write of the accumulators is all there is (44 MB at 1024-3072-768).
+struct FragGrad { const unsigned short* A; const unsigned short* B; float* C; int ldc, CTa, CTb, mtiles, ntiles; };
+struct GradsArgs {
+  FragGrad g2, g1;                             // dW2: A = Act (two planes), B = U; dW1: A = X (one plane), B = dH
+  int steps;                                   // row steps of 16
+  int n2, n1;                                  // tiles of dW2, of dW1
+  const float* hsum; const float* usum; float* db1; float* db2;   // bias gradients += sums of the block sums, in order
+  int blocks, dh, dout;
+};
+template <int PA>
+__device__ __forceinline__ void frag_grad_tile(const FragGrad& g, int mi, int ni, int steps) {
+  constexpr int PD = 2;
+  const int lane = threadIdx.x, h = lane >> 5, ln = lane & 31;
+  f32x16 acc[2][4];
+  float* c = g.C + (size_t)(64 * mi + 4 * h) * g.ldc + 128 * ni + ln;
+#pragma unroll
+  for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+    for (int nt = 0; nt < 4; nt++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) acc[mt][nt][r] = c[(size_t)(32 * mt + 8 * (r >> 2) + (r & 3)) * g.ldc + 32 * nt];
+  const unsigned short* ap = g.A + (size_t)(2 * mi) * PA * 512 + lane * 8;
+  const unsigned short* bp = g.B + (size_t)(4 * ni) * 2 * 512 + lane * 8;
+  const size_t as = (size_t)g.CTa * PA * 512, bs = (size_t)g.CTb * 2 * 512;
+  bf16x8 fa[PD][2][PA], fb[PD][4][2];
+  auto load = [&](int slot, int step) __attribute__((always_inline)) {
+    const unsigned short* a = ap + step * as;
+    const unsigned short* b = bp + step * bs;
+#pragma unroll
+    for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+      for (int p = 0; p < PA; p++) fa[slot][mt][p] = *(const bf16x8*)(a + (mt * PA + p) * 512);
+#pragma unroll
+    for (int nt = 0; nt < 4; nt++)
+#pragma unroll
+      for (int p = 0; p < 2; p++) fb[slot][nt][p] = *(const bf16x8*)(b + (nt * 2 + p) * 512);
+  };
+  auto products = [&](int slot) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < PA + 1; t++)   // (hi, lo), (lo, hi) where A has two planes, (hi, hi)
+#pragma unroll
+      for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+        for (int nt = 0; nt < 4; nt++)
+          acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[slot][mt][(PA == 2 && t == 1) ? PA - 1 : 0], fb[slot][nt][t == 0 ? 1 : 0], acc[mt][nt], 0, 0, 0);
+  };
+  // steps is even: whole 32-row blocks
+  load(0, 0);
+  load(1, 1);
+  for (int s = 0; s < steps; s += 2) {
+    products(0);
+    load(0, min(s + 2, steps - 1));
+    products(1);
+    load(1, min(s + 3, steps - 1));
+  }
+#pragma unroll
+  for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+    for (int nt = 0; nt < 4; nt++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) c[(size_t)(32 * mt + 8 * (r >> 2) + (r & 3)) * g.ldc + 32 * nt] = acc[mt][nt][r];
+}
+__global__ void __launch_bounds__(64) mlp_grads_kernel(GradsArgs a) {
+  int id = blockIdx.x;
+  const int nb = (a.dh + a.dout) / 64;
+  if (id < nb) {   // 64 columns of a bias gradient
+    int n = id * 64 + (int)threadIdx.x;
+    const bool two = n >= a.dh;
+    if (two) n -= a.dh;
+    const float* p = (two ? a.usum : a.hsum) + n;
+    const int ld = two ? a.dout : a.dh;
+    float s = 0.f;
+    for (int b0 = 0; b0 < a.blocks; b0 += 16) {   // sixteen loads in flight, added in order
+      float v[16];
+#pragma unroll
+      for (int k = 0; k < 16; k++) v[k] = b0 + k < a.blocks ? p[(size_t)(b0 + k) * ld] : 0.f;
+#pragma unroll
+      for (int k = 0; k < 16; k++) s += v[k];
+    }
+    float* out = (two ? a.db2 : a.db1) + n;
+    *out += s;
+    return;
+  }
+  id -= nb;
+  // consecutive tiles (on one XCD, behind one L2) share the wider operand's columns
+  if (id < a.n2) {
+    const int t = id;
+    frag_grad_tile<2>(a.g2, t / a.g2.ntiles, t % a.g2.ntiles, a.steps);
+  } else {
+    const int t = id - a.n2;
+    frag_grad_tile<1>(a.g1, t % a.g1.mtiles, t / a.g1.mtiles, a.steps);
   }
 }
 
@@ -590,29 +836,54 @@ __global__ void __launch_bounds__(256) transpose_bf16_kernel(const unsigned shor
   for (int i = 0; i < 4; i++) Wt[(size_t)(n0 + ty + 8 * i) * K + k0 + tx] = t[tx][ty + 8 * i];
 }
 
+static inline size_t up256(size_t x) { return (x + 255) / 256 * 256; }
+
+// A forward takes Act (fp32 [rows][dh]) and the fp32 partial products of its second layer; a backward takes the fragments
+// of Act, dH, X and U and the block sums, in the same bytes.
 struct MlpWs {
-  float* H;             // [rows][dh] fp32 pre-activations
-  float* ActF;          // [rows][dh] fp32 GELU(H)
-  float* dH;            // [rows][dh] fp32
+  char* act;            // the shared region
+  float* ActF;          // forward: [rows][dh] fp32 GELU(H)
+  float* part;          // forward: rows x dh floats for the partial products of the second layer
   unsigned short* W1T;  // [dh][din] bf16: W1 transposed
   unsigned short* W2T;  // [dout][dh] bf16: W2 transposed
   size_t total;
 };
-
-static inline size_t up256(size_t x) { return (x + 255) / 256 * 256; }
-
+// rows that RowSpan and the tiles of the backward may add: up to 31 between the inputs, up to 127 behind
+constexpr int kSpanPad = 160;
+static size_t backward_row_bytes(const gc_mlp_params* w) {
+  return (size_t)w->dh * 8 + (size_t)w->din * 2 + (size_t)w->dout * 4 + (size_t)(w->dh + w->dout) / 8;
+}
 static MlpWs carve_mlp_ws(char* base, int rows, const gc_mlp_params* w) {
   MlpWs m{};
   size_t off = 0;
   // integer arithmetic: the sizing calls carve from a null base
   auto at = [base](size_t o) { return (uintptr_t)base + o; };
-  m.H = (float*)at(off); off += up256((size_t)rows * w->dh * 4);
-  m.ActF = (float*)at(off); off += up256((size_t)rows * w->dh * 4);
-  m.dH = (float*)at(off); off += up256((size_t)rows * w->dh * 4);
   m.W1T = (unsigned short*)at(off); off += up256((size_t)w->din * w->dh * 2);
   m.W2T = (unsigned short*)at(off); off += up256((size_t)w->dh * w->dout * 2);
+  m.act = (char*)at(off);
+  // three fp32 activations a row (what a backward needs beyond 8 dh bytes a row usually fits into the third), and the
+  // rows of padding
+  const size_t one = up256((size_t)rows * w->dh * 4);
+  m.ActF = (float*)at(off);
+  m.part = (float*)at(off + one);
+  const size_t row = backward_row_bytes(w), more = row > (size_t)w->dh * 12 ? (row - (size_t)w->dh * 12) * rows : 0;
+  off += 3 * one + up256(more) + up256(row * kSpanPad) + 6 * 256;
   m.total = off;
   return m;
+}
+struct BackwardWs { unsigned short* act; unsigned short* dh; unsigned short* xt; unsigned short* ut; float* hsum; float* usum; };
+static BackwardWs carve_backward(const MlpWs& ws, const RowSpan& r, const gc_mlp_params* w) {
+  BackwardWs b{};
+  char* p = ws.act;
+  auto take = [&](size_t bytes) { char* q = p; p += up256(bytes); return q; };
+  const size_t rows = (size_t)(r.rows() + 127) / 128 * 128;
+  b.act = (unsigned short*)take(rows * w->dh * 4);
+  b.dh = (unsigned short*)take(rows * w->dh * 4);
+  b.xt = (unsigned short*)take(rows * w->din * 2);
+  b.ut = (unsigned short*)take(rows * w->dout * 4);
+  b.hsum = (float*)take(rows / 32 * w->dh * 4);
+  b.usum = (float*)take(rows / 32 * w->dout * 4);
+  return b;
 }
 
 static int check_mlp_params(const gc_mlp_params* w) {
@@ -624,119 +895,126 @@ static int check_mlp_params(const gc_mlp_params* w) {
   return GC_OK;
 }
 
-// the transposed weight copies that the skinny kernel streams (once per entry-point call: the weights do
-// not change inside a call)
+// the transposed weight copies that the forward kernels stream (once per entry-point call: the weights do not change
+// inside a call)
+static int transpose_jobs(PrepArgs& g, const gc_mlp_params* w, const MlpWs& ws, bool both) {
+  g.tr[0] = {(const unsigned short*)w->W1, ws.W1T, w->din, w->dh};
+  g.n_tr0 = (w->din / 64) * (w->dh / 64);
+  g.n_tr = g.n_tr0;
+  if (both) {
+    g.tr[1] = {(const unsigned short*)w->W2, ws.W2T, w->dh, w->dout};
+    g.n_tr += (w->dh / 64) * (w->dout / 64);
+  }
+  return g.n_tr;
+}
 static hipError_t mlp_prepare(const gc_mlp_params* w, const MlpWs& ws, hipStream_t s) {
-  transpose_bf16_kernel<<<dim3(w->dh / 32, w->din / 32), 256, 0, s>>>((const unsigned short*)w->W1, w->din, w->dh, ws.W1T);
-  transpose_bf16_kernel<<<dim3(w->dout / 32, w->dh / 32), 256, 0, s>>>((const unsigned short*)w->W2, w->dh, w->dout, ws.W2T);
+  PrepArgs g{};
+  mlp_prep_kernel<<<transpose_jobs(g, w, ws, true), 256, 0, s>>>(g);
   return hipGetLastError();
 }
 
-// H = x W1 + b1 (kept when keepH), Act = GELU(H)
-static SkinnyArgs layer1_args(const void* x, int rows, const gc_mlp_params* w, const MlpWs& ws, bool keepH) {
-  SkinnyArgs g{};
-  g.A = x; g.lda = w->din; g.Bt = ws.W1T; g.ldb = w->din; g.M = rows; g.N = w->dh; g.K = w->din;
-  g.bias = (const unsigned short*)w->b1; g.H = keepH ? ws.H : nullptr; g.ActF = ws.ActF; g.ldh = w->dh;
-  return g;
-}
-// dA = U W2^T, dH = dA * GELU'(H), db1 += column sums
-static SkinnyArgs dh_args(int rows, const gc_mlp_params* w, const float* u, const gc_mlp_grads* acc, const MlpWs& ws) {
-  SkinnyArgs g{};
-  g.A = u; g.lda = w->dout; g.Bt = (const unsigned short*)w->W2; g.ldb = w->dout; g.M = rows; g.N = w->dh; g.K = w->dout;
-  g.H = ws.H; g.ldh = w->dh; g.Cf = ws.dH; g.ldc = w->dh;
-  return g;
-}
-// dW2 += Act^T U, db2 += column sums of U (g2);  dW1 += X^T dH (g1)
-static void wgrad_args(const void* x, int rows, const gc_mlp_params* w, const float* u, const gc_mlp_grads* acc,
-                       const MlpWs& ws, WgradArgs& g2, WgradArgs& g1) {
-  g2 = WgradArgs{}; g1 = WgradArgs{};
-  g2.A = ws.ActF; g2.lda = w->dh; g2.B = u; g2.ldb = w->dout; g2.M = w->dh; g2.N = w->dout; g2.K = rows;
-  g2.C = acc->dW2; g2.ldc = w->dout; g2.colsum = acc->db2;
-  g1.A = x; g1.lda = w->din; g1.B = ws.dH; g1.ldb = w->dh; g1.M = w->din; g1.N = w->dh; g1.K = rows;
-  g1.C = acc->dW1; g1.ldc = w->dh; g1.colsum = acc->db1; g1.colsum_rows = 32;   // db1: 32-row tiles of dH, in order
-}
-
-constexpr int kGemmRows = 128;   // from this many rows on the graph-less forward runs as tiled GEMMs
+constexpr int kGemmRows = 128;   // from this many rows on the forward and the backward run as tiled GEMMs
 constexpr int kStep1Rows = 2048;  // rows per launch of Step 1 (see group_rows)
-// forward of one sub-batch (after mlp_prepare); keepH: also write the fp32 pre-activations (Step 3)
+// graph-less forward (after mlp_prepare)
 // tiled: the graph-less forward of many rows; the caller decides it per input (not per launch), so that a row's bits do
 // not depend on how the rows are cut into launches
 // x2 / rows2 / y2 (tiled only): a second input whose rows follow those of x in the same launches (the targets behind the
 // anchors: together they fill the GPU better than one after the other)
-static hipError_t mlp_forward(const void* x, int rows, const gc_mlp_params* w, const MlpWs& ws, bool keepH, void* y,
-                              hipStream_t s, bool tiled = false, const void* x2 = nullptr, int rows2 = 0, void* y2 = nullptr) {
-  if (tiled && !keepH && y) {
+static hipError_t mlp_forward(const void* x, int rows, const gc_mlp_params* w, const MlpWs& ws, void* y, hipStream_t s,
+                              bool tiled, const void* x2 = nullptr, int rows2 = 0, void* y2 = nullptr) {
+  if (tiled) {
     const int all = rows + rows2;
-    // many rows and nothing kept for a backward (Step 1): both layers as tiled GEMMs over all the rows at once, which
-    // read the weights once per 64 or 128 rows instead of once per 32
+    // both layers as tiled GEMMs over all the rows at once, which read the weights once per 64 or 128 rows instead of
+    // once per 32
     GemmArgs g1{};
     g1.A = x; g1.lda = w->din; g1.Bt = ws.W1T; g1.ldb = w->din; g1.M = all; g1.N = w->dh; g1.K = w->din;
-    g1.C = ws.ActF; g1.ldc = w->dh; g1.bias = (const unsigned short*)w->b1; g1.M1 = rows; g1.A2 = x2;
+    g1.C = ws.ActF; g1.ldc = w->dh; g1.bias = (const unsigned short*)w->b1; g1.M1 = g1.M1p = rows; g1.A2 = x2;
     if (hipError_t e = launch_gemm_nt<false, GO_GELU_F32>(g1, s); e != hipSuccess) return e;
     GemmArgs g2{};
     g2.A = ws.ActF; g2.lda = w->dh; g2.Bt = ws.W2T; g2.ldb = w->dh; g2.M = all; g2.N = w->dout; g2.K = w->dh;
-    g2.C = y; g2.ldc = w->dout; g2.bias = (const unsigned short*)w->b2; g2.M1 = rows; g2.C2 = y2;
+    g2.C = y; g2.ldc = w->dout; g2.bias = (const unsigned short*)w->b2; g2.M1 = g2.M1p = rows; g2.C2 = y2;
     // The second layer is narrow (dout columns) and long (dh): few tiles, each a long chain of k-steps.  While the tiles
-    // do not fill the GPU, the contraction is cut into up to four ranges whose fp32 partial products go to the dH
-    // buffer (unused by a graph-less forward; rows x dh floats hold dh / dout partial outputs) and are summed, in
-    // index order, by a kernel that adds the bias.  The split depends on the shape only, not on the rows of a launch.
+    // do not fill the GPU, the contraction is cut into up to four ranges whose fp32 partial products (dh / dout of them
+    // fit the rows x dh floats of `part`) are summed, in index order, by a kernel that adds the bias.  The split depends on
+    // the shape only, not on the rows of a launch.
     int ks = 1;
     const int tiles64 = ((kStep1Rows + 63) / 64) * (w->dout / GM_T);   // tiles of a full Step-1 launch
     while (ks < 4 && tiles64 * ks < 2 * num_cu() && (ks * 2) * w->dout <= w->dh && w->dh % (GM_BK * ks * 2) == 0) ks *= 2;
     if (ks == 1) return launch_gemm_nt<true, GO_BIAS_BF16>(g2, s);
-    g2.C = ws.dH; g2.C2 = nullptr; g2.bias = nullptr; g2.k_split = ks; g2.split_stride = (size_t)all * w->dout;
+    g2.C = ws.part; g2.C2 = nullptr; g2.bias = nullptr; g2.k_split = ks; g2.split_stride = (size_t)all * w->dout;
     if (hipError_t e = launch_gemm_nt<true, GO_F32>(g2, s); e != hipSuccess) return e;
     const size_t n4 = (size_t)all * w->dout / 4;
-    splitk_bias_bf16_kernel<<<(unsigned)((n4 + 255) / 256), 256, 0, s>>>(ws.dH, ks, g2.split_stride, (const unsigned short*)w->b2,
+    splitk_bias_bf16_kernel<<<(unsigned)((n4 + 255) / 256), 256, 0, s>>>(ws.part, ks, g2.split_stride, (const unsigned short*)w->b2,
                                                                       w->dout, (unsigned short*)y, n4, rows, (unsigned short*)y2);
     return hipGetLastError();
   }
-  mlp_skinny_kernel<false, EP_GELU><<<dim3(w->dh / 32, (rows + 31) / 32), 256, 0, s>>>(layer1_args(x, rows, w, ws, keepH));
-  if (y) {
-    SkinnyArgs g2{};
-    g2.A = ws.ActF; g2.lda = w->dh; g2.Bt = ws.W2T; g2.ldb = w->dh; g2.M = rows; g2.N = w->dout; g2.K = w->dh;
-    g2.bias = (const unsigned short*)w->b2; g2.Cb = (unsigned short*)y; g2.ldc = w->dout;
-    mlp_skinny_kernel<true, EP_BIAS><<<dim3(w->dout / 32, (rows + 31) / 32), 256, 0, s>>>(g2);
+  SkinnyArgs g1{};
+  g1.A = x; g1.lda = w->din; g1.Bt = ws.W1T; g1.ldb = w->din; g1.M = rows; g1.N = w->dh; g1.K = w->din;
+  g1.bias = (const unsigned short*)w->b1; g1.ActF = ws.ActF; g1.ldh = w->dh;
+  mlp_skinny_kernel<false, EP_GELU><<<dim3(w->dh / 32, (rows + 31) / 32), 256, 0, s>>>(g1);
+  SkinnyArgs g2{};
+  g2.A = ws.ActF; g2.lda = w->dh; g2.Bt = ws.W2T; g2.ldb = w->dh; g2.M = rows; g2.N = w->dout; g2.K = w->dh;
+  g2.bias = (const unsigned short*)w->b2; g2.Cb = (unsigned short*)y; g2.ldc = w->dout;
+  mlp_skinny_kernel<true, EP_BIAS><<<dim3(w->dout / 32, (rows + 31) / 32), 256, 0, s>>>(g2);
+  return hipGetLastError();
+}
+
+// Re-encode and surrogate backward of the rows of one or two inputs (Eq. 8 / 9), gradients added into acc.
+// transpose_w1: W1^T has not been made by this call yet.
+struct BackwardRows { const void* x; const float* u; int n; };
+static hipError_t mlp_backward(const BackwardRows& a, const BackwardRows& b, const gc_mlp_params* w, const gc_mlp_grads* acc,
+                               const MlpWs& ws, bool transpose_w1, hipStream_t s) {
+  const RowSpan r = row_span(a.n, b.n);
+  const BackwardWs bw = carve_backward(ws, r, w);
+  PrepArgs p{};
+  if (transpose_w1) transpose_jobs(p, w, ws, false);
+  p.x[0] = (const unsigned short*)a.x; p.x[1] = (const unsigned short*)b.x; p.u[0] = a.u; p.u[1] = b.u;
+  p.n1 = r.n1; p.n2 = r.n2; p.blocks1 = (r.n1 + 31) / 32; p.blocks = r.blocks(); p.din = w->din; p.dout = w->dout;
+  p.xt = bw.xt; p.ut = bw.ut; p.usum = bw.usum;
+  mlp_prep_kernel<<<p.n_tr + p.blocks * ((w->din + 127) / 128 + w->dout / 128), 256, 0, s>>>(p);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+
+  DhArgs d{};
+  for (int i = 0; i < 2; i++) { d.x[i] = p.x[i]; d.u[i] = p.u[i]; }
+  d.W1t = ws.W1T; d.b1 = (const unsigned short*)w->b1; d.W2 = (const unsigned short*)w->W2;
+  d.n1 = r.n1; d.n2 = r.n2; d.first2 = r.first2; d.rows = r.rows(); d.din = w->din; d.dh = w->dh; d.dout = w->dout;
+  d.act = bw.act; d.dhp = bw.dh; d.hsum = bw.hsum;
+  if (d.rows < kGemmRows) {
+    mlp_dh_skinny_kernel<<<dim3(w->dh / 32, r.blocks()), 512, 0, s>>>(d);
+  } else {
+    const int t128 = ((d.rows + 127) / 128) * (w->dh / GM_T);
+    if (t128 >= 2 * num_cu()) {
+      static bool done[64];
+      constexpr int lds = gemm_lds_bytes<true, 128>();
+      if (hipError_t e = ensure_dyn_lds((const void*)mlp_dh_tiled_kernel<128>, lds, done); e != hipSuccess) return e;
+      mlp_dh_tiled_kernel<128><<<t128, 256, lds, s>>>(d);
+    } else {
+      static bool done[64];
+      constexpr int lds = gemm_lds_bytes<true, 64>();
+      if (hipError_t e = ensure_dyn_lds((const void*)mlp_dh_tiled_kernel<64>, lds, done); e != hipSuccess) return e;
+      mlp_dh_tiled_kernel<64><<<((d.rows + 63) / 64) * (w->dh / GM_T), 256, lds, s>>>(d);
+    }
   }
-  return hipGetLastError();
-}
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
 
-// the surrogate backward of one sub-batch in three parts: (1) re-encode keeping H and Act = mlp_forward with
-// keepH, (2) dH and db1, (3) the weight gradients
-static hipError_t mlp_backward_dh(int rows, const gc_mlp_params* w, const float* u, const gc_mlp_grads* acc,
-                                  const MlpWs& ws, hipStream_t s) {
-  mlp_skinny_kernel<true, EP_DH><<<dim3(w->dh / 32, (rows + 31) / 32), 256, 0, s>>>(dh_args(rows, w, u, acc, ws));
+  GradsArgs g{};
+  g.g2 = {bw.act, bw.ut, acc->dW2, w->dout, w->dh / 32, w->dout / 32, w->dh / 64, w->dout / 128};
+  g.g1 = {bw.xt, bw.dh, acc->dW1, w->dh, w->din / 32, w->dh / 32, w->din / 64, w->dh / 128};
+  g.steps = 2 * r.blocks();
+  g.n2 = g.g2.mtiles * g.g2.ntiles; g.n1 = g.g1.mtiles * g.g1.ntiles;
+  g.hsum = bw.hsum; g.usum = bw.usum; g.db1 = acc->db1; g.db2 = acc->db2;
+  g.blocks = r.blocks(); g.dh = w->dh; g.dout = w->dout;
+  mlp_grads_kernel<<<(w->dh + w->dout) / 64 + g.n2 + g.n1, 64, 0, s>>>(g);
   return hipGetLastError();
-}
-
-// second half: the weight gradients, from what the first half left in ws
-static hipError_t mlp_backward_wgrad(const void* x, int rows, const gc_mlp_params* w, const float* u, const gc_mlp_grads* acc,
-                                     const MlpWs& ws, hipStream_t s) {
-  WgradArgs g2, g1;
-  wgrad_args(x, rows, w, u, acc, ws, g2, g1);
-  const int n2 = (w->dout / 128) * (w->dh / WG_M), n1 = (w->dh / 128) * (w->din / WG_M);
-  mlp_wgrad_kernel<<<n2 + n1, 256, 0, s>>>(g2, g1, n2);
-  return hipGetLastError();
-}
-
-static hipError_t mlp_backward(const void* x, int rows, const gc_mlp_params* w, const float* u, const gc_mlp_grads* acc,
-                               const MlpWs& ws, hipStream_t s) {
-  hipError_t e = mlp_forward(x, rows, w, ws, true, nullptr, s);
-  if (e != hipSuccess) return e;
-  e = mlp_backward_dh(rows, w, u, acc, ws, s);
-  if (e != hipSuccess) return e;
-  return mlp_backward_wgrad(x, rows, w, u, acc, ws, s);
 }
 
 // ---- the one-GPU driver of Steps 1-3 -----------------------------------------------------------------------
 // Sub-batches are small, so one of them cannot fill the GPU.  Step 1 keeps nothing but the representations and
 // its rows do not depend on each other, so many consecutive sub-batches go through each launch (group_rows; a row's
-// result does not depend on how many rows share the launch; only transient buffers grow).  In Step 3 the
-// accumulation order is fixed (sub-batch order), so it runs as a software pipeline of three stages, one launch
-// (mlp_step3_kernel) per iteration: re-encode of sub-batch c, dH and db1 of c-1, weight gradients of c-2, on three
-// sets of activation buffers.  Everything is enqueued on the caller's stream, in an order that does not depend
-// on timing.
-constexpr int kLanes = 3;   // buffer sets = pipeline stages of Step 3
+// result does not depend on how many rows share the launch).  Step 3 re-encodes and back-propagates whole sub-batches in
+// index order, as many of them per run of mlp_backward as the activation buffer that Step 1 has used holds: the memory of
+// a call is what Step 1 takes, and the fp32 accumulators make one trip through HBM per run instead of one per sub-batch.
+// Everything is enqueued on the caller's stream, in an order that does not depend on timing.
 constexpr int kGroup = 8;   // sub-batches per launch in Step 1
 static std::mutex g_step_mutex;
 
@@ -760,19 +1038,11 @@ static int step1_ws_rows(int B, int P, int chunk_q, int chunk_p) {
 }
 
 struct StepWs {
-  size_t off_q, off_p, off_dq, off_dp, off_loss, off_mlp, off_act, total;
-  size_t loss_bytes, mlp_bytes, act_bytes;
+  size_t off_q, off_p, off_dq, off_dp, off_loss, off_mlp, total;
+  size_t loss_bytes;
 };
 
-// sub-batches that one launch of Step 3 covers: the caller's accumulate_group where the sub-batch sizes allow the
-// result to stay bit-identical (whole 32-row MFMA k-chunks per sub-batch), else 1
-static int effective_group(int group, int chunk_q, int chunk_p) {
-  if (group < 1) group = 1;
-  if (group > kGroup) group = kGroup;
-  return (chunk_q % 32 == 0 && chunk_p % 32 == 0) ? group : 1;
-}
-
-static StepWs plan_step(int B, int P, int chunk_q, int chunk_p, const gc_mlp_params* w, int group) {
+static StepWs plan_step(int B, int P, int chunk_q, int chunk_p, const gc_mlp_params* w) {
   StepWs s{};
   size_t off = 0;
   auto take = [&](size_t b) { size_t o = off; off = up256(off + b); return o; };
@@ -782,12 +1052,7 @@ static StepWs plan_step(int B, int P, int chunk_q, int chunk_p, const gc_mlp_par
   s.off_dp = take((size_t)P * w->dout * 4);
   s.loss_bytes = make_loss_plan(B, P, w->dout, GC_BF16, false).total;
   s.off_loss = take(s.loss_bytes);
-  const int cmax = chunk_q > chunk_p ? chunk_q : chunk_p;
-  s.mlp_bytes = carve_mlp_ws(nullptr, step1_ws_rows(B, P, chunk_q, chunk_p), w).total;
-  s.off_mlp = take(s.mlp_bytes);
-  const int g3 = effective_group(group, chunk_q, chunk_p);
-  s.act_bytes = 3 * up256((size_t)cmax * g3 * w->dh * 4);  // H, Act, dH of one more lane
-  s.off_act = take((kLanes - 1) * s.act_bytes);
+  s.off_mlp = take(carve_mlp_ws(nullptr, step1_ws_rows(B, P, chunk_q, chunk_p), w).total);
   s.total = off;
   return s;
 }
@@ -802,7 +1067,6 @@ struct StepCall {
   gc_mlp_grads grads;
   void* q_rep; void* p_rep; float* dq; float* dp;
   void* workspace;
-  int group;   // accumulate_group
 };
 
 // enqueues Steps 1-3 on s
@@ -813,52 +1077,30 @@ static int enqueue_step(const StepCall& c, hipStream_t s) {
   const float scale = c.scale, temp = c.temp;
   float* loss = c.loss; void* q_rep = c.q_rep; void* p_rep = c.p_rep; float* dq = c.dq; float* dp = c.dp;
   void* workspace = c.workspace;
-  const StepWs sw = plan_step(B, P, chunk_q, chunk_p, w, c.group);
-  const int g3 = effective_group(c.group, chunk_q, chunk_p);
+  const StepWs sw = plan_step(B, P, chunk_q, chunk_p, w);
   char* base = (char*)workspace;
   unsigned short* Q = q_rep ? (unsigned short*)q_rep : (unsigned short*)(base + sw.off_q);
   unsigned short* Pm = p_rep ? (unsigned short*)p_rep : (unsigned short*)(base + sw.off_p);
   float* dQ = dq ? dq : (float*)(base + sw.off_dq);
   float* dP = dp ? dp : (float*)(base + sw.off_dp);
-  const int cmax = chunk_q > chunk_p ? chunk_q : chunk_p;
-  MlpWs lane[kLanes];  // buffer sets (set 0 also serves Step 1); all share the transposed weights
-  lane[0] = carve_mlp_ws(base + sw.off_mlp, step1_ws_rows(B, P, chunk_q, chunk_p), w);
-  for (int l = 1; l < kLanes; l++) {
-    lane[l] = lane[0];
-    char* ab = base + sw.off_act + (size_t)(l - 1) * sw.act_bytes;
-    const size_t one = up256((size_t)cmax * g3 * w->dh * 4);
-    lane[l].H = (float*)ab; lane[l].ActF = (float*)(ab + one); lane[l].dH = (float*)(ab + 2 * one);
-  }
+  const int room = step1_ws_rows(B, P, chunk_q, chunk_p);   // rows of the activation buffer
+  const MlpWs mw = carve_mlp_ws(base + sw.off_mlp, room, w);
   auto ok = [](hipError_t e) { return e == hipSuccess; };
-  if (!ok(mlp_prepare(w, lane[0], s))) return GC_ERR_HIP;
-  // the sub-batches in index order: anchors first, then targets.  With accumulate_group = G > 1 an entry covers G
-  // consecutive sub-batches of one side (their rows are contiguous): the kernels of Step 3 visit the rows in the same
-  // order and 32-row k-chunks as G single launches would, and add the bias gradients one sub-batch after the other
-  // (`chunk`), so the parameter gradients keep their bits while the fp32 accumulators make one trip through HBM
-  // instead of G.
-  struct Sub { const unsigned short* x; int rows; unsigned short* y; const float* u; int chunk; };
-  std::vector<Sub> subs;
-  for (int a = 0; a < B; a += chunk_q * g3)
-    subs.push_back({(const unsigned short*)x_q + (size_t)a * w->din, B - a < chunk_q * g3 ? B - a : chunk_q * g3, Q + (size_t)a * w->dout, dQ + (size_t)a * w->dout, chunk_q});
-  for (int a = 0; a < P; a += chunk_p * g3)
-    subs.push_back({(const unsigned short*)x_p + (size_t)a * w->din, P - a < chunk_p * g3 ? P - a : chunk_p * g3, Pm + (size_t)a * w->dout, dP + (size_t)a * w->dout, chunk_p});
-  const int nsub = (int)subs.size();
+  if (!ok(mlp_prepare(w, mw, s))) return GC_ERR_HIP;
   // Step 1: graph-less forward, representations kept: both inputs through the same launches where they fit one
   // (step1_joint), else group_rows rows of one input per launch
   if (step1_joint(B, P)) {
-    if (!ok(mlp_forward(x_q, B, w, lane[0], false, Q, s, true, x_p, P, Pm))) return GC_ERR_HIP;
+    if (!ok(mlp_forward(x_q, B, w, mw, Q, s, true, x_p, P, Pm))) return GC_ERR_HIP;
   } else {
     const int gq = group_rows(chunk_q, B), gp = group_rows(chunk_p, P);
     for (int a = 0; a < B; a += gq) {
       const int rows = B - a < gq ? B - a : gq;
-      if (!ok(mlp_forward((const unsigned short*)x_q + (size_t)a * w->din, rows, w, lane[0], false, Q + (size_t)a * w->dout, s,
-                          B >= kGemmRows)))
+      if (!ok(mlp_forward((const unsigned short*)x_q + (size_t)a * w->din, rows, w, mw, Q + (size_t)a * w->dout, s, B >= kGemmRows)))
         return GC_ERR_HIP;
     }
     for (int a = 0; a < P; a += gp) {
       const int rows = P - a < gp ? P - a : gp;
-      if (!ok(mlp_forward((const unsigned short*)x_p + (size_t)a * w->din, rows, w, lane[0], false, Pm + (size_t)a * w->dout, s,
-                          P >= kGemmRows)))
+      if (!ok(mlp_forward((const unsigned short*)x_p + (size_t)a * w->din, rows, w, mw, Pm + (size_t)a * w->dout, s, P >= kGemmRows)))
         return GC_ERR_HIP;
     }
   }
@@ -866,33 +1108,23 @@ static int enqueue_step(const StepCall& c, hipStream_t s) {
   int rc = gc_loss_and_rep_grad_ex(GC_BF16, Q, Pm, pos_idx, B, P, w->dout, scale, temp, 0, loss, dQ, dP, nullptr, nullptr,
                                base + sw.off_loss, sw.loss_bytes, (void*)s);
   if (rc != GC_OK) return rc;
-  // Step 3: per sub-batch re-encode and backward of the cached rows; gradients accumulated in index order
-  const int n2 = (w->dout / 128) * (w->dh / WG_M), n1 = (w->dh / 128) * (w->din / WG_M);
-  for (int i = 0; i < nsub + 2; i++) {
-    Step3Args a3{};
-    if (i >= 2) {                      // weight gradients of sub-batch i-2
-      const Sub& sb = subs[i - 2];
-      wgrad_args(sb.x, sb.rows, w, sb.u, grads, lane[(i - 2) % kLanes], a3.g2, a3.g1);
-      a3.g2.colsum_rows = sb.chunk;
-      a3.n_wg2 = n2; a3.n_wg = n2 + n1;
-    }
-    if (i >= 1 && i - 1 < nsub) {      // dH, db1 of sub-batch i-1
-      const Sub& sb = subs[i - 1];
-      a3.dh = dh_args(sb.rows, w, sb.u, grads, lane[(i - 1) % kLanes]);
-      a3.n_dh = (w->dh / 32) * ((sb.rows + 31) / 32);
-    }
-    if (i < nsub) {                    // re-encode of sub-batch i, keeping H and Act
-      const Sub& sb = subs[i];
-      a3.enc = layer1_args(sb.x, sb.rows, w, lane[i % kLanes], true);
-      a3.n_enc = (w->dh / 32) * ((sb.rows + 31) / 32);
-    }
-    mlp_step3_kernel<<<a3.n_wg + a3.n_dh + a3.n_enc, 256, 0, s>>>(a3);
+  // Step 3: re-encode and backward of the cached rows, whole sub-batches in index order: anchors, then targets
+  auto rows_of = [&](const void* x, const float* u, int first, int n) {
+    return BackwardRows{(const unsigned short*)x + (size_t)first * w->din, u + (size_t)first * w->dout, n};
+  };
+  if (B + P <= room) return ok(mlp_backward(rows_of(x_q, dQ, 0, B), rows_of(x_p, dP, 0, P), w, grads, mw, false, s)) ? GC_OK : GC_ERR_HIP;
+  for (int side = 0; side < 2; side++) {
+    const int n = side ? P : B, chunk = side ? chunk_p : chunk_q;
+    const int per = chunk < room ? room / chunk * chunk : room;   // (a sub-batch larger than the buffer has one of its own size)
+    for (int a = 0; a < n; a += per)
+      if (!ok(mlp_backward(rows_of(side ? x_p : x_q, side ? dP : dQ, a, n - a < per ? n - a : per), BackwardRows{nullptr, nullptr, 0}, w, grads, mw,
+                           false, s)))
+        return GC_ERR_HIP;
   }
-  if (!ok(hipGetLastError())) return GC_ERR_HIP;
   return GC_OK;
 }
 
-// A step is some seventy small launches, and a host that enqueues them one by one can fall behind the GPU.  The second time a call comes with exactly the same arguments, it is recorded into a HIP graph (on a
+// A step is a dozen launches, and a host that enqueues them one by one can fall behind the GPU.  The second time a call comes with exactly the same arguments, it is recorded into a HIP graph (on a
 // stream of the library's: the caller's may be the null stream, which cannot be captured) and from then on
 // replayed with one launch.  The graph holds kernel nodes only, no memset nodes.  Up to
 // kMaxGraphs argument sets are remembered per device (a graph in flight is never destroyed); others, calls
@@ -1278,7 +1510,7 @@ int gc_mlp_forward_nograd_bf16(const void* x, int rows, const gc_mlp_params* w, 
     return GC_ERR_WORKSPACE;
   const MlpWs ws = carve_mlp_ws((char*)workspace, rows, w);
   if (mlp_prepare(w, ws, (hipStream_t)stream) != hipSuccess) return GC_ERR_HIP;
-  return mlp_forward(x, rows, w, ws, false, y, (hipStream_t)stream, rows >= kGemmRows) == hipSuccess ? GC_OK : GC_ERR_HIP;
+  return mlp_forward(x, rows, w, ws, y, (hipStream_t)stream, rows >= kGemmRows) == hipSuccess ? GC_OK : GC_ERR_HIP;
 }
 
 int gc_chunk_surrogate_backward_bf16(const void* x_chunk, int rows, const gc_mlp_params* w, const float* cached_grad_rows,
@@ -1291,13 +1523,13 @@ int gc_chunk_surrogate_backward_bf16(const void* x_chunk, int rows, const gc_mlp
   if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < carve_mlp_ws(nullptr, rows, w).total)
     return GC_ERR_WORKSPACE;
   const MlpWs ws = carve_mlp_ws((char*)workspace, rows, w);
-  if (mlp_prepare(w, ws, (hipStream_t)stream) != hipSuccess) return GC_ERR_HIP;
-  return mlp_backward(x_chunk, rows, w, cached_grad_rows, acc, ws, (hipStream_t)stream) == hipSuccess ? GC_OK : GC_ERR_HIP;
+  const BackwardRows r{x_chunk, cached_grad_rows, rows}, none{nullptr, nullptr, 0};
+  return mlp_backward(r, none, w, acc, ws, true, (hipStream_t)stream) == hipSuccess ? GC_OK : GC_ERR_HIP;
 }
 
 size_t gc_step_mlp_grouped_workspace_bytes(int B, int P, int chunk_q, int chunk_p, const gc_mlp_params* w, int accumulate_group) {
   if (B < 1 || P < 1 || chunk_q < 1 || chunk_p < 1 || accumulate_group < 1 || check_mlp_params(w) != GC_OK) return 0;
-  return plan_step(B, P, chunk_q, chunk_p, w, accumulate_group).total;
+  return plan_step(B, P, chunk_q, chunk_p, w).total;
 }
 size_t gc_step_mlp_workspace_bytes(int B, int P, int chunk_q, int chunk_p, const gc_mlp_params* w) {
   return gc_step_mlp_grouped_workspace_bytes(B, P, chunk_q, chunk_p, w, 1);
@@ -1321,13 +1553,13 @@ int gc_step_mlp_grouped_bf16(const void* x_q, int B, const void* x_p, int P, con
   if (rc != GC_OK) return rc;
   if (B < 1 || P < 1 || chunk_q < 1 || chunk_p < 1 || B > (1 << 24) || P > (1 << 24)) return GC_ERR_SHAPE;
   if (!(scale > 0.f) || !(temp > 0.f) || !(scale / temp > 0.f) || !(scale / temp < 3.0e38f)) return GC_ERR_SHAPE;
-  const StepWs sw = plan_step(B, P, chunk_q, chunk_p, w, accumulate_group);
+  const StepWs sw = plan_step(B, P, chunk_q, chunk_p, w);
   if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < sw.total) return GC_ERR_WORKSPACE;
   StepCall c;
   memset(&c, 0, sizeof(c));  // the struct is compared bytewise: no stray padding
   c.x_q = x_q; c.x_p = x_p; c.pos_idx = pos_idx; c.B = B; c.P = P; c.chunk_q = chunk_q; c.chunk_p = chunk_p;
   c.w = *w; c.scale = scale; c.temp = temp; c.loss = loss; c.grads = *grads; c.q_rep = q_rep; c.p_rep = p_rep;
-  c.dq = dq; c.dp = dp; c.workspace = workspace; c.group = accumulate_group;
+  c.dq = dq; c.dp = dp; c.workspace = workspace;
   return run_step(c, (hipStream_t)stream);
 }
 

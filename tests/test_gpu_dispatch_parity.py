@@ -147,3 +147,22 @@ def test_capture_with_the_library_buffer_too_small_for_the_packed_inputs():
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     r = subprocess.run([sys.executable, "-c", CAPTURE % root], capture_output=True, text=True, timeout=100)
     assert r.returncode == 0 and "replays agree" in r.stdout, r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("rows,din,dh,dout", [(33, 192, 128, 128), (96, 64, 384, 256), (127, 128, 256, 128), (128, 320, 256, 128),
+                                              (129, 128, 256, 128), (300, 192, 384, 256), (1500, 64, 128, 128)])
+def test_chunk_backward_row_edges(rows, din, dh, dout):
+    """The 32-row tiles and the 64-row tiles of the backward, whole and ragged; inputs of an odd number of 64 columns."""
+    from oracle import gc_oracle as O
+    x, _, _, params = synth.mlp_problem(rows, 1, din, dh, dout, seed=4700 + rows)
+    u = torch.from_numpy((np.random.default_rng(rows).standard_normal((rows, dout)) * 1e-3).astype(np.float32))
+    want = O.mlp_backward(synth.widen(x), {k: synth.widen(v) for k, v in params.items()}, synth.widen(u))
+    dev = {k: v.to(DEV) for k, v in params.items()}
+    grads = {k: torch.full(v.shape, 0.25, dtype=torch.float32, device=DEV) for k, v in params.items()}   # added to
+    gc.gc_chunk_surrogate_backward_bf16(x.to(DEV), dev, u.to(DEV), grads)
+    torch.cuda.synchronize()
+    for k in ("W1", "b1", "W2", "b2"):
+        got = to_np(grads[k]) - 0.25
+        # 0.25 + g is stored in fp32: half an ulp of the sum beside the arithmetic
+        check("backward rows=%d %dx%dx%d d%s" % (rows, din, dh, dout, k), max(0.0, np.abs(got - want[k]).max() - 2.0 ** -25),
+              TOL_BF16 * np.abs(want[k]).max())
