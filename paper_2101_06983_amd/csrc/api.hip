@@ -29,7 +29,7 @@ int num_cu() {
   return cached;
 }
 
-static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent, int route, int max_splits) {
+static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent, int route, int max_splits, bool few, double parts_limit) {
   LossPlan pl{};
   const int kNumCU = num_cu();
   pl.route = route;
@@ -37,32 +37,61 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
   if (route == ROUTE_PLANES) {
     plan_planes(pl, B, P, d, dt, max_splits);
   } else if (pl.use_mfma) {
-    const int n_ablk = ceil_div(B, 256), tiles = ceil_div(P, 256);
-    // d = 128 has a statistics kernel of 256 threads, two workgroups to a CU
-    int splits = ceil_div(d == 128 ? 2 * kNumCU : kNumCU, n_ablk);
-    if (splits > 64) splits = 64;  // the merge kernel combines at most 64 splits per anchor
-    if (splits > tiles) splits = tiles;
-    if (splits < 1) splits = 1;
-    pl.stat_cols_per_split = ceil_div(tiles, splits) * 256;
-    pl.stat_splits = ceil_div(P, pl.stat_cols_per_split);
-    // gradient pass: one workgroup per CU, equal streamed length for both roles
+    if (few && (long long)B * P <= (1ll << 20)) {   // where the line lies: see stats_small_kernel
+      pl.stat_tile = kStatTile;
+      const int tiles = ceil_div(P, kStatTile), per = ceil_div(tiles, 64);   // the merge kernel combines at most 64 splits
+      pl.stat_cols_per_split = per * kStatTile;
+      pl.stat_splits = ceil_div(tiles, per);
+    } else {
+      const int n_ablk = ceil_div(B, 256), tiles = ceil_div(P, 256);
+      // d = 128 has a statistics kernel of 256 threads, two workgroups to a CU
+      int splits = ceil_div(d == 128 ? 2 * kNumCU : kNumCU, n_ablk);
+      if (splits > 64) splits = 64;
+      if (splits > tiles) splits = tiles;
+      if (splits < 1) splits = 1;
+      pl.stat_cols_per_split = ceil_div(tiles, splits) * 256;
+      pl.stat_splits = ceil_div(P, pl.stat_cols_per_split);
+    }
     const int own = (d == 128) ? 256 : 64;   // owner rows per workgroup of the gradient kernel for this width
     const long long obQ = ceil_div(B, own), obP = ceil_div(P, own);
     // NT-Xent on these kernels is one walk (the score matrix is symmetric: see launch_grad_mfma)
     pl.one_walk = ntxent ? 1 : 0;
-    const long long W = pl.one_walk ? obQ * P : obQ * P + obP * B;
-    long long L = (W + kNumCU - 1) / kNumCU;
-    if (L < 256) L = 256;
-    L = (L + 31) / 32 * 32;
-    auto split_of = [&](int n, int& ns, int& len) {
-      ns = (int)((n + L - 1) / L);
-      if (ns > 16) ns = 16;
-      if (ns < 1) ns = 1;
-      len = (ceil_div(n, ns) + 31) / 32 * 32;
-      ns = ceil_div(n, len);
+    // Gradient pass: every workgroup streams about the same number of rows, L.  Its time is ceil(workgroups / CUs) rounds (a
+    // compute unit holds one, of the d = 256 kernel two) of a fixed part and a part per streamed row, and every split of an output is a partial that is
+    // written and read again.  The splits that make L and the rounds come out even are tried: an equal share of the rows
+    // per compute unit can give a few workgroups more than there are CUs, and with them a second round (258 workgroups
+    // at 1021 x 4099 x 384: 46 us, 29 with 242), and few scores leave the CUs idle (6 workgroups at 128 x 256 x 768: 21 us,
+    // 15.6 with 32).
+    // Measured: 14 us and 0.03 to 0.05 us per row at d = 768, 0.03 at d = 128; partials about 4 TB/s.
+    // (Two workgroups of the d = 256 kernel share a compute unit, each at some 70 % of its speed.)
+    const double row_us = d == 128 ? 0.031 : 0.015 + 0.035 * d / 768.0;
+    const int per_cu = d == 256 ? 2 : 1;
+    auto len_of = [](int n, int ns) { return (ceil_div(n, ns) + 31) / 32 * 32; };
+    auto parts_bytes = [&](int nsq, int nsp) { return ((double)nsq * B + (double)nsp * P) * d * 4; };
+    double best_us = 0;
+    auto consider = [&](int L, bool walk_q, bool walk_p, int& bq, int& lq, int& bp, int& lp) {
+      const int nsq = walk_q ? (ceil_div(P, L) > 16 ? 16 : ceil_div(P, L)) : 0, nsp = walk_p ? (ceil_div(B, L) > 16 ? 16 : ceil_div(B, L)) : 0;
+      const int q = walk_q ? len_of(P, nsq) : 0, p = walk_p ? len_of(B, nsp) : 0;
+      const long long n = (walk_q ? obQ * ceil_div(P, q) : 0) + (walk_p ? obP * ceil_div(B, p) : 0);
+      const double parts = parts_bytes(walk_q ? ceil_div(P, q) : 0, walk_p ? ceil_div(B, p) : 0);
+      const double both = n > kNumCU && per_cu == 2 ? 1.4 : 1.0;
+      const double us = (double)((n + per_cu * kNumCU - 1) / (per_cu * kNumCU)) * (14.0 + row_us * both * (q > p ? q : p)) + 2.0 * parts / 4e6;
+      if (parts <= parts_limit && (best_us == 0 || us < best_us)) {
+        best_us = us;
+        if (walk_q) { bq = ceil_div(P, q); lq = q; }
+        if (walk_p) { bp = ceil_div(B, p); lp = p; }
+      }
     };
-    split_of(P, pl.nsq, pl.q_stream_len);
-    split_of(B, pl.nsp, pl.p_stream_len);
+    auto search = [&](bool walk_q, bool walk_p, int& bq, int& lq, int& bp, int& lp) {
+      best_us = 0;
+      for (int ns = 1; ns <= 16; ns++) {
+        if (walk_q) consider(len_of(P, ns), walk_q, walk_p, bq, lq, bp, lp);
+        if (walk_p) consider(len_of(B, ns), walk_q, walk_p, bq, lq, bp, lp);
+      }
+      if (best_us == 0) consider(B > P ? len_of(B, 1) : len_of(P, 1), walk_q, walk_p, bq, lq, bp, lp);
+    };
+    pl.nsq = pl.nsp = 1; pl.q_stream_len = len_of(P, 1); pl.p_stream_len = len_of(B, 1);
+    search(true, !pl.one_walk, pl.nsq, pl.q_stream_len, pl.nsp, pl.p_stream_len);
     if (pl.one_walk) { pl.nsp = 1; pl.p_stream_len = B; }
     // fused mode (workspace is planned for it wherever it can run; fused_auto says where it is also the faster one):
     // each walk is a launch of its own and has to fill the GPU alone
@@ -73,17 +102,14 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
     pl.fused = (d >= 256 && !ntxent) ? 1 : 0;
     pl.fused_auto = (pl.fused && d >= 384 && (long long)B * P >= (1ll << 24)) ? 1 : 0;
     if (pl.fused) {
-      auto split_alone = [&](long long own_blocks, int n, int& ns, int& len) {
-        long long La = (own_blocks * n + kNumCU - 1) / kNumCU;
-        if (La < 256) La = 256;
-        ns = (int)((n + La - 1) / La);
-        if (ns > 16) ns = 16;
-        if (ns < 1) ns = 1;
-        len = (ceil_div(n, ns) + 31) / 32 * 32;
-        ns = ceil_div(n, len);
-      };
-      split_alone(obQ, P, pl.fz_nsq, pl.fz_q_stream_len);
-      split_alone(obP, B, pl.fz_nsp, pl.fz_p_stream_len);
+      // (where only a flag asks for it, the splits, and so the workspace, of the other sequence)
+      pl.fz_nsq = pl.nsq; pl.fz_q_stream_len = pl.q_stream_len;
+      pl.fz_nsp = pl.nsp; pl.fz_p_stream_len = pl.p_stream_len;
+      int unused = 0;
+      if (pl.fused_auto) {
+        search(true, false, pl.fz_nsq, pl.fz_q_stream_len, unused, unused);
+        search(false, true, unused, unused, pl.fz_nsp, pl.fz_p_stream_len);
+      }
     }
   } else {
     const int blocks = ceil_div(B, 16), tiles = ceil_div(P, 16);
@@ -139,16 +165,44 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
 }
 // what the packed inputs and partials may take without being asked about (the rest of a 288 GB card is the caller's)
 constexpr size_t kPlanesMaxBytes = (size_t)32 << 30;
-LossPlan make_loss_plan(int B, int P, int d, gc_dtype dt, bool ntxent, size_t limit) {
-  if (dt == GC_BF16 && d % 128 == 0 && d >= 128 && d <= 768) return make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_MFMA, 16);
+static LossPlan plan_afresh(int B, int P, int d, gc_dtype dt, bool ntxent, size_t limit) {
+  if (dt == GC_BF16 && d % 128 == 0 && d >= 128 && d <= 768) {
+    LossPlan pl = make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_MFMA, 16, true, 1e300);
+    if (pl.total > (size_t)GC_STATIC_SCRATCH_BYTES) {
+      // the shapes that the entry point with the fixed array takes do not depend on the splits: those that fit with an
+      // equal share of the rows per compute unit, at least 256 of them, get splits that fit
+      const int own = (d == 128) ? 256 : 64;
+      const long long obQ = ceil_div(B, own), obP = ceil_div(P, own), W = obQ * P + (ntxent ? 0 : obP * B);
+      long long L = (W + num_cu() - 1) / num_cu();
+      L = L < 256 ? 256 : (L + 31) / 32 * 32;
+      const double limit = ((double)((P + L - 1) / L) * B + (double)((B + L - 1) / L) * P) * d * 4;
+      const LossPlan lean = make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_MFMA, 16, false, limit);
+      if (lean.total <= (size_t)GC_STATIC_SCRATCH_BYTES) {
+        const LossPlan both = make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_MFMA, 16, true, limit);
+        return both.total <= (size_t)GC_STATIC_SCRATCH_BYTES ? both : lean;
+      }
+    }
+    return pl;
+  }
   // a handful of scores: the five launches of the planes cost more than the four of the general kernels (30 against 29 us
   // at 8 x 16 x 64)
   const bool tiny = (long long)B * P * d <= (1ll << 14);
   for (int splits = 16; splits >= 1 && !tiny; splits /= 2) {
-    const LossPlan pl = make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_PLANES, splits);
+    const LossPlan pl = make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_PLANES, splits, false, 0.);
     if (pl.total <= limit && pl.total <= kPlanesMaxBytes) return pl;
   }
-  return make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_GENERAL, 1);
+  return make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_GENERAL, 1, false, 0.);
+}
+
+// A plan depends on nothing but these arguments; the last one of a thread is kept (the search over the splits is some
+// microseconds of host time, and a program asks for the same plan call after call).
+LossPlan make_loss_plan(int B, int P, int d, gc_dtype dt, bool ntxent, size_t limit) {
+  static thread_local struct { int B = 0, P, d; gc_dtype dt; bool ntxent; size_t limit; LossPlan pl; } last;
+  if (last.B != B || last.P != P || last.d != d || last.dt != dt || last.ntxent != ntxent || last.limit != limit) {
+    last.pl = plan_afresh(B, P, d, dt, ntxent, limit);
+    last.B = B; last.P = P; last.d = d; last.dt = dt; last.ntxent = ntxent; last.limit = limit;
+  }
+  return last.pl;
 }
 
 static bool shape_ok(int B, int P, int d) {

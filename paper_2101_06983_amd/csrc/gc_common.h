@@ -53,6 +53,7 @@ struct LossPlan {
   int one_walk;          // NT-Xent on the MFMA kernels: dz from a single walk (no dP role, no dP partials)
   int stat_splits;       // column (target) ranges of the statistics pass
   int stat_cols_per_split;
+  int stat_tile;         // ROUTE_MFMA: 0 = the 256 x 256 (d = 128: 256-anchor) kernels, else the kernel for few scores (kStatTile)
   int nsq, nsp;          // stream splits of the dQ-role / dP-role workgroups of the gradient pass
   int q_stream_len, p_stream_len;  // stream rows per split (multiple of the stream tile)
   int b_pad;             // B rounded up to 64: length of the padded lse2 / pos_pad arrays
@@ -71,6 +72,7 @@ struct LossPlan {
 
 // limit: bytes of workspace there are.  The calls of ROUTE_PLANES take fewer splits, and then ROUTE_GENERAL, to stay below
 // it (the sequence of the other route does not depend on it: the caller compares `total`).
+constexpr int kStatTile = 32;
 LossPlan make_loss_plan(int B, int P, int d, gc_dtype dt, bool ntxent, size_t limit = (size_t)-1);
 void plan_planes(LossPlan& pl, int B, int P, int d, gc_dtype dt, int max_splits);
 

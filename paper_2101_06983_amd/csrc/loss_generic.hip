@@ -261,15 +261,17 @@ __device__ __forceinline__ void add_row4(f32x4& acc, float c, const unsigned sho
 #pragma unroll
   for (int k = 0; k < 4; k++) acc[k] += c * bf2f((unsigned short)v[k]);
 }
-// Some target is the positive of several anchors: every anchor that names one of the rows of this workgroup's 1024
-// elements, in index order.  The workgroup looks through the anchors together, 256 at a time, and keeps the matches (in
-// index order: ballot and prefix inside a wave, waves one after the other) in LDS; each thread then adds those of its
-// own row.  (A scan by every thread for itself took 179 of the 253 us of a call with B = 1021, P = 4099, d = 384; the
-// list takes that launch to 8 us.  Rows that no anchor names, the most of them, are skipped.)
-__device__ __forceinline__ void add_shared_positives(f32x4& acc, const PosFix& fx, size_t n4, unsigned block, int row, int col, bool live,
-                                                     int* list /* [256] in LDS */, int* cnt /* [4] */) {
-  const size_t first = (size_t)block * 256, last = first + 255 < n4 ? first + 255 : n4 - 1;
-  const int row0 = (int)(first * 4 / (size_t)fx.d), row1 = (int)((last * 4 + 3) / (size_t)fx.d);
+// What a workgroup of the sum kernel keeps of up to 256 anchors that share a target: the anchor, its target and coefficient
+struct SharedList { int anchor[256]; int row[256]; float c[256]; int cnt[4]; };
+// Some target is the positive of several anchors: every anchor that names one of the rows of this workgroup's elements
+// (first .. last), in index order.  The workgroup looks through the anchors together, 256 at a time, and keeps the matches
+// with their coefficients (in index order: ballot and prefix inside a wave, waves one after the other) in LDS; each thread
+// then adds those of its own rows, eight loads in flight.  (A scan by every thread for itself took 179 of the 253 us of a
+// call with B = 1021, P = 4099, d = 384, and 1.0 ms where 2700 anchors share one target of 300.)  Workgroups none of whose
+// rows is named, the most of them, are done at once.
+__device__ __forceinline__ void add_shared_positives(f32x4& acc, const PosFix& fx, size_t first, size_t last, int row, int col, bool live,
+                                                     SharedList& list) {
+  const int row0 = (int)(first / (size_t)fx.d), row1 = (int)(last / (size_t)fx.d);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   bool named = false;
   if (live) {   // the merge records one of the anchors of every named target (whatever the workspace held, if none: checked)
@@ -282,82 +284,75 @@ __device__ __forceinline__ void add_shared_positives(f32x4& acc, const PosFix& f
     const int r = i < fx.B ? fx.pos[i] : -1;
     const bool match = r >= row0 && r <= row1;
     const unsigned long long mask = __builtin_amdgcn_ballot_w64(match);
-    if (lane == 0) cnt[w] = __builtin_popcountll(mask);
+    if (lane == 0) list.cnt[w] = __builtin_popcountll(mask);
     __syncthreads();
     int base = 0;
-    for (int k = 0; k < w; k++) base += cnt[k];
-    const int total = cnt[0] + cnt[1] + cnt[2] + cnt[3];
-    if (match) list[base + __builtin_popcountll(mask & ((1ull << lane) - 1ull))] = i;
+    for (int k = 0; k < w; k++) base += list.cnt[k];
+    const int total = list.cnt[0] + list.cnt[1] + list.cnt[2] + list.cnt[3];
+    if (match) {
+      const int at = base + __builtin_popcountll(mask & ((1ull << lane) - 1ull));
+      list.anchor[at] = i; list.row[at] = r; list.c[at] = pos_coeff(fx, i, r);
+    }
     __syncthreads();
-    for (int k = 0; k < total; k++) {
-      const int a = list[k];
-      if (live && fx.pos[a] == row) add_row4(acc, pos_coeff(fx, a, row), fx.other + (size_t)a * fx.d, col);
+    constexpr int FLY = 8;
+    for (int k0 = 0; k0 < total; k0 += FLY) {
+      s16x4 o[FLY];
+#pragma unroll
+      for (int k = 0; k < FLY; k++) {
+        o[k] = s16x4{0, 0, 0, 0};
+        if (k0 + k < total && live && list.row[k0 + k] == row) o[k] = *(const s16x4*)(fx.other + (size_t)list.anchor[k0 + k] * fx.d + col);
+      }
+#pragma unroll
+      for (int k = 0; k < FLY; k++)
+        if (k0 + k < total && live && list.row[k0 + k] == row) {
+          const float c = list.c[k0 + k];
+#pragma unroll
+          for (int e = 0; e < 4; e++) acc[e] += c * bf2f((unsigned short)o[k][e]);
+        }
     }
     __syncthreads();   // the list and the counts are free again
   }
 }
-__global__ void __launch_bounds__(256) partial_reduce_kernel(ReduceArgs a) {
-  __shared__ float red[1024];
-  __shared__ int cnt[4];
+// Four elements per thread.  Bound by memory: 88 MB in 16 us for the dP sums of 4096 x 8192 x 768, most of it out of the
+// memory-side cache, with eight waves per SIMD (18.5 us with six or with 8 elements per thread).
+// (JOBS = 1: every argument sits at a known place, so they are all loaded at once; picking one of two costs 2 us here.)
+template <int JOBS>
+__global__ void __launch_bounds__(256, 8) partial_reduce_kernel(ReduceArgs a) {
+  __shared__ union { float red[1024]; SharedList list; } lds;
   unsigned block = blockIdx.x;
   if (a.ls.rowloss) {
     if (block == 0) {
-      loss_sum_block<256>(a.ls, red);
+      loss_sum_block<256>(a.ls, lds.red);
       return;
     }
     block--;
   }
-  const bool second = block >= a.blocks0;
+  const bool second = JOBS > 1 && block >= a.blocks0;
   if (second) block -= a.blocks0;
   const ReduceJob& j = second ? a.job[1] : a.job[0];
   const PosFix& fx = j.fix;
-  const size_t e = (size_t)block * 256 + threadIdx.x, n4 = (j.n + 3) / 4;
+  const size_t n4 = (j.n + 3) / 4, e0 = (size_t)block * 256, e = e0 + threadIdx.x;
   const bool live = e < n4;
-  // The loads of the positive's term depend on each other three deep (anchor, its statistics, its row): they are issued
-  // around those of the first partials, so that a workgroup waits for memory about twice and not five times.
-  int row = 0, col = 0, pi = -1, shared = 0;
-  if (fx.mode && live) {   // (d is a multiple of 4 here)
-    const size_t first = (size_t)block * 1024;   // the same in every thread: the 64-bit division runs on the scalar unit
-    const unsigned row0 = (unsigned)(first / (unsigned)fx.d), off = (unsigned)(first - (size_t)row0 * (unsigned)fx.d) + 4 * threadIdx.x;
-    row = (int)(row0 + off / (unsigned)fx.d);
-    col = (int)(off % (unsigned)fx.d);
-    pi = fx.mode == 1 ? fx.pos[row] : fx.inv[row];   // inv: whatever the workspace held if no anchor names this target
-  }
-  if (fx.mode == 2) shared = *fx.shared;
-  f32x4 v[4];
-#pragma unroll
-  for (int k = 0; k < 4; k++) {
-    v[k] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (live && k < j.count[0]) v[k] = ((const f32x4*)(j.ptr[0] + (size_t)k * j.stride[0]))[e];
-  }
-  // anchor and target of the positive's term, and whether this element has one
-  int fi = row, fr = pi;
-  bool fix = false;
-  if (fx.mode == 1) {
-    fix = pi >= 0 && pi < fx.P;
-  } else if (fx.mode == 2) {
-    fi = pi; fr = row;
-    fix = shared == 0 && pi >= 0 && pi < fx.B && fx.pos[pi] == row;   // checked
-  }
-  float c = 0.f;
-  s16x4 other = {0, 0, 0, 0};
-  if (fix) {
-    other = *(const s16x4*)(fx.other + (size_t)(fx.mode == 1 ? fr : fi) * fx.d + col);
-    c = pos_coeff(fx, fi, fr);
-  }
-  f32x4 acc = v[0];
-#pragma unroll
-  for (int k = 1; k < 4; k++)
-    if (k < j.count[0]) acc += v[k];
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   if (live) {   // (partials have room for whole vectors)
-    for (int s = 0; s < j.nsrc; s++)
-      for (int k = s == 0 ? 4 : 0; k < j.count[s]; k++) acc += ((const f32x4*)(j.ptr[s] + (size_t)k * j.stride[s]))[e];
+    for (int k = 0; k < j.count[0]; k++) acc += ((const f32x4*)(j.ptr[0] + (size_t)k * j.stride[0]))[e];
+    if (j.nsrc > 1)
+      for (int k = 0; k < j.count[1]; k++) acc += ((const f32x4*)(j.ptr[1] + (size_t)k * j.stride[1]))[e];
   }
-  if (fix) {   // the positive's term, in fp32, after the partials
-#pragma unroll
-    for (int k = 0; k < 4; k++) acc[k] += c * bf2f((unsigned short)other[k]);
+  if (fx.mode) {   // the positive's term, in fp32, after the partials (d is a multiple of 4 here)
+    const size_t first = e0 * 4;   // the same in every thread: the 64-bit division runs on the scalar unit
+    const unsigned row0 = (unsigned)(first / (unsigned)fx.d), off = (unsigned)(first - (size_t)row0 * (unsigned)fx.d) + 4 * threadIdx.x;
+    const int row = (int)(row0 + off / (unsigned)fx.d), col = (int)(off % (unsigned)fx.d);
+    if (fx.mode == 1) {
+      const int r = live ? fx.pos[row] : -1;
+      if (r >= 0 && r < fx.P) add_row4(acc, pos_coeff(fx, row, r), fx.other + (size_t)r * fx.d, col);
+    } else if (*fx.shared == 0) {
+      const int i = live ? fx.inv[row] : -1;   // whatever the workspace held if no anchor names this target: checked
+      if (i >= 0 && i < fx.B && fx.pos[i] == row) add_row4(acc, pos_coeff(fx, i, row), fx.other + (size_t)i * fx.d, col);
+    } else {
+      add_shared_positives(acc, fx, first, (e0 + 256 < n4 ? e0 + 256 : n4) * 4 - 1, row, col, live, lds.list);
+    }
   }
-  if (shared) add_shared_positives(acc, fx, n4, block, row, col, live, (int*)red, cnt);
   if (!live) return;
   if (4 * e + 4 <= j.n && j.vec) {
     if (j.out_bf16) {
@@ -490,10 +485,11 @@ hipError_t launch_reduce_jobs(const ReduceJob* jobs, int njobs, hipStream_t stre
     if (jobs[k].fix.mode && (jobs[k].n % 4 || jobs[k].fix.d % 4)) return hipErrorInvalidValue;   // rows of whole vectors only
     blocks[k] = (unsigned)(((jobs[k].n + 3) / 4 + 255) / 256);
   }
-  a.blocks0 = blocks[0];
   if (loss_of) a.ls = loss_sum_of(*loss_of, *pl);
+  a.blocks0 = blocks[0];
   const unsigned n = blocks[0] + blocks[1] + (loss_of ? 1 : 0);
-  if (n) partial_reduce_kernel<<<dim3(n), 256, 0, stream>>>(a);
+  if (n && njobs > 1) partial_reduce_kernel<2><<<dim3(n), 256, 0, stream>>>(a);
+  else if (n) partial_reduce_kernel<1><<<dim3(n), 256, 0, stream>>>(a);
   return hipGetLastError();
 }
 

@@ -310,8 +310,115 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(const unsigned short* _
   }
 }
 
+// ===========================================================================
+// Statistics pass for few scores: 32 x 32 tiles, the contraction split over the four waves of a workgroup in 64-wide
+// chunks, every operand loaded straight into registers (lane (n, h) takes elements 32 h .. 32 h + 31 of a chunk of its
+// row, so that two lanes use a whole 128-byte line; any order of k works if both operands share it).  The kernel above
+// has 256 x 256 tiles: 23 us for the one workgroup of 128 x 256 scores and 26 us for the eight of 512 x 1024 at d = 768,
+// all latency of twelve dependent k-chunks.  Here a wave has all its loads in flight at once: 6.6 and 9.7 us.  It costs
+// B P d / 8 bytes of L2 traffic, so the larger tiles win again from about 2^20 scores (a version with 64 x 64 tiles took
+// 37 us at 1021 x 4099 x 384, the 256 x 256 kernel 23).
+// ===========================================================================
+struct StatsSmallArgs {
+  const unsigned short* Q; const unsigned short* P; const int32_t* pos_idx;
+  int B, Pn, d, n_ablk, tiles, tiles_per_split, mask_self;
+  float alpha2;
+  float* part_m; float* part_l; int* part_idx; float* pos_t;
+};
+__global__ void __launch_bounds__(256) stats_small_kernel(StatsSmallArgs g) {
+  constexpr int T = kStatTile, PD = 3, PARTS = 256 / T, TP = T / PARTS;   // TP: targets per thread of the epilogue
+  __shared__ float red[4][T][T + 1];                                     // partial tiles of the four waves: [target][anchor]
+  __shared__ float xm[PARTS][T], xl[PARTS][T];                           // per part: maximum, sum, index
+  __shared__ int xi[PARTS][T];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, ln = lane & 31;
+  const int task = xcd_task_id();
+  const int a0 = (task % g.n_ablk) * T, split = task / g.n_ablk;
+  const int nch = g.d / 64;
+  const char* qp = (const char*)(g.Q + (size_t)min(a0 + ln, g.B - 1) * g.d + 32 * h);
+  // epilogue: thread (part, n) takes targets TP part .. of anchor n
+  const int en = tid % T, part = tid / T, a = a0 + en;
+  const int r = a < g.B ? g.pos_idx[a] : -1;
+  float m = -INFINITY, l = 0.f;
+  int best = 0x7fffffff;
+  const int t_end = min(g.tiles, (split + 1) * g.tiles_per_split);
+  for (int t = split * g.tiles_per_split; t < t_end; t++) {
+    const int j0 = t * T;
+    const char* pp = (const char*)(g.P + (size_t)min(j0 + ln, g.Pn - 1) * g.d + 32 * h);
+    u32x4 fq[PD][4], fp[PD][4];
+    auto issue = [&](int slot, int c) __attribute__((always_inline)) {
+#pragma unroll
+      for (int v = 0; v < 4; v++) {
+        fq[slot][v] = *(const u32x4*)(qp + (size_t)c * 128 + 16 * v);
+        fp[slot][v] = *(const u32x4*)(pp + (size_t)c * 128 + 16 * v);
+      }
+    };
+    f32x16 acc;
+#pragma unroll
+    for (int e = 0; e < 16; e++) acc[e] = 0.f;
+#pragma unroll
+    for (int p = 0; p < PD; p++)
+      if (wave + 4 * p < nch) issue(p, wave + 4 * p);
+    for (int base = wave; base < nch; base += 4 * PD) {
+#pragma unroll
+      for (int p = 0; p < PD; p++) {
+        const int c = base + 4 * p;
+        if (c < nch) {
+#pragma unroll
+          for (int v = 0; v < 4; v++) acc = mfma32(__builtin_bit_cast(bf16x8, fp[p][v]), __builtin_bit_cast(bf16x8, fq[p][v]), acc);
+          if (c + 4 * PD < nch) issue(p, c + 4 * PD);
+        }
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 16; e++) red[wave][8 * (e >> 2) + 4 * h + (e & 3)][ln] = acc[e];
+    __syncthreads();
+    float v[TP], mt = -INFINITY;
+    int bt = 0x7fffffff;
+#pragma unroll
+    for (int e = 0; e < TP; e++) {
+      const int row = part * TP + e, j = j0 + row;
+      float x = (((red[0][row][en] + red[1][row][en]) + red[2][row][en]) + red[3][row][en]) * g.alpha2;
+      if (j >= g.Pn || (g.mask_self && j == a)) x = -INFINITY;
+      // (a positive that the self-mask removes has the logit -inf: its row loss is then +inf)
+      if (j == r && j < g.Pn && a < g.B) g.pos_t[a] = x;
+      v[e] = x;
+      if (x > mt) { mt = x; bt = j; }   // strict: the smallest index attaining the maximum
+    }
+    const float mn = fmaxf(m, mt), ms = (mn == -INFINITY) ? 0.f : mn;
+    float s = 0.f;
+#pragma unroll
+    for (int e = 0; e < TP; e++) s += fast_exp2(v[e] - ms);
+    l = l * fast_exp2(m - ms) + s;
+    if (mt > m) best = bt;
+    m = mn;
+    __syncthreads();   // the partial tiles have been read
+  }
+  xm[part][en] = m; xl[part][en] = l; xi[part][en] = best;
+  __syncthreads();
+  if (tid < T && a < g.B) {   // part 0 of every anchor: the others in order
+#pragma unroll
+    for (int k = 1; k < PARTS; k++) stat_merge(m, l, best, xm[k][en], xl[k][en], xi[k][en]);
+    const size_t o = (size_t)split * g.B + a;
+    g.part_m[o] = m; g.part_l[o] = l; g.part_idx[o] = best;
+  }
+}
+static hipError_t launch_stats_small(const LossArgs& a, const LossPlan& pl) {
+  constexpr int T = kStatTile;
+  char* ws = a.ws;
+  StatsSmallArgs g{};
+  g.Q = (const unsigned short*)a.q; g.P = (const unsigned short*)a.p; g.pos_idx = a.pos_idx;
+  g.B = a.B; g.Pn = a.P; g.d = a.d; g.n_ablk = (a.B + T - 1) / T; g.tiles = (a.P + T - 1) / T;
+  g.tiles_per_split = pl.stat_cols_per_split / T; g.mask_self = (a.flags & GC_MASK_SELF) ? 1 : 0;
+  g.alpha2 = a.alpha * kLog2e;
+  g.part_m = (float*)(ws + pl.off_part_m); g.part_l = (float*)(ws + pl.off_part_l); g.part_idx = (int*)(ws + pl.off_part_idx);
+  g.pos_t = (float*)(ws + pl.off_pos);
+  stats_small_kernel<<<g.n_ablk * pl.stat_splits, 256, 0, a.stream>>>(g);
+  return hipGetLastError();
+}
+
 static hipError_t launch_stats128(const LossArgs& a, const LossPlan& pl);
 hipError_t launch_stats_mfma(const LossArgs& a, const LossPlan& pl) {
+  if (pl.stat_tile) return launch_stats_small(a, pl);
   if (a.d == 128) return launch_stats128(a, pl);   // whole anchor rows in registers: a kernel of its own
   char* ws = a.ws;
   const int n_ablk = (a.B + ST_TN - 1) / ST_TN;

@@ -136,11 +136,15 @@ __global__ void __launch_bounds__(256) planes_pack_kernel(PackArgs a) {
 // ---- scores ------------------------------------------------------------------------------------------------------------
 // s[no] += R_tile O_no^T for one 32-row streamed tile (fragments at str, contiguous along k) and NO blocks of 32 owner
 // rows: their first ks_lds k-steps are in LDS (own_lds, [k-step][no][plane]), the rest is loaded (own_glb + no * own_stride).
-// Loads run PD k-steps ahead; k-steps past the end re-read the last one and are not used.  KS and ks_lds: multiples of 4.
-template <int NP, int NO>
+// A wave is alone on its SIMD or with one other, so the latency of L2 is hidden by loads in flight only: PD k-steps ahead,
+// 16 KB (12 KB for three planes; with half of that the fp32 call of 512 x 1024 scores at d = 768 took 77 us and not 69).
+// k-steps past the end re-read the last one and are not used.
+// ks_lds: a multiple of PD, or KS.
+// (The gradient kernel has its accumulators beside them: 8 KB for one plane.)
+constexpr int planes_pd(int NP, bool grad) { return NP == 1 ? (grad ? 8 : 16) : 4; }
+template <int NP, int NO, int PD>
 __device__ __forceinline__ void planes_scores(const unsigned short* str, const unsigned short* own_lds, const unsigned short* own_glb,
                                               size_t own_stride, int KS, int ks_lds, f32x16 (&s)[NO]) {
-  constexpr int PD = NP == 1 ? 4 : 2;
   const int lane = threadIdx.x & 63;
   str += lane * 8; own_lds += lane * 8; own_glb += lane * 8;
   auto products = [&](const bf16x8 (&r)[NP], const bf16x8 (&o)[NP], f32x16& acc) __attribute__((always_inline)) {
@@ -155,23 +159,26 @@ __device__ __forceinline__ void planes_scores(const unsigned short* str, const u
     for (int n = 0; n < NP; n++) rf[slot][n] = *(const bf16x8*)(str + ((size_t)ks * NP + n) * 512);
   };
 #pragma unroll
-  for (int p = 0; p < PD; p++) load_r(p, p);
+  for (int p = 0; p < PD; p++) load_r(p, min(p, KS - 1));
   for (int k0 = 0; k0 < ks_lds; k0 += PD) {
 #pragma unroll
     for (int p = 0; p < PD; p++) {
       const int ks = k0 + p;
+      if (ks < ks_lds) {   // uniform; false only behind the last k-step
 #pragma unroll
-      for (int no = 0; no < NO; no++) {
-        bf16x8 o[NP];
+        for (int no = 0; no < NO; no++) {
+          bf16x8 o[NP];
 #pragma unroll
-        for (int n = 0; n < NP; n++) o[n] = *(const bf16x8*)(own_lds + ((ks * NO + no) * NP + n) * 512);
-        products(rf[p], o, s[no]);
+          for (int n = 0; n < NP; n++) o[n] = *(const bf16x8*)(own_lds + ((ks * NO + no) * NP + n) * 512);
+          products(rf[p], o, s[no]);
+        }
+        load_r(p, min(ks + PD, KS - 1));
       }
-      load_r(p, min(ks + PD, KS - 1));
     }
   }
   if (ks_lds < KS) {
-    bf16x8 of[PD][NO][NP];
+    constexpr int PO = NP == 1 ? 8 : 2;   // (PD is a multiple: the ring slots of both loops agree)
+    bf16x8 of[PO][NO][NP];
     auto load_o = [&](int slot, int ks) __attribute__((always_inline)) {
 #pragma unroll
       for (int no = 0; no < NO; no++)
@@ -179,15 +186,17 @@ __device__ __forceinline__ void planes_scores(const unsigned short* str, const u
         for (int n = 0; n < NP; n++) of[slot][no][n] = *(const bf16x8*)(own_glb + no * own_stride + ((size_t)ks * NP + n) * 512);
     };
 #pragma unroll
-    for (int p = 0; p < PD; p++) load_o(p, ks_lds + p);
+    for (int p = 0; p < PO; p++) load_o(p, min(ks_lds + p, KS - 1));
     for (int k0 = ks_lds; k0 < KS; k0 += PD) {
 #pragma unroll
       for (int p = 0; p < PD; p++) {
         const int ks = k0 + p;
+        if (ks < KS) {
 #pragma unroll
-        for (int no = 0; no < NO; no++) products(rf[p], of[p][no], s[no]);
-        load_r(p, min(ks + PD, KS - 1));
-        load_o(p, min(ks + PD, KS - 1));
+          for (int no = 0; no < NO; no++) products(rf[p], of[p % PO][no], s[no]);
+          load_r(p, min(ks + PD, KS - 1));
+          load_o(p % PO, min(ks + PO, KS - 1));
+        }
       }
     }
   }
@@ -198,11 +207,19 @@ template <int NP, int NO>
 __device__ __forceinline__ void planes_stage_own(unsigned short* own_lds, const unsigned short* own_glb, size_t own_stride, int ks_lds) {
   const int per = ks_lds * NP * 64;   // 16-byte pieces per owner block
 #pragma unroll
-  for (int no = 0; no < NO; no++)
-    for (int q = threadIdx.x; q < per; q += blockDim.x) {
-      const int blk = q >> 6, ks = blk / NP, n = blk % NP;
-      *(u32x4*)(own_lds + ((ks * NO + no) * NP + n) * 512 + (q & 63) * 8) = *(const u32x4*)(own_glb + no * own_stride + (size_t)q * 8);
+  for (int no = 0; no < NO; no++) {
+    const u32x4* src = (const u32x4*)(own_glb + no * own_stride);
+    for (int q0 = threadIdx.x; q0 < per; q0 += 8 * 256) {   // eight loads in flight
+      u32x4 v[8];
+#pragma unroll
+      for (int i = 0; i < 8; i++) v[i] = src[min(q0 + 256 * i, per - 1)];
+#pragma unroll
+      for (int i = 0; i < 8; i++) {
+        const int q = q0 + 256 * i;
+        if (q < per) *(u32x4*)(own_lds + ((((q >> 6) / NP) * NO + no) * NP + (q >> 6) % NP) * 512 + (q & 63) * 8) = v[i];
+      }
     }
+  }
 }
 
 // ---- row statistics ------------------------------------------------------------------------------------------------------
@@ -243,7 +260,7 @@ __global__ void __launch_bounds__(256, 2) planes_stats_kernel(PlanesStatsArgs g)
     for (int no = 0; no < NO; no++)
 #pragma unroll
       for (int r = 0; r < 16; r++) s[no][r] = 0.f;
-    planes_scores<NP, NO>(g.pk + (size_t)t * blk, pl_lds, own, blk, g.KS, g.ks_lds, s);
+    planes_scores<NP, NO, planes_pd(NP, false)>(g.pk + (size_t)t * blk, pl_lds, own, blk, g.KS, g.ks_lds, s);
     const int j0 = t * 32 + 4 * h;   // register r: target j0 + 8 (r / 4) + r % 4, increasing in r
 #pragma unroll
     for (int no = 0; no < NO; no++) {
@@ -352,7 +369,7 @@ __global__ void __launch_bounds__(256, NO == 1 ? 2 : 1) planes_grad_kernel(Plane
     for (int no = 0; no < NO; no++)
 #pragma unroll
       for (int r = 0; r < 16; r++) s[no][r] = 0.f;
-    planes_scores<NP, NO>(R.str_k + (size_t)(t0 / 32 + w) * blk, own_lds, own, blk, g.KS, g.ks_lds, s);
+    planes_scores<NP, NO, planes_pd(NP, true)>(R.str_k + (size_t)(t0 / 32 + w) * blk, own_lds, own, blk, g.KS, g.ks_lds, s);
     const int j0 = t0 + 32 * w + 4 * h;
     float lse_s[16]; int pos_s[16];
     if (ri) {
@@ -389,7 +406,8 @@ __global__ void __launch_bounds__(256, NO == 1 ? 2 : 1) planes_grad_kernel(Plane
     __syncthreads();
     // dO[32 NO x columns] += g[32 NO x 128] R[128 x columns]; the row blocks of the packed copy are full (zero-padded)
     const unsigned short* xt = R.str_t + (size_t)(t0 / 16) * g.CT * NP * 512 + lane * 8;
-    constexpr int PD = NP == 1 ? (CTW < 8 ? CTW : 8) : (CTW < 2 ? CTW : 2);
+    constexpr int MOST = NP == 1 ? 8 : CTW == 8 ? 2 : CTW == 6 ? 3 : 4, PD = CTW < MOST ? CTW : MOST;   // column tiles of loads in flight
+    static_assert(CTW % PD == 0, "the ring of loads starts over at every row step");
     auto src = [&](int kk, int i) __attribute__((always_inline)) -> const unsigned short* {
       return xt + ((size_t)kk * g.CT + min(ct0 + w + 4 * i, g.CT - 1)) * (NP * 512);
     };
@@ -493,6 +511,9 @@ static hipError_t pack_t(const LossArgs& a, const LossPlan& pl) {
   return hipGetLastError();
 }
 
+// k-steps of the owner rows that LDS holds, of `room`: all, or whole turns of the ring of planes_scores
+static int ks_in_lds(int room, int KS, int pd) { return room >= KS ? KS : room / pd * pd; }
+
 template <int NP>
 static hipError_t stats_np(const LossArgs& a, const LossPlan& pl) {
   char* ws = a.ws;
@@ -505,8 +526,7 @@ static hipError_t stats_np(const LossArgs& a, const LossPlan& pl) {
   g.pos_t = (float*)(ws + pl.off_pos);
   const int nwg = g.n_own * (pl.stat_splits / 4);
   const int budget = (nwg <= num_cu() ? 152 : 76) * 1024;
-  g.ks_lds = budget / (NP * 1024) / 4 * 4;
-  if (g.ks_lds > g.KS) g.ks_lds = g.KS;
+  g.ks_lds = ks_in_lds(budget / (NP * 1024), g.KS, planes_pd(NP, false));
   static bool done[64];
   if (hipError_t e = ensure_dyn_lds((const void*)planes_stats_kernel<NP, 1>, 160 * 1024, done); e != hipSuccess) return e;
   planes_stats_kernel<NP, 1><<<nwg, 256, g.ks_lds * NP * 1024, a.stream>>>(g);
@@ -522,8 +542,7 @@ hipError_t launch_stats_planes(const LossArgs& a, const LossPlan& pl) {
 template <int NP, int NO, int CTW>
 static hipError_t grad_launch(PlanesGradArgs& g, int nwg, hipStream_t s) {
   const int budget = ((nwg <= num_cu() || NO == 2) ? 156 : 78) * 1024 - planes_g_bytes(NO);
-  g.ks_lds = budget / (NO * NP * 1024) / 4 * 4;
-  if (g.ks_lds > g.KS) g.ks_lds = g.KS;
+  g.ks_lds = ks_in_lds(budget / (NO * NP * 1024), g.KS, planes_pd(NP, true));
   static bool done[64];
   if (hipError_t e = ensure_dyn_lds((const void*)planes_grad_kernel<NP, NO, CTW>, 160 * 1024, done); e != hipSuccess) return e;
   planes_grad_kernel<NP, NO, CTW><<<nwg, 256, planes_g_bytes(NO) + g.ks_lds * NO * NP * 1024, s>>>(g);
