@@ -184,10 +184,8 @@ static LossPlan plan_afresh(int B, int P, int d, gc_dtype dt, bool ntxent, size_
     }
     return pl;
   }
-  // a handful of scores: the five launches of the planes cost more than the four of the general kernels (30 against 29 us
-  // at 8 x 16 x 64)
-  const bool tiny = (long long)B * P * d <= (1ll << 14);
-  for (int splits = 16; splits >= 1 && !tiny; splits /= 2) {
+  if (tiny_fits(B, P, d)) return make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_TINY, 1, false, 0.);
+  for (int splits = 16; splits >= 1; splits /= 2) {
     const LossPlan pl = make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_PLANES, splits, false, 0.);
     if (pl.total <= limit && pl.total <= kPlanesMaxBytes) return pl;
   }
@@ -317,6 +315,12 @@ static int run_loss(const LossArgs& a_in, const LossPlan& pl) {
   const int call = g_prof.calls;
   prof_mark(call, 0, a.stream);
   hipError_t e;
+  if (pl.route == ROUTE_TINY) {   // everything is the first phase
+    if (launch_loss_tiny(a, pl) != hipSuccess) return GC_ERR_HIP;
+    for (int mark = 1; mark < kMarks; mark++) prof_mark(call, mark, a.stream);
+    if (g_prof.on) g_prof.calls++;
+    return GC_OK;
+  }
   const bool want_online = (a.flags & GC_PATH_ONLINE) || (pl.fused_auto && !(a.flags & GC_PATH_STATS_PASS));
   if (pl.fused && want_online && a.dq && !a.dz && !a.lse2_t) {
     // fused mode: online-statistics dQ walk | merge of its splits (lse2, row losses, dQ) | dP walk | partial sums

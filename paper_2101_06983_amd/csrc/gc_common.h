@@ -45,7 +45,8 @@ __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_lo
 enum LossRoute {
   ROUTE_MFMA = 0,     // loss_mfma.hip: bf16, d a multiple of 128 up to 768
   ROUTE_PLANES = 1,   // loss_planes.hip: fp32 storage, and bf16 of any other width
-  ROUTE_GENERAL = 2   // loss_generic.hip: the same calls where the workspace is limited and the planes do not fit
+  ROUTE_GENERAL = 2,  // loss_generic.hip: the same calls where the workspace is limited and the planes do not fit
+  ROUTE_TINY = 3      // loss_generic.hip: the same calls with a handful of scores, in one launch of one workgroup
 };
 struct LossPlan {
   int route;
@@ -129,6 +130,8 @@ struct PosFix {
 // kernel-launching halves (one per .hip file)
 hipError_t launch_stats_generic(const LossArgs& a, const LossPlan& pl);
 hipError_t launch_grad_generic(const LossArgs& a, const LossPlan& pl);
+hipError_t launch_loss_tiny(const LossArgs& a, const LossPlan& pl);      // the whole call
+bool tiny_fits(int B, int P, int d);
 hipError_t launch_stats_planes(const LossArgs& a, const LossPlan& pl);   // packs the inputs first
 hipError_t launch_grad_planes(const LossArgs& a, const LossPlan& pl);
 hipError_t launch_stats_mfma(const LossArgs& a, const LossPlan& pl);

@@ -335,7 +335,15 @@ __global__ void __launch_bounds__(256, 8) partial_reduce_kernel(ReduceArgs a) {
   const bool live = e < n4;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   if (live) {   // (partials have room for whole vectors)
-    for (int k = 0; k < j.count[0]; k++) acc += ((const f32x4*)(j.ptr[0] + (size_t)k * j.stride[0]))[e];
+    int k = 0;
+    for (; k + 4 <= j.count[0]; k += 4) {   // four loads in flight, added in order
+      f32x4 v[4];
+#pragma unroll
+      for (int i = 0; i < 4; i++) v[i] = ((const f32x4*)(j.ptr[0] + (size_t)(k + i) * j.stride[0]))[e];
+#pragma unroll
+      for (int i = 0; i < 4; i++) acc += v[i];
+    }
+    for (; k < j.count[0]; k++) acc += ((const f32x4*)(j.ptr[0] + (size_t)k * j.stride[0]))[e];
     if (j.nsrc > 1)
       for (int k = 0; k < j.count[1]; k++) acc += ((const f32x4*)(j.ptr[1] + (size_t)k * j.stride[1]))[e];
   }
@@ -575,6 +583,131 @@ static hipError_t grad_generic_t(const LossArgs& a, const LossPlan& pl) {
 }
 hipError_t launch_grad_generic(const LossArgs& a, const LossPlan& pl) {
   return a.dt == GC_F32 ? grad_generic_t<float>(a, pl) : grad_generic_t<unsigned short>(a, pl);
+}
+
+
+// ---- a handful of scores -------------------------------------------------------------------------------------------------
+// The whole call in one workgroup: both inputs, the scores and then the coefficients stay in LDS.  Such a call is bound by
+// its launches (8 x 16 x 64 took five, 18 us of kernels); one workgroup is faster than the kernels of loss_planes.hip up
+// to some 2^17 products: 12.2 us at 8 x 16 x 64, 12.9 at 32 x 32 x 64 and 19 at 32 x 64 x 64 against 26; 32 at 8 x 32 x 768
+// against 55, but 34 at 64 x 64 x 64 against 26.
+constexpr long long kTinyWork = 1ll << 17;   // at small widths, see tiny_fits
+struct TinyArgs {
+  const void* q; const void* p; const int32_t* pos_idx;
+  int B, P, d, ld;                      // ld: odd row stride of the inputs in LDS
+  float alpha2, out_scale;
+  int mask_self;
+  float* loss; float* dq; float* dp; float* dz; float* lse; int32_t* argmax; float* rowloss; int* err;
+};
+template <typename T>
+__global__ void __launch_bounds__(1024) loss_tiny_kernel(TinyArgs g) {
+  extern __shared__ __attribute__((aligned(16))) float tiny_lds[];
+  float* Q = tiny_lds;
+  float* Pm = Q + g.B * g.ld;
+  float* S = Pm + g.P * g.ld;           // [B][P + 1]
+  float* rl = S + g.B * (g.P + 1);      // [B] row losses
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ls = g.P + 1;
+  for (int e = tid; e < g.B * g.d; e += 1024) Q[(e / g.d) * g.ld + e % g.d] = ldf<T>((const T*)g.q, e);
+  for (int e = tid; e < g.P * g.d; e += 1024) Pm[(e / g.d) * g.ld + e % g.d] = ldf<T>((const T*)g.p, e);
+  int bad = 0;
+  for (int i = tid; i < g.B; i += 1024) bad |= g.pos_idx[i] < 0 || g.pos_idx[i] >= g.P;
+  bad = __syncthreads_or(bad);
+  for (int e = tid; e < g.B * g.P; e += 1024) {
+    const int i = e / g.P, j = e % g.P;
+    const float* a = Q + i * g.ld;
+    const float* b = Pm + j * g.ld;
+    float s = 0.f;
+#pragma unroll 8
+    for (int k = 0; k < g.d; k++) s = fmaf(a[k], b[k], s);
+    S[i * ls + j] = (g.mask_self && i == j) ? -INFINITY : s * g.alpha2;
+  }
+  __syncthreads();
+  for (int i = wave; i < g.B; i += 16) {   // a wave per anchor
+    float* row = S + i * ls;
+    float m = -INFINITY;
+    int best = 0x7fffffff;
+    for (int j = lane; j < g.P; j += 64)
+      if (row[j] > m) { m = row[j]; best = j; }   // strict: the smallest index of this lane
+#pragma unroll
+    for (int w = 1; w < 64; w <<= 1) {
+      const float m2 = __shfl_xor(m, w);
+      const int b2 = __shfl_xor(best, w);
+      if (m2 > m || (m2 == m && b2 < best)) { m = m2; best = b2; }
+    }
+    const float ms = (m == -INFINITY) ? 0.f : m;
+    float l = 0.f;
+    for (int j = lane; j < g.P; j += 64) l += exp2f(row[j] - ms);
+#pragma unroll
+    for (int w = 1; w < 64; w <<= 1) l += __shfl_xor(l, w);
+    const float lse2 = ms + log2f(l);
+    const int r = g.pos_idx[i];
+    const bool ok = r >= 0 && r < g.P;
+    if (lane == 0) {
+      rl[i] = ok ? (lse2 - row[ok ? r : 0]) * kLn2 : NAN;
+      g.rowloss[i] = rl[i];
+      if (g.lse) g.lse[i] = lse2 * kLn2;
+      if (g.argmax) g.argmax[i] = best;
+    }
+    for (int j = lane; j < g.P; j += 64)
+      row[j] = (g.mask_self && i == j) ? 0.f : exp2f(row[j] - lse2) - (j == r ? 1.f : 0.f);
+  }
+  __syncthreads();
+  if (wave == 0) {   // mean of the row losses, in a fixed order
+    float s = 0.f;
+    for (int i = lane; i < g.B; i += 64) s += rl[i];
+#pragma unroll
+    for (int w = 1; w < 64; w <<= 1) s += __shfl_xor(s, w);
+    if (lane == 0) {
+      if (g.loss) *g.loss = bad ? NAN : s / (float)g.B;
+      *g.err = bad ? 1 : 0;
+    }
+  }
+  if (g.dq || g.dz)
+    for (int e = tid; e < g.B * g.d; e += 1024) {
+      const int i = e / g.d, c = e % g.d;
+      float s = 0.f;
+#pragma unroll 8
+      for (int j = 0; j < g.P; j++) s = fmaf(S[i * ls + j], Pm[j * g.ld + c], s);
+      if (g.dz) {   // (B == P, one input) + the target's part of the same row
+        float t = 0.f;
+#pragma unroll 8
+        for (int j = 0; j < g.B; j++) t = fmaf(S[j * ls + i], Q[j * g.ld + c], t);
+        g.dz[e] = s * g.out_scale + t * g.out_scale;
+      } else {
+        g.dq[e] = s * g.out_scale;
+      }
+    }
+  if (g.dp)
+    for (int e = tid; e < g.P * g.d; e += 1024) {
+      const int j = e / g.d, c = e % g.d;
+      float s = 0.f;
+#pragma unroll 8
+      for (int i = 0; i < g.B; i++) s = fmaf(S[i * ls + j], Q[i * g.ld + c], s);
+      g.dp[e] = s * g.out_scale;
+    }
+}
+static size_t tiny_lds_bytes(int B, int P, int d) { return ((size_t)(B + P) * (d | 1) + (size_t)B * (P + 1) + B) * 4; }
+bool tiny_fits(int B, int P, int d) {
+  if (B > 1024 || P > 1024 || d > 4096) return false;
+  // (the other kernels walk the width in one chain: 26 us at d = 64, 55 at 768)
+  return (long long)B * P * d <= kTinyWork + kTinyWork * d / 384 && tiny_lds_bytes(B, P, d) <= 150 * 1024;
+}
+template <typename T>
+static hipError_t tiny_t(const TinyArgs& g, size_t lds, hipStream_t s) {
+  static bool done[64];
+  if (hipError_t e = ensure_dyn_lds((const void*)loss_tiny_kernel<T>, 150 * 1024, done); e != hipSuccess) return e;
+  loss_tiny_kernel<T><<<1, 1024, lds, s>>>(g);
+  return hipGetLastError();
+}
+hipError_t launch_loss_tiny(const LossArgs& a, const LossPlan& pl) {
+  TinyArgs g{};
+  g.q = a.q; g.p = a.p; g.pos_idx = a.pos_idx; g.B = a.B; g.P = a.P; g.d = a.d; g.ld = a.d | 1;
+  g.alpha2 = a.alpha * kLog2e; g.out_scale = a.alpha / (float)a.B * (a.grad_mul != 0.f ? a.grad_mul : 1.f);
+  g.mask_self = (a.flags & GC_MASK_SELF) ? 1 : 0;
+  g.loss = a.defer_loss_sum ? nullptr : a.loss; g.dq = a.dq; g.dp = a.dp; g.dz = a.dz; g.lse = a.lse; g.argmax = a.argmax;
+  g.rowloss = (float*)(a.ws + pl.off_rowloss); g.err = (int*)(a.ws + pl.off_err);
+  const size_t lds = tiny_lds_bytes(a.B, a.P, a.d);
+  return a.dt == GC_F32 ? tiny_t<float>(g, lds, a.stream) : tiny_t<unsigned short>(g, lds, a.stream);
 }
 
 }  // namespace gc

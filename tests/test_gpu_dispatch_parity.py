@@ -166,3 +166,67 @@ def test_chunk_backward_row_edges(rows, din, dh, dout):
         # 0.25 + g is stored in fp32: half an ulp of the sum beside the arithmetic
         check("backward rows=%d %dx%dx%d d%s" % (rows, din, dh, dout, k), max(0.0, np.abs(got - want[k]).max() - 2.0 ** -25),
               TOL_BF16 * np.abs(want[k]).max())
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("B,P,d", [(1, 1, 1), (1, 17, 3), (17, 1, 5), (32, 64, 64), (70, 40, 33), (8, 32, 760), (3, 1000, 20), (1000, 3, 20)])
+def test_a_handful_of_scores(B, P, d, dtype):
+    """Calls that one workgroup serves whole, up to the line (32 x 64 x 64, 8 x 32 x 760; 768 in bf16 is one of the
+    widths with bf16 coefficients and not of this path) and beyond a wave and a workgroup of rows and columns."""
+    q, p, _ = synth.dpr_batch(B, P, d, dtype, seed=4800 + B)
+    r = torch.from_numpy(np.random.default_rng(B + P).integers(0, P, size=B).astype(np.int32))
+    want = oracle_loss(q, p, r, 1.0, 0.5)
+    check_fp32_grade("tiny %dx%dx%d %s" % (B, P, d, dtype), run_ex(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.5), want, q, p, 2.0)
+    if B >= 2:
+        r[1] = P   # out of range: reported, and the other rows' statistics are unaffected
+        out = gc.gc_loss_and_rep_grad_ex(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.5)
+        torch.cuda.synchronize()
+        assert gc.gc_check_async_error(out["workspace"]) == gc.GC_ERR_POS_IDX and torch.isnan(out["loss"]).all()
+        check("tiny lse beside a bad positive", relerr(to_np(out["lse"]), want["lse"]), TOL_F32)
+
+
+def test_a_handful_of_scores_masked_ntxent_and_symmetric():
+    n, d = 30, 24
+    q, p, _ = synth.dpr_batch(n, n, d, seed=4900, positive_mix=0.2)
+    r = torch.arange(n, dtype=torch.int32) ^ 1
+    want = oracle_loss(q, p, r, 1.0, 0.5, mask_self=True)
+    check_fp32_grade("tiny mask", run_ex(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.5, gc.GC_MASK_SELF), want, q, p, 2.0)
+    z = synth.ntxent_views(n, d, seed=4910)
+    want = oracle_loss(z, z, r, 1.0, 0.2, mask_self=True)
+    loss, dz = gc.gc_ntxent_loss_and_grad_bf16(z.to(DEV), 0.2)
+    torch.cuda.synchronize()
+    check_loss("tiny ntxent", loss.item(), want["loss"], TOL_F32)
+    check("tiny ntxent dz", relerr(to_np(dz), want["dq"] + want["dp"]), TOL_F32)
+    from oracle import gc_oracle as O
+    perm = torch.from_numpy(np.random.default_rng(n).permutation(n).astype(np.int32))
+    want = O.bidirectional(synth.widen(q), synth.widen(p), perm.numpy(), 1.0, 0.5)
+    out = gc.gc_bidirectional_loss_and_rep_grad_bf16(q.to(DEV), p.to(DEV), perm.to(DEV), 1.0, 0.5)
+    torch.cuda.synchronize()
+    check_loss("tiny symmetric", out["loss"].item(), want["loss"], TOL_F32)
+    for k in ("dq", "dp"):
+        check("tiny symmetric " + k, relerr(to_np(out[k]), want[k]), TOL_F32)
+
+
+@pytest.mark.parametrize("B,P", [(33, 70), (200, 130)])
+def test_deep_distance_with_saturated_rows(B, P):
+    """Pre-activations far beyond where 2^a 2^c can be formed from its factors, on some anchors and some targets (tiles with
+    and without such rows, pairs whose large parts cancel): z has an error of some ulp of its largest part, 100 here, and
+    so has tanh z where it is not saturated: 100 * 2^-22 = 2.4e-5, within the 1e-4 of the other cases."""
+    from oracle import gc_oracle as O
+    d = 128
+    q, p, _ = synth.dpr_batch(B, P, d, torch.float32, seed=5000 + B)
+    q[::3] *= 25.0
+    p[5::7] *= 25.0
+    p[40] = -q[3]
+    q, p = q.to(torch.bfloat16), p.to(torch.bfloat16)
+    om = synth.deep_omega(d)
+    om["C"] = om["A"].clone()      # a_3 + c_40 = 0 although both are large
+    r = torch.from_numpy(np.random.default_rng(B).integers(0, P, size=B).astype(np.int32))
+    om64 = {k: synth.widen(v) for k, v in om.items()}
+    assert np.abs(synth.widen(q) @ om64["A"].T).max() * 2 / np.log(2.0) > 120.0
+    want = O.deep_distance(synth.widen(q), synth.widen(p), synth.widen(r), om64, 1.0, 0.5)
+    out = gc.gc_deepdist_loss_and_grads_bf16(q.to(DEV), p.to(DEV), r.to(DEV), {k: v.to(DEV) for k, v in om.items()}, 1.0, 0.5)
+    torch.cuda.synchronize()
+    check_loss("saturated deep loss", out["loss"].item(), want["loss"], 1e-4)
+    for k in ("u", "v", "dA", "dC", "dw"):
+        check("saturated deep %dx%d %s" % (B, P, k), relerr(to_np(out[k]), want[k]), 1e-4)
