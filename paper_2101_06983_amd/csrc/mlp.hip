@@ -170,19 +170,24 @@ __device__ __forceinline__ void wgrad_tile(const WgradArgs& g, int bx, int by, u
     }
 }
 
-// C = A^T B with the rows (K) cut into slices: workgroup (tile, slice) adds its slice's product to partial s of C
-// (g.C + s * M * ldc, written whole: one workgroup per tile and slice), which a fixed-order sum combines afterwards.  A bf16.
+// C = A^T B with the rows (K) cut into slices: workgroup (tile, slice) writes its slice's product to partial s of C
+// (g.C + s * M * ldc), which a fixed-order sum combines afterwards.  The first n0 workgroups belong to g0, the others to g1.
+struct SplitkArgs { WgradArgs g; int rows_per_slice; };
 template <bool A_F32, bool B_F32>
-__global__ void __launch_bounds__(256) wgrad_splitk_kernel(WgradArgs g, int rows_per_slice) {
+__global__ void __launch_bounds__(256) wgrad_splitk_kernel(SplitkArgs a0, SplitkArgs a1, int first1) {
   __shared__ __attribute__((aligned(16))) unsigned short As[2 * WG_KCH * WG_A_LD];
   __shared__ __attribute__((aligned(16))) unsigned short Bs[2 * WG_KCH * WG_B_LD];
+  const bool second = (int)blockIdx.x >= first1;
+  const SplitkArgs& a = second ? a1 : a0;
+  const WgradArgs& g = a.g;
+  const int id = blockIdx.x - (second ? first1 : 0);
   const int nb = g.N / 128, tiles = nb * (g.M / WG_M);
-  const int tile = blockIdx.x % tiles, slice = blockIdx.x / tiles;
-  const int k0 = slice * rows_per_slice;
+  const int tile = id % tiles, slice = id / tiles;
+  const int k0 = slice * a.rows_per_slice;
   WgradArgs s = g;
   s.A = (const char*)g.A + (size_t)k0 * g.lda * (A_F32 ? 4 : 2);
   s.B = (const char*)g.B + (size_t)k0 * g.ldb * (B_F32 ? 4 : 2);
-  s.K = min(rows_per_slice, g.K - k0);
+  s.K = min(a.rows_per_slice, g.K - k0);
   s.C = g.C + (size_t)slice * g.M * g.ldc;
   wgrad_tile<A_F32, B_F32>(s, tile % nb, tile / nb, As, Bs);
 }
@@ -262,11 +267,14 @@ __device__ __forceinline__ float skinny_sum(const SkinnyRed* red, int em, int en
   return ((red[0][em][en] + red[1][em][en]) + red[2][em][en]) + red[3][em][en];
 }
 
-// grid (N / 32, m-tiles)
+// one workgroup per 32 x 32 tile; the first n0 of them belong to g0, the others to g1 (the two sides of a distance function)
 template <bool A_F32, Epilogue EP>
-__global__ void __launch_bounds__(256) mlp_skinny_kernel(SkinnyArgs g) {
+__global__ void __launch_bounds__(256) mlp_skinny_kernel(SkinnyArgs g0, SkinnyArgs g1, int first1) {
   __shared__ SkinnyRed red[4];
-  const int tid = threadIdx.x, n0 = blockIdx.x * 32, m0 = blockIdx.y * 32;
+  const bool second = (int)blockIdx.x >= first1;
+  const SkinnyArgs& g = second ? g1 : g0;
+  const int id = blockIdx.x - (second ? first1 : 0), nb = g.N / 32;
+  const int tid = threadIdx.x, n0 = (id % nb) * 32, m0 = (id / nb) * 32;
   skinny_product<A_F32, 4>(g.A, g.lda, m0, g.M - 1, g.Bt, g.ldb, n0, g.K, red, tid >> 6);
   __syncthreads();
   const int en = tid & 31, n = n0 + en;
@@ -285,6 +293,13 @@ __global__ void __launch_bounds__(256) mlp_skinny_kernel(SkinnyArgs g) {
       }
     }
   }
+}
+
+static int skinny_tiles(const SkinnyArgs& g) { return (g.N / 32) * ((g.M + 31) / 32); }
+template <bool A_F32, Epilogue EP>
+static void launch_skinny(const SkinnyArgs& g, hipStream_t s, const SkinnyArgs* g1 = nullptr) {
+  const int n0 = skinny_tiles(g);
+  mlp_skinny_kernel<A_F32, EP><<<n0 + (g1 ? skinny_tiles(*g1) : 0), 256, 0, s>>>(g, g1 ? *g1 : g, n0);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -829,19 +844,6 @@ __global__ void __launch_bounds__(64) mlp_grads_kernel(GradsArgs a) {
   }
 }
 
-// Wt[n][k] = W[k][n] (bf16), 32 x 32 tiles through LDS; K and N multiples of 32
-__global__ void __launch_bounds__(256) transpose_bf16_kernel(const unsigned short* __restrict__ W, int K, int N,
-                                                            unsigned short* __restrict__ Wt) {
-  __shared__ unsigned short t[32][33];
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  const int n0 = blockIdx.x * 32, k0 = blockIdx.y * 32;
-#pragma unroll
-  for (int i = 0; i < 4; i++) t[ty + 8 * i][tx] = W[(size_t)(k0 + ty + 8 * i) * N + n0 + tx];
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 4; i++) Wt[(size_t)(n0 + ty + 8 * i) * K + k0 + tx] = t[tx][ty + 8 * i];
-}
-
 static inline size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 
 // A forward takes Act (fp32 [rows][dh]) and the fp32 partial products of its second layer; a backward takes the fragments
@@ -957,11 +959,11 @@ static hipError_t mlp_forward(const void* x, int rows, const gc_mlp_params* w, c
   SkinnyArgs g1{};
   g1.A = x; g1.lda = w->din; g1.Bt = ws.W1T; g1.ldb = w->din; g1.M = rows; g1.N = w->dh; g1.K = w->din;
   g1.bias = (const unsigned short*)w->b1; g1.ActF = ws.ActF; g1.ldh = w->dh;
-  mlp_skinny_kernel<false, EP_GELU><<<dim3(w->dh / 32, (rows + 31) / 32), 256, 0, s>>>(g1);
+  launch_skinny<false, EP_GELU>(g1, s);
   SkinnyArgs g2{};
   g2.A = ws.ActF; g2.lda = w->dh; g2.Bt = ws.W2T; g2.ldb = w->dh; g2.M = rows; g2.N = w->dout; g2.K = w->dh;
   g2.bias = (const unsigned short*)w->b2; g2.Cb = (unsigned short*)y; g2.ldc = w->dout;
-  mlp_skinny_kernel<true, EP_BIAS><<<dim3(w->dout / 32, (rows + 31) / 32), 256, 0, s>>>(g2);
+  launch_skinny<true, EP_BIAS>(g2, s);
   return hipGetLastError();
 }
 
@@ -1177,6 +1179,10 @@ static int run_step(const StepCall& c, hipStream_t s) {
 // pair, plain vector arithmetic (no contraction for the MFMAs to take).  The pair part works on a_i = A f_i and
 // c_j = C g_j (two skinny products), both scaled by 2 log2(e), so that with r = 1 / (1 + 2^(a + c)):
 //   tanh z = 1 - 2 r,   1 - tanh^2 z = 4 r (1 - r).
+// 2^(a + c) = 2^a 2^c: the powers are taken once per row, not once per pair, which leaves one fma and one reciprocal per
+// (pair, k) instead of two additions, an exponential and a reciprocal (both at a quarter of the rate): 112 + 91 us for the
+// two walks of 1024 x 2048 pairs before, 76 + 62 since.  That holds while
+// no power over- or underflows: |a|, |c| <= kDdRange; tiles with a larger value (tanh saturates long before) take the sum.
 // One kernel walks the pairs in two roles, each with an owner side whose rows a workgroup keeps in registers and a
 // streamed side that passes through LDS 32 rows at a time:
 //   DD_DA     owner = anchors: d_ij for every pair and, in the same walk, the row's softmax statistics and the sums
@@ -1193,6 +1199,7 @@ static int run_step(const StepCall& c, hipStream_t s) {
 // row add their partial distances with two cross-lane moves, everything else stays in the thread's registers.
 constexpr int DD_OWN = 64, DD_TS = 32;
 enum DdRole { DD_DA = 0, DD_DC = 1 };
+constexpr float kDdRange = 60.f;    // 2^60 2^60 and its reciprocal are normal numbers
 constexpr float kDdMargin = 16.f;   // DD_DA: the reference of a row is raised when a logit exceeds it by more than this
 struct DdArgs {
   const float* own; const float* str;   // [n_own][H], [n_str][H]: 2 log2(e) (A f) resp. (C g), owner and streamed side
@@ -1220,17 +1227,24 @@ __global__ void __launch_bounds__(256, 2) deepdist_walk_kernel(DdArgs g) {
   __shared__ __attribute__((aligned(16))) float tile[2][DD_TS][H];
   __shared__ float st_lse[2][DD_TS];
   __shared__ int st_pos[2][DD_TS];
+  __shared__ int tile_big[2][4];   // per wave: an owner value or one of the tile it has loaded is out of range
   const int tid = threadIdx.x, o = tid >> 2, kq = tid & 3;
   const int oblk = blockIdx.x % g.n_oblk, split = blockIdx.x / g.n_oblk;
   const int row = oblk * DD_OWN + o, rowc = min(row, g.n_own - 1);
   const int sbeg = split * g.stream_len, send = min(g.n_str, sbeg + g.stream_len);
   const int nt = (send - sbeg + DD_TS - 1) / DD_TS;
 
-  float ao[HQ], wq[HQ];
+  float ea[HQ], wq[HQ];   // 2^a
+  const float* own_row = g.own + (size_t)rowc * H + kq * HQ;
+  bool own_big = false;
 #pragma unroll
   for (int k = 0; k < HQ; k += 4) {
-    const f32x4 v = *(const f32x4*)(g.own + (size_t)rowc * H + kq * HQ + k);
-    ao[k] = v[0]; ao[k + 1] = v[1]; ao[k + 2] = v[2]; ao[k + 3] = v[3];
+    const f32x4 v = *(const f32x4*)(own_row + k);
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      ea[k + e] = fast_exp2(v[e]);
+      own_big |= !(__builtin_fabsf(v[e]) <= kDdRange);
+    }
   }
   float w1 = 0.f;
 #pragma unroll
@@ -1259,12 +1273,21 @@ __global__ void __launch_bounds__(256, 2) deepdist_walk_kernel(DdArgs g) {
     }
   };
   auto stash = [&](int buf) __attribute__((always_inline)) {
+    bool big = own_big;
 #pragma unroll
     for (int v = 0; v < LD4; v++) {
       const int e4 = tid + 256 * v, rr = e4 / (H / 4), c4 = e4 % (H / 4);
       // 16-byte piece j of quarter kq sits at piece 4 j + kq: the four threads of a row then read 64 contiguous bytes
-      *(f32x4*)&tile[buf][rr][4 * ((c4 % (HQ / 4)) * 4 + c4 / (HQ / 4))] = pre[v];
+      f32x4 p;
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        p[e] = fast_exp2(pre[v][e]);
+        big |= !(__builtin_fabsf(pre[v][e]) <= kDdRange);
+      }
+      *(f32x4*)&tile[buf][rr][4 * ((c4 % (HQ / 4)) * 4 + c4 / (HQ / 4))] = p;
     }
+    const bool any = __builtin_amdgcn_ballot_w64(big) != 0;
+    if ((tid & 63) == 0) tile_big[buf][tid >> 6] = any ? 1 : 0;
     if (ROLE == DD_DC && tid < DD_TS) { st_lse[buf][tid] = pre_lse; st_pos[buf][tid] = pre_pos; }
   };
   fetch(0);
@@ -1274,17 +1297,32 @@ __global__ void __launch_bounds__(256, 2) deepdist_walk_kernel(DdArgs g) {
     const int buf = u & 1;
     if (u + 1 < nt) fetch(u + 1);
     const int t0 = sbeg + u * DD_TS, rows = min(DD_TS, send - t0);
+    const bool by_sum = (tile_big[buf][0] | tile_big[buf][1] | tile_big[buf][2] | tile_big[buf][3]) != 0;   // the same in the workgroup
     for (int s_ = 0; s_ < rows; s_++) {
       const float* cs = &tile[buf][s_][4 * kq];
       float rr[HQ], part = 0.f;
+      if (!by_sum) {
 #pragma unroll
-      for (int k = 0; k < HQ; k += 4) {
-        const f32x4 c4 = *(const f32x4*)(cs + 4 * k);
+        for (int k = 0; k < HQ; k += 4) {
+          const f32x4 c4 = *(const f32x4*)(cs + 4 * k);
 #pragma unroll
-        for (int e = 0; e < 4; e++) {
-          const float r = __builtin_amdgcn_rcpf(1.f + fast_exp2(ao[k + e] + c4[e]));   // 1 / (1 + e^(2 z))
-          rr[k + e] = r;
-          part = __builtin_fmaf(wq[k + e], r, part);
+          for (int e = 0; e < 4; e++) {
+            const float r = __builtin_amdgcn_rcpf(__builtin_fmaf(ea[k + e], c4[e], 1.f));   // 1 / (1 + e^(2 z))
+            rr[k + e] = r;
+            part = __builtin_fmaf(wq[k + e], r, part);
+          }
+        }
+      } else {
+        const float* str_row = g.str + (size_t)min(t0 + s_, g.n_str - 1) * H + kq * HQ;
+#pragma unroll
+        for (int k = 0; k < HQ; k += 4) {
+          const f32x4 a4 = *(const f32x4*)(own_row + k), c4 = *(const f32x4*)(str_row + k);
+#pragma unroll
+          for (int e = 0; e < 4; e++) {
+            const float r = __builtin_amdgcn_rcpf(1.f + fast_exp2(a4[e] + c4[e]));
+            rr[k + e] = r;
+            part = __builtin_fmaf(wq[k + e], r, part);
+          }
         }
       }
       const float t = g.alpha2 * (w1 - 2.f * quad_sum(part));   // base-2 logit of the pair
@@ -1413,17 +1451,18 @@ __global__ void __launch_bounds__(256) colsum_slices_kernel(const float* __restr
   }
 }
 
+constexpr int kColsumRows = 32;   // rows per slice, while that is at most 64 slices
 struct DeepWs {
   LossPlan st;                 // the statistics part of a loss workspace (split statistics, lse2, row losses, error word)
   size_t off_stat, off_a, off_c, off_AT, off_CT, off_da_part, off_e_part, off_dc_part, off_da, off_dc, off_e, off_wpart,
-      off_gpart, off_pos_r, total;
+      off_gpart, off_gpart2, off_pos_r, total;
   int nsa, len_a, nsc, len_c;  // stream splits of the anchor-owner walks / of the target-owner walk
   int slices_b, rps_b, slices_p, rps_p;   // row slices of the two parameter-gradient products
 };
 static void dd_split(int n_oblk, int n_str, int& ns, int& len) {
-  const int target = 2 * num_cu();               // two workgroups per CU
+  const int target = 2 * num_cu();               // two workgroups per CU (one: walks of 92 + 75 us and not 76 + 62 at 1024 x 2048)
   ns = (target + n_oblk - 1) / n_oblk;
-  const int max_ns = (n_str + 4 * DD_TS - 1) / (4 * DD_TS);   // at least four tiles per split
+  const int max_ns = (n_str + DD_TS - 1) / DD_TS;   // at least a tile per split
   if (ns > max_ns) ns = max_ns;
   if (ns > 64) ns = 64;
   if (ns < 1) ns = 1;
@@ -1464,8 +1503,8 @@ static DeepWs plan_deep(int B, int P, int d, int h) {
   };
   slices_of(B, w.slices_b, w.rps_b);
   slices_of(P, w.slices_p, w.rps_p);
-  const int smax = w.slices_b > w.slices_p ? w.slices_b : w.slices_p;
-  w.off_gpart = take((size_t)smax * h * d * 4);
+  w.off_gpart = take((size_t)w.slices_b * h * d * 4);
+  w.off_gpart2 = take((size_t)w.slices_p * h * d * 4);
   w.total = off;
   return w;
 }
@@ -1633,7 +1672,12 @@ int gc_bilinear_loss_and_grads_bf16(const void* q, const void* p, const int32_t*
   float* A = (float*)(ws + w.off_A);
   float* part = (float*)(ws + w.off_part);
   // H = F Omega (bf16): Bt[n][k] = Omega[k][n]
-  transpose_bf16_kernel<<<dim3(d / 32, d / 32), 256, 0, s>>>((const unsigned short*)omega, d, d, omT);
+  {
+    PrepArgs t{};
+    t.tr[0] = {(const unsigned short*)omega, omT, d, d};
+    t.n_tr0 = t.n_tr = (d / 64) * (d / 64);
+    mlp_prep_kernel<<<t.n_tr, 256, 0, s>>>(t);
+  }
   {
     GemmArgs g{};
     g.A = q; g.lda = d; g.Bt = omT; g.ldb = d; g.M = B; g.N = d; g.K = d; g.C = H; g.ldc = d;
@@ -1652,7 +1696,9 @@ int gc_bilinear_loss_and_grads_bf16(const void* q, const void* p, const int32_t*
   {  // dOmega = F^T A, the rows cut into slices, partial sums in a fixed order
     WgradArgs g{};
     g.A = q; g.lda = d; g.B = A; g.ldb = d; g.M = d; g.N = d; g.K = B; g.C = part; g.ldc = d;
-    wgrad_splitk_kernel<false, true><<<(d / 128) * (d / WG_M) * w.slices, 256, 0, s>>>(g, w.rows_per_slice);
+    const SplitkArgs a{g, w.rows_per_slice};
+    const int n = (d / 128) * (d / WG_M) * w.slices;
+    wgrad_splitk_kernel<false, true><<<n, 256, 0, s>>>(a, a, n);
     if (hipGetLastError() != hipSuccess) return GC_ERR_HIP;
     if (launch_partial_sum(domega, part, w.slices, (size_t)d * d, (size_t)d * d, s) != hipSuccess) return GC_ERR_HIP;
   }
@@ -1689,12 +1735,17 @@ int gc_deepdist_loss_and_grads_bf16(const void* q, const void* p, const int32_t*
     SkinnyArgs g{};
     g.A = x; g.lda = d; g.Bt = (const unsigned short*)M; g.ldb = d; g.M = rows; g.N = h; g.K = d; g.Cf = out; g.ldc = h;
     g.plain_mul = 2.f * kLog2e;
-    mlp_skinny_kernel<false, EP_PLAIN><<<dim3(h / 32, (rows + 31) / 32), 256, 0, s>>>(g);
+    return g;
   };
-  project(q, B, A, a2);
-  project(p, P, C, c2);
-  transpose_bf16_kernel<<<dim3(d / 32, h / 32), 256, 0, s>>>((const unsigned short*)A, h, d, AT);   // A^T [d][h]
-  transpose_bf16_kernel<<<dim3(d / 32, h / 32), 256, 0, s>>>((const unsigned short*)C, h, d, CT);
+  const SkinnyArgs proj_c = project(p, P, C, c2);
+  launch_skinny<false, EP_PLAIN>(project(q, B, A, a2), s, &proj_c);
+  {  // A^T, C^T [d][h]
+    PrepArgs t{};
+    t.tr[0] = {(const unsigned short*)A, AT, h, d};
+    t.tr[1] = {(const unsigned short*)C, CT, h, d};
+    t.n_tr0 = (h / 64) * (d / 64); t.n_tr = 2 * t.n_tr0;
+    mlp_prep_kernel<<<t.n_tr, 256, 0, s>>>(t);
+  }
   if (hipGetLastError() != hipSuccess) return GC_ERR_HIP;
   const int obA = (B + DD_OWN - 1) / DD_OWN, obC = (P + DD_OWN - 1) / DD_OWN;
   DdArgs g{};
@@ -1721,49 +1772,48 @@ int gc_deepdist_loss_and_grads_bf16(const void* q, const void* p, const int32_t*
     deepdist_finish_kernel<128><<<(pw.st.b_pad + 1) / 2, 256, 0, s>>>(f);
     if (hipGetLastError() != hipSuccess) return GC_ERR_HIP;
   }
-  LossArgs la{};
-  la.dt = GC_BF16; la.pos_idx = pos_idx; la.B = B; la.P = P; la.d = d; la.alpha = alpha; la.loss = loss; la.ws = ws; la.stream = s;
-  if (launch_loss_sum(la, pw.st) != hipSuccess) return GC_ERR_HIP;
+  // column sums of e (-> dL/dw), in row slices
+  const int w_slices = (B + kColsumRows - 1) / kColsumRows < 64 ? (B + kColsumRows - 1) / kColsumRows : 64;
+  const int w_rows = (B + w_slices - 1) / w_slices, w_parts = (B + w_rows - 1) / w_rows;
+  colsum_slices_kernel<<<dim3(h / 32, w_parts), 256, 0, s>>>(e, B, h, w_rows, (float*)(ws + pw.off_wpart));
+  if (hipGetLastError() != hipSuccess) return GC_ERR_HIP;
   // targets own, anchors streamed (with their final lse2)
   g.own = c2; g.str = a2; g.n_own = P; g.n_str = B; g.n_oblk = obC; g.stream_len = pw.len_c;
   g.out_a = (float*)(ws + pw.off_dc_part); g.out_e = nullptr;
   deepdist_walk_kernel<128, DD_DC><<<obC * pw.nsc, 256, 0, s>>>(g);
   if (hipGetLastError() != hipSuccess) return GC_ERR_HIP;
-  auto sum_parts = [&](float* out, size_t off_part, int parts, size_t n) {
-    return launch_partial_sum(out, (const float*)(ws + off_part), parts, n, n, s);
+  auto sum_job = [&](float* out, size_t off_part, int parts, size_t n) {
+    ReduceJob j{};
+    j.out = out; j.n = n; j.nsrc = 1; j.ptr[0] = (const float*)(ws + off_part); j.count[0] = parts; j.stride[0] = n;
+    return j;
   };
-  if (sum_parts(dc, pw.off_dc_part, pw.nsc, (size_t)P * h) != hipSuccess) return GC_ERR_HIP;
-  {  // dL/dw_k = sum_i e_ik: row slices, then their fixed-order sum
-    int sl = (B + 255) / 256;
-    if (sl > 64) sl = 64;
-    const int rps = (B + sl - 1) / sl;
-    sl = (B + rps - 1) / rps;
-    float* wp = (float*)(ws + pw.off_wpart);
-    colsum_slices_kernel<<<dim3(h / 32, sl), 256, 0, s>>>(e, B, h, rps, wp);
-    if (hipGetLastError() != hipSuccess) return GC_ERR_HIP;
-    if (sum_parts(dw, pw.off_wpart, sl, (size_t)h) != hipSuccess) return GC_ERR_HIP;
+  LossArgs la{};
+  la.dt = GC_BF16; la.pos_idx = pos_idx; la.B = B; la.P = P; la.d = d; la.alpha = alpha; la.loss = loss; la.ws = ws; la.stream = s;
+  {  // dL/dc and dL/dw from their partials; the launch takes the sum of the row losses along
+    const ReduceJob jobs[2] = {sum_job(dc, pw.off_dc_part, pw.nsc, (size_t)P * h), sum_job(dw, pw.off_wpart, w_parts, (size_t)h)};
+    if (launch_reduce_jobs(jobs, 2, s, &la, &pw.st) != hipSuccess) return GC_ERR_HIP;
   }
   // u = dL/da A, v = dL/dc C (third and fourth equation): Bt[n][k] = A^T[n][k]
   auto pull = [&](const float* grad, int rows, const unsigned short* MT, float* out) {
     SkinnyArgs k{};
     k.A = grad; k.lda = h; k.Bt = MT; k.ldb = h; k.M = rows; k.N = d; k.K = h; k.Cf = out; k.ldc = d;
-    mlp_skinny_kernel<true, EP_PLAIN><<<dim3(d / 32, (rows + 31) / 32), 256, 0, s>>>(k);
+    return k;
   };
-  pull(da, B, AT, u);
-  pull(dc, P, CT, v);
+  const SkinnyArgs pull_v = pull(dc, P, CT, v);
+  launch_skinny<true, EP_PLAIN>(pull(da, B, AT, u), s, &pull_v);
   if (hipGetLastError() != hipSuccess) return GC_ERR_HIP;
   // dL/dA = (dL/da)^T F, dL/dC = (dL/dc)^T G (second equation): rows cut into slices, partial sums in a fixed order
-  auto param_grad = [&](const float* grad, const void* x, int rows, int slices, int rps, float* out) {
-    float* part = (float*)(ws + pw.off_gpart);
+  auto param_grad = [&](const float* grad, const void* x, int rows, int rps, size_t off) {
     WgradArgs k{};
-    k.A = grad; k.lda = h; k.B = x; k.ldb = d; k.M = h; k.N = d; k.K = rows; k.C = part; k.ldc = d;
-    wgrad_splitk_kernel<true, false><<<(d / 128) * (h / WG_M) * slices, 256, 0, s>>>(k, rps);
-    if (hipGetLastError() != hipSuccess) return hipErrorUnknown;
-    return sum_parts(out, pw.off_gpart, slices, (size_t)h * d);
+    k.A = grad; k.lda = h; k.B = x; k.ldb = d; k.M = h; k.N = d; k.K = rows; k.C = (float*)(ws + off); k.ldc = d;
+    return SplitkArgs{k, rps};
   };
-  if (param_grad(da, q, B, pw.slices_b, pw.rps_b, dA) != hipSuccess) return GC_ERR_HIP;
-  if (param_grad(dc, p, P, pw.slices_p, pw.rps_p, dC) != hipSuccess) return GC_ERR_HIP;
-  return GC_OK;
+  const int tiles = (d / 128) * (h / WG_M);
+  wgrad_splitk_kernel<true, false><<<tiles * (pw.slices_b + pw.slices_p), 256, 0, s>>>(
+      param_grad(da, q, B, pw.rps_b, pw.off_gpart), param_grad(dc, p, P, pw.rps_p, pw.off_gpart2), tiles * pw.slices_b);
+  if (hipGetLastError() != hipSuccess) return GC_ERR_HIP;
+  const ReduceJob jobs[2] = {sum_job(dA, pw.off_gpart, pw.slices_b, (size_t)h * d), sum_job(dC, pw.off_gpart2, pw.slices_p, (size_t)h * d)};
+  return launch_reduce_jobs(jobs, 2, s) == hipSuccess ? GC_OK : GC_ERR_HIP;
 }
 
 }  // extern "C"
