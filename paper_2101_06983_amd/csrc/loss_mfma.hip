@@ -15,6 +15,7 @@
 #include <type_traits>
 
 #include "gc_common.h"
+#include "stats_tile.h"
 
 namespace gc {
 
@@ -94,16 +95,6 @@ constexpr int ST_ROWB = ST_KC * 2;                       // bytes per LDS row (8
 constexpr int ST_STAGE_BYTES = (ST_TM + ST_TN) * ST_ROWB;  // one stage: 256 target rows, then 256 anchor rows
 // LDS layout: chunk c of row r is stored at chunk position c ^ ((r >> 1) & 7): the 16 rows that a
 // 16-lane group reads in one fragment load then fall into 16 different 16-byte bank groups.
-
-__device__ __forceinline__ void stat_merge(float& m, float& l, int& idx, float m2, float l2, int idx2) {
-  // (m, idx): larger value wins, ties to the smaller index
-  bool take = (m2 > m) || (m2 == m && idx2 < idx);
-  float mn = fmaxf(m, m2);
-  float ms = (mn == -INFINITY) ? 0.f : mn;
-  l = l * fast_exp2(m - ms) + l2 * fast_exp2(m2 - ms);
-  idx = take ? idx2 : idx;
-  m = mn;
-}
 
 __global__ void __launch_bounds__(512) stats_mfma_kernel(const unsigned short* __restrict__ Q,
                                                          const unsigned short* __restrict__ Pm,
@@ -319,27 +310,15 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(const unsigned short* _
 // B P d / 8 bytes of L2 traffic, so the larger tiles win again from about 2^20 scores (a version with 64 x 64 tiles took
 // 37 us at 1021 x 4099 x 384, the 256 x 256 kernel 23).
 // ===========================================================================
-struct StatsSmallArgs {
-  const unsigned short* Q; const unsigned short* P; const int32_t* pos_idx;
-  int B, Pn, d, n_ablk, tiles, tiles_per_split, mask_self;
-  float alpha2;
-  float* part_m; float* part_l; int* part_idx; float* pos_t;
-};
 __global__ void __launch_bounds__(256) stats_small_kernel(StatsSmallArgs g) {
-  constexpr int T = kStatTile, PD = 3, PARTS = 256 / T, TP = T / PARTS;   // TP: targets per thread of the epilogue
-  __shared__ float red[4][T][T + 1];                                     // partial tiles of the four waves: [target][anchor]
-  __shared__ float xm[PARTS][T], xl[PARTS][T];                           // per part: maximum, sum, index
-  __shared__ int xi[PARTS][T];
+  constexpr int T = kStatTile, PD = 3;
+  __shared__ StatTileLds lds;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, ln = lane & 31;
   const int task = xcd_task_id();
   const int a0 = (task % g.n_ablk) * T, split = task / g.n_ablk;
   const int nch = g.d / 64;
   const char* qp = (const char*)(g.Q + (size_t)min(a0 + ln, g.B - 1) * g.d + 32 * h);
-  // epilogue: thread (part, n) takes targets TP part .. of anchor n
-  const int en = tid % T, part = tid / T, a = a0 + en;
-  const int r = a < g.B ? g.pos_idx[a] : -1;
-  float m = -INFINITY, l = 0.f;
-  int best = 0x7fffffff;
+  StatTile<false> st(g, a0);
   const int t_end = min(g.tiles, (split + 1) * g.tiles_per_split);
   for (int t = split * g.tiles_per_split; t < t_end; t++) {
     const int j0 = t * T;
@@ -369,49 +348,15 @@ __global__ void __launch_bounds__(256) stats_small_kernel(StatsSmallArgs g) {
         }
       }
     }
-#pragma unroll
-    for (int e = 0; e < 16; e++) red[wave][8 * (e >> 2) + 4 * h + (e & 3)][ln] = acc[e];
+    StatTile<false>::put(lds, wave, acc);
     __syncthreads();
-    float v[TP], mt = -INFINITY;
-    int bt = 0x7fffffff;
-#pragma unroll
-    for (int e = 0; e < TP; e++) {
-      const int row = part * TP + e, j = j0 + row;
-      float x = (((red[0][row][en] + red[1][row][en]) + red[2][row][en]) + red[3][row][en]) * g.alpha2;
-      if (j >= g.Pn || (g.mask_self && j == a)) x = -INFINITY;
-      // (a positive that the self-mask removes has the logit -inf: its row loss is then +inf)
-      if (j == r && j < g.Pn && a < g.B) g.pos_t[a] = x;
-      v[e] = x;
-      if (x > mt) { mt = x; bt = j; }   // strict: the smallest index attaining the maximum
-    }
-    const float mn = fmaxf(m, mt), ms = (mn == -INFINITY) ? 0.f : mn;
-    float s = 0.f;
-#pragma unroll
-    for (int e = 0; e < TP; e++) s += fast_exp2(v[e] - ms);
-    l = l * fast_exp2(m - ms) + s;
-    if (mt > m) best = bt;
-    m = mn;
+    st.tile(g, lds, j0);
     __syncthreads();   // the partial tiles have been read
   }
-  xm[part][en] = m; xl[part][en] = l; xi[part][en] = best;
-  __syncthreads();
-  if (tid < T && a < g.B) {   // part 0 of every anchor: the others in order
-#pragma unroll
-    for (int k = 1; k < PARTS; k++) stat_merge(m, l, best, xm[k][en], xl[k][en], xi[k][en]);
-    const size_t o = (size_t)split * g.B + a;
-    g.part_m[o] = m; g.part_l[o] = l; g.part_idx[o] = best;
-  }
+  st.finish(g, lds, split);
 }
 static hipError_t launch_stats_small(const LossArgs& a, const LossPlan& pl) {
-  constexpr int T = kStatTile;
-  char* ws = a.ws;
-  StatsSmallArgs g{};
-  g.Q = (const unsigned short*)a.q; g.P = (const unsigned short*)a.p; g.pos_idx = a.pos_idx;
-  g.B = a.B; g.Pn = a.P; g.d = a.d; g.n_ablk = (a.B + T - 1) / T; g.tiles = (a.P + T - 1) / T;
-  g.tiles_per_split = pl.stat_cols_per_split / T; g.mask_self = (a.flags & GC_MASK_SELF) ? 1 : 0;
-  g.alpha2 = a.alpha * kLog2e;
-  g.part_m = (float*)(ws + pl.off_part_m); g.part_l = (float*)(ws + pl.off_part_l); g.part_idx = (int*)(ws + pl.off_part_idx);
-  g.pos_t = (float*)(ws + pl.off_pos);
+  const StatsSmallArgs g = stats_small_args(a, pl, (const unsigned short*)a.q, (const unsigned short*)a.p);
   stats_small_kernel<<<g.n_ablk * pl.stat_splits, 256, 0, a.stream>>>(g);
   return hipGetLastError();
 }

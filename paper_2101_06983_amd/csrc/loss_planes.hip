@@ -23,6 +23,7 @@
 #include <type_traits>
 
 #include "gc_common.h"
+#include "stats_tile.h"
 
 namespace gc {
 
@@ -140,8 +141,7 @@ __global__ void __launch_bounds__(256) planes_pack_kernel(PackArgs a) {
 // 16 KB (12 KB for three planes; with half of that the fp32 call of 512 x 1024 scores at d = 768 took 77 us and not 69).
 // k-steps past the end re-read the last one and are not used.
 // ks_lds: a multiple of PD, or KS.
-// (The gradient kernel has its accumulators beside them: 8 KB for one plane.)
-constexpr int planes_pd(int NP, bool grad) { return NP == 1 ? (grad ? 8 : 16) : 4; }
+constexpr int planes_pd(int NP) { return NP == 1 ? 16 : 4; }
 template <int NP, int NO, int PD>
 __device__ __forceinline__ void planes_scores(const unsigned short* str, const unsigned short* own_lds, const unsigned short* own_glb,
                                               size_t own_stride, int KS, int ks_lds, f32x16 (&s)[NO]) {
@@ -260,7 +260,7 @@ __global__ void __launch_bounds__(256, 2) planes_stats_kernel(PlanesStatsArgs g)
     for (int no = 0; no < NO; no++)
 #pragma unroll
       for (int r = 0; r < 16; r++) s[no][r] = 0.f;
-    planes_scores<NP, NO, planes_pd(NP, false)>(g.pk + (size_t)t * blk, pl_lds, own, blk, g.KS, g.ks_lds, s);
+    planes_scores<NP, NO, planes_pd(NP)>(g.pk + (size_t)t * blk, pl_lds, own, blk, g.KS, g.ks_lds, s);
     const int j0 = t * 32 + 4 * h;   // register r: target j0 + 8 (r / 4) + r % 4, increasing in r
 #pragma unroll
     for (int no = 0; no < NO; no++) {
@@ -305,6 +305,55 @@ __global__ void __launch_bounds__(256, 2) planes_stats_kernel(PlanesStatsArgs g)
   }
 }
 
+// Few scores: 32 x 32 tiles, the k-steps dealt to the four waves of a workgroup, eight (three planes: three) of them in
+// flight per wave and nothing staged.  (512 x 1024 scores: PLANES_STATS.)
+template <int NP>
+__global__ void __launch_bounds__(256) planes_stats_small_kernel(StatsSmallArgs g, int KS) {
+  constexpr int T = kStatTile, PD = NP == 1 ? 8 : 3;
+  __shared__ StatTileLds lds;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int task = xcd_task_id();
+  const int ob = task % g.n_ablk, split = task / g.n_ablk;
+  const size_t blk = (size_t)KS * NP * 512;
+  const unsigned short* own = g.Q + (size_t)ob * blk + lane * 8;
+  StatTile<true> st(g, ob * T);
+  const int t_end = min(g.tiles, (split + 1) * g.tiles_per_split);
+  for (int t = split * g.tiles_per_split; t < t_end; t++) {
+    const unsigned short* str = g.P + (size_t)t * blk + lane * 8;
+    bf16x8 ro[PD][NP], rs[PD][NP];
+    auto load = [&](int slot, int ks) __attribute__((always_inline)) {
+#pragma unroll
+      for (int n = 0; n < NP; n++) {
+        rs[slot][n] = *(const bf16x8*)(str + ((size_t)ks * NP + n) * 512);
+        ro[slot][n] = *(const bf16x8*)(own + ((size_t)ks * NP + n) * 512);
+      }
+    };
+    f32x16 acc;
+#pragma unroll
+    for (int e = 0; e < 16; e++) acc[e] = 0.f;
+#pragma unroll
+    for (int p = 0; p < PD; p++) load(p, min(wave + 4 * p, KS - 1));
+    for (int k0 = wave; k0 < KS; k0 += 4 * PD) {
+#pragma unroll
+      for (int p = 0; p < PD; p++) {
+        const int ks = k0 + 4 * p;
+        if (ks < KS) {
+#pragma unroll
+          for (int x = NP - 1; x >= 0; x--)   // small terms first
+#pragma unroll
+            for (int i = 0; i <= x; i++) acc = mfma_p(rs[p][i], ro[p][x - i], acc);
+          load(p, min(ks + 4 * PD, KS - 1));
+        }
+      }
+    }
+    StatTile<true>::put(lds, wave, acc);
+    __syncthreads();
+    st.tile(g, lds, t * T);
+    __syncthreads();   // the partial tiles have been read
+  }
+  st.finish(g, lds, split);
+}
+
 // ---- gradients -----------------------------------------------------------------------------------------------------------
 // A workgroup owns 32 NO rows and up to 128 CTW columns of dQ (or dP) and walks a range of the other side 128 rows at a
 // time.  Per step each wave forms the scores of 32 of those rows against the owner rows over the whole width, turns them
@@ -328,7 +377,7 @@ constexpr int PG_STEP = 128;
 constexpr int planes_g_bytes(int NO) { return 4 * 2 * 3 * NO * 1024; }
 
 template <int NP, int NO, int CTW>
-__global__ void __launch_bounds__(256, NO == 1 ? 2 : 1) planes_grad_kernel(PlanesGradArgs g) {
+__global__ void __launch_bounds__(256, NO == 1 && CTW <= 4 ? 2 : 1) planes_grad_kernel(PlanesGradArgs g) {
   extern __shared__ __attribute__((aligned(16))) unsigned short pl_lds[];
   unsigned short* gl = pl_lds;                                    // [kk8][no][plane] blocks of 1 KB
   unsigned short* own_lds = pl_lds + planes_g_bytes(NO) / 2;
@@ -369,7 +418,18 @@ __global__ void __launch_bounds__(256, NO == 1 ? 2 : 1) planes_grad_kernel(Plane
     for (int no = 0; no < NO; no++)
 #pragma unroll
       for (int r = 0; r < 16; r++) s[no][r] = 0.f;
-    planes_scores<NP, NO, planes_pd(NP, true)>(R.str_k + (size_t)(t0 / 32 + w) * blk, own_lds, own, blk, g.KS, g.ks_lds, s);
+    planes_scores<NP, NO, planes_pd(NP)>(R.str_k + (size_t)(t0 / 32 + w) * blk, own_lds, own, blk, g.KS, g.ks_lds, s);
+    // the first loads of the second contraction
+    constexpr int MOST = NP == 1 ? 16 : CTW >= 6 ? 5 : 6, XD = 8 * CTW < MOST ? 8 * CTW : MOST;   // column tiles in flight
+    const unsigned short* xt = R.str_t + (size_t)(t0 / 16) * g.CT * NP * 512 + lane * 8;
+    bf16x8 xf[XD][NP];
+    auto load_x = [&](int slot, int kk, int i) __attribute__((always_inline)) {
+      const unsigned short* p = xt + ((size_t)kk * g.CT + min(ct0 + w + 4 * i, g.CT - 1)) * (NP * 512);
+#pragma unroll
+      for (int n = 0; n < NP; n++) xf[slot][n] = *(const bf16x8*)(p + n * 512);
+    };
+#pragma unroll
+    for (int p = 0; p < XD; p++) load_x(p, p / CTW, p % CTW);
     const int j0 = t0 + 32 * w + 4 * h;
     float lse_s[16]; int pos_s[16];
     if (ri) {
@@ -404,33 +464,27 @@ __global__ void __launch_bounds__(256, NO == 1 ? 2 : 1) planes_grad_kernel(Plane
       }
     }
     __syncthreads();
-    // dO[32 NO x columns] += g[32 NO x 128] R[128 x columns]; the row blocks of the packed copy are full (zero-padded)
-    const unsigned short* xt = R.str_t + (size_t)(t0 / 16) * g.CT * NP * 512 + lane * 8;
-    constexpr int MOST = NP == 1 ? 8 : CTW == 8 ? 2 : CTW == 6 ? 3 : 4, PD = CTW < MOST ? CTW : MOST;   // column tiles of loads in flight
-    static_assert(CTW % PD == 0, "the ring of loads starts over at every row step");
-    auto src = [&](int kk, int i) __attribute__((always_inline)) -> const unsigned short* {
-      return xt + ((size_t)kk * g.CT + min(ct0 + w + 4 * i, g.CT - 1)) * (NP * 512);
-    };
-    bf16x8 xf[PD][NP];
-#pragma unroll
-    for (int p = 0; p < PD; p++)
-#pragma unroll
-      for (int n = 0; n < NP; n++) xf[p][n] = *(const bf16x8*)(src(0, p) + n * 512);
-#pragma unroll 1
-    for (int kk = 0; kk < 8; kk++) {
-      bf16x8 gf[NO][3];
+    // dO[32 NO x columns] += g[32 NO x 128] R[128 x columns]; the row blocks of the packed copy are full (zero-padded).
+    // The first loads have been issued before the coefficients were formed; the coefficients come a row step ahead.
+    bf16x8 gf[2][NO][3];
+    auto load_g = [&](int slot, int kk) __attribute__((always_inline)) {
 #pragma unroll
       for (int no = 0; no < NO; no++)
 #pragma unroll
-        for (int n = 0; n < 3; n++) gf[no][n] = *(const bf16x8*)(gl + ((kk * NO + no) * 3 + n) * 512 + lane * 8);
+        for (int n = 0; n < 3; n++) gf[slot][no][n] = *(const bf16x8*)(gl + ((kk * NO + no) * 3 + n) * 512 + lane * 8);
+    };
+    load_g(0, 0);
+#pragma unroll
+    for (int kk = 0; kk < 8; kk++) {
+      if (kk < 7) load_g((kk + 1) & 1, kk + 1);
 #pragma unroll
       for (int i = 0; i < CTW; i++) {
+        constexpr int N = 8 * CTW;
+        const int at = kk * CTW + i;
         bf16x8 x[NP];
 #pragma unroll
-        for (int n = 0; n < NP; n++) x[n] = xf[i % PD][n];
-        const unsigned short* nx = (i + PD < CTW) ? src(kk, i + PD) : src(min(kk + 1, 7), i + PD - CTW);
-#pragma unroll
-        for (int n = 0; n < NP; n++) xf[i % PD][n] = *(const bf16x8*)(nx + n * 512);
+        for (int n = 0; n < NP; n++) x[n] = xf[at % XD][n];
+        if (at + XD < N) load_x(at % XD, (at + XD) / CTW, (at + XD) % CTW);
         if (ct0 + w + 4 * i < ct1) {
 #pragma unroll
           for (int no = 0; no < NO; no++)
@@ -438,7 +492,7 @@ __global__ void __launch_bounds__(256, NO == 1 ? 2 : 1) planes_grad_kernel(Plane
             for (int t = 2; t >= 0; t--)
 #pragma unroll
               for (int n = 0; n < NP; n++)
-                if (t - n >= 0) acc[no][i] = mfma_p(gf[no][t - n], x[n], acc[no][i]);
+                if (t - n >= 0) acc[no][i] = mfma_p(gf[kk & 1][no][t - n], x[n], acc[no][i]);
         }
       }
     }
@@ -472,20 +526,26 @@ void plan_planes(LossPlan& pl, int B, int P, int d, gc_dtype dt, int max_splits)
   const int dpad = pad_to(d, 64);
   pl.px_KS = dpad / 16; pl.px_CT = dpad / 32;
   pl.px_rows_q = pad_to(B, 128); pl.px_rows_p = pad_to(P, 128);
-  // statistics: about eight waves for every CU, each wave a split of its own (the merge takes up to 64)
-  const int nob = cdiv(B, 32), tiles = cdiv(P, 32);
-  int wgs = cdiv(2 * cu, nob);
-  if (wgs > 16) wgs = 16;
-  if (wgs > cdiv(tiles, 4)) wgs = cdiv(tiles, 4);
-  pl.px_tiles_per_wave = cdiv(tiles, 4 * wgs);
-  pl.stat_splits = 4 * cdiv(tiles, 4 * pl.px_tiles_per_wave);
+  const int tiles = cdiv(P, 32);
+  if ((long long)B * P <= (1ll << 20)) {   // few scores: small tiles (the line of the bf16 widths, see stats_small_kernel)
+    pl.stat_tile = kStatTile;
+    const int per = cdiv(tiles, 64);       // the merge kernel combines at most 64 splits
+    pl.stat_cols_per_split = per * kStatTile;
+    pl.stat_splits = cdiv(tiles, per);
+  } else {   // about eight waves for every CU, each wave a split of its own
+    int wgs = cdiv(2 * cu, cdiv(B, 32));
+    if (wgs > 16) wgs = 16;
+    if (wgs > cdiv(tiles, 4)) wgs = cdiv(tiles, 4);
+    pl.px_tiles_per_wave = cdiv(tiles, 4 * wgs);
+    pl.stat_splits = 4 * cdiv(tiles, 4 * pl.px_tiles_per_wave);
+  }
   // gradients
   pl.px_col_slices = cdiv(pl.px_CT, 32);                       // a workgroup holds up to 1024 columns
   pl.px_ct_per_slice = cdiv(pl.px_CT, pl.px_col_slices);
   const int stQ = cdiv(P, PG_STEP), stP = cdiv(B, PG_STEP);    // steps of a whole stream
   auto units = [&](int no) { return (long long)pl.px_col_slices * ((long long)cdiv(B, 32 * no) * stQ + (long long)cdiv(P, 32 * no) * stP); };
   pl.px_no = units(2) >= 8ll * cu ? 2 : 1;
-  const long long want = pl.px_no == 1 ? 2 * cu : cu;          // workgroups that run at once
+  const long long want = pl.px_no == 1 && pl.px_ct_per_slice <= 16 ? 2 * cu : cu;   // workgroups that run at once
   long long per = (units(pl.px_no) + want - 1) / want;
   if (per < 1) per = 1;
   auto split_of = [&](int steps, int rows, int& ns, int& len) {
@@ -517,6 +577,11 @@ static int ks_in_lds(int room, int KS, int pd) { return room >= KS ? KS : room /
 template <int NP>
 static hipError_t stats_np(const LossArgs& a, const LossPlan& pl) {
   char* ws = a.ws;
+  if (pl.stat_tile) {
+    const StatsSmallArgs g = stats_small_args(a, pl, (const unsigned short*)(a.ws2 + pl.off_qk), (const unsigned short*)(a.ws2 + pl.off_pk));
+    planes_stats_small_kernel<NP><<<g.n_ablk * pl.stat_splits, 256, 0, a.stream>>>(g, pl.px_KS);
+    return hipGetLastError();
+  }
   PlanesStatsArgs g{};
   g.qk = (const unsigned short*)(a.ws2 + pl.off_qk); g.pk = (const unsigned short*)(a.ws2 + pl.off_pk);
   g.pos_idx = a.pos_idx; g.B = a.B; g.P = a.P; g.KS = pl.px_KS;
@@ -526,7 +591,7 @@ static hipError_t stats_np(const LossArgs& a, const LossPlan& pl) {
   g.pos_t = (float*)(ws + pl.off_pos);
   const int nwg = g.n_own * (pl.stat_splits / 4);
   const int budget = (nwg <= num_cu() ? 152 : 76) * 1024;
-  g.ks_lds = ks_in_lds(budget / (NP * 1024), g.KS, planes_pd(NP, false));
+  g.ks_lds = ks_in_lds(budget / (NP * 1024), g.KS, planes_pd(NP));
   static bool done[64];
   if (hipError_t e = ensure_dyn_lds((const void*)planes_stats_kernel<NP, 1>, 160 * 1024, done); e != hipSuccess) return e;
   planes_stats_kernel<NP, 1><<<nwg, 256, g.ks_lds * NP * 1024, a.stream>>>(g);
@@ -541,8 +606,8 @@ hipError_t launch_stats_planes(const LossArgs& a, const LossPlan& pl) {
 
 template <int NP, int NO, int CTW>
 static hipError_t grad_launch(PlanesGradArgs& g, int nwg, hipStream_t s) {
-  const int budget = ((nwg <= num_cu() || NO == 2) ? 156 : 78) * 1024 - planes_g_bytes(NO);
-  g.ks_lds = ks_in_lds(budget / (NO * NP * 1024), g.KS, planes_pd(NP, true));
+  const int budget = ((nwg <= num_cu() || NO == 2 || CTW > 4) ? 156 : 78) * 1024 - planes_g_bytes(NO);
+  g.ks_lds = ks_in_lds(budget / (NO * NP * 1024), g.KS, planes_pd(NP));
   static bool done[64];
   if (hipError_t e = ensure_dyn_lds((const void*)planes_grad_kernel<NP, NO, CTW>, 160 * 1024, done); e != hipSuccess) return e;
   planes_grad_kernel<NP, NO, CTW><<<nwg, 256, planes_g_bytes(NO) + g.ks_lds * NO * NP * 1024, s>>>(g);

@@ -1,0 +1,90 @@
+// Row statistics of 32 x 32 score tiles whose contraction was split over the four waves of a workgroup: what the kernels
+// for few scores (bf16 widths and planes) share.
+#pragma once
+#include "gc_common.h"
+
+namespace gc {
+
+__device__ __forceinline__ void stat_merge(float& m, float& l, int& idx, float m2, float l2, int idx2) {
+  // (m, idx): larger value wins, ties to the smaller index
+  bool take = (m2 > m) || (m2 == m && idx2 < idx);
+  float mn = fmaxf(m, m2);
+  float ms = (mn == -INFINITY) ? 0.f : mn;
+  l = l * fast_exp2(m - ms) + l2 * fast_exp2(m2 - ms);
+  idx = take ? idx2 : idx;
+  m = mn;
+}
+
+struct StatsSmallArgs {
+  const unsigned short* Q; const unsigned short* P; const int32_t* pos_idx;
+  int B, Pn, d, n_ablk, tiles, tiles_per_split, mask_self;
+  float alpha2;
+  float* part_m; float* part_l; int* part_idx; float* pos_t;
+};
+struct StatTileLds {
+  float red[4][kStatTile][kStatTile + 1];                          // partial tiles of the four waves: [target][anchor]
+  float m[256 / kStatTile][kStatTile], l[256 / kStatTile][kStatTile];   // per part of the targets: maximum, sum, index
+  int idx[256 / kStatTile][kStatTile];
+};
+// Thread (part, n) of 256 takes targets TP part .. of anchor n.  EXACT: the library's exp2f instead of the hardware's.
+template <bool EXACT>
+struct StatTile {
+  static constexpr int T = kStatTile, PARTS = 256 / T, TP = T / PARTS;
+  float m = -INFINITY, l = 0.f;
+  int best = 0x7fffffff, en, part, a, r;
+  static __device__ __forceinline__ float ex(float x) { return EXACT ? exp2f(x) : fast_exp2(x); }
+  __device__ __forceinline__ StatTile(const StatsSmallArgs& g, int a0) {
+    en = threadIdx.x % T; part = threadIdx.x / T; a = a0 + en;
+    r = a < g.B ? g.pos_idx[a] : -1;
+  }
+  // this wave's partial products of the tile of targets j0 .. (targets on M: lane ln holds anchor ln)
+  static __device__ __forceinline__ void put(StatTileLds& s, int wave, const f32x16& acc) {
+    const int lane = threadIdx.x & 63, h = lane >> 5, ln = lane & 31;
+#pragma unroll
+    for (int e = 0; e < 16; e++) s.red[wave][8 * (e >> 2) + 4 * h + (e & 3)][ln] = acc[e];
+  }
+  // after a barrier; the caller puts another one behind it
+  __device__ __forceinline__ void tile(const StatsSmallArgs& g, const StatTileLds& s, int j0) {
+    float v[TP], mt = -INFINITY;
+    int bt = 0x7fffffff;
+#pragma unroll
+    for (int e = 0; e < TP; e++) {
+      const int row = part * TP + e, j = j0 + row;
+      float x = (((s.red[0][row][en] + s.red[1][row][en]) + s.red[2][row][en]) + s.red[3][row][en]) * g.alpha2;
+      if (j >= g.Pn || (g.mask_self && j == a)) x = -INFINITY;
+      // (a positive that the self-mask removes has the logit -inf: its row loss is then +inf)
+      if (j == r && j < g.Pn && a < g.B) g.pos_t[a] = x;
+      v[e] = x;
+      if (x > mt) { mt = x; bt = j; }   // strict: the smallest index attaining the maximum
+    }
+    const float mn = fmaxf(m, mt), ms = (mn == -INFINITY) ? 0.f : mn;
+    float sum = 0.f;
+#pragma unroll
+    for (int e = 0; e < TP; e++) sum += ex(v[e] - ms);
+    l = l * ex(m - ms) + sum;
+    if (mt > m) best = bt;
+    m = mn;
+  }
+  __device__ __forceinline__ void finish(const StatsSmallArgs& g, StatTileLds& s, int split) {
+    s.m[part][en] = m; s.l[part][en] = l; s.idx[part][en] = best;
+    __syncthreads();
+    if (threadIdx.x < T && a < g.B) {   // part 0 of every anchor: the others in order
+#pragma unroll
+      for (int k = 1; k < PARTS; k++) stat_merge(m, l, best, s.m[k][en], s.l[k][en], s.idx[k][en]);
+      const size_t o = (size_t)split * g.B + a;
+      g.part_m[o] = m; g.part_l[o] = l; g.part_idx[o] = best;
+    }
+  }
+};
+inline StatsSmallArgs stats_small_args(const LossArgs& a, const LossPlan& pl, const unsigned short* q, const unsigned short* p) {
+  StatsSmallArgs g{};
+  g.Q = q; g.P = p; g.pos_idx = a.pos_idx;
+  g.B = a.B; g.Pn = a.P; g.d = a.d; g.n_ablk = (a.B + kStatTile - 1) / kStatTile; g.tiles = (a.P + kStatTile - 1) / kStatTile;
+  g.tiles_per_split = pl.stat_cols_per_split / kStatTile; g.mask_self = (a.flags & GC_MASK_SELF) ? 1 : 0;
+  g.alpha2 = a.alpha * kLog2e;
+  g.part_m = (float*)(a.ws + pl.off_part_m); g.part_l = (float*)(a.ws + pl.off_part_l); g.part_idx = (int*)(a.ws + pl.off_part_idx);
+  g.pos_t = (float*)(a.ws + pl.off_pos);
+  return g;
+}
+
+}  // namespace gc
