@@ -296,18 +296,22 @@ __device__ __forceinline__ void add_shared_positives(f32x4& acc, const PosFix& f
     __syncthreads();
     constexpr int FLY = 8;
     for (int k0 = 0; k0 < total; k0 += FLY) {
-      s16x4 o[FLY];
+      s16x4 o[FLY];   // (loaded whether or not the anchor is this row's: a load behind a condition is waited for one by one)
+      bool mine[FLY];
+      float c[FLY];
 #pragma unroll
       for (int k = 0; k < FLY; k++) {
-        o[k] = s16x4{0, 0, 0, 0};
-        if (k0 + k < total && live && list.row[k0 + k] == row) o[k] = *(const s16x4*)(fx.other + (size_t)list.anchor[k0 + k] * fx.d + col);
+        const int at = min(k0 + k, total - 1);
+        mine[k] = k0 + k < total && live && list.row[at] == row;
+        c[k] = list.c[at];
+        o[k] = *(const s16x4*)(fx.other + (size_t)list.anchor[at] * fx.d + col);
       }
 #pragma unroll
       for (int k = 0; k < FLY; k++)
-        if (k0 + k < total && live && list.row[k0 + k] == row) {
-          const float c = list.c[k0 + k];
 #pragma unroll
-          for (int e = 0; e < 4; e++) acc[e] += c * bf2f((unsigned short)o[k][e]);
+        for (int e = 0; e < 4; e++) {
+          const float sum = acc[e] + c[k] * bf2f((unsigned short)o[k][e]);
+          acc[e] = mine[k] ? sum : acc[e];
         }
     }
     __syncthreads();   // the list and the counts are free again

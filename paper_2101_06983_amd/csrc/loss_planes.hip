@@ -306,7 +306,8 @@ __global__ void __launch_bounds__(256, 2) planes_stats_kernel(PlanesStatsArgs g)
 }
 
 // Few scores: 32 x 32 tiles, the k-steps dealt to the four waves of a workgroup, eight (three planes: three) of them in
-// flight per wave and nothing staged.  (512 x 1024 scores: PLANES_STATS.)
+// flight per wave and nothing staged.  (512 x 1024 scores: fp32 d = 768 11 us, 19.6 with the kernel
+// above; bf16 d = 1024 8 us, 12 above.)
 template <int NP>
 __global__ void __launch_bounds__(256) planes_stats_small_kernel(StatsSmallArgs g, int KS) {
   constexpr int T = kStatTile, PD = NP == 1 ? 8 : 3;

@@ -306,9 +306,10 @@ static void launch_skinny(const SkinnyArgs& g, hipStream_t s, const SkinnyArgs* 
 // C[M x N] = A[M x K] * Bt[N x K]^T for many rows (the whole batch at once: the projections of the distance function,
 // the graph-less forward), where the skinny kernel above would stream Bt once per 32 rows.  A workgroup owns a BM x 128
 // tile of C (BM = 128 or 64), its four waves BM/2 x 64 each (MFMA tiles 32x32x16); both operands go through LDS in
-// 64-wide k-steps (whole 128-byte lines of every row), two buffers, one barrier per step; the global loads run two steps
-// ahead in two register sets used in turn.  An fp32 A is split into hi + lo bf16 planes as everywhere in this file.
-// Rows of LDS are padded to 144 bytes, which spreads the 16-byte fragment reads of 8 consecutive rows over all banks.
+// k-steps of 64 (whole 128-byte lines of every row) or 32 (half the LDS, so three workgroups per unit instead of two; the
+// launch chooses), two buffers, one barrier per step; the global loads run two steps ahead in two register sets used in
+// turn.  An fp32 A is split into hi + lo bf16 planes as everywhere in this file.  Rows of LDS are padded by 16 bytes, which
+// spreads the 16-byte fragment reads of 8 consecutive rows over all banks.
 struct GemmArgs {
   const void* A; int lda;             // [M][K], bf16 or fp32
   const unsigned short* Bt; int ldb;  // [N][K] bf16
@@ -324,13 +325,14 @@ struct GemmArgs {
 };
 // what a tile writes: the product (times mul) as fp32 or bf16, GELU(product + bias) as fp32, product + bias as bf16
 enum GemmOut { GO_F32 = 0, GO_BF16 = 1, GO_GELU_F32 = 2, GO_BIAS_BF16 = 3 };
-constexpr int GM_T = 128, GM_BK = 32, GM_LD = GM_BK + 8;
-template <bool A_F32, int BM>
-constexpr int gemm_lds_bytes() { return 2 * ((A_F32 ? 2 : 1) * BM + GM_T) * GM_LD * 2; }
+constexpr int GM_T = 128;
+template <bool A_F32, int BM, int BK>
+constexpr int gemm_lds_bytes() { return 2 * ((A_F32 ? 2 : 1) * BM + GM_T) * (BK + 8) * 2; }
 // acc += the tile's product over k in [kbeg, kbeg + klen); ends with every wave past its last read of LDS
-template <bool A_F32, int BM>
+template <bool A_F32, int BM, int GM_BK>
 __device__ __forceinline__ void gemm_mainloop(const GemmArgs& g, int m0, int n0, int kbeg, int klen, unsigned short* gemm_lds,
                                               f32x16 (&acc)[BM / 64][2]) {
+  constexpr int GM_LD = GM_BK + 8;
   constexpr int AP = A_F32 ? 2 : 1;   // planes of A
   constexpr int MT = BM / 64;         // 32-row MFMA tiles per wave
   constexpr int PR = GM_BK / 8, NA = BM * PR / 256, NB = GM_T * PR / 256;   // staging pieces (8 elements): per row, of A and of Bt per thread
@@ -433,8 +435,8 @@ __device__ __forceinline__ void gemm_zero(f32x16 (&acc)[MT][2]) {
 #pragma unroll
       for (int r = 0; r < 16; r++) acc[mt][nt][r] = 0.f;
 }
-template <bool A_F32, GemmOut OUT, int BM>
-__global__ void __launch_bounds__(256, BM == 64 ? 3 : 2) gemm_nt_kernel(GemmArgs g) {
+template <bool A_F32, GemmOut OUT, int BM, int BK>
+__global__ void __launch_bounds__(256, BK == 32 && BM == 64 ? 3 : 2) gemm_nt_kernel(GemmArgs g) {
   constexpr int MT = BM / 64;
   extern __shared__ __attribute__((aligned(16))) unsigned short gemm_lds[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, ln = lane & 31;
@@ -447,7 +449,7 @@ __global__ void __launch_bounds__(256, BM == 64 ? 3 : 2) gemm_nt_kernel(GemmArgs
   const int wm = wave >> 1, wn = wave & 1;
   f32x16 acc[MT][2];
   gemm_zero<MT>(acc);
-  gemm_mainloop<A_F32, BM>(g, m0, n0, kbeg, klen, gemm_lds, acc);
+  gemm_mainloop<A_F32, BM, BK>(g, m0, n0, kbeg, klen, gemm_lds, acc);
   // lane (ln, h) holds column ln of each MFMA tile, rows 8 (r / 4) + 4 h + r % 4
   const float mul = g.mul != 0.f ? g.mul : 1.f;
 #pragma unroll
@@ -469,25 +471,25 @@ __global__ void __launch_bounds__(256, BM == 64 ? 3 : 2) gemm_nt_kernel(GemmArgs
         }
       }
 }
+template <bool A_F32, GemmOut OUT, int BM, int BK>
+static hipError_t gemm_nt_launch(const GemmArgs& g, int tiles, hipStream_t s) {
+  static bool done[64];
+  constexpr int lds = gemm_lds_bytes<A_F32, BM, BK>();
+  if (hipError_t e = ensure_dyn_lds((const void*)gemm_nt_kernel<A_F32, OUT, BM, BK>, lds, done); e != hipSuccess) return e;
+  gemm_nt_kernel<A_F32, OUT, BM, BK><<<tiles, 256, lds, s>>>(g);
+  return hipGetLastError();
+}
 template <bool A_F32, GemmOut OUT>
 static hipError_t launch_gemm_nt(const GemmArgs& g, hipStream_t s) {
   const int ks = g.k_split > 1 ? g.k_split : 1;
-  if (g.M < 1 || g.N % GM_T || g.K % (GM_BK * ks) || g.K < GM_BK * ks || (ks > 1 && OUT != GO_F32)) return hipErrorInvalidValue;
-  // 64-row tiles while 128-row tiles would leave compute units without one: several small workgroups per unit
-  // then cover each other's barriers and waits
-  const int t128 = ((g.M + 127) / 128) * (g.N / GM_T);
-  if (t128 * ks >= 2 * num_cu()) {
-    static bool done[64];
-    constexpr int lds = gemm_lds_bytes<A_F32, 128>();
-    if (hipError_t e = ensure_dyn_lds((const void*)gemm_nt_kernel<A_F32, OUT, 128>, lds, done); e != hipSuccess) return e;
-    gemm_nt_kernel<A_F32, OUT, 128><<<t128 * ks, 256, lds, s>>>(g);
-  } else {
-    static bool done[64];
-    constexpr int lds = gemm_lds_bytes<A_F32, 64>();
-    if (hipError_t e = ensure_dyn_lds((const void*)gemm_nt_kernel<A_F32, OUT, 64>, lds, done); e != hipSuccess) return e;
-    gemm_nt_kernel<A_F32, OUT, 64><<<((g.M + 63) / 64) * (g.N / GM_T) * ks, 256, lds, s>>>(g);
-  }
-  return hipGetLastError();
+  if (g.M < 1 || g.N % GM_T || g.K % (64 * ks) || g.K < 64 * ks || (ks > 1 && OUT != GO_F32)) return hipErrorInvalidValue;
+  // 64-row tiles while 128-row tiles would leave compute units without one: several small workgroups per unit then cover
+  // each other's barriers and waits.  32-wide k-steps, of which three workgroups fit a unit, where two per unit would not
+  // hold all tiles (40 against 33 us for 576 tiles of K = 1024); 64-wide ones, half the barriers, below.
+  const int t128 = ((g.M + 127) / 128) * (g.N / GM_T) * ks, t64 = ((g.M + 63) / 64) * (g.N / GM_T) * ks;
+  if (t128 >= 2 * num_cu()) return gemm_nt_launch<A_F32, OUT, 128, 64>(g, t128, s);
+  if (t64 > 2 * num_cu()) return gemm_nt_launch<A_F32, OUT, 64, 32>(g, t64, s);
+  return gemm_nt_launch<A_F32, OUT, 64, 64>(g, t64, s);
 }
 
 // out[m][n] = bf16(sum over the k_split partial products, in index order, + bias[n]); 4 elements per thread
@@ -683,6 +685,8 @@ __global__ void __launch_bounds__(512) mlp_dh_skinny_kernel(DhArgs g) {
 }
 
 // Many rows: BM x 128 tiles, both contractions through the tiled main loop.
+// (64-row tiles: three workgroups per unit with a few registers spilled, 62 us for the 576 tiles of 1536 rows x 3072; two
+// without spills leave a second, nearly empty round, 68 us)
 template <int BM>
 __global__ void __launch_bounds__(256, BM == 64 ? 3 : 1) mlp_dh_tiled_kernel(DhArgs g) {
   constexpr int MT = BM / 64;
@@ -696,7 +700,7 @@ __global__ void __launch_bounds__(256, BM == 64 ? 3 : 1) mlp_dh_tiled_kernel(DhA
   a.A = g.x[0]; a.A2 = g.n2 ? g.x[1] : nullptr; a.lda = g.din; a.Bt = g.W1t; a.ldb = g.din;
   f32x16 gp[MT][2];   // H, then GELU'(H)
   gemm_zero<MT>(gp);
-  gemm_mainloop<false, BM>(a, m0, n0, 0, g.din, gemm_lds, gp);
+  gemm_mainloop<false, BM, 32>(a, m0, n0, 0, g.din, gemm_lds, gp);
 #pragma unroll
   for (int nt = 0; nt < 2; nt++) {
     const int n = n0 + wn * 64 + nt * 32 + ln;
@@ -718,7 +722,7 @@ __global__ void __launch_bounds__(256, BM == 64 ? 3 : 1) mlp_dh_tiled_kernel(DhA
   a.A = g.u[0]; a.A2 = g.n2 ? g.u[1] : nullptr; a.lda = g.dout; a.Bt = g.W2; a.ldb = g.dout;
   f32x16 acc[MT][2];
   gemm_zero<MT>(acc);
-  gemm_mainloop<true, BM>(a, m0, n0, 0, g.dout, gemm_lds, acc);
+  gemm_mainloop<true, BM, 32>(a, m0, n0, 0, g.dout, gemm_lds, acc);
 #pragma unroll
   for (int nt = 0; nt < 2; nt++) {
     const int n = n0 + wn * 64 + nt * 32 + ln;
@@ -947,7 +951,7 @@ static hipError_t mlp_forward(const void* x, int rows, const gc_mlp_params* w, c
     // the shape only, not on the rows of a launch.
     int ks = 1;
     const int tiles64 = ((kStep1Rows + 63) / 64) * (w->dout / GM_T);   // tiles of a full Step-1 launch
-    while (ks < 4 && tiles64 * ks < 2 * num_cu() && (ks * 2) * w->dout <= w->dh && w->dh % (GM_BK * ks * 2) == 0) ks *= 2;
+    while (ks < 4 && tiles64 * ks < 2 * num_cu() && (ks * 2) * w->dout <= w->dh && w->dh % (64 * ks * 2) == 0) ks *= 2;
     if (ks == 1) return launch_gemm_nt<true, GO_BIAS_BF16>(g2, s);
     g2.C = ws.part; g2.C2 = nullptr; g2.bias = nullptr; g2.k_split = ks; g2.split_stride = (size_t)all * w->dout;
     if (hipError_t e = launch_gemm_nt<true, GO_F32>(g2, s); e != hipSuccess) return e;
@@ -993,12 +997,12 @@ static hipError_t mlp_backward(const BackwardRows& a, const BackwardRows& b, con
     const int t128 = ((d.rows + 127) / 128) * (w->dh / GM_T);
     if (t128 >= 2 * num_cu()) {
       static bool done[64];
-      constexpr int lds = gemm_lds_bytes<true, 128>();
+      constexpr int lds = gemm_lds_bytes<true, 128, 32>();
       if (hipError_t e = ensure_dyn_lds((const void*)mlp_dh_tiled_kernel<128>, lds, done); e != hipSuccess) return e;
       mlp_dh_tiled_kernel<128><<<t128, 256, lds, s>>>(d);
     } else {
       static bool done[64];
-      constexpr int lds = gemm_lds_bytes<true, 64>();
+      constexpr int lds = gemm_lds_bytes<true, 64, 32>();
       if (hipError_t e = ensure_dyn_lds((const void*)mlp_dh_tiled_kernel<64>, lds, done); e != hipSuccess) return e;
       mlp_dh_tiled_kernel<64><<<((d.rows + 63) / 64) * (w->dh / GM_T), 256, lds, s>>>(d);
     }
