@@ -48,10 +48,12 @@ __device__ __forceinline__ void to_planes(f32x8_t v, bf16x8 (&out)[N]) {
     if (CHECKED && odd) {
 #pragma unroll
       for (int e = 0; e < 8; e++) {
+        const float x = v[e];   // (a bit cast of v[e] itself reads element 0 of the vector)
         if (__builtin_fabsf(r[e]) < INFINITY) continue;
-        const float t = (__builtin_fabsf(v[e]) < INFINITY) ? __builtin_bit_cast(float, __builtin_bit_cast(unsigned, v[e]) & 0xffff0000u) : v[e];
+        const bool finite = __builtin_fabsf(x) < INFINITY;
+        const float t = finite ? __builtin_bit_cast(float, __builtin_bit_cast(unsigned, x) & 0xffff0000u) : x;
         out[0][e] = (__bf16)t;
-        r[e] = (__builtin_fabsf(v[e]) < INFINITY) ? v[e] - t : 0.f;
+        r[e] = finite ? x - t : 0.f;
       }
     }
     out[1] = __builtin_convertvector(r, bf16x8);

@@ -230,3 +230,30 @@ def test_deep_distance_with_saturated_rows(B, P):
     check_loss("saturated deep loss", out["loss"].item(), want["loss"], 1e-4)
     for k in ("u", "v", "dA", "dC", "dw"):
         check("saturated deep %dx%d %s" % (B, P, k), relerr(to_np(out[k]), want[k]), 1e-4)
+
+
+def masked_batch(B, P, d, seed):
+    """Features of one sign, so that a target with a large negative feature has a large negative logit for every anchor;
+    the targets of `out` are masked (by the caller) and nobody's positive."""
+    rng = np.random.default_rng(seed)
+    q = torch.from_numpy((0.05 + rng.random((B, d))).astype(np.float32)) * (2.0 / d)
+    p = torch.from_numpy((0.05 + rng.random((P, d))).astype(np.float32))
+    out = rng.permutation(P)[:max(2, P // 16)]
+    r = torch.from_numpy(rng.choice(np.setdiff1d(np.arange(P), out), size=B).astype(np.int32))
+    return q, p, r, torch.from_numpy(out)
+
+
+# one workgroup; few scores; the larger statistics kernel; 64 owner rows per workgroup
+MASK_SHAPES = [(8, 24, 40), (64, 96, 200), (70, 130, 776), (1100, 1000, 96), (2100, 4100, 130)]
+
+
+@pytest.mark.parametrize("lowest", [torch.finfo(torch.float32).min, -3.3961775e38, -3.39e38])
+@pytest.mark.parametrize("B,P,d", MASK_SHAPES)
+def test_targets_masked_by_the_types_lowest_value(B, P, d, lowest):
+    """A feature (of some targets: every feature) at the lowest fp32 value, which rounds to minus infinity in bf16, at the
+    first value that does, and at one just above: the target's weight is 0 and everything else is as if it were not there."""
+    q, p, r, out = masked_batch(B, P, d, 5100 + B)
+    p[out, 3] = lowest
+    p[out[0]] = lowest
+    want = oracle_loss(q, p, r, 1.0, 0.5)
+    check_fp32_grade("lowest %dx%dx%d" % (B, P, d), run_ex(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.5), want, q, p, 2.0)
