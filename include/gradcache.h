@@ -100,7 +100,9 @@ size_t gc_workspace_bytes(int B, int P, int d, int dt);
  * a multiple of 128 up to 768 keeps the softmax coefficients in bf16 where they
  * enter the gradient contractions; fp32 inputs and every other width are computed
  * in fp32-grade arithmetic throughout (three bf16 numbers per fp32 value on the
- * matrix cores), from packed copies of the inputs in the workspace.
+ * matrix cores), from packed copies of the inputs in the workspace.  Infinite
+ * features give the logits fp32 arithmetic gives (a target with logit -inf has
+ * weight 0); a gradient element whose sum has an infinite term is infinite or NaN.
  * Errors: GC_ERR_NULL, GC_ERR_SHAPE, GC_ERR_HIP.
  */
 int gc_loss_and_rep_grad_bf16(const void* q, const void* p, const int32_t* pos_idx, int B, int P, int d,

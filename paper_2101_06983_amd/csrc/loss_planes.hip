@@ -137,6 +137,29 @@ __global__ void __launch_bounds__(256) planes_pack_kernel(PackArgs a) {
 }
 
 // ---- scores ------------------------------------------------------------------------------------------------------------
+// An infinite operand, or a product beyond 3.4e38, is an infinity of the right sign in the product of the first planes, but
+// times the zeros and the remainders of either sign in the other planes it makes the sum NaN, where an fp32 product is
+// +-inf (a target that is masked by such a feature has weight 0).  A tile with a NaN score takes those scores from the
+// first planes alone: +-inf or NaN as fp32 arithmetic gives it, since every finite product is lost in the infinite one.
+__device__ __forceinline__ bool any_nan(const f32x16& s) {
+  bool nan = false;
+#pragma unroll
+  for (int r = 0; r < 16; r += 2) nan |= __builtin_isunordered(s[r], s[r + 1]);   // either of the two
+  return __builtin_amdgcn_ballot_w64(nan) != 0;
+}
+// (k-steps first, first + step, .. ; str and own point at this lane's piece of fragment 0)
+template <int NP>
+__device__ __forceinline__ void first_planes_for_nan(const unsigned short* str, const unsigned short* own, int first, int step, int KS, f32x16& s) {
+  f32x16 t;
+#pragma unroll
+  for (int r = 0; r < 16; r++) t[r] = 0.f;
+#pragma unroll 4
+  for (int ks = first; ks < KS; ks += step)
+    t = mfma_p(*(const bf16x8*)(str + (size_t)ks * NP * 512), *(const bf16x8*)(own + (size_t)ks * NP * 512), t);
+#pragma unroll
+  for (int r = 0; r < 16; r++) s[r] = s[r] != s[r] ? t[r] : s[r];
+}
+
 // s[no] += R_tile O_no^T for one 32-row streamed tile (fragments at str, contiguous along k) and NO blocks of 32 owner
 // rows: their first ks_lds k-steps are in LDS (own_lds, [k-step][no][plane]), the rest is loaded (own_glb + no * own_stride).
 // A wave is alone on its SIMD or with one other, so the latency of L2 is hidden by loads in flight only: PD k-steps ahead,
@@ -201,6 +224,11 @@ __device__ __forceinline__ void planes_scores(const unsigned short* str, const u
         }
       }
     }
+  }
+  if constexpr (NP > 1) {
+#pragma unroll
+    for (int no = 0; no < NO; no++)
+      if (any_nan(s[no])) first_planes_for_nan<NP>(str, own_glb + no * own_stride, 0, 1, KS, s[no]);
   }
 }
 
@@ -349,6 +377,8 @@ __global__ void __launch_bounds__(256) planes_stats_small_kernel(StatsSmallArgs 
         }
       }
     }
+    if constexpr (NP > 1)
+      if (any_nan(acc)) first_planes_for_nan<NP>(str, own, wave, 4, KS, acc);
     StatTile<true>::put(lds, wave, acc);
     __syncthreads();
     st.tile(g, lds, t * T);

@@ -257,3 +257,32 @@ def test_targets_masked_by_the_types_lowest_value(B, P, d, lowest):
     p[out[0]] = lowest
     want = oracle_loss(q, p, r, 1.0, 0.5)
     check_fp32_grade("lowest %dx%dx%d" % (B, P, d), run_ex(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.5), want, q, p, 2.0)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("B,P,d", MASK_SHAPES)
+def test_targets_masked_by_an_infinite_feature(B, P, d, dtype):
+    """Weight 0 times the infinity is NaN in that column of dq, as in any arithmetic; nothing else sees it."""
+    q, p, r, out = masked_batch(B, P, d, 5200 + B)
+    p[out, 3] = -torch.inf
+    q, p = q.to(dtype), p.to(dtype)
+    with np.errstate(invalid="ignore"):
+        want = oracle_loss(q, p, r, 1.0, 0.5)
+    got = run_ex(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.5)
+    assert torch.isnan(got["dq"][:, 3]).all() and np.isnan(want["dq"][:, 3]).all()
+    got["dq"][:, 3] = 0.0
+    want["dq"][:, 3] = 0.0
+    with np.errstate(invalid="ignore"):
+        check_fp32_grade("infinite feature %dx%dx%d" % (B, P, d), got, want, q, p, 2.0)
+
+
+@pytest.mark.parametrize("B,P,d", MASK_SHAPES)
+def test_targets_masked_by_products_beyond_the_fp32_range(B, P, d):
+    """Anchors with a large feature against masked targets: the product, and products of the remainders of the two factors
+    with either sign, are beyond 3.4e38."""
+    q, p, r, out = masked_batch(B, P, d, 5300 + B)
+    q[:, 3] = 1e3 * (1.0 + q[:, 3] * d)
+    p[:, 3] = 1e-6
+    p[out, 3] = -3e38
+    want = oracle_loss(q, p, r, 1.0, 0.5)
+    check_fp32_grade("overflow %dx%dx%d" % (B, P, d), run_ex(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.5), want, q, p, 2.0)
