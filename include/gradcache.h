@@ -17,7 +17,8 @@
  *     nothing the caller passed.  gc_loss_and_rep_grad_bf16 / _f32 take no
  *     workspace argument: they use a per-device buffer the library allocates
  *     with hipMalloc on first use and grows on demand (growing frees the old
- *     buffer with hipFree, which waits for the device; while `stream` is being
+ *     buffer with hipFree, which waits for the device, unless a captured call
+ *     has used it: it then stays allocated for the graph; while `stream` is being
  *     captured into a graph a call that would have to grow it takes the kernels
  *     that fit, or returns GC_ERR_UNSUPPORTED).  Such calls share the buffer, so the library
  *     puts them in order: a call made on another stream than the previous one

@@ -213,6 +213,12 @@ static bool shape_ok(int B, int P, int d) {
 static std::mutex g_ws_mutex;
 static void* g_ws_ptr[64];
 static size_t g_ws_bytes[64];
+// A buffer that a captured call has used belongs to the recorded graph as well: growing leaves it allocated (until the
+// process ends: nothing says when the last graph is gone)
+static bool g_ws_recorded[64];
+constexpr int kMaxKept = 32;   // (more are kept all the same, but gc_check_async_error does not read them)
+static void* g_ws_kept[64][kMaxKept];
+static int g_ws_nkept[64];
 
 // `have` (with *out) also tells what there is when the answer is GC_ERR_UNSUPPORTED
 static int own_workspace(size_t need, hipStream_t stream, void** out, size_t* have) {
@@ -229,9 +235,14 @@ static int own_workspace(size_t need, hipStream_t stream, void** out, size_t* ha
       *have = g_ws_bytes[dev];
       return GC_ERR_UNSUPPORTED;
     }
-    if (g_ws_ptr[dev]) (void)hipFree(g_ws_ptr[dev]);  // waits for work that still uses it
+    if (g_ws_ptr[dev] && g_ws_recorded[dev]) {
+      if (g_ws_nkept[dev] < kMaxKept) g_ws_kept[dev][g_ws_nkept[dev]++] = g_ws_ptr[dev];
+    } else if (g_ws_ptr[dev]) {
+      (void)hipFree(g_ws_ptr[dev]);  // waits for work that still uses it
+    }
     g_ws_ptr[dev] = nullptr;
     g_ws_bytes[dev] = 0;
+    g_ws_recorded[dev] = false;
     size_t sz = align_up(need + need / 4, 1 << 20);
     if (hipMalloc(&g_ws_ptr[dev], sz) != hipSuccess) return GC_ERR_HIP;
     g_ws_bytes[dev] = sz;
@@ -256,8 +267,9 @@ static bool is_capturing(hipStream_t stream) {
 static int own_workspace_enter(hipStream_t stream) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return GC_ERR_HIP;
-  if (is_capturing(stream)) return GC_OK;
+  const bool capturing = is_capturing(stream);
   std::lock_guard<std::mutex> lock(g_ws_mutex);
+  if (capturing) { g_ws_recorded[dev] = true; return GC_OK; }
   if (g_ws_used[dev] && g_ws_last[dev] != stream && hipStreamWaitEvent(stream, g_ws_done[dev], 0) != hipSuccess) return GC_ERR_HIP;
   return GC_OK;
 }
@@ -498,16 +510,24 @@ int gc_loss_and_rep_grad_f32(const float* q, const float* p, const int32_t* pos_
 
 int gc_check_async_error(const void* workspace) {
   const void* ws[2] = {workspace, nullptr};
+  int word = 0;
   if (!workspace) {   // the library's own buffers of this device, as far as they have been used
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return GC_ERR_HIP;
     std::lock_guard<std::mutex> lock(g_ws_mutex);
     ws[0] = g_ws_ptr[dev];
     ws[1] = g_scratch_ptr[dev];
+    // what a replayed graph has left in a buffer that only it uses is reported once
+    for (int i = 0; i < g_ws_nkept[dev]; i++) {
+      if (hipMemcpy(&word, g_ws_kept[dev][i], sizeof(int), hipMemcpyDeviceToHost) != hipSuccess) return GC_ERR_HIP;
+      if (!word) continue;
+      word = 0;
+      if (hipMemcpy(g_ws_kept[dev][i], &word, sizeof(int), hipMemcpyHostToDevice) != hipSuccess) return GC_ERR_HIP;
+      return GC_ERR_POS_IDX;
+    }
   }
   for (const void* w : ws) {
     if (!w) continue;
-    int word = 0;
     if (hipMemcpy(&word, w, sizeof(int), hipMemcpyDeviceToHost) != hipSuccess) return GC_ERR_HIP;
     if (word) return GC_ERR_POS_IDX;
   }

@@ -286,3 +286,19 @@ def test_targets_masked_by_products_beyond_the_fp32_range(B, P, d):
     p[out, 3] = -3e38
     want = oracle_loss(q, p, r, 1.0, 0.5)
     check_fp32_grade("overflow %dx%dx%d" % (B, P, d), run_ex(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.5), want, q, p, 2.0)
+
+
+def test_replay_after_the_library_has_grown_its_buffer():
+    """The graph of a captured call goes on using the buffer it has recorded."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    grow = """
+gc.gc_loss_and_rep_grad_f32(mk(300, 200), mk(500, 200), r)     # wants a larger buffer
+full = torch.full((1 << 24,), float("nan"), device="cuda")     # where memory that was given back would show
+for k in range(3):"""
+    code = (CAPTURE % root).replace("\nfor k in range(3):", grow)
+    assert "wants a larger" in code
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "replays agree" in r.stdout, r.stdout + r.stderr
