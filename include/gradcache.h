@@ -20,7 +20,9 @@
  *     buffer with hipFree, which waits for the device, unless a captured call
  *     has used it: it then stays allocated for the graph; while `stream` is being
  *     captured into a graph a call that would have to grow it takes the kernels
- *     that fit, or returns GC_ERR_UNSUPPORTED).  Such calls share the buffer, so the library
+ *     that fit, or returns GC_ERR_UNSUPPORTED; on a device without room for it a
+ *     call takes the kernels that need less, to fp32 rounding the same results,
+ *     or returns GC_ERR_HIP).  Such calls share the buffer, so the library
  *     puts them in order: a call made on another stream than the previous one
  *     first waits (on the GPU, through an event) for that one's kernels.  Calls
  *     made while their stream is being captured are not ordered this way and

@@ -220,36 +220,47 @@ constexpr int kMaxKept = 32;   // (more are kept all the same, but gc_check_asyn
 static void* g_ws_kept[64][kMaxKept];
 static int g_ws_nkept[64];
 
-// `have` (with *out) also tells what there is when the answer is GC_ERR_UNSUPPORTED
+// GC_OK with the buffer in *out; else what there is in *out and *have, and GC_ERR_UNSUPPORTED where a capture forbids
+// growing it, GC_ERR_HIP where the device has no room for `need`.
 static int own_workspace(size_t need, hipStream_t stream, void** out, size_t* have) {
   int dev = 0;
+  *out = nullptr;
+  *have = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return GC_ERR_HIP;
   std::lock_guard<std::mutex> lock(g_ws_mutex);
+  int rc = GC_OK;
   if (g_ws_bytes[dev] < need) {
     // growing allocates, and frees the old buffer (which waits for the device): neither is legal while the
     // caller's stream is being captured into a graph
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &cap) != hipSuccess) { (void)hipGetLastError(); cap = hipStreamCaptureStatusNone; }
+    // room that there cannot be is not asked for: the old buffer then stays in use, call after call
+    size_t room = 0, total = 0;
+    if (hipMemGetInfo(&room, &total) != hipSuccess) { (void)hipGetLastError(); room = need; }
     if (cap != hipStreamCaptureStatusNone) {
-      *out = g_ws_ptr[dev];
-      *have = g_ws_bytes[dev];
-      return GC_ERR_UNSUPPORTED;
+      rc = GC_ERR_UNSUPPORTED;
+    } else if (room + (g_ws_recorded[dev] ? 0 : g_ws_bytes[dev]) < need) {
+      rc = GC_ERR_HIP;
+    } else {
+      if (g_ws_ptr[dev] && g_ws_recorded[dev]) {
+        if (g_ws_nkept[dev] < kMaxKept) g_ws_kept[dev][g_ws_nkept[dev]++] = g_ws_ptr[dev];
+      } else if (g_ws_ptr[dev]) {
+        (void)hipFree(g_ws_ptr[dev]);  // waits for work that still uses it
+      }
+      g_ws_ptr[dev] = nullptr;
+      g_ws_bytes[dev] = 0;
+      g_ws_recorded[dev] = false;
+      for (const size_t sz : {align_up(need + need / 4, 1 << 20), align_up(need, 4096)}) {
+        if (hipMalloc(&g_ws_ptr[dev], sz) == hipSuccess) { g_ws_bytes[dev] = sz; break; }
+        (void)hipGetLastError();   // a refused allocation is no error of the launches that follow
+        g_ws_ptr[dev] = nullptr;
+      }
+      if (!g_ws_ptr[dev]) rc = GC_ERR_HIP;
     }
-    if (g_ws_ptr[dev] && g_ws_recorded[dev]) {
-      if (g_ws_nkept[dev] < kMaxKept) g_ws_kept[dev][g_ws_nkept[dev]++] = g_ws_ptr[dev];
-    } else if (g_ws_ptr[dev]) {
-      (void)hipFree(g_ws_ptr[dev]);  // waits for work that still uses it
-    }
-    g_ws_ptr[dev] = nullptr;
-    g_ws_bytes[dev] = 0;
-    g_ws_recorded[dev] = false;
-    size_t sz = align_up(need + need / 4, 1 << 20);
-    if (hipMalloc(&g_ws_ptr[dev], sz) != hipSuccess) return GC_ERR_HIP;
-    g_ws_bytes[dev] = sz;
   }
   *out = g_ws_ptr[dev];
   *have = g_ws_bytes[dev];
-  return GC_OK;
+  return rc;
 }
 
 // Calls that share the library's buffer from different streams are put in order: each call leaves an event behind
@@ -469,13 +480,12 @@ static int simple_loss(gc_dtype dt, const void* q, const void* p, const int32_t*
   LossPlan pl = make_loss_plan(B, P, d, dt, false);
   void* ws = nullptr;
   size_t have = 0;
-  rc = own_workspace(pl.total, (hipStream_t)stream, &ws, &have);
-  if (rc == GC_ERR_UNSUPPORTED) {   // a capture cannot grow the buffer: what fits the one there is?
-    pl = make_loss_plan(B, P, d, dt, false, have);
-    if (!ws || pl.total > have) return rc;
-    rc = GC_OK;
+  while ((rc = own_workspace(pl.total, (hipStream_t)stream, &ws, &have)) != GC_OK) {
+    // a capture cannot grow the buffer: what fits the one there is?  A device without room: what needs less?
+    const LossPlan less = make_loss_plan(B, P, d, dt, false, rc == GC_ERR_UNSUPPORTED ? have : pl.total - 1);
+    if (less.total >= pl.total || (rc == GC_ERR_UNSUPPORTED && (!ws || less.total > have))) return rc;
+    pl = less;
   }
-  if (rc != GC_OK) return rc;
   rc = own_workspace_enter((hipStream_t)stream);
   if (rc != GC_OK) return rc;
   rc = loss_with_plan(pl, dt, q, p, pos_idx, B, P, d, scale, temp, 0, loss, dq, dp, nullptr, nullptr, ws, stream);

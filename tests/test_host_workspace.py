@@ -73,3 +73,30 @@ report(first=first, captured=captured, general=general, later=later, mallocs=stu
     assert got["mallocs"] == 1 and got["frees"] == 0
     assert got["frees_again"] == 1      # the second buffer was in no capture
     assert got["error"] == 0
+
+
+@pytest.mark.parametrize("mib,kernel", [(45, "planes_grad_kernel"), (25, "planes_grad_kernel"), (1, "grad_generic_kernel")])
+def test_first_call_on_a_device_with_little_room(stub, mib, kernel):
+    """512 x 1024 x 768 in fp32 wants 40 MB for packed inputs and partial sums, a quarter more to grow, 22 MB with one split,
+    and needs 0.2 MB of row statistics."""
+    got = run(stub, """
+stub.stub_room(%d * MIB)
+rc = [plain(F32, 512, 1024, 768) for _ in range(3)]
+report(rc=rc, names=stub.stub_launches().decode(), mallocs=stub.stub_mallocs(), frees=stub.stub_frees(), error=stub.stub_last_error(),
+       none=plain(BF16, 4096, 8192, 768), none_error=stub.stub_last_error())
+""" % mib)
+    assert got["rc"] == [0, 0, 0] and kernel in got["names"]
+    assert got["mallocs"] <= 2 and got["frees"] == 0 and got["error"] == 0
+    assert got["none"] == -6 and got["none_error"] == 0      # no kernels of this width need that little
+
+
+def test_a_buffer_that_cannot_grow_stays_in_use(stub):
+    got = run(stub, """
+first = plain(F32, 32, 64, 200)
+stub.stub_room(stub.stub_used() + MIB // 2)
+stub.stub_reset()
+rc = [plain(F32, 512, 1024, 768) for _ in range(3)]
+report(first=first, rc=rc, names=stub.stub_launches().decode(), mallocs=stub.stub_mallocs(), frees=stub.stub_frees(), error=stub.stub_last_error())
+""")
+    assert got["first"] == 0 and got["rc"] == [0, 0, 0] and "grad_generic_kernel" in got["names"]
+    assert got["mallocs"] == 0 and got["frees"] == 0 and got["error"] == 0
