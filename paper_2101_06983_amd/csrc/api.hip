@@ -234,14 +234,12 @@ static int own_workspace(size_t need, hipStream_t stream, void** out, size_t* ha
     // caller's stream is being captured into a graph
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &cap) != hipSuccess) { (void)hipGetLastError(); cap = hipStreamCaptureStatusNone; }
+    size_t room = need, total = 0;
+    if (cap != hipStreamCaptureStatusNone) rc = GC_ERR_UNSUPPORTED;
+    else if (hipMemGetInfo(&room, &total) != hipSuccess) { (void)hipGetLastError(); room = need; }
     // room that there cannot be is not asked for: the old buffer then stays in use, call after call
-    size_t room = 0, total = 0;
-    if (hipMemGetInfo(&room, &total) != hipSuccess) { (void)hipGetLastError(); room = need; }
-    if (cap != hipStreamCaptureStatusNone) {
-      rc = GC_ERR_UNSUPPORTED;
-    } else if (room + (g_ws_recorded[dev] ? 0 : g_ws_bytes[dev]) < need) {
-      rc = GC_ERR_HIP;
-    } else {
+    if (rc == GC_OK && room + (g_ws_recorded[dev] ? 0 : g_ws_bytes[dev]) < need) rc = GC_ERR_HIP;
+    if (rc == GC_OK) {
       if (g_ws_ptr[dev] && g_ws_recorded[dev]) {
         if (g_ws_nkept[dev] < kMaxKept) g_ws_kept[dev][g_ws_nkept[dev]++] = g_ws_ptr[dev];
       } else if (g_ws_ptr[dev]) {

@@ -29,6 +29,7 @@ void stub_reset(void) { names[0] = 0; mallocs = frees = 0; peak = used; }
 
 int hipMalloc(void** out, size_t n) {
   mallocs++;
+  if (capturing) { last_error = 900; return 900; }
   if (n > room - used || blocks == MAXN) { last_error = 2; return 2; }
   if (posix_memalign(out, 4096, n < (1u << 20) ? n : (1u << 20))) return 2;   /* the first part is enough: no kernel writes */
   memset(*out, 0, n < (1u << 20) ? n : (1u << 20));
@@ -39,12 +40,13 @@ int hipMalloc(void** out, size_t n) {
 }
 int hipFree(void* p) {
   frees++;
+  if (capturing) { last_error = 900; return 900; }
   for (int i = 0; i < blocks; i++)
     if (block[i].p == p) { used -= block[i].n; free(p); block[i] = block[--blocks]; return 0; }
   last_error = 1;
   return 1;
 }
-int hipMemGetInfo(size_t* f, size_t* t) { *f = room - used; *t = room; return 0; }
+int hipMemGetInfo(size_t* f, size_t* t) { if (capturing) { last_error = 900; return 900; } *f = room - used; *t = room; return 0; }
 int hipGetLastError(void) { int e = last_error; last_error = 0; return e; }
 int hipGetDevice(int* d) { *d = 0; return 0; }
 int hipDeviceGetAttribute(int* v, int attr, int dev) { (void)attr; (void)dev; *v = 256; return 0; }
