@@ -59,7 +59,7 @@ typedef enum {
   GC_ERR_NULL = -1,        /* a required pointer is NULL */
   GC_ERR_SHAPE = -2,       /* a size is <= 0 / too large, or scale/temp is not a positive finite number */
   GC_ERR_UNSUPPORTED = -3, /* dtype, flag or shape combination not implemented */
-  GC_ERR_WORKSPACE = -4,   /* workspace NULL, misaligned (256 B) or smaller than the *_workspace_bytes value */
+  GC_ERR_WORKSPACE = -4,   /* workspace NULL, misaligned (256 B) or too small (see gc_workspace_bytes) */
   GC_ERR_POS_IDX = -5,     /* reported by gc_check_async_error: some pos_idx[i] was outside [0, P) */
   GC_ERR_HIP = -6,         /* a HIP runtime call failed (launch, allocation) */
   GC_ERR_TOO_LARGE = -7    /* gc_loss_and_rep_grad_bf16_static: the shape needs more scratch than GC_STATIC_SCRATCH_BYTES */
@@ -84,7 +84,11 @@ typedef enum { GC_F32 = 0, GC_BF16 = 1 } gc_dtype;
 /* Text for a gc_status value (host; static storage, never NULL). */
 const char* gc_strerror(int status);
 
-/* Bytes of workspace gc_loss_and_rep_grad_ex needs for this shape (host, pure).
+/* Bytes of workspace gc_loss_and_rep_grad_ex wants for this shape (host, pure).
+ * (This and the other *_workspace_bytes of calls that contain the loss name what
+ * the fastest kernels use.  A smaller workspace is taken while fewer splits, or at
+ * fp32 and general widths kernels without packed inputs, fit it: to fp32 rounding
+ * the same results, and GC_ERR_WORKSPACE below that.)
  * Holds per-row softmax statistics and the split partial sums of dq and dp:
  * O((B + P) * d), never O(B * P) (Sec. "Gradient Cache Technique": the cache is
  * (|S| d + |T| d) numbers).  Returns 0 for an invalid shape. */

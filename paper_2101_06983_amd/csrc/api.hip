@@ -29,7 +29,15 @@ int num_cu() {
   return cached;
 }
 
-static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent, int route, int max_splits, bool few, double parts_limit) {
+// rows per workgroup of the gradient pass when every compute unit gets one and all get an equal share, at least 256
+static long long equal_share(long long rows) {
+  const long long L = (rows + num_cu() - 1) / num_cu();
+  return L < 256 ? 256 : (L + 31) / 32 * 32;
+}
+// few, parts_limit, equal: ROUTE_MFMA.  few: small statistics tiles where the scores are few.  Splits: the fastest whose
+// partials stay below parts_limit bytes, or (equal) the fewest that give every compute unit an equal share of the rows.
+static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent, int route, int max_splits, bool few, double parts_limit,
+                                   bool equal = false) {
   LossPlan pl{};
   const int kNumCU = num_cu();
   pl.route = route;
@@ -90,8 +98,20 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
       }
       if (best_us == 0) consider(B > P ? len_of(B, 1) : len_of(P, 1), walk_q, walk_p, bq, lq, bp, lp);
     };
+    auto share = [&](long long rows, int n, int& ns, int& len) {   // rows: those that all workgroups stream together
+      const long long L = equal_share(rows);
+      ns = (int)((n + L - 1) / L > 16 ? 16 : (n + L - 1) / L);
+      len = len_of(n, ns);
+      ns = ceil_div(n, len);
+    };
     pl.nsq = pl.nsp = 1; pl.q_stream_len = len_of(P, 1); pl.p_stream_len = len_of(B, 1);
-    search(true, !pl.one_walk, pl.nsq, pl.q_stream_len, pl.nsp, pl.p_stream_len);
+    const long long rows_q = obQ * P, rows_p = obP * B, rows_all = pl.one_walk ? rows_q : rows_q + rows_p;
+    if (equal) {
+      share(rows_all, P, pl.nsq, pl.q_stream_len);
+      share(rows_all, B, pl.nsp, pl.p_stream_len);
+    } else {
+      search(true, !pl.one_walk, pl.nsq, pl.q_stream_len, pl.nsp, pl.p_stream_len);
+    }
     if (pl.one_walk) { pl.nsp = 1; pl.p_stream_len = B; }
     // fused mode (workspace is planned for it wherever it can run; fused_auto says where it is also the faster one):
     // each walk is a launch of its own and has to fill the GPU alone
@@ -106,7 +126,10 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
       pl.fz_nsq = pl.nsq; pl.fz_q_stream_len = pl.q_stream_len;
       pl.fz_nsp = pl.nsp; pl.fz_p_stream_len = pl.p_stream_len;
       int unused = 0;
-      if (pl.fused_auto) {
+      if (pl.fused_auto && equal) {
+        share(rows_q, P, pl.fz_nsq, pl.fz_q_stream_len);
+        share(rows_p, B, pl.fz_nsp, pl.fz_p_stream_len);
+      } else if (pl.fused_auto) {
         search(true, false, pl.fz_nsq, pl.fz_q_stream_len, unused, unused);
         search(false, true, unused, unused, pl.fz_nsp, pl.fz_p_stream_len);
       }
@@ -165,42 +188,57 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
 }
 // what the packed inputs and partials may take without being asked about (the rest of a 288 GB card is the caller's)
 constexpr size_t kPlanesMaxBytes = (size_t)32 << 30;
-static LossPlan plan_afresh(int B, int P, int d, gc_dtype dt, bool ntxent, size_t limit) {
+// The plan with the first in order of speed whose workspace `fits` takes; if it takes none, the last.
+template <class Fits>
+static LossPlan choose_plan(int B, int P, int d, gc_dtype dt, bool ntxent, Fits fits) {
   if (dt == GC_BF16 && d % 128 == 0 && d >= 128 && d <= 768) {
-    LossPlan pl = make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_MFMA, 16, true, 1e300);
+    const int own = (d == 128) ? 256 : 64;
+    const long long obQ = ceil_div(B, own), obP = ceil_div(P, own), L = equal_share(obQ * P + (ntxent ? 0 : obP * B));
+    const double parts = ((double)((P + L - 1) / L) * B + (double)((B + L - 1) / L) * P) * d * 4;   // partials of an equal share
+    auto plan = [&](bool few, double parts_limit, bool equal) {
+      return make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_MFMA, 16, few, parts_limit, equal);
+    };
+    LossPlan pl = plan(true, 1e300, false);
     if (pl.total > (size_t)GC_STATIC_SCRATCH_BYTES) {
       // the shapes that the entry point with the fixed array takes do not depend on the splits: those that fit with an
       // equal share of the rows per compute unit, at least 256 of them, get splits that fit
-      const int own = (d == 128) ? 256 : 64;
-      const long long obQ = ceil_div(B, own), obP = ceil_div(P, own), W = obQ * P + (ntxent ? 0 : obP * B);
-      long long L = (W + num_cu() - 1) / num_cu();
-      L = L < 256 ? 256 : (L + 31) / 32 * 32;
-      const double limit = ((double)((P + L - 1) / L) * B + (double)((B + L - 1) / L) * P) * d * 4;
-      const LossPlan lean = make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_MFMA, 16, false, limit);
+      const LossPlan lean = plan(false, parts, false);
       if (lean.total <= (size_t)GC_STATIC_SCRATCH_BYTES) {
-        const LossPlan both = make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_MFMA, 16, true, limit);
-        return both.total <= (size_t)GC_STATIC_SCRATCH_BYTES ? both : lean;
+        const LossPlan both = plan(true, parts, false);
+        pl = both.total <= (size_t)GC_STATIC_SCRATCH_BYTES ? both : lean;
       }
     }
-    return pl;
+    if (fits(pl)) return pl;
+    for (const bool few : {true, false}) {
+      pl = plan(few, parts, false);
+      if (fits(pl)) return pl;
+    }
+    return plan(false, parts, true);
   }
   if (tiny_fits(B, P, d)) return make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_TINY, 1, false, 0.);
   for (int splits = 16; splits >= 1; splits /= 2) {
     const LossPlan pl = make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_PLANES, splits, false, 0.);
-    if (pl.total <= limit && pl.total <= kPlanesMaxBytes) return pl;
+    if (pl.total <= kPlanesMaxBytes && fits(pl)) return pl;
   }
   return make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_GENERAL, 1, false, 0.);
 }
 
-// A plan depends on nothing but these arguments; the last one of a thread is kept (the search over the splits is some
-// microseconds of host time, and a program asks for the same plan call after call).
+// A plan depends on nothing but these arguments; the last ones of a thread, without a limit and with one, are kept (the
+// search over the splits is some microseconds of host time, and a program asks for the same plan call after call).
 LossPlan make_loss_plan(int B, int P, int d, gc_dtype dt, bool ntxent, size_t limit) {
-  static thread_local struct { int B = 0, P, d; gc_dtype dt; bool ntxent; size_t limit; LossPlan pl; } last;
-  if (last.B != B || last.P != P || last.d != d || last.dt != dt || last.ntxent != ntxent || last.limit != limit) {
-    last.pl = plan_afresh(B, P, d, dt, ntxent, limit);
-    last.B = B; last.P = P; last.d = d; last.dt = dt; last.ntxent = ntxent; last.limit = limit;
-  }
-  return last.pl;
+  struct Kept {
+    int B = 0, P, d; gc_dtype dt; bool ntxent; size_t limit; LossPlan pl;
+    const LossPlan& get(int B_, int P_, int d_, gc_dtype dt_, bool ntxent_, size_t limit_) {
+      if (B != B_ || P != P_ || d != d_ || dt != dt_ || ntxent != ntxent_ || limit != limit_) {
+        pl = choose_plan(B_, P_, d_, dt_, ntxent_, [limit_](const LossPlan& p) { return p.total <= limit_; });
+        B = B_; P = P_; d = d_; dt = dt_; ntxent = ntxent_; limit = limit_;
+      }
+      return pl;
+    }
+  };
+  static thread_local Kept whole, limited;
+  const LossPlan& pl = whole.get(B, P, d, dt, ntxent, (size_t)-1);
+  return pl.total <= limit ? pl : limited.get(B, P, d, dt, ntxent, limit);
 }
 
 static bool shape_ok(int B, int P, int d) {
@@ -465,8 +503,9 @@ int gc_loss_and_rep_grad_ex(int dt_int, const void* q, const void* p, const int3
   int rc = check_loss_args(dt_int, q, p, pos_idx, B, P, d, scale, temp, flags);
   if (rc != GC_OK) return rc;
   const gc_dtype dt = (gc_dtype)dt_int;
-  const LossPlan pl = make_loss_plan(B, P, d, dt, false);
-  if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < pl.total) return GC_ERR_WORKSPACE;
+  if (!workspace || ((uintptr_t)workspace & 255)) return GC_ERR_WORKSPACE;
+  const LossPlan pl = make_loss_plan(B, P, d, dt, false, workspace_bytes);
+  if (workspace_bytes < pl.total) return GC_ERR_WORKSPACE;
   return loss_with_plan(pl, dt, q, p, pos_idx, B, P, d, scale, temp, flags, loss, dq, dp, lse, argmax, workspace, stream);
 }
 
@@ -501,7 +540,8 @@ int gc_loss_and_rep_grad_bf16_static(const void* q, const void* p, const int32_t
   int rc = check_loss_args(GC_BF16, q, p, pos_idx, B, P, d, scale, temp, 0);
   if (rc != GC_OK) return rc;
   if (!loss || !dq || !dp) return GC_ERR_NULL;
-  const LossPlan pl = make_loss_plan(B, P, d, GC_BF16, false, (size_t)GC_STATIC_SCRATCH_BYTES);
+  LossPlan pl = make_loss_plan(B, P, d, GC_BF16, false);
+  if (!pl.use_mfma) pl = make_loss_plan(B, P, d, GC_BF16, false, (size_t)GC_STATIC_SCRATCH_BYTES);
   if (pl.total > (size_t)GC_STATIC_SCRATCH_BYTES) return GC_ERR_TOO_LARGE;
   void* ws = nullptr;
   rc = static_scratch(&ws);
@@ -596,8 +636,9 @@ int gc_ntxent_loss_and_grad_bf16(const void* z, int n_views, int d, float temp, 
   if (!z) return GC_ERR_NULL;
   if (n_views < 2 || (n_views & 1) || !shape_ok(n_views, n_views, d)) return GC_ERR_SHAPE;
   if (!(temp > 0.f) || !std::isfinite(temp) || !std::isfinite(1.f / temp)) return GC_ERR_SHAPE;
-  const LossPlan pl = make_loss_plan(n_views, n_views, d, GC_BF16, true);
-  if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < pl.total) return GC_ERR_WORKSPACE;
+  if (!workspace || ((uintptr_t)workspace & 255)) return GC_ERR_WORKSPACE;
+  const LossPlan pl = make_loss_plan(n_views, n_views, d, GC_BF16, true, workspace_bytes);
+  if (workspace_bytes < pl.total) return GC_ERR_WORKSPACE;
   LossArgs a{};
   a.dt = GC_BF16; a.q = z; a.p = z; a.B = n_views; a.P = n_views; a.d = d;
   a.alpha = 1.f / temp; a.flags = GC_MASK_SELF;
@@ -614,9 +655,9 @@ int gc_ntxent_loss_and_grad_bf16(const void* z, int n_views, int d, float temp, 
 // With the MFMA kernels one gradient pass serves both directions: the second workspace then holds statistics only
 // and there are no gradient buffers.  The general widths share the packed inputs and partials between the directions.
 struct SymPlan { LossPlan pl; size_t off2, off_rinv, off_l, off_g, total; };
-static SymPlan make_sym_plan(int n, int d) {
+static SymPlan sym_plan_of(const LossPlan& pl, int n, int d) {
   SymPlan sp{};
-  sp.pl = make_loss_plan(n, n, d, GC_BF16, false);
+  sp.pl = pl;
   size_t off = align_up(sp.pl.total, 256);
   sp.off2 = off; off = align_up(off + (sp.pl.route == ROUTE_GENERAL ? sp.pl.total : sp.pl.off_dq_part), 256);
   sp.off_rinv = off; off = align_up(off + (size_t)n * 4, 256);
@@ -624,6 +665,11 @@ static SymPlan make_sym_plan(int n, int d) {
   sp.off_g = off; off += sp.pl.use_mfma ? 0 : 4 * align_up((size_t)n * d * 4, 256);
   sp.total = off;
   return sp;
+}
+static SymPlan make_sym_plan(int n, int d, size_t limit = (size_t)-1) {
+  const SymPlan sp = sym_plan_of(make_loss_plan(n, n, d, GC_BF16, false), n, d);
+  if (sp.total <= limit) return sp;
+  return sym_plan_of(choose_plan(n, n, d, GC_BF16, false, [=](const LossPlan& pl) { return sym_plan_of(pl, n, d).total <= limit; }), n, d);
 }
 
 size_t gc_bidirectional_workspace_bytes(int n, int d) {
@@ -637,8 +683,9 @@ int gc_bidirectional_loss_and_rep_grad_bf16(const void* q, const void* p, const 
   int rc = check_loss_args(GC_BF16, q, p, pos_idx, n, n, d, scale, temp, 0);
   if (rc != GC_OK) return rc;
   if (!loss || !dq || !dp) return GC_ERR_NULL;
-  const SymPlan sp = make_sym_plan(n, d);
-  if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < sp.total) return GC_ERR_WORKSPACE;
+  if (!workspace || ((uintptr_t)workspace & 255)) return GC_ERR_WORKSPACE;
+  const SymPlan sp = make_sym_plan(n, d, workspace_bytes);
+  if (workspace_bytes < sp.total) return GC_ERR_WORKSPACE;
   char* ws = (char*)workspace;
   hipStream_t s = (hipStream_t)stream;
   int32_t* rinv = (int32_t*)(ws + sp.off_rinv);

@@ -71,8 +71,8 @@ struct LossPlan {
       off_dp_part, off_pos_idx, off_on_ref, off_inv, total;
 };
 
-// limit: bytes of workspace there are.  The calls of ROUTE_PLANES take fewer splits, and then ROUTE_GENERAL, to stay below
-// it (the sequence of the other route does not depend on it: the caller compares `total`).
+// limit: bytes of workspace there are.  To stay below it the calls of ROUTE_MFMA take fewer splits, those of ROUTE_PLANES
+// fewer splits and then ROUTE_GENERAL; what needs the least is returned where nothing fits (the caller compares `total`).
 constexpr int kStatTile = 32;
 LossPlan make_loss_plan(int B, int P, int d, gc_dtype dt, bool ntxent, size_t limit = (size_t)-1);
 void plan_planes(LossPlan& pl, int B, int P, int d, gc_dtype dt, int max_splits);

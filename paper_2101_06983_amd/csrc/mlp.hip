@@ -1054,7 +1054,7 @@ struct StepWs {
   size_t loss_bytes;
 };
 
-static StepWs plan_step(int B, int P, int chunk_q, int chunk_p, const gc_mlp_params* w) {
+static StepWs plan_step(int B, int P, int chunk_q, int chunk_p, const gc_mlp_params* w, size_t limit = (size_t)-1, size_t loss_limit = (size_t)-1) {
   StepWs s{};
   size_t off = 0;
   auto take = [&](size_t b) { size_t o = off; off = up256(off + b); return o; };
@@ -1062,10 +1062,13 @@ static StepWs plan_step(int B, int P, int chunk_q, int chunk_p, const gc_mlp_par
   s.off_p = take((size_t)P * w->dout * 2);
   s.off_dq = take((size_t)B * w->dout * 4);
   s.off_dp = take((size_t)P * w->dout * 4);
-  s.loss_bytes = make_loss_plan(B, P, w->dout, GC_BF16, false).total;
+  s.loss_bytes = make_loss_plan(B, P, w->dout, GC_BF16, false, loss_limit).total;
   s.off_loss = take(s.loss_bytes);
   s.off_mlp = take(carve_mlp_ws(nullptr, step1_ws_rows(B, P, chunk_q, chunk_p), w).total);
   s.total = off;
+  const size_t rest = s.total - s.loss_bytes;
+  if (s.total > limit && limit >= rest && loss_limit == (size_t)-1)   // the loss takes what is left of it
+    return plan_step(B, P, chunk_q, chunk_p, w, limit, limit - rest);
   return s;
 }
 
@@ -1078,7 +1081,7 @@ struct StepCall {
   float* loss;
   gc_mlp_grads grads;
   void* q_rep; void* p_rep; float* dq; float* dp;
-  void* workspace;
+  void* workspace; size_t workspace_bytes;
 };
 
 // enqueues Steps 1-3 on s
@@ -1089,7 +1092,7 @@ static int enqueue_step(const StepCall& c, hipStream_t s) {
   const float scale = c.scale, temp = c.temp;
   float* loss = c.loss; void* q_rep = c.q_rep; void* p_rep = c.p_rep; float* dq = c.dq; float* dp = c.dp;
   void* workspace = c.workspace;
-  const StepWs sw = plan_step(B, P, chunk_q, chunk_p, w);
+  const StepWs sw = plan_step(B, P, chunk_q, chunk_p, w, c.workspace_bytes);
   char* base = (char*)workspace;
   unsigned short* Q = q_rep ? (unsigned short*)q_rep : (unsigned short*)(base + sw.off_q);
   unsigned short* Pm = p_rep ? (unsigned short*)p_rep : (unsigned short*)(base + sw.off_p);
@@ -1602,13 +1605,13 @@ int gc_step_mlp_grouped_bf16(const void* x_q, int B, const void* x_p, int P, con
   if (rc != GC_OK) return rc;
   if (B < 1 || P < 1 || chunk_q < 1 || chunk_p < 1 || B > (1 << 24) || P > (1 << 24)) return GC_ERR_SHAPE;
   if (!(scale > 0.f) || !(temp > 0.f) || !(scale / temp > 0.f) || !(scale / temp < 3.0e38f)) return GC_ERR_SHAPE;
-  const StepWs sw = plan_step(B, P, chunk_q, chunk_p, w);
+  const StepWs sw = plan_step(B, P, chunk_q, chunk_p, w, workspace_bytes);
   if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < sw.total) return GC_ERR_WORKSPACE;
   StepCall c;
   memset(&c, 0, sizeof(c));  // the struct is compared bytewise: no stray padding
   c.x_q = x_q; c.x_p = x_p; c.pos_idx = pos_idx; c.B = B; c.P = P; c.chunk_q = chunk_q; c.chunk_p = chunk_p;
   c.w = *w; c.scale = scale; c.temp = temp; c.loss = loss; c.grads = *grads; c.q_rep = q_rep; c.p_rep = p_rep;
-  c.dq = dq; c.dp = dp; c.workspace = workspace;
+  c.dq = dq; c.dp = dp; c.workspace = workspace; c.workspace_bytes = workspace_bytes;
   return run_step(c, (hipStream_t)stream);
 }
 
@@ -1618,11 +1621,11 @@ int gc_step_mlp_grouped_bf16(const void* x_q, int B, const void* x_p, int P, con
 // (rows a_i = sum_j w_ij g_j) and v = dL/dG (rows sum_i w_ij h_i); then u = A Omega^T and dOmega = F^T A.
 // The weights w_ij live only inside the tiles of the loss kernels.
 struct BilinearWs { size_t off_loss, loss_bytes, off_omT, off_H, off_A, off_part, total; int slices, rows_per_slice; };
-static BilinearWs plan_bilinear(int B, int P, int d) {
+static BilinearWs plan_bilinear(int B, int P, int d, size_t loss_limit = (size_t)-1) {
   BilinearWs w{};
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = up256(off + bytes); return o; };
-  w.loss_bytes = gc_workspace_bytes(B, P, d, GC_BF16);
+  w.loss_bytes = make_loss_plan(B, P, d, GC_BF16, false, loss_limit).total;
   w.off_loss = take(w.loss_bytes);
   w.off_omT = take((size_t)d * d * 2);
   w.off_H = take((size_t)B * d * 2);
@@ -1667,8 +1670,11 @@ int gc_bilinear_loss_and_grads_bf16(const void* q, const void* p, const int32_t*
       !(scale / temp > 0.f))
     return GC_ERR_SHAPE;
   if (d % 128 || d > 768) return GC_ERR_UNSUPPORTED;
-  const BilinearWs w = plan_bilinear(B, P, d);
-  if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < w.total) return GC_ERR_WORKSPACE;
+  if (!workspace || ((uintptr_t)workspace & 255)) return GC_ERR_WORKSPACE;
+  BilinearWs w = plan_bilinear(B, P, d);
+  if (workspace_bytes < w.total && workspace_bytes >= w.total - w.loss_bytes)   // the loss takes what is left of it
+    w = plan_bilinear(B, P, d, workspace_bytes - (w.total - w.loss_bytes));
+  if (workspace_bytes < w.total) return GC_ERR_WORKSPACE;
   char* ws = (char*)workspace;
   hipStream_t s = (hipStream_t)stream;
   unsigned short* omT = (unsigned short*)(ws + w.off_omT);

@@ -6,6 +6,7 @@ import torch
 from paper_2101_06983_amd import binding as gc
 from paper_2101_06983_amd import synth
 from parity import TOL_BF16, TOL_F32, check, check_argmax, check_loss, oracle_loss, relerr, to_np
+from test_host_workspace import SMALLER
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -302,3 +303,40 @@ for k in range(3):"""
     assert "wants a larger" in code
     r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=100)
     assert r.returncode == 0 and "replays agree" in r.stdout, r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("kind,B,P,d,nbytes", SMALLER)
+def test_smaller_workspaces(kind, B, P, d, nbytes):
+    """What serves a call whose workspace is smaller than the named one, and nothing written behind it."""
+    from oracle import gc_oracle as O
+    buf = torch.full((nbytes + 8192,), 0xA5, dtype=torch.uint8, device=DEV)
+    assert buf.data_ptr() % 256 == 0
+    ws = buf[:nbytes]
+    q, p, r = synth.dpr_batch(B, P, d, torch.float32 if kind == "f32" else torch.bfloat16, seed=5400 + d, positive_mix=0.3)
+    tol = TOL_F32 if kind == "f32" or d % 128 or d > 768 else TOL_BF16
+    label = "%s %dx%dx%d in %d" % (kind, B, P, d, nbytes)
+    if kind == "ntxent":
+        z = synth.ntxent_views(B, d, seed=5400)
+        want = oracle_loss(z, z, torch.arange(B, dtype=torch.int32) ^ 1, 1.0, 0.2, mask_self=True)
+        want["dz"] = want["dq"] + want["dp"]
+        loss, dz = gc.gc_ntxent_loss_and_grad_bf16(z.to(DEV), 0.2, ws)
+        got = dict(loss=loss, dz=dz)
+    elif kind == "symmetric":
+        r = torch.from_numpy(np.random.default_rng(B).permutation(B).astype(np.int32))
+        want = O.bidirectional(synth.widen(q), synth.widen(p), r.numpy(), 1.0, 0.5)
+        got = gc.gc_bidirectional_loss_and_rep_grad_bf16(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.5, ws)
+    elif kind == "bilinear":
+        om = (torch.eye(d) + 0.5 * torch.randn(d, d, generator=torch.Generator().manual_seed(d)) * d ** -0.5).to(torch.bfloat16)
+        whole = gc.gc_bilinear_loss_and_grads_bf16(q.to(DEV), p.to(DEV), r.to(DEV), om.to(DEV), 1.0, 0.5)
+        got = gc.gc_bilinear_loss_and_grads_bf16(q.to(DEV), p.to(DEV), r.to(DEV), om.to(DEV), 1.0, 0.5, ws)
+        want = {k: to_np(whole[k]) for k in ("loss", "u", "v", "domega")}   # (that one is held to the oracle elsewhere)
+        want["loss"] = want["loss"][0]
+    else:
+        want = oracle_loss(q, p, r, 1.0, 0.5)
+        got = gc.gc_loss_and_rep_grad_ex(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.5, 0, ("loss", "dq", "dp", "lse"), ws)
+    torch.cuda.synchronize()
+    check_loss(label + " loss", got["loss"].item(), want["loss"], tol)
+    for k in ("dq", "dp", "dz", "lse", "u", "v", "domega"):
+        if k in got and k in want:
+            check(label + " " + k, relerr(to_np(got[k]), want[k]), tol)
+    assert bool((buf[nbytes:] == 0xA5).all())

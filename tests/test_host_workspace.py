@@ -41,6 +41,14 @@ def report(**k):
 """
 
 
+# a workspace smaller than the named one: row statistics only at fp32 and general widths, the splits of an equal share of the
+# rows per compute unit at the widths of the bf16 kernels, and some bytes between (packed inputs with fewer splits)
+SMALLER = [("f32", 512, 1024, 768, 205056), ("f32", 512, 1024, 768, 24 << 20), ("bf16", 300, 260, 1000, 66816), ("f32", 2000, 2500, 200, 249600),
+           ("bf16", 128, 256, 768, 1185024), ("bf16", 690, 1792, 128, 5302528), ("bf16", 2018, 16468, 512, 67486208), ("bf16", 700, 900, 128, 2865152),
+           ("ntxent", 300, 300, 200, 556032), ("ntxent", 1000, 1000, 256, 4169216), ("symmetric", 300, 300, 200, 1111040),
+           ("symmetric", 300, 300, 200, 3 << 20), ("symmetric", 700, 700, 768, 12993280), ("bilinear", 300, 500, 256, 3034368)]
+
+
 @pytest.fixture(scope="module")
 def stub(tmp_path_factory):
     out = str(tmp_path_factory.mktemp("hip") / "libhipstub.so")
@@ -100,3 +108,34 @@ report(first=first, rc=rc, names=stub.stub_launches().decode(), mallocs=stub.stu
 """)
     assert got["first"] == 0 and got["rc"] == [0, 0, 0] and "grad_generic_kernel" in got["names"]
     assert got["mallocs"] == 0 and got["frees"] == 0 and got["error"] == 0
+
+
+def test_a_workspace_smaller_than_the_named_one_is_taken_while_some_kernels_fit_it(stub):
+    """These sizes were the named ones before the kernels that want more; they are what a program may have kept."""
+    got = run(stub, """
+from_list = json.loads(%r)
+def call(kind, B, P, d, n):
+    if kind == "ntxent":
+        return lib.gc_ntxent_loss_and_grad_bf16(X, B, d, 0.1, X, X, X, n, None)
+    if kind == "symmetric":
+        return lib.gc_bidirectional_loss_and_rep_grad_bf16(X, X, X, B, d, 1.0, 1.0, X, X, X, X, n, None)
+    if kind == "bilinear":
+        return lib.gc_bilinear_loss_and_grads_bf16(X, X, X, B, P, d, X, 1.0, 1.0, X, X, X, X, X, n, None)
+    return ex(F32 if kind == "f32" else BF16, B, P, d, n)
+def named(kind, B, P, d):
+    if kind == "ntxent":
+        return lib.gc_ntxent_workspace_bytes(B, d)
+    if kind == "symmetric":
+        return lib.gc_bidirectional_workspace_bytes(B, d)
+    if kind == "bilinear":
+        return lib.gc_bilinear_workspace_bytes(B, P, d)
+    return lib.gc_workspace_bytes(B, P, d, F32 if kind == "f32" else BF16)
+out = []
+for c in from_list:
+    stub.stub_reset()
+    out.append(dict(rc=call(*c), whole=call(*c[:4], named(*c[:4])), named=named(*c[:4]), little=call(*c[:4], 4096), error=stub.stub_last_error()))
+report(out=out)
+""" % json.dumps(SMALLER))
+    for c, o in zip(SMALLER, got["out"]):
+        assert o["rc"] == 0 and o["whole"] == 0 and o["little"] == -4 and o["error"] == 0, (c, o)
+        assert o["named"] > c[4], (c, o)
