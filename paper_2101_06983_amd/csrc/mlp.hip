@@ -16,6 +16,7 @@
 // (2^-9) would sit right at the error budget.
 #include "gc_common.h"
 #include <mutex>
+#include <utility>
 #include <string.h>
 
 namespace gc {
@@ -202,6 +203,7 @@ struct SkinnyArgs {
   unsigned short* Cb; int ldc;       // EP_BIAS: bf16 output; EP_PLAIN: bf16 output if set
   float* Cf;                         // EP_PLAIN: fp32 output if Cb is not set
   float plain_mul;                   // EP_PLAIN: factor on the product (0 means 1)
+  int* beyond; float range;          // EP_PLAIN, if set: [row tile][column tile], a result of the tile is not within +-range
 };
 
 typedef float SkinnyRed[32][33];   // one partial tile; a workgroup holds four
@@ -278,6 +280,7 @@ __global__ void __launch_bounds__(256) mlp_skinny_kernel(SkinnyArgs g0, SkinnyAr
   skinny_product<A_F32, 4>(g.A, g.lda, m0, g.M - 1, g.Bt, g.ldb, n0, g.K, red, tid >> 6);
   __syncthreads();
   const int en = tid & 31, n = n0 + en;
+  bool beyond = false;
 #pragma unroll
   for (int i = 0; i < 4; i++) {
     const int em = (tid >> 5) + 8 * i, mm = m0 + em;
@@ -288,10 +291,16 @@ __global__ void __launch_bounds__(256) mlp_skinny_kernel(SkinnyArgs g0, SkinnyAr
       } else if (EP == EP_BIAS) {
         g.Cb[(size_t)mm * g.ldc + n] = f2bf(sum + bf2f(g.bias[n]));
       } else {   // the product itself
+        const float v = g.plain_mul != 0.f ? sum * g.plain_mul : sum;
         if (g.Cb) g.Cb[(size_t)mm * g.ldc + n] = f2bf(sum);
-        else g.Cf[(size_t)mm * g.ldc + n] = g.plain_mul != 0.f ? sum * g.plain_mul : sum;
+        else g.Cf[(size_t)mm * g.ldc + n] = v;
+        beyond |= !(__builtin_fabsf(v) <= g.range);
       }
     }
+  }
+  if (EP == EP_PLAIN && g.beyond) {
+    beyond = __syncthreads_or(beyond);
+    if (tid == 0) g.beyond[id] = beyond ? 1 : 0;
   }
 }
 
@@ -1188,8 +1197,10 @@ static int run_step(const StepCall& c, hipStream_t s) {
 //   tanh z = 1 - 2 r,   1 - tanh^2 z = 4 r (1 - r).
 // 2^(a + c) = 2^a 2^c: the powers are taken once per row, not once per pair, which leaves one fma and one reciprocal per
 // (pair, k) instead of two additions, an exponential and a reciprocal (both at a quarter of the rate): 112 + 91 us for the
-// two walks of 1024 x 2048 pairs before, 76 + 62 since.  That holds while
-// no power over- or underflows: |a|, |c| <= kDdRange; tiles with a larger value (tanh saturates long before) take the sum.
+// two walks of 1024 x 2048 pairs before, 76 + 62 since.  That holds while 2^a and 2^c are normal numbers, |a|, |c| <=
+// kDdRange (their product over- or underflows only where 2^(a + c) does).  A workgroup with a larger value among its rows or
+// in its range of the other side (the projections leave a word per 32 x 32 values) keeps a and c and takes the sum, at the
+// cost of before: a whole call of saturated rows, 1024 x 2048 at d = 768, 229 us (269 with the earlier kernel), 183 otherwise.
 // One kernel walks the pairs in two roles, each with an owner side whose rows a workgroup keeps in registers and a
 // streamed side that passes through LDS 32 rows at a time:
 //   DD_DA     owner = anchors: d_ij for every pair and, in the same walk, the row's softmax statistics and the sums
@@ -1206,10 +1217,11 @@ static int run_step(const StepCall& c, hipStream_t s) {
 // row add their partial distances with two cross-lane moves, everything else stays in the thread's registers.
 constexpr int DD_OWN = 64, DD_TS = 32;
 enum DdRole { DD_DA = 0, DD_DC = 1 };
-constexpr float kDdRange = 60.f;    // 2^60 2^60 and its reciprocal are normal numbers
+constexpr float kDdRange = 126.f;
 constexpr float kDdMargin = 16.f;   // DD_DA: the reference of a row is raised when a logit exceeds it by more than this
 struct DdArgs {
   const float* own; const float* str;   // [n_own][H], [n_str][H]: 2 log2(e) (A f) resp. (C g), owner and streamed side
+  const int* own_big; const int* str_big;   // [row block of 32][H / 32]: a value there is beyond kDdRange
   const unsigned short* wv;             // [H] bf16: w
   int n_own, n_str, n_oblk, stream_len; // owner blocks; streamed rows per split
   float alpha2, out_scale;              // alpha log2(e); alpha / B
@@ -1234,24 +1246,18 @@ __global__ void __launch_bounds__(256, 2) deepdist_walk_kernel(DdArgs g) {
   __shared__ __attribute__((aligned(16))) float tile[2][DD_TS][H];
   __shared__ float st_lse[2][DD_TS];
   __shared__ int st_pos[2][DD_TS];
-  __shared__ int tile_big[2][4];   // per wave: an owner value or one of the tile it has loaded is out of range
   const int tid = threadIdx.x, o = tid >> 2, kq = tid & 3;
   const int oblk = blockIdx.x % g.n_oblk, split = blockIdx.x / g.n_oblk;
   const int row = oblk * DD_OWN + o, rowc = min(row, g.n_own - 1);
   const int sbeg = split * g.stream_len, send = min(g.n_str, sbeg + g.stream_len);
   const int nt = (send - sbeg + DD_TS - 1) / DD_TS;
 
-  float ea[HQ], wq[HQ];   // 2^a
-  const float* own_row = g.own + (size_t)rowc * H + kq * HQ;
-  bool own_big = false;
+  float ea[HQ], wq[HQ];   // 2^a, or a
 #pragma unroll
   for (int k = 0; k < HQ; k += 4) {
-    const f32x4 v = *(const f32x4*)(own_row + k);
+    const f32x4 v = *(const f32x4*)(g.own + (size_t)rowc * H + kq * HQ + k);
 #pragma unroll
-    for (int e = 0; e < 4; e++) {
-      ea[k + e] = fast_exp2(v[e]);
-      own_big |= !(__builtin_fabsf(v[e]) <= kDdRange);
-    }
+    for (int e = 0; e < 4; e++) ea[k + e] = v[e];
   }
   float w1 = 0.f;
 #pragma unroll
@@ -1279,32 +1285,33 @@ __global__ void __launch_bounds__(256, 2) deepdist_walk_kernel(DdArgs g) {
       pre_lse = g.lse2[t0 + tid]; pre_pos = g.pos_pad[t0 + tid];
     }
   };
+  fetch(0);
+  bool big = false;
+  for (int x = oblk * (DD_OWN / 32) * (H / 32) + tid; x < min((g.n_own + 31) / 32, (oblk + 1) * (DD_OWN / 32)) * (H / 32); x += 256) big |= g.own_big[x] != 0;
+  for (int x = sbeg / 32 * (H / 32) + tid; x < (send + 31) / 32 * (H / 32); x += 256) big |= g.str_big[x] != 0;
+  const bool by_sum = __syncthreads_or(big);
+  if (!by_sum) {
+#pragma unroll
+    for (int k = 0; k < HQ; k++) ea[k] = fast_exp2(ea[k]);
+  }
   auto stash = [&](int buf) __attribute__((always_inline)) {
-    bool big = own_big;
 #pragma unroll
     for (int v = 0; v < LD4; v++) {
       const int e4 = tid + 256 * v, rr = e4 / (H / 4), c4 = e4 % (H / 4);
       // 16-byte piece j of quarter kq sits at piece 4 j + kq: the four threads of a row then read 64 contiguous bytes
       f32x4 p;
 #pragma unroll
-      for (int e = 0; e < 4; e++) {
-        p[e] = fast_exp2(pre[v][e]);
-        big |= !(__builtin_fabsf(pre[v][e]) <= kDdRange);
-      }
+      for (int e = 0; e < 4; e++) p[e] = by_sum ? pre[v][e] : fast_exp2(pre[v][e]);
       *(f32x4*)&tile[buf][rr][4 * ((c4 % (HQ / 4)) * 4 + c4 / (HQ / 4))] = p;
     }
-    const bool any = __builtin_amdgcn_ballot_w64(big) != 0;
-    if ((tid & 63) == 0) tile_big[buf][tid >> 6] = any ? 1 : 0;
     if (ROLE == DD_DC && tid < DD_TS) { st_lse[buf][tid] = pre_lse; st_pos[buf][tid] = pre_pos; }
   };
-  fetch(0);
   stash(0);
   __syncthreads();
   for (int u = 0; u < nt; u++) {
     const int buf = u & 1;
     if (u + 1 < nt) fetch(u + 1);
     const int t0 = sbeg + u * DD_TS, rows = min(DD_TS, send - t0);
-    const bool by_sum = (tile_big[buf][0] | tile_big[buf][1] | tile_big[buf][2] | tile_big[buf][3]) != 0;   // the same in the workgroup
     for (int s_ = 0; s_ < rows; s_++) {
       const float* cs = &tile[buf][s_][4 * kq];
       float rr[HQ], part = 0.f;
@@ -1320,13 +1327,12 @@ __global__ void __launch_bounds__(256, 2) deepdist_walk_kernel(DdArgs g) {
           }
         }
       } else {
-        const float* str_row = g.str + (size_t)min(t0 + s_, g.n_str - 1) * H + kq * HQ;
 #pragma unroll
         for (int k = 0; k < HQ; k += 4) {
-          const f32x4 a4 = *(const f32x4*)(own_row + k), c4 = *(const f32x4*)(str_row + k);
+          const f32x4 c4 = *(const f32x4*)(cs + 4 * k);
 #pragma unroll
           for (int e = 0; e < 4; e++) {
-            const float r = __builtin_amdgcn_rcpf(1.f + fast_exp2(a4[e] + c4[e]));
+            const float r = __builtin_amdgcn_rcpf(1.f + fast_exp2(ea[k + e] + c4[e]));
             rr[k + e] = r;
             part = __builtin_fmaf(wq[k + e], r, part);
           }
@@ -1461,7 +1467,7 @@ __global__ void __launch_bounds__(256) colsum_slices_kernel(const float* __restr
 constexpr int kColsumRows = 32;   // rows per slice, while that is at most 64 slices
 struct DeepWs {
   LossPlan st;                 // the statistics part of a loss workspace (split statistics, lse2, row losses, error word)
-  size_t off_stat, off_a, off_c, off_AT, off_CT, off_da_part, off_e_part, off_dc_part, off_da, off_dc, off_e, off_wpart,
+  size_t off_stat, off_a, off_c, off_big_a, off_big_c, off_AT, off_CT, off_da_part, off_e_part, off_dc_part, off_da, off_dc, off_e, off_wpart,
       off_gpart, off_gpart2, off_pos_r, total;
   int nsa, len_a, nsc, len_c;  // stream splits of the anchor-owner walks / of the target-owner walk
   int slices_b, rps_b, slices_p, rps_p;   // row slices of the two parameter-gradient products
@@ -1488,10 +1494,11 @@ static DeepWs plan_deep(int B, int P, int d, int h) {
   st.use_mfma = 0; st.stat_splits = w.nsa; st.b_pad = (B + 63) / 64 * 64;
   w.off_stat = 0;
   st.off_err = take(256);
-  st.off_part_m = take((size_t)w.nsa * B * 4); st.off_part_l = take((size_t)w.nsa * B * 4); st.off_part_idx = take((size_t)w.nsa * B * 4);
+  st.off_part_m = take((size_t)w.nsa * B * 4); st.off_part_l = take((size_t)w.nsa * B * 4);
   st.off_pos = take((size_t)B * 4); st.off_lse2 = take((size_t)st.b_pad * 4); st.off_pos_pad = take((size_t)st.b_pad * 4);
   st.off_rowloss = take((size_t)B * 4);
   w.off_a = take((size_t)B * h * 4); w.off_c = take((size_t)P * h * 4);
+  w.off_big_a = take((size_t)((B + 31) / 32) * (h / 32) * 4); w.off_big_c = take((size_t)((P + 31) / 32) * (h / 32) * 4);
   w.off_AT = take((size_t)d * h * 2); w.off_CT = take((size_t)d * h * 2);
   w.off_da_part = take((size_t)w.nsa * B * h * 4); w.off_e_part = take((size_t)w.nsa * B * h * 4);
   w.off_dc_part = take((size_t)w.nsc * P * h * 4);
@@ -1741,14 +1748,14 @@ int gc_deepdist_loss_and_grads_bf16(const void* q, const void* p, const int32_t*
   unsigned short* AT = (unsigned short*)(ws + pw.off_AT);
   unsigned short* CT = (unsigned short*)(ws + pw.off_CT);
   // a = 2 log2(e) F A^T, c = 2 log2(e) G C^T (fp32): Bt[n][k] = A[n][k] as stored
-  auto project = [&](const void* x, int rows, const void* M, float* out) {
+  auto project = [&](const void* x, int rows, const void* M, float* out, size_t off_big) {
     SkinnyArgs g{};
     g.A = x; g.lda = d; g.Bt = (const unsigned short*)M; g.ldb = d; g.M = rows; g.N = h; g.K = d; g.Cf = out; g.ldc = h;
-    g.plain_mul = 2.f * kLog2e;
+    g.plain_mul = 2.f * kLog2e; g.beyond = (int*)(ws + off_big); g.range = kDdRange;
     return g;
   };
-  const SkinnyArgs proj_c = project(p, P, C, c2);
-  launch_skinny<false, EP_PLAIN>(project(q, B, A, a2), s, &proj_c);
+  const SkinnyArgs proj_c = project(p, P, C, c2, pw.off_big_c);
+  launch_skinny<false, EP_PLAIN>(project(q, B, A, a2, pw.off_big_a), s, &proj_c);
   {  // A^T, C^T [d][h]
     PrepArgs t{};
     t.tr[0] = {(const unsigned short*)A, AT, h, d};
@@ -1768,7 +1775,7 @@ int gc_deepdist_loss_and_grads_bf16(const void* q, const void* p, const int32_t*
   float* da = (float*)(ws + pw.off_da);
   float* dc = (float*)(ws + pw.off_dc);
   float* e = (float*)(ws + pw.off_e);
-  g.own = a2; g.str = c2; g.n_own = B; g.n_str = P; g.n_oblk = obA; g.stream_len = pw.len_a;
+  g.own = a2; g.str = c2; g.own_big = (const int*)(ws + pw.off_big_a); g.str_big = (const int*)(ws + pw.off_big_c); g.n_own = B; g.n_str = P; g.n_oblk = obA; g.stream_len = pw.len_a;
   g.out_a = (float*)(ws + pw.off_da_part); g.out_e = (float*)(ws + pw.off_e_part); g.pos_r = (float*)(ws + pw.off_pos_r);
   deepdist_walk_kernel<128, DD_DA><<<obA * pw.nsa, 256, 0, s>>>(g);
   if (hipGetLastError() != hipSuccess) return GC_ERR_HIP;
@@ -1788,7 +1795,7 @@ int gc_deepdist_loss_and_grads_bf16(const void* q, const void* p, const int32_t*
   colsum_slices_kernel<<<dim3(h / 32, w_parts), 256, 0, s>>>(e, B, h, w_rows, (float*)(ws + pw.off_wpart));
   if (hipGetLastError() != hipSuccess) return GC_ERR_HIP;
   // targets own, anchors streamed (with their final lse2)
-  g.own = c2; g.str = a2; g.n_own = P; g.n_str = B; g.n_oblk = obC; g.stream_len = pw.len_c;
+  g.own = c2; g.str = a2; std::swap(g.own_big, g.str_big); g.n_own = P; g.n_str = B; g.n_oblk = obC; g.stream_len = pw.len_c;
   g.out_a = (float*)(ws + pw.off_dc_part); g.out_e = nullptr;
   deepdist_walk_kernel<128, DD_DC><<<obC * pw.nsc, 256, 0, s>>>(g);
   if (hipGetLastError() != hipSuccess) return GC_ERR_HIP;

@@ -340,3 +340,37 @@ def test_smaller_workspaces(kind, B, P, d, nbytes):
         if k in got and k in want:
             check(label + " " + k, relerr(to_np(got[k]), want[k]), tol)
     assert bool((buf[nbytes:] == 0xA5).all())
+
+
+@pytest.mark.parametrize("rows", ["within", "one anchor", "one target", "every row"])
+@pytest.mark.parametrize("B,P", [(33, 70), (200, 330)])
+def test_deep_distance_where_the_powers_end(B, P, rows):
+    """Scaled pre-activations up to the largest whose powers of two are normal numbers (126), and beyond on one anchor, one
+    target or everywhere: workgroups that multiply powers beside workgroups that exponentiate sums.  Bound as above."""
+    from oracle import gc_oracle as O
+    d = 128
+    q, p, _ = synth.dpr_batch(B, P, d, torch.float32, seed=5500 + B)
+    om = synth.deep_omega(d)
+    om["C"] = om["A"].clone()
+    r = torch.from_numpy(np.random.default_rng(B).integers(0, P, size=B).astype(np.int32))
+    scaled = lambda x: np.abs(synth.widen(x.to(torch.bfloat16)) @ synth.widen(om["A"]).T).max(axis=1) * 2 / np.log(2.0)  # noqa: E731
+    q *= torch.from_numpy(100.0 / scaled(q)).float()[:, None]      # every row: largest entry 100 (bf16: within half a percent)
+    p *= torch.from_numpy(100.0 / scaled(p)).float()[:, None]
+    if rows == "one anchor":
+        q[B - 2] *= 1.8
+    if rows == "one target":
+        p[P - 3] *= 1.8
+    if rows == "every row":
+        q *= 1.4
+        p *= 1.4
+    p[40] = -q[3]
+    p[P - 1] = -q[B - 2]
+    q, p = q.to(torch.bfloat16), p.to(torch.bfloat16)
+    assert (max(scaled(q).max(), scaled(p).max()) < 126.0) == (rows == "within")
+    om64 = {k: synth.widen(v) for k, v in om.items()}
+    want = O.deep_distance(synth.widen(q), synth.widen(p), synth.widen(r), om64, 1.0, 0.5)
+    out = gc.gc_deepdist_loss_and_grads_bf16(q.to(DEV), p.to(DEV), r.to(DEV), {k: v.to(DEV) for k, v in om.items()}, 1.0, 0.5)
+    torch.cuda.synchronize()
+    check_loss("deep %s loss" % rows, out["loss"].item(), want["loss"], 1e-4)
+    for k in ("u", "v", "dA", "dC", "dw"):
+        check("deep %s %dx%d %s" % (rows, B, P, k), relerr(to_np(out[k]), want[k]), 1e-4)
