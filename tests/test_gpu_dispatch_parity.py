@@ -101,10 +101,11 @@ def test_masked_ntxent_and_symmetric_at_any_width(n, d):
         check("symmetric n=%d d=%d %s" % (n, d, k), relerr(to_np(out[k]), want[k]), TOL_F32)
 
 
-@pytest.mark.parametrize("B,P,d", [(300, 500, 200), (512, 1024, 1000), (2000, 3000, 520)])
+@pytest.mark.parametrize("B,P,d", [(300, 500, 200), (512, 1024, 1000), (2000, 3000, 520), (3000, 4000, 520)])
 def test_static_scratch_takes_every_width_it_took(B, P, d):
-    """Where the packed inputs do not fit the fixed array beside the partials, fewer splits or the general kernels serve
-    the call; the workspace-less entry point takes the same shapes with the room it wants."""
+    """Where the packed inputs do not fit the fixed array beside the partials, fewer splits (the second and third shape) or
+    the general kernels (the last) serve the call; the workspace-less entry point takes the same shapes with the room it
+    wants."""
     q, p, r = synth.dpr_batch(B, P, d, seed=4600 + d, positive_mix=0.3)
     want = oracle_loss(q, p, r, 1.0, 0.5)
     for call in (gc.gc_loss_and_rep_grad_bf16_static, gc.gc_loss_and_rep_grad_bf16):
@@ -151,9 +152,10 @@ def test_capture_with_the_library_buffer_too_small_for_the_packed_inputs():
 
 
 @pytest.mark.parametrize("rows,din,dh,dout", [(33, 192, 128, 128), (96, 64, 384, 256), (127, 128, 256, 128), (128, 320, 256, 128),
-                                              (129, 128, 256, 128), (300, 192, 384, 256), (1500, 64, 128, 128)])
+                                              (129, 128, 256, 128), (300, 192, 384, 256), (1500, 64, 128, 128),
+                                              (2731, 64, 3072, 128)])
 def test_chunk_backward_row_edges(rows, din, dh, dout):
-    """The 32-row tiles and the 64-row tiles of the backward, whole and ragged; inputs of an odd number of 64 columns."""
+    """The 32-row, 64-row and 128-row tiles of the backward, whole and ragged; inputs of an odd number of 64 columns."""
     from oracle import gc_oracle as O
     x, _, _, params = synth.mlp_problem(rows, 1, din, dh, dout, seed=4700 + rows)
     u = torch.from_numpy((np.random.default_rng(rows).standard_normal((rows, dout)) * 1e-3).astype(np.float32))
@@ -374,3 +376,38 @@ def test_deep_distance_where_the_powers_end(B, P, rows):
     check_loss("deep %s loss" % rows, out["loss"].item(), want["loss"], 1e-4)
     for k in ("u", "v", "dA", "dC", "dw"):
         check("deep %s %dx%d %s" % (rows, B, P, k), relerr(to_np(out[k]), want[k]), 1e-4)
+
+
+@pytest.mark.parametrize("B,P,d,dtype", [(3000, 3100, 500, torch.float32), (3000, 3000, 768, torch.float32), (2800, 3000, 1000, torch.float32),
+                                         (3000, 3100, 500, torch.bfloat16), (3000, 3000, 700, torch.bfloat16), (3000, 3000, 1000, torch.bfloat16),
+                                         (2000, 2100, 1300, torch.bfloat16)])
+def test_large_batches_of_larger_widths(B, P, d, dtype):
+    """64 owner rows per workgroup with four, six and eight column tiles per wave, of which owner rows are staged in part; the
+    larger statistics kernel with owner rows beyond what it stages (from 24 k-steps of fp32, 76 of bf16 on)."""
+    q, p, r = synth.dpr_batch(B, P, d, dtype, seed=5600 + d, positive_mix=0.3)
+    want = oracle_loss(q, p, r, 1.0, 0.25)
+    check_fp32_grade("%dx%dx%d %s" % (B, P, d, dtype), run_ex(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.25), want, q, p, 4.0)
+
+
+@pytest.mark.parametrize("n,d", [(1200, 130), (3000, 200)])
+def test_masked_ntxent_and_symmetric_above_the_few_scores(n, d):
+    """The larger statistics kernel, and the gradients with 32 and 64 owner rows per workgroup, with the diagonal masked."""
+    from oracle import gc_oracle as O
+    q, p, _ = synth.dpr_batch(n, n, d, torch.float32, seed=5700 + n, positive_mix=0.2)
+    r = torch.arange(n, dtype=torch.int32) ^ 1
+    want = oracle_loss(q, p, r, 1.0, 0.5, mask_self=True)
+    check_fp32_grade("mask n=%d d=%d" % (n, d), run_ex(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.5, gc.GC_MASK_SELF), want, q, p, 2.0)
+    z = synth.ntxent_views(n, d, seed=5710)
+    want = oracle_loss(z, z, r, 1.0, 0.2, mask_self=True)
+    loss, dz = gc.gc_ntxent_loss_and_grad_bf16(z.to(DEV), 0.2)
+    torch.cuda.synchronize()
+    check_loss("ntxent n=%d d=%d" % (n, d), loss.item(), want["loss"], TOL_F32)
+    check("ntxent n=%d d=%d dz" % (n, d), relerr(to_np(dz), want["dq"] + want["dp"]), TOL_F32)
+    q, p = q.to(torch.bfloat16), p.to(torch.bfloat16)
+    perm = torch.from_numpy(np.random.default_rng(n).permutation(n).astype(np.int32))
+    want = O.bidirectional(synth.widen(q), synth.widen(p), perm.numpy(), 1.0, 0.5)
+    out = gc.gc_bidirectional_loss_and_rep_grad_bf16(q.to(DEV), p.to(DEV), perm.to(DEV), 1.0, 0.5)
+    torch.cuda.synchronize()
+    check_loss("symmetric n=%d d=%d" % (n, d), out["loss"].item(), want["loss"], TOL_F32)
+    for k in ("dq", "dp"):
+        check("symmetric n=%d d=%d %s" % (n, d, k), relerr(to_np(out[k]), want[k]), TOL_F32)

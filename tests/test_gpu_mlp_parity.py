@@ -191,25 +191,42 @@ def test_config5_full_size():
     assert torch.equal(out["q"], again["q"]) and torch.equal(out["dp"], again["dp"])
 
 
-@pytest.mark.parametrize("B,P,cq,cp,group", [(512, 1024, 32, 32, 8), (200, 330, 32, 64, 3), (96, 96, 16, 32, 4)])
-def test_accumulate_group_keeps_the_bits(B, P, cq, cp, group):
-    """Step 3 on groups of sub-batches (gc_step_mlp_grouped_bf16) reads and writes the gradient accumulators once per
-    group; the sub-batches are still added in index order and in the same 32-row pieces: bit-identical to the
-    ungrouped call (the last case has a sub-batch size that is no multiple of 32 and runs ungrouped)."""
-    if (B, P) == (512, 1024):
-        xq, xp, r, params = synth.mlp_problem()
-    else:
-        xq, xp, r, params = synth.mlp_problem(B, P, 128, 256, 128, seed=synth.SEED0 + 70 + B)
+@pytest.mark.parametrize("B,P,cq,cp,group", [(200, 330, 32, 64, 3), (96, 96, 16, 32, 8)])
+def test_accumulate_group_is_accepted_and_changes_nothing(B, P, cq, cp, group):
+    """Step 3 takes as many whole sub-batches at a time as the activation buffer of Step 1 holds, whatever the argument says."""
+    xq, xp, r, params = synth.mlp_problem(B, P, 128, 256, 128, seed=synth.SEED0 + 70 + B)
     dp = dev_params(params)
     one = gc.gc_step_mlp_bf16(xq.to(DEV), xp.to(DEV), r.to(DEV), cq, cp, dp, keep=True)
     grp = gc.gc_step_mlp_bf16(xq.to(DEV), xp.to(DEV), r.to(DEV), cq, cp, dp, keep=True, accumulate_group=group)
     torch.cuda.synchronize()
-    assert torch.equal(one["loss"], grp["loss"])
-    for k in ("q", "p", "dq", "dp"):
-        assert torch.equal(one[k], grp[k]), k
+    assert torch.equal(one["loss"], grp["loss"]) and float(one["grads"]["W1"].abs().max()) > 0
     for k in ("W1", "b1", "W2", "b2"):
         assert torch.equal(one["grads"][k], grp["grads"][k]), k
-    assert float(one["grads"]["W1"].abs().max()) > 0
+
+
+@pytest.mark.parametrize("B,P,dh,chunks", [(300, 4200, 128, [(24, 48), (500, 33), (300, 4200)]), (4200, 300, 256, [(48, 24), (2100, 64)]),
+                                           (700, 1300, 4096, [(64, 64)])])
+def test_step3_in_several_runs(B, P, dh, chunks):
+    """A side above what the activation buffer holds (2048 rows, or 8 sub-batches) goes through Step 3 in runs that add to
+    the gradients of the earlier ones: three and two runs of one side by the sub-batch size, one run with a single
+    sub-batch; both sides in one run with the 128-row tiles (the last shape).  Gradients are added to what is there."""
+    xq, xp, r, params = synth.mlp_problem(B, P, 64, dh, 128, seed=synth.SEED0 + 80 + dh)
+    dp = dev_params(params)
+    start = 2.0 ** -7
+    first = None
+    for cq, cp in chunks:
+        grads = {k: torch.full(v.shape, start, dtype=torch.float32, device=DEV) for k, v in params.items()}
+        out = gc.gc_step_mlp_bf16(xq.to(DEV), xp.to(DEV), r.to(DEV), cq, cp, dp, 1.0, 0.2, grads=grads, keep=True)
+        torch.cuda.synchronize()
+        for k in grads:
+            grads[k] -= start
+        stagewise("%dx%d step in %d/%d" % (B, P, cq, cp), out, xq, xp, r, params, cq, cp, 1.0, 0.2)
+        if first is None:
+            first = out
+        for k in ("q", "p", "dq", "dp"):   # nothing before Step 3 depends on the sub-batches
+            assert torch.equal(out[k], first[k]), k
+        for k in grads:   # the same terms in the same order but for where a run ends: fp32 rounding of the sums
+            check("%dx%d d%s, %d/%d" % (B, P, k, cq, cp), relerr(to_np(grads[k]), to_np(first["grads"][k])), 1e-5 + 2.0 ** -31 / float(grads[k].abs().max()))
 
 
 def test_step_replayed_with_the_same_buffers_matches_the_first_call():
