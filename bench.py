@@ -130,7 +130,7 @@ def side_workload(args, gc, synth, dev):
         step = lambda: gc.gc_step_mlp_bf16(xq, xp, r, 32, 32, params, out=res, accumulate_group=G)   # same buffers every step
         rows = 512 + 1024
         flops = rows * 2.0 * (1024 * 3072 + 3072 * 768) * 4 + 6.0 * 512 * 1024 * 768   # fwd + (re-fwd layer 1, 3 bwd GEMMs) + loss
-        what = "Gradient Cache step, MLP 1024-3072-768, B=512 P=1024, chunk 32, accumulate_group %d" % G
+        what = "Gradient Cache step, MLP 1024-3072-768, B=512 P=1024, chunk 32"
     for _ in range(args.warmup):
         step()
     torch.cuda.synchronize()
@@ -160,7 +160,7 @@ def main():
     ap.add_argument("--workload", default="config3", choices=["config3", "config2", "config4", "config5", "bidir", "bilinear", "deepdist"],
                     help="config3 (default) is the headline workload; the others print a shorter timing line")
     ap.add_argument("--accumulate-group", type=int, default=1,
-                    help="config5 only: sub-batches per launch of Step 3 (1 = the sub-batch is the unit, as in the method)")
+                    help="config5 only: passed on; Step 3 takes as many whole sub-batches at a time as its buffer holds, whatever it is")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="also run a plain elementwise kernel 4 times that reads 1 GiB and writes 1 GiB (known HBM "
                          "traffic, larger than the 256 MB Infinity Cache; scales rocprofv3 FETCH_SIZE / WRITE_SIZE)")

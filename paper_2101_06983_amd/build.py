@@ -64,8 +64,8 @@ def build(force=True, extra_flags=(), verbose=False):
 def build_host_checked(out, bdir):
     """A second library whose HOST code carries UndefinedBehaviorSanitizer checks that abort at the first finding
     (device code is unchanged: the sanitizer does not exist for it).  For the argument-check tests, which need no
-    GPU.  api.hip, mlp.hip and loss_generic.hip are compiled again with the checks; the object of loss_mfma.hip,
-    minutes of device compilation and no argument checks of its own, is taken from the ordinary build."""
+    GPU.  Every source but loss_mfma.hip is compiled again with the checks; the object of that one, minutes of device
+    compilation and no argument checks of its own, is taken from the ordinary build."""
     mfma = os.path.join(ROOT, "_build", "loss_mfma.o")
     if not os.path.exists(mfma):
         raise FileNotFoundError(mfma)

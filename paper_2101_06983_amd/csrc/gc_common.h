@@ -30,9 +30,6 @@ __device__ __forceinline__ unsigned short f2bf(float f) {
   u += 0x7fffu + ((u >> 16) & 1u);
   return (unsigned short)(u >> 16);
 }
-__device__ __forceinline__ unsigned pack2bf(float lo, float hi) {
-  return (unsigned)f2bf(lo) | ((unsigned)f2bf(hi) << 16);
-}
 __device__ __forceinline__ float bf2f(unsigned short b) { return __builtin_bit_cast(float, (unsigned)b << 16); }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -54,10 +51,10 @@ struct LossPlan {
   int one_walk;          // NT-Xent on the MFMA kernels: dz from a single walk (no dP role, no dP partials)
   int stat_splits;       // column (target) ranges of the statistics pass
   int stat_cols_per_split;
-  int stat_tile;         // ROUTE_MFMA: 0 = the 256 x 256 (d = 128: 256-anchor) kernels, else the kernel for few scores (kStatTile)
+  int stat_tile;         // the kernel for few scores (kStatTile); 0: ROUTE_MFMA the 256 x 256 (d = 128: 256-anchor) kernels, ROUTE_PLANES the larger one
   int nsq, nsp;          // stream splits of the dQ-role / dP-role workgroups of the gradient pass
   int q_stream_len, p_stream_len;  // stream rows per split (multiple of the stream tile)
-  int b_pad;             // B rounded up to 64: length of the padded lse2 / pos_pad arrays
+  int b_pad;             // B rounded up to 64 (ROUTE_PLANES: 128): length of the padded lse2 / pos_pad arrays
   // fused mode (MFMA kernels, d >= 256, dQ wanted): no statistics pass; an online-statistics dQ walk, a kernel that
   // merges its splits into lse2 and dQ, then the dP walk.  Each walk fills the GPU alone, so they have splits of their own
   int fused, fused_auto, fz_nsq, fz_nsp, fz_q_stream_len, fz_p_stream_len;   // can run / is chosen without a flag

@@ -1,8 +1,9 @@
 // What every kernel sequence of the loss / representation-gradient path shares -- the merge of split row statistics, the
 // loss reduction, the fixed-order sum of split gradient partials -- and the general kernels (any d, fp32 or bf16 storage,
 // fp32 FMA arithmetic) for calls whose workspace is limited (the fixed array of the entry point that allocates nothing,
-// the library's buffer during a capture): they need no packed inputs and no partials, and are some hundred times slower
-// than those of loss_planes.hip (5.76 ms against 77 us at B = 512, P = 1024, d = 768 in fp32).
+// the library's buffer during a capture or on a full card, a workspace smaller than the named one): they need no packed
+// inputs and no partials, and are some hundred times slower than those of loss_planes.hip (5.76 ms against 62 us at
+// B = 512, P = 1024, d = 768 in fp32).
 //
 // Scores are kept in the base-2 domain: t_ij = s_ij * log2(e), so that
 // softmax_j = 2^(t_ij - lse2_i) with lse2_i = log2 sum_j 2^t_ij (Eq. 4).

@@ -392,6 +392,7 @@ __global__ void __launch_bounds__(256) planes_stats_small_kernel(StatsSmallArgs 
 // time.  Per step each wave forms the scores of 32 of those rows against the owner rows over the whole width, turns them
 // into coefficients g = 2^(t - lse2) - [j = r_i] (fp32, Eq. 5 / Eq. 6) and publishes them as three bf16 planes of
 // ready-made A fragments; then every wave multiplies all 128 rows' coefficients with its own column tiles (w, w + 4, ..).
+// (Registers spilled: 15 by <3, 1, 2>, fp32 of 129 to 256 columns, and 16 by <1, 2, 8>; none by the others.)
 struct PlanesRole {
   const unsigned short* own_k; const unsigned short* str_k; const unsigned short* str_t;
   int n_own, n_str;         // valid rows

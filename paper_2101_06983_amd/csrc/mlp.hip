@@ -30,27 +30,6 @@ __device__ __forceinline__ float gelu_prime_f(float h) {
   return 0.5f * (1.f + erff(h * 0.70710678118654752f)) + h * 0.3989422804014327f * __expf(-0.5f * h * h);
 }
 
-// 8 consecutive elements starting at index idx as packed bf16.  fp32 source: hi = bf16(v) and
-// lo = bf16(v - hi); bf16 source: lo is unused.
-template <bool F32>
-__device__ __forceinline__ void load8(const void* base, size_t idx, bool live, u32x4& hi, u32x4& lo) {
-  hi = u32x4{0u, 0u, 0u, 0u};
-  lo = hi;
-  if (!live) return;
-  if (F32) {
-    const f32x4* p = (const f32x4*)((const float*)base + idx);
-    f32x4 a = p[0], b = p[1];
-    typedef __attribute__((ext_vector_type(8))) float f32x8;
-    f32x8 v = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-    bf16x8 h = __builtin_convertvector(v, bf16x8);
-    f32x8 r = v - __builtin_convertvector(h, f32x8);
-    hi = __builtin_bit_cast(u32x4, h);
-    lo = __builtin_bit_cast(u32x4, __builtin_convertvector(r, bf16x8));
-  } else {
-    hi = *(const u32x4*)((const unsigned short*)base + idx);
-  }
-}
-
 // C[M x N] = A^T B over the rows (K): A [K][M] (bf16 or fp32), B [K][N] (fp32 or bf16), C fp32.
 struct WgradArgs {
   const void* A; int lda;   // elements
@@ -694,7 +673,7 @@ __global__ void __launch_bounds__(512) mlp_dh_skinny_kernel(DhArgs g) {
 }
 
 // Many rows: BM x 128 tiles, both contractions through the tiled main loop.
-// (64-row tiles: three workgroups per unit with a few registers spilled, 62 us for the 576 tiles of 1536 rows x 3072; two
+// (64-row tiles: three workgroups per unit, 168 registers and 76 spilled, 62 us for the 576 tiles of 1536 rows x 3072; two
 // without spills leave a second, nearly empty round, 68 us)
 template <int BM>
 __global__ void __launch_bounds__(256, BM == 64 ? 3 : 1) mlp_dh_tiled_kernel(DhArgs g) {
@@ -1466,7 +1445,7 @@ __global__ void __launch_bounds__(256) colsum_slices_kernel(const float* __restr
 
 constexpr int kColsumRows = 32;   // rows per slice, while that is at most 64 slices
 struct DeepWs {
-  LossPlan st;                 // the statistics part of a loss workspace (split statistics, lse2, row losses, error word)
+  LossPlan st;                 // split statistics, lse2, row losses, error word
   size_t off_stat, off_a, off_c, off_big_a, off_big_c, off_AT, off_CT, off_da_part, off_e_part, off_dc_part, off_da, off_dc, off_e, off_wpart,
       off_gpart, off_gpart2, off_pos_r, total;
   int nsa, len_a, nsc, len_c;  // stream splits of the anchor-owner walks / of the target-owner walk
@@ -1489,7 +1468,7 @@ static DeepWs plan_deep(int B, int P, int d, int h) {
   dd_split(obC, B, w.nsc, w.len_c);
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = up256(off + bytes); return o; };
-  // statistics, laid out as the loss kernels' merge expects them
+  // statistics, where the sum of the row losses (LossSum) looks for them
   LossPlan& st = w.st;
   st.use_mfma = 0; st.stat_splits = w.nsa; st.b_pad = (B + 63) / 64 * 64;
   w.off_stat = 0;
