@@ -16,7 +16,8 @@
  *   - The caller owns every buffer, the workspace included; the library frees
  *     nothing the caller passed.  gc_loss_and_rep_grad_bf16 / _f32 take no
  *     workspace argument: they use a per-device buffer the library allocates
- *     with hipMalloc on first use and grows on demand (growing frees the old
+ *     with hipMalloc on first use and grows on demand (to what gc_workspace_bytes
+ *     names and a quarter more, held until the process ends; growing frees the old
  *     buffer with hipFree, which waits for the device, unless a captured call
  *     has used it: it then stays allocated for the graph; while `stream` is being
  *     captured into a graph a call that would have to grow it takes the kernels

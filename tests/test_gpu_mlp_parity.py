@@ -251,3 +251,21 @@ def test_step_replayed_with_the_same_buffers_matches_the_first_call():
         assert torch.equal(out["dq"], ref_dq), rep
         for k in ref:
             assert torch.equal(out["grads"][k], ref[k]), (rep, k)
+
+
+def test_step_with_a_workspace_that_leaves_the_loss_less_than_it_wants():
+    """dout = 896 takes the loss kernels with packed inputs; without room for them the general kernels, in 0.1 MB."""
+    import ctypes
+    B, P, c = 300, 500, 32
+    xq, xp, r, params = synth.mlp_problem(B, P, 64, 128, 896, seed=synth.SEED0 + 95)
+    dp = dev_params(params)
+    lib, w = gc.load(), gc.make_mlp_params(dp)
+    named = lib.gc_step_mlp_workspace_bytes(B, P, c, c, ctypes.byref(w))
+    nbytes = named - lib.gc_workspace_bytes(B, P, 896, gc.GC_BF16) + 120576   # row statistics
+    buf = torch.full((nbytes + 8192,), 0xA5, dtype=torch.uint8, device=DEV)
+    out = gc.gc_step_mlp_bf16(xq.to(DEV), xp.to(DEV), r.to(DEV), c, c, dp, 1.0, 0.2, keep=True, workspace=buf[:nbytes])
+    torch.cuda.synchronize()
+    stagewise("step in %d of %d" % (nbytes, named), out, xq, xp, r, params, c, c, 1.0, 0.2)
+    assert bool((buf[nbytes:] == 0xA5).all())
+    with pytest.raises(gc.GradCacheError):
+        gc.gc_step_mlp_bf16(xq.to(DEV), xp.to(DEV), r.to(DEV), c, c, dp, 1.0, 0.2, workspace=buf[:nbytes - 256])
