@@ -320,8 +320,10 @@ __device__ __forceinline__ void add_shared_positives(f32x4& acc, const PosFix& f
 }
 // Four elements per thread.  Bound by memory: 88 MB in 16 us for the dP sums of 4096 x 8192 x 768, most of it out of the
 // memory-side cache, with eight waves per SIMD (18.5 us with six or with 8 elements per thread).
-// (Results stored, or partials loaded, past the caches: no faster at 4096 x 8192 x 768, 245.3 and 245.2 us against 245.5,
-// and whoever reads dq and dp next waits longer: 258.6 us with a cast of both behind the call, 256.8 with plain stores.)
+// Partials are loaded past the caches, results stored through them.  With inputs that change from call to call the loads
+// matter, 241.1 us against 247.3 at 4096 x 8192 x 768 (324 and 337 for the bilinear loss); results stored past the caches as
+// well gain nothing there (241.4) and 1 % at 1021 x 4099 x 384 (63.8 and 64.4), but whoever reads dq and dp next pays for it:
+// with a cast of both behind the call 258.6 and 256.8 us, 72.1 and 71.5.
 // (JOBS = 1: every argument sits at a known place, so they are all loaded at once; picking one of two costs 2 us here.)
 template <int JOBS>
 __global__ void __launch_bounds__(256, 8) partial_reduce_kernel(ReduceArgs a) {
@@ -346,11 +348,11 @@ __global__ void __launch_bounds__(256, 8) partial_reduce_kernel(ReduceArgs a) {
     for (; k + 4 <= j.count[0]; k += 4) {   // four loads in flight, added in order
       f32x4 v[4];
 #pragma unroll
-      for (int i = 0; i < 4; i++) v[i] = ((const f32x4*)(j.ptr[0] + (size_t)(k + i) * j.stride[0]))[e];
+      for (int i = 0; i < 4; i++) v[i] = __builtin_nontemporal_load((const f32x4*)(j.ptr[0] + (size_t)(k + i) * j.stride[0]) + e);
 #pragma unroll
       for (int i = 0; i < 4; i++) acc += v[i];
     }
-    for (; k < j.count[0]; k++) acc += ((const f32x4*)(j.ptr[0] + (size_t)k * j.stride[0]))[e];
+    for (; k < j.count[0]; k++) acc += __builtin_nontemporal_load((const f32x4*)(j.ptr[0] + (size_t)k * j.stride[0]) + e);
     if (j.nsrc > 1)
       for (int k = 0; k < j.count[1]; k++) acc += ((const f32x4*)(j.ptr[1] + (size_t)k * j.stride[1]))[e];
   }
@@ -460,7 +462,7 @@ __global__ void __launch_bounds__(256) online_finish_kernel(FinishArgs f) {
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < 16; s++)
-      if (s < f.nsq) acc += w[s] * ((const f32x4*)(f.part + (size_t)s * f.part_stride + (size_t)i * f.d))[c];
+      if (s < f.nsq) acc += w[s] * __builtin_nontemporal_load((const f32x4*)(f.part + (size_t)s * f.part_stride + (size_t)i * f.d) + c);
     const s16x4 pv = ((const s16x4*)(f.P + (size_t)r_safe * f.d))[c];
 #pragma unroll
     for (int e = 0; e < 4; e++) acc[e] += cpos * bf2f((unsigned short)pv[e]);
