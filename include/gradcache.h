@@ -43,7 +43,8 @@
  *   - loss, dq, dp, dz, lse, argmax, y are overwritten; gc_mlp_grads buffers are
  *     accumulated into (+=).
  *   - Same inputs give bit-identical outputs from run to run (no atomics, fixed
- *     reduction order).
+ *     reduction order), as long as the same kernels serve the call: a smaller
+ *     workspace, a capture or a full device can put it on others.
  */
 #ifndef GRADCACHE_H
 #define GRADCACHE_H
