@@ -1179,7 +1179,7 @@ static int run_step(const StepCall& c, hipStream_t s) {
 // two walks of 1024 x 2048 pairs before, 76 + 62 since.  That holds while 2^a and 2^c are normal numbers, |a|, |c| <=
 // kDdRange (their product over- or underflows only where 2^(a + c) does).  A workgroup with a larger value among its rows or
 // in its range of the other side (the projections leave a word per 32 x 32 values) keeps a and c and takes the sum, at the
-// cost of before: a whole call of saturated rows, 1024 x 2048 at d = 768, 229 us (269 with the earlier kernel), 183 otherwise.
+// cost of before: a whole call of saturated rows, 1024 x 2048 at d = 768, 229 us (269 with the earlier kernel), 181 otherwise.
 // One kernel walks the pairs in two roles, each with an owner side whose rows a workgroup keeps in registers and a
 // streamed side that passes through LDS 32 rows at a time:
 //   DD_DA     owner = anchors: d_ij for every pair and, in the same walk, the row's softmax statistics and the sums
@@ -1265,9 +1265,11 @@ __global__ void __launch_bounds__(256, 2) deepdist_walk_kernel(DdArgs g) {
     }
   };
   fetch(0);
+  constexpr int HB = H / 32;   // words per row block
+  const int own_words = min((g.n_own + 31) / 32 - oblk * (DD_OWN / 32), DD_OWN / 32) * HB, str_words = ((send + 31) / 32 - sbeg / 32) * HB;
   bool big = false;
-  for (int x = oblk * (DD_OWN / 32) * (H / 32) + tid; x < min((g.n_own + 31) / 32, (oblk + 1) * (DD_OWN / 32)) * (H / 32); x += 256) big |= g.own_big[x] != 0;
-  for (int x = sbeg / 32 * (H / 32) + tid; x < (send + 31) / 32 * (H / 32); x += 256) big |= g.str_big[x] != 0;
+  for (int x = tid; x < own_words + str_words; x += 256)   // (once, but for very long ranges)
+    big |= *(x < own_words ? g.own_big + oblk * (DD_OWN / 32) * HB + x : g.str_big + sbeg / 32 * HB + (x - own_words)) != 0;
   const bool by_sum = __syncthreads_or(big);
   if (!by_sum) {
 #pragma unroll
