@@ -846,7 +846,7 @@ struct MlpWs {
   float* part;          // forward: rows x dh floats for the partial products of the second layer
   unsigned short* W1T;  // [dh][din] bf16: W1 transposed
   unsigned short* W2T;  // [dout][dh] bf16: W2 transposed
-  size_t total;
+  size_t total, forward;   // bytes; those that a forward uses
 };
 // rows that RowSpan and the tiles of the backward may add: up to 31 between the inputs, up to 127 behind
 constexpr int kSpanPad = 160;
@@ -866,6 +866,7 @@ static MlpWs carve_mlp_ws(char* base, int rows, const gc_mlp_params* w) {
   const size_t one = up256((size_t)rows * w->dh * 4);
   m.ActF = (float*)at(off);
   m.part = (float*)at(off + one);
+  m.forward = off + 2 * one;
   const size_t row = backward_row_bytes(w), more = row > (size_t)w->dh * 12 ? (row - (size_t)w->dh * 12) * rows : 0;
   off += 3 * one + up256(more) + up256(row * kSpanPad) + 6 * 256;
   m.total = off;
@@ -1546,7 +1547,7 @@ int gc_mlp_forward_nograd_bf16(const void* x, int rows, const gc_mlp_params* w, 
   int rc = check_mlp_params(w);
   if (rc != GC_OK) return rc;
   if (rows < 1 || rows > (1 << 24)) return GC_ERR_SHAPE;
-  if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < carve_mlp_ws(nullptr, rows, w).total)
+  if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < carve_mlp_ws(nullptr, rows, w).forward)
     return GC_ERR_WORKSPACE;
   const MlpWs ws = carve_mlp_ws((char*)workspace, rows, w);
   if (mlp_prepare(w, ws, (hipStream_t)stream) != hipSuccess) return GC_ERR_HIP;

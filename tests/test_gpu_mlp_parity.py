@@ -269,3 +269,16 @@ def test_step_with_a_workspace_that_leaves_the_loss_less_than_it_wants():
     assert bool((buf[nbytes:] == 0xA5).all())
     with pytest.raises(gc.GradCacheError):
         gc.gc_step_mlp_bf16(xq.to(DEV), xp.to(DEV), r.to(DEV), c, c, dp, 1.0, 0.2, workspace=buf[:nbytes - 256])
+
+
+@pytest.mark.parametrize("rows,dh", [(33, 256), (200, 512), (200, 2048)])
+def test_forward_in_the_bytes_it_uses(rows, dh):
+    """The transposed weights and two activations (the second for the partial products of the narrow layer: all of it at
+    dh = 512), nothing behind them."""
+    xq, _, _, params = small_problem(B=rows, dh=dh)
+    nbytes = (128 * dh + dh * 128) * 2 + 2 * rows * dh * 4
+    buf = torch.full((nbytes + 8192,), 0xA5, dtype=torch.uint8, device=DEV)
+    y = gc.gc_mlp_forward_nograd_bf16(xq.to(DEV), dev_params(params), workspace=buf[:nbytes])
+    torch.cuda.synchronize()
+    check("forward in %d bytes" % nbytes, relerr(to_np(y), O.mlp_forward(synth.widen(xq), widen_params(params))), TOL_STORED)
+    assert bool((buf[nbytes:] == 0xA5).all())

@@ -139,3 +139,21 @@ report(out=out)
     for c, o in zip(SMALLER, got["out"]):
         assert o["rc"] == 0 and o["whole"] == 0 and o["little"] == -4 and o["error"] == 0, (c, o)
         assert o["named"] > c[4], (c, o)
+
+
+def test_a_forward_needs_the_transposed_weights_and_two_activations_only(stub):
+    """The named size also covers the fragments of a backward."""
+    got = run(stub, """
+class Params(ctypes.Structure):
+    _fields_ = [(n, vp) for n in ("W1", "b1", "W2", "b2")] + [(n, ci) for n in ("din", "dh", "dout")]
+lib.gc_mlp_workspace_bytes.restype, lib.gc_mlp_workspace_bytes.argtypes = sz, [ci, vp]
+lib.gc_mlp_forward_nograd_bf16.argtypes = [vp, ci, vp, vp, vp, sz, vp]
+out = []
+for rows, din, dh, dout in ((1, 64, 128, 128), (200, 128, 256, 128), (2048, 1024, 3072, 768)):
+    w = Params(X, X, X, X, din, dh, dout)
+    need = (din * dh + dh * dout) * 2 + 2 * rows * dh * 4
+    call = lambda n: lib.gc_mlp_forward_nograd_bf16(X, rows, ctypes.byref(w), X, X, n, None)
+    out.append([call(need), call(need - 256), need < lib.gc_mlp_workspace_bytes(rows, ctypes.byref(w))])
+report(out=out)
+""")
+    assert got["out"] == [[0, -4, True]] * 3
