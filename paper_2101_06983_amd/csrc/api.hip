@@ -153,8 +153,8 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
   pl.off_part_m = take((size_t)stat_parts * B * 4);
   pl.off_part_l = take((size_t)stat_parts * B * 4);
   pl.off_part_idx = take((size_t)stat_parts * B * 4);
-  pl.off_pos = take((size_t)B * 4);
   pl.b_pad = route == ROUTE_PLANES ? (B + 127) / 128 * 128 : (B + 63) / 64 * 64;
+  pl.off_pos = take((size_t)(route == ROUTE_PLANES ? pl.b_pad : B) * 4);
   pl.off_lse2 = take((size_t)pl.b_pad * 4);
   pl.off_pos_pad = take((size_t)pl.b_pad * 4);
   pl.off_rowloss = take((size_t)B * 4);

@@ -104,7 +104,7 @@ __global__ void __launch_bounds__(256) stats_generic_kernel(const T* __restrict_
 // whole tiles without bounds checks (a padded row gives g = 0).
 template <int LANES>
 __global__ void __launch_bounds__(256) stats_merge_kernel(const float* __restrict__ part_m, const float* __restrict__ part_l,
-                                                         const int* __restrict__ part_idx, const float* __restrict__ pos_t,
+                                                         const int* __restrict__ part_idx, float* pos_t, int pos_to_coeff,
                                                          const int32_t* __restrict__ pos_idx, int B, int P, int nsplit,
                                                          int b_pad, float* __restrict__ lse2, int32_t* __restrict__ pos_pad,
                                                          float* __restrict__ rowloss, float* __restrict__ lse_out,
@@ -138,7 +138,9 @@ __global__ void __launch_bounds__(256) stats_merge_kernel(const float* __restric
   const int r = pos_idx[i];
   pos_pad[i] = r;
   const bool ok = (r >= 0 && r < P);
-  rowloss[i] = ok ? (l2 - pos_t[i]) * kLn2 : NAN;
+  const float pt = ok ? pos_t[i] : 0.f;
+  rowloss[i] = ok ? (l2 - pt) * kLn2 : NAN;
+  if (pos_to_coeff) pos_t[i] = exp2f(pt - l2) - 1.f;   // (read by the gradient kernel of loss_planes.hip)
   if (inv && ok) inv[r] = i;   // an anchor per target; which one, when several share it, is not relied upon
   if (lse_out) lse_out[i] = l2 * kLn2;
   if (argmax_out) argmax_out[i] = bi;
@@ -557,7 +559,7 @@ hipError_t launch_stats_merge(const LossArgs& a, const LossPlan& pl) {
     constexpr int ROWS = 256 / LANES;
     stats_merge_kernel<LANES><<<(pl.b_pad + ROWS - 1) / ROWS, 256, 0, a.stream>>>(
         (const float*)(ws + pl.off_part_m), (const float*)(ws + pl.off_part_l), (const int*)(ws + pl.off_part_idx),
-        (const float*)(ws + pl.off_pos), a.pos_idx, a.B, a.P, pl.stat_splits, pl.b_pad, (float*)(ws + pl.off_lse2),
+        (float*)(ws + pl.off_pos), pl.route == ROUTE_PLANES ? 1 : 0, a.pos_idx, a.B, a.P, pl.stat_splits, pl.b_pad, (float*)(ws + pl.off_lse2),
         (int32_t*)(ws + pl.off_pos_pad), (float*)(ws + pl.off_rowloss), a.lse, a.argmax,
         pl.use_mfma ? (int32_t*)(ws + pl.off_inv) : nullptr, pl.use_mfma ? (int*)(ws + pl.off_err) + 1 : nullptr);
   };

@@ -392,6 +392,9 @@ __global__ void __launch_bounds__(256) planes_stats_small_kernel(StatsSmallArgs 
 // time.  Per step each wave forms the scores of 32 of those rows against the owner rows over the whole width, turns them
 // into coefficients g = 2^(t - lse2) - [j = r_i] (fp32, Eq. 5 / Eq. 6) and publishes them as three bf16 planes of
 // ready-made A fragments; then every wave multiplies all 128 rows' coefficients with its own column tiles (w, w + 4, ..).
+// The positive's coefficient comes from the statistics' own sum of its score, the one that is part of lse2: where the softmax
+// has converged on it, the rounding of a second sum would be most of the coefficient (5.7e-5 of dq at 512 x 1024 x 776 and
+// temperature 0.1, 4.2e-6 so).
 // (Registers spilled: 15 by <3, 1, 2>, fp32 of 129 to 256 columns, and 16 by <1, 2, 8>; none by the others.)
 struct PlanesRole {
   const unsigned short* own_k; const unsigned short* str_k; const unsigned short* str_t;
@@ -404,6 +407,7 @@ struct PlanesGradArgs {
   int n0;                   // workgroups of role 0
   int d, KS, CT, ks_lds, col_slices, ct_per_slice;
   const float* lse2; const int32_t* pos;   // per anchor, padded to 128 rows with +inf / -1
+  const float* pos_c;                      // ... the positive's coefficient, with room for 128 rows
   float alpha2, out_scale;
   int mask_self;
 };
@@ -429,11 +433,12 @@ __global__ void __launch_bounds__(256, NO == 1 && CTW <= 4 ? 2 : 1) planes_grad_
   const int ct0 = cs * g.ct_per_slice, ct1 = min(g.CT, ct0 + g.ct_per_slice);
 
   int own_idx[NO], r_o[NO];
-  float lse_o[NO];
+  float lse_o[NO], c_o[NO];
 #pragma unroll
   for (int no = 0; no < NO; no++) {
     own_idx[no] = (ob * NO + no) * 32 + ln;
     lse_o[no] = ri ? 0.f : g.lse2[own_idx[no]];
+    c_o[no] = ri ? 0.f : g.pos_c[own_idx[no]];
     r_o[no] = ri ? -1 : g.pos[own_idx[no]];
   }
   f32x16 acc[NO][CTW];
@@ -465,14 +470,15 @@ __global__ void __launch_bounds__(256, NO == 1 && CTW <= 4 ? 2 : 1) planes_grad_
 #pragma unroll
     for (int p = 0; p < XD; p++) load_x(p, p / CTW, p % CTW);
     const int j0 = t0 + 32 * w + 4 * h;
-    float lse_s[16]; int pos_s[16];
+    float lse_s[16], c_s[16]; int pos_s[16];
     if (ri) {
 #pragma unroll
       for (int q = 0; q < 4; q++) {
         const f32x4 a = *(const f32x4*)(g.lse2 + j0 + 8 * q);
         const i32x4 b = *(const i32x4*)(g.pos + j0 + 8 * q);
+        const f32x4 c = *(const f32x4*)(g.pos_c + j0 + 8 * q);
 #pragma unroll
-        for (int e = 0; e < 4; e++) { lse_s[4 * q + e] = a[e]; pos_s[4 * q + e] = b[e]; }
+        for (int e = 0; e < 4; e++) { lse_s[4 * q + e] = a[e]; pos_s[4 * q + e] = b[e]; c_s[4 * q + e] = c[e]; }
       }
     }
 #pragma unroll
@@ -482,7 +488,7 @@ __global__ void __launch_bounds__(256, NO == 1 && CTW <= 4 ? 2 : 1) planes_grad_
         const int j = j0 + 8 * (r >> 2) + (r & 3);
         const float lse = ri ? lse_s[r] : lse_o[no];
         const bool hit = ri ? pos_s[r] == own_idx[no] : r_o[no] == j;
-        float v = exp2f(s[no][r] * g.alpha2 - lse) - (hit ? 1.f : 0.f);
+        float v = hit ? (ri ? c_s[r] : c_o[no]) : exp2f(s[no][r] * g.alpha2 - lse);
         if (j >= R.n_str || (g.mask_self && j == own_idx[no])) v = 0.f;
         s[no][r] = v;
       }
@@ -662,7 +668,7 @@ hipError_t launch_grad_planes(const LossArgs& a, const LossPlan& pl) {
   auto at = [&](size_t off) { return (const unsigned short*)(a.ws2 + off); };
   PlanesGradArgs g{};
   g.d = a.d; g.KS = pl.px_KS; g.CT = pl.px_CT; g.col_slices = pl.px_col_slices; g.ct_per_slice = pl.px_ct_per_slice;
-  g.lse2 = (const float*)(ws + pl.off_lse2); g.pos = (const int32_t*)(ws + pl.off_pos_pad);
+  g.lse2 = (const float*)(ws + pl.off_lse2); g.pos = (const int32_t*)(ws + pl.off_pos_pad); g.pos_c = (const float*)(ws + pl.off_pos);
   g.alpha2 = a.alpha * kLog2e; g.out_scale = a.alpha / (float)a.B * (a.grad_mul != 0.f ? a.grad_mul : 1.f);
   g.mask_self = (a.flags & GC_MASK_SELF) ? 1 : 0;
   const bool want_q = a.dq || a.dz, want_p = a.dp || a.dz;

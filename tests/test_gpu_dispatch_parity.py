@@ -411,3 +411,26 @@ def test_masked_ntxent_and_symmetric_above_the_few_scores(n, d):
     check_loss("symmetric n=%d d=%d" % (n, d), out["loss"].item(), want["loss"], TOL_F32)
     for k in ("dq", "dp"):
         check("symmetric n=%d d=%d %s" % (n, d, k), relerr(to_np(out[k]), want[k]), TOL_F32)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("B,P,d", [(64, 100, 200), (512, 1024, 776), (1500, 1600, 200), (2100, 2200, 96)])
+def test_gradients_where_the_softmax_has_converged(B, P, d, dtype):
+    """Aligned positives at temperature 0.1: p - 1 of the positive is the small difference of 2^(t - lse2) and 1.  t is part
+    of lse2, so that the rounding of its sum cancels: what is left is that of lse2 (half a unit in its last place, another
+    half for log2 and the sum) and of the exponential, times the largest entry of the row it multiplies."""
+    g = torch.Generator().manual_seed(5800 + B)
+    q = torch.nn.functional.normalize(torch.randn(B, d, generator=g), dim=1)
+    p = torch.nn.functional.normalize(torch.randn(P, d, generator=g), dim=1)
+    r = torch.randperm(P, generator=g)[:B]
+    p[r] = torch.nn.functional.normalize(0.9 * q + 0.1 * p[r], dim=1)
+    q, p, r = q.to(dtype), p.to(dtype), r.to(torch.int32)
+    alpha = 10.0
+    want = oracle_loss(q, p, r, 1.0, 1.0 / alpha)
+    out = run_ex(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 1.0 / alpha)
+    lse2 = np.abs(want["lse"]).max() / np.log(2.0)
+    coeff = np.log(2.0) * 2.0 ** (np.floor(np.log2(lse2)) - 23) + 2.0 ** -23
+    for k, other in (("dq", p), ("dp", q)):
+        err = np.abs(to_np(out[k]) - want[k]).max()
+        bound = alpha / B * coeff * float(other.float().abs().max()) + 2e-6 * np.abs(want[k]).max()
+        check("converged %dx%dx%d %s %s" % (B, P, d, dtype, k), err, bound)
