@@ -395,7 +395,7 @@ __global__ void __launch_bounds__(256) planes_stats_small_kernel(StatsSmallArgs 
 // The positive's coefficient comes from the statistics' own sum of its score, the one that is part of lse2: where the softmax
 // has converged on it, the rounding of a second sum would be most of the coefficient (5.7e-5 of dq at 512 x 1024 x 776 and
 // temperature 0.1, 4.2e-6 so).
-// (Registers spilled: 15 by <3, 1, 2>, fp32 of 129 to 256 columns, and 16 by <1, 2, 8>; none by the others.)
+// (Registers spilled: 30 by <1, 2, 8>, bf16 of 769 to 1024 columns with 64 owner rows; none by the others.)
 struct PlanesRole {
   const unsigned short* own_k; const unsigned short* str_k; const unsigned short* str_t;
   int n_own, n_str;         // valid rows

@@ -1096,7 +1096,9 @@ static int enqueue_step(const StepCall& c, hipStream_t s) {
   if (step1_joint(B, P)) {
     if (!ok(mlp_forward(x_q, B, w, mw, Q, s, true, x_p, P, Pm))) return GC_ERR_HIP;
   } else {
-    const int gq = group_rows(chunk_q, B), gp = group_rows(chunk_p, P);
+    // (the buffer is sized by the larger sub-batch, which can leave it some rows less than whole sub-batches of the other)
+    const int gq = group_rows(chunk_q, B) < room ? group_rows(chunk_q, B) : room;
+    const int gp = group_rows(chunk_p, P) < room ? group_rows(chunk_p, P) : room;
     for (int a = 0; a < B; a += gq) {
       const int rows = B - a < gq ? B - a : gq;
       if (!ok(mlp_forward((const unsigned short*)x_q + (size_t)a * w->din, rows, w, mw, Q + (size_t)a * w->dout, s, B >= kGemmRows)))

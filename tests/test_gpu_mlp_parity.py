@@ -282,3 +282,17 @@ def test_forward_in_the_bytes_it_uses(rows, dh):
     torch.cuda.synchronize()
     check("forward in %d bytes" % nbytes, relerr(to_np(y), O.mlp_forward(synth.widen(xq), widen_params(params))), TOL_STORED)
     assert bool((buf[nbytes:] == 0xA5).all())
+
+
+@pytest.mark.parametrize("B,P,cq,cp", [(9, 2067, 190, 6), (2344, 31, 3, 110), (26, 2395, 85, 13)])
+def test_step_with_sub_batches_that_fill_a_launch_differently(B, P, cq, cp):
+    """The activation buffer holds whole sub-batches of the larger size: 1900, 1980 and 2040 rows here, where whole
+    sub-batches of the other size come to 2046, 2046 and 2041.  Rows beyond the buffer would share memory with the partial
+    products of the second layer."""
+    xq, xp, r, params = synth.mlp_problem(B, P, 64, 512, 128, seed=synth.SEED0 + 96 + B)
+    out = gc.gc_step_mlp_bf16(xq.to(DEV), xp.to(DEV), r.to(DEV), cq, cp, dev_params(params), 1.0, 0.2, keep=True)
+    one = gc.gc_step_mlp_bf16(xq.to(DEV), xp.to(DEV), r.to(DEV), 32, 32, dev_params(params), 1.0, 0.2, keep=True)
+    torch.cuda.synchronize()
+    stagewise("%dx%d step in %d/%d" % (B, P, cq, cp), out, xq, xp, r, params, cq, cp, 1.0, 0.2)
+    for k in ("q", "p", "dq", "dp", "loss"):
+        assert torch.equal(out[k], one[k]), k
