@@ -14,7 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libgradcache.so")
-SOURCES = ["api.hip", "loss_generic.hip", "loss_mfma.hip", "loss_planes.hip", "mlp.hip"]
+SOURCES = ["api.hip", "loss_generic.hip", "loss_mfma.hip", "loss_mfma128.hip", "loss_planes.hip", "loss_stats.hip", "mlp.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
@@ -64,13 +64,14 @@ def build(force=True, extra_flags=(), verbose=False):
 def build_host_checked(out, bdir):
     """A second library whose HOST code carries UndefinedBehaviorSanitizer checks that abort at the first finding
     (device code is unchanged: the sanitizer does not exist for it).  For the argument-check tests, which need no
-    GPU.  Every source but loss_mfma.hip is compiled again with the checks; the object of that one, minutes of device
-    compilation and no argument checks of its own, is taken from the ordinary build."""
-    mfma = os.path.join(ROOT, "_build", "loss_mfma.o")
-    if not os.path.exists(mfma):
-        raise FileNotFoundError(mfma)
+    GPU.  The sources whose names begin with loss_mfma are not compiled again with the checks: their objects, minutes
+    of device compilation and no argument checks of their own, are taken from the ordinary build."""
+    mfma = [os.path.join(ROOT, "_build", s.replace(".hip", ".o")) for s in SOURCES if s.startswith("loss_mfma")]
+    for m in mfma:
+        if not os.path.exists(m):
+            raise FileNotFoundError(m)
     san = ["-Xarch_host", "-fsanitize=undefined", "-Xarch_host", "-fno-sanitize-recover=undefined", "-g"]
-    srcs = [s for s in SOURCES if s != "loss_mfma.hip"]
+    srcs = [s for s in SOURCES if not s.startswith("loss_mfma")]
     objs = [os.path.join(bdir, s.replace(".hip", "_ubsan.o")) for s in srcs]
     with ThreadPoolExecutor(max_workers=len(srcs)) as ex:
         list(ex.map(lambda j: _compile(j[0], j[1], san), zip(srcs, objs)))
@@ -80,7 +81,7 @@ def build_host_checked(out, bdir):
         raise FileNotFoundError("the compiler's shared UBSan runtime")
     rt = os.path.dirname(os.path.realpath(rt))
     r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-fno-gpu-rdc", "-fsanitize=undefined",
-                        "-shared-libsan", "-Wl,-rpath," + rt, "-Wno-option-ignored", "-o", out] + objs + [mfma],
+                        "-shared-libsan", "-Wl,-rpath," + rt, "-Wno-option-ignored", "-o", out] + objs + mfma,
                        capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)

@@ -1,382 +1,11 @@
-// bf16 MFMA kernels of the loss / representation-gradient path for gfx950.
+// Gradient walks of the bf16 loss path for gfx950, widths from 256 (d = 128: loss_mfma128.hip).
 //
-//   stats pass   Eq. 1 / Eq. 4: per anchor, online max and sum of 2^t over target tiles, the
-//                positive's score and the argmax; the score tile lives in MFMA accumulators only.
 //   gradient pass  Eq. 5 / Eq. 6: a workgroup owns 64 rows of dQ (or dP), streams the other
-//                matrix 32 rows at a time, recomputes the score tile, forms
-//                g = softmax - Y in registers and accumulates g * rows with MFMA.
-//
-// MFMA operand layouts used throughout (v_mfma_f32_32x32x16_bf16, D = A * B + C, wave of 64):
-//   A fragment: lane l holds A[m = l % 32][k = 8 * (l / 32) + 0..7]
-//   B fragment: lane l holds B[k = 8 * (l / 32) + 0..7][n = l % 32]
-//   C/D:        lane l, register r holds D[m = 8 * (r / 4) + 4 * (l / 32) + r % 4][n = l % 32]
-// The reduction over targets is put on the M axis (registers) so that every lane owns one
-// anchor column and the softmax statistics need no cross-lane traffic inside a tile.
-#include <type_traits>
-
-#include "gc_common.h"
-#include "stats_tile.h"
+//                matrix, recomputes the score tile, forms g = softmax - Y in registers and
+//                accumulates g * rows with MFMA.
+#include "mfma_common.h"
 
 namespace gc {
-
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-
-__device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
-
-// N (1..4) direct global->LDS loads of 16 bytes per lane that share one M0 value.  Load k lands at
-// lds_base + 1024 k + lane * 16 and reads gbase + voff[k] + 1024 k: the instruction's immediate
-// offset moves both addresses, so callers pass voff[k] with 1024 k already subtracted.  The
-// compiler does not see these loads: the reader waits with wait_vmem<N>().
-// Every statement below that sets M0 says so in its clobber list.  M0 is a register the backend reserves (it never
-// keeps a value of its own there across other code and sets it right before each instruction of its own that needs
-// it); the clobber states the write, so that nothing it may ever cache there is assumed to survive.
-template <int N>
-__device__ __forceinline__ void dma_group(const void* gbase, const unsigned* voff, unsigned lds_base) {
-  if constexpr (N == 1) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(voff[0]), "s"(gbase) : "memory", "m0");
-  } else if constexpr (N == 2) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\tglobal_load_lds_dwordx4 %2, %3 offset:1024"
-                 ::"s"(lds_base), "v"(voff[0]), "v"(voff[1]), "s"(gbase) : "memory", "m0");
-  } else if constexpr (N == 3) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %4\n\tglobal_load_lds_dwordx4 %2, %4 offset:1024\n\t"
-                 "global_load_lds_dwordx4 %3, %4 offset:2048"
-                 ::"s"(lds_base), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "s"(gbase) : "memory", "m0");
-  } else {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %5\n\tglobal_load_lds_dwordx4 %2, %5 offset:1024\n\t"
-                 "global_load_lds_dwordx4 %3, %5 offset:2048\n\tglobal_load_lds_dwordx4 %4, %5 offset:3072"
-                 ::"s"(lds_base), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "s"(gbase) : "memory", "m0");
-  }
-}
-// One such load with immediate offset IMM (a multiple of 1024 below 4096): lands at lds_base + IMM +
-// lane * 16 and reads gbase + voff + IMM.  No memory clobber: the compiler may move unrelated LDS
-// traffic across it; callers order it against the readers of its target with wait_vmem / barriers.
-template <int IMM>
-__device__ __forceinline__ void dma_piece(const void* gbase, unsigned voff, unsigned lds_base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" ::"s"(lds_base), "v"(voff), "s"(gbase), "n"(IMM) : "m0");
-}
-// The same, placed by data dependences instead of fences: the statement claims to rewrite the
-// registers pin_a / pin_b (it does not touch them), so it is scheduled after the last reader of
-// their old values and before the first reader of the new ones, and nothing else is held up.
-// LANES8: only lanes 0-7 load (128 bytes); EXEC is narrowed inside the statement and restored.
-template <int IMM, bool LANES8, bool TWO>
-__device__ __forceinline__ void dma_piece_pinned(const void* gbase, unsigned voff, unsigned lds_base, u32x4& pin_a, u32x4& pin_b) {
-  unsigned pa = pin_a[0], pb = TWO ? pin_b[0] : 0u;
-  if constexpr (LANES8) {
-    unsigned long long keep;
-    if constexpr (TWO)
-      asm volatile("s_mov_b64 %2, exec\n\ts_mov_b64 exec, 0xff\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, %5 offset:%6\n\ts_mov_b64 exec, %2"
-                   : "+v"(pa), "+v"(pb), "=&s"(keep) : "s"(lds_base), "v"(voff), "s"(gbase), "n"(IMM) : "m0");
-    else
-      asm volatile("s_mov_b64 %1, exec\n\ts_mov_b64 exec, 0xff\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, %4 offset:%5\n\ts_mov_b64 exec, %1"
-                   : "+v"(pa), "=&s"(keep) : "s"(lds_base), "v"(voff), "s"(gbase), "n"(IMM) : "m0");
-  } else {
-    if constexpr (TWO)
-      asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, %4 offset:%5"
-                   : "+v"(pa), "+v"(pb) : "s"(lds_base), "v"(voff), "s"(gbase), "n"(IMM) : "m0");
-    else
-      asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3 offset:%4"
-                   : "+v"(pa) : "s"(lds_base), "v"(voff), "s"(gbase), "n"(IMM) : "m0");
-  }
-  pin_a[0] = pa;
-  if constexpr (TWO) pin_b[0] = pb;
-}
-template <int N>
-__device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-
-// ===========================================================================
-// Statistics pass.  Workgroup = 512 threads = 8 waves as 2 (targets, M) x 4 (anchors, N);
-// workgroup tile 256 targets x 256 anchors, wave tile 128 x 64 (4 x 2 MFMA tiles).
-// k is staged through LDS in chunks of 64, two stages.
-// ===========================================================================
-constexpr int ST_TM = 256, ST_TN = 256, ST_KC = 64;
-constexpr int ST_ROWB = ST_KC * 2;                       // bytes per LDS row (8 chunks of 16 bytes, unpadded)
-constexpr int ST_STAGE_BYTES = (ST_TM + ST_TN) * ST_ROWB;  // one stage: 256 target rows, then 256 anchor rows
-// LDS layout: chunk c of row r is stored at chunk position c ^ ((r >> 1) & 7): the 16 rows that a
-// 16-lane group reads in one fragment load then fall into 16 different 16-byte bank groups.
-
-__global__ void __launch_bounds__(512) stats_mfma_kernel(const unsigned short* __restrict__ Q,
-                                                         const unsigned short* __restrict__ Pm,
-                                                         const int32_t* __restrict__ pos_idx, int B, int P, int d,
-                                                         float alpha2, int mask_self, int n_ablk, int cols_per_split,
-                                                         float* __restrict__ part_m, float* __restrict__ part_l,
-                                                         int* __restrict__ part_idx, float* __restrict__ pos_t) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_b[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave & 1, wn = wave >> 1;
-  const int task = xcd_task_id();
-  const int ablk = task % n_ablk, split = task / n_ablk;
-  const int a0 = ablk * ST_TN;
-  const int cbeg = split * cols_per_split, cend = min(P, cbeg + cols_per_split);
-  const int nk = d / ST_KC;
-
-  // ---- direct global->LDS loads: wave w fills rows 64 w .. 64 w + 63 of a stage (waves 0-3 the target
-  // rows, waves 4-7 the anchor rows), 8 instructions of 8 rows x 8 chunks each -------------------------
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);  // as a scalar: what follows from it stays uniform
-  const bool loads_q = wave_u >= 4;
-  const unsigned short* lmat = loads_q ? Q : Pm;
-  const int lrows = loads_q ? B : P;
-  const int lrow_in = (wave_u & 3) * 64 + (lane >> 3);  // + 8 j: row inside the 256-row tile
-  const unsigned stage_m0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)smem_b + wave_u * 64 * ST_ROWB);
-  auto src_of = [&](int j, int tile_row0, bool clamp) -> unsigned {  // byte offset from the tile's first row, chunk kc = 0
-    int r = lrow_in + 8 * j;
-    const int c = (lane & 7) ^ ((r >> 1) & 7);
-    if (clamp) r = min(r, lrows - 1 - tile_row0);
-    return (unsigned)(r * d * 2 + c * 16);
-  };
-  unsigned voff_full[8];  // full tile, with the instruction offset 1024 (j % 4) pre-subtracted
-#pragma unroll
-  for (int j = 0; j < 8; j++) voff_full[j] = src_of(j, 0, false) - 1024u * (j & 3);
-  auto prefetch = [&](int tile_row0, int kc, int stage) __attribute__((always_inline)) {
-    const unsigned short* base_v = lmat + (size_t)tile_row0 * d + kc * ST_KC;  // the same in every lane of a wave
-    const unsigned long long bu = (unsigned long long)(uintptr_t)base_v;
-    const unsigned short* base = (const unsigned short*)(uintptr_t)(
-        // readfirstlane returns int: go through unsigned, or the low half sign-extends into the high one
-        ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((unsigned)(bu >> 32)) << 32) |
-        (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((unsigned)bu));
-    const unsigned m0 = stage_m0 + stage * ST_STAGE_BYTES;
-    if (tile_row0 + 256 <= lrows) {
-      dma_group<4>(base, &voff_full[0], m0);
-      dma_group<4>(base, &voff_full[4], m0 + 4096);
-    } else {  // ragged tile: rows past the end re-read the last valid row (masked later)
-#pragma unroll
-      for (int j = 0; j < 8; j++) {
-        const unsigned off = src_of(j, tile_row0, true);
-        dma_group<1>(base, &off, m0 + j * 1024);
-      }
-    }
-  };
-
-  // ---- fragment addresses: row (lane & 31) of an MFMA tile, chunk 2 ks + (lane >> 5), swizzled ---------
-  const int swz_l = ((lane & 31) >> 1) & 7;
-  unsigned koff[4];
-#pragma unroll
-  for (int ks = 0; ks < 4; ks++) koff[ks] = (unsigned)(((2 * ks + (lane >> 5)) ^ swz_l) * 16);
-  const unsigned char* a_base = smem_b + (wm * 128 + (lane & 31)) * ST_ROWB;               // + mt * 32 rows
-  const unsigned char* b_base = smem_b + (ST_TM + wn * 64 + (lane & 31)) * ST_ROWB;        // + nt * 32 rows
-
-  // per-lane running statistics for its two anchor columns
-  float rm[2], rl[2], rpos[2];
-  int ridx[2], a_col[2], r_of[2];
-#pragma unroll
-  for (int nt = 0; nt < 2; nt++) {
-    rm[nt] = -INFINITY; rl[nt] = 0.f; rpos[nt] = 0.f; ridx[nt] = 0x7fffffff;
-    a_col[nt] = a0 + wn * 64 + nt * 32 + (lane & 31);
-    r_of[nt] = (a_col[nt] < B) ? pos_idx[a_col[nt]] : -1;
-  }
-
-  // The k-chunks of all the tiles of this workgroup form one sequence of steps; step st lives in stage st & 1 and
-  // its loads are issued one step ahead inside a tile.  (Loading the first chunk of the next tile under the last
-  // MFMAs of this one was measured too: no gain at 2 tiles of 12 chunks, a loss at 16 tiles of 2 chunks.)
-  int st = 0;
-  for (int b0 = cbeg; b0 < cend; b0 += ST_TM) {
-    f32x16 acc[4][2];
-#pragma unroll
-    for (int mt = 0; mt < 4; mt++)
-#pragma unroll
-      for (int nt = 0; nt < 2; nt++)
-#pragma unroll
-        for (int r = 0; r < 16; r++) acc[mt][nt][r] = 0.f;
-
-    const int row0 = loads_q ? a0 : b0;
-    // nothing is in flight and every reader is past the last barrier: both stages are free
-    prefetch(row0, 0, st & 1);
-    wait_vmem<0>();
-    __syncthreads();
-    bf16x8 af[2][4], bfg[2][2];
-    for (int kc = 0; kc < nk; kc++, st++) {
-      if (kc + 1 < nk) prefetch(row0, kc + 1, (st + 1) & 1);
-      const int so = (st & 1) * ST_STAGE_BYTES;
-      __builtin_amdgcn_iglp_opt(0);  // scheduler hint: interleave the fragment reads with the MFMA stream
-      auto load_frags = [&](int ks, int buf) __attribute__((always_inline)) {
-#pragma unroll
-        for (int mt = 0; mt < 4; mt++) af[buf][mt] = *(const bf16x8*)(a_base + so + mt * 32 * ST_ROWB + koff[ks]);
-#pragma unroll
-        for (int nt = 0; nt < 2; nt++) bfg[buf][nt] = *(const bf16x8*)(b_base + so + nt * 32 * ST_ROWB + koff[ks]);
-      };
-      load_frags(0, 0);
-#pragma unroll
-      for (int ks = 0; ks < ST_KC / 16; ks++) {
-        if (ks + 1 < ST_KC / 16) load_frags(ks + 1, (ks + 1) & 1);
-#pragma unroll
-        for (int mt = 0; mt < 4; mt++)
-#pragma unroll
-          for (int nt = 0; nt < 2; nt++) acc[mt][nt] = mfma32(af[ks & 1][mt], bfg[ks & 1][nt], acc[mt][nt]);
-      }
-      wait_vmem<0>();   // this wave's part of the next stage has landed
-      __syncthreads();  // ... and everybody's; nobody still reads the stage that is overwritten next
-    }
-
-    // ---- tile epilogue: online softmax statistics, all in registers; acc holds the raw dot products, the
-    // base-2 logit is t = alpha2 * acc (alpha2 > 0: the order of the raw values is the order of the logits) -------
-    const int brow0 = b0 + wm * 128 + 4 * (lane >> 5);  // + mt*32 + 8*(r/4) + r%4
-    const bool edge = (b0 + ST_TM > cend);
-#pragma unroll
-    for (int nt = 0; nt < 2; nt++) {
-      const int a = a_col[nt];
-      // the masks that can touch this tile
-      const bool diag = mask_self && (a >= b0 && a < b0 + ST_TM);
-      const bool haspos = (unsigned)(r_of[nt] - b0) < (unsigned)ST_TM;
-      if (edge || diag || haspos) {  // rare: the general slow walk
-#pragma unroll
-        for (int mt = 0; mt < 4; mt++)
-#pragma unroll
-          for (int r = 0; r < 16; r++) {
-            int j = brow0 + mt * 32 + 8 * (r >> 2) + (r & 3);
-            if (j == r_of[nt]) rpos[nt] = acc[mt][nt][r] * alpha2;
-            if (j >= cend || (mask_self && j == a)) acc[mt][nt][r] = -INFINITY;
-          }
-      }
-      // tile max + first index attaining it (rows are visited in increasing j within mt; across
-      // register order j is increasing too, so a strict > keeps the smallest index)
-      float tmr = -INFINITY; int tc = 0;
-#pragma unroll
-      for (int mt = 0; mt < 4; mt++)
-#pragma unroll
-        for (int r = 0; r < 16; r++) {
-          const float t = acc[mt][nt][r];
-          const bool le = t <= tmr;
-          tmr = le ? tmr : t;
-          tc = le ? tc : (mt * 32 + 8 * (r >> 2) + (r & 3));
-        }
-      if (tmr > -INFINITY) {
-        const float tm = tmr * alpha2;
-        const float mn = fmaxf(rm[nt], tm);
-        float s = 0.f;
-#pragma unroll
-        for (int mt = 0; mt < 4; mt++)
-#pragma unroll
-          for (int r = 0; r < 16; r++) s += fast_exp2(__builtin_fmaf(acc[mt][nt][r], alpha2, -mn));
-        rl[nt] = rl[nt] * fast_exp2(rm[nt] - mn) + s;
-        if (tm > rm[nt]) ridx[nt] = brow0 + tc;  // later tiles have larger j: strict >
-        rm[nt] = mn;
-      }
-    }
-  }
-
-  // ---- combine the two half-waves (same anchor column, different target rows) -------------------
-#pragma unroll
-  for (int nt = 0; nt < 2; nt++) {
-    float m2 = __shfl_xor(rm[nt], 32), l2 = __shfl_xor(rl[nt], 32);
-    int i2 = __shfl_xor(ridx[nt], 32);
-    stat_merge(rm[nt], rl[nt], ridx[nt], m2, l2, i2);
-  }
-  // ---- combine the two waves along M through LDS, then write the split partial ------------------
-  __syncthreads();
-  float* xs = (float*)smem_b;  // [4 wn][2 nt][32][3]
-  if (wm == 1 && lane < 32) {
-#pragma unroll
-    for (int nt = 0; nt < 2; nt++) {
-      float* x = xs + ((wn * 2 + nt) * 32 + lane) * 3;
-      x[0] = rm[nt]; x[1] = rl[nt]; x[2] = __builtin_bit_cast(float, ridx[nt]);
-    }
-  }
-  __syncthreads();
-  if (wm == 0 && lane < 32) {
-#pragma unroll
-    for (int nt = 0; nt < 2; nt++) {
-      const float* x = xs + ((wn * 2 + nt) * 32 + lane) * 3;
-      stat_merge(rm[nt], rl[nt], ridx[nt], x[0], x[1], __builtin_bit_cast(int, x[2]));
-      int a = a_col[nt];
-      if (a < B) {
-        part_m[(size_t)split * B + a] = rm[nt];
-        part_l[(size_t)split * B + a] = rl[nt];
-        part_idx[(size_t)split * B + a] = ridx[nt];
-      }
-    }
-  }
-  // the positive's score is seen by exactly one lane of one workgroup
-#pragma unroll
-  for (int nt = 0; nt < 2; nt++) {
-    int a = a_col[nt], r = r_of[nt];
-    if (a < B && r >= cbeg && r < cend) {
-      // lane that held row r: rows of this lane are brow(mt, reg) with 4*(lane>>5) offset
-      int rel = (r - cbeg) % ST_TM;  // row inside its tile
-      int wmr = rel / 128, in = rel % 128;
-      int half = (in % 8) / 4;
-      // a positive that the self-mask removes has the logit -inf (its row loss is then +inf)
-      if (wmr == wm && half == (lane >> 5)) pos_t[a] = (mask_self && r == a) ? -INFINITY : rpos[nt];
-    }
-  }
-}
-
-// ===========================================================================
-// Statistics pass for few scores: 32 x 32 tiles, the contraction split over the four waves of a workgroup in 64-wide
-// chunks, every operand loaded straight into registers (lane (n, h) takes elements 32 h .. 32 h + 31 of a chunk of its
-// row, so that two lanes use a whole 128-byte line; any order of k works if both operands share it).  The kernel above
-// has 256 x 256 tiles: 23 us for the one workgroup of 128 x 256 scores and 26 us for the eight of 512 x 1024 at d = 768,
-// all latency of twelve dependent k-chunks.  Here a wave has all its loads in flight at once: 6.6 and 9.7 us.  It costs
-// B P d / 8 bytes of L2 traffic, so the larger tiles win again from about 2^20 scores (a version with 64 x 64 tiles took
-// 37 us at 1021 x 4099 x 384, the 256 x 256 kernel 23).
-// ===========================================================================
-__global__ void __launch_bounds__(256) stats_small_kernel(StatsSmallArgs g) {
-  constexpr int T = kStatTile, PD = 3;
-  __shared__ StatTileLds lds;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, ln = lane & 31;
-  const int task = xcd_task_id();
-  const int a0 = (task % g.n_ablk) * T, split = task / g.n_ablk;
-  const int nch = g.d / 64;
-  const char* qp = (const char*)(g.Q + (size_t)min(a0 + ln, g.B - 1) * g.d + 32 * h);
-  StatTile<false> st(g, a0);
-  const int t_end = min(g.tiles, (split + 1) * g.tiles_per_split);
-  for (int t = split * g.tiles_per_split; t < t_end; t++) {
-    const int j0 = t * T;
-    const char* pp = (const char*)(g.P + (size_t)min(j0 + ln, g.Pn - 1) * g.d + 32 * h);
-    u32x4 fq[PD][4], fp[PD][4];
-    auto issue = [&](int slot, int c) __attribute__((always_inline)) {
-#pragma unroll
-      for (int v = 0; v < 4; v++) {
-        fq[slot][v] = *(const u32x4*)(qp + (size_t)c * 128 + 16 * v);
-        fp[slot][v] = *(const u32x4*)(pp + (size_t)c * 128 + 16 * v);
-      }
-    };
-    f32x16 acc;
-#pragma unroll
-    for (int e = 0; e < 16; e++) acc[e] = 0.f;
-#pragma unroll
-    for (int p = 0; p < PD; p++)
-      if (wave + 4 * p < nch) issue(p, wave + 4 * p);
-    for (int base = wave; base < nch; base += 4 * PD) {
-#pragma unroll
-      for (int p = 0; p < PD; p++) {
-        const int c = base + 4 * p;
-        if (c < nch) {
-#pragma unroll
-          for (int v = 0; v < 4; v++) acc = mfma32(__builtin_bit_cast(bf16x8, fp[p][v]), __builtin_bit_cast(bf16x8, fq[p][v]), acc);
-          if (c + 4 * PD < nch) issue(p, c + 4 * PD);
-        }
-      }
-    }
-    StatTile<false>::put(lds, wave, acc);
-    __syncthreads();
-    st.tile(g, lds, j0);
-    __syncthreads();   // the partial tiles have been read
-  }
-  st.finish(g, lds, split);
-}
-static hipError_t launch_stats_small(const LossArgs& a, const LossPlan& pl) {
-  const StatsSmallArgs g = stats_small_args(a, pl, (const unsigned short*)a.q, (const unsigned short*)a.p);
-  stats_small_kernel<<<g.n_ablk * pl.stat_splits, 256, 0, a.stream>>>(g);
-  return hipGetLastError();
-}
-
-static hipError_t launch_stats128(const LossArgs& a, const LossPlan& pl);
-hipError_t launch_stats_mfma(const LossArgs& a, const LossPlan& pl) {
-  if (pl.stat_tile) return launch_stats_small(a, pl);
-  if (a.d == 128) return launch_stats128(a, pl);   // whole anchor rows in registers: a kernel of its own
-  char* ws = a.ws;
-  const int n_ablk = (a.B + ST_TN - 1) / ST_TN;
-  const size_t smem = (size_t)2 * ST_STAGE_BYTES;
-  static bool attr_done[64];
-  if (hipError_t e = ensure_dyn_lds((const void*)stats_mfma_kernel, (int)smem, attr_done); e != hipSuccess) return e;
-  stats_mfma_kernel<<<n_ablk * pl.stat_splits, 512, smem, a.stream>>>(
-      (const unsigned short*)a.q, (const unsigned short*)a.p, a.pos_idx, a.B, a.P, a.d, a.alpha * kLog2e,
-      (a.flags & GC_MASK_SELF) ? 1 : 0, n_ablk, pl.stat_cols_per_split, (float*)(ws + pl.off_part_m),
-      (float*)(ws + pl.off_part_l), (int*)(ws + pl.off_part_idx), (float*)(ws + pl.off_pos));
-  return hipGetLastError();
-}
-
 
 // ===========================================================================
 // Gradient pass.  Workgroup = 256 threads = 4 waves, one per SIMD (up to 512 registers a lane).
@@ -439,87 +68,6 @@ struct GradCfg {
 // and 767 others are free of conflicts for both; the first choice, bits 2 and 3 of the row into bits 0 and 1, left
 // the 16-byte fragment reads of phase 1 with a two-way conflict, 21 % of the walks' LDS cycles.)
 __device__ __forceinline__ int swz3(int row) { return (((row >> 1) & 1) << 2) | (((row >> 2) & 1) << 1); }
-
-struct GradArgs {
-  const unsigned short* Q;
-  const unsigned short* P;
-  const int32_t* pos_pad;   // pos_idx copied and padded with -1 to a multiple of 64 rows
-  const float* lse2;        // log2-domain log-sum-exp per anchor, padded with +inf
-  const float* lse2_t;      // symmetric loss only: the same per target (over the anchors), padded alike
-  int B, Pn;
-  float alpha2, out_scale;
-  int mask_self;
-  int obQ, nsq, q_stream_len;  // dQ-role workgroups: obQ owner blocks x nsq stream splits
-  int obP, nsp, p_stream_len;
-  float* dq_out; size_t dq_split_stride;  // split s writes dq_out + s * stride
-  float* dp_out; size_t dp_split_stride;
-  // online-statistics walk (dQ role, no statistics pass before it): per split and anchor the reference the
-  // accumulators are relative to and sum 2^(t - reference); per anchor the positive's logit
-  float* on_ref; float* on_l; int* on_idx; float* on_pos;
-  float* on_best;  // per split and anchor: the true maximum, written (with on_idx) only when on_argmax is set
-  int on_argmax;   // track the true maximum and its first index
-  // an anchor per target, as the statistics merge left it, and the word that check_shared_positives raises
-  const int32_t* inv; int* shared;
-};
-
-// The kernel that sums the partials adds each positive's own term to its dP row through inv[j] (an anchor with
-// r_i = j).  That is enough when no two anchors share a target; here every workgroup looks at a slice of the anchors
-// and raises *shared when one of them is not the anchor recorded for its target (the sum kernel then scans).
-__device__ __forceinline__ void check_shared_positives(const GradArgs& ga) {
-  if (!ga.inv) return;
-  const int per = (ga.B + (int)gridDim.x - 1) / (int)gridDim.x;
-  const int i0 = (int)blockIdx.x * per, i1 = min(ga.B, i0 + per);
-  for (int i = i0 + (int)threadIdx.x; i < i1; i += (int)blockDim.x) {
-    const int r = ga.pos_pad[i];
-    if (r >= 0 && r < ga.Pn && ga.inv[r] != i) *ga.shared = 1;
-  }
-}
-
-// max / sum over the four lanes that share lane % 16 (v_permlane16_swap / v_permlane32_swap give every lane both
-// partners' values, so all four lanes end with the same bits)
-__device__ __forceinline__ void swap16(unsigned x, unsigned& a, unsigned& b) {
-  auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false); a = r[0]; b = r[1];
-}
-__device__ __forceinline__ void swap32(unsigned x, unsigned& a, unsigned& b) {
-  auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false); a = r[0]; b = r[1];
-}
-__device__ __forceinline__ float max_g16(float x) {
-  unsigned a, b;
-  swap16(__builtin_bit_cast(unsigned, x), a, b);
-  x = fmaxf(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
-  swap32(__builtin_bit_cast(unsigned, x), a, b);
-  return fmaxf(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
-}
-__device__ __forceinline__ float sum_g16(float x) {
-  unsigned a, b;
-  swap16(__builtin_bit_cast(unsigned, x), a, b);
-  x = __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
-  swap32(__builtin_bit_cast(unsigned, x), a, b);
-  return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
-}
-// (value, index): larger value wins, ties go to the smaller index
-__device__ __forceinline__ void argmax_g16(float& v, int& i) {
-  unsigned a, b, ia, ib;
-  auto pick = [&]() {
-    const float va = __builtin_bit_cast(float, a), vb = __builtin_bit_cast(float, b);
-    const bool tb = (vb > va) || (vb == va && (int)ib < (int)ia);
-    v = tb ? vb : va; i = tb ? (int)ib : (int)ia;
-  };
-  swap16(__builtin_bit_cast(unsigned, v), a, b); swap16((unsigned)i, ia, ib); pick();
-  swap32(__builtin_bit_cast(unsigned, v), a, b); swap32((unsigned)i, ia, ib); pick();
-}
-
-__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-
-template <int N, int I = 0, class F>
-__device__ __forceinline__ void static_for(F&& f) {  // f(integral_constant<int, I>) for I = 0 .. N-1
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<N, I + 1>(f);
-  }
-}
 
 template <int D>
 constexpr bool grad_offsets_fit() {  // voff[k] - 1024 (k % 4) must stay >= 0 for a full tile
@@ -1048,504 +596,6 @@ __device__ __forceinline__ void grad_body(const GradArgs& ga, int oblk, int spli
 }
 
 
-// ===========================================================================
-// Gradient pass for d = 128 (the NT-Xent workload).  At this width a wave can hold whole owner rows, so
-// nothing is exchanged between waves: a workgroup (4 waves, one per SIMD) owns 256 rows, each wave 64 of
-// them with all 128 columns in registers (64 VGPRs as MFMA B fragments), and all four share the streamed
-// tiles (32 rows x 128 columns, 8 KB) through one LDS ring of four stages.  Per tile and wave:
-//   phase 1  S^T[32 streamed x 64 owner] = R_tile * O^T, 16 MFMAs 32x32x16.  Lane (n, h) then holds, for owner
-//            row n, the scores of streamed rows 8 j + 4 h + i (j, i = 0..3): registers 8 kk .. 8 kk + 7 are
-//            streamed rows 16 kk + {4 h .. 4 h + 3, 8 + 4 h .. 8 + 4 h + 3}.
-//   g        = 2^(t - lse2) - [j = r_i] in place, rounded to bf16: registers 8 kk .. 8 kk + 7 ARE the B
-//            fragment (k = those streamed rows, n = owner) of
-//   phase 2  dO^T[128 x 64 owner] += R_tile^T * g^T, 16 MFMAs 32x32x16, whose A fragments (columns of the tile,
-//            the same streamed rows in the same k order) come from two transposing LDS reads each.
-// The contraction order over the streamed rows is thus a permutation that both operands of phase 2 share.
-// LDS per tile: every wave reads the tile twice (8 KB + 8 KB), 72 KB per workgroup against 64 MFMAs per SIMD.
-// ===========================================================================
-constexpr int G1_OWN = 256, G1_OWN_W = 64, G1_T = 32, G1_STAGES = 8, G1_AHEAD = 6;  // tiles u-1 .. u+1 alive, up to u+5 started
-constexpr int G1_STAT = 256;                      // a stage starts with lse2[32], then pos_idx[32] of the streamed rows
-constexpr int G1_STAGE = G1_STAT + G1_T * 256;    // bytes
-constexpr int G1_SMEM = G1_STAGES * G1_STAGE;
-// chunk c (16 bytes) of tile row r is stored at chunk position c ^ swz128(r): 8 consecutive rows of a
-// fragment read, and the 4 rows x 2 chunks of a transposing read, fall into different 16-byte bank groups.
-// (The bank-conflict counter still shows a conflict on every second LDS cycle of these kernels.  4-bit maps that remove
-// them all -- e.g. ((row & 3) << 2) | ((row >> 2) & 3): the low row bits pick the 64-byte quarter, the next two the
-// chunk inside it -- were measured on the kernels themselves: LDS cycles halved, waits for LDS a tenth, the time of the
-// gradient kernel equal within 1 %.  With a 3-bit map fragment k + 4 of a row sits a fixed 128 bytes behind fragment k,
-// an immediate offset; a 4-bit map needs a second set of address registers, which this kernel, at 512 of 512, does not
-// have: it spills again.  The loop is paced by its barrier and the waits for the tile loads, not by LDS.)
-__device__ __forceinline__ int swz128(int row) { return ((row & 3) << 1) | ((row >> 2) & 1); }
-
-// the first `LANES` lanes of the wave load 16 bytes each to lds_base + lane * 16 (EXEC narrowed inside)
-__device__ __forceinline__ void dma_lanes16(const void* gbase, unsigned voff, unsigned lds_base) {
-  unsigned long long keep;
-  asm volatile("s_mov_b64 %0, exec\n\ts_mov_b64 exec, 0xffff\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b64 exec, %0"
-               : "=&s"(keep) : "s"(lds_base), "v"(voff), "s"(gbase) : "memory", "m0");
-}
-
-template <bool OWNER_IS_Q, bool SYM>
-__device__ __forceinline__ void grad128_body(const GradArgs& ga, int oblk, int split, unsigned char* smem) {
-  constexpr int D = 128;
-  constexpr bool STR_STATS = SYM || !OWNER_IS_Q;   // as in grad_body
-  const float* lse_own = (SYM && !OWNER_IS_Q) ? ga.lse2_t : ga.lse2;
-  const float* lse_str = (SYM && OWNER_IS_Q) ? ga.lse2_t : ga.lse2;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, h = lane >> 5, ln = lane & 31;
-  const int l16 = lane & 15, g16 = lane >> 4;
-  const unsigned short* O = OWNER_IS_Q ? ga.Q : ga.P;
-  const unsigned short* R = OWNER_IS_Q ? ga.P : ga.Q;
-  const int No = OWNER_IS_Q ? ga.B : ga.Pn, Nr = OWNER_IS_Q ? ga.Pn : ga.B;
-  const int slen = OWNER_IS_Q ? ga.q_stream_len : ga.p_stream_len;
-  const int a0 = oblk * G1_OWN + w * G1_OWN_W;   // this wave's first owner row
-  const int sbeg = split * slen, send = min(Nr, sbeg + slen);
-  const int nt = (send - sbeg + G1_T - 1) / G1_T;   // >= 1
-  const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)smem);
-  const int wu = __builtin_amdgcn_readfirstlane(w);   // the wave index as a scalar
-
-  // owner rows as phase-1 B fragments: lane (ln, h) holds owner row 32 n + ln, columns 16 ks + 8 h .. + 7
-  bf16x8 ofrag[2][8];
-  int own_idx[2];
-  float lse_o[2]; int r_o[2];
-#pragma unroll
-  for (int n = 0; n < 2; n++) {
-    own_idx[n] = a0 + 32 * n + ln;
-    const int row = min(own_idx[n], No - 1);
-#pragma unroll
-    for (int ks = 0; ks < 8; ks++) ofrag[n][ks] = *(const bf16x8*)(O + (size_t)row * D + 16 * ks + 8 * h);
-    lse_o[n] = INFINITY; r_o[n] = -1;            // a row past the end: g = 0
-    if ((OWNER_IS_Q || SYM) && own_idx[n] < No) lse_o[n] = lse_own[own_idx[n]];
-    if (OWNER_IS_Q && own_idx[n] < No) r_o[n] = ga.pos_pad[own_idx[n]];
-  }
-  // The compiler's own loads end here: it does not see the direct-to-LDS loads below, and a wait of its own for
-  // these registers inside the loop would also wait for those.  An empty statement that "uses" every loaded register.
-#pragma unroll
-  for (int n = 0; n < 2; n++) {
-#pragma unroll
-    for (int ks = 0; ks < 8; ks++) asm volatile("" : "+v"(ofrag[n][ks]));
-    asm volatile("" : "+v"(lse_o[n]), "+v"(r_o[n]));
-  }
-
-  // ---- loads of a streamed tile: 8 instructions of 4 rows, two per wave; lane -> (row, chunk position) ------
-  auto src_of = [&](int it, int max_row) __attribute__((always_inline)) -> unsigned {
-    const int row = 4 * it + (lane >> 4);
-    const int c = (lane & 15) ^ swz128(row);
-    return (unsigned)(min(row, max_row) * (D * 2) + c * 16);
-  };
-  const unsigned voff_full[2] = {src_of(2 * w, G1_T - 1), src_of(2 * w + 1, G1_T - 1)};
-  const unsigned stat_off = ((lane & 8) && !OWNER_IS_Q) ? (unsigned)((const char*)ga.pos_pad - (const char*)ga.lse2) + 16u * (lane & 7) : 16u * (lane & 7);
-  const bool stat_wave = STR_STATS && wu == 0;
-  auto prefetch = [&](int u) __attribute__((always_inline)) {   // tile u -> stage u % 4
-    const int t0 = sbeg + u * G1_T;
-    const unsigned st = lds0 + (u & (G1_STAGES - 1)) * G1_STAGE;
-    const unsigned short* tile = R + (size_t)t0 * D;
-    if (stat_wave) dma_lanes16(lse_str + t0, stat_off, st);
-    if (t0 + G1_T <= Nr) {
-      dma_group<1>(tile, &voff_full[0], st + G1_STAT + (2 * wu) * 1024);
-      dma_group<1>(tile, &voff_full[1], st + G1_STAT + (2 * wu + 1) * 1024);
-    } else {  // ragged last tile: rows past the end re-read the last valid row (their g is forced to 0)
-#pragma unroll
-      for (int k = 0; k < 2; k++) {
-        const unsigned off = src_of(2 * w + k, Nr - 1 - t0);
-        dma_group<1>(tile, &off, st + G1_STAT + (2 * wu + k) * 1024);
-      }
-    }
-  };
-
-  // per-lane LDS addresses inside a stage
-  const unsigned sw_ln = swz128(ln);
-  // transposing reads: rows 16 kk + 8 e + 4 h + (l16 >> 2), chunk 4 mt + 2 (g16 & 1) + ((l16 & 3) >> 1), half l16 & 1
-  const int tr_r = 4 * h + (l16 >> 2), tr_c = 2 * (g16 & 1) + ((l16 & 3) >> 1);
-  unsigned troff[2][2];  // [kk][e]: the swizzle depends on the row, so one base per (kk, e); + 64 * mt
-#pragma unroll
-  for (int kk = 0; kk < 2; kk++)
-#pragma unroll
-    for (int e = 0; e < 2; e++) {
-      const int row = 16 * kk + 8 * e + tr_r;
-      troff[kk][e] = G1_STAT + row * 256 + 8 * (l16 & 1);   // chunk part added per mt (it is swizzled)
-    }
-
-  f32x16 acc[4][2];
-#pragma unroll
-  for (int mt = 0; mt < 4; mt++)
-#pragma unroll
-    for (int n = 0; n < 2; n++)
-#pragma unroll
-      for (int r = 0; r < 16; r++) acc[mt][n][r] = 0.f;
-
-  // ---- software pipeline over the tiles: iteration u interleaves, MFMA by MFMA, phase 1 of tile u+1, the
-  // exp2 arithmetic of tile u (whose scores iteration u-1 left in registers) and phase 2 of tile u-1 (whose g the
-  // previous iteration left as fragments): a wave's VALU work hides behind its own MFMAs only when interleaved.
-  // Tiles u-1, u, u+1 are alive in the ring, u+2 .. u+5 in flight.
-  f32x16 sacc[2][2];     // [tile parity][owner half]
-  bf16x8 gfr[2][2];      // g of the tile last through the softmax: [owner half][kk]
-#pragma unroll
-  for (int n = 0; n < 2; n++)
-#pragma unroll
-    for (int kk = 0; kk < 2; kk++)
-#pragma unroll
-      for (int e = 0; e < 8; e++) gfr[n][kk][e] = 0;
-
-#pragma unroll 1
-  for (int u = 0; u < min(nt, G1_AHEAD - 1); u++) prefetch(u);   // iteration -1 starts tile G1_AHEAD - 1
-
-  // PT: parity of tile u+1 (where phase 1 writes); the softmax reads parity PT ^ 1
-  // STEADY: all three parts are live (1 <= u, u + 1 < nt): no branches inside the MFMA stream
-  auto body = [&](int u, auto pt_tag, auto steady_tag) __attribute__((always_inline)) {
-    constexpr int PT = decltype(pt_tag)::value;
-    constexpr bool STEADY = decltype(steady_tag)::value;
-    const bool p1 = STEADY || (u + 1 < nt), sm = STEADY || (u >= 0 && u < nt), p2 = STEADY || (u >= 1);
-    // my loads of tile u+1 have landed (tiles up to u + G1_AHEAD - 1 have been started)
-    if (p1) {
-      const int later = min(nt - 1, u + G1_AHEAD - 1) - (u + 1);   // tiles started after u+1: 0 .. G1_AHEAD - 2
-      if (stat_wave) { if (later >= 4) wait_vmem<12>(); else if (later == 3) wait_vmem<9>(); else if (later == 2) wait_vmem<6>(); else if (later == 1) wait_vmem<3>(); else wait_vmem<0>(); }
-      else { if (later >= 4) wait_vmem<8>(); else if (later == 3) wait_vmem<6>(); else if (later == 2) wait_vmem<4>(); else if (later == 1) wait_vmem<2>(); else wait_vmem<0>(); }
-    }
-    __syncthreads();  // ... and everybody's; everybody is done with tile u-2, whose stage is loaded next
-    if (u + G1_AHEAD < nt) prefetch(u + G1_AHEAD);
-    const unsigned char* st_p1 = smem + ((u + 1) & (G1_STAGES - 1)) * G1_STAGE;
-    const unsigned char* st_sm = smem + (u & (G1_STAGES - 1)) * G1_STAGE;
-    const unsigned char* st_p2 = smem + ((u - 1) & (G1_STAGES - 1)) * G1_STAGE;
-    const int t0 = sbeg + u * G1_T;   // first streamed row of tile u
-
-    // fragments: row statistics of tile u, then tile u+1 for phase 1 and transposed tile u-1 for phase 2 in
-    // the order in which the rounds below consume them (LDS returns reads in order, and the 24 reads of the
-    // four waves keep the LDS busy for most of an iteration: the first MFMAs must not wait for the last read)
-    f32x4 lse_r[4]; i32x4 pos_r[4];
-    if (STR_STATS && sm) {
-#pragma unroll
-      for (int j = 0; j < 4; j++) {
-        lse_r[j] = *(const f32x4*)(st_sm + (8 * j + 4 * h) * 4);
-        if (!OWNER_IS_Q) pos_r[j] = *(const i32x4*)(st_sm + 128 + (8 * j + 4 * h) * 4);
-      }
-    }
-    bf16x8 pfr[8];
-    bf16x8 afr[4][2];
-    // round 2 k needs pfr[k] and afr[k / 2][k % 2]: the first four pairs are read here, pair k + 4 behind round 2 k + 1,
-    // into the registers that pair k has just left (all eight at once cost 32 registers that the loop does not have)
-    auto load_pair = [&](auto k_tag) __attribute__((always_inline)) {
-      constexpr int k = decltype(k_tag)::value;
-      if (p1) pfr[k] = *(const bf16x8*)(st_p1 + G1_STAT + ln * 256 + (((2 * k + h) ^ (int)sw_ln) * 16));
-      if (p2) {
-        constexpr int mt = k / 2, kk = k % 2;
-        s16x4 q[2];
-#pragma unroll
-        for (int e = 0; e < 2; e++) {
-          const int row = 16 * kk + 8 * e + tr_r;
-          const int c = (4 * mt + tr_c) ^ swz128(row);
-          q[e] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(st_p2 + troff[kk][e] + c * 16));
-        }
-        s16x8 t = {q[0][0], q[0][1], q[0][2], q[0][3], q[1][0], q[1][1], q[1][2], q[1][3]};
-        afr[mt][kk] = __builtin_bit_cast(bf16x8, t);
-      }
-    };
-    static_for<4>(load_pair);
-    // 16 rounds: one phase-1 MFMA pair position, one phase-2 MFMA, the exp2 of two scores
-    static_for<16>([&](auto i_tag) __attribute__((always_inline)) {
-      constexpr int i = decltype(i_tag)::value;
-      if (p1) {
-        constexpr int ks = i / 2, n = i % 2;
-        if constexpr (ks == 0) {
-          f32x16 z;
-#pragma unroll
-          for (int r = 0; r < 16; r++) z[r] = 0.f;
-          sacc[PT][n] = mfma32(pfr[ks], ofrag[n][ks], z);
-        } else {
-          sacc[PT][n] = mfma32(pfr[ks], ofrag[n][ks], sacc[PT][n]);
-        }
-      }
-      if (p2) {
-        constexpr int mt = i / 4, kk = (i / 2) % 2, n = i % 2;
-        acc[mt][n] = mfma32(afr[mt][kk], gfr[n][kk], acc[mt][n]);
-      }
-      if (sm) {
-#pragma unroll
-        for (int n = 0; n < 2; n++) {
-          float e;
-          if constexpr (SYM) {  // mean of the row softmax and the column softmax (folding the halves into the
-            // exponents saves two operations per score and measured slower here: 8 % while the kernel spilled, 1 % since)
-            const float t = sacc[PT ^ 1][n][i] * ga.alpha2;
-            e = 0.5f * fast_exp2(t - lse_o[n]) + 0.5f * fast_exp2(t - lse_r[i >> 2][i & 3]);
-          } else {
-            const float l = OWNER_IS_Q ? lse_o[n] : lse_r[i >> 2][i & 3];
-            e = fast_exp2(sacc[PT ^ 1][n][i] * ga.alpha2 - l);
-          }
-          // an empty statement that "uses" the value: it keeps the arithmetic inside this round (pure
-          // arithmetic would otherwise be moved behind all the MFMAs and run exposed)
-          if constexpr (STEADY) asm volatile("" : "+v"(e));
-          sacc[PT ^ 1][n][i] = e;
-        }
-      }
-      if constexpr (i % 2 == 1 && i / 2 + 4 < 8) load_pair(std::integral_constant<int, i / 2 + 4>{});
-      if constexpr (STEADY) __builtin_amdgcn_sched_barrier(0);  // the rounds stay in order
-    });
-    if (sm) {
-      // 0 at the positive (j == r_i: its term is added in fp32 by the kernel that sums the partials, see PosFix),
-      // zeros for rows past the end of the split and on the diagonal: few tiles
-      bool rare = (t0 + G1_T > send) || (ga.mask_self && (t0 < a0 + G1_OWN_W) && (t0 + G1_T > a0));
-      if (OWNER_IS_Q) {
-        rare = rare || (unsigned)(r_o[0] - t0) < (unsigned)G1_T || (unsigned)(r_o[1] - t0) < (unsigned)G1_T;
-      } else {
-#pragma unroll
-        for (int j = 0; j < 4; j++)
-#pragma unroll
-          for (int e = 0; e < 4; e++) rare = rare || (unsigned)(pos_r[j][e] - a0) < (unsigned)G1_OWN_W;
-      }
-      if (__builtin_amdgcn_ballot_w64(rare) != 0) {
-#pragma unroll
-        for (int n = 0; n < 2; n++)
-#pragma unroll
-          for (int r = 0; r < 16; r++) {
-            const int m = t0 + 8 * (r >> 2) + 4 * h + (r & 3);   // streamed row of this register
-            const bool hit = OWNER_IS_Q ? (r_o[n] == m) : (pos_r[r >> 2][r & 3] == own_idx[n]);
-            if (hit || m >= send || (ga.mask_self && m == own_idx[n])) sacc[PT ^ 1][n][r] = 0.f;
-          }
-      }
-    }
-    // the phase-2 MFMAs above have read the old fragments: now they take the g of tile u
-    if (sm) {
-#pragma unroll
-      for (int n = 0; n < 2; n++)
-#pragma unroll
-        for (int kk = 0; kk < 2; kk++) {
-          typedef __attribute__((ext_vector_type(8))) float f32x8;
-          const f32x16& g = sacc[PT ^ 1][n];
-          const f32x8 v = {g[8 * kk], g[8 * kk + 1], g[8 * kk + 2], g[8 * kk + 3], g[8 * kk + 4], g[8 * kk + 5], g[8 * kk + 6], g[8 * kk + 7]};
-          gfr[n][kk] = __builtin_convertvector(v, bf16x8);
-        }
-    }
-  };
-  // iterations u = -1 .. nt (phase 1 of tile 0 first, phase 2 of tile nt-1 last), two per trip so that the
-  // parity of the score registers is a compile-time constant
-  constexpr std::integral_constant<int, 0> pt0{};   // u odd: tile u+1 has parity 0
-  constexpr std::integral_constant<int, 1> pt1{};
-  body(-1, pt0, std::false_type{});
-  body(0, pt1, std::false_type{});
-  int u = 1;
-#pragma unroll 1
-  for (; u + 2 < nt; u += 2) {
-    body(u, pt0, std::true_type{});
-    body(u + 1, pt1, std::true_type{});
-  }
-#pragma unroll 1
-  for (; u <= nt; u += 2) {
-    body(u, pt0, std::false_type{});
-    if (u + 1 <= nt) body(u + 1, pt1, std::false_type{});
-  }
-
-  // ---- epilogue: lane (ln, h) holds owner row 32 n + ln, columns 32 mt + 8 (r / 4) + 4 h + r % 4 -----------------
-  float* out = OWNER_IS_Q ? (ga.dq_out + (size_t)split * ga.dq_split_stride) : (ga.dp_out + (size_t)split * ga.dp_split_stride);
-#pragma unroll
-  for (int n = 0; n < 2; n++) {
-    if (own_idx[n] < No) {
-#pragma unroll
-      for (int mt = 0; mt < 4; mt++)
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-          const f32x4 v = {acc[mt][n][4 * j] * ga.out_scale, acc[mt][n][4 * j + 1] * ga.out_scale,
-                           acc[mt][n][4 * j + 2] * ga.out_scale, acc[mt][n][4 * j + 3] * ga.out_scale};
-          *(f32x4*)(out + (size_t)own_idx[n] * D + 32 * mt + 8 * j + 4 * h) = v;
-        }
-    }
-  }
-}
-
-template <bool SYM>
-__global__ void __launch_bounds__(256) grad128_kernel(GradArgs ga) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char gsmem[];
-  check_shared_positives(ga);
-  const int nQ = ga.obQ * ga.nsq;
-  const int id = xcd_task_id();
-  if (id < nQ) {
-    grad128_body<true, SYM>(ga, id % ga.obQ, id / ga.obQ, gsmem);
-  } else {
-    const int t = id - nQ;
-    grad128_body<false, SYM>(ga, t % ga.obP, t / ga.obP, gsmem);
-  }
-}
-
-// ===========================================================================
-// Statistics pass for d = 128 (Eq. 4's normaliser, the positive's logit and the arg-max, per anchor and split).
-// The layout of the d = 128 gradient pass without its second contraction: a workgroup (4 waves) owns 256 anchors,
-// each wave 64 of them with all 128 columns in registers, and all four share the streamed target tiles (32 rows)
-// through the same LDS ring.  Lane (n, h) holds, for its two anchors 32 i + n, the scores of 16 of a tile's 32
-// targets; the other 16 are in lane (n, h ^ 1).  The running (max, sum, arg-max) of an anchor therefore lives in
-// a lane of its own and no lane talks to another before the end of the stream: 16 MFMAs against about 5 vector
-// operations per score, which a second workgroup on the same CU runs behind the first one's MFMAs.
-// ===========================================================================
-constexpr int S1_AHEAD = 6;   // tile u is read, tiles u+1 .. u+5 are in flight, tile u+6 goes where tile u-2 was
-template <bool ARGMAX>
-__global__ void __launch_bounds__(256, 2) stats128_kernel(const unsigned short* __restrict__ Q,
-                                                          const unsigned short* __restrict__ Pm,
-                                                          const int32_t* __restrict__ pos_idx, int B, int P,
-                                                          float alpha2, int mask_self, int n_ablk, int cols_per_split,
-                                                          float* __restrict__ part_m, float* __restrict__ part_l,
-                                                          int* __restrict__ part_idx, float* __restrict__ pos_t) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char s1mem[];
-  constexpr int D = 128;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, h = lane >> 5, ln = lane & 31;
-  const int task = xcd_task_id();
-  const int ablk = task % n_ablk, split = task / n_ablk;
-  const int a0 = ablk * G1_OWN + w * G1_OWN_W;   // this wave's first anchor
-  const int sbeg = split * cols_per_split, send = min(P, sbeg + cols_per_split);
-  const int nt = (send - sbeg + G1_T - 1) / G1_T;   // >= 1
-  const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)s1mem);
-  const int wu = __builtin_amdgcn_readfirstlane(w);
-
-  // anchors as B fragments: lane (ln, h) holds anchor 32 n + ln, columns 16 ks + 8 h .. + 7
-  bf16x8 ofrag[2][8];
-  int own_idx[2], r_o[2];
-#pragma unroll
-  for (int n = 0; n < 2; n++) {
-    own_idx[n] = a0 + 32 * n + ln;
-    const int row = min(own_idx[n], B - 1);
-#pragma unroll
-    for (int ks = 0; ks < 8; ks++) ofrag[n][ks] = *(const bf16x8*)(Q + (size_t)row * D + 16 * ks + 8 * h);
-    r_o[n] = (own_idx[n] < B) ? pos_idx[own_idx[n]] : -1;
-  }
-  // the compiler's own loads end here (it does not see the direct-to-LDS loads counted by wait_vmem below)
-#pragma unroll
-  for (int n = 0; n < 2; n++) {
-#pragma unroll
-    for (int ks = 0; ks < 8; ks++) asm volatile("" : "+v"(ofrag[n][ks]));
-    asm volatile("" : "+v"(r_o[n]));
-  }
-
-  // loads of a streamed tile: 8 instructions of 4 rows, two per wave; lane -> (row, chunk position)
-  auto src_of = [&](int it, int max_row) __attribute__((always_inline)) -> unsigned {
-    const int row = 4 * it + (lane >> 4);
-    const int c = (lane & 15) ^ swz128(row);
-    return (unsigned)(min(row, max_row) * (D * 2) + c * 16);
-  };
-  const unsigned voff_full[2] = {src_of(2 * w, G1_T - 1), src_of(2 * w + 1, G1_T - 1)};
-  auto prefetch = [&](int u) __attribute__((always_inline)) {
-    const int t0 = sbeg + u * G1_T;
-    const unsigned st = lds0 + (u & (G1_STAGES - 1)) * G1_STAGE;
-    const unsigned short* tile = Pm + (size_t)t0 * D;
-    if (t0 + G1_T <= P) {
-      dma_group<1>(tile, &voff_full[0], st + G1_STAT + (2 * wu) * 1024);
-      dma_group<1>(tile, &voff_full[1], st + G1_STAT + (2 * wu + 1) * 1024);
-    } else {  // ragged last tile: rows past the end re-read the last valid row (masked below)
-#pragma unroll
-      for (int k = 0; k < 2; k++) {
-        const unsigned off = src_of(2 * w + k, P - 1 - t0);
-        dma_group<1>(tile, &off, st + G1_STAT + (2 * wu + k) * 1024);
-      }
-    }
-  };
-  const unsigned sw_ln = swz128(ln);
-
-  float rm[2], rl[2], rpos[2];
-  int ridx[2];
-  bool got[2];
-#pragma unroll
-  for (int n = 0; n < 2; n++) { rm[n] = -INFINITY; rl[n] = 0.f; rpos[n] = 0.f; ridx[n] = 0x7fffffff; got[n] = false; }
-
-#pragma unroll 1
-  for (int u = 0; u < min(nt, S1_AHEAD); u++) prefetch(u);
-
-#pragma unroll 1
-  for (int u = 0; u < nt; u++) {
-    // my loads of tile u have landed: two instructions per tile, tiles up to u + S1_AHEAD - 1 have been started
-    const int later = min(nt - 1, u + S1_AHEAD - 1) - u;
-    if (later >= 5) wait_vmem<10>(); else if (later == 4) wait_vmem<8>(); else if (later == 3) wait_vmem<6>();
-    else if (later == 2) wait_vmem<4>(); else if (later == 1) wait_vmem<2>(); else wait_vmem<0>();
-    __syncthreads();  // ... and everybody's; everybody is past tile u-1, so the stage of tile u-2 is free
-    if (u + S1_AHEAD < nt) prefetch(u + S1_AHEAD);
-    const unsigned char* st = s1mem + (u & (G1_STAGES - 1)) * G1_STAGE;
-    const int t0 = sbeg + u * G1_T;
-
-    bf16x8 pfr[8];
-#pragma unroll
-    for (int k = 0; k < 8; k++) pfr[k] = *(const bf16x8*)(st + G1_STAT + ln * 256 + (((2 * k + h) ^ (int)sw_ln) * 16));
-    f32x16 s[2];
-#pragma unroll
-    for (int n = 0; n < 2; n++)
-#pragma unroll
-      for (int r = 0; r < 16; r++) s[n][r] = 0.f;
-#pragma unroll
-    for (int k = 0; k < 8; k++)
-#pragma unroll
-      for (int n = 0; n < 2; n++) s[n] = mfma32(pfr[k], ofrag[n][k], s[n]);
-
-    // online statistics; s holds raw dot products, the base-2 logit is alpha2 * s (alpha2 > 0: same order).
-    // Register r of lane (ln, h) is target t0 + 8 (r / 4) + 4 h + r % 4: increasing in r.
-    // the masks that can touch this tile: few tiles, and one scalar branch for the wave (as a per-lane condition the
-    // compiler turns the masking into selects that every tile then pays for)
-    bool rare = (t0 + G1_T > send) || (mask_self && t0 < a0 + G1_OWN_W && t0 + G1_T > a0);
-    rare = rare || (unsigned)(r_o[0] - t0) < (unsigned)G1_T || (unsigned)(r_o[1] - t0) < (unsigned)G1_T;
-    if (__builtin_amdgcn_ballot_w64(rare) != 0) {
-#pragma unroll
-      for (int n = 0; n < 2; n++)
-#pragma unroll
-        for (int r = 0; r < 16; r++) {
-          const int j = t0 + 8 * (r >> 2) + 4 * h + (r & 3);
-          const bool self = mask_self && j == own_idx[n];
-          const bool masked = j >= send || self;
-          // (a positive that the self-mask removes has the logit -inf: its row loss is then +inf)
-          if (j == r_o[n] && j < send) { rpos[n] = self ? -INFINITY : s[n][r] * alpha2; got[n] = true; }
-          if (masked) s[n][r] = -INFINITY;
-        }
-    }
-#pragma unroll
-    for (int n = 0; n < 2; n++) {
-      float tmr = -INFINITY; int tc = 0;
-#pragma unroll
-      for (int r = 0; r < 16; r++) {
-        const float t = s[n][r];
-        if (ARGMAX) {
-          const bool le = t <= tmr;   // strict >: the first (smallest) index attaining the maximum
-          tmr = le ? tmr : t;
-          tc = le ? tc : r;
-        } else {
-          tmr = fmaxf(tmr, t);
-        }
-      }
-      if (tmr > -INFINITY) {
-        const float tm = tmr * alpha2;
-        const float mn = fmaxf(rm[n], tm);
-        float sum = 0.f;
-#pragma unroll
-        for (int r = 0; r < 16; r++) sum += fast_exp2(__builtin_fmaf(s[n][r], alpha2, -mn));
-        rl[n] = rl[n] * fast_exp2(rm[n] - mn) + sum;
-        if (ARGMAX && tm > rm[n]) ridx[n] = t0 + 8 * (tc >> 2) + 4 * h + (tc & 3);  // later tiles have larger indices
-        rm[n] = mn;
-      }
-    }
-  }
-
-  // the positive's score is seen by exactly one lane of one workgroup
-#pragma unroll
-  for (int n = 0; n < 2; n++)
-    if (got[n] && own_idx[n] < B) pos_t[own_idx[n]] = rpos[n];
-  // combine the two half-waves (same anchor, the other 16 targets of every tile), then write the split partial
-#pragma unroll
-  for (int n = 0; n < 2; n++) {
-    const float m2 = __shfl_xor(rm[n], 32), l2 = __shfl_xor(rl[n], 32);
-    const int i2 = __shfl_xor(ridx[n], 32);
-    stat_merge(rm[n], rl[n], ridx[n], m2, l2, i2);
-    if (h == 0 && own_idx[n] < B) {
-      const size_t o = (size_t)split * B + own_idx[n];
-      part_m[o] = rm[n]; part_l[o] = rl[n]; part_idx[o] = ridx[n];
-    }
-  }
-}
-
-template <bool ARGMAX>
-static hipError_t stats128_launch(const LossArgs& a, const LossPlan& pl) {
-  static bool attr_done[64];
-  if (hipError_t e = ensure_dyn_lds((const void*)stats128_kernel<ARGMAX>, G1_SMEM, attr_done); e != hipSuccess) return e;
-  char* ws = a.ws;
-  const int n_ablk = (a.B + G1_OWN - 1) / G1_OWN;
-  stats128_kernel<ARGMAX><<<n_ablk * pl.stat_splits, 256, G1_SMEM, a.stream>>>(
-      (const unsigned short*)a.q, (const unsigned short*)a.p, a.pos_idx, a.B, a.P, a.alpha * kLog2e,
-      (a.flags & GC_MASK_SELF) ? 1 : 0, n_ablk, pl.stat_cols_per_split, (float*)(ws + pl.off_part_m),
-      (float*)(ws + pl.off_part_l), (int*)(ws + pl.off_part_idx), (float*)(ws + pl.off_pos));
-  return hipGetLastError();
-}
-static hipError_t launch_stats128(const LossArgs& a, const LossPlan& pl) {
-  return a.argmax ? stats128_launch<true>(a, pl) : stats128_launch<false>(a, pl);
-}
-
 template <int D, bool SYM>
 __global__ void __launch_bounds__(256) grad_mfma_kernel(GradArgs ga) {
   extern __shared__ __attribute__((aligned(16))) unsigned char gsmem[];
@@ -1613,14 +663,6 @@ template <int D>
 static hipError_t grad_mfma_launch(const GradArgs& ga, int nwg, hipStream_t stream) {
   return ga.lse2_t ? grad_mfma_launch_as<D, true>(ga, nwg, stream) : grad_mfma_launch_as<D, false>(ga, nwg, stream);
 }
-template <bool SYM>
-static hipError_t grad128_launch(const GradArgs& ga, int nwg, hipStream_t stream) {
-  static bool attr_done[64];
-  if (hipError_t e = ensure_dyn_lds((const void*)grad128_kernel<SYM>, G1_SMEM, attr_done); e != hipSuccess) return e;
-  grad128_kernel<SYM><<<nwg, 256, G1_SMEM, stream>>>(ga);
-  return hipGetLastError();
-}
-
 hipError_t launch_grad_mfma(const LossArgs& a, const LossPlan& pl) {
   char* ws = a.ws;
   GradArgs ga{};
@@ -1652,7 +694,7 @@ hipError_t launch_grad_mfma(const LossArgs& a, const LossPlan& pl) {
   if (nwg == 0) { prof_mark_grad_kernel_done(a.stream); return hipSuccess; }
   hipError_t e;
   switch (a.d) {
-    case 128: e = ga.lse2_t ? grad128_launch<true>(ga, nwg, a.stream) : grad128_launch<false>(ga, nwg, a.stream); break;
+    case 128: e = grad128_launch(ga, nwg, a.stream); break;
     case 256: e = grad_mfma_launch<256>(ga, nwg, a.stream); break;
     case 384: e = grad_mfma_launch<384>(ga, nwg, a.stream); break;
     case 512: e = grad_mfma_launch<512>(ga, nwg, a.stream); break;

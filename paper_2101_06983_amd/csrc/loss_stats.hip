@@ -1,0 +1,301 @@
+// Statistics pass of the bf16 loss path for gfx950 (widths from 256; d = 128: loss_mfma128.hip), Eq. 1 / Eq. 4: per anchor,
+// online max and sum of 2^t over target tiles, the positive's score and the argmax; the score tile lives in MFMA
+// accumulators only.
+#include "mfma_common.h"
+#include "stats_tile.h"
+
+namespace gc {
+
+// ===========================================================================
+// Statistics pass.  Workgroup = 512 threads = 8 waves as 2 (targets, M) x 4 (anchors, N);
+// workgroup tile 256 targets x 256 anchors, wave tile 128 x 64 (4 x 2 MFMA tiles).
+// k is staged through LDS in chunks of 64, two stages.
+// ===========================================================================
+constexpr int ST_TM = 256, ST_TN = 256, ST_KC = 64;
+constexpr int ST_ROWB = ST_KC * 2;                       // bytes per LDS row (8 chunks of 16 bytes, unpadded)
+constexpr int ST_STAGE_BYTES = (ST_TM + ST_TN) * ST_ROWB;  // one stage: 256 target rows, then 256 anchor rows
+// LDS layout: chunk c of row r is stored at chunk position c ^ ((r >> 1) & 7): the 16 rows that a
+// 16-lane group reads in one fragment load then fall into 16 different 16-byte bank groups.
+
+__global__ void __launch_bounds__(512) stats_mfma_kernel(const unsigned short* __restrict__ Q,
+                                                         const unsigned short* __restrict__ Pm,
+                                                         const int32_t* __restrict__ pos_idx, int B, int P, int d,
+                                                         float alpha2, int mask_self, int n_ablk, int cols_per_split,
+                                                         float* __restrict__ part_m, float* __restrict__ part_l,
+                                                         int* __restrict__ part_idx, float* __restrict__ pos_t) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_b[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave & 1, wn = wave >> 1;
+  const int task = xcd_task_id();
+  const int ablk = task % n_ablk, split = task / n_ablk;
+  const int a0 = ablk * ST_TN;
+  const int cbeg = split * cols_per_split, cend = min(P, cbeg + cols_per_split);
+  const int nk = d / ST_KC;
+
+  // ---- direct global->LDS loads: wave w fills rows 64 w .. 64 w + 63 of a stage (waves 0-3 the target
+  // rows, waves 4-7 the anchor rows), 8 instructions of 8 rows x 8 chunks each -------------------------
+  const int wave_u = __builtin_amdgcn_readfirstlane(wave);  // as a scalar: what follows from it stays uniform
+  const bool loads_q = wave_u >= 4;
+  const unsigned short* lmat = loads_q ? Q : Pm;
+  const int lrows = loads_q ? B : P;
+  const int lrow_in = (wave_u & 3) * 64 + (lane >> 3);  // + 8 j: row inside the 256-row tile
+  const unsigned stage_m0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)smem_b + wave_u * 64 * ST_ROWB);
+  auto src_of = [&](int j, int tile_row0, bool clamp) -> unsigned {  // byte offset from the tile's first row, chunk kc = 0
+    int r = lrow_in + 8 * j;
+    const int c = (lane & 7) ^ ((r >> 1) & 7);
+    if (clamp) r = min(r, lrows - 1 - tile_row0);
+    return (unsigned)(r * d * 2 + c * 16);
+  };
+  unsigned voff_full[8];  // full tile, with the instruction offset 1024 (j % 4) pre-subtracted
+#pragma unroll
+  for (int j = 0; j < 8; j++) voff_full[j] = src_of(j, 0, false) - 1024u * (j & 3);
+  auto prefetch = [&](int tile_row0, int kc, int stage) __attribute__((always_inline)) {
+    const unsigned short* base_v = lmat + (size_t)tile_row0 * d + kc * ST_KC;  // the same in every lane of a wave
+    const unsigned long long bu = (unsigned long long)(uintptr_t)base_v;
+    const unsigned short* base = (const unsigned short*)(uintptr_t)(
+        // readfirstlane returns int: go through unsigned, or the low half sign-extends into the high one
+        ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((unsigned)(bu >> 32)) << 32) |
+        (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((unsigned)bu));
+    const unsigned m0 = stage_m0 + stage * ST_STAGE_BYTES;
+    if (tile_row0 + 256 <= lrows) {
+      dma_group<4>(base, &voff_full[0], m0);
+      dma_group<4>(base, &voff_full[4], m0 + 4096);
+    } else {  // ragged tile: rows past the end re-read the last valid row (masked later)
+#pragma unroll
+      for (int j = 0; j < 8; j++) {
+        const unsigned off = src_of(j, tile_row0, true);
+        dma_group<1>(base, &off, m0 + j * 1024);
+      }
+    }
+  };
+
+  // ---- fragment addresses: row (lane & 31) of an MFMA tile, chunk 2 ks + (lane >> 5), swizzled ---------
+  const int swz_l = ((lane & 31) >> 1) & 7;
+  unsigned koff[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ks++) koff[ks] = (unsigned)(((2 * ks + (lane >> 5)) ^ swz_l) * 16);
+  const unsigned char* a_base = smem_b + (wm * 128 + (lane & 31)) * ST_ROWB;               // + mt * 32 rows
+  const unsigned char* b_base = smem_b + (ST_TM + wn * 64 + (lane & 31)) * ST_ROWB;        // + nt * 32 rows
+
+  // per-lane running statistics for its two anchor columns
+  float rm[2], rl[2], rpos[2];
+  int ridx[2], a_col[2], r_of[2];
+#pragma unroll
+  for (int nt = 0; nt < 2; nt++) {
+    rm[nt] = -INFINITY; rl[nt] = 0.f; rpos[nt] = 0.f; ridx[nt] = 0x7fffffff;
+    a_col[nt] = a0 + wn * 64 + nt * 32 + (lane & 31);
+    r_of[nt] = (a_col[nt] < B) ? pos_idx[a_col[nt]] : -1;
+  }
+
+  // The k-chunks of all the tiles of this workgroup form one sequence of steps; step st lives in stage st & 1 and
+  // its loads are issued one step ahead inside a tile.  (Loading the first chunk of the next tile under the last
+  // MFMAs of this one was measured too: no gain at 2 tiles of 12 chunks, a loss at 16 tiles of 2 chunks.)
+  int st = 0;
+  for (int b0 = cbeg; b0 < cend; b0 += ST_TM) {
+    f32x16 acc[4][2];
+#pragma unroll
+    for (int mt = 0; mt < 4; mt++)
+#pragma unroll
+      for (int nt = 0; nt < 2; nt++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) acc[mt][nt][r] = 0.f;
+
+    const int row0 = loads_q ? a0 : b0;
+    // nothing is in flight and every reader is past the last barrier: both stages are free
+    prefetch(row0, 0, st & 1);
+    wait_vmem<0>();
+    __syncthreads();
+    bf16x8 af[2][4], bfg[2][2];
+    for (int kc = 0; kc < nk; kc++, st++) {
+      if (kc + 1 < nk) prefetch(row0, kc + 1, (st + 1) & 1);
+      const int so = (st & 1) * ST_STAGE_BYTES;
+      __builtin_amdgcn_iglp_opt(0);  // scheduler hint: interleave the fragment reads with the MFMA stream
+      auto load_frags = [&](int ks, int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int mt = 0; mt < 4; mt++) af[buf][mt] = *(const bf16x8*)(a_base + so + mt * 32 * ST_ROWB + koff[ks]);
+#pragma unroll
+        for (int nt = 0; nt < 2; nt++) bfg[buf][nt] = *(const bf16x8*)(b_base + so + nt * 32 * ST_ROWB + koff[ks]);
+      };
+      load_frags(0, 0);
+#pragma unroll
+      for (int ks = 0; ks < ST_KC / 16; ks++) {
+        if (ks + 1 < ST_KC / 16) load_frags(ks + 1, (ks + 1) & 1);
+#pragma unroll
+        for (int mt = 0; mt < 4; mt++)
+#pragma unroll
+          for (int nt = 0; nt < 2; nt++) acc[mt][nt] = mfma32(af[ks & 1][mt], bfg[ks & 1][nt], acc[mt][nt]);
+      }
+      wait_vmem<0>();   // this wave's part of the next stage has landed
+      __syncthreads();  // ... and everybody's; nobody still reads the stage that is overwritten next
+    }
+
+    // ---- tile epilogue: online softmax statistics, all in registers; acc holds the raw dot products, the
+    // base-2 logit is t = alpha2 * acc (alpha2 > 0: the order of the raw values is the order of the logits) -------
+    const int brow0 = b0 + wm * 128 + 4 * (lane >> 5);  // + mt*32 + 8*(r/4) + r%4
+    const bool edge = (b0 + ST_TM > cend);
+#pragma unroll
+    for (int nt = 0; nt < 2; nt++) {
+      const int a = a_col[nt];
+      // the masks that can touch this tile
+      const bool diag = mask_self && (a >= b0 && a < b0 + ST_TM);
+      const bool haspos = (unsigned)(r_of[nt] - b0) < (unsigned)ST_TM;
+      if (edge || diag || haspos) {  // rare: the general slow walk
+#pragma unroll
+        for (int mt = 0; mt < 4; mt++)
+#pragma unroll
+          for (int r = 0; r < 16; r++) {
+            int j = brow0 + mt * 32 + 8 * (r >> 2) + (r & 3);
+            if (j == r_of[nt]) rpos[nt] = acc[mt][nt][r] * alpha2;
+            if (j >= cend || (mask_self && j == a)) acc[mt][nt][r] = -INFINITY;
+          }
+      }
+      // tile max + first index attaining it (rows are visited in increasing j within mt; across
+      // register order j is increasing too, so a strict > keeps the smallest index)
+      float tmr = -INFINITY; int tc = 0;
+#pragma unroll
+      for (int mt = 0; mt < 4; mt++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+          const float t = acc[mt][nt][r];
+          const bool le = t <= tmr;
+          tmr = le ? tmr : t;
+          tc = le ? tc : (mt * 32 + 8 * (r >> 2) + (r & 3));
+        }
+      if (tmr > -INFINITY) {
+        const float tm = tmr * alpha2;
+        const float mn = fmaxf(rm[nt], tm);
+        float s = 0.f;
+#pragma unroll
+        for (int mt = 0; mt < 4; mt++)
+#pragma unroll
+          for (int r = 0; r < 16; r++) s += fast_exp2(__builtin_fmaf(acc[mt][nt][r], alpha2, -mn));
+        rl[nt] = rl[nt] * fast_exp2(rm[nt] - mn) + s;
+        if (tm > rm[nt]) ridx[nt] = brow0 + tc;  // later tiles have larger j: strict >
+        rm[nt] = mn;
+      }
+    }
+  }
+
+  // ---- combine the two half-waves (same anchor column, different target rows) -------------------
+#pragma unroll
+  for (int nt = 0; nt < 2; nt++) {
+    float m2 = __shfl_xor(rm[nt], 32), l2 = __shfl_xor(rl[nt], 32);
+    int i2 = __shfl_xor(ridx[nt], 32);
+    stat_merge(rm[nt], rl[nt], ridx[nt], m2, l2, i2);
+  }
+  // ---- combine the two waves along M through LDS, then write the split partial ------------------
+  __syncthreads();
+  float* xs = (float*)smem_b;  // [4 wn][2 nt][32][3]
+  if (wm == 1 && lane < 32) {
+#pragma unroll
+    for (int nt = 0; nt < 2; nt++) {
+      float* x = xs + ((wn * 2 + nt) * 32 + lane) * 3;
+      x[0] = rm[nt]; x[1] = rl[nt]; x[2] = __builtin_bit_cast(float, ridx[nt]);
+    }
+  }
+  __syncthreads();
+  if (wm == 0 && lane < 32) {
+#pragma unroll
+    for (int nt = 0; nt < 2; nt++) {
+      const float* x = xs + ((wn * 2 + nt) * 32 + lane) * 3;
+      stat_merge(rm[nt], rl[nt], ridx[nt], x[0], x[1], __builtin_bit_cast(int, x[2]));
+      int a = a_col[nt];
+      if (a < B) {
+        part_m[(size_t)split * B + a] = rm[nt];
+        part_l[(size_t)split * B + a] = rl[nt];
+        part_idx[(size_t)split * B + a] = ridx[nt];
+      }
+    }
+  }
+  // the positive's score is seen by exactly one lane of one workgroup
+#pragma unroll
+  for (int nt = 0; nt < 2; nt++) {
+    int a = a_col[nt], r = r_of[nt];
+    if (a < B && r >= cbeg && r < cend) {
+      // lane that held row r: rows of this lane are brow(mt, reg) with 4*(lane>>5) offset
+      int rel = (r - cbeg) % ST_TM;  // row inside its tile
+      int wmr = rel / 128, in = rel % 128;
+      int half = (in % 8) / 4;
+      // a positive that the self-mask removes has the logit -inf (its row loss is then +inf)
+      if (wmr == wm && half == (lane >> 5)) pos_t[a] = (mask_self && r == a) ? -INFINITY : rpos[nt];
+    }
+  }
+}
+
+// ===========================================================================
+// Statistics pass for few scores: 32 x 32 tiles, the contraction split over the four waves of a workgroup in 64-wide
+// chunks, every operand loaded straight into registers (lane (n, h) takes elements 32 h .. 32 h + 31 of a chunk of its
+// row, so that two lanes use a whole 128-byte line; any order of k works if both operands share it).  The kernel above
+// has 256 x 256 tiles: 23 us for the one workgroup of 128 x 256 scores and 26 us for the eight of 512 x 1024 at d = 768,
+// all latency of twelve dependent k-chunks.  Here a wave has all its loads in flight at once: 6.6 and 9.7 us.  It costs
+// B P d / 8 bytes of L2 traffic, so the larger tiles win again from about 2^20 scores (a version with 64 x 64 tiles took
+// 37 us at 1021 x 4099 x 384, the 256 x 256 kernel 23).
+// ===========================================================================
+__global__ void __launch_bounds__(256) stats_small_kernel(StatsSmallArgs g) {
+  constexpr int T = kStatTile, PD = 3;
+  __shared__ StatTileLds lds;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, ln = lane & 31;
+  const int task = xcd_task_id();
+  const int a0 = (task % g.n_ablk) * T, split = task / g.n_ablk;
+  const int nch = g.d / 64;
+  const char* qp = (const char*)(g.Q + (size_t)min(a0 + ln, g.B - 1) * g.d + 32 * h);
+  StatTile<false> st(g, a0);
+  const int t_end = min(g.tiles, (split + 1) * g.tiles_per_split);
+  for (int t = split * g.tiles_per_split; t < t_end; t++) {
+    const int j0 = t * T;
+    const char* pp = (const char*)(g.P + (size_t)min(j0 + ln, g.Pn - 1) * g.d + 32 * h);
+    u32x4 fq[PD][4], fp[PD][4];
+    auto issue = [&](int slot, int c) __attribute__((always_inline)) {
+#pragma unroll
+      for (int v = 0; v < 4; v++) {
+        fq[slot][v] = *(const u32x4*)(qp + (size_t)c * 128 + 16 * v);
+        fp[slot][v] = *(const u32x4*)(pp + (size_t)c * 128 + 16 * v);
+      }
+    };
+    f32x16 acc;
+#pragma unroll
+    for (int e = 0; e < 16; e++) acc[e] = 0.f;
+#pragma unroll
+    for (int p = 0; p < PD; p++)
+      if (wave + 4 * p < nch) issue(p, wave + 4 * p);
+    for (int base = wave; base < nch; base += 4 * PD) {
+#pragma unroll
+      for (int p = 0; p < PD; p++) {
+        const int c = base + 4 * p;
+        if (c < nch) {
+#pragma unroll
+          for (int v = 0; v < 4; v++) acc = mfma32(__builtin_bit_cast(bf16x8, fp[p][v]), __builtin_bit_cast(bf16x8, fq[p][v]), acc);
+          if (c + 4 * PD < nch) issue(p, c + 4 * PD);
+        }
+      }
+    }
+    StatTile<false>::put(lds, wave, acc);
+    __syncthreads();
+    st.tile(g, lds, j0);
+    __syncthreads();   // the partial tiles have been read
+  }
+  st.finish(g, lds, split);
+}
+static hipError_t launch_stats_small(const LossArgs& a, const LossPlan& pl) {
+  const StatsSmallArgs g = stats_small_args(a, pl, (const unsigned short*)a.q, (const unsigned short*)a.p);
+  stats_small_kernel<<<g.n_ablk * pl.stat_splits, 256, 0, a.stream>>>(g);
+  return hipGetLastError();
+}
+
+hipError_t launch_stats_mfma(const LossArgs& a, const LossPlan& pl) {
+  if (pl.stat_tile) return launch_stats_small(a, pl);
+  if (a.d == 128) return launch_stats128(a, pl);   // whole anchor rows in registers: a kernel of its own
+  char* ws = a.ws;
+  const int n_ablk = (a.B + ST_TN - 1) / ST_TN;
+  const size_t smem = (size_t)2 * ST_STAGE_BYTES;
+  static bool attr_done[64];
+  if (hipError_t e = ensure_dyn_lds((const void*)stats_mfma_kernel, (int)smem, attr_done); e != hipSuccess) return e;
+  stats_mfma_kernel<<<n_ablk * pl.stat_splits, 512, smem, a.stream>>>(
+      (const unsigned short*)a.q, (const unsigned short*)a.p, a.pos_idx, a.B, a.P, a.d, a.alpha * kLog2e,
+      (a.flags & GC_MASK_SELF) ? 1 : 0, n_ablk, pl.stat_cols_per_split, (float*)(ws + pl.off_part_m),
+      (float*)(ws + pl.off_part_l), (int*)(ws + pl.off_part_idx), (float*)(ws + pl.off_pos));
+  return hipGetLastError();
+}
+
+
+}  // namespace gc
