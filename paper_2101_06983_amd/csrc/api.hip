@@ -60,7 +60,7 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
       pl.stat_cols_per_split = ceil_div(tiles, splits) * 256;
       pl.stat_splits = ceil_div(P, pl.stat_cols_per_split);
     }
-    const int own = (d == 128) ? 256 : 64;   // owner rows per workgroup of the gradient kernel for this width
+    const int own = (d == 128) ? 128 : 64;   // owner rows per workgroup of the gradient kernel for this width
     const long long obQ = ceil_div(B, own), obP = ceil_div(P, own);
     // NT-Xent on these kernels is one walk (the score matrix is symmetric: see launch_grad_mfma)
     pl.one_walk = ntxent ? 1 : 0;
@@ -72,8 +72,8 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
     // 15.6 with 32).
     // Measured: 14 us and 0.03 to 0.05 us per row at d = 768, 0.03 at d = 128; partials about 4 TB/s.
     // (Two workgroups of the d = 256 kernel share a compute unit, each at some 70 % of its speed.)
-    const double row_us = d == 128 ? 0.031 : 0.015 + 0.035 * d / 768.0;
-    const int per_cu = d == 256 ? 2 : 1;
+    const double row_us = d == 128 ? 0.0145 : 0.015 + 0.035 * d / 768.0;
+    const int per_cu = d <= 256 ? 2 : 1;
     auto len_of = [](int n, int ns) { return (ceil_div(n, ns) + 31) / 32 * 32; };
     auto parts_bytes = [&](int nsq, int nsp) { return ((double)nsq * B + (double)nsp * P) * d * 4; };
     double best_us = 0;
@@ -105,7 +105,9 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
       ns = ceil_div(n, len);
     };
     pl.nsq = pl.nsp = 1; pl.q_stream_len = len_of(P, 1); pl.p_stream_len = len_of(B, 1);
-    const long long rows_q = obQ * P, rows_p = obP * B, rows_all = pl.one_walk ? rows_q : rows_q + rows_p;
+    // (equal shares count 256 rows of width 128 to a block: what a limited workspace takes does not depend on the kernel)
+    const int share_own = (d == 128) ? 256 : 64;
+    const long long rows_q = (long long)ceil_div(B, share_own) * P, rows_p = (long long)ceil_div(P, share_own) * B, rows_all = pl.one_walk ? rows_q : rows_q + rows_p;
     if (equal) {
       share(rows_all, P, pl.nsq, pl.q_stream_len);
       share(rows_all, B, pl.nsp, pl.p_stream_len);
@@ -370,7 +372,7 @@ static int run_loss(const LossArgs& a_in, const LossPlan& pl) {
   LossArgs a = a_in;
   if (!a.ws2) a.ws2 = a.ws;
   // does the gradient pass of this call end in a sum of split partials that takes the row losses along?
-  a.loss_with_partials = pl.route != ROUTE_GENERAL && !a.lse2_t && !a.defer_loss_sum && (a.dz || a.dq || a.dp);
+  a.loss_with_partials = pl.route != ROUTE_GENERAL && (a.sym[0] || (!a.lse2_t && !a.defer_loss_sum)) && (a.dz || a.dq || a.dp);
   const int call = g_prof.calls;
   prof_mark(call, 0, a.stream);
   hipError_t e;
@@ -407,12 +409,16 @@ static int run_loss(const LossArgs& a_in, const LossPlan& pl) {
     if (g_prof.on) g_prof.calls++;
     return GC_OK;
   }
-  if (!a.lse2_t) {
+  if (a.both) {
+    if (launch_stats_both(a, pl, *a.both) != hipSuccess) return GC_ERR_HIP;
+  } else if (!a.lse2_t) {
     e = pl.route == ROUTE_MFMA ? launch_stats_mfma(a, pl) : pl.route == ROUTE_PLANES ? launch_stats_planes(a, pl) : launch_stats_generic(a, pl);
     if (e != hipSuccess) return GC_ERR_HIP;
   }
   prof_mark(call, 1, a.stream);
-  if (!a.lse2_t) {
+  if (a.both) {
+    if (launch_both_merge(a, pl, *a.both) != hipSuccess) return GC_ERR_HIP;
+  } else if (!a.lse2_t) {
     e = launch_stats_merge(a, pl);
     if (e != hipSuccess) return GC_ERR_HIP;
   }
@@ -442,16 +448,18 @@ static int check_loss_args(int dt, const void* q, const void* p, const int32_t* 
   return GC_OK;
 }
 
-__global__ void pair_index_kernel(int32_t* r, int n) {
+__global__ void pair_index_kernel(int32_t* r, int n, int* zero) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) r[i] = i ^ 1;
+  if (i == 0) *zero = 0;
 }
 
 // rinv[r[i]] = i; entries that no r[i] points at keep -1 (then r is no bijection, and the second direction of the
 // symmetric loss reports them as positives out of range)
-__global__ void fill_i32_kernel(int32_t* x, int n, int v) {
+__global__ void fill_i32_kernel(int32_t* x, int n, int v, int* zero) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) x[i] = v;
+  if (i == 0) *zero = 0;
 }
 __global__ void invert_perm_kernel(const int32_t* r, int32_t* rinv, int n) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -645,9 +653,17 @@ int gc_ntxent_loss_and_grad_bf16(const void* z, int n_views, int d, float temp, 
   a.loss = loss; a.dz = dz;
   a.ws = (char*)workspace; a.stream = (hipStream_t)stream;
   int32_t* r = (int32_t*)(a.ws + pl.off_pos_idx);
-  pair_index_kernel<<<(n_views + 255) / 256, 256, 0, a.stream>>>(r, n_views);
-  if (hipGetLastError() != hipSuccess) return GC_ERR_HIP;
-  a.pos_idx = r;
+  a.wide = (int*)(a.ws + pl.off_err) + 2;
+  if (pl.one_walk) a.wexp = (float*)(a.ws + pl.off_part_idx);
+  const BothPlan both = plan_both(n_views, d, true, pl);
+  if (both.use) {   // the pairs are written by the kernel that merges the statistics
+    a.both = &both;
+    a.pos_idx = (const int32_t*)(a.ws + pl.off_pos_pad);
+  } else {
+    pair_index_kernel<<<(n_views + 255) / 256, 256, 0, a.stream>>>(r, n_views, a.wide);
+    if (hipGetLastError() != hipSuccess) return GC_ERR_HIP;
+    a.pos_idx = r;
+  }
   return run_loss(a, pl);
 }
 
@@ -690,30 +706,37 @@ int gc_bidirectional_loss_and_rep_grad_bf16(const void* q, const void* p, const 
   hipStream_t s = (hipStream_t)stream;
   int32_t* rinv = (int32_t*)(ws + sp.off_rinv);
   float* l = (float*)(ws + sp.off_l);
-  fill_i32_kernel<<<(n + 255) / 256, 256, 0, s>>>(rinv, n, -1);
-  invert_perm_kernel<<<(n + 255) / 256, 256, 0, s>>>(pos_idx, rinv, n);
-  if (hipGetLastError() != hipSuccess) return GC_ERR_HIP;
+  int* wide = (int*)(ws + sp.pl.off_err) + 2;
+  const BothPlan both = sp.pl.use_mfma ? plan_both(n, d, false, sp.pl) : BothPlan{};
+  if (!both.use) {   // (else the statistics pass inverts the pairing, and its merge checks it)
+    fill_i32_kernel<<<(n + 255) / 256, 256, 0, s>>>(rinv, n, -1, wide);
+    invert_perm_kernel<<<(n + 255) / 256, 256, 0, s>>>(pos_idx, rinv, n);
+    if (hipGetLastError() != hipSuccess) return GC_ERR_HIP;
+  }
   LossArgs a{};
   a.dt = GC_BF16; a.B = n; a.P = n; a.d = d; a.alpha = scale / temp; a.stream = s;
   a.defer_loss_sum = true;   // one launch sums the row losses of both directions at the end
   LossArgs a1, a2;
   if (sp.pl.use_mfma) {
-    // statistics of both directions (Eq. 1 as it stands, then with the two sides exchanged) ...
-    a.q = q; a.p = p; a.pos_idx = pos_idx; a.loss = l; a.ws = ws;
-    a1 = a;
-    rc = run_loss(a, sp.pl);
-    if (rc != GC_OK) return rc;
-    a.q = p; a.p = q; a.pos_idx = rinv; a.loss = l + 1; a.ws = ws + sp.off2;
-    a2 = a;
-    rc = run_loss(a, sp.pl);
-    if (rc != GC_OK) return rc;
+    a.wide = wide;
+    a1 = a2 = a;   // (for the sum of the row losses)
+    a1.q = q; a1.p = p; a1.pos_idx = pos_idx; a1.loss = l; a1.ws = ws; a1.wexp = (float*)(ws + sp.pl.off_part_idx);
+    a2.q = p; a2.p = q; a2.pos_idx = rinv; a2.loss = l + 1; a2.ws = ws + sp.off2; a2.wexp = (float*)(ws + sp.off2 + sp.pl.off_part_idx);
+    if (!both.use) {   // statistics of both directions (Eq. 1 as it stands, then with the two sides exchanged) ...
+      rc = run_loss(a1, sp.pl);
+      if (rc != GC_OK) return rc;
+      rc = run_loss(a2, sp.pl);
+      if (rc != GC_OK) return rc;
+    }
     // ... and one gradient pass with the mean of the two softmaxes as coefficients
     a.q = q; a.p = p; a.pos_idx = pos_idx; a.loss = nullptr; a.ws = ws; a.dq = dq; a.dp = dp;
     a.lse2_t = (const float*)(ws + sp.off2 + sp.pl.off_lse2);
+    a.wexp = a1.wexp; a.wexp_t = a2.wexp;
+    if (both.use) { a.both = &both; a.ws_t = ws + sp.off2; }   // ... (the statistics in one pass where that is faster)
     a.pos_inv = rinv;
+    a.sym[0] = &a1; a.sym[1] = &a2; a.sym_loss = loss;
     a.zero_word = (const int*)(ws + sp.pl.off_err) + 1;   // zeroed by the first direction's merge, raised by nobody here
-    rc = run_loss(a, sp.pl);
-    if (rc != GC_OK) return rc;
+    return run_loss(a, sp.pl);   // (its last launch also sums the row losses)
   } else {
     const size_t gsz = align_up((size_t)n * d * 4, 256);
     float* g[4];

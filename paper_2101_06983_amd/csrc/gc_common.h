@@ -74,6 +74,15 @@ constexpr int kStatTile = 32;
 LossPlan make_loss_plan(int B, int P, int d, gc_dtype dt, bool ntxent, size_t limit = (size_t)-1);
 void plan_planes(LossPlan& pl, int B, int P, int d, gc_dtype dt, int max_splits);
 
+// Statistics of both sides of a symmetric form from one pass over the scores (stats_mfma_kernel, stats128_both_kernel).
+struct LossArgs;
+struct BothPlan {
+  bool use, triangle;
+  int n_ablk, cols_per_split, row_slots, nwg;   // blocks of 256 owners; streamed rows of a workgroup; ranges of a block at most
+  void partials(const LossArgs& a, const LossPlan& pl, float*& row_m, float*& row_l, float*& col_m, float*& col_l) const;
+};
+BothPlan plan_both(int n, int d, bool triangle, const LossPlan& pl);
+
 struct LossArgs {
   gc_dtype dt;
   const void* q;
@@ -94,16 +103,31 @@ struct LossArgs {
   const float* lse2_t;
   // ... with the inverse of the pairing (pos_inv[r_i] = i, a bijection there) and a device word that holds 0, for
   // the positive's term of the dP rows (PosFix)
-  const int32_t* pos_inv;
+  int32_t* pos_inv;
   const int* zero_word;
   // set by run_loss when the gradient pass ends in a sum of split partials: that launch then also sums the row
   // losses (one launch less); the statistics merge leaves the sum to it
   bool loss_with_partials;
+  // symmetric forms: the merge of the statistics also writes 2^(-lse2 - 1) per row (padded with 0), where the partials'
+  // indices were (nobody asks these calls for an arg-max), and raises *wide when a row's |lse2| is beyond kWideLse; the
+  // gradient pass of the symmetric loss takes both directions' (wexp, wexp_t)
+  float* wexp;
+  const float* wexp_t;
+  int* wide;
+  const BothPlan* both;  // the statistics of both sides in one pass; `ws_t`: workspace of the other direction's (symmetric loss)
+  char* ws_t;
+  const LossArgs* sym[2];   // symmetric loss: the launch that sums its partials also sums the row losses of both directions
+  float* sym_loss;
   bool defer_loss_sum;   // the caller sums the row losses itself (the symmetric loss: both directions in one launch)
   char* ws;
   char* ws2;             // base of the offsets from off_dq_part on (ws; the symmetric loss shares that part between its directions)
   hipStream_t stream;
 };
+
+// The coefficient of the symmetric forms is 1/2 (2^(t - lse2_i) + 2^(t - lse2_j)) = 2^t (w_i + w_j), w = 2^(-lse2 - 1): one
+// exponential a score instead of two, a quarter of the rate each.  With |lse2| up to kWideLse no factor overflows, and
+// what 2^t flushes is below 2^(-126 + kWideLse) of its row's sum.  Beyond (one row is enough) the two exponentials stay.
+constexpr float kWideLse = 60.f;
 
 // The positive's own term of Eq. 5 / Eq. 6, (p_{i r_i} - 1) g(t_{r_i}) resp. (p_{i r_i} - 1) f(s_i), is not part of the bf16
 // contractions of the MFMA walks (they take the coefficient 0 at the positive): rounded to bf16, this one coefficient
@@ -124,7 +148,16 @@ struct PosFix {
   float scale;
 };
 
+inline void BothPlan::partials(const LossArgs& a, const LossPlan& pl, float*& row_m, float*& row_l, float*& col_m, float*& col_l) const {
+  row_m = (float*)(a.ws + pl.off_dq_part);   // (the gradient pass writes there later)
+  row_l = row_m + (size_t)row_slots * a.B;
+  col_m = row_l + (size_t)row_slots * a.B;
+  col_l = col_m + (size_t)n_ablk * a.B;
+}
+
 // kernel-launching halves (one per .hip file)
+hipError_t launch_stats_both(const LossArgs& a, const LossPlan& pl, const BothPlan& b);
+hipError_t launch_both_merge(const LossArgs& a, const LossPlan& pl, const BothPlan& b);
 hipError_t launch_stats_generic(const LossArgs& a, const LossPlan& pl);
 hipError_t launch_grad_generic(const LossArgs& a, const LossPlan& pl);
 hipError_t launch_loss_tiny(const LossArgs& a, const LossPlan& pl);      // the whole call

@@ -109,7 +109,8 @@ __global__ void __launch_bounds__(256) stats_merge_kernel(const float* __restric
                                                          int b_pad, float* __restrict__ lse2, int32_t* __restrict__ pos_pad,
                                                          float* __restrict__ rowloss, float* __restrict__ lse_out,
                                                          int32_t* __restrict__ argmax_out, int32_t* __restrict__ inv,
-                                                         int* __restrict__ shared) {
+                                                         int* __restrict__ shared, float* __restrict__ wexp,
+                                                         int* __restrict__ wide) {
   constexpr int ROWS = 256 / LANES;
   if (shared && blockIdx.x == 0 && threadIdx.x == 0) *shared = 0;   // raised later by the gradient kernel's check
   const int s = threadIdx.x % LANES;
@@ -117,7 +118,7 @@ __global__ void __launch_bounds__(256) stats_merge_kernel(const float* __restric
   const bool live = (i < B) && (s < nsplit);
   float m = live ? part_m[(size_t)s * B + i] : -INFINITY;
   float l = live ? part_l[(size_t)s * B + i] : 0.f;
-  int bi = live ? part_idx[(size_t)s * B + i] : 0x7fffffff;
+  int bi = live && argmax_out ? part_idx[(size_t)s * B + i] : 0x7fffffff;   // (wexp may lie where the indices would)
 #pragma unroll
   for (int w = 1; w < LANES; w <<= 1) {
     const float m2 = __shfl_xor(m, w), l2 = __shfl_xor(l, w);
@@ -132,9 +133,17 @@ __global__ void __launch_bounds__(256) stats_merge_kernel(const float* __restric
     m = mn;
   }
   if (s != 0 || i >= b_pad) return;
-  if (i >= B) { lse2[i] = INFINITY; pos_pad[i] = -1; return; }
+  if (i >= B) {
+    lse2[i] = INFINITY; pos_pad[i] = -1;
+    if (wexp) wexp[i] = 0.f;
+    return;
+  }
   const float l2 = m + log2f(l);
   lse2[i] = l2;
+  if (wexp) {
+    wexp[i] = exp2f(-l2 - 1.f);
+    if (!(fabsf(l2) <= kWideLse)) *wide = 1;   // (zeroed by the kernel that makes the call's pairing)
+  }
   const int r = pos_idx[i];
   pos_pad[i] = r;
   const bool ok = (r >= 0 && r < P);
@@ -144,6 +153,108 @@ __global__ void __launch_bounds__(256) stats_merge_kernel(const float* __restric
   if (inv && ok) inv[r] = i;   // an anchor per target; which one, when several share it, is not relied upon
   if (lse_out) lse_out[i] = l2 * kLn2;
   if (argmax_out) argmax_out[i] = bi;
+}
+
+// The same for statistics of both sides from one pass (BothPlan): sixteen rows per workgroup, sixteen threads share the slots
+// of a row.  Triangle: row i has the column partials of the blocks before its own and the row partials of its block.
+// Otherwise the first half of the workgroups merges the anchors' row partials, the second the targets' column partials (a
+// target's positive is the anchor that inv names).
+struct BothMergeArgs {
+  const float* row_m; const float* row_l; const float* col_m; const float* col_l; const float* pos_t;
+  const int32_t* pos; int32_t* inv;
+  int triangle, n, b_pad, n_ablk, row_slots, cols_per_split, blocks;   // blocks: workgroups of a direction
+  float* lse2[2]; float* rowloss[2]; float* wexp[2];
+  int32_t* pos_pad; int* wide; int* shared;
+};
+__global__ void __launch_bounds__(256) both_merge_kernel(BothMergeArgs g) {
+  constexpr int FLY = 8;   // loads in flight
+  __shared__ float sm[4][16], sl[4][16];
+  const int dir = (int)blockIdx.x >= g.blocks ? 1 : 0;
+  const int row = threadIdx.x & 15, grp = threadIdx.x >> 4, w = threadIdx.x >> 6;
+  const int i = ((int)blockIdx.x - dir * g.blocks) * 16 + row;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *g.shared = 0;
+  const int blk = min(i, g.n - 1) / 256;
+  const int ncol = g.triangle ? blk : dir ? g.n_ablk : 0;
+  const int nrow = g.triangle ? (g.n - 256 * blk + g.cols_per_split - 1) / g.cols_per_split : dir ? 0 : g.row_slots;
+  float m = -INFINITY, l = 0.f;
+  for (int s0 = grp; s0 < ncol + nrow; s0 += 16 * FLY) {
+    float vm[FLY], vl[FLY];
+#pragma unroll
+    for (int k = 0; k < FLY; k++) {
+      const int s = s0 + 16 * k;
+      const bool live = i < g.n && s < ncol + nrow, col = s < ncol;
+      const size_t o = live ? (size_t)(col ? s : s - ncol) * g.n + i : 0;
+      vm[k] = (col ? g.col_m : g.row_m)[o]; vl[k] = (col ? g.col_l : g.row_l)[o];
+      if (!live) { vm[k] = -INFINITY; vl[k] = 0.f; }
+    }
+    float mn = m;
+#pragma unroll
+    for (int k = 0; k < FLY; k++) mn = fmaxf(mn, vm[k]);
+    const float ms = mn == -INFINITY ? 0.f : mn;
+    l *= exp2f(m - ms);
+#pragma unroll
+    for (int k = 0; k < FLY; k++) l += vl[k] * exp2f(vm[k] - ms);
+    m = mn;
+  }
+  auto merge = [&](float m2, float l2) {   // (both partners: the same value whichever is first)
+    const float mn = fmaxf(m, m2), ms = mn == -INFINITY ? 0.f : mn;
+    l = l * exp2f(m - ms) + l2 * exp2f(m2 - ms);
+    m = mn;
+  };
+  merge(__shfl_xor(m, 16), __shfl_xor(l, 16));
+  merge(__shfl_xor(m, 32), __shfl_xor(l, 32));
+  if ((threadIdx.x & 63) < 16) { sm[w][row] = m; sl[w][row] = l; }
+  __syncthreads();
+  if (threadIdx.x >= 16 || i >= g.b_pad) return;
+  for (int k = 1; k < 4; k++) merge(sm[k][row], sl[k][row]);
+  if (i >= g.n) {
+    g.lse2[dir][i] = INFINITY; g.wexp[dir][i] = 0.f;
+    if (!dir) g.pos_pad[i] = -1;
+    return;
+  }
+  int r = g.triangle ? (i ^ 1) : dir ? g.inv[i] : g.pos[i];
+  if (dir && !(r >= 0 && r < g.n && g.pos[r] == i)) g.inv[i] = r = -1;   // nobody's positive: the pairing is no bijection
+  if (!dir) g.pos_pad[i] = r;
+  const bool ok = r >= 0 && r < g.n;
+  const float pt = ok ? g.pos_t[dir ? r : i] : 0.f;
+  // l's exponent to its reference: the logarithm is then of a number near 1, and its error that of one rounding of the result
+  if (l > 0.f && l < INFINITY) {
+    const int e = ilogbf(l);
+    l = ldexpf(l, -e);
+    m += (float)e;
+  }
+  // the sums leave the positive out: where the softmax has converged on it, the loss is log(1 + (sum of the others) / its term)
+  // and not the difference of two rounded logarithms
+  float l2, loss;
+  const float x = l * exp2f(m - pt);
+  if (ok && fabsf(pt) < INFINITY && (x <= 1.f || l == 0.f)) {
+    loss = log1pf(l == 0.f ? 0.f : x);
+    l2 = pt + loss * kLog2e;
+  } else {
+    l2 = m + log2f(ok ? l + exp2f(pt - m) : l);
+    if (pt == INFINITY) l2 = NAN;   // (as any infinite score)
+    loss = (l2 - pt) * kLn2;
+  }
+  g.lse2[dir][i] = l2;
+  g.wexp[dir][i] = exp2f(-l2 - 1.f);
+  if (!(fabsf(l2) <= kWideLse)) *g.wide = 1;   // (zeroed by the kernel that makes the call's pairing)
+  g.rowloss[dir][i] = ok ? loss : NAN;
+}
+hipError_t launch_both_merge(const LossArgs& a, const LossPlan& pl, const BothPlan& b) {
+  BothMergeArgs g{};
+  float *rm, *rl, *cm, *cl;
+  b.partials(a, pl, rm, rl, cm, cl);
+  g.row_m = rm; g.row_l = rl; g.col_m = cm; g.col_l = cl;
+  g.pos_t = (const float*)(a.ws + pl.off_pos); g.pos = a.pos_idx; g.inv = a.pos_inv;
+  g.triangle = b.triangle; g.n = a.B; g.b_pad = pl.b_pad; g.n_ablk = b.n_ablk; g.row_slots = b.row_slots; g.cols_per_split = b.cols_per_split;
+  g.blocks = (pl.b_pad + 15) / 16;
+  char* const ws[2] = {a.ws, a.ws_t};
+  for (int k = 0; k < (b.triangle ? 1 : 2); k++) {
+    g.lse2[k] = (float*)(ws[k] + pl.off_lse2); g.rowloss[k] = (float*)(ws[k] + pl.off_rowloss); g.wexp[k] = (float*)(ws[k] + pl.off_part_idx);
+  }
+  g.pos_pad = (int32_t*)(a.ws + pl.off_pos_pad); g.wide = a.wide; g.shared = (int*)(a.ws + pl.off_err) + 1;
+  both_merge_kernel<<<g.blocks * (b.triangle ? 1 : 2), 256, 0, a.stream>>>(g);
+  return hipGetLastError();
 }
 
 // loss = (1/B) sum_i rowloss_i by one workgroup; raises the error word when a row was flagged because its
@@ -199,6 +310,16 @@ __device__ __forceinline__ void loss_sum_block(const LossSum& ls, float* red /* 
     *ls.err = bad ? 1 : 0;
   }
 }
+// symmetric loss: the second direction's sum, the mean of both, and one error word for both
+template <int NT>
+__device__ __forceinline__ void sym_loss_second(const LossSum& l1, const LossSum& l2, float* loss, float* red) {
+  __syncthreads();                 // thread 0 has written *l1.loss and *l1.err ...
+  loss_sum_block<NT>(l2, red);
+  if (threadIdx.x == 0) {          // ... and reads them back itself
+    if (loss) *loss = 0.5f * (*l1.loss + *l2.loss);
+    if (*l2.err) *l1.err = *l2.err;
+  }
+}
 __global__ void __launch_bounds__(1024) loss_reduce_kernel(LossSum ls) {
   __shared__ float red[1024];
   loss_sum_block<1024>(ls, red);
@@ -251,7 +372,10 @@ __global__ void __launch_bounds__(256) grad_generic_kernel(const T* __restrict__
 // up to two outputs (dq and dp) in one launch.  With a loss sum attached the grid has one more workgroup, the first (so
 // that it runs beside the others), which carries it (it has nothing to do with the partial sums; it only saves a launch
 // on the path that needs both).
-struct ReduceArgs { ReduceJob job[2]; unsigned blocks0; LossSum ls; };
+struct ReduceArgs {
+  ReduceJob job[2]; unsigned blocks0; LossSum ls;
+  LossSum ls2; float* sym_loss;   // with ls: the other direction of the symmetric loss, and the mean's place
+};
 // coefficient of the positive of anchor i (target r), see PosFix
 __device__ __forceinline__ float pos_coeff(const PosFix& f, int i, int r) {
   const float t = f.pos_t[i];
@@ -334,6 +458,7 @@ __global__ void __launch_bounds__(256, 8) partial_reduce_kernel(ReduceArgs a) {
   if (a.ls.rowloss) {
     if (block == 0) {
       loss_sum_block<256>(a.ls, lds.red);
+      if (JOBS > 1 && a.ls2.rowloss) sym_loss_second<256>(a.ls, a.ls2, a.sym_loss, lds.red);
       return;
     }
     block--;
@@ -509,7 +634,13 @@ hipError_t launch_reduce_jobs(const ReduceJob* jobs, int njobs, hipStream_t stre
     if (jobs[k].fix.mode && (jobs[k].n % 4 || jobs[k].fix.d % 4)) return hipErrorInvalidValue;   // rows of whole vectors only
     blocks[k] = (unsigned)(((jobs[k].n + 3) / 4 + 255) / 256);
   }
-  if (loss_of) a.ls = loss_sum_of(*loss_of, *pl);
+  if (loss_of && loss_of->sym[0]) {   // (two jobs: both gradients of the symmetric loss)
+    a.ls = loss_sum_of(*loss_of->sym[0], *pl);
+    a.ls2 = loss_sum_of(*loss_of->sym[1], *pl);
+    a.sym_loss = loss_of->sym_loss;
+  } else if (loss_of) {
+    a.ls = loss_sum_of(*loss_of, *pl);
+  }
   a.blocks0 = blocks[0];
   const unsigned n = blocks[0] + blocks[1] + (loss_of ? 1 : 0);
   if (n && njobs > 1) partial_reduce_kernel<2><<<dim3(n), 256, 0, stream>>>(a);
@@ -539,13 +670,8 @@ hipError_t launch_loss_sum(const LossArgs& a, const LossPlan& pl) {
 
 __global__ void __launch_bounds__(1024) sym_loss_reduce_kernel(LossSum l1, LossSum l2, float* loss) {
   __shared__ float red[1024];
-  loss_sum_block<1024>(l1, red);   // thread 0 writes *l1.loss and *l1.err ...
-  __syncthreads();
-  loss_sum_block<1024>(l2, red);
-  if (threadIdx.x == 0) {          // ... and reads them back itself
-    if (loss) *loss = 0.5f * (*l1.loss + *l2.loss);
-    if (*l2.err) *l1.err = *l2.err;
-  }
+  loss_sum_block<1024>(l1, red);
+  sym_loss_second<1024>(l1, l2, loss, red);
 }
 hipError_t launch_sym_loss_sum(const LossArgs& a1, const LossArgs& a2, const LossPlan& pl, float* loss) {
   sym_loss_reduce_kernel<<<1, 1024, 0, a1.stream>>>(loss_sum_of(a1, pl), loss_sum_of(a2, pl), loss);
@@ -561,7 +687,8 @@ hipError_t launch_stats_merge(const LossArgs& a, const LossPlan& pl) {
         (const float*)(ws + pl.off_part_m), (const float*)(ws + pl.off_part_l), (const int*)(ws + pl.off_part_idx),
         (float*)(ws + pl.off_pos), pl.route == ROUTE_PLANES ? 1 : 0, a.pos_idx, a.B, a.P, pl.stat_splits, pl.b_pad, (float*)(ws + pl.off_lse2),
         (int32_t*)(ws + pl.off_pos_pad), (float*)(ws + pl.off_rowloss), a.lse, a.argmax,
-        pl.use_mfma ? (int32_t*)(ws + pl.off_inv) : nullptr, pl.use_mfma ? (int*)(ws + pl.off_err) + 1 : nullptr);
+        pl.use_mfma ? (int32_t*)(ws + pl.off_inv) : nullptr, pl.use_mfma ? (int*)(ws + pl.off_err) + 1 : nullptr,
+        a.wexp, a.wide);
   };
   if (pl.stat_splits <= 1) merge(std::integral_constant<int, 1>{});
   else if (pl.stat_splits <= 4) merge(std::integral_constant<int, 4>{});

@@ -94,6 +94,11 @@ __device__ __forceinline__ void grad_body(const GradArgs& ga, int oblk, int spli
   constexpr bool STR_STATS = SYM || !OWNER_IS_Q;   // the streamed rows' statistics ride in the LDS stage
   const float* lse_own = (SYM && !OWNER_IS_Q) ? ga.lse2_t : ga.lse2;
   const float* lse_str = (SYM && OWNER_IS_Q) ? ga.lse2_t : ga.lse2;
+  bool one_exp = false;   // SYM: one exponential a score (see kWideLse)
+  if constexpr (SYM) {
+    one_exp = __builtin_amdgcn_readfirstlane(*ga.wide) == 0;
+    if (one_exp) { lse_own = OWNER_IS_Q ? ga.wexp : ga.wexp_t; lse_str = OWNER_IS_Q ? ga.wexp_t : ga.wexp; }
+  }
   static_assert(grad_offsets_fit<D>(), "direct-to-LDS load offsets");
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, h = lane >> 5, ln = lane & 31;
   const int l16 = lane & 15, g16 = lane >> 4;
@@ -160,7 +165,7 @@ __device__ __forceinline__ void grad_body(const GradArgs& ga, int oblk, int spli
   for (int it = 0; it < NT; it++) src_off[it] = slot_src(it * 64 + lane, GR_T - 1) - 1024u * (it & 3);
   // row statistics of the streamed rows: lanes 0-3 load lse_str[t0 + 4 l ..], lanes 4-7 pos_pad (dP role; in
   // the dQ role of the symmetric loss they load the same as lanes 0-3 and nobody reads it)
-  const unsigned ri_off = ((lane & 4) && !OWNER_IS_Q) ? (unsigned)((const char*)ga.pos_pad - (const char*)ga.lse2) + 16u * (lane & 3) : 16u * (lane & 3);
+  const unsigned ri_off = ((lane & 4) && !OWNER_IS_Q) ? (unsigned)((const char*)ga.pos_pad - (const char*)lse_str) + 16u * (lane & 3) : 16u * (lane & 3);
   constexpr int NI = STR_STATS ? NT + 1 : NT;  // load instructions per tile
   // piece k (0 .. NI-1) of the loads of a full tile that starts at row t0, into the stage at byte offset so
   auto prefetch_piece = [&](auto k_tag, auto two_tag, int t0, unsigned so, u32x4& pin_a, u32x4& pin_b) __attribute__((always_inline)) {
@@ -397,10 +402,10 @@ __device__ __forceinline__ void grad_body(const GradArgs& ga, int oblk, int spli
       }
     }
     // ---- from the summed scores of tile u+1 to its coefficients.  The arithmetic that every tile needs is cut into
-    // pieces; in a steady iteration (not for SYM) piece k runs right behind MFMA k * MC / NP of phase 2, where a
+    // pieces; in a steady iteration piece k runs right behind MFMA k * MC / NP of phase 2, where a
     // wave's own arithmetic is free, instead of after the last MFMA, where it is not.  What only few tiles need
     // (the positive, masks, the arg-max) stays behind phase 2.
-    constexpr bool INTER = STEADY && !SYM;
+    constexpr bool INTER = STEADY;
     constexpr int NP = ONLINE ? 10 : 5;
     const int b0 = sbeg + (u + 1) * GR_T + 4 * g16;      // first of this lane's 4 streamed rows
     f32x4 sv = {0.f, 0.f, 0.f, 0.f}, tt = {0.f, 0.f, 0.f, 0.f}, gv = {0.f, 0.f, 0.f, 0.f};
@@ -414,10 +419,10 @@ __device__ __forceinline__ void grad_body(const GradArgs& ga, int oblk, int spli
       else if constexpr (!ONLINE) {
         if constexpr (K == 3) {
 #pragma unroll
-          for (int e = 0; e < 4; e++) tt[e] = sv[e] * ga.alpha2 - (OWNER_IS_Q ? lse_a : lse_r[e]);
+          for (int e = 0; e < 4; e++) tt[e] = SYM ? sv[e] * ga.alpha2 : sv[e] * ga.alpha2 - (OWNER_IS_Q ? lse_a : lse_r[e]);
         } else {
 #pragma unroll
-          for (int e = 0; e < 4; e++) gv[e] = fast_exp2(tt[e]);  // softmax
+          for (int e = 0; e < 4; e++) gv[e] = SYM ? fast_exp2(tt[e]) * (lse_a + lse_r[e]) : fast_exp2(tt[e]);  // softmax
         }
       } else {
         if constexpr (K == 3) {
@@ -496,10 +501,12 @@ __device__ __forceinline__ void grad_body(const GradArgs& ga, int oblk, int spli
         }
         gq = __builtin_convertvector(gv, bf16x4);
       } else {
-        if constexpr (SYM) {  // mean of the row softmax and the column softmax
+        if constexpr (SYM) {  // mean of the row softmax and the column softmax, with an exponential each
+          if (__builtin_expect(!one_exp, 0)) {
 #pragma unroll
-          for (int e = 0; e < 4; e++)
-            gv[e] = fast_exp2(__builtin_fmaf(sv[e], ga.alpha2, -(lse_a + 1.f))) + fast_exp2(__builtin_fmaf(sv[e], ga.alpha2, -(lse_r[e] + 1.f)));
+            for (int e = 0; e < 4; e++)
+              gv[e] = fast_exp2(tt[e] - (lse_a + 1.f)) + fast_exp2(tt[e] - (lse_r[e] + 1.f));
+          }
         }
         // the rest touches few tiles and is decided per wave: 0 at the positive (j == r_i; its term is added in fp32
         // by the kernel that sums the partials, see PosFix), zeros for rows past the end of the split and on the
@@ -676,7 +683,8 @@ hipError_t launch_grad_mfma(const LossArgs& a, const LossPlan& pl) {
   //   dz_i = (alpha/n) sum_j (g_ij + g_ji) z_j,   g_ij + g_ji = 2^(t_ij - lse2_i) + 2^(t_ij - lse2_j) - 2 [j = pair(i)]:
   // twice the coefficient of the symmetric loss with both statistics taken from the one array.  Only the dQ role runs.
   const bool one_walk = pl.one_walk && a.dz;
-  if (one_walk) { ga.lse2_t = ga.lse2; ga.out_scale *= 2.f; }
+  ga.wexp = a.wexp; ga.wexp_t = a.wexp_t; ga.wide = a.wide;
+  if (one_walk) { ga.lse2_t = ga.lse2; ga.wexp_t = ga.wexp; ga.out_scale *= 2.f; }
   const bool want_q = a.dq || a.dz, want_p = (a.dp || a.dz) && !one_walk;
   const size_t nq = (size_t)a.B * a.d, np = (size_t)a.P * a.d;
   const int own = (a.d == 128) ? G1_OWN : GR_OWN;   // owner rows per workgroup

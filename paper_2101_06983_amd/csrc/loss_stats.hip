@@ -17,19 +17,27 @@ constexpr int ST_STAGE_BYTES = (ST_TM + ST_TN) * ST_ROWB;  // one stage: 256 tar
 // LDS layout: chunk c of row r is stored at chunk position c ^ ((r >> 1) & 7): the 16 rows that a
 // 16-lane group reads in one fragment load then fall into 16 different 16-byte bank groups.
 
-__global__ void __launch_bounds__(512) stats_mfma_kernel(const unsigned short* __restrict__ Q,
-                                                         const unsigned short* __restrict__ Pm,
-                                                         const int32_t* __restrict__ pos_idx, int B, int P, int d,
-                                                         float alpha2, int mask_self, int n_ablk, int cols_per_split,
-                                                         float* __restrict__ part_m, float* __restrict__ part_l,
-                                                         int* __restrict__ part_idx, float* __restrict__ pos_t) {
+// ARGMAX: the plain pass with the first index of the maximum; BOTH, TRI: the statistics of both sides of the symmetric forms
+// from one pass over the scores (see kBothMin), TRI (NT-Xent, q = p) over the tiles on and above the diagonal only.
+enum StatsMode { ST_PLAIN, ST_ARGMAX, ST_BOTH, ST_TRI };
+template <StatsMode MODE>
+__global__ void __launch_bounds__(512) stats_mfma_kernel(StatsArgs g) {
+  constexpr bool TRI = MODE == ST_TRI, BOTH = MODE == ST_BOTH || TRI, ARGMAX = MODE == ST_ARGMAX;
+  const unsigned short* const Q = g.Q;
+  const unsigned short* const Pm = g.P;
+  const int32_t* const pos_idx = g.pos_idx;
+  const int B = g.B, P = g.Pn, d = g.d, cols_per_split = g.cols_per_split;
+  const float alpha2 = g.alpha2;
+  const int mask_self = BOTH ? 0 : g.mask_self;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_b[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave & 1, wn = wave >> 1;
-  const int task = xcd_task_id();
-  const int ablk = task % n_ablk, split = task / n_ablk;
+  if constexpr (BOTH) both_begin(g);
+  int task = xcd_task_id(), ablk, split;
+  if (TRI) split = tri_task(task, P, cols_per_split, ablk);
+  else { ablk = task % g.n_ablk; split = task / g.n_ablk; }
   const int a0 = ablk * ST_TN;
-  const int cbeg = split * cols_per_split, cend = min(P, cbeg + cols_per_split);
+  const int cbeg = (TRI ? a0 : 0) + split * cols_per_split, cend = min(P, cbeg + cols_per_split);
   const int nk = d / ST_KC;
 
   // ---- direct global->LDS loads: wave w fills rows 64 w .. 64 w + 63 of a stage (waves 0-3 the target
@@ -46,9 +54,8 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(const unsigned short* _
     if (clamp) r = min(r, lrows - 1 - tile_row0);
     return (unsigned)(r * d * 2 + c * 16);
   };
-  unsigned voff_full[8];  // full tile, with the instruction offset 1024 (j % 4) pre-subtracted
-#pragma unroll
-  for (int j = 0; j < 8; j++) voff_full[j] = src_of(j, 0, false) - 1024u * (j & 3);
+  // full tile: row 8 j moves the chunk by its swizzle's bit 2 only, so two offsets and a scalar step serve the eight loads
+  const unsigned voff_full[2] = {src_of(0, 0, false), src_of(1, 0, false) - 16u * (unsigned)d};
   auto prefetch = [&](int tile_row0, int kc, int stage) __attribute__((always_inline)) {
     const unsigned short* base_v = lmat + (size_t)tile_row0 * d + kc * ST_KC;  // the same in every lane of a wave
     const unsigned long long bu = (unsigned long long)(uintptr_t)base_v;
@@ -58,8 +65,8 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(const unsigned short* _
         (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((unsigned)bu));
     const unsigned m0 = stage_m0 + stage * ST_STAGE_BYTES;
     if (tile_row0 + 256 <= lrows) {
-      dma_group<4>(base, &voff_full[0], m0);
-      dma_group<4>(base, &voff_full[4], m0 + 4096);
+#pragma unroll
+      for (int j = 0; j < 8; j++) dma_group<1>((const char*)base + 16 * j * d, &voff_full[j & 1], m0 + 1024 * j);
     } else {  // ragged tile: rows past the end re-read the last valid row (masked later)
 #pragma unroll
       for (int j = 0; j < 8; j++) {
@@ -84,8 +91,15 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(const unsigned short* _
   for (int nt = 0; nt < 2; nt++) {
     rm[nt] = -INFINITY; rl[nt] = 0.f; rpos[nt] = 0.f; ridx[nt] = 0x7fffffff;
     a_col[nt] = a0 + wn * 64 + nt * 32 + (lane & 31);
-    r_of[nt] = (a_col[nt] < B) ? pos_idx[a_col[nt]] : -1;
+    r_of[nt] = (a_col[nt] >= B) ? -1 : TRI ? a_col[nt] ^ 1 : pos_idx[a_col[nt]];
   }
+  // BOTH: sums with the reference 0 (rm, rl: of the tiles that needed one of their own); whether this lane saw the positive
+  float lf[2] = {0.f, 0.f};
+  bool got[2] = {false, false};
+  typedef __attribute__((ext_vector_type(2))) float f32x2;
+  f32x2* cbuf = (f32x2*)(smem_b + 2 * ST_STAGE_BYTES);   // [4 wn][256 columns] (maximum, sum)
+  const int col_in = 8 * (reduce16_reg_of(lane) >> 2) + 4 * (lane >> 5) + (reduce16_reg_of(lane) & 3);
+  const bool own_edge = a0 + wn * 64 + 64 > B;
 
   // The k-chunks of all the tiles of this workgroup form one sequence of steps; step st lives in stage st & 1 and
   // its loads are issued one step ahead inside a tile.  (Loading the first chunk of the next tile under the last
@@ -133,6 +147,106 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(const unsigned short* _
     // base-2 logit is t = alpha2 * acc (alpha2 > 0: the order of the raw values is the order of the logits) -------
     const int brow0 = b0 + wm * 128 + 4 * (lane >> 5);  // + mt*32 + 8*(r/4) + r%4
     const bool edge = (b0 + ST_TM > cend);
+    if constexpr (BOTH) {
+      const bool has_pos = (unsigned)(r_of[0] - b0) < (unsigned)ST_TM || (unsigned)(r_of[1] - b0) < (unsigned)ST_TM;
+      if (__builtin_amdgcn_ballot_w64(has_pos) != 0) {
+#pragma unroll
+        for (int nt = 0; nt < 2; nt++)
+#pragma unroll
+          for (int mt = 0; mt < 4; mt++)
+#pragma unroll
+            for (int r = 0; r < 16; r++)
+              if (brow0 + mt * 32 + 8 * (r >> 2) + (r & 3) == r_of[nt] && r_of[nt] < cend) {
+                rpos[nt] = acc[mt][nt][r] * alpha2; got[nt] = true;
+                acc[mt][nt][r] = -INFINITY;   // the positive is no part of the sums (both_merge_kernel adds it)
+              }
+      }
+      const bool cols = !TRI || b0 > a0;
+      bool done = false;
+      if (cols && !own_edge && !edge) {
+        float rs[2] = {0.f, 0.f}, c[4], lo = INFINITY, hi = 0.f;
+#pragma unroll
+        for (int mt = 0; mt < 4; mt++) {
+          float v[16];
+#pragma unroll
+          for (int r = 0; r < 16; r++) {
+            const float e0 = fast_exp2(acc[mt][0][r] * alpha2), e1 = fast_exp2(acc[mt][1][r] * alpha2);
+            rs[0] += e0; rs[1] += e1;
+            v[r] = e0 + e1;
+          }
+          c[mt] = reduce16_lanes32<false>(v, lane);
+          lo = fminf(lo, c[mt]); hi = fmaxf(hi, c[mt]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        lo = fminf(lo, fminf(rs[0], rs[1])); hi = fmaxf(hi, fmaxf(rs[0], rs[1]));
+        if (__builtin_amdgcn_ballot_w64(!(lo >= kBothMin && hi <= kBothMax)) == 0) {
+          lf[0] += rs[0]; lf[1] += rs[1];
+          if (!(lane & 1)) {
+#pragma unroll
+            for (int mt = 0; mt < 4; mt++) cbuf[wn * 256 + wm * 128 + mt * 32 + col_in] = f32x2{0.f, c[mt]};
+          }
+          done = true;
+        }
+      }
+      if (!done) {   // masks, and references of its own for every row and column
+        float tm[2] = {-INFINITY, -INFINITY}, mn[2], sum[2] = {0.f, 0.f};
+#pragma unroll
+        for (int nt = 0; nt < 2; nt++) {
+#pragma unroll
+          for (int mt = 0; mt < 4; mt++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) {
+              const int j = brow0 + mt * 32 + 8 * (r >> 2) + (r & 3);
+              acc[mt][nt][r] = (j >= cend || a_col[nt] >= B || (TRI && j == a_col[nt])) ? -INFINITY : acc[mt][nt][r] * alpha2;
+              tm[nt] = fmaxf(tm[nt], acc[mt][nt][r]);
+            }
+          mn[nt] = fmaxf(rm[nt], tm[nt]);
+          if (mn[nt] == -INFINITY) mn[nt] = 0.f;
+        }
+#pragma unroll
+        for (int mt = 0; mt < 4; mt++) {
+#pragma unroll
+          for (int nt = 0; nt < 2; nt++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) sum[nt] += fast_exp2(acc[mt][nt][r] - mn[nt]);
+          if (cols) {
+            float mx[16], v[16];
+#pragma unroll
+            for (int r = 0; r < 16; r++) {
+              mx[r] = fmaxf(acc[mt][0][r], acc[mt][1][r]);
+              float m = max_lanes32(mx[r]);
+              m = m == -INFINITY ? 0.f : m;
+              v[r] = fast_exp2(acc[mt][0][r] - m) + fast_exp2(acc[mt][1][r] - m);
+              if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+            }
+            const float cm = reduce16_lanes32<true>(mx, lane), cl = reduce16_lanes32<false>(v, lane);
+            if (!(lane & 1)) cbuf[wn * 256 + wm * 128 + mt * 32 + col_in] = f32x2{cm, cl};
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int nt = 0; nt < 2; nt++) {
+          if (tm[nt] == -INFINITY) continue;
+          rl[nt] = rl[nt] * fast_exp2(rm[nt] - mn[nt]) + sum[nt];
+          rm[nt] = mn[nt];
+        }
+      }
+      if (cols) {   // the four waves' sums of a column, in wave order (the next tile writes them behind many barriers)
+        __syncthreads();
+        if (tid < 256 && b0 + tid < cend) {
+          f32x2 x[4];
+          float m = -INFINITY, l = 0.f;
+#pragma unroll
+          for (int k = 0; k < 4; k++) { x[k] = cbuf[k * 256 + tid]; m = fmaxf(m, x[k][0]); }
+          const float ms = m == -INFINITY ? 0.f : m;
+#pragma unroll
+          for (int k = 0; k < 4; k++) l += x[k][1] * fast_exp2(x[k][0] - ms);
+          const size_t o = (size_t)ablk * P + b0 + tid;
+          g.col_m[o] = m; g.col_l[o] = l;
+        }
+      }
+      continue;
+    }
 #pragma unroll
     for (int nt = 0; nt < 2; nt++) {
       const int a = a_col[nt];
@@ -157,9 +271,13 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(const unsigned short* _
 #pragma unroll
         for (int r = 0; r < 16; r++) {
           const float t = acc[mt][nt][r];
-          const bool le = t <= tmr;
-          tmr = le ? tmr : t;
-          tc = le ? tc : (mt * 32 + 8 * (r >> 2) + (r & 3));
+          if constexpr (ARGMAX) {
+            const bool le = t <= tmr;
+            tmr = le ? tmr : t;
+            tc = le ? tc : (mt * 32 + 8 * (r >> 2) + (r & 3));
+          } else {
+            tmr = fmaxf(tmr, t);
+          }
         }
       if (tmr > -INFINITY) {
         const float tm = tmr * alpha2;
@@ -170,7 +288,7 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(const unsigned short* _
 #pragma unroll
           for (int r = 0; r < 16; r++) s += fast_exp2(__builtin_fmaf(acc[mt][nt][r], alpha2, -mn));
         rl[nt] = rl[nt] * fast_exp2(rm[nt] - mn) + s;
-        if (tm > rm[nt]) ridx[nt] = brow0 + tc;  // later tiles have larger j: strict >
+        if (ARGMAX && tm > rm[nt]) ridx[nt] = brow0 + tc;  // later tiles have larger j: strict >
         rm[nt] = mn;
       }
     }
@@ -179,6 +297,7 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(const unsigned short* _
   // ---- combine the two half-waves (same anchor column, different target rows) -------------------
 #pragma unroll
   for (int nt = 0; nt < 2; nt++) {
+    if constexpr (BOTH) stat_merge(rm[nt], rl[nt], ridx[nt], lf[nt] > 0.f ? 0.f : -INFINITY, lf[nt], 0x7fffffff);
     float m2 = __shfl_xor(rm[nt], 32), l2 = __shfl_xor(rl[nt], 32);
     int i2 = __shfl_xor(ridx[nt], 32);
     stat_merge(rm[nt], rl[nt], ridx[nt], m2, l2, i2);
@@ -201,9 +320,9 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(const unsigned short* _
       stat_merge(rm[nt], rl[nt], ridx[nt], x[0], x[1], __builtin_bit_cast(int, x[2]));
       int a = a_col[nt];
       if (a < B) {
-        part_m[(size_t)split * B + a] = rm[nt];
-        part_l[(size_t)split * B + a] = rl[nt];
-        part_idx[(size_t)split * B + a] = ridx[nt];
+        g.row_m[(size_t)split * B + a] = rm[nt];
+        g.row_l[(size_t)split * B + a] = rl[nt];
+        if constexpr (ARGMAX) g.row_idx[(size_t)split * B + a] = ridx[nt];
       }
     }
   }
@@ -211,13 +330,17 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(const unsigned short* _
 #pragma unroll
   for (int nt = 0; nt < 2; nt++) {
     int a = a_col[nt], r = r_of[nt];
+    if constexpr (BOTH) {
+      if (got[nt] && a < B) g.pos_t[a] = rpos[nt];
+      continue;
+    }
     if (a < B && r >= cbeg && r < cend) {
       // lane that held row r: rows of this lane are brow(mt, reg) with 4*(lane>>5) offset
       int rel = (r - cbeg) % ST_TM;  // row inside its tile
       int wmr = rel / 128, in = rel % 128;
       int half = (in % 8) / 4;
       // a positive that the self-mask removes has the logit -inf (its row loss is then +inf)
-      if (wmr == wm && half == (lane >> 5)) pos_t[a] = (mask_self && r == a) ? -INFINITY : rpos[nt];
+      if (wmr == wm && half == (lane >> 5)) g.pos_t[a] = (mask_self && r == a) ? -INFINITY : rpos[nt];
     }
   }
 }
@@ -282,20 +405,62 @@ static hipError_t launch_stats_small(const LossArgs& a, const LossPlan& pl) {
   return hipGetLastError();
 }
 
+template <StatsMode MODE>
+static hipError_t stats_mfma_launch(const StatsArgs& g, int nwg, hipStream_t stream) {
+  constexpr int smem = 2 * ST_STAGE_BYTES + (MODE >= ST_BOTH ? 4 * 256 * 8 : 0);
+  static bool attr_done[64];
+  if (hipError_t e = ensure_dyn_lds((const void*)stats_mfma_kernel<MODE>, smem, attr_done); e != hipSuccess) return e;
+  stats_mfma_kernel<MODE><<<nwg, 512, smem, stream>>>(g);
+  return hipGetLastError();
+}
 hipError_t launch_stats_mfma(const LossArgs& a, const LossPlan& pl) {
   if (pl.stat_tile) return launch_stats_small(a, pl);
   if (a.d == 128) return launch_stats128(a, pl);   // whole anchor rows in registers: a kernel of its own
   char* ws = a.ws;
-  const int n_ablk = (a.B + ST_TN - 1) / ST_TN;
-  const size_t smem = (size_t)2 * ST_STAGE_BYTES;
-  static bool attr_done[64];
-  if (hipError_t e = ensure_dyn_lds((const void*)stats_mfma_kernel, (int)smem, attr_done); e != hipSuccess) return e;
-  stats_mfma_kernel<<<n_ablk * pl.stat_splits, 512, smem, a.stream>>>(
-      (const unsigned short*)a.q, (const unsigned short*)a.p, a.pos_idx, a.B, a.P, a.d, a.alpha * kLog2e,
-      (a.flags & GC_MASK_SELF) ? 1 : 0, n_ablk, pl.stat_cols_per_split, (float*)(ws + pl.off_part_m),
-      (float*)(ws + pl.off_part_l), (int*)(ws + pl.off_part_idx), (float*)(ws + pl.off_pos));
-  return hipGetLastError();
+  StatsArgs g{};
+  g.Q = (const unsigned short*)a.q; g.P = (const unsigned short*)a.p; g.pos_idx = a.pos_idx; g.B = a.B; g.Pn = a.P; g.d = a.d;
+  g.alpha2 = a.alpha * kLog2e; g.mask_self = (a.flags & GC_MASK_SELF) ? 1 : 0;
+  g.n_ablk = (a.B + ST_TN - 1) / ST_TN; g.cols_per_split = pl.stat_cols_per_split;
+  g.row_m = (float*)(ws + pl.off_part_m); g.row_l = (float*)(ws + pl.off_part_l); g.row_idx = (int*)(ws + pl.off_part_idx);
+  g.pos_t = (float*)(ws + pl.off_pos);
+  const int nwg = g.n_ablk * pl.stat_splits;
+  return a.argmax ? stats_mfma_launch<ST_ARGMAX>(g, nwg, a.stream) : stats_mfma_launch<ST_PLAIN>(g, nwg, a.stream);
 }
 
+// ---- statistics of both sides (the symmetric forms) ------------------------------------------------------------------
+// One pass pays where the plain passes would have their large tiles and each side's partials stay in order: see plan_both.
+BothPlan plan_both(int n, int d, bool triangle, const LossPlan& pl) {
+  BothPlan b{};
+  const int n_ablk = (n + 255) / 256;
+  if (pl.route != ROUTE_MFMA || pl.stat_tile || n_ablk > 64) return b;
+  b.triangle = triangle;
+  b.n_ablk = n_ablk;
+  if (triangle) {
+    // ranges of equal length (whole tiles: 32 rows at d = 128, else 256) that fill the chip once
+    const int unit = d == 128 ? 32 : 256, slots = d == 128 ? 2 * num_cu() : num_cu();
+    for (int len = d == 128 ? 64 : 256;; len += unit) {
+      int wgs = 0;
+      for (int k = 0; k < n_ablk; k++) wgs += (n - 256 * k + len - 1) / len;
+      if (wgs > slots && len < n) continue;
+      b.cols_per_split = len; b.nwg = wgs; b.row_slots = (n + len - 1) / len;
+      break;
+    }
+  } else {
+    b.cols_per_split = pl.stat_cols_per_split; b.row_slots = pl.stat_splits; b.nwg = n_ablk * pl.stat_splits;
+  }
+  // the partials lie where the gradient pass will put its own
+  b.use = (size_t)(b.row_slots + n_ablk) * n * 8 <= pl.off_dp_part - pl.off_dq_part;
+  return b;
+}
+hipError_t launch_stats_both(const LossArgs& a, const LossPlan& pl, const BothPlan& b) {
+  StatsArgs g{};
+  g.Q = (const unsigned short*)a.q; g.P = (const unsigned short*)a.p; g.pos_idx = a.pos_idx; g.B = a.B; g.Pn = a.P; g.d = a.d;
+  g.alpha2 = a.alpha * kLog2e; g.n_ablk = b.n_ablk; g.cols_per_split = b.cols_per_split;
+  b.partials(a, pl, g.row_m, g.row_l, g.col_m, g.col_l);
+  g.pos_t = (float*)(a.ws + pl.off_pos);
+  g.zero = a.wide; g.inv = b.triangle ? nullptr : a.pos_inv;
+  if (a.d == 128) return launch_stats128_both(g, b.triangle, b.nwg, a.stream);
+  return b.triangle ? stats_mfma_launch<ST_TRI>(g, b.nwg, a.stream) : stats_mfma_launch<ST_BOTH>(g, b.nwg, a.stream);
+}
 
 }  // namespace gc

@@ -86,6 +86,7 @@ struct GradArgs {
   const int32_t* pos_pad;   // pos_idx copied and padded with -1 to a multiple of 64 rows
   const float* lse2;        // log2-domain log-sum-exp per anchor, padded with +inf
   const float* lse2_t;      // symmetric loss only: the same per target (over the anchors), padded alike
+  const float* wexp; const float* wexp_t; const int* wide;   // with it: 2^(-lse2 - 1) of both, and the word that forbids them
   int B, Pn;
   float alpha2, out_scale;
   int mask_self;
@@ -161,8 +162,81 @@ __device__ __forceinline__ void static_for(F&& f) {  // f(integral_constant<int,
   }
 }
 
+// Sum (or maximum) of N registers (16 or 64), each over the 32 lanes of its half-wave, by halving: every exchange combines two
+// registers into one, so N registers cost about 2.5 N operations, not 10 N.  The result of register r is in the lanes whose
+// bits 4, 3, 2, 1 spell bits 0, 1, 2, 3 of r (bit 0 of the lane: a copy); N = 64: registers 16 k + r go to out[k].
+template <bool MAX>
+__device__ __forceinline__ float lane_op(float a, float b) { return MAX ? fmaxf(a, b) : a + b; }
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+constexpr int kRor8 = 0x128, kHalfMirror = 0x141, kXor2 = 0x4e, kXor1 = 0xb1;   // row_ror:8, row_half_mirror, quad_perm
+template <bool MAX>
+__device__ __forceinline__ float reduce16_lanes32(const float (&v)[16], int lane) {
+  const bool b3 = lane & 8, b2 = lane & 4, b1 = lane & 2;
+  float u[8], w[4], x[2];
+#pragma unroll
+  for (int k = 0; k < 8; k++) {
+    auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, v[2 * k]), __builtin_bit_cast(unsigned, v[2 * k + 1]), false, false);
+    u[k] = lane_op<MAX>(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1]));
+  }
+#pragma unroll
+  for (int k = 0; k < 4; k++) w[k] = lane_op<MAX>(b3 ? u[2 * k + 1] : u[2 * k], dpp<kRor8>(b3 ? u[2 * k] : u[2 * k + 1]));
+#pragma unroll
+  for (int k = 0; k < 2; k++) x[k] = lane_op<MAX>(b2 ? w[2 * k + 1] : w[2 * k], dpp<kHalfMirror>(b2 ? w[2 * k] : w[2 * k + 1]));
+  const float y = lane_op<MAX>(b1 ? x[1] : x[0], dpp<kXor2>(b1 ? x[0] : x[1]));
+  return lane_op<MAX>(y, dpp<kXor1>(y));
+}
+__device__ __forceinline__ int reduce16_reg_of(int lane) { return ((lane >> 4) & 1) | ((lane >> 2) & 2) | (lane & 4) | ((lane << 2) & 8); }
+// maximum over the 32 lanes of the half-wave, in every lane
+__device__ __forceinline__ float max_lanes32(float x) {
+  unsigned a, b;
+  swap16(__builtin_bit_cast(unsigned, x), a, b);
+  x = fmaxf(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
+  x = fmaxf(x, dpp<kRor8>(x));
+  x = fmaxf(x, dpp<kHalfMirror>(x));
+  x = fmaxf(x, dpp<kXor2>(x));
+  return fmaxf(x, dpp<kXor1>(x));
+}
+
+// Statistics of both sides of a score matrix from one pass over its scores (the symmetric forms): sums of 2^t per row (lanes)
+// and per column of a tile with the reference 0.  A tile whose sums all lie in these bounds has lost nothing: what 2^t flushes
+// is below 2^-126.  Any other tile (and one with masked scores) takes the maxima of its rows and columns as references.
+constexpr float kBothMin = 0x1p-60f, kBothMax = 0x1p100f;
+struct StatsArgs {
+  const unsigned short* Q; const unsigned short* P; const int32_t* pos_idx;
+  int B, Pn, d;              // owners (lanes), streamed rows
+  int n_ablk, cols_per_split, mask_self;
+  float alpha2;
+  // partials (maximum, sum relative to it): [slot][row].  Rows: slot = range of the streamed rows; columns: slot = owner block
+  float* row_m; float* row_l; int* row_idx; float* col_m; float* col_l;
+  float* pos_t;
+  // statistics of both sides: word that the merge may raise; symmetric loss: inv[r_i] = i for every valid r_i (whatever the
+  // workspace held stays elsewhere: whoever reads an entry checks it)
+  int* zero; int32_t* inv;
+};
+__device__ __forceinline__ void both_begin(const StatsArgs& g) {
+  const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (t == 0) *g.zero = 0;
+  if (!g.inv) return;
+  for (int i = t; i < g.B; i += (int)(gridDim.x * blockDim.x)) {
+    const int r = g.pos_idx[i];
+    if (r >= 0 && r < g.Pn) g.inv[r] = i;
+  }
+}
+// TRI: tasks are block 0's ranges of the rows from the block's first one on, then block 1's, ...
+__device__ __forceinline__ int tri_task(int task, int n, int len, int& ablk) {
+  for (ablk = 0;; ablk++) {
+    const int c = (n - ablk * 256 + len - 1) / len;
+    if (task < c) return task;
+    task -= c;
+  }
+}
+hipError_t launch_stats128_both(const StatsArgs& g, bool triangle, int nwg, hipStream_t stream);
+
 // d = 128 (loss_mfma128.hip)
-constexpr int G1_OWN = 256;   // owner rows per workgroup
+constexpr int G1_OWN = 128;   // owner rows per workgroup of the gradient pass
 hipError_t launch_stats128(const LossArgs& a, const LossPlan& pl);
 hipError_t grad128_launch(const GradArgs& ga, int nwg, hipStream_t stream);
 
