@@ -36,6 +36,8 @@ static long long equal_share(long long rows) {
 }
 // few, parts_limit, equal: ROUTE_MFMA.  few: small statistics tiles where the scores are few.  Splits: the fastest whose
 // partials stay below parts_limit bytes, or (equal) the fewest that give every compute unit an equal share of the rows.
+// (`few` also: the splits of the d = 128 kernel as it is; without it, as where the plan is for a limited workspace, those that the
+// 256-row blocks of an earlier form of it had, so that the sizes taken stay the same.)
 static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent, int route, int max_splits, bool few, double parts_limit,
                                    bool equal = false) {
   LossPlan pl{};
@@ -51,16 +53,19 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
       pl.stat_cols_per_split = per * kStatTile;
       pl.stat_splits = ceil_div(tiles, per);
     } else {
-      const int n_ablk = ceil_div(B, 256), tiles = ceil_div(P, 256);
-      // d = 128 has a statistics kernel of 256 threads, two workgroups to a CU
-      int splits = ceil_div(d == 128 ? 2 * kNumCU : kNumCU, n_ablk);
+      // two workgroups to a CU, blocks of 256 anchors at d = 128; without `few`: one of 256 x 256 scores, for fewer partials
+      const bool mid = few && d > 128;
+      const int T = mid ? kStatBlock : 256, n_ablk = ceil_div(B, T), tiles = ceil_div(P, T);
+      int splits = ceil_div(mid || d == 128 ? 2 * kNumCU : kNumCU, n_ablk);
       if (splits > 64) splits = 64;
       if (splits > tiles) splits = tiles;
       if (splits < 1) splits = 1;
-      pl.stat_cols_per_split = ceil_div(tiles, splits) * 256;
+      pl.stat_cols_per_split = ceil_div(tiles, splits) * T;
       pl.stat_splits = ceil_div(P, pl.stat_cols_per_split);
     }
-    const int own = (d == 128) ? 128 : 64;   // owner rows per workgroup of the gradient kernel for this width
+    // owner rows per workgroup of the gradient kernel for this width
+    const bool wide128 = d == 128 && (!few || parts_limit < 1e299);
+    const int own = d > 128 ? 64 : wide128 ? 256 : 128;
     const long long obQ = ceil_div(B, own), obP = ceil_div(P, own);
     // NT-Xent on these kernels is one walk (the score matrix is symmetric: see launch_grad_mfma)
     pl.one_walk = ntxent ? 1 : 0;
@@ -70,10 +75,11 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
     // per compute unit can give a few workgroups more than there are CUs, and with them a second round (258 workgroups
     // at 1021 x 4099 x 384: 46 us, 29 with 242), and few scores leave the CUs idle (6 workgroups at 128 x 256 x 768: 21 us,
     // 15.6 with 32).
-    // Measured: 14 us and 0.03 to 0.05 us per row at d = 768, 0.03 at d = 128; partials about 4 TB/s.
-    // (Two workgroups of the d = 256 kernel share a compute unit, each at some 70 % of its speed.)
-    const double row_us = d == 128 ? 0.0145 : 0.015 + 0.035 * d / 768.0;
-    const int per_cu = d <= 256 ? 2 : 1;
+    // Measured: 14 us and 0.03 to 0.05 us per row at d = 768; 8 and 0.022 at d = 128; partials about 4 TB/s.
+    // (Two workgroups of the d = 128 and d = 256 kernels share a compute unit, each at some 70 % of its speed.)
+    const bool two128 = d == 128 && !wide128;
+    const double row_us = wide128 ? 0.031 : two128 ? 0.022 : 0.015 + 0.035 * d / 768.0, fixed_us = two128 ? 8.0 : 14.0;
+    const int per_cu = d <= 256 && !wide128 ? 2 : 1;
     auto len_of = [](int n, int ns) { return (ceil_div(n, ns) + 31) / 32 * 32; };
     auto parts_bytes = [&](int nsq, int nsp) { return ((double)nsq * B + (double)nsp * P) * d * 4; };
     double best_us = 0;
@@ -83,7 +89,7 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
       const long long n = (walk_q ? obQ * ceil_div(P, q) : 0) + (walk_p ? obP * ceil_div(B, p) : 0);
       const double parts = parts_bytes(walk_q ? ceil_div(P, q) : 0, walk_p ? ceil_div(B, p) : 0);
       const double both = n > kNumCU && per_cu == 2 ? 1.4 : 1.0;
-      const double us = (double)((n + per_cu * kNumCU - 1) / (per_cu * kNumCU)) * (14.0 + row_us * both * (q > p ? q : p)) + 2.0 * parts / 4e6;
+      const double us = (double)((n + per_cu * kNumCU - 1) / (per_cu * kNumCU)) * (fixed_us + row_us * both * (q > p ? q : p)) + 2.0 * parts / 4e6;
       if (parts <= parts_limit && (best_us == 0 || us < best_us)) {
         best_us = us;
         if (walk_q) { bq = ceil_div(P, q); lq = q; }
@@ -105,9 +111,7 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
       ns = ceil_div(n, len);
     };
     pl.nsq = pl.nsp = 1; pl.q_stream_len = len_of(P, 1); pl.p_stream_len = len_of(B, 1);
-    // (equal shares count 256 rows of width 128 to a block: what a limited workspace takes does not depend on the kernel)
-    const int share_own = (d == 128) ? 256 : 64;
-    const long long rows_q = (long long)ceil_div(B, share_own) * P, rows_p = (long long)ceil_div(P, share_own) * B, rows_all = pl.one_walk ? rows_q : rows_q + rows_p;
+    const long long rows_q = obQ * P, rows_p = obP * B, rows_all = pl.one_walk ? rows_q : rows_q + rows_p;
     if (equal) {
       share(rows_all, P, pl.nsq, pl.q_stream_len);
       share(rows_all, B, pl.nsp, pl.p_stream_len);
@@ -201,6 +205,8 @@ static LossPlan choose_plan(int B, int P, int d, gc_dtype dt, bool ntxent, Fits 
       return make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_MFMA, 16, few, parts_limit, equal);
     };
     LossPlan pl = plan(true, 1e300, false);
+    // (which shapes the entry point with the fixed array takes is decided by the plan that parts_limit = 1e298 asks for)
+    pl.over_static = d == 128 ? plan(true, 1e298, false).total > (size_t)GC_STATIC_SCRATCH_BYTES && plan(false, parts, false).total > (size_t)GC_STATIC_SCRATCH_BYTES : 0;
     if (pl.total > (size_t)GC_STATIC_SCRATCH_BYTES) {
       // the shapes that the entry point with the fixed array takes do not depend on the splits: those that fit with an
       // equal share of the rows per compute unit, at least 256 of them, get splits that fit
@@ -550,7 +556,7 @@ int gc_loss_and_rep_grad_bf16_static(const void* q, const void* p, const int32_t
   if (!loss || !dq || !dp) return GC_ERR_NULL;
   LossPlan pl = make_loss_plan(B, P, d, GC_BF16, false);
   if (!pl.use_mfma) pl = make_loss_plan(B, P, d, GC_BF16, false, (size_t)GC_STATIC_SCRATCH_BYTES);
-  if (pl.total > (size_t)GC_STATIC_SCRATCH_BYTES) return GC_ERR_TOO_LARGE;
+  if (pl.total > (size_t)GC_STATIC_SCRATCH_BYTES || pl.over_static) return GC_ERR_TOO_LARGE;
   void* ws = nullptr;
   rc = static_scratch(&ws);
   if (rc != GC_OK) return rc;

@@ -48,10 +48,11 @@ enum LossRoute {
 struct LossPlan {
   int route;
   int use_mfma;          // route == ROUTE_MFMA
+  int over_static;       // more than the entry point with the fixed array takes, whatever `total` says
   int one_walk;          // NT-Xent on the MFMA kernels: dz from a single walk (no dP role, no dP partials)
   int stat_splits;       // column (target) ranges of the statistics pass
   int stat_cols_per_split;
-  int stat_tile;         // the kernel for few scores (kStatTile); 0: ROUTE_MFMA the 256 x 256 (d = 128: 256-anchor) kernels, ROUTE_PLANES the larger one
+  int stat_tile;         // the kernel for few scores (kStatTile); 0: ROUTE_MFMA the 128 x 128 (d = 128: 256-anchor) kernels, ROUTE_PLANES the larger one
   int nsq, nsp;          // stream splits of the dQ-role / dP-role workgroups of the gradient pass
   int q_stream_len, p_stream_len;  // stream rows per split (multiple of the stream tile)
   int b_pad;             // B rounded up to 64 (ROUTE_PLANES: 128): length of the padded lse2 / pos_pad arrays
@@ -70,7 +71,7 @@ struct LossPlan {
 
 // limit: bytes of workspace there are.  To stay below it the calls of ROUTE_MFMA take fewer splits, those of ROUTE_PLANES
 // fewer splits and then ROUTE_GENERAL; what needs the least is returned where nothing fits (the caller compares `total`).
-constexpr int kStatTile = 32;
+constexpr int kStatTile = 32, kStatBlock = 128;
 LossPlan make_loss_plan(int B, int P, int d, gc_dtype dt, bool ntxent, size_t limit = (size_t)-1);
 void plan_planes(LossPlan& pl, int B, int P, int d, gc_dtype dt, int max_splits);
 
@@ -78,7 +79,7 @@ void plan_planes(LossPlan& pl, int B, int P, int d, gc_dtype dt, int max_splits)
 struct LossArgs;
 struct BothPlan {
   bool use, triangle;
-  int n_ablk, cols_per_split, row_slots, nwg;   // blocks of 256 owners; streamed rows of a workgroup; ranges of a block at most
+  int block, n_ablk, cols_per_split, row_slots, nwg;   // owners of a block, blocks; streamed rows of a workgroup; ranges of a block at most
   void partials(const LossArgs& a, const LossPlan& pl, float*& row_m, float*& row_l, float*& col_m, float*& col_l) const;
 };
 BothPlan plan_both(int n, int d, bool triangle, const LossPlan& pl);

@@ -162,7 +162,7 @@ __global__ void __launch_bounds__(256) stats_merge_kernel(const float* __restric
 struct BothMergeArgs {
   const float* row_m; const float* row_l; const float* col_m; const float* col_l; const float* pos_t;
   const int32_t* pos; int32_t* inv;
-  int triangle, n, b_pad, n_ablk, row_slots, cols_per_split, blocks;   // blocks: workgroups of a direction
+  int triangle, n, b_pad, block, n_ablk, row_slots, cols_per_split, blocks;   // blocks: workgroups of a direction
   float* lse2[2]; float* rowloss[2]; float* wexp[2];
   int32_t* pos_pad; int* wide; int* shared;
 };
@@ -173,9 +173,9 @@ __global__ void __launch_bounds__(256) both_merge_kernel(BothMergeArgs g) {
   const int row = threadIdx.x & 15, grp = threadIdx.x >> 4, w = threadIdx.x >> 6;
   const int i = ((int)blockIdx.x - dir * g.blocks) * 16 + row;
   if (blockIdx.x == 0 && threadIdx.x == 0) *g.shared = 0;
-  const int blk = min(i, g.n - 1) / 256;
+  const int blk = min(i, g.n - 1) / g.block;
   const int ncol = g.triangle ? blk : dir ? g.n_ablk : 0;
-  const int nrow = g.triangle ? (g.n - 256 * blk + g.cols_per_split - 1) / g.cols_per_split : dir ? 0 : g.row_slots;
+  const int nrow = g.triangle ? (g.n - g.block * blk + g.cols_per_split - 1) / g.cols_per_split : dir ? 0 : g.row_slots;
   float m = -INFINITY, l = 0.f;
   for (int s0 = grp; s0 < ncol + nrow; s0 += 16 * FLY) {
     float vm[FLY], vl[FLY];
@@ -246,7 +246,7 @@ hipError_t launch_both_merge(const LossArgs& a, const LossPlan& pl, const BothPl
   b.partials(a, pl, rm, rl, cm, cl);
   g.row_m = rm; g.row_l = rl; g.col_m = cm; g.col_l = cl;
   g.pos_t = (const float*)(a.ws + pl.off_pos); g.pos = a.pos_idx; g.inv = a.pos_inv;
-  g.triangle = b.triangle; g.n = a.B; g.b_pad = pl.b_pad; g.n_ablk = b.n_ablk; g.row_slots = b.row_slots; g.cols_per_split = b.cols_per_split;
+  g.triangle = b.triangle; g.n = a.B; g.b_pad = pl.b_pad; g.block = b.block; g.n_ablk = b.n_ablk; g.row_slots = b.row_slots; g.cols_per_split = b.cols_per_split;
   g.blocks = (pl.b_pad + 15) / 16;
   char* const ws[2] = {a.ws, a.ws_t};
   for (int k = 0; k < (b.triangle ? 1 : 2); k++) {

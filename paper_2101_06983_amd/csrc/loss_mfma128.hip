@@ -481,7 +481,7 @@ __global__ void __launch_bounds__(256, 2) stats128_both_kernel(StatsArgs g) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, h = lane >> 5, ln = lane & 31;
   both_begin(g);
   int task = xcd_task_id(), ablk, split;
-  if (TRI) split = tri_task(task, g.Pn, g.cols_per_split, ablk);
+  if (TRI) split = tri_task(task, g.Pn, S1_OWN, g.cols_per_split, ablk);
   else { ablk = task % g.n_ablk; split = task / g.n_ablk; }
   const int blk_end = (ablk + 1) * S1_OWN;
   const int a0 = ablk * S1_OWN + w * S1_OWN_W;   // this wave's first owner

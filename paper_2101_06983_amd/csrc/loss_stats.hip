@@ -7,13 +7,16 @@
 namespace gc {
 
 // ===========================================================================
-// Statistics pass.  Workgroup = 512 threads = 8 waves as 2 (targets, M) x 4 (anchors, N);
-// workgroup tile 256 targets x 256 anchors, wave tile 128 x 64 (4 x 2 MFMA tiles).
-// k is staged through LDS in chunks of 64, two stages.
+// Statistics pass.  Workgroup = 512 threads = 8 waves as 2 (targets, M) x 4 (anchors, N); wave tile MT x NT = 2 x 1 MFMA
+// tiles, workgroup tile 128 x 128, two workgroups to a compute unit.  k is staged through LDS in chunks of 64, two stages.
+// One workgroup of 256 x 256 (wave tile 4 x 2) halves the LDS bytes per MFMA and is no faster where it fills the chip
+// (4096 x 8192 x 256: 137 us a call with either), but leaves most of it idle below (68 tiles at 1021 x 4099 x 384: 22.6 us of a
+// call of 69.7, now 59.1), and has no registers left for the sums of both sides (symmetric 8192 x 256: 283 us, now 253).
 // ===========================================================================
-constexpr int ST_TM = 256, ST_TN = 256, ST_KC = 64;
-constexpr int ST_ROWB = ST_KC * 2;                       // bytes per LDS row (8 chunks of 16 bytes, unpadded)
-constexpr int ST_STAGE_BYTES = (ST_TM + ST_TN) * ST_ROWB;  // one stage: 256 target rows, then 256 anchor rows
+constexpr int ST_KC = 64, ST_ROWB = ST_KC * 2;           // bytes per LDS row (8 chunks of 16 bytes, unpadded)
+constexpr int MT = 2, NT = 1, ST_TM = 64 * MT, ST_TN = 128 * NT;
+constexpr int ST_STAGE_BYTES = (ST_TM + ST_TN) * ST_ROWB;   // one stage: the target rows, then the anchor rows
+static_assert(ST_TM == kStatBlock && ST_TN == kStatBlock, "waves 0-3 load the target rows, waves 4-7 as many anchor rows");
 // LDS layout: chunk c of row r is stored at chunk position c ^ ((r >> 1) & 7): the 16 rows that a
 // 16-lane group reads in one fragment load then fall into 16 different 16-byte bank groups.
 
@@ -21,7 +24,8 @@ constexpr int ST_STAGE_BYTES = (ST_TM + ST_TN) * ST_ROWB;  // one stage: 256 tar
 // from one pass over the scores (see kBothMin), TRI (NT-Xent, q = p) over the tiles on and above the diagonal only.
 enum StatsMode { ST_PLAIN, ST_ARGMAX, ST_BOTH, ST_TRI };
 template <StatsMode MODE>
-__global__ void __launch_bounds__(512) stats_mfma_kernel(StatsArgs g) {
+__global__ void __launch_bounds__(512, 4) stats_mfma_kernel(StatsArgs g) {
+  constexpr int LROWS = ST_TM / 4;   // rows of a stage that a wave loads
   constexpr bool TRI = MODE == ST_TRI, BOTH = MODE == ST_BOTH || TRI, ARGMAX = MODE == ST_ARGMAX;
   const unsigned short* const Q = g.Q;
   const unsigned short* const Pm = g.P;
@@ -34,27 +38,27 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(StatsArgs g) {
   const int wm = wave & 1, wn = wave >> 1;
   if constexpr (BOTH) both_begin(g);
   int task = xcd_task_id(), ablk, split;
-  if (TRI) split = tri_task(task, P, cols_per_split, ablk);
+  if (TRI) split = tri_task(task, P, ST_TN, cols_per_split, ablk);
   else { ablk = task % g.n_ablk; split = task / g.n_ablk; }
   const int a0 = ablk * ST_TN;
   const int cbeg = (TRI ? a0 : 0) + split * cols_per_split, cend = min(P, cbeg + cols_per_split);
   const int nk = d / ST_KC;
 
-  // ---- direct global->LDS loads: wave w fills rows 64 w .. 64 w + 63 of a stage (waves 0-3 the target
-  // rows, waves 4-7 the anchor rows), 8 instructions of 8 rows x 8 chunks each -------------------------
+  // ---- direct global->LDS loads: wave w fills rows LROWS w .. of a stage (waves 0-3 the target rows,
+  // waves 4-7 the anchor rows), each instruction 8 rows x 8 chunks ------------------------------------
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);  // as a scalar: what follows from it stays uniform
   const bool loads_q = wave_u >= 4;
   const unsigned short* lmat = loads_q ? Q : Pm;
   const int lrows = loads_q ? B : P;
-  const int lrow_in = (wave_u & 3) * 64 + (lane >> 3);  // + 8 j: row inside the 256-row tile
-  const unsigned stage_m0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)smem_b + wave_u * 64 * ST_ROWB);
+  const int lrow_in = (wave_u & 3) * LROWS + (lane >> 3);  // + 8 j: row inside the tile
+  const unsigned stage_m0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)smem_b + wave_u * LROWS * ST_ROWB);
   auto src_of = [&](int j, int tile_row0, bool clamp) -> unsigned {  // byte offset from the tile's first row, chunk kc = 0
     int r = lrow_in + 8 * j;
     const int c = (lane & 7) ^ ((r >> 1) & 7);
     if (clamp) r = min(r, lrows - 1 - tile_row0);
     return (unsigned)(r * d * 2 + c * 16);
   };
-  // full tile: row 8 j moves the chunk by its swizzle's bit 2 only, so two offsets and a scalar step serve the eight loads
+  // full tile: row 8 j moves the chunk by its swizzle's bit 2 only, so two offsets and a scalar step serve all loads
   const unsigned voff_full[2] = {src_of(0, 0, false), src_of(1, 0, false) - 16u * (unsigned)d};
   auto prefetch = [&](int tile_row0, int kc, int stage) __attribute__((always_inline)) {
     const unsigned short* base_v = lmat + (size_t)tile_row0 * d + kc * ST_KC;  // the same in every lane of a wave
@@ -64,12 +68,12 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(StatsArgs g) {
         ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((unsigned)(bu >> 32)) << 32) |
         (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((unsigned)bu));
     const unsigned m0 = stage_m0 + stage * ST_STAGE_BYTES;
-    if (tile_row0 + 256 <= lrows) {
+    if (tile_row0 + ST_TM <= lrows) {
 #pragma unroll
-      for (int j = 0; j < 8; j++) dma_group<1>((const char*)base + 16 * j * d, &voff_full[j & 1], m0 + 1024 * j);
+      for (int j = 0; j < LROWS / 8; j++) dma_group<1>((const char*)base + 16 * j * d, &voff_full[j & 1], m0 + 1024 * j);
     } else {  // ragged tile: rows past the end re-read the last valid row (masked later)
 #pragma unroll
-      for (int j = 0; j < 8; j++) {
+      for (int j = 0; j < LROWS / 8; j++) {
         const unsigned off = src_of(j, tile_row0, true);
         dma_group<1>(base, &off, m0 + j * 1024);
       }
@@ -81,36 +85,38 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(StatsArgs g) {
   unsigned koff[4];
 #pragma unroll
   for (int ks = 0; ks < 4; ks++) koff[ks] = (unsigned)(((2 * ks + (lane >> 5)) ^ swz_l) * 16);
-  const unsigned char* a_base = smem_b + (wm * 128 + (lane & 31)) * ST_ROWB;               // + mt * 32 rows
-  const unsigned char* b_base = smem_b + (ST_TM + wn * 64 + (lane & 31)) * ST_ROWB;        // + nt * 32 rows
+  const unsigned char* a_base = smem_b + (wm * 32 * MT + (lane & 31)) * ST_ROWB;               // + mt * 32 rows
+  const unsigned char* b_base = smem_b + (ST_TM + wn * 32 * NT + (lane & 31)) * ST_ROWB;        // + nt * 32 rows
 
-  // per-lane running statistics for its two anchor columns
-  float rm[2], rl[2], rpos[2];
-  int ridx[2], a_col[2], r_of[2];
+  // per-lane running statistics for its anchor columns
+  float rm[NT], rl[NT], rpos[NT];
+  int ridx[NT], a_col[NT], r_of[NT];
 #pragma unroll
-  for (int nt = 0; nt < 2; nt++) {
+  for (int nt = 0; nt < NT; nt++) {
     rm[nt] = -INFINITY; rl[nt] = 0.f; rpos[nt] = 0.f; ridx[nt] = 0x7fffffff;
-    a_col[nt] = a0 + wn * 64 + nt * 32 + (lane & 31);
+    a_col[nt] = a0 + wn * 32 * NT + nt * 32 + (lane & 31);
     r_of[nt] = (a_col[nt] >= B) ? -1 : TRI ? a_col[nt] ^ 1 : pos_idx[a_col[nt]];
   }
   // BOTH: sums with the reference 0 (rm, rl: of the tiles that needed one of their own); whether this lane saw the positive
-  float lf[2] = {0.f, 0.f};
-  bool got[2] = {false, false};
+  float lf[NT];
+  bool got[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; nt++) { lf[nt] = 0.f; got[nt] = false; }
   typedef __attribute__((ext_vector_type(2))) float f32x2;
-  f32x2* cbuf = (f32x2*)(smem_b + 2 * ST_STAGE_BYTES);   // [4 wn][256 columns] (maximum, sum)
+  f32x2* cbuf = (f32x2*)(smem_b + 2 * ST_STAGE_BYTES);   // [4 wn][ST_TM columns] (maximum, sum)
   const int col_in = 8 * (reduce16_reg_of(lane) >> 2) + 4 * (lane >> 5) + (reduce16_reg_of(lane) & 3);
-  const bool own_edge = a0 + wn * 64 + 64 > B;
+  const bool own_edge = a0 + wn * 32 * NT + 32 * NT > B;
 
   // The k-chunks of all the tiles of this workgroup form one sequence of steps; step st lives in stage st & 1 and
   // its loads are issued one step ahead inside a tile.  (Loading the first chunk of the next tile under the last
   // MFMAs of this one was measured too: no gain at 2 tiles of 12 chunks, a loss at 16 tiles of 2 chunks.)
   int st = 0;
   for (int b0 = cbeg; b0 < cend; b0 += ST_TM) {
-    f32x16 acc[4][2];
+    f32x16 acc[MT][NT];
 #pragma unroll
-    for (int mt = 0; mt < 4; mt++)
+    for (int mt = 0; mt < MT; mt++)
 #pragma unroll
-      for (int nt = 0; nt < 2; nt++)
+      for (int nt = 0; nt < NT; nt++)
 #pragma unroll
         for (int r = 0; r < 16; r++) acc[mt][nt][r] = 0.f;
 
@@ -119,25 +125,25 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(StatsArgs g) {
     prefetch(row0, 0, st & 1);
     wait_vmem<0>();
     __syncthreads();
-    bf16x8 af[2][4], bfg[2][2];
+    bf16x8 af[2][MT], bfg[2][NT];
     for (int kc = 0; kc < nk; kc++, st++) {
       if (kc + 1 < nk) prefetch(row0, kc + 1, (st + 1) & 1);
       const int so = (st & 1) * ST_STAGE_BYTES;
       __builtin_amdgcn_iglp_opt(0);  // scheduler hint: interleave the fragment reads with the MFMA stream
       auto load_frags = [&](int ks, int buf) __attribute__((always_inline)) {
 #pragma unroll
-        for (int mt = 0; mt < 4; mt++) af[buf][mt] = *(const bf16x8*)(a_base + so + mt * 32 * ST_ROWB + koff[ks]);
+        for (int mt = 0; mt < MT; mt++) af[buf][mt] = *(const bf16x8*)(a_base + so + mt * 32 * ST_ROWB + koff[ks]);
 #pragma unroll
-        for (int nt = 0; nt < 2; nt++) bfg[buf][nt] = *(const bf16x8*)(b_base + so + nt * 32 * ST_ROWB + koff[ks]);
+        for (int nt = 0; nt < NT; nt++) bfg[buf][nt] = *(const bf16x8*)(b_base + so + nt * 32 * ST_ROWB + koff[ks]);
       };
       load_frags(0, 0);
 #pragma unroll
       for (int ks = 0; ks < ST_KC / 16; ks++) {
         if (ks + 1 < ST_KC / 16) load_frags(ks + 1, (ks + 1) & 1);
 #pragma unroll
-        for (int mt = 0; mt < 4; mt++)
+        for (int mt = 0; mt < MT; mt++)
 #pragma unroll
-          for (int nt = 0; nt < 2; nt++) acc[mt][nt] = mfma32(af[ks & 1][mt], bfg[ks & 1][nt], acc[mt][nt]);
+          for (int nt = 0; nt < NT; nt++) acc[mt][nt] = mfma32(af[ks & 1][mt], bfg[ks & 1][nt], acc[mt][nt]);
       }
       wait_vmem<0>();   // this wave's part of the next stage has landed
       __syncthreads();  // ... and everybody's; nobody still reads the stage that is overwritten next
@@ -145,15 +151,17 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(StatsArgs g) {
 
     // ---- tile epilogue: online softmax statistics, all in registers; acc holds the raw dot products, the
     // base-2 logit is t = alpha2 * acc (alpha2 > 0: the order of the raw values is the order of the logits) -------
-    const int brow0 = b0 + wm * 128 + 4 * (lane >> 5);  // + mt*32 + 8*(r/4) + r%4
+    const int brow0 = b0 + wm * 32 * MT + 4 * (lane >> 5);  // + mt*32 + 8*(r/4) + r%4
     const bool edge = (b0 + ST_TM > cend);
     if constexpr (BOTH) {
-      const bool has_pos = (unsigned)(r_of[0] - b0) < (unsigned)ST_TM || (unsigned)(r_of[1] - b0) < (unsigned)ST_TM;
+      bool has_pos = false;
+#pragma unroll
+      for (int nt = 0; nt < NT; nt++) has_pos = has_pos || (unsigned)(r_of[nt] - b0) < (unsigned)ST_TM;
       if (__builtin_amdgcn_ballot_w64(has_pos) != 0) {
 #pragma unroll
-        for (int nt = 0; nt < 2; nt++)
+        for (int nt = 0; nt < NT; nt++)
 #pragma unroll
-          for (int mt = 0; mt < 4; mt++)
+          for (int mt = 0; mt < MT; mt++)
 #pragma unroll
             for (int r = 0; r < 16; r++)
               if (brow0 + mt * 32 + 8 * (r >> 2) + (r & 3) == r_of[nt] && r_of[nt] < cend) {
@@ -164,36 +172,44 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(StatsArgs g) {
       const bool cols = !TRI || b0 > a0;
       bool done = false;
       if (cols && !own_edge && !edge) {
-        float rs[2] = {0.f, 0.f}, c[4], lo = INFINITY, hi = 0.f;
+        float rs[NT], c[MT], lo = INFINITY, hi = 0.f;
 #pragma unroll
-        for (int mt = 0; mt < 4; mt++) {
+        for (int nt = 0; nt < NT; nt++) rs[nt] = 0.f;
+#pragma unroll
+        for (int mt = 0; mt < MT; mt++) {
           float v[16];
 #pragma unroll
           for (int r = 0; r < 16; r++) {
-            const float e0 = fast_exp2(acc[mt][0][r] * alpha2), e1 = fast_exp2(acc[mt][1][r] * alpha2);
-            rs[0] += e0; rs[1] += e1;
-            v[r] = e0 + e1;
+#pragma unroll
+            for (int nt = 0; nt < NT; nt++) {
+              const float e = fast_exp2(acc[mt][nt][r] * alpha2);
+              rs[nt] += e;
+              v[r] = nt ? v[r] + e : e;
+            }
           }
           c[mt] = reduce16_lanes32<false>(v, lane);
           lo = fminf(lo, c[mt]); hi = fmaxf(hi, c[mt]);
           __builtin_amdgcn_sched_barrier(0);
         }
-        lo = fminf(lo, fminf(rs[0], rs[1])); hi = fmaxf(hi, fmaxf(rs[0], rs[1]));
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++) { lo = fminf(lo, rs[nt]); hi = fmaxf(hi, rs[nt]); }
         if (__builtin_amdgcn_ballot_w64(!(lo >= kBothMin && hi <= kBothMax)) == 0) {
-          lf[0] += rs[0]; lf[1] += rs[1];
+#pragma unroll
+          for (int nt = 0; nt < NT; nt++) lf[nt] += rs[nt];
           if (!(lane & 1)) {
 #pragma unroll
-            for (int mt = 0; mt < 4; mt++) cbuf[wn * 256 + wm * 128 + mt * 32 + col_in] = f32x2{0.f, c[mt]};
+            for (int mt = 0; mt < MT; mt++) cbuf[wn * ST_TM + wm * 32 * MT + mt * 32 + col_in] = f32x2{0.f, c[mt]};
           }
           done = true;
         }
       }
       if (!done) {   // masks, and references of its own for every row and column
-        float tm[2] = {-INFINITY, -INFINITY}, mn[2], sum[2] = {0.f, 0.f};
+        float tm[NT], mn[NT], sum[NT];
 #pragma unroll
-        for (int nt = 0; nt < 2; nt++) {
+        for (int nt = 0; nt < NT; nt++) {
+          tm[nt] = -INFINITY; sum[nt] = 0.f;
 #pragma unroll
-          for (int mt = 0; mt < 4; mt++)
+          for (int mt = 0; mt < MT; mt++)
 #pragma unroll
             for (int r = 0; r < 16; r++) {
               const int j = brow0 + mt * 32 + 8 * (r >> 2) + (r & 3);
@@ -204,28 +220,30 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(StatsArgs g) {
           if (mn[nt] == -INFINITY) mn[nt] = 0.f;
         }
 #pragma unroll
-        for (int mt = 0; mt < 4; mt++) {
+        for (int mt = 0; mt < MT; mt++) {
 #pragma unroll
-          for (int nt = 0; nt < 2; nt++)
+          for (int nt = 0; nt < NT; nt++)
 #pragma unroll
             for (int r = 0; r < 16; r++) sum[nt] += fast_exp2(acc[mt][nt][r] - mn[nt]);
           if (cols) {
             float mx[16], v[16];
 #pragma unroll
             for (int r = 0; r < 16; r++) {
-              mx[r] = fmaxf(acc[mt][0][r], acc[mt][1][r]);
+#pragma unroll
+              for (int nt = 0; nt < NT; nt++) mx[r] = nt ? fmaxf(mx[r], acc[mt][nt][r]) : acc[mt][nt][r];
               float m = max_lanes32(mx[r]);
               m = m == -INFINITY ? 0.f : m;
-              v[r] = fast_exp2(acc[mt][0][r] - m) + fast_exp2(acc[mt][1][r] - m);
+#pragma unroll
+              for (int nt = 0; nt < NT; nt++) v[r] = (nt ? v[r] : 0.f) + fast_exp2(acc[mt][nt][r] - m);
               if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
             }
             const float cm = reduce16_lanes32<true>(mx, lane), cl = reduce16_lanes32<false>(v, lane);
-            if (!(lane & 1)) cbuf[wn * 256 + wm * 128 + mt * 32 + col_in] = f32x2{cm, cl};
+            if (!(lane & 1)) cbuf[wn * ST_TM + wm * 32 * MT + mt * 32 + col_in] = f32x2{cm, cl};
           }
           __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
-        for (int nt = 0; nt < 2; nt++) {
+        for (int nt = 0; nt < NT; nt++) {
           if (tm[nt] == -INFINITY) continue;
           rl[nt] = rl[nt] * fast_exp2(rm[nt] - mn[nt]) + sum[nt];
           rm[nt] = mn[nt];
@@ -233,11 +251,11 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(StatsArgs g) {
       }
       if (cols) {   // the four waves' sums of a column, in wave order (the next tile writes them behind many barriers)
         __syncthreads();
-        if (tid < 256 && b0 + tid < cend) {
+        if (tid < ST_TM && b0 + tid < cend) {
           f32x2 x[4];
           float m = -INFINITY, l = 0.f;
 #pragma unroll
-          for (int k = 0; k < 4; k++) { x[k] = cbuf[k * 256 + tid]; m = fmaxf(m, x[k][0]); }
+          for (int k = 0; k < 4; k++) { x[k] = cbuf[k * ST_TM + tid]; m = fmaxf(m, x[k][0]); }
           const float ms = m == -INFINITY ? 0.f : m;
 #pragma unroll
           for (int k = 0; k < 4; k++) l += x[k][1] * fast_exp2(x[k][0] - ms);
@@ -248,14 +266,14 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(StatsArgs g) {
       continue;
     }
 #pragma unroll
-    for (int nt = 0; nt < 2; nt++) {
+    for (int nt = 0; nt < NT; nt++) {
       const int a = a_col[nt];
       // the masks that can touch this tile
       const bool diag = mask_self && (a >= b0 && a < b0 + ST_TM);
       const bool haspos = (unsigned)(r_of[nt] - b0) < (unsigned)ST_TM;
       if (edge || diag || haspos) {  // rare: the general slow walk
 #pragma unroll
-        for (int mt = 0; mt < 4; mt++)
+        for (int mt = 0; mt < MT; mt++)
 #pragma unroll
           for (int r = 0; r < 16; r++) {
             int j = brow0 + mt * 32 + 8 * (r >> 2) + (r & 3);
@@ -267,7 +285,7 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(StatsArgs g) {
       // register order j is increasing too, so a strict > keeps the smallest index)
       float tmr = -INFINITY; int tc = 0;
 #pragma unroll
-      for (int mt = 0; mt < 4; mt++)
+      for (int mt = 0; mt < MT; mt++)
 #pragma unroll
         for (int r = 0; r < 16; r++) {
           const float t = acc[mt][nt][r];
@@ -284,7 +302,7 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(StatsArgs g) {
         const float mn = fmaxf(rm[nt], tm);
         float s = 0.f;
 #pragma unroll
-        for (int mt = 0; mt < 4; mt++)
+        for (int mt = 0; mt < MT; mt++)
 #pragma unroll
           for (int r = 0; r < 16; r++) s += fast_exp2(__builtin_fmaf(acc[mt][nt][r], alpha2, -mn));
         rl[nt] = rl[nt] * fast_exp2(rm[nt] - mn) + s;
@@ -296,7 +314,7 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(StatsArgs g) {
 
   // ---- combine the two half-waves (same anchor column, different target rows) -------------------
 #pragma unroll
-  for (int nt = 0; nt < 2; nt++) {
+  for (int nt = 0; nt < NT; nt++) {
     if constexpr (BOTH) stat_merge(rm[nt], rl[nt], ridx[nt], lf[nt] > 0.f ? 0.f : -INFINITY, lf[nt], 0x7fffffff);
     float m2 = __shfl_xor(rm[nt], 32), l2 = __shfl_xor(rl[nt], 32);
     int i2 = __shfl_xor(ridx[nt], 32);
@@ -304,19 +322,19 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(StatsArgs g) {
   }
   // ---- combine the two waves along M through LDS, then write the split partial ------------------
   __syncthreads();
-  float* xs = (float*)smem_b;  // [4 wn][2 nt][32][3]
+  float* xs = (float*)smem_b;  // [4 wn][NT][32][3]
   if (wm == 1 && lane < 32) {
 #pragma unroll
-    for (int nt = 0; nt < 2; nt++) {
-      float* x = xs + ((wn * 2 + nt) * 32 + lane) * 3;
+    for (int nt = 0; nt < NT; nt++) {
+      float* x = xs + ((wn * NT + nt) * 32 + lane) * 3;
       x[0] = rm[nt]; x[1] = rl[nt]; x[2] = __builtin_bit_cast(float, ridx[nt]);
     }
   }
   __syncthreads();
   if (wm == 0 && lane < 32) {
 #pragma unroll
-    for (int nt = 0; nt < 2; nt++) {
-      const float* x = xs + ((wn * 2 + nt) * 32 + lane) * 3;
+    for (int nt = 0; nt < NT; nt++) {
+      const float* x = xs + ((wn * NT + nt) * 32 + lane) * 3;
       stat_merge(rm[nt], rl[nt], ridx[nt], x[0], x[1], __builtin_bit_cast(int, x[2]));
       int a = a_col[nt];
       if (a < B) {
@@ -328,7 +346,7 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(StatsArgs g) {
   }
   // the positive's score is seen by exactly one lane of one workgroup
 #pragma unroll
-  for (int nt = 0; nt < 2; nt++) {
+  for (int nt = 0; nt < NT; nt++) {
     int a = a_col[nt], r = r_of[nt];
     if constexpr (BOTH) {
       if (got[nt] && a < B) g.pos_t[a] = rpos[nt];
@@ -337,7 +355,7 @@ __global__ void __launch_bounds__(512) stats_mfma_kernel(StatsArgs g) {
     if (a < B && r >= cbeg && r < cend) {
       // lane that held row r: rows of this lane are brow(mt, reg) with 4*(lane>>5) offset
       int rel = (r - cbeg) % ST_TM;  // row inside its tile
-      int wmr = rel / 128, in = rel % 128;
+      int wmr = rel / (32 * MT), in = rel % (32 * MT);
       int half = (in % 8) / 4;
       // a positive that the self-mask removes has the logit -inf (its row loss is then +inf)
       if (wmr == wm && half == (lane >> 5)) g.pos_t[a] = (mask_self && r == a) ? -INFINITY : rpos[nt];
@@ -407,7 +425,7 @@ static hipError_t launch_stats_small(const LossArgs& a, const LossPlan& pl) {
 
 template <StatsMode MODE>
 static hipError_t stats_mfma_launch(const StatsArgs& g, int nwg, hipStream_t stream) {
-  constexpr int smem = 2 * ST_STAGE_BYTES + (MODE >= ST_BOTH ? 4 * 256 * 8 : 0);
+  constexpr int smem = 2 * ST_STAGE_BYTES + (MODE >= ST_BOTH ? 4 * ST_TM * 8 : 0);
   static bool attr_done[64];
   if (hipError_t e = ensure_dyn_lds((const void*)stats_mfma_kernel<MODE>, smem, attr_done); e != hipSuccess) return e;
   stats_mfma_kernel<MODE><<<nwg, 512, smem, stream>>>(g);
@@ -428,27 +446,28 @@ hipError_t launch_stats_mfma(const LossArgs& a, const LossPlan& pl) {
 }
 
 // ---- statistics of both sides (the symmetric forms) ------------------------------------------------------------------
-// One pass pays where the plain passes would have their large tiles and each side's partials stay in order: see plan_both.
+// One pass where the plain one does not have its tiles for few scores.  At most 128 blocks: each leaves a partial per column
+// (n^2 / 16 bytes), and they lie where the gradient pass will put its own.
 BothPlan plan_both(int n, int d, bool triangle, const LossPlan& pl) {
   BothPlan b{};
-  const int n_ablk = (n + 255) / 256;
-  if (pl.route != ROUTE_MFMA || pl.stat_tile || n_ablk > 64) return b;
+  const int T = d == 128 ? 256 : kStatBlock, n_ablk = (n + T - 1) / T;
+  if (pl.route != ROUTE_MFMA || pl.stat_tile || n_ablk > 128) return b;
   b.triangle = triangle;
+  b.block = T;
   b.n_ablk = n_ablk;
   if (triangle) {
-    // ranges of equal length (whole tiles: 32 rows at d = 128, else 256) that fill the chip once
-    const int unit = d == 128 ? 32 : 256, slots = d == 128 ? 2 * num_cu() : num_cu();
-    for (int len = d == 128 ? 64 : 256;; len += unit) {
+    // ranges of equal length (whole tiles: 32 rows at d = 128) that fill the chip once
+    const int unit = d == 128 ? 32 : T;
+    for (int len = d == 128 ? 64 : T;; len += unit) {
       int wgs = 0;
-      for (int k = 0; k < n_ablk; k++) wgs += (n - 256 * k + len - 1) / len;
-      if (wgs > slots && len < n) continue;
+      for (int k = 0; k < n_ablk; k++) wgs += (n - T * k + len - 1) / len;
+      if (wgs > 2 * num_cu() && len < n) continue;
       b.cols_per_split = len; b.nwg = wgs; b.row_slots = (n + len - 1) / len;
       break;
     }
   } else {
     b.cols_per_split = pl.stat_cols_per_split; b.row_slots = pl.stat_splits; b.nwg = n_ablk * pl.stat_splits;
   }
-  // the partials lie where the gradient pass will put its own
   b.use = (size_t)(b.row_slots + n_ablk) * n * 8 <= pl.off_dp_part - pl.off_dq_part;
   return b;
 }

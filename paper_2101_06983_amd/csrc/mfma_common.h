@@ -226,9 +226,9 @@ __device__ __forceinline__ void both_begin(const StatsArgs& g) {
   }
 }
 // TRI: tasks are block 0's ranges of the rows from the block's first one on, then block 1's, ...
-__device__ __forceinline__ int tri_task(int task, int n, int len, int& ablk) {
+__device__ __forceinline__ int tri_task(int task, int n, int block, int len, int& ablk) {
   for (ablk = 0;; ablk++) {
-    const int c = (n - ablk * 256 + len - 1) / len;
+    const int c = (n - ablk * block + len - 1) / len;
     if (task < c) return task;
     task -= c;
   }
