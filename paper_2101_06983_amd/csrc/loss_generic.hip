@@ -388,37 +388,58 @@ __device__ __forceinline__ void add_row4(f32x4& acc, float c, const unsigned sho
 #pragma unroll
   for (int k = 0; k < 4; k++) acc[k] += c * bf2f((unsigned short)v[k]);
 }
-// What a workgroup of the sum kernel keeps of up to 256 anchors that share a target: the anchor, its target and coefficient
-struct SharedList { int anchor[256]; int row[256]; float c[256]; int cnt[4]; };
+// What a workgroup of the sum kernel keeps of up to 1024 anchors that share a target: the anchor, its target and coefficient
+constexpr int kListLen = 1024, kListPer = kListLen / 256;
+struct SharedList { int anchor[kListLen]; int row[kListLen]; float c[kListLen]; int cnt[kListPer][4]; };
 // Some target is the positive of several anchors: every anchor that names one of the rows of this workgroup's elements
-// (first .. last), in index order.  The workgroup looks through the anchors together, 256 at a time, and keeps the matches
-// with their coefficients (in index order: ballot and prefix inside a wave, waves one after the other) in LDS; each thread
-// then adds those of its own rows, eight loads in flight.  (A scan by every thread for itself took 179 of the 253 us of a
-// call with B = 1021, P = 4099, d = 384, and 1.0 ms where 2700 anchors share one target of 300.)  Workgroups none of whose
-// rows is named, the most of them, are done at once.
+// (first .. last), in index order.  The workgroup looks through the anchors together, 1024 at a time (four a thread, loaded
+// together: at 256 a time each round's loads and barriers are a latency of their own, 14.3 us for the sums of 1021 x 4099 x 384,
+// now XX), and keeps the matches with their coefficients (in index order: ballot and prefix inside a wave, waves one after the
+// other) in LDS; each thread then adds those of its own rows, eight loads in flight.  (A scan by every thread for itself took
+// 179 us there, and 1.0 ms where 2700 anchors share one target of 300.)  Workgroups none of whose rows is named, the most of
+// them, are done at once.
 __device__ __forceinline__ void add_shared_positives(f32x4& acc, const PosFix& fx, size_t first, size_t last, int row, int col, bool live,
                                                      SharedList& list) {
   const int row0 = (int)(first / (size_t)fx.d), row1 = (int)(last / (size_t)fx.d);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int r[kListPer];
+  auto load = [&](int i0) {
+#pragma unroll
+    for (int k = 0; k < kListPer; k++) {
+      const int i = i0 + 256 * k + (int)threadIdx.x;
+      r[k] = i < fx.B ? fx.pos[i] : -1;
+    }
+  };
+  load(0);   // (in flight while the check below waits for its own loads)
   bool named = false;
   if (live) {   // the merge records one of the anchors of every named target (whatever the workspace held, if none: checked)
     const int i = fx.inv[row];
     named = i >= 0 && i < fx.B && fx.pos[i] == row;
   }
   if (!__syncthreads_or(named)) return;
-  for (int i0 = 0; i0 < fx.B; i0 += 256) {
-    const int i = i0 + (int)threadIdx.x;
-    const int r = i < fx.B ? fx.pos[i] : -1;
-    const bool match = r >= row0 && r <= row1;
-    const unsigned long long mask = __builtin_amdgcn_ballot_w64(match);
-    if (lane == 0) list.cnt[w] = __builtin_popcountll(mask);
+  for (int i0 = 0; i0 < fx.B; i0 += kListLen) {
+    if (i0) load(i0);
+    unsigned long long mask[kListPer];
+#pragma unroll
+    for (int k = 0; k < kListPer; k++) {
+      mask[k] = __builtin_amdgcn_ballot_w64(r[k] >= row0 && r[k] <= row1);
+      if (lane == 0) list.cnt[k][w] = __builtin_popcountll(mask[k]);
+    }
     __syncthreads();
-    int base = 0;
-    for (int k = 0; k < w; k++) base += list.cnt[k];
-    const int total = list.cnt[0] + list.cnt[1] + list.cnt[2] + list.cnt[3];
-    if (match) {
-      const int at = base + __builtin_popcountll(mask & ((1ull << lane) - 1ull));
-      list.anchor[at] = i; list.row[at] = r; list.c[at] = pos_coeff(fx, i, r);
+    int total = 0;
+#pragma unroll
+    for (int k = 0; k < kListPer; k++) {
+      int base = total;
+#pragma unroll
+      for (int x = 0; x < 4; x++) {
+        const int n = list.cnt[k][x];
+        base += x < w ? n : 0;
+        total += n;
+      }
+      if (r[k] >= row0 && r[k] <= row1) {
+        const int at = base + __builtin_popcountll(mask[k] & ((1ull << lane) - 1ull)), i = i0 + 256 * k + (int)threadIdx.x;
+        list.anchor[at] = i; list.row[at] = r[k]; list.c[at] = pos_coeff(fx, i, r[k]);
+      }
     }
     __syncthreads();
     constexpr int FLY = 8;
