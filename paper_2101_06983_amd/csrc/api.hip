@@ -36,10 +36,10 @@ static long long equal_share(long long rows) {
 }
 // few, parts_limit, equal: ROUTE_MFMA.  few: small statistics tiles where the scores are few.  Splits: the fastest whose
 // partials stay below parts_limit bytes, or (equal) the fewest that give every compute unit an equal share of the rows.
-// (`few` also: the splits of the d = 128 kernel as it is; without it, as where the plan is for a limited workspace, those that the
-// 256-row blocks of an earlier form of it had, so that the sizes taken stay the same.)
+// now: the gradient kernels as they are.  Without it, as in the plans for a limited workspace, the blocks and costs that decide
+// the splits are those of the walks with 64 rows (d = 128: 256 rows), so that the sizes taken do not change with the kernels.
 static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent, int route, int max_splits, bool few, double parts_limit,
-                                   bool equal = false) {
+                                   bool equal = false, bool now = false) {
   LossPlan pl{};
   const int kNumCU = num_cu();
   pl.route = route;
@@ -64,8 +64,10 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
       pl.stat_splits = ceil_div(P, pl.stat_cols_per_split);
     }
     // owner rows per workgroup of the gradient kernel for this width
-    const bool wide128 = d == 128 && (!few || parts_limit < 1e299);
-    const int own = d > 128 ? 64 : wide128 ? 256 : 128;
+    const bool wide128 = d == 128 && !now;
+    // calls with few scores have a gradient kernel of their own (see loss_few.hip); limited workspaces do not
+    pl.few_grad = pl.stat_tile && now;
+    const int own = pl.few_grad ? 32 : d > 128 ? 64 : wide128 ? 256 : 128;
     const long long obQ = ceil_div(B, own), obP = ceil_div(P, own);
     // NT-Xent on these kernels is one walk (the score matrix is symmetric: see launch_grad_mfma)
     pl.one_walk = ntxent ? 1 : 0;
@@ -78,7 +80,7 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
     // Measured: 14 us and 0.03 to 0.05 us per row at d = 768; 8 and 0.022 at d = 128; partials about 4 TB/s.
     // (Two workgroups of the d = 128 and d = 256 kernels share a compute unit, each at some 70 % of its speed.)
     const bool two128 = d == 128 && !wide128;
-    const double row_us = wide128 ? 0.031 : two128 ? 0.022 : 0.015 + 0.035 * d / 768.0, fixed_us = two128 ? 8.0 : 14.0;
+    const double row_us = pl.few_grad ? 0.02 + 0.027 * d / 768.0 : wide128 ? 0.031 : two128 ? 0.022 : 0.015 + 0.035 * d / 768.0, fixed_us = pl.few_grad ? 7.0 : two128 ? 8.0 : 14.0;
     const int per_cu = d <= 256 && !wide128 ? 2 : 1;
     auto len_of = [](int n, int ns) { return (ceil_div(n, ns) + 31) / 32 * 32; };
     auto parts_bytes = [&](int nsq, int nsp) { return ((double)nsq * B + (double)nsp * P) * d * 4; };
@@ -119,6 +121,7 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
       search(true, !pl.one_walk, pl.nsq, pl.q_stream_len, pl.nsp, pl.p_stream_len);
     }
     if (pl.one_walk) { pl.nsp = 1; pl.p_stream_len = B; }
+    pl.few_merge = pl.few_grad && !ntxent && pl.p_stream_len <= kFewMergeRows;
     // fused mode (workspace is planned for it wherever it can run; fused_auto says where it is also the faster one):
     // each walk is a launch of its own and has to fill the GPU alone
     // (it pays where the statistics pass it replaces is expensive against the extra partial sums: measured faster
@@ -194,6 +197,7 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
 }
 // what the packed inputs and partials may take without being asked about (the rest of a 288 GB card is the caller's)
 constexpr size_t kPlanesMaxBytes = (size_t)32 << 30;
+static double parts_bytes_of(const LossPlan& pl, int B, int P, int d) { return ((double)pl.nsq * B + (double)pl.nsp * P) * d * 4; }
 // The plan with the first in order of speed whose workspace `fits` takes; if it takes none, the last.
 template <class Fits>
 static LossPlan choose_plan(int B, int P, int d, gc_dtype dt, bool ntxent, Fits fits) {
@@ -201,12 +205,19 @@ static LossPlan choose_plan(int B, int P, int d, gc_dtype dt, bool ntxent, Fits 
     const int own = (d == 128) ? 256 : 64;
     const long long obQ = ceil_div(B, own), obP = ceil_div(P, own), L = equal_share(obQ * P + (ntxent ? 0 : obP * B));
     const double parts = ((double)((P + L - 1) / L) * B + (double)((B + L - 1) / L) * P) * d * 4;   // partials of an equal share
-    auto plan = [&](bool few, double parts_limit, bool equal) {
-      return make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_MFMA, 16, few, parts_limit, equal);
+    auto plan = [&](bool few, double parts_limit, bool equal, bool now = false) {
+      return make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_MFMA, 16, few, parts_limit, equal, now);
     };
-    LossPlan pl = plan(true, 1e300, false);
-    // (which shapes the entry point with the fixed array takes is decided by the plan that parts_limit = 1e298 asks for)
-    pl.over_static = d == 128 ? plan(true, 1e298, false).total > (size_t)GC_STATIC_SCRATCH_BYTES && plan(false, parts, false).total > (size_t)GC_STATIC_SCRATCH_BYTES : 0;
+    LossPlan pl = plan(true, 1e300, false, true);
+    // which shapes the entry point with the fixed array takes is decided by the plans without `now`
+    const size_t fixed = (size_t)GC_STATIC_SCRATCH_BYTES;
+    const bool taken = plan(true, 1e300, false).total <= fixed || plan(false, parts, false).total <= fixed;
+    if (pl.total > fixed && pl.few_grad && taken) {   // fewer splits of the same kernel, if they fit it
+      const double now_parts = parts_bytes_of(pl, B, P, d), room = (double)fixed - ((double)pl.total - now_parts);
+      const LossPlan less = plan(true, room, false, true);
+      if (less.total <= fixed) pl = less;
+    }
+    pl.over_static = !taken;
     if (pl.total > (size_t)GC_STATIC_SCRATCH_BYTES) {
       // the shapes that the entry point with the fixed array takes do not depend on the splits: those that fit with an
       // equal share of the rows per compute unit, at least 256 of them, get splits that fit
@@ -424,7 +435,7 @@ static int run_loss(const LossArgs& a_in, const LossPlan& pl) {
   prof_mark(call, 1, a.stream);
   if (a.both) {
     if (launch_both_merge(a, pl, *a.both) != hipSuccess) return GC_ERR_HIP;
-  } else if (!a.lse2_t) {
+  } else if (!a.lse2_t && !merges_itself(a, pl)) {
     e = launch_stats_merge(a, pl);
     if (e != hipSuccess) return GC_ERR_HIP;
   }

@@ -48,6 +48,7 @@ enum LossRoute {
 struct LossPlan {
   int route;
   int use_mfma;          // route == ROUTE_MFMA
+  int few_grad, few_merge;   // the gradient kernel for short walks (loss_few.hip); it can merge the statistics it needs
   int over_static;       // more than the entry point with the fixed array takes, whatever `total` says
   int one_walk;          // NT-Xent on the MFMA kernels: dz from a single walk (no dP role, no dP partials)
   int stat_splits;       // column (target) ranges of the statistics pass
@@ -72,6 +73,7 @@ struct LossPlan {
 // limit: bytes of workspace there are.  To stay below it the calls of ROUTE_MFMA take fewer splits, those of ROUTE_PLANES
 // fewer splits and then ROUTE_GENERAL; what needs the least is returned where nothing fits (the caller compares `total`).
 constexpr int kStatTile = 32, kStatBlock = 128;
+constexpr int kFewMergeRows = 256;   // streamed rows of a workgroup of the gradient kernel for short walks that merges statistics
 LossPlan make_loss_plan(int B, int P, int d, gc_dtype dt, bool ntxent, size_t limit = (size_t)-1);
 void plan_planes(LossPlan& pl, int B, int P, int d, gc_dtype dt, int max_splits);
 
@@ -148,6 +150,9 @@ struct PosFix {
   int B, P, d;
   float scale;
 };
+
+// The gradient kernel of this call merges the split statistics: one launch less.  (The dQ role writes what the merge would.)
+inline bool merges_itself(const LossArgs& a, const LossPlan& pl) { return pl.few_merge && a.dq && !a.lse2_t && !a.wexp && !a.dz; }
 
 inline void BothPlan::partials(const LossArgs& a, const LossPlan& pl, float*& row_m, float*& row_l, float*& col_m, float*& col_l) const {
   row_m = (float*)(a.ws + pl.off_dq_part);   // (the gradient pass writes there later)

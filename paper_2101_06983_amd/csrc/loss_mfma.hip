@@ -687,7 +687,7 @@ hipError_t launch_grad_mfma(const LossArgs& a, const LossPlan& pl) {
   if (one_walk) { ga.lse2_t = ga.lse2; ga.wexp_t = ga.wexp; ga.out_scale *= 2.f; }
   const bool want_q = a.dq || a.dz, want_p = (a.dp || a.dz) && !one_walk;
   const size_t nq = (size_t)a.B * a.d, np = (size_t)a.P * a.d;
-  const int own = (a.d == 128) ? G1_OWN : GR_OWN;   // owner rows per workgroup
+  const int own = pl.few_grad ? kFewOwn : (a.d == 128) ? G1_OWN : GR_OWN;   // owner rows per workgroup
   ga.obQ = want_q ? (a.B + own - 1) / own : 0; ga.nsq = pl.nsq; ga.q_stream_len = pl.q_stream_len;
   ga.obP = want_p ? (a.P + own - 1) / own : 0; ga.nsp = pl.nsp; ga.p_stream_len = pl.p_stream_len;
   // every output goes through the kernel that sums the split partials (a single split included): it adds the
@@ -701,7 +701,16 @@ hipError_t launch_grad_mfma(const LossArgs& a, const LossPlan& pl) {
   const int nwg = ga.obQ * ga.nsq + ga.obP * ga.nsp;
   if (nwg == 0) { prof_mark_grad_kernel_done(a.stream); return hipSuccess; }
   hipError_t e;
-  switch (a.d) {
+  FewMerge fm{};
+  if (merges_itself(a, pl)) {
+    ga.pos_pad = a.pos_idx;
+    fm.splits = pl.stat_splits;
+    fm.part_m = (const float*)(ws + pl.off_part_m); fm.part_l = (const float*)(ws + pl.off_part_l); fm.part_idx = (const int*)(ws + pl.off_part_idx);
+    fm.pos_t = (const float*)(ws + pl.off_pos); fm.lse2 = (float*)(ws + pl.off_lse2); fm.rowloss = (float*)(ws + pl.off_rowloss);
+    fm.lse_out = a.lse; fm.argmax_out = a.argmax;
+  }
+  if (pl.few_grad) e = grad_few_launch(ga, fm, a.d, nwg, a.stream);
+  else switch (a.d) {
     case 128: e = grad128_launch(ga, nwg, a.stream); break;
     case 256: e = grad_mfma_launch<256>(ga, nwg, a.stream); break;
     case 384: e = grad_mfma_launch<384>(ga, nwg, a.stream); break;

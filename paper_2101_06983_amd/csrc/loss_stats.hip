@@ -375,6 +375,14 @@ __global__ void __launch_bounds__(512, 4) stats_mfma_kernel(StatsArgs g) {
 __global__ void __launch_bounds__(256) stats_small_kernel(StatsSmallArgs g) {
   constexpr int T = kStatTile, PD = 3;
   __shared__ StatTileLds lds;
+  if (g.inv) {
+    const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (i == 0) *g.shared = 0;
+    if (i < g.B) {   // (at least one workgroup of 256 threads per 32 anchors)
+      const int r = g.pos_idx[i];
+      if (r >= 0 && r < g.Pn) g.inv[r] = i;
+    }
+  }
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, ln = lane & 31;
   const int task = xcd_task_id();
   const int a0 = (task % g.n_ablk) * T, split = task / g.n_ablk;
@@ -418,7 +426,8 @@ __global__ void __launch_bounds__(256) stats_small_kernel(StatsSmallArgs g) {
   st.finish(g, lds, split);
 }
 static hipError_t launch_stats_small(const LossArgs& a, const LossPlan& pl) {
-  const StatsSmallArgs g = stats_small_args(a, pl, (const unsigned short*)a.q, (const unsigned short*)a.p);
+  StatsSmallArgs g = stats_small_args(a, pl, (const unsigned short*)a.q, (const unsigned short*)a.p);
+  if (merges_itself(a, pl)) { g.inv = (int32_t*)(a.ws + pl.off_inv); g.shared = (int*)(a.ws + pl.off_err) + 1; }
   stats_small_kernel<<<g.n_ablk * pl.stat_splits, 256, 0, a.stream>>>(g);
   return hipGetLastError();
 }

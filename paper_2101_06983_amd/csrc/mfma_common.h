@@ -106,14 +106,33 @@ struct GradArgs {
 // The kernel that sums the partials adds each positive's own term to its dP row through inv[j] (an anchor with
 // r_i = j).  That is enough when no two anchors share a target; here every workgroup looks at a slice of the anchors
 // and raises *shared when one of them is not the anchor recorded for its target (the sum kernel then scans).
-__device__ __forceinline__ void check_shared_positives(const GradArgs& ga) {
-  if (!ga.inv) return;
-  const int per = (ga.B + (int)gridDim.x - 1) / (int)gridDim.x;
-  const int i0 = (int)blockIdx.x * per, i1 = min(ga.B, i0 + per);
-  for (int i = i0 + (int)threadIdx.x; i < i1; i += (int)blockDim.x) {
-    const int r = ga.pos_pad[i];
-    if (r >= 0 && r < ga.Pn && ga.inv[r] != i) *ga.shared = 1;
+// In three parts, each where the load before it has long arrived: two loads in turn before or behind a kernel's work are 1.5 us.
+struct SharedCheck {
+  int i, i1, r, seen;
+  __device__ __forceinline__ SharedCheck(const GradArgs& ga) : i(0), i1(0), r(-1), seen(0) {
+    if (!ga.inv) return;
+    const int per = (ga.B + (int)gridDim.x - 1) / (int)gridDim.x;
+    i = (int)blockIdx.x * per + (int)threadIdx.x;
+    i1 = min(ga.B, ((int)blockIdx.x + 1) * per);
+    if (i < i1) r = ga.pos_pad[i];
   }
+  __device__ __forceinline__ void look(const GradArgs& ga) {
+    seen = i;
+    if (r >= 0 && r < ga.Pn) seen = ga.inv[r];
+  }
+  __device__ __forceinline__ void finish(const GradArgs& ga) {
+    if (seen != i) *ga.shared = 1;
+    if (i1 - i <= (int)blockDim.x) return;   // (slices longer than the workgroup: the rest of them)
+    for (i += (int)blockDim.x; i < i1; i += (int)blockDim.x) {
+      r = ga.pos_pad[i];
+      if (r >= 0 && r < ga.Pn && ga.inv[r] != i) *ga.shared = 1;
+    }
+  }
+};
+__device__ __forceinline__ void check_shared_positives(const GradArgs& ga) {
+  SharedCheck c(ga);
+  c.look(ga);
+  c.finish(ga);
 }
 
 // max / sum over the four lanes that share lane % 16 (v_permlane16_swap / v_permlane32_swap give every lane both
@@ -239,5 +258,14 @@ hipError_t launch_stats128_both(const StatsArgs& g, bool triangle, int nwg, hipS
 constexpr int G1_OWN = 128;   // owner rows per workgroup of the gradient pass
 hipError_t launch_stats128(const LossArgs& a, const LossPlan& pl);
 hipError_t grad128_launch(const GradArgs& ga, int nwg, hipStream_t stream);
+
+// few scores (loss_few.hip)
+constexpr int kFewOwn = 32;   // owner rows per workgroup
+struct FewMerge {             // the split statistics, and what the merge of them leaves for the launch that follows
+  int splits;                 // 0: already merged
+  const float* part_m; const float* part_l; const int* part_idx; const float* pos_t;
+  float* lse2; float* rowloss; float* lse_out; int32_t* argmax_out;
+};
+hipError_t grad_few_launch(const GradArgs& ga, const FewMerge& fm, int d, int nwg, hipStream_t stream);
 
 }  // namespace gc

@@ -20,6 +20,7 @@ struct StatsSmallArgs {
   int B, Pn, d, n_ablk, tiles, tiles_per_split, mask_self;
   float alpha2;
   float* part_m; float* part_l; int* part_idx; float* pos_t;
+  int32_t* inv; int* shared;   // where no merge follows: an anchor per target, and the word that the gradient kernel may raise
 };
 struct StatTileLds {
   float red[4][kStatTile][kStatTile + 1];                          // partial tiles of the four waves: [target][anchor]
