@@ -33,8 +33,7 @@ struct FewCfg {
 };
 __device__ __forceinline__ int few_swz(int row) { return (((row >> 1) & 1) << 2) | (((row >> 2) & 1) << 1); }
 
-// MERGE: statistics come as splits (few, and the rows that a workgroup needs are few): every workgroup merges its own, and the
-// dQ role's first splits write what the sum kernel and the caller want of them.  Saves a launch of 3.5 us and its gap.
+// MERGE: the statistics come as splits, see StatMerge.
 template <int D, bool OWNER_IS_Q, bool SYM, bool MERGE>
 __device__ __forceinline__ void grad_few_body(const GradArgs& ga, const FewMerge& fm, int oblk, int split, unsigned char* smem) {
   using C = FewCfg<D, MERGE>;
@@ -104,63 +103,8 @@ __device__ __forceinline__ void grad_few_body(const GradArgs& ga, const FewMerge
   float* const lds_lse = (float*)(smem + C::L_OFF);
   int* const lds_pos = (int*)(smem + C::L_OFF) + kFewMergeRows;
   if constexpr (MERGE) {
-    // rows first .. first + n - 1 of the anchors: 256 / n2 threads a row (n2: n rounded up to a power of two from 32), whose
-    // loads are all in flight at once; merged in the order of the splits
-    const int first = OWNER_IS_Q ? a0 : sbeg, n = OWNER_IS_Q ? GF_OWN : send - sbeg;
-    const int lg = n <= 32 ? 5 : n <= 64 ? 6 : n <= 128 ? 7 : 8, grps = 256 >> lg;
-    const int row = threadIdx.x & ((1 << lg) - 1), grp = threadIdx.x >> lg, i = min(first + row, ga.B - 1);
-    const bool want_idx = OWNER_IS_Q && split == 0 && fm.argmax_out;
-    const int pos = ga.pos_pad[i];
-    const float pt = OWNER_IS_Q && split == 0 ? fm.pos_t[i] : 0.f;   // (read whether or not pos is valid: no load behind another)
-    float m = -INFINITY, l = 0.f;
-    int idx = 0x7fffffff;
-    constexpr int FLY = 8;
-    for (int s0 = grp * FLY; s0 < fm.splits; s0 += grps * FLY) {
-      float vm[FLY], vl[FLY];
-      int vi[FLY];
-#pragma unroll
-      for (int k = 0; k < FLY; k++) {
-        const bool live = s0 + k < fm.splits;
-        const size_t o = (size_t)(live ? s0 + k : 0) * ga.B + i;
-        vm[k] = fm.part_m[o]; vl[k] = fm.part_l[o]; vi[k] = want_idx ? fm.part_idx[o] : 0x7fffffff;
-        if (!live) { vm[k] = -INFINITY; vl[k] = 0.f; }
-      }
-      float mn = m;
-#pragma unroll
-      for (int k = 0; k < FLY; k++) mn = fmaxf(mn, vm[k]);
-      const float ms = mn == -INFINITY ? 0.f : mn;
-      l *= fast_exp2(m - ms);
-#pragma unroll
-      for (int k = 0; k < FLY; k++) {
-        l += vl[k] * fast_exp2(vm[k] - ms);
-        if (vm[k] > m || (vm[k] == m && vi[k] < idx)) { m = vm[k]; idx = vi[k]; }
-      }
-    }
-    float* const x = (float*)(smem + C::X_OFF);   // [3][256]: not in use yet
-    x[threadIdx.x] = m; x[256 + threadIdx.x] = l; ((int*)x)[512 + threadIdx.x] = idx;
-    __syncthreads();
-    if (grp == 0) {
-      for (int k = 1; k < grps; k++) {
-        const int o = (k << lg) + row;
-        const float m2 = x[o], l2 = x[256 + o];
-        const int i2 = ((int*)x)[512 + o];
-        const float mn = fmaxf(m, m2), ms = mn == -INFINITY ? 0.f : mn;
-        l = l * fast_exp2(m - ms) + l2 * fast_exp2(m2 - ms);
-        if (m2 > m || (m2 == m && i2 < idx)) idx = i2;
-        m = mn;
-      }
-      const float l2 = m + log2f(l);
-      const bool ok = (unsigned)pos < (unsigned)ga.Pn;
-      lds_lse[row] = l2;
-      lds_pos[row] = pos;
-      if (OWNER_IS_Q && split == 0 && first + row < ga.B) {
-        fm.lse2[i] = l2;
-        fm.rowloss[i] = ok ? (l2 - pt) * kLn2 : NAN;
-        if (fm.lse_out) fm.lse_out[i] = l2 * kLn2;
-        if (fm.argmax_out) fm.argmax_out[i] = idx;
-      }
-    }
-    __syncthreads();
+    StatMerge<false> sm(fm, ga.pos_pad, ga.B, OWNER_IS_Q ? a0 : sbeg, OWNER_IS_Q ? GF_OWN : send - sbeg, OWNER_IS_Q && split == 0);
+    sm.finish(fm, ga.B, ga.Pn, (float*)(smem + C::X_OFF), lds_lse, lds_pos, nullptr);   // (the partial scores are not there yet)
     if (OWNER_IS_Q) lse_a = lds_lse[ln];
   }
 #pragma unroll

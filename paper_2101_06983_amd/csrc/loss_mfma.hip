@@ -704,10 +704,7 @@ hipError_t launch_grad_mfma(const LossArgs& a, const LossPlan& pl) {
   FewMerge fm{};
   if (merges_itself(a, pl)) {
     ga.pos_pad = a.pos_idx;
-    fm.splits = pl.stat_splits;
-    fm.part_m = (const float*)(ws + pl.off_part_m); fm.part_l = (const float*)(ws + pl.off_part_l); fm.part_idx = (const int*)(ws + pl.off_part_idx);
-    fm.pos_t = (const float*)(ws + pl.off_pos); fm.lse2 = (float*)(ws + pl.off_lse2); fm.rowloss = (float*)(ws + pl.off_rowloss);
-    fm.lse_out = a.lse; fm.argmax_out = a.argmax;
+    fm = few_merge_args(a, pl);
   }
   if (pl.few_grad) e = grad_few_launch(ga, fm, a.d, nwg, a.stream);
   else switch (a.d) {

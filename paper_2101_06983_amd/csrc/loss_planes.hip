@@ -410,8 +410,9 @@ struct PlanesGradArgs {
   const float* pos_c;                      // ... the positive's coefficient, with room for 128 rows
   float alpha2, out_scale;
   int mask_self;
+  FewMerge fm; int P;                      // fm.splits > 0: lse2, pos (not padded) and pos_c are formed here, see StatMerge
 };
-constexpr int PG_STEP = 128;
+constexpr int PG_STEP = 128, PG_MERGE_BYTES = 3 * kFewMergeRows * 4;
 constexpr int planes_g_bytes(int NO) { return 4 * 2 * 3 * NO * 1024; }
 
 template <int NP, int NO, int CTW>
@@ -428,18 +429,29 @@ __global__ void __launch_bounds__(256, NO == 1 && CTW <= 4 ? 2 : 1) planes_grad_
   const int ob = id % R.oblk, cs = (id / R.oblk) % g.col_slices, split = id / (R.oblk * g.col_slices);
   const size_t blk = (size_t)g.KS * NP * 512;
   const unsigned short* own = R.own_k + (size_t)ob * NO * blk;
-  planes_stage_own<NP, NO>(own_lds, own, blk, g.ks_lds);
   const int sbeg = split * R.len, send = min(R.n_str, sbeg + R.len);
   const int ct0 = cs * g.ct_per_slice, ct1 = min(g.CT, ct0 + g.ct_per_slice);
+  const bool merge = g.fm.splits > 0;
+  float* const l_lse = (float*)(own_lds + (size_t)g.ks_lds * NO * NP * 512);   // (with merge) of rows from the first owner / streamed row on
+  int* const l_pos = (int*)l_lse + kFewMergeRows;
+  float* const l_c = l_lse + 2 * kFewMergeRows;
+  if (merge) {
+    const int B = ri ? R.n_str : R.n_own;
+    StatMerge<true> sm(g.fm, g.pos, B, ri ? sbeg : ob * NO * 32, ri ? send - sbeg : NO * 32, !ri && split == 0 && cs == 0);
+    planes_stage_own<NP, NO>(own_lds, own, blk, g.ks_lds);
+    sm.finish(g.fm, B, g.P, (float*)gl, l_lse, l_pos, l_c);
+  } else {
+    planes_stage_own<NP, NO>(own_lds, own, blk, g.ks_lds);
+  }
 
   int own_idx[NO], r_o[NO];
   float lse_o[NO], c_o[NO];
 #pragma unroll
   for (int no = 0; no < NO; no++) {
     own_idx[no] = (ob * NO + no) * 32 + ln;
-    lse_o[no] = ri ? 0.f : g.lse2[own_idx[no]];
-    c_o[no] = ri ? 0.f : g.pos_c[own_idx[no]];
-    r_o[no] = ri ? -1 : g.pos[own_idx[no]];
+    lse_o[no] = ri ? 0.f : merge ? l_lse[no * 32 + ln] : g.lse2[own_idx[no]];
+    c_o[no] = ri ? 0.f : merge ? l_c[no * 32 + ln] : g.pos_c[own_idx[no]];
+    r_o[no] = ri ? -1 : merge ? l_pos[no * 32 + ln] : g.pos[own_idx[no]];
   }
   f32x16 acc[NO][CTW];
 #pragma unroll
@@ -474,9 +486,14 @@ __global__ void __launch_bounds__(256, NO == 1 && CTW <= 4 ? 2 : 1) planes_grad_
     if (ri) {
 #pragma unroll
       for (int q = 0; q < 4; q++) {
-        const f32x4 a = *(const f32x4*)(g.lse2 + j0 + 8 * q);
-        const i32x4 b = *(const i32x4*)(g.pos + j0 + 8 * q);
-        const f32x4 c = *(const f32x4*)(g.pos_c + j0 + 8 * q);
+        f32x4 a, c;
+        i32x4 b;
+        if (merge) {
+          const int o = j0 - sbeg + 8 * q;
+          a = *(const f32x4*)(l_lse + o); b = *(const i32x4*)(l_pos + o); c = *(const f32x4*)(l_c + o);
+        } else {
+          a = *(const f32x4*)(g.lse2 + j0 + 8 * q); b = *(const i32x4*)(g.pos + j0 + 8 * q); c = *(const f32x4*)(g.pos_c + j0 + 8 * q);
+        }
 #pragma unroll
         for (int e = 0; e < 4; e++) { lse_s[4 * q + e] = a[e]; pos_s[4 * q + e] = b[e]; c_s[4 * q + e] = c[e]; }
       }
@@ -596,6 +613,7 @@ void plan_planes(LossPlan& pl, int B, int P, int d, gc_dtype dt, int max_splits)
   };
   split_of(stQ, P, pl.nsq, pl.q_stream_len);
   split_of(stP, B, pl.nsp, pl.p_stream_len);
+  pl.few_merge = pl.stat_tile && pl.p_stream_len <= kFewMergeRows;
 }
 
 template <typename T>
@@ -646,11 +664,12 @@ hipError_t launch_stats_planes(const LossArgs& a, const LossPlan& pl) {
 
 template <int NP, int NO, int CTW>
 static hipError_t grad_launch(PlanesGradArgs& g, int nwg, hipStream_t s) {
-  const int budget = ((nwg <= num_cu() || NO == 2 || CTW > 4) ? 156 : 78) * 1024 - planes_g_bytes(NO);
+  const int merge = g.fm.splits ? PG_MERGE_BYTES : 0;
+  const int budget = ((nwg <= num_cu() || NO == 2 || CTW > 4) ? 156 : 78) * 1024 - planes_g_bytes(NO) - merge;
   g.ks_lds = ks_in_lds(budget / (NO * NP * 1024), g.KS, planes_pd(NP));
   static bool done[64];
   if (hipError_t e = ensure_dyn_lds((const void*)planes_grad_kernel<NP, NO, CTW>, 160 * 1024, done); e != hipSuccess) return e;
-  planes_grad_kernel<NP, NO, CTW><<<nwg, 256, planes_g_bytes(NO) + g.ks_lds * NO * NP * 1024, s>>>(g);
+  planes_grad_kernel<NP, NO, CTW><<<nwg, 256, planes_g_bytes(NO) + g.ks_lds * NO * NP * 1024 + merge, s>>>(g);
   return hipGetLastError();
 }
 template <int NP, int NO>
@@ -671,6 +690,7 @@ hipError_t launch_grad_planes(const LossArgs& a, const LossPlan& pl) {
   g.lse2 = (const float*)(ws + pl.off_lse2); g.pos = (const int32_t*)(ws + pl.off_pos_pad); g.pos_c = (const float*)(ws + pl.off_pos);
   g.alpha2 = a.alpha * kLog2e; g.out_scale = a.alpha / (float)a.B * (a.grad_mul != 0.f ? a.grad_mul : 1.f);
   g.mask_self = (a.flags & GC_MASK_SELF) ? 1 : 0;
+  if (merges_itself(a, pl)) { g.fm = few_merge_args(a, pl); g.pos = a.pos_idx; g.P = a.P; }
   const bool want_q = a.dq || a.dz, want_p = a.dp || a.dz;
   const int own = 32 * pl.px_no;
   // a single split writes the result itself, several (and the two halves of dz) leave partials

@@ -11,6 +11,7 @@
 #include <type_traits>
 
 #include "gc_common.h"
+#include "stats_tile.h"
 
 namespace gc {
 
@@ -261,11 +262,6 @@ hipError_t grad128_launch(const GradArgs& ga, int nwg, hipStream_t stream);
 
 // few scores (loss_few.hip)
 constexpr int kFewOwn = 32;   // owner rows per workgroup
-struct FewMerge {             // the split statistics, and what the merge of them leaves for the launch that follows
-  int splits;                 // 0: already merged
-  const float* part_m; const float* part_l; const int* part_idx; const float* pos_t;
-  float* lse2; float* rowloss; float* lse_out; int32_t* argmax_out;
-};
 hipError_t grad_few_launch(const GradArgs& ga, const FewMerge& fm, int d, int nwg, hipStream_t stream);
 
 }  // namespace gc

@@ -79,6 +79,95 @@ struct StatTile {
     }
   }
 };
+// The gradient kernels for few scores merge the split statistics of the rows they need (merges_itself): one launch of 3.5 us
+// and its gap less.  The workgroups that own a block of anchors with `write` leave what the merge kernel would.
+struct FewMerge {
+  int splits;                 // 0: already merged
+  const float* part_m; const float* part_l; const int* part_idx; const float* pos_t;
+  float* lse2; float* rowloss; float* lse_out; int32_t* argmax_out;
+};
+// Anchors first .. first + n - 1 (n <= kFewMergeRows) by a workgroup of 256: 256 / n2 threads a row (n2: n rounded up to a power
+// of two from 32), eight splits' loads in flight each.  The constructor issues the first loads; what the caller loads between
+// it and finish() is in flight beside them.
+template <bool EXACT>
+struct StatMerge {
+  static constexpr int FLY = 8;
+  static __device__ __forceinline__ float ex(float v) { return EXACT ? exp2f(v) : fast_exp2(v); }
+  int lg, grps, row, grp, i, r;
+  bool live, write;
+  float pt, vm[FLY], vl[FLY];
+  int vi[FLY];
+  __device__ __forceinline__ void load(const FewMerge& fm, int B, int s0) {
+    const bool want_idx = write && fm.argmax_out;
+#pragma unroll
+    for (int k = 0; k < FLY; k++) {
+      const bool in = s0 + k < fm.splits;
+      const size_t o = (size_t)(in ? s0 + k : 0) * B + i;
+      vm[k] = fm.part_m[o]; vl[k] = fm.part_l[o]; vi[k] = want_idx ? fm.part_idx[o] : 0x7fffffff;
+      if (!in) { vm[k] = -INFINITY; vl[k] = 0.f; }
+    }
+  }
+  __device__ __forceinline__ StatMerge(const FewMerge& fm, const int32_t* pos_idx, int B, int first, int n, bool write_) : write(write_) {
+    lg = n <= 32 ? 5 : n <= 64 ? 6 : n <= 128 ? 7 : 8;
+    grps = 256 >> lg; row = threadIdx.x & ((1 << lg) - 1); grp = threadIdx.x >> lg;
+    i = min(first + row, B - 1); live = first + row < B;
+    r = pos_idx[i];
+    pt = fm.pos_t[i];   // (whether or not r is valid: no load behind another)
+    load(fm, B, grp * FLY);
+  }
+  // x: 768 floats of LDS; lse, pos and, unless null, coeff (2^(t - lse2) - 1 of the positive) take rows 0 .. n2 - 1; rows past
+  // the last anchor get +inf / -1 / 0.  Ends with a barrier.
+  __device__ __forceinline__ void finish(const FewMerge& fm, int B, int Pn, float* x, float* lse, int* pos, float* coeff) {
+    float m = -INFINITY, l = 0.f;
+    int idx = 0x7fffffff;
+    for (int s0 = grp * FLY; s0 < fm.splits; s0 += grps * FLY) {
+      if (s0 != grp * FLY) load(fm, B, s0);
+      float mn = m;
+#pragma unroll
+      for (int k = 0; k < FLY; k++) mn = fmaxf(mn, vm[k]);
+      const float ms = mn == -INFINITY ? 0.f : mn;
+      l *= ex(m - ms);
+#pragma unroll
+      for (int k = 0; k < FLY; k++) {
+        l += vl[k] * ex(vm[k] - ms);
+        if (vm[k] > m || (vm[k] == m && vi[k] < idx)) { m = vm[k]; idx = vi[k]; }
+      }
+    }
+    x[threadIdx.x] = m; x[256 + threadIdx.x] = l; ((int*)x)[512 + threadIdx.x] = idx;
+    __syncthreads();
+    if (grp == 0) {
+      for (int k = 1; k < grps; k++) {
+        const int o = (k << lg) + row;
+        const float m2 = x[o], l2 = x[256 + o];
+        const int i2 = ((int*)x)[512 + o];
+        const float mn = fmaxf(m, m2), ms = mn == -INFINITY ? 0.f : mn;
+        l = l * ex(m - ms) + l2 * ex(m2 - ms);
+        if (m2 > m || (m2 == m && i2 < idx)) idx = i2;
+        m = mn;
+      }
+      const bool ok = r >= 0 && r < Pn;
+      const float l2 = m + log2f(l);
+      lse[row] = live ? l2 : INFINITY;
+      pos[row] = live ? r : -1;
+      if (coeff) coeff[row] = live && ok ? exp2f(pt - l2) - 1.f : 0.f;
+      if (write && live) {
+        fm.lse2[i] = l2;
+        fm.rowloss[i] = ok ? (l2 - pt) * kLn2 : NAN;
+        if (fm.lse_out) fm.lse_out[i] = l2 * kLn2;
+        if (fm.argmax_out) fm.argmax_out[i] = idx;
+      }
+    }
+    __syncthreads();
+  }
+};
+inline FewMerge few_merge_args(const LossArgs& a, const LossPlan& pl) {
+  FewMerge fm{};
+  fm.splits = pl.stat_splits;
+  fm.part_m = (const float*)(a.ws + pl.off_part_m); fm.part_l = (const float*)(a.ws + pl.off_part_l); fm.part_idx = (const int*)(a.ws + pl.off_part_idx);
+  fm.pos_t = (const float*)(a.ws + pl.off_pos); fm.lse2 = (float*)(a.ws + pl.off_lse2); fm.rowloss = (float*)(a.ws + pl.off_rowloss);
+  fm.lse_out = a.lse; fm.argmax_out = a.argmax;
+  return fm;
+}
 inline StatsSmallArgs stats_small_args(const LossArgs& a, const LossPlan& pl, const unsigned short* q, const unsigned short* p) {
   StatsSmallArgs g{};
   g.Q = q; g.P = p; g.pos_idx = a.pos_idx;
