@@ -1,0 +1,120 @@
+"""GPU parity of the one-pass statistics of the symmetric forms (rows and columns of a score matrix together), of the
+coefficients with one exponential, and of the kernels for few scores, at the edges of their tiles and rules, against the
+fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import gc_oracle as O
+from paper_2101_06983_amd import binding as gc
+from paper_2101_06983_amd import synth
+from parity import TOL_BF16, TOL_F32, check, check_argmax, check_loss, oracle_loss, relerr, to_np
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def sym_problem(n, d, seed, mix=0.5):
+    r = torch.from_numpy(np.random.default_rng(seed).permutation(n).astype(np.int32))
+    q, p, _ = synth.dpr_batch(n, n, d, seed=seed, positive_mix=mix, pos_idx=r)
+    return q, p, r
+
+
+# the first size beyond the small tiles, one below / at / above a block of 128 (d = 128: 256) rows, several ranges per block
+# grow: factor on the rows.  12: |log-sum-exp| beyond what one exponential takes (kWideLse) and sums beyond what a tile's fast
+# path takes; "one": a single such row.
+@pytest.mark.parametrize("n,d,temp,grow", [(1025, 128, 0.3, 1), (1281, 128, 0.3, 12), (1535, 256, 0.3, 1), (1409, 256, 0.3, "one"),
+                                           (1153, 768, 1.0, 1), (1100, 384, 0.3, 12)])
+def test_symmetric_loss_one_pass(n, d, temp, grow):
+    q, p, r = sym_problem(n, d, 9100 + n, 0.5 if grow == 1 else 0.0)
+    if grow == "one":
+        q[7] *= 200
+    else:
+        q = q * grow
+        p = p * (grow if grow == 1 else 2 * grow)
+    want = O.bidirectional(synth.widen(q), synth.widen(p), r.numpy(), 1.0, temp)
+    out = gc.gc_bidirectional_loss_and_rep_grad_bf16(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, temp)
+    torch.cuda.synchronize()
+    check_loss("one pass loss", out["loss"].item(), want["loss"], 1e-5)
+    for k in ("dq", "dp"):
+        check("one pass n=%d d=%d %s" % (n, d, k), relerr(to_np(out[k]), want[k]), TOL_BF16)
+
+
+@pytest.mark.parametrize("n,d,tau,grow", [(1026, 128, 0.07, 1), (1790, 128, 0.3, 1), (1280, 128, 0.3, 9), (2562, 128, 0.07, 1),
+                                          (1026, 256, 0.1, 1), (1410, 512, 0.3, 12), (1150, 768, 0.07, 1)])
+def test_ntxent_over_the_triangle(n, d, tau, grow):
+    z = synth.ntxent_views(n, d, seed=9300 + n) * grow
+    want = O.ntxent(synth.widen(z), tau)
+    loss, dz = gc.gc_ntxent_loss_and_grad_bf16(z.to(DEV), tau)
+    torch.cuda.synchronize()
+    check_loss("triangle loss", loss.item(), want["loss"], 1e-5)
+    check("triangle n=%d d=%d dz" % (n, d), relerr(to_np(dz), want["dz"]), TOL_BF16)
+
+
+def test_loss_of_a_converged_softmax():
+    """Rows whose positive outweighs everything: the loss is log(1 + x), x the others' sum over the positive's term.  x is off
+    by ln 2 times the rounding of two logits of size 150 to fp32 (2^-24 * 150 each), 1.3e-5 of it; the bound is 1e-4."""
+    n, d = 1100, 128
+    q, p, r = sym_problem(n, d, 9500)
+    want = O.bidirectional(synth.widen(q), synth.widen(p), r.numpy(), 1.0, 0.01)
+    assert 0 < want["loss"] < 1e-3
+    out = gc.gc_bidirectional_loss_and_rep_grad_bf16(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.01)
+    torch.cuda.synchronize()
+    check_loss("converged loss", out["loss"].item(), want["loss"], 1e-4)
+
+
+@pytest.mark.parametrize("bad", ["twice", "outside"])
+def test_a_pairing_that_is_no_bijection_one_pass(bad):
+    n, d = 1200, 128
+    q, p, r = sym_problem(n, d, 9600)
+    r[5] = r[6] if bad == "twice" else n
+    ws = gc.alloc_workspace(gc.load().gc_bidirectional_workspace_bytes(n, d), DEV)
+    ws.view(torch.uint8).fill_(1)   # whatever the workspace held
+    out = gc.gc_bidirectional_loss_and_rep_grad_bf16(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 1.0, ws)
+    torch.cuda.synchronize()
+    assert np.isnan(out["loss"].item()) and gc.gc_check_async_error(ws) == gc.GC_ERR_POS_IDX
+
+
+# (B, P): one row and tile of each role, remainders, several splits; a dP walk longer than the rows a workgroup merges
+# statistics for (8200 anchors); more than 8 splits of the statistics per thread
+@pytest.mark.parametrize("B,P,d", [(1, 7, 768), (31, 33, 128), (33, 64, 256), (129, 257, 640), (512, 1024, 768), (260, 1500, 384),
+                                   (8200, 96, 128), (40, 2100, 512)])
+def test_few_scores(B, P, d):
+    q, p, r = synth.dpr_batch(B, P, d, seed=9700 + B + P)
+    want = oracle_loss(q, p, r, 1.0, 0.3)
+    dev = (q.to(DEV), p.to(DEV), r.to(DEV))
+    out = gc.gc_loss_and_rep_grad_ex(*dev, 1.0, 0.3)
+    alone = {k: gc.gc_loss_and_rep_grad_ex(*dev, 1.0, 0.3, 0, ("loss", k)) for k in ("dq", "dp")}
+    torch.cuda.synchronize()
+    check_loss("few loss", out["loss"].item(), want["loss"], TOL_F32)
+    check("few lse", relerr(to_np(out["lse"]), want["lse"]), TOL_F32)
+    check_argmax(to_np(out["argmax"]), want, synth.widen(q), synth.widen(p), 1.0 / 0.3, 1e-5)
+    for k in ("dq", "dp"):
+        check("few %dx%dx%d %s" % (B, P, d, k), relerr(to_np(out[k]), want[k]), TOL_BF16)
+        assert relerr(to_np(alone[k][k]), to_np(out[k])) <= 1e-5 and alone[k]["loss"].item() == pytest.approx(out["loss"].item(), rel=1e-6)
+
+
+# more anchors than one round of the sum kernel looks at: exactly one, one more, several rounds with few and many named rows
+@pytest.mark.parametrize("B,P,d,named", [(1024, 40, 128, 40), (1025, 40, 256, 1), (2100, 300, 384, 300), (2600, 500, 128, 3)])
+def test_targets_shared_by_more_anchors_than_a_round(B, P, d, named):
+    q, p, _ = synth.dpr_batch(B, P, d, seed=9800 + B)
+    r = torch.from_numpy(np.random.default_rng(B).integers(0, named, size=B).astype(np.int32))
+    want = oracle_loss(q, p, r, 1.0, 0.3)
+    out = gc.gc_loss_and_rep_grad_ex(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.3)
+    torch.cuda.synchronize()
+    for k in ("dq", "dp"):
+        check("shared %dx%dx%d %s" % (B, P, d, k), relerr(to_np(out[k]), want[k]), TOL_BF16)
+
+
+@pytest.mark.parametrize("B,P,d,f32", [(33, 129, 100, True), (300, 70, 768, True), (257, 600, 200, False), (100, 2000, 1000, False)])
+def test_few_scores_of_any_width(B, P, d, f32):
+    q, p, r = synth.dpr_batch(B, P, d, seed=9900 + B)
+    if f32:
+        q, p = q.float() * 1.001, p.float() * 0.999
+    want = oracle_loss(q, p, r, 1.0, 0.3)
+    out = gc.gc_loss_and_rep_grad_ex(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.3)
+    torch.cuda.synchronize()
+    check_loss("any width loss", out["loss"].item(), want["loss"], TOL_F32)
+    check_argmax(to_np(out["argmax"]), want, synth.widen(q), synth.widen(p), 1.0 / 0.3, 1e-5)
+    for k in ("dq", "dp", "lse"):
+        check("any width %s" % k, relerr(to_np(out[k]), want[k]), TOL_F32)
