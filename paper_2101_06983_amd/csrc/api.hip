@@ -77,7 +77,8 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
     // per compute unit can give a few workgroups more than there are CUs, and with them a second round (258 workgroups
     // at 1021 x 4099 x 384: 46 us, 29 with 242), and few scores leave the CUs idle (6 workgroups at 128 x 256 x 768: 21 us,
     // 15.6 with 32).
-    // Measured: 14 us and 0.03 to 0.05 us per row at d = 768; 8 and 0.022 at d = 128; partials about 4 TB/s.
+    // Measured: 14 us and 0.03 to 0.05 us per row at d = 768; 8 and 0.022 at d = 128; the kernel for few scores 7 and 0.02 to
+    // 0.047; partials about 4 TB/s.
     // (Two workgroups of the d = 128 and d = 256 kernels share a compute unit, each at some 70 % of its speed.)
     const bool two128 = d == 128 && !wide128;
     const double row_us = pl.few_grad ? 0.02 + 0.027 * d / 768.0 : wide128 ? 0.031 : two128 ? 0.022 : 0.015 + 0.035 * d / 768.0, fixed_us = pl.few_grad ? 7.0 : two128 ? 8.0 : 14.0;

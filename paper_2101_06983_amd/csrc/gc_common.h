@@ -130,6 +130,7 @@ struct LossArgs {
 // The coefficient of the symmetric forms is 1/2 (2^(t - lse2_i) + 2^(t - lse2_j)) = 2^t (w_i + w_j), w = 2^(-lse2 - 1): one
 // exponential a score instead of two, a quarter of the rate each.  With |lse2| up to kWideLse no factor overflows, and
 // what 2^t flushes is below 2^(-126 + kWideLse) of its row's sum.  Beyond (one row is enough) the two exponentials stay.
+// (d = 128, 16384 views, before that kernel had two waves per SIMD: 233 us with two, 216 with one.)
 constexpr float kWideLse = 60.f;
 
 // The positive's own term of Eq. 5 / Eq. 6, (p_{i r_i} - 1) g(t_{r_i}) resp. (p_{i r_i} - 1) f(s_i), is not part of the bf16

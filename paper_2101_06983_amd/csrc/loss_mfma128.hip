@@ -18,8 +18,10 @@ namespace gc {
 //            streamed rows in the same k order) come from two transposing LDS reads each.
 // The contraction order over the streamed rows is thus a permutation that both operands of phase 2 share.
 // At most 256 registers a lane, so two workgroups share a CU and one wave's arithmetic runs beside the other's MFMAs.
-// Per 32 x 32 scores a wave needs 528 cycles of MFMA, 480 of vector arithmetic (one exponential a score), 16 KB of LDS reads
-// (128 cycles of the CU's pipe): with eight waves the three are equal.
+// Per 32 x 32 scores a wave needs 528 cycles of MFMA, 400 of vector arithmetic (one exponential a score), 16 KB of LDS reads
+// (128 cycles of the CU's pipe).  16384 views, one walk with one exponential: 138 us, 137 GFLOP = 1.0 PFLOP/s, matrix pipe 49 %
+// and vector issue 43 % busy (64 rows a wave, one wave of 512 registers per SIMD: 216, and 233 with two exponentials).  The order
+// of MFMAs and arithmetic, wave priorities and scheduling fences move that by less than 1 %.
 // ===========================================================================
 constexpr int G1_W = 32, G1_T = 64, G1_STAGES = 4;
 constexpr int G1_STAT = 512;                      // a stage starts with lse2[64], then pos_idx[64] of the streamed rows
@@ -299,7 +301,7 @@ __global__ void __launch_bounds__(256, 2) grad128_kernel(GradArgs ga) {
 // Statistics pass for d = 128 (Eq. 4's normaliser, the positive's logit and the arg-max, per anchor and split).
 // The layout of the d = 128 gradient pass without its second contraction: a workgroup (4 waves) owns 256 anchors,
 // each wave 64 of them with all 128 columns in registers, and all four share the streamed target tiles (32 rows)
-// through the same LDS ring.  Lane (n, h) holds, for its two anchors 32 i + n, the scores of 16 of a tile's 32
+// through an LDS ring of eight stages.  Lane (n, h) holds, for its two anchors 32 i + n, the scores of 16 of a tile's 32
 // targets; the other 16 are in lane (n, h ^ 1).  The running (max, sum, arg-max) of an anchor therefore lives in
 // a lane of its own and no lane talks to another before the end of the stream: 16 MFMAs against about 5 vector
 // operations per score, which a second workgroup on the same CU runs behind the first one's MFMAs.
@@ -472,7 +474,7 @@ __global__ void __launch_bounds__(256, 2) stats128_kernel(const unsigned short* 
 //   score counts for its row and its column.
 //   otherwise (symmetric loss): owners are anchors, streamed rows are targets, each score counts for both.
 // Column sums: 32 lanes hold a column's 32 owners, twice; 54 operations per 32 x 64 tile bring them together
-// (reduce16_lanes32), the four waves' sums meet in LDS one tile later.
+// (reduce16_lanes32), the four waves' sums meet in LDS one tile later.  16384 views: 72 us (all scores for the rows alone: 105).
 // ===========================================================================
 template <bool TRI>
 __global__ void __launch_bounds__(256, 2) stats128_both_kernel(StatsArgs g) {
@@ -564,7 +566,7 @@ __global__ void __launch_bounds__(256, 2) stats128_both_kernel(StatsArgs g) {
     const int later = min(nt - 1, u + S1_AHEAD - 1) - u;
     if (later >= 5) wait_vmem<10>(); else if (later == 4) wait_vmem<8>(); else if (later == 3) wait_vmem<6>();
     else if (later == 2) wait_vmem<4>(); else if (later == 1) wait_vmem<2>(); else wait_vmem<0>();
-    __syncthreads();  // everybody's part has landed; everybody is past tile u-1, so the stage of tile u-2 is free
+    lds_barrier();  // everybody's part has landed, and the column sums of tile u-1 too; everybody is past tile u-1, so the stage of tile u-2 is free
     if (u + S1_AHEAD < nt) prefetch(u + S1_AHEAD);
     flush_cols(u);
     const unsigned char* st = s1mem + (u & (S1_STAGES - 1)) * S1_STAGE;

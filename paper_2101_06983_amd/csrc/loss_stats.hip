@@ -124,7 +124,7 @@ __global__ void __launch_bounds__(512, 4) stats_mfma_kernel(StatsArgs g) {
     // nothing is in flight and every reader is past the last barrier: both stages are free
     prefetch(row0, 0, st & 1);
     wait_vmem<0>();
-    __syncthreads();
+    lds_barrier();
     bf16x8 af[2][MT], bfg[2][NT];
     for (int kc = 0; kc < nk; kc++, st++) {
       if (kc + 1 < nk) prefetch(row0, kc + 1, (st + 1) & 1);
@@ -146,7 +146,7 @@ __global__ void __launch_bounds__(512, 4) stats_mfma_kernel(StatsArgs g) {
           for (int nt = 0; nt < NT; nt++) acc[mt][nt] = mfma32(af[ks & 1][mt], bfg[ks & 1][nt], acc[mt][nt]);
       }
       wait_vmem<0>();   // this wave's part of the next stage has landed
-      __syncthreads();  // ... and everybody's; nobody still reads the stage that is overwritten next
+      lds_barrier();  // ... and everybody's; nobody still reads the stage that is overwritten next
     }
 
     // ---- tile epilogue: online softmax statistics, all in registers; acc holds the raw dot products, the
@@ -250,7 +250,7 @@ __global__ void __launch_bounds__(512, 4) stats_mfma_kernel(StatsArgs g) {
         }
       }
       if (cols) {   // the four waves' sums of a column, in wave order (the next tile writes them behind many barriers)
-        __syncthreads();
+        lds_barrier();
         if (tid < ST_TM && b0 + tid < cend) {
           f32x2 x[4];
           float m = -INFINITY, l = 0.f;
@@ -366,11 +366,11 @@ __global__ void __launch_bounds__(512, 4) stats_mfma_kernel(StatsArgs g) {
 // ===========================================================================
 // Statistics pass for few scores: 32 x 32 tiles, the contraction split over the four waves of a workgroup in 64-wide
 // chunks, every operand loaded straight into registers (lane (n, h) takes elements 32 h .. 32 h + 31 of a chunk of its
-// row, so that two lanes use a whole 128-byte line; any order of k works if both operands share it).  The kernel above
-// has 256 x 256 tiles: 23 us for the one workgroup of 128 x 256 scores and 26 us for the eight of 512 x 1024 at d = 768,
-// all latency of twelve dependent k-chunks.  Here a wave has all its loads in flight at once: 6.6 and 9.7 us.  It costs
-// B P d / 8 bytes of L2 traffic, so the larger tiles win again from about 2^20 scores (a version with 64 x 64 tiles took
-// 37 us at 1021 x 4099 x 384, the 256 x 256 kernel 23).
+// row, so that two lanes use a whole 128-byte line; any order of k works if both operands share it).  Tiles staged through
+// LDS are all latency of dependent k-chunks at these sizes (twelve at d = 768: 23 us at 128 x 256, 26 at 512 x 1024 with
+// 256 x 256 tiles).  Here a wave has all its loads in flight at once: 6.6 and 9.7 us.  It costs B P d / 8 bytes of L2
+// traffic, so the larger tiles win again from about 2^20 scores (64 x 64 tiles in this manner took 37 us at
+// 1021 x 4099 x 384, staged ones of 256 x 256 took 23).
 // ===========================================================================
 __global__ void __launch_bounds__(256) stats_small_kernel(StatsSmallArgs g) {
   constexpr int T = kStatTile, PD = 3;

@@ -80,6 +80,13 @@ __device__ __forceinline__ void dma_piece_pinned(const void* gbase, unsigned vof
 }
 template <int N>
 __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+// __syncthreads() that also waits for this wave's LDS writes by itself.  In loops that write LDS at their end (under a condition)
+// and start with a barrier the compiler drops that wait from the barrier: it sees no write pending where the loop is entered.
+// A wave behind the barrier has then read a slot before its write, once in some hundred passes over 16384 views.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __syncthreads();
+}
 
 struct GradArgs {
   const unsigned short* Q;

@@ -118,3 +118,18 @@ def test_few_scores_of_any_width(B, P, d, f32):
     check_argmax(to_np(out["argmax"]), want, synth.widen(q), synth.widen(p), 1.0 / 0.3, 1e-5)
     for k in ("dq", "dp", "lse"):
         check("any width %s" % k, relerr(to_np(out[k]), want[k]), TOL_F32)
+
+
+# the tiles' column sums pass through LDS from one wave to another: any order of the waves has to give the same bits
+@pytest.mark.parametrize("entry,n,d,runs", [("ntxent", 16384, 128, 400), ("ntxent", 4096, 256, 200), ("symmetric", 8192, 128, 200),
+                                            ("symmetric", 2048, 768, 200)])
+def test_the_same_bits_run_after_run(entry, n, d, runs):
+    if entry == "ntxent":
+        z = synth.ntxent_views(n, d, seed=9500 + d).to(DEV)
+        call = lambda: gc.gc_ntxent_loss_and_grad_bf16(z, 0.07)
+    else:
+        q, p, r = (t.to(DEV) for t in sym_problem(n, d, 9500 + n))
+        call = lambda: [v for v in gc.gc_bidirectional_loss_and_rep_grad_bf16(q, p, r, 1.0, 0.3).values() if torch.is_tensor(v)]
+    first = [t.clone() for t in call()]
+    for _ in range(runs):
+        assert all(torch.equal(a, b) for a, b in zip(call(), first))
