@@ -199,26 +199,35 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
 // what the packed inputs and partials may take without being asked about (the rest of a 288 GB card is the caller's)
 constexpr size_t kPlanesMaxBytes = (size_t)32 << 30;
 static double parts_bytes_of(const LossPlan& pl, int B, int P, int d) { return ((double)pl.nsq * B + (double)pl.nsp * P) * d * 4; }
+// partials of an equal share of the rows per compute unit
+static double equal_parts(int B, int P, int d, bool ntxent) {
+  const int own = (d == 128) ? 256 : 64;
+  const long long obQ = ceil_div(B, own), obP = ceil_div(P, own), L = equal_share(obQ * P + (ntxent ? 0 : obP * B));
+  return ((double)((P + L - 1) / L) * B + (double)((B + L - 1) / L) * P) * d * 4;
+}
+// Which bf16 shapes of the MFMA route the entry point with the fixed array takes is decided by the plans without `now`, so that
+// it does not change with the kernels.  (Two searches over the splits, some 4 us of host time each:
+// the other entry points do not ask, unless a plan of theirs has to be made to fit.)
+static bool static_takes(int B, int P, int d) {
+  auto total = [&](bool few, double limit) { return make_loss_plan_for(B, P, d, GC_BF16, false, ROUTE_MFMA, 16, few, limit, false).total; };
+  const size_t fixed = (size_t)GC_STATIC_SCRATCH_BYTES;
+  return total(true, 1e300) <= fixed || total(false, equal_parts(B, P, d, false)) <= fixed;
+}
 // The plan with the first in order of speed whose workspace `fits` takes; if it takes none, the last.
 template <class Fits>
 static LossPlan choose_plan(int B, int P, int d, gc_dtype dt, bool ntxent, Fits fits) {
   if (dt == GC_BF16 && d % 128 == 0 && d >= 128 && d <= 768) {
-    const int own = (d == 128) ? 256 : 64;
-    const long long obQ = ceil_div(B, own), obP = ceil_div(P, own), L = equal_share(obQ * P + (ntxent ? 0 : obP * B));
-    const double parts = ((double)((P + L - 1) / L) * B + (double)((B + L - 1) / L) * P) * d * 4;   // partials of an equal share
+    const double parts = equal_parts(B, P, d, ntxent);
     auto plan = [&](bool few, double parts_limit, bool equal, bool now = false) {
       return make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_MFMA, 16, few, parts_limit, equal, now);
     };
     LossPlan pl = plan(true, 1e300, false, true);
-    // which shapes the entry point with the fixed array takes is decided by the plans without `now`
     const size_t fixed = (size_t)GC_STATIC_SCRATCH_BYTES;
-    const bool taken = plan(true, 1e300, false).total <= fixed || plan(false, parts, false).total <= fixed;
-    if (pl.total > fixed && pl.few_grad && taken) {   // fewer splits of the same kernel, if they fit it
+    if (pl.total > fixed && pl.few_grad && static_takes(B, P, d)) {   // fewer splits of the same kernel, if they fit it
       const double now_parts = parts_bytes_of(pl, B, P, d), room = (double)fixed - ((double)pl.total - now_parts);
       const LossPlan less = plan(true, room, false, true);
       if (less.total <= fixed) pl = less;
     }
-    pl.over_static = !taken;
     if (pl.total > (size_t)GC_STATIC_SCRATCH_BYTES) {
       // the shapes that the entry point with the fixed array takes do not depend on the splits: those that fit with an
       // equal share of the rows per compute unit, at least 256 of them, get splits that fit
@@ -568,7 +577,13 @@ int gc_loss_and_rep_grad_bf16_static(const void* q, const void* p, const int32_t
   if (!loss || !dq || !dp) return GC_ERR_NULL;
   LossPlan pl = make_loss_plan(B, P, d, GC_BF16, false);
   if (!pl.use_mfma) pl = make_loss_plan(B, P, d, GC_BF16, false, (size_t)GC_STATIC_SCRATCH_BYTES);
-  if (pl.total > (size_t)GC_STATIC_SCRATCH_BYTES || pl.over_static) return GC_ERR_TOO_LARGE;
+  if (pl.total > (size_t)GC_STATIC_SCRATCH_BYTES) return GC_ERR_TOO_LARGE;
+  if (pl.use_mfma) {
+    struct Kept { int B, P, d; bool takes; };   // (the thread's last shape, as the plan's)
+    static thread_local Kept kept{};
+    if (kept.B != B || kept.P != P || kept.d != d) kept = Kept{B, P, d, static_takes(B, P, d)};
+    if (!kept.takes) return GC_ERR_TOO_LARGE;
+  }
   void* ws = nullptr;
   rc = static_scratch(&ws);
   if (rc != GC_OK) return rc;

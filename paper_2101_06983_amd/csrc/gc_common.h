@@ -49,7 +49,6 @@ struct LossPlan {
   int route;
   int use_mfma;          // route == ROUTE_MFMA
   int few_grad, few_merge;   // the gradient kernel for short walks (loss_few.hip); it can merge the statistics it needs
-  int over_static;       // more than the entry point with the fixed array takes, whatever `total` says
   int one_walk;          // NT-Xent on the MFMA kernels: dz from a single walk (no dP role, no dP partials)
   int stat_splits;       // column (target) ranges of the statistics pass
   int stat_cols_per_split;
