@@ -254,6 +254,8 @@ hipError_t launch_both_merge(const LossArgs& a, const LossPlan& pl, const BothPl
   }
   g.pos_pad = (int32_t*)(a.ws + pl.off_pos_pad); g.wide = a.wide; g.shared = (int*)(a.ws + pl.off_err) + 1;
   both_merge_kernel<<<g.blocks * (b.triangle ? 1 : 2), 256, 0, a.stream>>>(g);
+  // without gradients (NT-Xent with dz = NULL) no sum of partials follows that carries the row losses
+  if (!a.loss_with_partials && !a.defer_loss_sum) return launch_loss_sum(a, pl);
   return hipGetLastError();
 }
 

@@ -51,6 +51,22 @@ def test_ntxent_over_the_triangle(n, d, tau, grow):
     check("triangle n=%d d=%d dz" % (n, d), relerr(to_np(dz), want["dz"]), TOL_BF16)
 
 
+# without a gradient no sum of partials carries the row losses; 512: few scores, the others one pass over the triangle
+@pytest.mark.parametrize("n,d", [(512, 128), (1026, 128), (1100, 256)])
+def test_ntxent_loss_alone(n, d):
+    z = synth.ntxent_views(n, d, seed=9400 + n)
+    want = O.ntxent(synth.widen(z), 0.3)["loss"]
+    lib, zd = gc.load(), z.to(DEV)
+    ws = gc.alloc_workspace(lib.gc_ntxent_workspace_bytes(n, d), DEV)
+    ws.fill_(0x5a)   # whatever the workspace held
+    wp, wn = gc._ws_ptr(ws)
+    loss = torch.full((1,), -7.0, device=DEV)
+    rc = lib.gc_ntxent_loss_and_grad_bf16(zd.data_ptr(), n, d, 0.3, loss.data_ptr(), None, wp, wn, gc._stream(None))
+    torch.cuda.synchronize()
+    assert rc == gc.GC_OK and gc.gc_check_async_error(ws) == gc.GC_OK
+    check_loss("loss alone n=%d d=%d" % (n, d), loss.item(), want, 1e-5)
+
+
 def test_loss_of_a_converged_softmax():
     """Rows whose positive outweighs everything: the loss is log(1 + x), x the others' sum over the positive's term.  x is off
     by ln 2 times the rounding of two logits of size 150 to fp32 (2^-24 * 150 each), 1.3e-5 of it; the bound is 1e-4."""
