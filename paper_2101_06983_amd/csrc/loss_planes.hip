@@ -410,12 +410,14 @@ struct PlanesGradArgs {
   const float* pos_c;                      // ... the positive's coefficient, with room for 128 rows
   float alpha2, out_scale;
   int mask_self;
-  FewMerge fm; int P;                      // fm.splits > 0: lse2, pos (not padded) and pos_c are formed here, see StatMerge
+  FewMerge fm; int P;                      // MERGE: lse2, pos (not padded) and pos_c are formed from these
 };
 constexpr int PG_STEP = 128, PG_MERGE_BYTES = 3 * kFewMergeRows * 4;
 constexpr int planes_g_bytes(int NO) { return 4 * 2 * 3 * NO * 1024; }
 
-template <int NP, int NO, int CTW>
+// MERGE: the statistics come as splits, see StatMerge (a template argument: as a branch at run time it costs the instantiations
+// that never take it registers, and <3, 2, 8> seven spills inside its loop; 58.9 us a call at 512 x 1024 x 768 in fp32, 57.7 so).
+template <int NP, int NO, int CTW, bool MERGE>
 __global__ void __launch_bounds__(256, NO == 1 && CTW <= 4 ? 2 : 1) planes_grad_kernel(PlanesGradArgs g) {
   extern __shared__ __attribute__((aligned(16))) unsigned short pl_lds[];
   unsigned short* gl = pl_lds;                                    // [kk8][no][plane] blocks of 1 KB
@@ -431,11 +433,10 @@ __global__ void __launch_bounds__(256, NO == 1 && CTW <= 4 ? 2 : 1) planes_grad_
   const unsigned short* own = R.own_k + (size_t)ob * NO * blk;
   const int sbeg = split * R.len, send = min(R.n_str, sbeg + R.len);
   const int ct0 = cs * g.ct_per_slice, ct1 = min(g.CT, ct0 + g.ct_per_slice);
-  const bool merge = g.fm.splits > 0;
-  float* const l_lse = (float*)(own_lds + (size_t)g.ks_lds * NO * NP * 512);   // (with merge) of rows from the first owner / streamed row on
+  float* const l_lse = (float*)(own_lds + (size_t)g.ks_lds * NO * NP * 512);   // (MERGE) of rows from the first owner / streamed row on
   int* const l_pos = (int*)l_lse + kFewMergeRows;
   float* const l_c = l_lse + 2 * kFewMergeRows;
-  if (merge) {
+  if constexpr (MERGE) {
     const int B = ri ? R.n_str : R.n_own;
     StatMerge<true> sm(g.fm, g.pos, B, ri ? sbeg : ob * NO * 32, ri ? send - sbeg : NO * 32, !ri && split == 0 && cs == 0);
     planes_stage_own<NP, NO>(own_lds, own, blk, g.ks_lds);
@@ -449,9 +450,9 @@ __global__ void __launch_bounds__(256, NO == 1 && CTW <= 4 ? 2 : 1) planes_grad_
 #pragma unroll
   for (int no = 0; no < NO; no++) {
     own_idx[no] = (ob * NO + no) * 32 + ln;
-    lse_o[no] = ri ? 0.f : merge ? l_lse[no * 32 + ln] : g.lse2[own_idx[no]];
-    c_o[no] = ri ? 0.f : merge ? l_c[no * 32 + ln] : g.pos_c[own_idx[no]];
-    r_o[no] = ri ? -1 : merge ? l_pos[no * 32 + ln] : g.pos[own_idx[no]];
+    lse_o[no] = ri ? 0.f : MERGE ? l_lse[no * 32 + ln] : g.lse2[own_idx[no]];
+    c_o[no] = ri ? 0.f : MERGE ? l_c[no * 32 + ln] : g.pos_c[own_idx[no]];
+    r_o[no] = ri ? -1 : MERGE ? l_pos[no * 32 + ln] : g.pos[own_idx[no]];
   }
   f32x16 acc[NO][CTW];
 #pragma unroll
@@ -488,7 +489,7 @@ __global__ void __launch_bounds__(256, NO == 1 && CTW <= 4 ? 2 : 1) planes_grad_
       for (int q = 0; q < 4; q++) {
         f32x4 a, c;
         i32x4 b;
-        if (merge) {
+        if constexpr (MERGE) {
           const int o = j0 - sbeg + 8 * q;
           a = *(const f32x4*)(l_lse + o); b = *(const i32x4*)(l_pos + o); c = *(const f32x4*)(l_c + o);
         } else {
@@ -613,7 +614,8 @@ void plan_planes(LossPlan& pl, int B, int P, int d, gc_dtype dt, int max_splits)
   };
   split_of(stQ, P, pl.nsq, pl.q_stream_len);
   split_of(stP, B, pl.nsp, pl.p_stream_len);
-  pl.few_merge = pl.stat_tile && pl.p_stream_len <= kFewMergeRows;
+  // (64 owner rows are for many steps a workgroup, where a launch more is nothing: no instantiations of their own)
+  pl.few_merge = pl.stat_tile && pl.px_no == 1 && pl.p_stream_len <= kFewMergeRows;
 }
 
 template <typename T>
@@ -662,15 +664,22 @@ hipError_t launch_stats_planes(const LossArgs& a, const LossPlan& pl) {
   return pl.np == 3 ? stats_np<3>(a, pl) : stats_np<1>(a, pl);
 }
 
-template <int NP, int NO, int CTW>
-static hipError_t grad_launch(PlanesGradArgs& g, int nwg, hipStream_t s) {
-  const int merge = g.fm.splits ? PG_MERGE_BYTES : 0;
+template <int NP, int NO, int CTW, bool MERGE>
+static hipError_t grad_launch_as(PlanesGradArgs& g, int nwg, hipStream_t s) {
+  constexpr int merge = MERGE ? PG_MERGE_BYTES : 0;
   const int budget = ((nwg <= num_cu() || NO == 2 || CTW > 4) ? 156 : 78) * 1024 - planes_g_bytes(NO) - merge;
   g.ks_lds = ks_in_lds(budget / (NO * NP * 1024), g.KS, planes_pd(NP));
   static bool done[64];
-  if (hipError_t e = ensure_dyn_lds((const void*)planes_grad_kernel<NP, NO, CTW>, 160 * 1024, done); e != hipSuccess) return e;
-  planes_grad_kernel<NP, NO, CTW><<<nwg, 256, planes_g_bytes(NO) + g.ks_lds * NO * NP * 1024 + merge, s>>>(g);
+  if (hipError_t e = ensure_dyn_lds((const void*)planes_grad_kernel<NP, NO, CTW, MERGE>, 160 * 1024, done); e != hipSuccess) return e;
+  planes_grad_kernel<NP, NO, CTW, MERGE><<<nwg, 256, planes_g_bytes(NO) + g.ks_lds * NO * NP * 1024 + merge, s>>>(g);
   return hipGetLastError();
+}
+template <int NP, int NO, int CTW>
+static hipError_t grad_launch(PlanesGradArgs& g, int nwg, hipStream_t s) {
+  if constexpr (NO == 1) {   // (few_merge: plan_planes)
+    if (g.fm.splits) return grad_launch_as<NP, NO, CTW, true>(g, nwg, s);
+  }
+  return grad_launch_as<NP, NO, CTW, false>(g, nwg, s);
 }
 template <int NP, int NO>
 static hipError_t grad_ctw(PlanesGradArgs& g, int nwg, hipStream_t s) {

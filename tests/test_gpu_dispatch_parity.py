@@ -378,6 +378,14 @@ def test_deep_distance_where_the_powers_end(B, P, rows):
         check("deep %s %dx%d %s" % (rows, B, P, k), relerr(to_np(out[k]), want[k]), 1e-4)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_few_scores_with_64_owner_rows(dtype):
+    """A few anchors against so many targets that a workgroup owns 64 rows: the statistics of few scores, merged by a launch."""
+    q, p, r = synth.dpr_batch(3, 100000, 24, dtype, seed=5500)
+    want = oracle_loss(q, p, r, 1.0, 0.25)
+    check_fp32_grade("3x100000x24 %s" % dtype, run_ex(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.25), want, q, p, 4.0)
+
+
 @pytest.mark.parametrize("B,P,d,dtype", [(3000, 3100, 500, torch.float32), (3000, 3000, 768, torch.float32), (2800, 3000, 1000, torch.float32),
                                          (3000, 3100, 500, torch.bfloat16), (3000, 3000, 700, torch.bfloat16), (3000, 3000, 1000, torch.bfloat16),
                                          (2000, 2100, 1300, torch.bfloat16)])
