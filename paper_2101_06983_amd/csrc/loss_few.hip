@@ -238,11 +238,27 @@ __device__ __forceinline__ void grad_few_body(const GradArgs& ga, const FewMerge
   chk.finish(ga);
 }
 
+// Workgroup `o` of `n` -> task, such that an XCD (ids go to the eight round-robin) has a contiguous range.
+__device__ __forceinline__ int xcd_share(int o, int n) {
+  const int x = o % 8, more = n % 8;
+  return x * (n / 8) + (x < more ? x : more) + o / 8;
+}
+// A grid of one round is numbered through both roles: an XCD then fetches the code of one of them (with a share of either 32 x 2048
+// x 768 takes 27.6 us for 25.3, the 180 shapes of one round 1 % more).  Beyond a round every XCD gets its share of
+// either, those with the longer walks first: otherwise the long walks are all on one or two XCDs, two rounds of them there
+// (128 x 8192 x 768, 64 walks of 512 rows and 256 of 128: 84.7 us a call, 60.1 so; 8192 x 128 x 768 125.5 and 98.0).
+__device__ __forceinline__ int few_spread_id(const GradArgs& ga) {
+  const int nQ = ga.obQ * ga.nsq, nP = ga.obP * ga.nsp, id = (int)blockIdx.x;
+  if (ga.p_stream_len > ga.q_stream_len) return id < nP ? nQ + xcd_share(id, nP) : xcd_share(id - nP, nQ);
+  return id < nQ ? xcd_share(id, nQ) : nQ + xcd_share(id - nQ, nP);
+}
 template <int D, bool SYM, bool MERGE>
 __global__ void __launch_bounds__(256) grad_few_kernel(GradArgs ga, FewMerge fm) {
   extern __shared__ __attribute__((aligned(16))) unsigned char gsmem[];
   const int nQ = ga.obQ * ga.nsq;
-  const int id = xcd_task_id();
+  constexpr unsigned ROUND = (D <= 256 ? 2 : 1) * kNumCUDefault;   // workgroups that run at once, by their LDS
+  int id = xcd_task_id();
+  if (__builtin_expect(gridDim.x > ROUND, 0)) id = few_spread_id(ga);
   if (id < nQ) {
     grad_few_body<D, true, SYM, MERGE>(ga, fm, id % ga.obQ, id / ga.obQ, gsmem);
   } else {

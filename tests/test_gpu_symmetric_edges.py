@@ -110,6 +110,18 @@ def test_few_scores(B, P, d):
         assert relerr(to_np(alone[k][k]), to_np(out[k])) <= 1e-5 and alone[k]["loss"].item() == pytest.approx(out["loss"].item(), rel=1e-6)
 
 
+# more workgroups than run at once: the longer walks are the anchors' / the targets', their numbers a multiple of 8 or not
+@pytest.mark.parametrize("B,P,d", [(128, 8192, 768), (45, 11585, 512), (8190, 128, 384), (11585, 45, 640), (64, 16384, 128)])
+def test_few_scores_beyond_one_round_of_workgroups(B, P, d):
+    q, p, r = synth.dpr_batch(B, P, d, seed=9750 + B, pos_idx=torch.from_numpy(np.random.default_rng(B).integers(0, P, size=B).astype(np.int32)))
+    want = oracle_loss(q, p, r, 1.0, 0.3)
+    out = gc.gc_loss_and_rep_grad_ex(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.3)
+    torch.cuda.synchronize()
+    check_loss("beyond a round loss", out["loss"].item(), want["loss"], TOL_F32)
+    for k in ("dq", "dp"):
+        check("beyond a round %dx%dx%d %s" % (B, P, d, k), relerr(to_np(out[k]), want[k]), TOL_BF16)
+
+
 # more anchors than one round of the sum kernel looks at: exactly one, one more, several rounds with few and many named rows
 @pytest.mark.parametrize("B,P,d,named", [(1024, 40, 128, 40), (1025, 40, 256, 1), (2100, 300, 384, 300), (2600, 500, 128, 3)])
 def test_targets_shared_by_more_anchors_than_a_round(B, P, d, named):
