@@ -54,7 +54,7 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
       pl.stat_splits = ceil_div(tiles, per);
     } else {
       // two workgroups to a CU, blocks of 256 anchors at d = 128; without `few`: one of 256 x 256 scores, for fewer partials
-      const bool mid = few && d > 128;
+      const bool mid = few && d > 128 && stats_block(B, P, d) == kStatBlock;
       const int T = mid ? kStatBlock : 256, n_ablk = ceil_div(B, T), tiles = ceil_div(P, T);
       int splits = ceil_div(mid || d == 128 ? 2 * kNumCU : kNumCU, n_ablk);
       if (splits > 64) splits = 64;

@@ -7,24 +7,22 @@
 namespace gc {
 
 // ===========================================================================
-// Statistics pass.  Workgroup = 512 threads = 8 waves as 2 (targets, M) x 4 (anchors, N); wave tile MT x NT = 2 x 1 MFMA
-// tiles, workgroup tile 128 x 128, two workgroups to a compute unit.  k is staged through LDS in chunks of 64, two stages.
-// One workgroup of 256 x 256 (wave tile 4 x 2) halves the LDS bytes per MFMA and is no faster where it fills the chip
-// (4096 x 8192 x 256: 137 us a call with either), but leaves most of it idle below (68 tiles at 1021 x 4099 x 384: 22.6 us of a
-// call of 69.7, now 59.1), and has no registers left for the sums of both sides (symmetric 8192 x 256: 283 us, now 253).
+// Statistics pass.  Workgroup = 512 threads = 8 waves as 2 (targets, M) x 4 (anchors, N); wave tile MT x NT MFMA tiles.
+// k is staged through LDS in chunks of 64, two stages.  2 x 1: workgroup tile 128 x 128, two workgroups to a compute unit.
+// 4 x 2: 256 x 256, one workgroup to a compute unit, for the largest calls (see stats_block).
 // ===========================================================================
 constexpr int ST_KC = 64, ST_ROWB = ST_KC * 2;           // bytes per LDS row (8 chunks of 16 bytes, unpadded)
-constexpr int MT = 2, NT = 1, ST_TM = 64 * MT, ST_TN = 128 * NT;
-constexpr int ST_STAGE_BYTES = (ST_TM + ST_TN) * ST_ROWB;   // one stage: the target rows, then the anchor rows
-static_assert(ST_TM == kStatBlock && ST_TN == kStatBlock, "waves 0-3 load the target rows, waves 4-7 as many anchor rows");
+constexpr int stats_stage_bytes(int block) { return 2 * block * ST_ROWB; }   // one stage: the target rows, then the anchor rows
 // LDS layout: chunk c of row r is stored at chunk position c ^ ((r >> 1) & 7): the 16 rows that a
 // 16-lane group reads in one fragment load then fall into 16 different 16-byte bank groups.
 
 // ARGMAX: the plain pass with the first index of the maximum; BOTH, TRI: the statistics of both sides of the symmetric forms
 // from one pass over the scores (see kBothMin), TRI (NT-Xent, q = p) over the tiles on and above the diagonal only.
 enum StatsMode { ST_PLAIN, ST_ARGMAX, ST_BOTH, ST_TRI };
-template <StatsMode MODE>
-__global__ void __launch_bounds__(512, 4) stats_mfma_kernel(StatsArgs g) {
+template <StatsMode MODE, int BLOCK>
+__global__ void __launch_bounds__(512, BLOCK == kStatBlock ? 4 : 2) stats_mfma_kernel(StatsArgs g) {
+  constexpr int MT = BLOCK / 64, NT = BLOCK / 128, ST_TM = BLOCK, ST_TN = BLOCK;
+  constexpr int ST_STAGE_BYTES = stats_stage_bytes(BLOCK);
   constexpr int LROWS = ST_TM / 4;   // rows of a stage that a wave loads
   constexpr bool TRI = MODE == ST_TRI, BOTH = MODE == ST_BOTH || TRI, ARGMAX = MODE == ST_ARGMAX;
   const unsigned short* const Q = g.Q;
@@ -432,13 +430,28 @@ static hipError_t launch_stats_small(const LossArgs& a, const LossPlan& pl) {
   return hipGetLastError();
 }
 
-template <StatsMode MODE>
-static hipError_t stats_mfma_launch(const StatsArgs& g, int nwg, hipStream_t stream) {
-  constexpr int smem = 2 * ST_STAGE_BYTES + (MODE >= ST_BOTH ? 4 * ST_TM * 8 : 0);
+// Rows and columns of a workgroup's scores.  128 fills the chip from few scores on (1021 x 4099 x 384: 68 blocks of 256 leave
+// most of it idle, 27.6 us for the loss alone, 17.0 so) and is as fast or faster almost everywhere, in spite of twice the LDS bytes per MFMA:
+//   loss alone, us (256 / 128)   2^25 scores      2^26            2^28            2^29
+//     d = 256                    40.1 / 33.3   70.1 / 57.2     231 / 186       428 / 354
+//     d = 512                    53.1 / 48.9   99.4 / 92.5     333 / 324       627 / 625
+//     d = 640                    59.6 / 56.6    113 / 111      381 / 391       725 / 773
+//     d = 768                    65.6 / 66.2  121..127 / 129   431 / 470       815 / 917
+// but reads the inputs twice as often, past what an XCD's L2 holds of wide rows: at 2^27 scores 199 / 203 (d = 640), 227 / 239 (768);
+// at 6000 x 12000 x 768, 2^26.1, whose last blocks of 256 are part empty, 145 / 139.
+int stats_block(int B, int P, int d) { return d >= 640 && (long long)B * P >= (1ll << 27) ? 256 : kStatBlock; }
+
+template <StatsMode MODE, int BLOCK>
+static hipError_t stats_mfma_launch_as(const StatsArgs& g, int nwg, hipStream_t stream) {
+  constexpr int smem = 2 * stats_stage_bytes(BLOCK) + (MODE >= ST_BOTH ? 4 * BLOCK * 8 : 0);
   static bool attr_done[64];
-  if (hipError_t e = ensure_dyn_lds((const void*)stats_mfma_kernel<MODE>, smem, attr_done); e != hipSuccess) return e;
-  stats_mfma_kernel<MODE><<<nwg, 512, smem, stream>>>(g);
+  if (hipError_t e = ensure_dyn_lds((const void*)stats_mfma_kernel<MODE, BLOCK>, smem, attr_done); e != hipSuccess) return e;
+  stats_mfma_kernel<MODE, BLOCK><<<nwg, 512, smem, stream>>>(g);
   return hipGetLastError();
+}
+template <StatsMode MODE>
+static hipError_t stats_mfma_launch(const StatsArgs& g, int block, int splits, hipStream_t stream) {
+  return block == 256 ? stats_mfma_launch_as<MODE, 256>(g, g.n_ablk * splits, stream) : stats_mfma_launch_as<MODE, kStatBlock>(g, g.n_ablk * splits, stream);
 }
 hipError_t launch_stats_mfma(const LossArgs& a, const LossPlan& pl) {
   if (pl.stat_tile) return launch_stats_small(a, pl);
@@ -447,11 +460,11 @@ hipError_t launch_stats_mfma(const LossArgs& a, const LossPlan& pl) {
   StatsArgs g{};
   g.Q = (const unsigned short*)a.q; g.P = (const unsigned short*)a.p; g.pos_idx = a.pos_idx; g.B = a.B; g.Pn = a.P; g.d = a.d;
   g.alpha2 = a.alpha * kLog2e; g.mask_self = (a.flags & GC_MASK_SELF) ? 1 : 0;
-  g.n_ablk = (a.B + ST_TN - 1) / ST_TN; g.cols_per_split = pl.stat_cols_per_split;
+  const int block = stats_block(a.B, a.P, a.d);
+  g.n_ablk = (a.B + block - 1) / block; g.cols_per_split = pl.stat_cols_per_split;
   g.row_m = (float*)(ws + pl.off_part_m); g.row_l = (float*)(ws + pl.off_part_l); g.row_idx = (int*)(ws + pl.off_part_idx);
   g.pos_t = (float*)(ws + pl.off_pos);
-  const int nwg = g.n_ablk * pl.stat_splits;
-  return a.argmax ? stats_mfma_launch<ST_ARGMAX>(g, nwg, a.stream) : stats_mfma_launch<ST_PLAIN>(g, nwg, a.stream);
+  return a.argmax ? stats_mfma_launch<ST_ARGMAX>(g, block, pl.stat_splits, a.stream) : stats_mfma_launch<ST_PLAIN>(g, block, pl.stat_splits, a.stream);
 }
 
 // ---- statistics of both sides (the symmetric forms) ------------------------------------------------------------------
@@ -488,7 +501,7 @@ hipError_t launch_stats_both(const LossArgs& a, const LossPlan& pl, const BothPl
   g.pos_t = (float*)(a.ws + pl.off_pos);
   g.zero = a.wide; g.inv = b.triangle ? nullptr : a.pos_inv;
   if (a.d == 128) return launch_stats128_both(g, b.triangle, b.nwg, a.stream);
-  return b.triangle ? stats_mfma_launch<ST_TRI>(g, b.nwg, a.stream) : stats_mfma_launch<ST_BOTH>(g, b.nwg, a.stream);
+  return b.triangle ? stats_mfma_launch_as<ST_TRI, kStatBlock>(g, b.nwg, a.stream) : stats_mfma_launch_as<ST_BOTH, kStatBlock>(g, b.nwg, a.stream);
 }
 
 }  // namespace gc

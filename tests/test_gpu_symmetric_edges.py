@@ -134,6 +134,33 @@ def test_targets_shared_by_more_anchors_than_a_round(B, P, d, named):
         check("shared %dx%dx%d %s" % (B, P, d, k), relerr(to_np(out[k]), want[k]), TOL_BF16)
 
 
+# the largest calls of wide rows: blocks of 256 x 256 scores, both sides ragged; the diagonal masked
+@pytest.mark.parametrize("B,P,d,mask", [(1025, 131100, 640, False), (11602, 11602, 768, True)])
+def test_statistics_in_blocks_of_256(B, P, d, mask):
+    q, p, r = synth.dpr_batch(B, P, d, seed=9850 + d, positive_mix=0.3,
+                              pos_idx=torch.arange(B, dtype=torch.int32) ^ 1 if mask else torch.arange(B, dtype=torch.int32) * 127)
+    dev = (q.to(DEV), p.to(DEV), r.to(DEV))
+    flags = gc.GC_PATH_STATS_PASS | (gc.GC_MASK_SELF if mask else 0)
+    out = gc.gc_loss_and_rep_grad_ex(*dev, 1.0, 0.1, flags, ("loss", "lse", "argmax"))
+    plain = gc.gc_loss_and_rep_grad_ex(*dev, 1.0, 0.1, flags, ("loss", "lse"))
+    assert torch.equal(plain["lse"], out["lse"]) and torch.equal(plain["loss"], out["loss"])
+    lse, pos, best, gap = [], [], [], []
+    for i in range(0, B, 1024):   # fp64, 1024 anchors at a time
+        s = (dev[0][i:i + 1024].double() @ dev[1].double().T) / 0.1
+        rows = torch.arange(s.shape[0], device=DEV)
+        if mask:
+            s[rows, rows + i] = -float("inf")
+        lse.append(torch.logsumexp(s, 1))
+        pos.append(s[rows, dev[2][i:i + 1024].long()])
+        top = s.topk(2, 1)
+        best.append(top.indices[:, 0])
+        gap.append(top.values[:, 0] - top.values[:, 1])
+    lse, pos, best, gap = (torch.cat(x) for x in (lse, pos, best, gap))
+    check_loss("256 blocks loss", out["loss"].item(), (lse - pos).mean().item(), 1e-5)
+    check("256 blocks lse", relerr(to_np(out["lse"]), to_np(lse)), TOL_F32)
+    assert not ((out["argmax"].long() != best) & (gap > 1e-5)).any()
+
+
 @pytest.mark.parametrize("B,P,d,f32", [(33, 129, 100, True), (300, 70, 768, True), (257, 600, 200, False), (100, 2000, 1000, False)])
 def test_few_scores_of_any_width(B, P, d, f32):
     q, p, r = synth.dpr_batch(B, P, d, seed=9900 + B)

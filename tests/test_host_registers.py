@@ -8,7 +8,8 @@ import msgpack
 from paper_2101_06983_amd import build
 
 # bytes of scratch a lane may use; every kernel that is not named here uses none
-SPILLS = {"gemm_nt_kernel<true, ": 72, "grad128_kernel<true, true>": 12, "planes_grad_kernel<1, 2, 8, false>": 124, "mlp_dh_tiled_kernel<64>": 232}
+SPILLS = {"gemm_nt_kernel<true, ": 72, "grad128_kernel<true, true>": 12, "planes_grad_kernel<1, 2, 8, false>": 124, "mlp_dh_tiled_kernel<64>": 232,
+          "stats_mfma_kernel<(gc::StatsMode)1, 256>": 20}
 NT_AMDGPU_METADATA, SHT_NOTE, EM_AMDGPU = 32, 7, 224
 
 
