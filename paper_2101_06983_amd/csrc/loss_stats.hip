@@ -104,6 +104,7 @@ __global__ void __launch_bounds__(512, BLOCK == kStatBlock ? 4 : 2) stats_mfma_k
   f32x2* cbuf = (f32x2*)(smem_b + 2 * ST_STAGE_BYTES);   // [4 wn][ST_TM columns] (maximum, sum)
   const int col_in = 8 * (reduce16_reg_of(lane) >> 2) + 4 * (lane >> 5) + (reduce16_reg_of(lane) & 3);
   const bool own_edge = a0 + wn * 32 * NT + 32 * NT > B;
+  bool fast = true;   // (of this wave) the sums of the last tile that took references of its own were within the bounds
 
   // The k-chunks of all the tiles of this workgroup form one sequence of steps; step st lives in stage st & 1 and
   // its loads are issued one step ahead inside a tile.  (Loading the first chunk of the next tile under the last
@@ -168,8 +169,9 @@ __global__ void __launch_bounds__(512, BLOCK == kStatBlock ? 4 : 2) stats_mfma_k
               }
       }
       const bool cols = !TRI || b0 > a0;
+      const bool masked = edge || own_edge || (TRI && !cols);
       bool done = false;
-      if (cols && !own_edge && !edge) {
+      if (!masked && fast) {
         float rs[NT], c[MT], lo = INFINITY, hi = 0.f;
 #pragma unroll
         for (int nt = 0; nt < NT; nt++) rs[nt] = 0.f;
@@ -202,49 +204,60 @@ __global__ void __launch_bounds__(512, BLOCK == kStatBlock ? 4 : 2) stats_mfma_k
         }
       }
       if (!done) {   // masks, and references of its own for every row and column
-        float tm[NT], mn[NT], sum[NT];
-#pragma unroll
-        for (int nt = 0; nt < NT; nt++) {
-          tm[nt] = -INFINITY; sum[nt] = 0.f;
-#pragma unroll
-          for (int mt = 0; mt < MT; mt++)
-#pragma unroll
-            for (int r = 0; r < 16; r++) {
-              const int j = brow0 + mt * 32 + 8 * (r >> 2) + (r & 3);
-              acc[mt][nt][r] = (j >= cend || a_col[nt] >= B || (TRI && j == a_col[nt])) ? -INFINITY : acc[mt][nt][r] * alpha2;
-              tm[nt] = fmaxf(tm[nt], acc[mt][nt][r]);
-            }
-          mn[nt] = fmaxf(rm[nt], tm[nt]);
-          if (mn[nt] == -INFINITY) mn[nt] = 0.f;
-        }
-#pragma unroll
-        for (int mt = 0; mt < MT; mt++) {
+        if (masked) {
 #pragma unroll
           for (int nt = 0; nt < NT; nt++)
 #pragma unroll
-            for (int r = 0; r < 16; r++) sum[nt] += fast_exp2(acc[mt][nt][r] - mn[nt]);
-          if (cols) {
-            float mx[16], v[16];
+            for (int mt = 0; mt < MT; mt++)
 #pragma unroll
-            for (int r = 0; r < 16; r++) {
-#pragma unroll
-              for (int nt = 0; nt < NT; nt++) mx[r] = nt ? fmaxf(mx[r], acc[mt][nt][r]) : acc[mt][nt][r];
-              float m = max_lanes32(mx[r]);
-              m = m == -INFINITY ? 0.f : m;
-#pragma unroll
-              for (int nt = 0; nt < NT; nt++) v[r] = (nt ? v[r] : 0.f) + fast_exp2(acc[mt][nt][r] - m);
-              if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-            }
-            const float cm = reduce16_lanes32<true>(mx, lane), cl = reduce16_lanes32<false>(v, lane);
-            if (!(lane & 1)) cbuf[wn * ST_TM + wm * 32 * MT + mt * 32 + col_in] = f32x2{cm, cl};
-          }
-          __builtin_amdgcn_sched_barrier(0);
+              for (int r = 0; r < 16; r++) {
+                const int j = brow0 + mt * 32 + 8 * (r >> 2) + (r & 3);
+                if (j >= cend || a_col[nt] >= B || (TRI && j == a_col[nt])) acc[mt][nt][r] = -INFINITY;
+              }
         }
+        float lo = INFINITY, hi = -INFINITY;   // of the references
 #pragma unroll
         for (int nt = 0; nt < NT; nt++) {
-          if (tm[nt] == -INFINITY) continue;
-          rl[nt] = rl[nt] * fast_exp2(rm[nt] - mn[nt]) + sum[nt];
-          rm[nt] = mn[nt];
+          float tm = -INFINITY, sum = 0.f;
+#pragma unroll
+          for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) tm = fmaxf(tm, acc[mt][nt][r]);
+          tm *= alpha2;
+          lo = fminf(lo, tm); hi = fmaxf(hi, tm);
+          if (tm == -INFINITY) continue;
+          const float mn = fmaxf(rm[nt], tm);
+#pragma unroll
+          for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) sum += fast_exp2(__builtin_fmaf(acc[mt][nt][r], alpha2, -mn));
+          rl[nt] = rl[nt] * fast_exp2(rm[nt] - mn) + sum;
+          rm[nt] = mn;
+        }
+        if (cols) {
+#pragma unroll
+          for (int mt = 0; mt < MT; mt++) {
+            float v[16];
+#pragma unroll
+            for (int r = 0; r < 16; r++) {
+              v[r] = acc[mt][0][r];
+#pragma unroll
+              for (int nt = 1; nt < NT; nt++) v[r] = fmaxf(v[r], acc[mt][nt][r]);
+            }
+            const float cm = reduce16_lanes32<true>(v, lane) * alpha2, cs = cm == -INFINITY ? 0.f : cm;
+            static_for<16>([&](auto r_tag) __attribute__((always_inline)) {
+              constexpr int r = decltype(r_tag)::value;
+              const float m = reduce16_spread<r>(cs);
+#pragma unroll
+              for (int nt = 0; nt < NT; nt++) v[r] = (nt ? v[r] : 0.f) + fast_exp2(__builtin_fmaf(acc[mt][nt][r], alpha2, -m));
+            });
+            const float cl = reduce16_lanes32<false>(v, lane);
+            lo = fminf(lo, cm); hi = fmaxf(hi, cm);
+            if (!(lane & 1)) cbuf[wn * ST_TM + wm * 32 * MT + mt * 32 + col_in] = f32x2{cm, cl};
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          // (a sum relative to its maximum is in 1 .. 32)
+          if (!masked) fast = __builtin_amdgcn_ballot_w64(!(lo >= kBothMinLog2 && hi <= kBothMaxLog2 - 5)) == 0;
         }
       }
       if (cols) {   // the four waves' sums of a column, in wave order (the next tile writes them behind many barriers)

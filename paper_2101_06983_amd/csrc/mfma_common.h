@@ -189,9 +189,9 @@ __device__ __forceinline__ void static_for(F&& f) {  // f(integral_constant<int,
   }
 }
 
-// Sum (or maximum) of N registers (16 or 64), each over the 32 lanes of its half-wave, by halving: every exchange combines two
-// registers into one, so N registers cost about 2.5 N operations, not 10 N.  The result of register r is in the lanes whose
-// bits 4, 3, 2, 1 spell bits 0, 1, 2, 3 of r (bit 0 of the lane: a copy); N = 64: registers 16 k + r go to out[k].
+// Sum (or maximum) of 16 registers, each over the 32 lanes of its half-wave, by halving: every exchange combines two
+// registers into one, so they cost about 40 operations, not 160.  The result of register r is in the lanes whose
+// bits 4, 3, 2, 1 spell bits 0, 1, 2, 3 of r (bit 0 of the lane: a copy).
 template <bool MAX>
 __device__ __forceinline__ float lane_op(float a, float b) { return MAX ? fmaxf(a, b) : a + b; }
 template <int CTRL>
@@ -216,6 +216,12 @@ __device__ __forceinline__ float reduce16_lanes32(const float (&v)[16], int lane
   return lane_op<MAX>(y, dpp<kXor1>(y));
 }
 __device__ __forceinline__ int reduce16_reg_of(int lane) { return ((lane >> 4) & 1) | ((lane >> 2) & 2) | (lane & 4) | ((lane << 2) & 8); }
+// ... and back: what reduce16_lanes32 left for register R, in every lane of the half-wave (ds_swizzle: all from one lane)
+template <int R>
+__device__ __forceinline__ float reduce16_spread(float x) {
+  constexpr int from = ((R & 1) << 4) | ((R & 2) << 2) | (R & 4) | ((R & 8) >> 2);
+  return __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, x), from << 5));
+}
 // maximum over the 32 lanes of the half-wave, in every lane
 __device__ __forceinline__ float max_lanes32(float x) {
   unsigned a, b;
@@ -230,7 +236,9 @@ __device__ __forceinline__ float max_lanes32(float x) {
 // Statistics of both sides of a score matrix from one pass over its scores (the symmetric forms): sums of 2^t per row (lanes)
 // and per column of a tile with the reference 0.  A tile whose sums all lie in these bounds has lost nothing: what 2^t flushes
 // is below 2^-126.  Any other tile (and one with masked scores) takes the maxima of its rows and columns as references.
-constexpr float kBothMin = 0x1p-60f, kBothMax = 0x1p100f;
+// (stats_mfma_kernel: a column's maximum goes back to its lanes by ds_swizzle, and a wave tries the reference 0 again once the
+// references of a tile allow it.  4096 views of 256, logits far beyond: 30 us before that, 20.5 so, 16.5 with the reference 0.)
+constexpr float kBothMin = 0x1p-60f, kBothMax = 0x1p100f, kBothMinLog2 = -60.f, kBothMaxLog2 = 100.f;
 struct StatsArgs {
   const unsigned short* Q; const unsigned short* P; const int32_t* pos_idx;
   int B, Pn, d;              // owners (lanes), streamed rows

@@ -40,6 +40,21 @@ def test_symmetric_loss_one_pass(n, d, temp, grow):
         check("one pass n=%d d=%d %s" % (n, d, k), relerr(to_np(out[k]), want[k]), TOL_BF16)
 
 
+@pytest.mark.parametrize("side", ["anchors", "targets"])
+@pytest.mark.parametrize("d", [128, 256])
+def test_symmetric_loss_one_pass_where_some_tiles_need_their_own_references(side, d):
+    """Several tiles a workgroup, of which a band of large rows makes some, but not all, leave and take the reference 0."""
+    n = 6000
+    q, p, r = sym_problem(n, d, 9250 + d, 0.0)
+    (q if side == "anchors" else p)[2100:2500] *= 150
+    want = O.bidirectional(synth.widen(q), synth.widen(p), r.numpy(), 1.0, 0.3)
+    out = gc.gc_bidirectional_loss_and_rep_grad_bf16(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.3)
+    torch.cuda.synchronize()
+    check_loss("band loss", out["loss"].item(), want["loss"], 1e-5)
+    for k in ("dq", "dp"):
+        check("band of %s d=%d %s" % (side, d, k), relerr(to_np(out[k]), want[k]), TOL_BF16)
+
+
 @pytest.mark.parametrize("n,d,tau,grow", [(1026, 128, 0.07, 1), (1790, 128, 0.3, 1), (1280, 128, 0.3, 9), (2562, 128, 0.07, 1),
                                           (1026, 256, 0.1, 1), (1410, 512, 0.3, 12), (1150, 768, 0.07, 1)])
 def test_ntxent_over_the_triangle(n, d, tau, grow):
