@@ -14,7 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libgradcache.so")
-SOURCES = ["api.hip", "loss_few.hip", "loss_generic.hip", "loss_mfma.hip", "loss_mfma128.hip", "loss_planes.hip", "loss_stats.hip", "mlp.hip"]
+SOURCES = ["api.hip", "loss_few.hip", "loss_generic.hip", "loss_mfma.hip", "loss_mfma128.hip", "loss_mfma_sym.hip", "loss_planes.hip", "loss_stats.hip", "mlp.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",

@@ -275,6 +275,9 @@ constexpr int G1_OWN = 128;   // owner rows per workgroup of the gradient pass
 hipError_t launch_stats128(const LossArgs& a, const LossPlan& pl);
 hipError_t grad128_launch(const GradArgs& ga, int nwg, hipStream_t stream);
 
+// symmetric forms, d >= 256 (loss_mfma_sym.hip)
+hipError_t grad_sym_launch(const GradArgs& ga, int d, int nwg, hipStream_t stream);
+
 // few scores (loss_few.hip)
 constexpr int kFewOwn = 32;   // owner rows per workgroup
 hipError_t grad_few_launch(const GradArgs& ga, const FewMerge& fm, int d, int nwg, hipStream_t stream);
