@@ -491,12 +491,15 @@ BothPlan plan_both(int n, int d, bool triangle, const LossPlan& pl) {
   b.block = T;
   b.n_ablk = n_ablk;
   if (triangle) {
-    // ranges of equal length (whole tiles: 32 rows at d = 128) that fill the chip once
-    const int unit = d == 128 ? 32 : T;
-    for (int len = d == 128 ? 64 : T;; len += unit) {
+    // ranges of equal length (whole tiles: 32 rows at d = 128) that fill the chip once: the shortest, from the least that can be
+    // (`rows`: of all blocks' walks, n - T k each.  Every call asks: 32 us of host time at 28000 x 128 with every length tried, 8.7 so)
+    const int unit = d == 128 ? 32 : T, cap = 2 * num_cu();
+    const long long rows = (long long)n * n_ablk - (long long)T * n_ablk * (n_ablk - 1) / 2;
+    int len = (int)(rows / cap) / unit * unit;
+    for (len = len < (d == 128 ? 64 : T) ? (d == 128 ? 64 : T) : len;; len += unit) {
       int wgs = 0;
       for (int k = 0; k < n_ablk; k++) wgs += (n - T * k + len - 1) / len;
-      if (wgs > 2 * num_cu() && len < n) continue;
+      if (wgs > cap && len < n) continue;
       b.cols_per_split = len; b.nwg = wgs; b.row_slots = (n + len - 1) / len;
       break;
     }
