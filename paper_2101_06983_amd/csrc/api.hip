@@ -67,7 +67,7 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
     const bool wide128 = d == 128 && !now;
     // calls with few scores have a gradient kernel of their own (see loss_few.hip); limited workspaces do not
     pl.few_grad = pl.stat_tile && now;
-    const int own = pl.few_grad ? 32 : d > 128 ? 64 : wide128 ? 256 : 128;
+    const int own = pl.few_grad ? kFewOwn : d > 128 ? 64 : wide128 ? 256 : 128;
     const long long obQ = ceil_div(B, own), obP = ceil_div(P, own);
     // NT-Xent on these kernels is one walk (the score matrix is symmetric: see launch_grad_mfma)
     pl.one_walk = ntxent ? 1 : 0;
@@ -252,7 +252,7 @@ static LossPlan choose_plan(int B, int P, int d, gc_dtype dt, bool ntxent, Fits 
   return make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_GENERAL, 1, false, 0.);
 }
 
-// A plan depends on nothing but these arguments; the last ones of a thread, without a limit and with one, are kept (the
+// A plan depends on nothing but these arguments (and num_cu(), one number per process); the last ones of a thread, without a limit and with one, are kept (the
 // search over the splits is some microseconds of host time, and a program asks for the same plan call after call).
 LossPlan make_loss_plan(int B, int P, int d, gc_dtype dt, bool ntxent, size_t limit) {
   struct Kept {

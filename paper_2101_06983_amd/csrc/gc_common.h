@@ -73,6 +73,7 @@ struct LossPlan {
 // fewer splits and then ROUTE_GENERAL; what needs the least is returned where nothing fits (the caller compares `total`).
 constexpr int kStatTile = 32, kStatBlock = 128;
 int stats_block(int B, int P, int d);   // ROUTE_MFMA, d >= 256: edge of a workgroup's scores in the statistics pass, kStatBlock or 256
+constexpr int kFewOwn = 32;          // owner rows of a workgroup of the bf16 gradient kernel for few scores (loss_few.hip)
 constexpr int kFewMergeRows = 256;   // streamed rows of a workgroup of the gradient kernel for short walks that merges statistics
 LossPlan make_loss_plan(int B, int P, int d, gc_dtype dt, bool ntxent, size_t limit = (size_t)-1);
 void plan_planes(LossPlan& pl, int B, int P, int d, gc_dtype dt, int max_splits);

@@ -10,7 +10,7 @@ namespace gc {
 // it has done anything (15 us for 2 workgroups of a 64 x 64 problem): its 60 KB of code, of which a short walk runs every
 // instruction once, come out of L2 line by line.  Per step: 12 + 12 MFMAs a wave at d = 768 and two barriers.
 // ===========================================================================
-constexpr int GF_OWN = 32, GF_T = 32, GF_STAGES = 3;
+constexpr int GF_OWN = kFewOwn, GF_T = 32, GF_STAGES = 3;
 
 template <int D, bool MERGE>
 struct FewCfg {
@@ -30,6 +30,7 @@ struct FewCfg {
   static constexpr int G_OFF = X_OFF + X_BYTES, L_OFF = G_OFF + 2 * 1024;       // coefficients as A fragments [k-step]
   static constexpr int SMEM = L_OFF + (MERGE ? 2 * kFewMergeRows * 4 : 0);      // merged lse2, and pos_idx, of the rows that need one
   static_assert(SMEM <= 160 * 1024, "LDS budget");
+  static_assert(GF_OWN == 32, "a wave's owner rows are one MFMA tile");
 };
 __device__ __forceinline__ int few_swz(int row) { return (((row >> 1) & 1) << 2) | (((row >> 2) & 1) << 1); }
 

@@ -279,7 +279,6 @@ hipError_t grad128_launch(const GradArgs& ga, int nwg, hipStream_t stream);
 hipError_t grad_sym_launch(const GradArgs& ga, int d, int nwg, hipStream_t stream);
 
 // few scores (loss_few.hip)
-constexpr int kFewOwn = 32;   // owner rows per workgroup
 hipError_t grad_few_launch(const GradArgs& ga, const FewMerge& fm, int d, int nwg, hipStream_t stream);
 
 }  // namespace gc
