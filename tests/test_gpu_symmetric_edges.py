@@ -82,6 +82,75 @@ def test_ntxent_loss_alone(n, d):
     check_loss("loss alone n=%d d=%d" % (n, d), loss.item(), want, 1e-5)
 
 
+def both_sides_fp64(q, p, r, temp, mask=False):
+    """Mean of the two directions' losses and its gradients in fp64 on the device, 1024 rows at a time (mask: the diagonal)."""
+    q, p, r, n = q.to(DEV).double(), p.to(DEV).double(), r.to(DEV).long(), q.shape[0]
+
+    def scores(i):
+        s = q[i:i + 1024] @ p.T / temp
+        if mask:
+            k = torch.arange(s.shape[0], device=DEV)
+            s[k, k + i] = -float("inf")
+        return s
+    rows, cols, pos = [], torch.full((n,), -float("inf"), dtype=torch.float64, device=DEV), []
+    for i in range(0, n, 1024):
+        s = scores(i)
+        rows.append(torch.logsumexp(s, 1))
+        cols = torch.logaddexp(cols, torch.logsumexp(s, 0))
+        pos.append(s.gather(1, r[i:i + 1024, None])[:, 0])
+    rows, pos = torch.cat(rows), torch.cat(pos)
+    dq, dp = torch.empty_like(q), torch.zeros_like(p)
+    for i in range(0, n, 1024):
+        s = scores(i)
+        g = 0.5 * (torch.exp(s - rows[i:i + 1024, None]) + torch.exp(s - cols))
+        g[torch.arange(g.shape[0], device=DEV), r[i:i + 1024]] -= 1
+        dq[i:i + 1024] = g @ p / (n * temp)
+        dp += g.T @ q[i:i + 1024] / (n * temp)
+    return (0.5 * (rows.sum() + cols.sum()) - pos.sum()).item() / n, dq, dp
+
+
+# 129 blocks: two passes over the scores again; 32768 x 128: the column sums of 128 blocks do not fit beside the row sums
+@pytest.mark.parametrize("form,n,d", [("ntxent", 32770, 128), ("ntxent", 32768, 128), ("ntxent", 16386, 256), ("symmetric", 16385, 256)])
+def test_symmetric_forms_beyond_one_pass(form, n, d):
+    if form == "ntxent":
+        z = synth.ntxent_views(n, d, seed=9450)
+        loss, dz = gc.gc_ntxent_loss_and_grad_bf16(z.to(DEV), 0.2)
+        want, dq, dp = both_sides_fp64(z, z, torch.arange(n) ^ 1, 0.2, mask=True)
+        got = [(dz, dq + dp)]
+    else:
+        q, p, r = sym_problem(n, d, 9460)
+        out = gc.gc_bidirectional_loss_and_rep_grad_bf16(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.2)
+        loss, (want, dq, dp) = out["loss"], both_sides_fp64(q, p, r, 0.2)
+        got = [(out["dq"], dq), (out["dp"], dp)]
+    torch.cuda.synchronize()
+    check_loss("%s %dx%d loss" % (form, n, d), loss.item(), want, 1e-5)
+    for a, b in got:
+        check("%s %dx%d" % (form, n, d), relerr(to_np(a), to_np(b)), TOL_BF16)
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), -float("inf"), 3e38])
+@pytest.mark.parametrize("d", [128, 256])
+def test_one_pass_with_values_that_are_no_numbers_or_overflow(d, value):
+    """A feature that is no number, is infinite or makes infinite products: every score of its row, and so a score of every
+    column, and with it the loss and all coefficients, are no finite numbers (as with a pass for each side)."""
+    n = 1300
+    q, p, r = sym_problem(n, d, 9470)
+    q[77, 5] = value
+    if value == 3e38:
+        p[:, 5] = 3e38
+    out = gc.gc_bidirectional_loss_and_rep_grad_bf16(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.3)
+    z = synth.ntxent_views(n, d, seed=9480)
+    z[78, 3] = value
+    if value == 3e38:
+        z[:, 3] = 3e38
+    loss, dz = gc.gc_ntxent_loss_and_grad_bf16(z.to(DEV), 0.3)
+    torch.cuda.synchronize()
+    for x in (out["loss"], loss):
+        assert not torch.isfinite(x).any()
+    for x in (out["dq"], out["dp"], dz):
+        assert not torch.isfinite(x).all(dim=1).any()
+
+
 def test_loss_of_a_converged_softmax():
     """Rows whose positive outweighs everything: the loss is log(1 + x), x the others' sum over the positive's term.  x is off
     by ln 2 times the rounding of two logits of size 150 to fp32 (2^-24 * 150 each), 1.3e-5 of it; the bound is 1e-4."""
