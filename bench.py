@@ -259,7 +259,7 @@ def main():
                      "hbm_frac": round(traffic / (prof["ms_stats"] * 1e-3) / PEAK_HBM_BYTES_PER_S, 4) if tr else None,
                      # ... and the whole step's algorithmic bytes (inputs read once, outputs written once)
                      "hbm_frac_algorithmic_whole_step": round(alg_bytes / (ms * 1e-3) / PEAK_HBM_BYTES_PER_S, 4),
-                     "dp_walk": {"kernel": "grad_mfma_kernel<768, false>", "achieved": round(dp_alg, 2),
+                     "dp_walk": {"kernel": "grad_mfma_kernel<768>", "achieved": round(dp_alg, 2),
                                  "frac": round(dp_alg / PEAK_BF16_TFLOPS, 4),
                                  "executed_frac": round(2 * dp_alg / PEAK_BF16_TFLOPS, 4)},
                      "kernel_ms": {"dq_walk_online": round(prof["ms_stats"], 4), "merge_and_dq": round(prof["ms_merge"], 4),

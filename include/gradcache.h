@@ -126,7 +126,8 @@ int gc_loss_and_rep_grad_f32(const float* q, const float* p, const int32_t* pos_
  * the library's device image, one copy per GPU, held until the process ends: the call makes no hipMalloc, hipFree
  * or other allocating call, and its first use on a device only looks the array's address up.  Shapes with
  * gc_workspace_bytes(B, P, d, GC_BF16) > GC_STATIC_SCRATCH_BYTES are rejected with GC_ERR_TOO_LARGE and nothing is
- * enqueued (the limit covers e.g. B = 512, P = 1024, d = 768).  Widths that are no multiple of 128 up to 768 are not
+ * enqueued (the limit covers e.g. B = 512, P = 1024, d = 768; at d = 128 a few shapes named just below the limit are
+ * rejected too: which shapes are taken does not change with the kernels).  Widths that are no multiple of 128 up to 768 are not
  * rejected for their packed inputs: where those do not fit beside the statistics, fewer splits or slower kernels without
  * packed inputs serve the call, and results agree with gc_loss_and_rep_grad_bf16 to fp32 rounding.  Every call on a GPU uses that GPU's one array,
  * which keeps the previous call's contents (the kernels overwrite what they read): two calls that overlap in time
@@ -177,7 +178,8 @@ int gc_profile_end(float* ms_stats, float* ms_merge, float* ms_grad, float* ms_r
  * remark; SimCLR is cited in Related Work): z[n_views,d] bf16, rows already
  * L2-normalised; views 2k and 2k+1 are positives of each other; logits
  * <z_i,z_j>/temp with the self-similarity removed; loss = mean over all n_views
- * anchors; dz[n_views,d] float = gradient w.r.t. z (anchor part + target part).
+ * anchors; dz[n_views,d] float = gradient w.r.t. z (anchor part + target part), or
+ * NULL for the loss alone.
  * workspace: gc_ntxent_workspace_bytes(n_views, d).
  */
 size_t gc_ntxent_workspace_bytes(int n_views, int d);

@@ -125,10 +125,13 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
     pl.few_merge = pl.few_grad && !ntxent && pl.p_stream_len <= kFewMergeRows;
     // fused mode (workspace is planned for it wherever it can run; fused_auto says where it is also the faster one):
     // each walk is a launch of its own and has to fill the GPU alone
-    // (it pays where the statistics pass it replaces is expensive against the extra partial sums: measured faster
-    // from d = 512 and 2^24 scores up, e.g. 0.251 against 0.261 ms at config 3 and 0.156 against 0.226 ms at
-    // B = 1024, P = 16384, and slower below, where launches and partials dominate)
-    // d = 384: a tie at config 3's size, 0.110 against 0.153 ms at B = 1024, P = 16384)
+    // (it pays where the statistics pass it replaces is expensive against the extra partial sums.  A call with it / with
+    // the statistics pass, us:    4096 x 4096   1024 x 16384   4096 x 6000   4096 x 8192   2048 x 16384
+    //   d = 256                   101 / 83      101 / 82       240 / 151     165 / 135     166 / 136
+    //   d = 384                   112 / 108     118 / 117      160 / 176     183 / 187     187 / 197
+    //   d = 512                   131 / 130     141 / 145      188 / 206     212 / 221     220 / 243
+    //   d = 768                   165 / 158     178 / 184      224 / 248     259 / 273     263 / 295
+    // and far slower below 2^24 scores, where launches and partials dominate)
     pl.fused = (d >= 256 && !ntxent) ? 1 : 0;
     pl.fused_auto = (pl.fused && d >= 384 && (long long)B * P >= (1ll << 24)) ? 1 : 0;
     if (pl.fused) {

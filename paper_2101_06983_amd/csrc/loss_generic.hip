@@ -396,7 +396,7 @@ struct SharedList { int anchor[kListLen]; int row[kListLen]; float c[kListLen]; 
 // Some target is the positive of several anchors: every anchor that names one of the rows of this workgroup's elements
 // (first .. last), in index order.  The workgroup looks through the anchors together, 1024 at a time (four a thread, loaded
 // together: at 256 a time each round's loads and barriers are a latency of their own, 14.3 us for the sums of 1021 x 4099 x 384,
-// now XX), and keeps the matches with their coefficients (in index order: ballot and prefix inside a wave, waves one after the
+// now 11.9), and keeps the matches with their coefficients (in index order: ballot and prefix inside a wave, waves one after the
 // other) in LDS; each thread then adds those of its own rows, eight loads in flight.  (A scan by every thread for itself took
 // 179 us there, and 1.0 ms where 2700 anchors share one target of 300.)  Workgroups none of whose rows is named, the most of
 // them, are done at once.

@@ -378,10 +378,15 @@ __global__ void __launch_bounds__(512, BLOCK == kStatBlock ? 4 : 2) stats_mfma_k
 // Statistics pass for few scores: 32 x 32 tiles, the contraction split over the four waves of a workgroup in 64-wide
 // chunks, every operand loaded straight into registers (lane (n, h) takes elements 32 h .. 32 h + 31 of a chunk of its
 // row, so that two lanes use a whole 128-byte line; any order of k works if both operands share it).  Tiles staged through
-// LDS are all latency of dependent k-chunks at these sizes (twelve at d = 768: 23 us at 128 x 256, 26 at 512 x 1024 with
-// 256 x 256 tiles).  Here a wave has all its loads in flight at once: 6.6 and 9.7 us.  It costs B P d / 8 bytes of L2
-// traffic, so the larger tiles win again from about 2^20 scores (64 x 64 tiles in this manner took 37 us at
-// 1021 x 4099 x 384, staged ones of 256 x 256 took 23).
+// LDS are all latency of dependent k-chunks at these sizes; here a wave has all its loads in flight at once: 6.6 us at
+// 128 x 256 x 768.  It costs B P d / 8 bytes of L2 traffic, so that the staged tiles (128 x 128; d = 128: 256 anchors) win again.
+//   loss alone, us (32 x 32 / staged)   2^18 scores   2^19          2^20          2^21
+//     d = 128                           12.3 / 26.0   14.7 / 26.1   15.3 / 26.3   22.0 / 26.8
+//     d = 256                           13.6 / 14.3   14.8 / 14.3   16.9 / 14.4   23.6 / 14.4
+//     d = 512                           13.7 / 15.2   17.0 / 15.5   19.4 / 15.0   29.6 / 16.1
+//     d = 768                           14.3 / 16.6   19.0 / 16.9   22.4 / 16.9   37.0 / 17.3
+// The line, 2^20, is that of the gradient kernel for few scores, which merges these statistics (a call with it instead of a merge
+// and the long walks: 1 to 14 % shorter at 2^20); between 2^18.5 and 2^20 the statistics alone would be 0.5 to 5 us shorter with staged tiles.
 // ===========================================================================
 __global__ void __launch_bounds__(256) stats_small_kernel(StatsSmallArgs g) {
   constexpr int T = kStatTile, PD = 3;
@@ -482,7 +487,8 @@ hipError_t launch_stats_mfma(const LossArgs& a, const LossPlan& pl) {
 
 // ---- statistics of both sides (the symmetric forms) ------------------------------------------------------------------
 // One pass where the plain one does not have its tiles for few scores.  At most 128 blocks: each leaves a partial per column
-// (n^2 / 16 bytes), and they lie where the gradient pass will put its own.
+// (n^2 / 16 bytes), and they lie where the gradient pass will put its own: where that has few splits, and so little room, the
+// plain passes stay as well (`use`; 32768 x 128 for NT-Xent, 16384 x 256 for the symmetric loss).
 BothPlan plan_both(int n, int d, bool triangle, const LossPlan& pl) {
   BothPlan b{};
   const int T = d == 128 ? 256 : kStatBlock, n_ablk = (n + T - 1) / T;

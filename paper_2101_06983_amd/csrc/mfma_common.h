@@ -237,7 +237,7 @@ __device__ __forceinline__ float max_lanes32(float x) {
 // and per column of a tile with the reference 0.  A tile whose sums all lie in these bounds has lost nothing: what 2^t flushes
 // is below 2^-126.  Any other tile (and one with masked scores) takes the maxima of its rows and columns as references.
 // (stats_mfma_kernel: a column's maximum goes back to its lanes by ds_swizzle, and a wave tries the reference 0 again once the
-// references of a tile allow it.  4096 views of 256, logits far beyond: 30 us before that, 20.5 so, 16.5 with the reference 0.)
+// references of a tile allow it.  4096 views of 256, logits far beyond: about 30 us before that, 20.5 so, 16.5 with the reference 0.)
 constexpr float kBothMin = 0x1p-60f, kBothMax = 0x1p100f, kBothMinLog2 = -60.f, kBothMaxLog2 = 100.f;
 struct StatsArgs {
   const unsigned short* Q; const unsigned short* P; const int32_t* pos_idx;
