@@ -122,7 +122,7 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
       search(true, !pl.one_walk, pl.nsq, pl.q_stream_len, pl.nsp, pl.p_stream_len);
     }
     if (pl.one_walk) { pl.nsp = 1; pl.p_stream_len = B; }
-    pl.few_merge = pl.few_grad && !ntxent && pl.p_stream_len <= kFewMergeRows;
+    pl.few_merge = pl.few_grad && !ntxent && pl.p_stream_len <= kFewMergeRows && pl.p_stream_len * pl.stat_splits <= kFewMergeEntries;
     // fused mode (workspace is planned for it wherever it can run; fused_auto says where it is also the faster one):
     // each walk is a launch of its own and has to fill the GPU alone
     // (it pays where the statistics pass it replaces is expensive against the extra partial sums.  A call with it / with

@@ -75,6 +75,9 @@ constexpr int kStatTile = 32, kStatBlock = 128;
 int stats_block(int B, int P, int d);   // ROUTE_MFMA, d >= 256: edge of a workgroup's scores in the statistics pass, kStatBlock or 256
 constexpr int kFewOwn = 32;          // owner rows of a workgroup of the bf16 gradient kernel for few scores (loss_few.hip)
 constexpr int kFewMergeRows = 256;   // streamed rows of a workgroup of the gradient kernel for short walks that merges statistics
+// ... and rows times splits: every workgroup with the dP role reads so many.  Beyond, a launch that merges them once is faster:
+// 512 x 2048 (256 x 64) 2 us, planes of 1024 columns 3.3, 140 x 6000 there (256 x 63) 12; up to it the launch is 1 to 3 us saved.
+constexpr int kFewMergeEntries = 160 * 64;
 LossPlan make_loss_plan(int B, int P, int d, gc_dtype dt, bool ntxent, size_t limit = (size_t)-1);
 void plan_planes(LossPlan& pl, int B, int P, int d, gc_dtype dt, int max_splits);
 

@@ -615,7 +615,7 @@ void plan_planes(LossPlan& pl, int B, int P, int d, gc_dtype dt, int max_splits)
   split_of(stQ, P, pl.nsq, pl.q_stream_len);
   split_of(stP, B, pl.nsp, pl.p_stream_len);
   // (64 owner rows are for many steps a workgroup, where a launch more is nothing: no instantiations of their own)
-  pl.few_merge = pl.stat_tile && pl.px_no == 1 && pl.p_stream_len <= kFewMergeRows;
+  pl.few_merge = pl.stat_tile && pl.px_no == 1 && pl.p_stream_len <= kFewMergeRows && pl.p_stream_len * pl.stat_splits <= kFewMergeEntries;
 }
 
 template <typename T>

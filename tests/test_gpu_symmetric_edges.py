@@ -194,6 +194,21 @@ def test_few_scores(B, P, d):
         assert relerr(to_np(alone[k][k]), to_np(out[k])) <= 1e-5 and alone[k]["loss"].item() == pytest.approx(out["loss"].item(), rel=1e-6)
 
 
+# rows times splits beyond what the gradient kernels merge themselves (and just within): a launch merges the statistics
+@pytest.mark.parametrize("B,P,d,dtype", [(256, 4000, 384, torch.bfloat16), (160, 2048, 128, torch.bfloat16), (161, 2048, 128, torch.bfloat16),
+                                         (140, 6000, 200, torch.bfloat16), (512, 2048, 96, torch.float32)])
+def test_few_scores_of_many_rows_and_splits(B, P, d, dtype):
+    q, p, r = synth.dpr_batch(B, P, d, dtype, seed=9720 + B)
+    want = oracle_loss(q, p, r, 1.0, 0.3)
+    out = gc.gc_loss_and_rep_grad_ex(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.3)
+    torch.cuda.synchronize()
+    check_loss("many splits loss", out["loss"].item(), want["loss"], TOL_F32)
+    check_argmax(to_np(out["argmax"]), want, synth.widen(q), synth.widen(p), 1.0 / 0.3, 1e-5)
+    check("many splits lse", relerr(to_np(out["lse"]), want["lse"]), TOL_F32)
+    for k in ("dq", "dp"):
+        check("many splits %dx%dx%d %s" % (B, P, d, k), relerr(to_np(out[k]), want[k]), TOL_BF16 if d % 128 == 0 else TOL_F32)
+
+
 # more workgroups than run at once: the longer walks are the anchors' / the targets', their numbers a multiple of 8 or not
 @pytest.mark.parametrize("B,P,d", [(128, 8192, 768), (45, 11585, 512), (8190, 128, 384), (11585, 45, 640), (64, 16384, 128)])
 def test_few_scores_beyond_one_round_of_workgroups(B, P, d):
