@@ -92,7 +92,19 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
       const long long n = (walk_q ? obQ * ceil_div(P, q) : 0) + (walk_p ? obP * ceil_div(B, p) : 0);
       const double parts = parts_bytes(walk_q ? ceil_div(P, q) : 0, walk_p ? ceil_div(B, p) : 0);
       const double both = n > kNumCU && per_cu == 2 ? 1.4 : 1.0;
-      const double us = (double)((n + per_cu * kNumCU - 1) / (per_cu * kNumCU)) * (fixed_us + row_us * both * (q > p ? q : p)) + 2.0 * parts / 4e6;
+      const long long slots = (long long)per_cu * kNumCU;
+      double walk_us = (double)((n + slots - 1) / slots) * (fixed_us + row_us * both * (q > p ? q : p));
+      if (pl.few_grad && n > slots) {
+        // The kernel for few scores starts the longer walks first: the longer of one of them, in as many rounds as they take, and an
+        // equal share of all the work with one of the shorter walks behind it.  (A whole round of the longest for the last few short
+        // walks sent 46 x 7607 x 768, 16 walks of 480 rows and 238 of 46, to 8 of 960: 71.4 us a call, 56.7 so, 64.0 with the long walks.)
+        const double uq = walk_q ? fixed_us + row_us * both * q : 0, up = walk_p ? fixed_us + row_us * both * p : 0;
+        const long long wq = walk_q ? obQ * ceil_div(P, q) : 0, wp = n - wq, wl = uq > up ? wq : wp;
+        const double longest = uq > up ? uq : up, alone = longest * (double)((wl + slots - 1) / slots);
+        const double share = (wq * uq + wp * up) / (double)slots + (wq == 0 || wp == 0 ? 0 : uq < up ? uq : up);
+        walk_us = alone > share ? alone : share;
+      }
+      const double us = walk_us + 2.0 * parts / 4e6;
       if (parts <= parts_limit && (best_us == 0 || us < best_us)) {
         best_us = us;
         if (walk_q) { bq = ceil_div(P, q); lq = q; }

@@ -210,7 +210,8 @@ def test_few_scores_of_many_rows_and_splits(B, P, d, dtype):
 
 
 # more workgroups than run at once: the longer walks are the anchors' / the targets', their numbers a multiple of 8 or not
-@pytest.mark.parametrize("B,P,d", [(128, 8192, 768), (45, 11585, 512), (8190, 128, 384), (11585, 45, 640), (64, 16384, 128)])
+@pytest.mark.parametrize("B,P,d", [(128, 8192, 768), (45, 11585, 512), (8190, 128, 384), (11585, 45, 640), (64, 16384, 128),
+                                   (46, 7607, 768), (7426, 70, 640)])
 def test_few_scores_beyond_one_round_of_workgroups(B, P, d):
     q, p, r = synth.dpr_batch(B, P, d, seed=9750 + B, pos_idx=torch.from_numpy(np.random.default_rng(B).integers(0, P, size=B).astype(np.int32)))
     want = oracle_loss(q, p, r, 1.0, 0.3)
