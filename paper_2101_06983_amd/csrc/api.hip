@@ -134,6 +134,11 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
       search(true, !pl.one_walk, pl.nsq, pl.q_stream_len, pl.nsp, pl.p_stream_len);
     }
     if (pl.one_walk) { pl.nsp = 1; pl.p_stream_len = B; }
+    if (pl.few_grad && d > 128) {
+      auto rounds = [&](int n, int own_rows, int splits) { return ceil_div(ceil_div(n, own_rows) * splits, per_cu * kNumCU); };
+      pl.few_not_q = rounds(B, kFewOwn, pl.nsq) > 1 && rounds(B, 64, pl.nsq) == 1;
+      pl.few_not_p = rounds(P, kFewOwn, pl.nsp) > 1 && rounds(P, 64, pl.nsp) == 1;
+    }
     pl.few_merge = pl.few_grad && !ntxent && pl.p_stream_len <= kFewMergeRows && pl.p_stream_len * pl.stat_splits <= kFewMergeEntries;
     // fused mode (workspace is planned for it wherever it can run; fused_auto says where it is also the faster one):
     // each walk is a launch of its own and has to fill the GPU alone

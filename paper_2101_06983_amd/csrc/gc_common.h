@@ -49,6 +49,7 @@ struct LossPlan {
   int route;
   int use_mfma;          // route == ROUTE_MFMA
   int few_grad, few_merge;   // the gradient kernel for short walks (loss_few.hip); it can merge the statistics it needs
+  int few_not_q, few_not_p;  // ... but not for the dQ (dP) role alone, see few_kernel
   int one_walk;          // NT-Xent on the MFMA kernels: dz from a single walk (no dP role, no dP partials)
   int stat_splits;       // column (target) ranges of the statistics pass
   int stat_cols_per_split;
@@ -156,8 +157,16 @@ struct PosFix {
   float scale;
 };
 
+// The gradient kernel for few scores serves this call.  It owns half as many rows as the long walks: a call for one gradient alone
+// that takes it two rounds of workgroups, and them one, is theirs (dp of 100 x 10000 x 512 51.7 us, 45.7 so; dq of 10000 x 100 x 512
+// 48.0 and 43.3; not at d = 128: dp of 16 x 20000 33.2 and 35.2).
+inline bool few_kernel(const LossArgs& a, const LossPlan& pl) {
+  return pl.few_grad && (a.dz || (a.dq ? a.dp || !pl.few_not_q : !pl.few_not_p));
+}
 // The gradient kernel of this call merges the split statistics: one launch less.  (The dQ role writes what the merge would.)
-inline bool merges_itself(const LossArgs& a, const LossPlan& pl) { return pl.few_merge && a.dq && !a.lse2_t && !a.wexp && !a.dz; }
+inline bool merges_itself(const LossArgs& a, const LossPlan& pl) {
+  return pl.few_merge && (pl.route != ROUTE_MFMA || few_kernel(a, pl)) && a.dq && !a.lse2_t && !a.wexp && !a.dz;
+}
 
 inline void BothPlan::partials(const LossArgs& a, const LossPlan& pl, float*& row_m, float*& row_l, float*& col_m, float*& col_l) const {
   row_m = (float*)(a.ws + pl.off_dq_part);   // (the gradient pass writes there later)

@@ -83,7 +83,8 @@ hipError_t launch_grad_mfma(const LossArgs& a, const LossPlan& pl) {
   if (one_walk) { ga.lse2_t = ga.lse2; ga.wexp_t = ga.wexp; ga.out_scale *= 2.f; }
   const bool want_q = a.dq || a.dz, want_p = (a.dp || a.dz) && !one_walk;
   const size_t nq = (size_t)a.B * a.d, np = (size_t)a.P * a.d;
-  const int own = pl.few_grad ? kFewOwn : (a.d == 128) ? G1_OWN : GR_OWN;   // owner rows per workgroup
+  const bool few = few_kernel(a, pl);
+  const int own = few ? kFewOwn : (a.d == 128) ? G1_OWN : GR_OWN;   // owner rows per workgroup
   ga.obQ = want_q ? (a.B + own - 1) / own : 0; ga.nsq = pl.nsq; ga.q_stream_len = pl.q_stream_len;
   ga.obP = want_p ? (a.P + own - 1) / own : 0; ga.nsp = pl.nsp; ga.p_stream_len = pl.p_stream_len;
   // every output goes through the kernel that sums the split partials (a single split included): it adds the
@@ -102,7 +103,7 @@ hipError_t launch_grad_mfma(const LossArgs& a, const LossPlan& pl) {
     ga.pos_pad = a.pos_idx;
     fm = few_merge_args(a, pl);
   }
-  if (pl.few_grad) e = grad_few_launch(ga, fm, a.d, nwg, a.stream);
+  if (few) e = grad_few_launch(ga, fm, a.d, nwg, a.stream);
   else if (a.d == 128) e = grad128_launch(ga, nwg, a.stream);
   else if (ga.lse2_t) e = grad_sym_launch(ga, a.d, nwg, a.stream);
   else switch (a.d) {

@@ -194,6 +194,20 @@ def test_few_scores(B, P, d):
         assert relerr(to_np(alone[k][k]), to_np(out[k])) <= 1e-5 and alone[k]["loss"].item() == pytest.approx(out["loss"].item(), rel=1e-6)
 
 
+# one gradient alone, for which the kernel for few scores would need two rounds of workgroups: the long walks
+@pytest.mark.parametrize("B,P,d,want_", [(69, 9315, 384, "dp"), (33, 8200, 768, "dp"), (9315, 69, 384, "dq"), (8250, 40, 640, "dq"), (30, 17000, 256, "dp")])
+def test_one_gradient_of_few_scores_beyond_a_round(B, P, d, want_):
+    q, p, r = synth.dpr_batch(B, P, d, seed=9730 + B, pos_idx=torch.from_numpy(np.random.default_rng(B).integers(0, P, size=B).astype(np.int32)))
+    want = oracle_loss(q, p, r, 1.0, 0.3)
+    for flags in (0, gc.GC_PATH_STATS_PASS):
+        out = gc.gc_loss_and_rep_grad_ex(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.3, flags, ("loss", "lse", "argmax", want_))
+        torch.cuda.synchronize()
+        check_loss("one gradient loss", out["loss"].item(), want["loss"], TOL_F32)
+        check("one gradient lse", relerr(to_np(out["lse"]), want["lse"]), TOL_F32)
+        check_argmax(to_np(out["argmax"]), want, synth.widen(q), synth.widen(p), 1.0 / 0.3, 1e-5)
+        check("one gradient %dx%dx%d %s" % (B, P, d, want_), relerr(to_np(out[want_]), want[want_]), TOL_BF16)
+
+
 # rows times splits beyond what the gradient kernels merge themselves (and just within): a launch merges the statistics
 @pytest.mark.parametrize("B,P,d,dtype", [(256, 4000, 384, torch.bfloat16), (160, 2048, 128, torch.bfloat16), (161, 2048, 128, torch.bfloat16),
                                          (140, 6000, 200, torch.bfloat16), (512, 2048, 96, torch.float32)])
