@@ -60,6 +60,23 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
       if (splits > 64) splits = 64;
       if (splits > tiles) splits = tiles;
       if (splits < 1) splits = 1;
+      if (mid && n_ablk * ceil_div(tiles, ceil_div(tiles, splits)) > 2 * kNumCU) {
+        // A few workgroups more than run at once can be a second round (544 at 8642 x 7000 x 512: 115 us for the loss alone; 7 splits,
+        // 476 workgroups: 79).  The splits with the least time, in tiles and half a one for a workgroup's start: whole rounds, then
+        // the last split's workgroups, which have `rest` tiles, on the places that are left and, those beyond, behind one another.
+        // (A multiple of 8 workgroups is dealt to the XCDs in contiguous ranges: most of them then have no short ones, and one more
+        // than they have places for is a round, 0.65 of one where the places are half empty.)
+        double best = 0;
+        for (int s = 1; s <= 64 && s <= tiles; s++) {
+          const int cap = 2 * kNumCU, per = ceil_div(tiles, s), full = ceil_div(tiles, per) - 1, rest = tiles - full * per;
+          const int in = n_ablk * full % cap, left = in + n_ablk - cap;
+          const double first = in ? per + 0.5 : rest + 0.5, behind = left > 0 ? (rest + 0.5) * (1 + 0.9 * ceil_div(left, cap)) : 0;
+          double t = (per + 0.5) * (n_ablk * full / cap) + (first > behind ? first : behind);
+          const int wgs = n_ablk * (full + 1), last = wgs % cap;
+          if (wgs % 8 == 0) t = (per + 0.5) * (wgs / cap + (last == 0 ? 0. : last <= cap / 2 ? 0.65 : 1.));
+          if (best == 0 || t < best) { best = t; splits = s; }
+        }
+      }
       pl.stat_cols_per_split = ceil_div(tiles, splits) * T;
       pl.stat_splits = ceil_div(P, pl.stat_cols_per_split);
     }
