@@ -36,10 +36,11 @@ static long long equal_share(long long rows) {
 }
 // few, parts_limit, equal: ROUTE_MFMA.  few: small statistics tiles where the scores are few.  Splits: the fastest whose
 // partials stay below parts_limit bytes, or (equal) the fewest that give every compute unit an equal share of the rows.
+// fewer_stats: as many splits of the statistics as with blocks of 256, two of which share no compute unit.
 // now: the gradient kernels as they are.  Without it, as in the plans for a limited workspace, the blocks and costs that decide
 // the splits are those of the walks with 64 rows (d = 128: 256 rows), so that the sizes taken do not change with the kernels.
 static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent, int route, int max_splits, bool few, double parts_limit,
-                                   bool equal = false, bool now = false) {
+                                   bool equal = false, bool now = false, bool fewer_stats = false) {
   LossPlan pl{};
   const int kNumCU = num_cu();
   pl.route = route;
@@ -54,7 +55,7 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
       pl.stat_splits = ceil_div(tiles, per);
     } else {
       // two workgroups to a CU, blocks of 256 anchors at d = 128; without `few`: one of 256 x 256 scores, for fewer partials
-      const bool mid = few && d > 128 && stats_block(B, P, d) == kStatBlock;
+      const bool mid = few && !fewer_stats && d > 128 && stats_block(B, P, d) == kStatBlock;
       const int T = mid ? kStatBlock : 256, n_ablk = ceil_div(B, T), tiles = ceil_div(P, T);
       int splits = ceil_div(mid || d == 128 ? 2 * kNumCU : kNumCU, n_ablk);
       if (splits > 64) splits = 64;
@@ -255,8 +256,8 @@ template <class Fits>
 static LossPlan choose_plan(int B, int P, int d, gc_dtype dt, bool ntxent, Fits fits) {
   if (dt == GC_BF16 && d % 128 == 0 && d >= 128 && d <= 768) {
     const double parts = equal_parts(B, P, d, ntxent);
-    auto plan = [&](bool few, double parts_limit, bool equal, bool now = false) {
-      return make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_MFMA, 16, few, parts_limit, equal, now);
+    auto plan = [&](bool few, double parts_limit, bool equal, bool now = false, bool fewer_stats = false) {
+      return make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_MFMA, 16, few, parts_limit, equal, now, fewer_stats);
     };
     LossPlan pl = plan(true, 1e300, false, true);
     const size_t fixed = (size_t)GC_STATIC_SCRATCH_BYTES;
@@ -275,6 +276,13 @@ static LossPlan choose_plan(int B, int P, int d, gc_dtype dt, bool ntxent, Fits 
       }
     }
     if (fits(pl)) return pl;
+    // the same with fewer splits.  (A workspace that an earlier version named is often just short of the present one: with the
+    // plans below 5750 x 10557 x 384 took 388 us a call in it and 1621 x 13677 x 256, dq alone, 114; 330 and 74 so.)
+    const double now_bytes = (double)(pl.off_on_ref - pl.off_dq_part);
+    for (const double part : {1., 0.95, 0.85, 0.7, 0.55, 0.4, 0.3, 0.2, 0.1}) {
+      pl = plan(true, part * now_bytes, false, true, true);
+      if (fits(pl)) return pl;
+    }
     for (const bool few : {true, false}) {
       pl = plan(few, parts, false);
       if (fits(pl)) return pl;

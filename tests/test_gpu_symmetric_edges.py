@@ -302,3 +302,34 @@ def test_the_same_bits_run_after_run(entry, n, d, runs):
     first = [t.clone() for t in call()]
     for _ in range(runs):
         assert all(torch.equal(a, b) for a, b in zip(call(), first))
+
+
+# a little, somewhat and much less than the named workspace: the same kernels with fewer splits, then those that need less
+@pytest.mark.parametrize("share", [0.99, 0.9, 0.6])
+@pytest.mark.parametrize("kind,B,P,d", [("ex", 700, 900, 384), ("ex", 512, 1024, 128), ("ex", 300, 3000, 256), ("ex", 1100, 2100, 256),
+                                        ("ex", 1500, 1500, 128), ("symmetric", 1300, 1300, 256), ("ntxent", 1500, 1500, 128)])
+def test_somewhat_less_than_the_named_workspace(kind, B, P, d, share):
+    lib = gc.load()
+    named = {"ex": lambda: gc.gc_workspace_bytes(B, P, d, gc.GC_BF16), "ntxent": lambda: lib.gc_ntxent_workspace_bytes(B, d),
+             "symmetric": lambda: lib.gc_bidirectional_workspace_bytes(B, d)}[kind]()
+    nbytes = int(named * share) // 256 * 256
+    buf = torch.full((nbytes + 8192,), 0xA5, dtype=torch.uint8, device=DEV)
+    q, p, r = sym_problem(B, d, 9950) if kind == "symmetric" else synth.dpr_batch(B, P, d, seed=9950, positive_mix=0.3)
+    if kind == "ex":
+        call = lambda ws: gc.gc_loss_and_rep_grad_ex(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.3, 0, ("loss", "dq", "dp", "lse"), ws)
+    elif kind == "symmetric":
+        call = lambda ws: gc.gc_bidirectional_loss_and_rep_grad_bf16(q.to(DEV), p.to(DEV), r.to(DEV), 1.0, 0.3, ws)
+    else:
+        z = synth.ntxent_views(B, d, seed=9951).to(DEV)
+        call = lambda ws: dict(zip(("loss", "dq"), gc.gc_ntxent_loss_and_grad_bf16(z, 0.2, ws)))
+    whole = call(None)   # (held to the oracle elsewhere)
+    try:
+        less = call(buf[:nbytes])
+    except gc.GradCacheError as e:
+        assert e.status == gc.GC_ERR_WORKSPACE and share == 0.6
+        return
+    torch.cuda.synchronize()
+    assert bool((buf[nbytes:] == 0xA5).all())
+    for k in ("loss", "dq", "dp", "lse"):
+        if k in whole:
+            check("%s %dx%dx%d at %g %s" % (kind, B, P, d, share, k), relerr(to_np(less[k]), to_np(whole[k])), 2 * TOL_BF16 if k[0] == "d" else TOL_F32)
