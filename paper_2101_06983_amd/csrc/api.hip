@@ -36,11 +36,12 @@ static long long equal_share(long long rows) {
 }
 // few, parts_limit, equal: ROUTE_MFMA.  few: small statistics tiles where the scores are few.  Splits: the fastest whose
 // partials stay below parts_limit bytes, or (equal) the fewest that give every compute unit an equal share of the rows.
-// fewer_stats: as many splits of the statistics as with blocks of 256, two of which share no compute unit.
+// lean: 1: as many splits of the statistics as with blocks of 256, two of which share no compute unit; 2: and a second round of
+// workgroups priced as a whole one, which takes fewer splits.
 // now: the gradient kernels as they are.  Without it, as in the plans for a limited workspace, the blocks and costs that decide
 // the splits are those of the walks with 64 rows (d = 128: 256 rows), so that the sizes taken do not change with the kernels.
 static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent, int route, int max_splits, bool few, double parts_limit,
-                                   bool equal = false, bool now = false, bool fewer_stats = false) {
+                                   bool equal = false, bool now = false, int lean = 0) {
   LossPlan pl{};
   const int kNumCU = num_cu();
   pl.route = route;
@@ -55,7 +56,7 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
       pl.stat_splits = ceil_div(tiles, per);
     } else {
       // two workgroups to a CU, blocks of 256 anchors at d = 128; without `few`: one of 256 x 256 scores, for fewer partials
-      const bool mid = few && !fewer_stats && d > 128 && stats_block(B, P, d) == kStatBlock;
+      const bool mid = few && !lean && d > 128 && stats_block(B, P, d) == kStatBlock;
       const int T = mid ? kStatBlock : 256, n_ablk = ceil_div(B, T), tiles = ceil_div(P, T);
       int splits = ceil_div(mid || d == 128 ? 2 * kNumCU : kNumCU, n_ablk);
       if (splits > 64) splits = 64;
@@ -112,7 +113,7 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
       const double both = n > kNumCU && per_cu == 2 ? 1.4 : 1.0;
       const long long slots = (long long)per_cu * kNumCU;
       double walk_us = (double)((n + slots - 1) / slots) * (fixed_us + row_us * both * (q > p ? q : p));
-      if (pl.few_grad && n > slots) {
+      if (pl.few_grad && n > slots && lean < 2) {
         // The kernel for few scores starts the longer walks first: the longer of one of them, in as many rounds as they take, and an
         // equal share of all the work with one of the shorter walks behind it.  (A whole round of the longest for the last few short
         // walks sent 46 x 7607 x 768, 16 walks of 480 rows and 238 of 46, to 8 of 960: 71.4 us a call, 56.7 so, 64.0 with the long walks.)
@@ -256,38 +257,45 @@ template <class Fits>
 static LossPlan choose_plan(int B, int P, int d, gc_dtype dt, bool ntxent, Fits fits) {
   if (dt == GC_BF16 && d % 128 == 0 && d >= 128 && d <= 768) {
     const double parts = equal_parts(B, P, d, ntxent);
-    auto plan = [&](bool few, double parts_limit, bool equal, bool now = false, bool fewer_stats = false) {
-      return make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_MFMA, 16, few, parts_limit, equal, now, fewer_stats);
+    auto plan = [&](bool few, double parts_limit, bool equal, bool now = false, int lean = 0) {
+      return make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_MFMA, 16, few, parts_limit, equal, now, lean);
     };
-    LossPlan pl = plan(true, 1e300, false, true);
     const size_t fixed = (size_t)GC_STATIC_SCRATCH_BYTES;
-    if (pl.total > fixed && pl.few_grad && static_takes(B, P, d)) {   // fewer splits of the same kernel, if they fit it
-      const double now_parts = parts_bytes_of(pl, B, P, d), room = (double)fixed - ((double)pl.total - now_parts);
-      const LossPlan less = plan(true, room, false, true);
-      if (less.total <= fixed) pl = less;
-    }
-    if (pl.total > (size_t)GC_STATIC_SCRATCH_BYTES) {
-      // the shapes that the entry point with the fixed array takes do not depend on the splits: those that fit with an
-      // equal share of the rows per compute unit, at least 256 of them, get splits that fit
-      const LossPlan lean = plan(false, parts, false);
-      if (lean.total <= (size_t)GC_STATIC_SCRATCH_BYTES) {
-        const LossPlan both = plan(true, parts, false);
-        pl = both.total <= (size_t)GC_STATIC_SCRATCH_BYTES ? both : lean;
+    auto first = [&](int lean) {
+      LossPlan pl = plan(true, 1e300, false, true, lean);
+      if (pl.total > fixed && pl.few_grad && static_takes(B, P, d)) {   // fewer splits of the same kernel, if they fit it
+        const double now_parts = parts_bytes_of(pl, B, P, d), room = (double)fixed - ((double)pl.total - now_parts);
+        const LossPlan less = plan(true, room, false, true, lean);
+        if (less.total <= fixed) pl = less;
       }
-    }
+      if (pl.total > fixed) {
+        // the shapes that the entry point with the fixed array takes do not depend on the splits: those that fit with an
+        // equal share of the rows per compute unit, at least 256 of them, get splits that fit
+        const LossPlan share = plan(false, parts, false);
+        if (share.total <= fixed) {
+          const LossPlan both = plan(true, parts, false);
+          pl = both.total <= fixed ? both : share;
+        }
+      }
+      return pl;
+    };
+    LossPlan pl = first(0);
     if (fits(pl)) return pl;
-    // the same with fewer splits.  (A workspace that an earlier version named is often just short of the present one: with the
-    // plans below 5750 x 10557 x 384 took 388 us a call in it and 1621 x 13677 x 256, dq alone, 114; 330 and 74 so.)
+    // What a call needs at least does not change with the kernels: one of these has to fit.
+    const LossPlan least[] = {first(2), plan(true, parts, false), plan(false, parts, false), plan(false, parts, true)};
+    const LossPlan* fit = nullptr;
+    for (const LossPlan& l : least)
+      if (!fit && fits(l)) fit = &l;
+    if (!fit) return least[3];
+    // Then the first plan again with fewer splits.  (A workspace that an earlier version named is often just short of the present one:
+    // with the plans above 5750 x 10557 x 384 took 388 us a call in it and 1621 x 13677 x 256, dq alone, 114; 330 and 74 so.)
     const double now_bytes = (double)(pl.off_on_ref - pl.off_dq_part);
     for (const double part : {1., 0.95, 0.85, 0.7, 0.55, 0.4, 0.3, 0.2, 0.1}) {
-      pl = plan(true, part * now_bytes, false, true, true);
+      pl = plan(true, part * now_bytes, false, true, 1);
+      if (pl.total < fit->total) pl.total = fit->total;   // (asked again with this plan's size as the limit: the same plan)
       if (fits(pl)) return pl;
     }
-    for (const bool few : {true, false}) {
-      pl = plan(few, parts, false);
-      if (fits(pl)) return pl;
-    }
-    return plan(false, parts, true);
+    return *fit;
   }
   if (tiny_fits(B, P, d)) return make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_TINY, 1, false, 0.);
   for (int splits = 16; splits >= 1; splits /= 2) {

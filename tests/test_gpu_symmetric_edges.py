@@ -304,10 +304,11 @@ def test_the_same_bits_run_after_run(entry, n, d, runs):
         assert all(torch.equal(a, b) for a, b in zip(call(), first))
 
 
-# a little, somewhat and much less than the named workspace: the same kernels with fewer splits, then those that need less
-@pytest.mark.parametrize("share", [0.99, 0.9, 0.6])
-@pytest.mark.parametrize("kind,B,P,d", [("ex", 700, 900, 384), ("ex", 512, 1024, 128), ("ex", 300, 3000, 256), ("ex", 1100, 2100, 256),
-                                        ("ex", 1500, 1500, 128), ("symmetric", 1300, 1300, 256), ("ntxent", 1500, 1500, 128)])
+# less than the named workspace, down to about the least that is taken: the same kernels with fewer splits, then others
+@pytest.mark.parametrize("kind,B,P,d,share", [("ex", 700, 900, 384, 0.99), ("ex", 700, 900, 384, 0.8), ("ex", 512, 1024, 128, 0.9), ("ex", 512, 1024, 128, 0.5),
+                                              ("ex", 300, 3000, 256, 0.985), ("ex", 1621, 3700, 256, 0.99), ("ex", 2000, 3000, 384, 0.987),
+                                              ("symmetric", 700, 700, 512, 0.9), ("symmetric", 700, 700, 512, 0.75), ("symmetric", 1300, 1300, 256, 0.993),
+                                              ("ntxent", 1500, 1500, 128, 0.9), ("ntxent", 1500, 1500, 128, 0.77), ("ntxent", 700, 700, 512, 0.6)])
 def test_somewhat_less_than_the_named_workspace(kind, B, P, d, share):
     lib = gc.load()
     named = {"ex": lambda: gc.gc_workspace_bytes(B, P, d, gc.GC_BF16), "ntxent": lambda: lib.gc_ntxent_workspace_bytes(B, d),
@@ -323,11 +324,7 @@ def test_somewhat_less_than_the_named_workspace(kind, B, P, d, share):
         z = synth.ntxent_views(B, d, seed=9951).to(DEV)
         call = lambda ws: dict(zip(("loss", "dq"), gc.gc_ntxent_loss_and_grad_bf16(z, 0.2, ws)))
     whole = call(None)   # (held to the oracle elsewhere)
-    try:
-        less = call(buf[:nbytes])
-    except gc.GradCacheError as e:
-        assert e.status == gc.GC_ERR_WORKSPACE and share == 0.6
-        return
+    less = call(buf[:nbytes])
     torch.cuda.synchronize()
     assert bool((buf[nbytes:] == 0xA5).all())
     for k in ("loss", "dq", "dp", "lse"):
