@@ -9,7 +9,7 @@
  * stand-in two-layer MLP encoder: the graph-less forward (Step 1) and the
  * per-sub-batch re-encode + backward of the cached rows (Step 3, Eq. 8-9).
  * The B x P score matrix is not written to device memory, but for calls of at
- * most 2^20 scores, which keep it in the workspace from a width on.
+ * most 2^20 scores in fp32 or of a general width, which keep it in the workspace.
  *
  * Conventions for every entry point
  *   - All tensor pointers are DEVICE pointers unless marked "host".  Matrices

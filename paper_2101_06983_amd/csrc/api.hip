@@ -282,12 +282,6 @@ static LossPlan choose_plan(int B, int P, int d, gc_dtype dt, bool ntxent, Fits 
       return pl;
     };
     LossPlan pl = first(0);
-    // Room for the scores comes on top (what the entry point with the fixed array takes does not change with it).
-    if (pl.few_grad && !ntxent && d >= kFewStoredWidth) {
-      LossPlan st = pl;
-      st.px_stored = 1; st.off_scores = st.total; st.total += scores_bytes(B, P);
-      if ((st.total <= fixed || pl.total > fixed) && fits(st)) return st;
-    }
     if (fits(pl)) return pl;
     // What a call needs at least does not change with the kernels: one of these has to fit.
     const LossPlan least[] = {first(2), plan(true, parts, false), plan(false, parts, false), plan(false, parts, true)};
@@ -486,7 +480,6 @@ static int run_loss(const LossArgs& a_in, const LossPlan& pl) {
       LossArgs b = a;
       LossPlan pb = pl;
       b.dq = nullptr;
-      pb.px_stored = 0;   // (no statistics pass has left them)
       pb.nsp = pl.fz_nsp; pb.p_stream_len = pl.fz_p_stream_len;
       b.loss_with_partials = true;   // the dP walk always ends in the sum of its partials
       loss_done = true;

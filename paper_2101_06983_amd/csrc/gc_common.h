@@ -80,8 +80,7 @@ constexpr int kFewMergeRows = 256;   // streamed rows of a workgroup of the grad
 // 512 x 2048 (256 x 64) 2 us, planes of 1024 columns 3.3, 140 x 6000 there (256 x 63) 12; up to it the launch is 1 to 3 us saved.
 constexpr int kFewMergeEntries = 160 * 64;
 LossPlan make_loss_plan(int B, int P, int d, gc_dtype dt, bool ntxent, size_t limit = (size_t)-1);
-constexpr int kFewStoredWidth = 256;   // ROUTE_MFMA: least width whose few scores are stored (see grad_few_body)
-// Stored scores (few scores): tiles of 32 x 32.
+// Stored scores (ROUTE_PLANES, few scores): tiles of 32 x 32.
 inline size_t scores_bytes(int B, int P) { return (size_t)((B + kStatTile - 1) / kStatTile) * ((P + kStatTile - 1) / kStatTile) * (kStatTile * kStatTile * 4); }
 void plan_planes(LossPlan& pl, int B, int P, int d, gc_dtype dt, int max_splits);
 
@@ -166,9 +165,9 @@ struct PosFix {
 inline bool few_kernel(const LossArgs& a, const LossPlan& pl) {
   return pl.few_grad && (a.dz || (a.dq ? a.dp || !pl.few_not_q : !pl.few_not_p));
 }
-// The statistics of this call leave the scores, which its gradients read (stored_planes_grad_kernel, grad_few_kernel<STORED>).
+// The statistics of this call leave the scores, which its gradients read (stored_planes_grad_kernel).
 inline bool grads_from_scores(const LossArgs& a, const LossPlan& pl) {
-  return pl.px_stored && (pl.route != ROUTE_MFMA || few_kernel(a, pl)) && (a.dq || a.dp) && !a.dz && !a.lse2_t && !a.wexp && !a.both && !a.defer_loss_sum && !a.sym[0];
+  return pl.px_stored && (a.dq || a.dp) && !a.dz && !a.lse2_t && !a.wexp && !a.both && !a.defer_loss_sum && !a.sym[0];
 }
 // The gradient kernel of this call merges the split statistics: one launch less.  (It writes what the merge would.)
 inline bool merges_itself(const LossArgs& a, const LossPlan& pl) {

@@ -35,14 +35,7 @@ struct FewCfg {
 __device__ __forceinline__ int few_swz(int row) { return (((row >> 1) & 1) << 2) | (((row >> 2) & 1) << 1); }
 
 // MERGE: the statistics come as splits, see StatMerge.
-// STORED: the statistics have left the scores, and each wave's 1 KB of a tile's rides in a ring where the partial scores would meet:
-// no first contraction, no owner rows, no exchange.  A whole call with the scores formed again and so, us (in a graph, back to back):
-//   d      128 x 256     512 x 1024    64 x 8192     8192 x 64     1000 x 1040
-//   256    13.9  13.3    21.9  22.0    34.8  31.7    110   109     34.3  34.2
-//   512    17.2  16.0    30.6  29.8    51.6  45.5    92.8  87.6    47.1  47.5
-//   768    19.9  17.7    38.1  34.3    59.5  51.4    103   94.8    54.5  48.9
-// At d = 128, where a wave's first contraction is two MFMAs, 1000 x 1040 lost (27.8 and 29.3): from 256 on.
-template <int D, bool OWNER_IS_Q, bool SYM, bool MERGE, bool STORED>
+template <int D, bool OWNER_IS_Q, bool SYM, bool MERGE>
 __device__ __forceinline__ void grad_few_body(const GradArgs& ga, const FewMerge& fm, int oblk, int split, unsigned char* smem) {
   using C = FewCfg<D, MERGE>;
   constexpr bool STR_STATS = (SYM || !OWNER_IS_Q) && !MERGE;   // they ride in the stage
@@ -75,16 +68,8 @@ __device__ __forceinline__ void grad_few_body(const GradArgs& ga, const FewMerge
   for (int it = 0; it < C::NP; it++) src_off[it] = slot_src(it, GF_T - 1);
   // lanes 0-1 load lse_str of rows 8 w .. 8 w + 7 of the tile, lanes 2-3 pos_pad (dP role)
   const unsigned ri_off = 32u * w + 16u * (lane & 1) + ((lane & 2) && !OWNER_IS_Q ? (unsigned)((const char*)ga.pos_pad - (const char*)lse_str) : 0u);
-  // STORED: the scores of streamed rows 8 w .. 8 w + 7, see StatTile::tile; dQ role: as they lie, dP role: lane 8 i + k takes
-  // targets 4 i .. 4 i + 3 of anchor 8 w + k
-  const unsigned sc_lds = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)smem) + C::X_OFF + w * 1024;   // + 4 KB a stage
-  const unsigned sc_off = OWNER_IS_Q ? 1024u * w + 16u * lane : 512u * (lane >> 3) + 16u * (8 * w + (lane & 7));
   auto prefetch = [&](int u, int stage) __attribute__((always_inline)) {
     const int t0 = sbeg + u * GF_T;
-    if constexpr (STORED) {
-      const size_t t = t0 / GF_T;
-      dma_group<1>(ga.scores + (OWNER_IS_Q ? t * ga.n_ablk + oblk : (size_t)oblk * ga.n_ablk + t) * (GF_T * GF_OWN), &sc_off, sc_lds + stage * 4096);
-    }
     const unsigned short* tile = R + (size_t)t0 * D;
     const unsigned lds = ring + stage * C::STAGE;
     if (STR_STATS && lane < 4) dma_piece<0>(lse_str + t0, ri_off, lds);
@@ -100,12 +85,11 @@ __device__ __forceinline__ void grad_few_body(const GradArgs& ga, const FewMerge
     }
   };
   SharedCheck chk(ga);
-  constexpr int FIRST = STORED && MERGE ? GF_STAGES - 1 : GF_STAGES;   // (the merge works in the last stage's place for scores)
-  for (int u = 0; u < min(nt, FIRST); u++) prefetch(u, u);
+  for (int u = 0; u < min(nt, GF_STAGES); u++) prefetch(u, u);
 
   // owner slice as phase-1 B fragments: lane (ln, h) holds owner row ln, columns w DS + 16 ks + 8 h .. + 7
   bf16x8 ofrag[C::KS];
-  if constexpr (!STORED) {
+  {
     const int row = min(a0 + ln, No - 1);
 #pragma unroll
     for (int ks = 0; ks < C::KS; ks++) ofrag[ks] = *(const bf16x8*)(O + (size_t)row * D + w * C::DS + 16 * ks + 8 * h);
@@ -121,16 +105,13 @@ __device__ __forceinline__ void grad_few_body(const GradArgs& ga, const FewMerge
   int* const lds_pos = (int*)(smem + C::L_OFF) + kFewMergeRows;
   if constexpr (MERGE) {
     StatMerge<false> sm(fm, ga.pos_pad, ga.B, OWNER_IS_Q ? a0 : sbeg, OWNER_IS_Q ? GF_OWN : send - sbeg, OWNER_IS_Q && split == 0);
-    sm.finish(fm, ga.B, ga.Pn, (float*)(smem + C::X_OFF + (STORED ? C::X_BYTES - 3072 : 0)), lds_lse, lds_pos, nullptr);   // (the partial scores are not there yet)
+    sm.finish(fm, ga.B, ga.Pn, (float*)(smem + C::X_OFF), lds_lse, lds_pos, nullptr);   // (the partial scores are not there yet)
     if (OWNER_IS_Q) lse_a = lds_lse[ln];
   }
-  if constexpr (!STORED) {
 #pragma unroll
-    for (int ks = 0; ks < C::KS; ks++) asm volatile("" : "+v"(ofrag[ks]));   // the compiler's own loads end here
-  }
+  for (int ks = 0; ks < C::KS; ks++) asm volatile("" : "+v"(ofrag[ks]));   // the compiler's own loads end here
   asm volatile("" : "+v"(lse_a), "+v"(r_a));
   chk.look(ga);
-  if (FIRST < GF_STAGES && FIRST < nt) prefetch(FIRST, FIRST);
 
   // per-lane LDS addresses (see lane_base of the walks): + stage, + 64 i for chunk 4 i + j
   auto lane_base = [&](int row, int j, int parity) __attribute__((always_inline)) -> unsigned {
@@ -155,7 +136,7 @@ __device__ __forceinline__ void grad_few_body(const GradArgs& ga, const FewMerge
 
   // ---- a step: the partial scores of tile u meet while phase 1 of tile u + 1 runs, the coefficients of tile u are published,
   // phase 2 of tile u.  What only needs the tile itself is read ahead of the barriers.
-  constexpr int PER = C::NI + (STR_STATS ? 1 : 0) + (STORED ? 1 : 0);   // loads of a tile
+  constexpr int PER = C::NI + (STR_STATS ? 1 : 0);   // loads of a tile
   bf16x8 afr[C::KS], bfr[C::CT][2];
   f32x16 s;
   auto load_a = [&](unsigned so) __attribute__((always_inline)) {
@@ -178,21 +159,18 @@ __device__ __forceinline__ void grad_few_body(const GradArgs& ga, const FewMerge
       else *(f32x4*)(smem + C::X_OFF + j * 3072 + ((w ^ j) - 1) * 1024 + lane * 16) = v;
     }
   };
-  if constexpr (!STORED) {
-    if (nt > 2) wait_vmem<2 * PER>();
-    else if (nt > 1) wait_vmem<PER>();
-    else wait_vmem<0>();
-    load_a(0);
-    phase1();
-    publish_s();
-  }
+  if (nt > 2) wait_vmem<2 * PER>();
+  else if (nt > 1) wait_vmem<PER>();
+  else wait_vmem<0>();
+  load_a(0);
+  phase1();
+  publish_s();
   int stage = 0;
 #pragma unroll 1
   for (int u = 0; u < nt; u++) {
     const int stage1 = stage + 1 == GF_STAGES ? 0 : stage + 1;
     const unsigned so = stage * C::STAGE;
-    if (STORED && u + 2 < nt) wait_vmem<2 * PER>();   // tile u has landed
-    else if (STORED ? u + 1 < nt : u + 2 < nt) wait_vmem<PER>();   // ... (not STORED: tile u + 1)
+    if (u + 2 < nt) wait_vmem<PER>();   // tile u + 1 has landed
     else wait_vmem<0>();
 #pragma unroll
     for (int ct = 0; ct < C::CT; ct++)
@@ -215,24 +193,13 @@ __device__ __forceinline__ void grad_few_body(const GradArgs& ga, const FewMerge
       lse_r = *(const f32x4*)st;
       if (!OWNER_IS_Q) pos_r = *(const i32x4*)(st + 32);
     }
-    f32x4 sv;
-    if constexpr (STORED) {
-      const unsigned char* sc = smem + C::X_OFF + stage * 4096 + w * 1024;
-      if (OWNER_IS_Q) sv = *(const f32x4*)(sc + lane * 16);
-      else {
+    load_a(stage1 * C::STAGE);   // (behind the last tile: whatever the stage holds, and nothing uses the scores)
+    __syncthreads();
+    f32x4 x[3];
 #pragma unroll
-        for (int e = 0; e < 4; e++) sv[e] = *(const float*)(sc + ((ln >> 2) * 8 + 4 * h + e) * 16 + (ln & 3) * 4);
-      }
-      __syncthreads();   // (everybody has read the coefficients of tile u - 1)
-    } else {
-      load_a(stage1 * C::STAGE);   // (behind the last tile: whatever the stage holds, and nothing uses the scores)
-      __syncthreads();
-      f32x4 x[3];
-#pragma unroll
-      for (int k = 0; k < 3; k++) x[k] = *(const f32x4*)(smem + C::X_OFF + (w * 3 + k) * 1024 + lane * 16);
-      phase1();
-      sv = ((own + x[0]) + x[1]) + x[2];
-    }
+    for (int k = 0; k < 3; k++) x[k] = *(const f32x4*)(smem + C::X_OFF + (w * 3 + k) * 1024 + lane * 16);
+    phase1();
+    const f32x4 sv = ((own + x[0]) + x[1]) + x[2];
 #pragma unroll
     for (int e = 0; e < 4; e++) {
       const float t = sv[e] * ga.alpha2;
@@ -246,7 +213,7 @@ __device__ __forceinline__ void grad_few_body(const GradArgs& ga, const FewMerge
     // A fragments of phase 2 (k = streamed rows): this lane's four are elements 4 h .. of lane 32 (w & 1) + ln, k-step w / 2
     *(bf16x4*)(smem + C::G_OFF + (w >> 1) * 1024 + (32 * (w & 1) + ln) * 16 + 8 * h) = __builtin_convertvector(g, bf16x4);
     __syncthreads();
-    if constexpr (!STORED) publish_s();   // (everybody has read the partial scores of tile u)
+    publish_s();   // (everybody has read the partial scores of tile u)
     bf16x8 gf[2];
 #pragma unroll
     for (int kk = 0; kk < 2; kk++) gf[kk] = *(const bf16x8*)(smem + C::G_OFF + kk * 1024 + lane * 16);
@@ -286,7 +253,7 @@ __device__ __forceinline__ int few_spread_id(const GradArgs& ga) {
   if (ga.p_stream_len > ga.q_stream_len) return id < nP ? nQ + xcd_share(id, nP) : xcd_share(id - nP, nQ);
   return id < nQ ? xcd_share(id, nQ) : nQ + xcd_share(id - nQ, nP);
 }
-template <int D, bool SYM, bool MERGE, bool STORED>
+template <int D, bool SYM, bool MERGE>
 __global__ void __launch_bounds__(256) grad_few_kernel(GradArgs ga, FewMerge fm) {
   extern __shared__ __attribute__((aligned(16))) unsigned char gsmem[];
   const int nQ = ga.obQ * ga.nsq;
@@ -294,25 +261,23 @@ __global__ void __launch_bounds__(256) grad_few_kernel(GradArgs ga, FewMerge fm)
   int id = xcd_task_id();
   if (__builtin_expect(gridDim.x > ROUND, 0)) id = few_spread_id(ga);
   if (id < nQ) {
-    grad_few_body<D, true, SYM, MERGE, STORED>(ga, fm, id % ga.obQ, id / ga.obQ, gsmem);
+    grad_few_body<D, true, SYM, MERGE>(ga, fm, id % ga.obQ, id / ga.obQ, gsmem);
   } else {
     const int t = id - nQ;
-    grad_few_body<D, false, SYM, MERGE, STORED>(ga, fm, t % ga.obP, t / ga.obP, gsmem);
+    grad_few_body<D, false, SYM, MERGE>(ga, fm, t % ga.obP, t / ga.obP, gsmem);
   }
 }
-template <int D, bool SYM, bool MERGE, bool STORED = false>
+template <int D, bool SYM, bool MERGE>
 static hipError_t grad_few_as(const GradArgs& ga, const FewMerge& fm, int nwg, hipStream_t stream) {
   constexpr int smem = FewCfg<D, MERGE>::SMEM;
   static bool attr_done[64];
-  if (hipError_t e = ensure_dyn_lds((const void*)grad_few_kernel<D, SYM, MERGE, STORED>, smem, attr_done); e != hipSuccess) return e;
-  grad_few_kernel<D, SYM, MERGE, STORED><<<nwg, 256, smem, stream>>>(ga, fm);
+  if (hipError_t e = ensure_dyn_lds((const void*)grad_few_kernel<D, SYM, MERGE>, smem, attr_done); e != hipSuccess) return e;
+  grad_few_kernel<D, SYM, MERGE><<<nwg, 256, smem, stream>>>(ga, fm);
   return hipGetLastError();
 }
 template <int D>
 static hipError_t grad_few_of(const GradArgs& ga, const FewMerge& fm, int nwg, hipStream_t stream) {
   if (ga.lse2_t) return grad_few_as<D, true, false>(ga, fm, nwg, stream);
-  if constexpr (D >= kFewStoredWidth)
-    if (ga.scores) return fm.splits ? grad_few_as<D, false, true, true>(ga, fm, nwg, stream) : grad_few_as<D, false, false, true>(ga, fm, nwg, stream);
   return fm.splits ? grad_few_as<D, false, true>(ga, fm, nwg, stream) : grad_few_as<D, false, false>(ga, fm, nwg, stream);
 }
 hipError_t grad_few_launch(const GradArgs& ga, const FewMerge& fm, int d, int nwg, hipStream_t stream) {

@@ -103,7 +103,6 @@ hipError_t launch_grad_mfma(const LossArgs& a, const LossPlan& pl) {
     ga.pos_pad = a.pos_idx;
     fm = few_merge_args(a, pl);
   }
-  if (grads_from_scores(a, pl)) { ga.scores = (const float*)(a.ws2 + pl.off_scores); ga.n_ablk = (a.B + kStatTile - 1) / kStatTile; }
   if (few) e = grad_few_launch(ga, fm, a.d, nwg, a.stream);
   else if (a.d == 128) e = grad128_launch(ga, nwg, a.stream);
   else if (ga.lse2_t) e = grad_sym_launch(ga, a.d, nwg, a.stream);

@@ -442,7 +442,7 @@ __global__ void __launch_bounds__(256) stats_small_kernel(StatsSmallArgs g) {
   st.finish(g, lds, split);
 }
 static hipError_t launch_stats_small(const LossArgs& a, const LossPlan& pl) {
-  StatsSmallArgs g = stats_small_args(a, pl, (const unsigned short*)a.q, (const unsigned short*)a.p, grads_from_scores(a, pl) ? (float*)(a.ws2 + pl.off_scores) : nullptr);
+  StatsSmallArgs g = stats_small_args(a, pl, (const unsigned short*)a.q, (const unsigned short*)a.p);
   if (merges_itself(a, pl)) { g.inv = (int32_t*)(a.ws + pl.off_inv); g.shared = (int*)(a.ws + pl.off_err) + 1; }
   stats_small_kernel<<<g.n_ablk * pl.stat_splits, 256, 0, a.stream>>>(g);
   return hipGetLastError();

@@ -109,7 +109,6 @@ struct GradArgs {
   int on_argmax;   // track the true maximum and its first index
   // an anchor per target, as the statistics merge left it, and the word that check_shared_positives raises
   const int32_t* inv; int* shared;
-  const float* scores; int n_ablk;   // few scores: what the statistics left (see StatTile::tile), or nullptr
 };
 
 // The kernel that sums the partials adds each positive's own term to its dP row through inv[j] (an anchor with

@@ -20,7 +20,7 @@ struct StatsSmallArgs {
   int B, Pn, d, n_ablk, tiles, tiles_per_split, mask_self;
   float alpha2;
   float* part_m; float* part_l; int* part_idx; float* pos_t;
-  float* scores;               // not nullptr: the scores, see StatTile::tile
+  float* scores;               // not nullptr (EXACT only): the scores, see StatTile::tile
   int32_t* inv; int* shared;   // where no merge follows: an anchor per target, and the word that the gradient kernel may raise
 };
 struct StatTileLds {
@@ -59,14 +59,15 @@ struct StatTile {
       const int row = part * TP + e, j = j0 + row;
       const float sum = ((s.red[0][row][en] + s.red[1][row][en]) + s.red[2][row][en]) + s.red[3][row][en];
       float x = sum * g.alpha2;
-      raw[e] = sum;
+      if constexpr (EXACT) raw[e] = sum;
       if (j >= g.Pn || (g.mask_self && j == a)) x = -INFINITY;
       // (a positive that the self-mask removes has the logit -inf: its row loss is then +inf)
       if (j == r && j < g.Pn && a < g.B) g.pos_t[a] = x;
       v[e] = x;
       if (x > mt) { mt = x; bt = j; }   // strict: the smallest index attaining the maximum
     }
-    if (g.scores) *(f32x4*)(g.scores + ((size_t)(j0 / T) * g.n_ablk + a / T) * (T * T) + 4 * threadIdx.x) = raw;
+    if constexpr (EXACT)
+      if (g.scores) *(f32x4*)(g.scores + ((size_t)(j0 / T) * g.n_ablk + a / T) * (T * T) + 4 * threadIdx.x) = raw;
     const float mn = fmaxf(m, mt), ms = (mn == -INFINITY) ? 0.f : mn;
     float sum = 0.f;
 #pragma unroll

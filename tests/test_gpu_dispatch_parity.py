@@ -481,27 +481,3 @@ def test_gradients_from_stored_scores(B, P, d, masked, dtype):
         torch.cuda.synchronize()
         check_loss("... %s alone, loss" % k, one["loss"].item(), want["loss"], TOL_F32, 1e-30)
         check("... %s alone" % k, relerr(to_np(one[k]), want[k]), TOL_F32)
-
-
-@pytest.mark.parametrize("B,P,d,masked", [(1, 1, 256, False), (33, 31, 768, False), (1, 300, 256, False), (300, 1, 640, False), (129, 257, 384, False),
-                                          (512, 512, 768, True), (70, 9000, 512, False), (9000, 70, 768, False), (1000, 1040, 256, False),
-                                          (1021, 1000, 640, False), (97, 4000, 768, False), (4000, 97, 384, False)])
-def test_walks_of_few_scores_from_stored_scores(B, P, d, masked):
-    """bf16, widths that are multiples of 128: scores read by the gradients or (a workspace without room for them) formed again, merged
-    inside the gradient kernel or by a launch (many rows); and one gradient alone."""
-    q, p, r = synth.dpr_batch(B, P, d, torch.bfloat16, seed=6100 + d + B, positive_mix=0.3)
-    if masked:
-        r = torch.arange(B, dtype=torch.int32) ^ 1
-    want = oracle_loss(q, p, r, 1.0, 0.25, mask_self=masked)
-    flags = gc.GC_MASK_SELF if masked else 0
-    dev = [x.to(DEV) for x in (q, p, r)]
-    need = gc.load().gc_workspace_bytes(B, P, d, gc.GC_BF16)
-    for label, n, want_ in (("stored", need, None), ("formed again", need - 4096, None), ("dq alone", need, ("loss", "dq")), ("dp alone", need, ("loss", "dp"))):
-        kw = dict(want=want_) if want_ else {}
-        out = gc.gc_loss_and_rep_grad_ex(*dev, 1.0, 0.25, flags, workspace=gc.alloc_workspace(n, DEV), **kw)
-        torch.cuda.synchronize()
-        check_loss("few %s loss" % label, out["loss"].item(), want["loss"], TOL_F32, 1e-30)
-        for k in ("dq", "dp"):
-            if not want_ or k in want_:
-                err = np.abs(to_np(out[k]) - want[k]).max() / max(np.abs(want[k]).max(), 1e-30)
-                check("few %dx%dx%d %s %s" % (B, P, d, label, k), err if np.abs(want[k]).max() > 1e-12 else 0.0, TOL_BF16)
