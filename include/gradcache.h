@@ -8,8 +8,7 @@
  * Gradient Cache" of Step 2.  It also runs the sub-batch steps around it for a
  * stand-in two-layer MLP encoder: the graph-less forward (Step 1) and the
  * per-sub-batch re-encode + backward of the cached rows (Step 3, Eq. 8-9).
- * The B x P score matrix is not written to device memory, but for calls of at
- * most 2^20 scores in fp32 or of a general width, which keep it in the workspace.
+ * The B x P score matrix is never written to device memory.
  *
  * Conventions for every entry point
  *   - All tensor pointers are DEVICE pointers unless marked "host".  Matrices
@@ -93,9 +92,8 @@ const char* gc_strerror(int status);
  * fp32 and general widths kernels without packed inputs, fit it: to fp32 rounding
  * the same results, and GC_ERR_WORKSPACE below that.)
  * Holds per-row softmax statistics and the split partial sums of dq and dp:
- * O((B + P) * d), not O(B * P) (Sec. "Gradient Cache Technique": the cache is
- * (|S| d + |T| d) numbers; the scores of a call of at most 2^20 of them, where
- * they are kept, are at most 4 MB and 124 bytes a row).  Returns 0 for an invalid shape. */
+ * O((B + P) * d), never O(B * P) (Sec. "Gradient Cache Technique": the cache is
+ * (|S| d + |T| d) numbers).  Returns 0 for an invalid shape. */
 size_t gc_workspace_bytes(int B, int P, int d, int dt);
 
 /*

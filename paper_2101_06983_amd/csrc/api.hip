@@ -34,7 +34,7 @@ static long long equal_share(long long rows) {
   const long long L = (rows + num_cu() - 1) / num_cu();
   return L < 256 ? 256 : (L + 31) / 32 * 32;
 }
-// few on ROUTE_PLANES: the scores are stored where they are few.  few, parts_limit, equal on ROUTE_MFMA.  few: small statistics tiles where the scores are few.  Splits: the fastest whose
+// few, parts_limit, equal: ROUTE_MFMA.  few: small statistics tiles where the scores are few.  Splits: the fastest whose
 // partials stay below parts_limit bytes, or (equal) the fewest that give every compute unit an equal share of the rows.
 // lean: 1: as many splits of the statistics as with blocks of 256, two of which share no compute unit; 2: and a second round of
 // workgroups priced as a whole one, which takes fewer splits.
@@ -229,8 +229,6 @@ static LossPlan make_loss_plan_for(int B, int P, int d, gc_dtype dt, bool ntxent
     pl.off_qt = take(pl.px_rows_q * per_row);
     pl.off_pk = take(pl.px_rows_p * per_row);
     pl.off_pt = take(pl.px_rows_p * per_row);
-    pl.px_stored = pl.px_stored && few && !ntxent;
-    pl.off_scores = take(pl.px_stored ? scores_bytes(B, P) : 0);
   }
   pl.off_on_ref = take((size_t)pl.fz_nsq * B * 4);
   pl.off_pos_idx = take(ntxent ? (size_t)B * 4 : 0);
@@ -300,11 +298,10 @@ static LossPlan choose_plan(int B, int P, int d, gc_dtype dt, bool ntxent, Fits 
     return *fit;
   }
   if (tiny_fits(B, P, d)) return make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_TINY, 1, false, 0.);
-  for (int splits = 16; splits >= 1; splits /= 2)
-    for (const bool few : {true, false}) {
-      const LossPlan pl = make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_PLANES, splits, few, 0.);
-      if (pl.total <= kPlanesMaxBytes && fits(pl)) return pl;
-    }
+  for (int splits = 16; splits >= 1; splits /= 2) {
+    const LossPlan pl = make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_PLANES, splits, false, 0.);
+    if (pl.total <= kPlanesMaxBytes && fits(pl)) return pl;
+  }
   return make_loss_plan_for(B, P, d, dt, ntxent, ROUTE_GENERAL, 1, false, 0.);
 }
 

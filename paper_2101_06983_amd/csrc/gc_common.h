@@ -63,8 +63,8 @@ struct LossPlan {
   // ROUTE_PLANES: bf16 planes per stored value; fragments along d (k-steps of 16, column tiles of 32); rows padded to 128;
   // target tiles per wave of the statistics pass; 32-row blocks a workgroup of the gradient pass owns; column slices;
   // floats between the partials of an output
-  int np, px_KS, px_CT, px_rows_q, px_rows_p, px_tiles_per_wave, px_no, px_col_slices, px_ct_per_slice, px_stored;
-  size_t px_stride_q, px_stride_p, off_qk, off_qt, off_pk, off_pt, off_scores;
+  int np, px_KS, px_CT, px_rows_q, px_rows_p, px_tiles_per_wave, px_no, px_col_slices, px_ct_per_slice;
+  size_t px_stride_q, px_stride_p, off_qk, off_qt, off_pk, off_pt;
   // (everything below off_dq_part is what a call that only forms statistics touches)
   size_t off_err, off_part_m, off_part_l, off_part_idx, off_pos, off_lse2, off_pos_pad, off_rowloss, off_dq_part,
       off_dp_part, off_pos_idx, off_on_ref, off_inv, total;
@@ -80,8 +80,6 @@ constexpr int kFewMergeRows = 256;   // streamed rows of a workgroup of the grad
 // 512 x 2048 (256 x 64) 2 us, planes of 1024 columns 3.3, 140 x 6000 there (256 x 63) 12; up to it the launch is 1 to 3 us saved.
 constexpr int kFewMergeEntries = 160 * 64;
 LossPlan make_loss_plan(int B, int P, int d, gc_dtype dt, bool ntxent, size_t limit = (size_t)-1);
-// Stored scores (ROUTE_PLANES, few scores): tiles of 32 x 32.
-inline size_t scores_bytes(int B, int P) { return (size_t)((B + kStatTile - 1) / kStatTile) * ((P + kStatTile - 1) / kStatTile) * (kStatTile * kStatTile * 4); }
 void plan_planes(LossPlan& pl, int B, int P, int d, gc_dtype dt, int max_splits);
 
 // Statistics of both sides of a symmetric form from one pass over the scores (stats_mfma_kernel, stats128_both_kernel).
@@ -165,11 +163,7 @@ struct PosFix {
 inline bool few_kernel(const LossArgs& a, const LossPlan& pl) {
   return pl.few_grad && (a.dz || (a.dq ? a.dp || !pl.few_not_q : !pl.few_not_p));
 }
-// The statistics of this call leave the scores, which its gradients read (stored_planes_grad_kernel).
-inline bool grads_from_scores(const LossArgs& a, const LossPlan& pl) {
-  return pl.px_stored && (a.dq || a.dp) && !a.dz && !a.lse2_t && !a.wexp && !a.both && !a.defer_loss_sum && !a.sym[0];
-}
-// The gradient kernel of this call merges the split statistics: one launch less.  (It writes what the merge would.)
+// The gradient kernel of this call merges the split statistics: one launch less.  (The dQ role writes what the merge would.)
 inline bool merges_itself(const LossArgs& a, const LossPlan& pl) {
   return pl.few_merge && (pl.route != ROUTE_MFMA || few_kernel(a, pl)) && a.dq && !a.lse2_t && !a.wexp && !a.dz;
 }

@@ -13,8 +13,7 @@
 //                        gradient products).  Rows are padded to 128, columns to 64 with zeros, so nothing after this
 //                        kernel knows about alignment, odd widths or bounds of its loads.
 //   planes_stats_kernel  per anchor: running maximum, sum of 2^t, arg-max, the positive's logit (Eq. 1 / Eq. 4)
-//   planes_grad_kernel   Eq. 5 and Eq. 6 in one launch; the scores are formed again (stored_planes_grad_kernel: up to 2^20 of them
-//                        the statistics have left in the workspace)
+//   planes_grad_kernel   Eq. 5 and Eq. 6 in one launch; scores are recomputed, never stored
 //
 // Layouts (v_mfma_f32_32x32x16_bf16): A lane l holds A[m = l % 32][k = 8 (l / 32) + 0..7], B alike with n, D register r
 // of lane l holds D[m = 8 (r / 4) + 4 (l / 32) + r % 4][n = l % 32].  Scores are formed with the streamed rows on M and
@@ -411,7 +410,6 @@ struct PlanesGradArgs {
   const float* pos_c;                      // ... the positive's coefficient, with room for 128 rows
   float alpha2, out_scale;
   int mask_self;
-  const float* scores; int n_ablk;         // STORED: what the statistics left, and anchor blocks (a row of score tiles)
   FewMerge fm; int P;                      // MERGE: lse2, pos (not padded) and pos_c are formed from these
 };
 constexpr int PG_STEP = 128, PG_MERGE_BYTES = 3 * kFewMergeRows * 4;
@@ -425,8 +423,9 @@ constexpr int planes_g_waves(int NO, int CTW) { return CTW > 4 && NO == 1 ? 8 : 
 
 // MERGE: the statistics come as splits, see StatMerge (a template argument: as a branch at run time it costs the instantiations
 // that never take it registers, and <3, 2, 8> seven spills inside its loop; 58.9 us a call at 512 x 1024 x 768 in fp32, 57.7 so).
-template <int NP, int NO, int CTW, bool MERGE, bool STORED>
-__device__ __forceinline__ void planes_grad_body(const PlanesGradArgs& g) {
+template <int NP, int NO, int CTW, bool MERGE>
+__global__ void __launch_bounds__(64 * planes_g_waves(NO, CTW), planes_g_waves(NO, CTW) == 8 || (NO == 1 && CTW <= 4) ? 2 : 1)
+planes_grad_kernel(PlanesGradArgs g) {
   constexpr int NW = planes_g_waves(NO, CTW), NH = NW / 4, CW = CTW / NH;   // halves of the k-steps; column tiles of a wave
   extern __shared__ __attribute__((aligned(16))) unsigned short pl_lds[];
   unsigned short* gl = pl_lds;                                    // [kk8][no][plane] blocks of 1 KB
@@ -434,7 +433,7 @@ __device__ __forceinline__ void planes_grad_body(const PlanesGradArgs& g) {
   const int lane = threadIdx.x & 63, h = lane >> 5, ln = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), wr = w & 3, wh = w >> 2;   // rows and half of the k-steps
   int k0 = 0, k1 = g.KS;
-  if constexpr (NH == 2 && !STORED) {   // (whole turns of the ring of planes_scores where LDS does not hold every k-step of the owner rows)
+  if constexpr (NH == 2) {   // (whole turns of the ring of planes_scores where LDS does not hold every k-step of the owner rows)
     constexpr int PD = planes_pd(NP);
     const int km = g.ks_lds == g.KS ? g.KS / 2 : (g.KS / 2 + PD / 2) / PD * PD;
     if (wh) k0 = km; else k1 = km;
@@ -451,37 +450,12 @@ __device__ __forceinline__ void planes_grad_body(const PlanesGradArgs& g) {
   float* const l_lse = (float*)(own_lds + (size_t)g.ks_lds * NO * NP * 512);   // (MERGE) of rows from the first owner / streamed row on
   int* const l_pos = (int*)l_lse + kFewMergeRows;
   float* const l_c = l_lse + 2 * kFewMergeRows;
-  constexpr int NS = 16 / NH;   // scores of this lane: NH = 2: registers 8 wh .. 8 wh + 7, both halves of the sum
-  const int rq = NH == 2 ? 16 * wh : 0;   // their first streamed row beyond j0
-  f32x16 s[NO];
-  auto load_s = [&](int t0) __attribute__((always_inline)) {   // (STORED) tile [target tile][anchor block], see StatTile::tile
-    const int jt = t0 / 32 + wr;
-    if (32 * jt >= R.n_str) return;   // (no such tile; its coefficients are forced to 0)
-    if (ri) {
-      const float* t = g.scores + ((size_t)ob * g.n_ablk + jt) * 1024 + (ln >> 2) * 128 + (ln & 3) + 16 * h + 4 * rq;
-#pragma unroll
-      for (int r = 0; r < NS; r++) s[0][r] = t[32 * (r >> 2) + 4 * (r & 3)];
-    } else {
-      const float* t = g.scores + ((size_t)jt * g.n_ablk + ob) * 1024 + h * 128 + ln * 4 + 32 * rq;
-#pragma unroll
-      for (int q = 0; q < NS / 4; q++) {
-        const f32x4 v = *(const f32x4*)(t + 256 * q);
-#pragma unroll
-        for (int e = 0; e < 4; e++) s[0][4 * q + e] = v[e];
-      }
-    }
-  };
-  if constexpr (STORED) {
-#pragma unroll
-    for (int r = 0; r < 16; r++) s[0][r] = 0.f;
-    load_s(sbeg);
-  }
   if constexpr (MERGE) {
     const int B = ri ? R.n_str : R.n_own;
     StatMerge<true, 64 * NW> sm(g.fm, g.pos, B, ri ? sbeg : ob * NO * 32, ri ? send - sbeg : NO * 32, !ri && split == 0 && cs == 0);
-    if constexpr (!STORED) planes_stage_own<NP, NO, 64 * NW>(own_lds, own, blk, g.ks_lds);
+    planes_stage_own<NP, NO, 64 * NW>(own_lds, own, blk, g.ks_lds);
     sm.finish(g.fm, B, g.P, (float*)gl, l_lse, l_pos, l_c);
-  } else if constexpr (!STORED) {
+  } else {
     planes_stage_own<NP, NO, 64 * NW>(own_lds, own, blk, g.ks_lds);
   }
 
@@ -505,14 +479,13 @@ __device__ __forceinline__ void planes_grad_body(const PlanesGradArgs& g) {
 
   for (int t0 = sbeg; t0 < send; t0 += PG_STEP) {
     // scores of streamed rows t0 + 32 wr .. + 31, k-steps k0 .. k1 - 1
-    if constexpr (!STORED) {
+    f32x16 s[NO];
 #pragma unroll
-      for (int no = 0; no < NO; no++)
+    for (int no = 0; no < NO; no++)
 #pragma unroll
-        for (int r = 0; r < 16; r++) s[no][r] = 0.f;
-      planes_scores<NP, NO, planes_pd(NP)>(R.str_k + (size_t)(t0 / 32 + wr) * blk + k0 * NP * 512, own_lds + k0 * NO * NP * 512, own + k0 * NP * 512,
-                                           blk, k1 - k0, min(max(g.ks_lds - k0, 0), k1 - k0), s);
-    }
+      for (int r = 0; r < 16; r++) s[no][r] = 0.f;
+    planes_scores<NP, NO, planes_pd(NP)>(R.str_k + (size_t)(t0 / 32 + wr) * blk + k0 * NP * 512, own_lds + k0 * NO * NP * 512, own + k0 * NP * 512,
+                                         blk, k1 - k0, min(max(g.ks_lds - k0, 0), k1 - k0), s);
     // the first loads of the second contraction
     constexpr int MOST = NP == 1 ? 16 : CW >= 6 ? 5 : 6, XD = 8 * CW < MOST ? 8 * CW : MOST;   // column tiles in flight
     const unsigned short* xt = R.str_t + (size_t)(t0 / 16) * g.CT * NP * 512 + lane * 8;
@@ -525,7 +498,9 @@ __device__ __forceinline__ void planes_grad_body(const PlanesGradArgs& g) {
 #pragma unroll
     for (int p = 0; p < XD; p++) load_x(p, p / CW, p % CW);
     const int j0 = t0 + 32 * wr + 4 * h;
-    if constexpr (NH == 2 && !STORED) {
+    constexpr int NS = 16 / NH;   // scores of this lane: NH = 2: registers 8 wh .. 8 wh + 7, both halves of the sum
+    const int rq = NH == 2 ? 16 * wh : 0;   // their first streamed row beyond j0
+    if constexpr (NH == 2) {
       // The other half's registers go to where that wave puts its coefficients, which is behind its reads.
       f32x4* mine = (f32x4*)(gl + (2 * wr + wh) * 3 * 512) + lane;
       f32x4* other = (f32x4*)(gl + (2 * wr + 1 - wh) * 3 * 512) + lane;
@@ -580,8 +555,6 @@ __device__ __forceinline__ void planes_grad_body(const PlanesGradArgs& g) {
         for (int n = 0; n < 3; n++) *(bf16x8*)(gl + (((2 * wr + wh + kk) * NO + no) * 3 + n) * 512 + lane * 8) = p[n];
       }
     }
-    if constexpr (STORED)
-      if (t0 + PG_STEP < send) load_s(t0 + PG_STEP);
     __syncthreads();
     // dO[32 NO x columns] += g[32 NO x 128] R[128 x columns]; the row blocks of the packed copy are full (zero-padded).
     // The first loads have been issued before the coefficients were formed; the coefficients come a row step ahead.
@@ -604,8 +577,7 @@ __device__ __forceinline__ void planes_grad_body(const PlanesGradArgs& g) {
 #pragma unroll
         for (int n = 0; n < NP; n++) x[n] = xf[at % XD][n];
         if (at + XD < N) load_x(at % XD, (at + XD) / CW, (at + XD) % CW);
-        // (a branch per tile, threaded through all of them, spills 42 registers of <3, 2>; a tile past the last isn't stored)
-        if ((STORED && CTW == 2) || ct0 + w + NW * i < ct1) {
+        if (ct0 + w + NW * i < ct1) {
 #pragma unroll
           for (int no = 0; no < NO; no++)
 #pragma unroll
@@ -634,21 +606,6 @@ __device__ __forceinline__ void planes_grad_body(const PlanesGradArgs& g) {
     }
   }
 }
-
-template <int NP, int NO, int CTW, bool MERGE>
-__global__ void __launch_bounds__(64 * planes_g_waves(NO, CTW), planes_g_waves(NO, CTW) == 8 || (NO == 1 && CTW <= 4) ? 2 : 1)
-planes_grad_kernel(PlanesGradArgs g) { planes_grad_body<NP, NO, CTW, MERGE, false>(g); }
-// Few scores: the statistics have left every score, and the gradients read them: half of the products, the owner rows and more than
-// half of the reads from L2 are gone (the kernel alone, with the merge inside, at 512 x 1024: fp32 x 768 32 us and 19.5 so, bf16 x 1024
-// 24 and 18.7).  What is left is the loads of the streamed rows, of which each is used for 32 owners, and the start of a launch.
-// A call with scores formed again and stored: fp32 512 x 1024 x 768 55.9 and 45.8 us, x 500 50.0 and 41.9, 64 x 8192 x 776 179 and 105,
-// 1024 x 1024 x 200 46.2 and 40.5, x 100 34.8 and 35.5; bf16 512 x 1024 x 1024 45.2 and 41.2, 1024 x 1024 x 400 43.9 and 40.4, x 200
-// 35.7 and 37.9, 512 x 1500 x 200 34.9 and 34.2: from 129 columns in fp32 and 257 in bf16 on.  A walk of all rows by one workgroup of 128
-// columns, without partials, forms the coefficients once per 128 columns: 54.9 and 44.4 us at the first and the sixth of these.
-constexpr int planes_stored_ctw(int NP) { return NP == 3 ? 2 : 4; }
-template <int NP, int CTW, bool MERGE>
-__global__ void __launch_bounds__(64 * planes_g_waves(1, CTW), 2)
-stored_planes_grad_kernel(PlanesGradArgs g) { planes_grad_body<NP, 1, CTW, MERGE, true>(g); }
 
 // ---- host ------------------------------------------------------------------------------------------------------------
 static inline int cdiv(int a, int b) { return (a + b - 1) / b; }
@@ -691,7 +648,6 @@ void plan_planes(LossPlan& pl, int B, int P, int d, gc_dtype dt, int max_splits)
   };
   split_of(stQ, P, pl.nsq, pl.q_stream_len);
   split_of(stP, B, pl.nsp, pl.p_stream_len);
-  pl.px_stored = pl.stat_tile && pl.px_no == 1 && cdiv(pl.px_ct_per_slice, 4) > planes_stored_ctw(pl.np) / 2;
   // (64 owner rows are for many steps a workgroup, where a launch more is nothing: no instantiations of their own)
   pl.few_merge = pl.stat_tile && pl.px_no == 1 && pl.p_stream_len <= kFewMergeRows && pl.p_stream_len * pl.stat_splits <= kFewMergeEntries;
 }
@@ -716,8 +672,7 @@ template <int NP>
 static hipError_t stats_np(const LossArgs& a, const LossPlan& pl) {
   char* ws = a.ws;
   if (pl.stat_tile) {
-    const StatsSmallArgs g = stats_small_args(a, pl, (const unsigned short*)(a.ws2 + pl.off_qk), (const unsigned short*)(a.ws2 + pl.off_pk),
-                                             grads_from_scores(a, pl) ? (float*)(a.ws2 + pl.off_scores) : nullptr);
+    const StatsSmallArgs g = stats_small_args(a, pl, (const unsigned short*)(a.ws2 + pl.off_qk), (const unsigned short*)(a.ws2 + pl.off_pk));
     planes_stats_small_kernel<NP><<<g.n_ablk * pl.stat_splits, 256, 0, a.stream>>>(g, pl.px_KS);
     return hipGetLastError();
   }
@@ -746,13 +701,6 @@ hipError_t launch_stats_planes(const LossArgs& a, const LossPlan& pl) {
 template <int NP, int NO, int CTW, bool MERGE>
 static hipError_t grad_launch_as(PlanesGradArgs& g, int nwg, hipStream_t s) {
   constexpr int merge = MERGE ? PG_MERGE_BYTES : 0;
-  if constexpr (NO == 1 && CTW >= planes_stored_ctw(NP)) {
-    if (g.scores) {
-      g.ks_lds = 0;
-      stored_planes_grad_kernel<NP, CTW, MERGE><<<nwg, 64 * planes_g_waves(1, CTW), planes_g_bytes(1) + merge, s>>>(g);
-      return hipGetLastError();
-    }
-  }
   const int budget = ((nwg <= num_cu() || NO == 2 || CTW > 4) ? 156 : 78) * 1024 - planes_g_bytes(NO) - merge;
   g.ks_lds = ks_in_lds(budget / (NO * NP * 1024), g.KS, planes_pd(NP));
   static bool done[64];
@@ -785,7 +733,6 @@ hipError_t launch_grad_planes(const LossArgs& a, const LossPlan& pl) {
   g.lse2 = (const float*)(ws + pl.off_lse2); g.pos = (const int32_t*)(ws + pl.off_pos_pad); g.pos_c = (const float*)(ws + pl.off_pos);
   g.alpha2 = a.alpha * kLog2e; g.out_scale = a.alpha / (float)a.B * (a.grad_mul != 0.f ? a.grad_mul : 1.f);
   g.mask_self = (a.flags & GC_MASK_SELF) ? 1 : 0;
-  if (grads_from_scores(a, pl)) { g.scores = (const float*)(a.ws2 + pl.off_scores); g.n_ablk = cdiv(a.B, kStatTile); }
   if (merges_itself(a, pl)) { g.fm = few_merge_args(a, pl); g.pos = a.pos_idx; g.P = a.P; }
   const bool want_q = a.dq || a.dz, want_p = a.dp || a.dz;
   const int own = 32 * pl.px_no;

@@ -20,7 +20,6 @@ struct StatsSmallArgs {
   int B, Pn, d, n_ablk, tiles, tiles_per_split, mask_self;
   float alpha2;
   float* part_m; float* part_l; int* part_idx; float* pos_t;
-  float* scores;               // not nullptr (EXACT only): the scores, see StatTile::tile
   int32_t* inv; int* shared;   // where no merge follows: an anchor per target, and the word that the gradient kernel may raise
 };
 struct StatTileLds {
@@ -47,27 +46,20 @@ struct StatTile {
 #pragma unroll
     for (int e = 0; e < 16; e++) s.red[wave][8 * (e >> 2) + 4 * h + (e & 3)][ln] = acc[e];
   }
-  // After a barrier; the caller puts another one behind it.  g.scores: the scores before any mask as tiles of 4 KB, [target tile]
-  // [anchor block]: thread (part, n)'s four are elements 4 threadIdx.x .. of its tile.
+  // after a barrier; the caller puts another one behind it
   __device__ __forceinline__ void tile(const StatsSmallArgs& g, const StatTileLds& s, int j0) {
     float v[TP], mt = -INFINITY;
-    f32x4 raw;
-    static_assert(TP == 4);
     int bt = 0x7fffffff;
 #pragma unroll
     for (int e = 0; e < TP; e++) {
       const int row = part * TP + e, j = j0 + row;
-      const float sum = ((s.red[0][row][en] + s.red[1][row][en]) + s.red[2][row][en]) + s.red[3][row][en];
-      float x = sum * g.alpha2;
-      if constexpr (EXACT) raw[e] = sum;
+      float x = (((s.red[0][row][en] + s.red[1][row][en]) + s.red[2][row][en]) + s.red[3][row][en]) * g.alpha2;
       if (j >= g.Pn || (g.mask_self && j == a)) x = -INFINITY;
       // (a positive that the self-mask removes has the logit -inf: its row loss is then +inf)
       if (j == r && j < g.Pn && a < g.B) g.pos_t[a] = x;
       v[e] = x;
       if (x > mt) { mt = x; bt = j; }   // strict: the smallest index attaining the maximum
     }
-    if constexpr (EXACT)
-      if (g.scores) *(f32x4*)(g.scores + ((size_t)(j0 / T) * g.n_ablk + a / T) * (T * T) + 4 * threadIdx.x) = raw;
     const float mn = fmaxf(m, mt), ms = (mn == -INFINITY) ? 0.f : mn;
     float sum = 0.f;
 #pragma unroll
@@ -176,9 +168,8 @@ inline FewMerge few_merge_args(const LossArgs& a, const LossPlan& pl) {
   fm.lse_out = a.lse; fm.argmax_out = a.argmax;
   return fm;
 }
-inline StatsSmallArgs stats_small_args(const LossArgs& a, const LossPlan& pl, const unsigned short* q, const unsigned short* p, float* scores = nullptr) {
+inline StatsSmallArgs stats_small_args(const LossArgs& a, const LossPlan& pl, const unsigned short* q, const unsigned short* p) {
   StatsSmallArgs g{};
-  g.scores = scores;
   g.Q = q; g.P = p; g.pos_idx = a.pos_idx;
   g.B = a.B; g.Pn = a.P; g.d = a.d; g.n_ablk = (a.B + kStatTile - 1) / kStatTile; g.tiles = (a.P + kStatTile - 1) / kStatTile;
   g.tiles_per_split = pl.stat_cols_per_split / kStatTile; g.mask_self = (a.flags & GC_MASK_SELF) ? 1 : 0;

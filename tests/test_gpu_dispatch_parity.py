@@ -461,9 +461,9 @@ def test_scores_in_halves_of_the_width(B, P, d, masked, dtype):
 @pytest.mark.parametrize("B,P,d,masked", [(33, 31, 776, False), (1, 300, 300, False), (300, 1, 520, False), (129, 257, 129, False),
                                           (129, 257, 257, False), (512, 512, 400, True), (70, 9000, 300, False), (9000, 70, 520, False),
                                           (200, 300, 2100, False), (1000, 1040, 1000, False)])
-def test_gradients_from_stored_scores(B, P, d, masked, dtype):
-    """Few scores, read by the gradients or (a workspace without room for them, and fp32 up to 128 columns, bf16 up to 256) formed again:
-    one answer; and one gradient alone."""
+def test_few_scores_of_general_widths(B, P, d, masked, dtype):
+    """Few scores in the named workspace and in one a little smaller (fewer splits, packed for the same kernels or not at all): one
+    answer; and one gradient alone."""
     q, p, r = synth.dpr_batch(B, P, d, dtype, seed=6000 + d, positive_mix=0.3)
     if masked:
         r = torch.arange(B, dtype=torch.int32) ^ 1
@@ -481,3 +481,58 @@ def test_gradients_from_stored_scores(B, P, d, masked, dtype):
         torch.cuda.synchronize()
         check_loss("... %s alone, loss" % k, one["loss"].item(), want["loss"], TOL_F32, 1e-30)
         check("... %s alone" % k, relerr(to_np(one[k]), want[k]), TOL_F32)
+
+
+@pytest.mark.parametrize("B,P,d,masked", [(1, 1, 256, False), (33, 31, 768, False), (1, 300, 256, False), (300, 1, 640, False), (129, 257, 384, False),
+                                          (512, 512, 768, True), (70, 9000, 512, False), (9000, 70, 768, False), (1000, 1040, 256, False),
+                                          (1021, 1000, 640, False), (97, 4000, 768, False), (4000, 97, 384, False)])
+def test_walks_of_few_scores(B, P, d, masked):
+    """bf16, widths that are multiples of 128: in the named workspace and in one a little smaller (fewer splits), merged inside the
+    gradient kernel or by a launch (many rows); and one gradient alone."""
+    q, p, r = synth.dpr_batch(B, P, d, torch.bfloat16, seed=6100 + d + B, positive_mix=0.3)
+    if masked:
+        r = torch.arange(B, dtype=torch.int32) ^ 1
+    want = oracle_loss(q, p, r, 1.0, 0.25, mask_self=masked)
+    flags = gc.GC_MASK_SELF if masked else 0
+    dev = [x.to(DEV) for x in (q, p, r)]
+    need = gc.load().gc_workspace_bytes(B, P, d, gc.GC_BF16)
+    for label, n, want_ in (("named workspace", need, None), ("less workspace", need - 4096, None), ("dq alone", need, ("loss", "dq")), ("dp alone", need, ("loss", "dp"))):
+        kw = dict(want=want_) if want_ else {}
+        if n < need and (B, P) in ((1, 1), (1000, 1040)):   # the named one is the least there is
+            with pytest.raises(gc.GradCacheError):
+                gc.gc_loss_and_rep_grad_ex(*dev, 1.0, 0.25, flags, workspace=gc.alloc_workspace(n, DEV))
+            continue
+        out = gc.gc_loss_and_rep_grad_ex(*dev, 1.0, 0.25, flags, workspace=gc.alloc_workspace(n, DEV), **kw)
+        torch.cuda.synchronize()
+        check_loss("few %s loss" % label, out["loss"].item(), want["loss"], TOL_F32, 1e-30)
+        for k in ("dq", "dp"):
+            if not want_ or k in want_:
+                # With one target the softmax is 1 and the gradients are 0: what is left is the rounding of the positive's
+                # coefficient 2^(t - lse2) - 1, by ulp(t) + ulp(lse2) <= 2^-22 |t|, times a row of the other side and alpha / B.
+                other, t = (p if k == "dq" else q), 4.0 * np.log2(np.e) * np.abs(synth.widen(q) @ synth.widen(p).T).max()
+                floor = 4.0 / B * float(other.float().abs().max()) * 2.0 ** -22 * (1.0 + t) * (B if k == "dp" else 1)
+                err = np.abs(to_np(out[k]) - want[k]).max()
+                check("few %dx%dx%d %s %s" % (B, P, d, label, k), err, TOL_BF16 * np.abs(want[k]).max() + floor)
+
+
+@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 256), (torch.bfloat16, 768), (torch.float32, 300), (torch.float32, 768), (torch.bfloat16, 520), (torch.bfloat16, 1000)])
+def test_no_scores_in_memory(dtype, d):
+    """s_ij = 256 i + j, exact in either type and no two alike: after a call next to none of them, scaled or not, lies in the workspace
+    (of the row statistics, the positives and the row maxima may)."""
+    B, P = 128, 256
+    q, p = torch.zeros(B, d), torch.zeros(P, d)
+    q[:, 0], q[:, 1] = 256.0 * torch.arange(B), 1.0
+    p[:, 0], p[:, 1] = 1.0, torch.arange(P).float()
+    temp = 4096.0
+    ws = gc.alloc_workspace(gc.load().gc_workspace_bytes(B, P, d, gc.GC_F32 if dtype == torch.float32 else gc.GC_BF16), DEV)
+    ws.zero_()
+    r = torch.arange(B, dtype=torch.int32)
+    gc.gc_loss_and_rep_grad_ex(q.to(dtype).to(DEV), p.to(dtype).to(DEV), r.to(DEV), 1.0, temp, 0, workspace=ws)
+    torch.cuda.synchronize()
+    words = np.unique(ws.cpu().numpy()[:ws.numel() // 4 * 4].view(np.float32))
+    words = words[np.isfinite(words)].astype(np.float64)
+    scores = np.arange(1, B * P, dtype=np.float64)
+    for mul in (1.0, 1.0 / temp, np.log2(np.e) / temp):
+        at = np.clip(np.searchsorted(words, scores * mul), 1, len(words) - 1)
+        near = np.minimum(np.abs(words[at] - scores * mul), np.abs(words[at - 1] - scores * mul))
+        check("scores in memory (x %.1e)" % mul, float((near <= 2.0 ** -23 * scores * mul).mean()), 4 * (B + P) / (B * P))

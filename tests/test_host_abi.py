@@ -45,6 +45,10 @@ def test_workspace_bytes_is_linear_in_rows_not_quadratic():
     assert w2 < 8192 * 16384 * 2 / 2      # well below a bf16 score matrix
     w3 = lib.gc_workspace_bytes(32768, 65536, 768, gc.GC_BF16)
     assert w3 < 16 * (32768 + 65536) * 4 + 4096 or w3 < 2 * (32768 + 65536) * 768 * 4
+    # few scores: partial sums of so many splits of both outputs (fp32 and general widths: packed inputs, too), and no score matrix
+    for B, P, d, dt, splits in ((1024, 1024, 256, gc.GC_BF16, 4.3), (1024, 1024, 768, gc.GC_BF16, 4.2), (1, 1 << 20, 256, gc.GC_BF16, 1.1),
+                                (1 << 20, 1, 256, gc.GC_BF16, 1.1), (1024, 1024, 130, gc.GC_F32, 13.0), (1024, 1024, 300, gc.GC_BF16, 9.5)):
+        assert lib.gc_workspace_bytes(B, P, d, dt) <= splits * (B + P) * d * 4, (B, P, d, dt)
     assert lib.gc_workspace_bytes(0, 5, 8, gc.GC_F32) == 0
     assert lib.gc_workspace_bytes(5, 5, 8, 7) == 0
     assert lib.gc_ntxent_workspace_bytes(7, 128) == 0

@@ -157,3 +157,25 @@ for rows, din, dh, dout in ((1, 64, 128, 128), (200, 128, 256, 128), (2048, 1024
 report(out=out)
 """)
     assert got["out"] == [[0, -4, True]] * 3
+
+
+# (type, B, P, d, gradient kernel of the call): D and whether it merges the statistics itself; planes, owner blocks, column tiles, merge
+FEW = [("bf16", 1, 1, 256, "grad_few_kernelILi256ELb0ELb1E"), ("bf16", 129, 257, 384, "grad_few_kernelILi384ELb0ELb1E"),
+       ("bf16", 70, 9000, 512, "grad_few_kernelILi512ELb0ELb1E"), ("bf16", 9000, 70, 768, "grad_few_kernelILi768ELb0ELb0E"),
+       ("bf16", 1021, 1000, 640, "grad_few_kernelILi640ELb0ELb1E"), ("bf16", 97, 4000, 768, "grad_few_kernelILi768ELb0ELb1E"),
+       ("f32", 33, 31, 776, "planes_grad_kernelILi3ELi1ELi8ELb1E"), ("f32", 129, 257, 129, "planes_grad_kernelILi3ELi1ELi2ELb1E"),
+       ("f32", 9000, 70, 520, "planes_grad_kernelILi3ELi1ELi6ELb0E"), ("f32", 200, 300, 2100, "planes_grad_kernelILi3ELi1ELi6ELb1E"),
+       ("bf16", 512, 512, 400, "planes_grad_kernelILi1ELi1ELi4ELb1E"), ("bf16", 1000, 1040, 1000, "planes_grad_kernelILi1ELi1ELi8ELb0E")]
+
+
+def test_few_scores_reach_the_kernels_that_their_parity_tests_mean(stub):
+    got = run(stub, """
+out = []
+for dt, B, P, d, _ in json.loads(%r):
+    stub.stub_reset()
+    rc = ex(F32 if dt == "f32" else BF16, B, P, d, lib.gc_workspace_bytes(B, P, d, F32 if dt == "f32" else BF16))
+    out.append([rc, stub.stub_launches().decode()])
+report(out=out)
+""" % json.dumps(FEW))
+    for c, (rc, names) in zip(FEW, got["out"]):
+        assert rc == 0 and c[4] in names, (c, names)
