@@ -352,3 +352,30 @@ def test_gelu_far_out():
         phi = np.array([0.5 * math.erfc(-t / math.sqrt(2.0)) for t in h])
         prime = phi + h * np.exp(-0.5 * np.minimum(h * h, 1e4)) / math.sqrt(2 * math.pi)
         check("gelu far out rows=%d db1" % rows, relerr(to_np(grads["b1"]), rows * prime * synth.widen(params["W2"])[:, 0]), 2.0 ** -14)
+
+
+@pytest.mark.parametrize("rows", [1, 40, 300])
+@pytest.mark.parametrize("sd", [0.1, 0.3, 1.0, 3.0])
+def test_gelu_in_fp32(rows, sd):
+    """db1 is GELU'(h) in fp32 where one row has dA = 1, dW2 GELU(h) in two bf16 planes; h = b1 + W1[0], two bf16 numbers.  GELU' is two
+    or three values below 1 added up: each rounding up to 2^-25 off, 2^-25 / sqrt 3 in the mean, so 2^-25 root mean square."""
+    din, dh, dout = 64, 8192, 128
+    g = np.random.default_rng(int(100 * sd))
+    params = dict(W1=torch.zeros(din, dh), b1=torch.from_numpy(g.standard_normal(dh) * sd), W2=torch.zeros(dh, dout), b2=torch.zeros(dout))
+    params["W1"][0] = torch.from_numpy(g.standard_normal(dh) * sd / 512)
+    params["W2"][:, 0] = 1.0
+    params = {k: v.to(torch.bfloat16) for k, v in params.items()}
+    x = torch.zeros(rows, din, dtype=torch.bfloat16)
+    x[:, 0] = 1.0
+    u = torch.zeros(rows, dout)
+    u[0, 0] = 1.0
+    grads = gc.zero_mlp_grads(dev_params(params))
+    gc.gc_chunk_surrogate_backward_bf16(x.to(DEV), dev_params(params), u.to(DEV), grads)
+    torch.cuda.synchronize()
+    h = synth.widen(params["b1"]) + synth.widen(params["W1"])[0]
+    h = h.astype(np.float32).astype(np.float64)
+    phi = np.array([0.5 * math.erfc(-t / math.sqrt(2.0)) for t in h])
+    prime = phi + h * np.exp(-0.5 * h * h) / math.sqrt(2 * math.pi)
+    check("gelu' rows=%d s=%g" % (rows, sd), float(np.sqrt(((to_np(grads["b1"]) - prime) ** 2).mean())), 2.0 ** -25)
+    some = (np.abs(h) > 1e-3) & (h > -13)   # (GELU itself: 8e-6 of its value down to -13)
+    check("gelu rows=%d s=%g" % (rows, sd), float(np.abs(to_np(grads["W2"])[some, 0] / (h * phi)[some] - 1.0).max()), 2.0 ** -17 + 8e-6)
