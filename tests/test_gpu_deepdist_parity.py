@@ -80,3 +80,15 @@ def test_unsupported_shapes_and_bad_positive():
     torch.cuda.synchronize()
     assert math.isnan(out["loss"].item())
     assert gc.gc_check_async_error(out["workspace"]) == gc.GC_ERR_POS_IDX
+
+
+def test_dw_of_many_rows_is_not_one_long_sum():
+    """B copies of one anchor: dw, a mean over them, is that of 32 copies, up to 2^-24 of itself for each of the B / 512 + 4 + 32
+    additions that a value passes through (copies round alike, so errors of a longer sum would add up)."""
+    q1, p, _ = synth.dpr_batch(32, 2, 128, seed=8400)
+    om = synth.deep_omega(128, seed=8401)
+    dw = {}
+    for B in (32, 131072):
+        q = q1[:1].expand(B, 128).contiguous()
+        dw[B] = to_np(run(q, p, torch.zeros(B, dtype=torch.int32), om)["dw"])
+    check("dw of copies", float((np.abs(dw[131072] - dw[32]) / np.abs(dw[32])).max()), (131072 / 512 + 4 + 32) * 2.0 ** -24)
