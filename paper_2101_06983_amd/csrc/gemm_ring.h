@@ -146,6 +146,16 @@ struct RingWave {
   }
 };
 
+template <int MT, int NT>
+__device__ __forceinline__ void ring_zero(f32x16 (&acc)[MT][NT]) {
+#pragma unroll
+  for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+    for (int nt = 0; nt < NT; nt++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) acc[mt][nt][r] = 0.f;
+}
+
 // Piece round I (A's rounds, then B's) of the loads of stage kt, into the ring slot at LDS address `lds`
 template <int I, class A, class B>
 __device__ __forceinline__ void ring_issue(const A& a, const B& b, int kt, unsigned lds, const RingWave& wv) {
@@ -175,12 +185,13 @@ __device__ __forceinline__ void ring_fill(const A& a, const B& b, int nk, unsign
     });
 }
 // acc += this wave's share of the product over stages 0 .. nk - 1, after ring_fill.  PA, PB: planes; products of planes i and j
-// with i + j < 2.  Ends behind a barrier: LDS is free.
+// with i + j < 2.  SMALL: those with i + j = 1 add up by themselves (beside acc each of them costs acc a rounding: for contractions so
+// long that it shows).  Ends behind a barrier: LDS is free.
 // The fragments of the next k-step are read while the MFMAs of this one run, across the barrier of a stage too: it stands before the
 // last k-step of the stage before.  Every wave then has the stage before in registers, whose slot takes the loads of the stage NS
 // further on; they are spread over the MFMAs of that k-step and the next (a wave waits at a load until the unit's load path has
 // taken it, one in 16 cycles: eight waves that issue theirs at once behind a barrier all wait for the last).
-template <int MT, int NT, int PA, int PB, int NS, class A, class B>
+template <int MT, int NT, int PA, int PB, int NS, bool SMALL = false, class A, class B>
 __device__ __forceinline__ void ring_run(const A& a, const B& b, int nk, unsigned char* smem, const RingWave& wv, f32x16 (&acc)[MT][NT]) {
   static_assert(A::SUBS == B::SUBS && A::SUBS % 2 == 0, "stages of both operands hold the same k-steps");
   constexpr int STAGE = ring_stage_bytes<A, B>(), AB = A::PIECES * 1024, S2 = A::SUBS / 2, ROUNDS = A::N + B::N;
@@ -188,6 +199,8 @@ __device__ __forceinline__ void ring_run(const A& a, const B& b, int nk, unsigne
   constexpr int PRODUCTS = PA + PB - 1, MF = MT * NT * PRODUCTS;       // MFMAs of a k-step
   constexpr int EARLY = ring_early<A, B>(), LATE = ROUNDS - EARLY;
   struct Frags { bf16x8 a[MT][PA], b[NT][PB]; } cur;
+  f32x16 small[MT][NT];
+  if constexpr (SMALL) ring_zero<MT, NT>(small);
   auto read = [&](Frags& f, const unsigned char* st, int s2) __attribute__((always_inline)) {
     const int sub = 2 * s2 + wv.kg;
 #pragma unroll
@@ -234,7 +247,8 @@ __device__ __forceinline__ void ring_run(const A& a, const B& b, int nk, unsigne
     static_for<MF>([&](auto i_tag) __attribute__((always_inline)) {
       constexpr int i = decltype(i_tag)::value, t = PRODUCTS - 1 - i / (MT * NT), mt = i % (MT * NT) / NT, nt = i % NT;   // the small products first
       constexpr int pa = PA == 2 && PB == 2 ? (t == 1) : PA == 2 ? t : 0, pb = PA == 2 && PB == 2 ? (t == 2) : PB == 2 ? t : 0;
-      acc[mt][nt] = mfma32(cur.a[mt][pa], cur.b[nt][pb], acc[mt][nt]);
+      f32x16& sum = SMALL && t > 0 ? small[mt][nt] : acc[mt][nt];
+      sum = mfma32(cur.a[mt][pa], cur.b[nt][pb], sum);
       if constexpr (STEADY) {
         constexpr int N = LAST ? EARLY : s2 == 0 ? LATE : 0;
         static_for<N>([&](auto k_tag) __attribute__((always_inline)) {
@@ -278,17 +292,13 @@ __device__ __forceinline__ void ring_run(const A& a, const B& b, int nk, unsigne
   }
 #pragma unroll 1
   for (; kt < nk; kt++) stage(kt, std::false_type{});
+  if constexpr (SMALL) {
+#pragma unroll
+    for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+      for (int nt = 0; nt < NT; nt++) acc[mt][nt] += small[mt][nt];
+  }
   __syncthreads();
-}
-
-template <int MT, int NT>
-__device__ __forceinline__ void ring_zero(f32x16 (&acc)[MT][NT]) {
-#pragma unroll
-  for (int mt = 0; mt < MT; mt++)
-#pragma unroll
-    for (int nt = 0; nt < NT; nt++)
-#pragma unroll
-      for (int r = 0; r < 16; r++) acc[mt][nt][r] = 0.f;
 }
 
 // The two groups' sums: a wave keeps half of its tile, units kg U .. kg U + U - 1 (U = MT NT) of eight registers each, and takes the

@@ -124,3 +124,20 @@ def test_products_at_the_edges(B, P, d):
     a64, q64, om64 = to_np(a), synth.widen(q), synth.widen(om)
     check("bilinear edges %dx%d u" % (B, d), relerr(to_np(out["u"]), a64 @ om64.T), 2.0 ** -14)
     check("bilinear edges %dx%d dOmega" % (B, d), relerr(to_np(out["domega"]), q64.T @ a64), 2.0 ** -14)
+
+
+@pytest.mark.parametrize("B", [4096, 65536])
+def test_domega_of_many_rows(B):
+    """Beside what the two bf16 planes of A leave only the roundings of at most rows / 8 + slices additions in a row (fifteen slices),
+    independent of one another, 2^-25 of the sum in the mean."""
+    P, d = 64, 768
+    q, p, _ = synth.dpr_batch(B, P, d, seed=7700)
+    r = torch.from_numpy(np.random.default_rng(B).integers(0, P, size=B).astype(np.int32))
+    om = synth.bilinear_omega(d, seed=7701)
+    out = run(q, p, r, om)
+    a = gc.bilinear_intermediates(out["workspace"], B, P, d)[1].double()
+    off = lambda got, want: float((got.double() - want).norm() / want.norm())  # noqa: E731
+    hi = a.bfloat16().double()
+    two, q64 = hi + (a - hi).bfloat16().double(), q.to(DEV).double()
+    planes = off(q64.T @ two, q64.T @ a)
+    check("dOmega of %d rows" % B, off(out["domega"], q64.T @ a), math.hypot(planes, math.sqrt(B / 15 / 8 + 15) * 2.0 ** -25))
