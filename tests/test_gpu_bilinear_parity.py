@@ -141,3 +141,24 @@ def test_domega_of_many_rows(B):
     two, q64 = hi + (a - hi).bfloat16().double(), q.to(DEV).double()
     planes = off(q64.T @ two, q64.T @ a)
     check("dOmega of %d rows" % B, off(out["domega"], q64.T @ a), math.hypot(planes, math.sqrt(B / 15 / 8 + 15) * 2.0 ** -25))
+
+
+@pytest.mark.parametrize("B,P,d", [(5, 9, 128), (300, 500, 384), (1100, 200, 256)])
+def test_inputs_aligned_to_their_elements_only(B, P, d):
+    """q and Omega at odd addresses are copied first: the same bits."""
+    q, p, _ = synth.dpr_batch(B, P, d, seed=7800 + B, positive_mix=0.3)
+    r = torch.from_numpy(np.random.default_rng(B + P).integers(0, P, size=B).astype(np.int32))
+    om = synth.bilinear_omega(d, seed=7801)
+
+    def shifted(t, by):
+        buf = torch.empty(t.numel() + by, dtype=t.dtype, device=DEV)
+        buf[by:] = t.reshape(-1).to(DEV)
+        return buf[by:].view(t.shape)
+
+    want = run(q, p, r, om)
+    for q_, om_ in ((shifted(q, 1), om.to(DEV)), (q.to(DEV), shifted(om, 3)), (shifted(q, 7), shifted(om, 1))):
+        outs = dict(loss=torch.empty(1, device=DEV), u=shifted(torch.zeros(B, d), 1), v=torch.empty(P, d, device=DEV), domega=torch.empty(d, d, device=DEV))
+        got = gc.gc_bilinear_loss_and_grads_bf16(q_, p.to(DEV), r.to(DEV), om_, 1.0, 1.0, None, outs)
+        torch.cuda.synchronize()
+        for k in ("loss", "u", "v", "domega"):
+            assert torch.equal(got[k], want[k]), k

@@ -379,3 +379,33 @@ def test_gelu_in_fp32(rows, sd):
     check("gelu' rows=%d s=%g" % (rows, sd), float(np.sqrt(((to_np(grads["b1"]) - prime) ** 2).mean())), 2.0 ** -25)
     some = (np.abs(h) > 1e-3) & (h > -13)   # (GELU itself: 8e-6 of its value down to -13)
     check("gelu rows=%d s=%g" % (rows, sd), float(np.abs(to_np(grads["W2"])[some, 0] / (h * phi)[some] - 1.0).max()), 2.0 ** -17 + 8e-6)
+
+
+def shifted(t, by):
+    """The same values `by` elements into a buffer: aligned to their elements only."""
+    buf = torch.empty(t.numel() + by, dtype=t.dtype, device=DEV)
+    buf[by:] = t.reshape(-1).to(DEV)
+    return buf[by:].view(t.shape)
+
+
+@pytest.mark.parametrize("rows", [31, 200])
+@pytest.mark.parametrize("what", ["x", "W1", "W2", "b1", "all"])
+def test_operands_aligned_to_their_elements_only(rows, what):
+    # (200 rows at dh = 2048: tiles in the ring where everything is aligned)
+    xq, xp, r, params = small_problem(B=rows, P=rows + 37, din=192, dh=2048, dout=256)
+    p64 = widen_params(params)
+    put = lambda name, t: shifted(t, 1 if name != "W2" else 5) if what in (name, "all") else t.to(DEV)  # noqa: E731
+    dp = {k: put(k, v) for k, v in params.items()}
+    x, other = put("x", xq), put("x", xp)
+    y = gc.gc_mlp_forward_nograd_bf16(x, dp)
+    u = torch.from_numpy((np.random.default_rng(rows).standard_normal((rows, 256)) * 1e-3).astype(np.float32))
+    grads = gc.zero_mlp_grads(dp)
+    gc.gc_chunk_surrogate_backward_bf16(x, dp, shifted(u, 1) if what == "all" else u.to(DEV), grads)
+    torch.cuda.synchronize()
+    check("shifted %s y" % what, relerr(to_np(y), O.mlp_forward(synth.widen(xq), p64)), 2.0 ** -8)
+    want = O.mlp_backward(synth.widen(xq), p64, synth.widen(u))
+    for k in ("W1", "b1", "W2", "b2"):
+        check("shifted %s d%s" % (what, k), relerr(to_np(grads[k]), want[k]), 2.0 ** -14)
+    out = gc.gc_step_mlp_bf16(x, other, r.to(DEV), 32, 64, dp, 1.0, 0.2, keep=True)
+    torch.cuda.synchronize()
+    stagewise("shifted %s step" % what, out, xq, xp, r, params, 32, 64, 1.0, 0.2)

@@ -179,3 +179,63 @@ report(out=out)
 """ % json.dumps(FEW))
     for c, (rc, names) in zip(FEW, got["out"]):
         assert rc == 0 and c[4] in names, (c, names)
+
+
+ENCODER = """
+class Params(ctypes.Structure):
+    _fields_ = [(n, vp) for n in ("W1", "b1", "W2", "b2")] + [(n, ci) for n in ("din", "dh", "dout")]
+class Grads(ctypes.Structure):
+    _fields_ = [(n, vp) for n in ("dW1", "db1", "dW2", "db2")]
+lib.gc_mlp_workspace_bytes.restype, lib.gc_mlp_workspace_bytes.argtypes = sz, [ci, vp]
+lib.gc_mlp_forward_nograd_bf16.argtypes = [vp, ci, vp, vp, vp, sz, vp]
+lib.gc_chunk_surrogate_backward_bf16.argtypes = [vp, ci, vp, vp, vp, vp, sz, vp]
+lib.gc_step_mlp_workspace_bytes.restype, lib.gc_step_mlp_workspace_bytes.argtypes = sz, [ci] * 4 + [vp]
+lib.gc_step_mlp_bf16.argtypes = [vp, ci, vp, ci, vp, ci, ci, vp, cf, cf, vp, vp, vp, vp, vp, vp, vp, sz, vp]
+G = Grads(X, X, X, X)
+def of(call):
+    stub.stub_reset()
+    rc = call()
+    return [rc, stub.stub_last_error(), [l.split()[0] for l in stub.stub_launches().decode().splitlines()]]
+def forward(rows, w, x=X):
+    return of(lambda: lib.gc_mlp_forward_nograd_bf16(x, rows, ctypes.byref(w), X, X, lib.gc_mlp_workspace_bytes(rows, ctypes.byref(w)), None))
+def backward(rows, w, x=X, u=X):
+    return of(lambda: lib.gc_chunk_surrogate_backward_bf16(x, rows, ctypes.byref(w), u, ctypes.byref(G), X, lib.gc_mlp_workspace_bytes(rows, ctypes.byref(w)), None))
+def step(B, P, w, xq=X, xp=X):
+    return of(lambda: lib.gc_step_mlp_bf16(xq, B, xp, P, X, 32, 32, ctypes.byref(w), 1.0, 1.0, X, ctypes.byref(G), X, X, X, X, X,
+                                           lib.gc_step_mlp_workspace_bytes(B, P, 32, 32, ctypes.byref(w)), None))
+def bilinear(B, P, d, q=X, om=X):
+    return of(lambda: lib.gc_bilinear_loss_and_grads_bf16(q, X, X, B, P, d, om, 1.0, 1.0, X, X, X, X, X, lib.gc_bilinear_workspace_bytes(B, P, d), None))
+"""
+RING = ("mlp_hidden_kernel", "mlp_output_kernel", "mlp_dh_tiled_kernel")
+
+
+def test_operands_aligned_to_their_elements_only_stay_off_the_16_byte_loads(stub):
+    """The ring's loads into LDS take 16 bytes at 16-byte addresses: an operand that they would read elsewhere goes to the kernels for few
+    rows, or (bilinear distance) is copied first."""
+    got = run(stub, ENCODER + """
+w = lambda **k: Params(*[X + 2 * k.get(n, 0) for n in ("W1", "b1", "W2", "b2")], 256, 2048, 256)
+out = dict(
+    aligned=[forward(300, w()), backward(300, w()), step(200, 300, w()), bilinear(300, 600, 256)],
+    forward=[forward(300, w(), X + 2), forward(300, w(W1=1)), forward(300, w(W2=5))], biases=[forward(300, w(b1=1, b2=3))],
+    many=[forward(5000, w(), X + 2)], backward=[backward(300, w(), X + 2), backward(300, w(W1=1))], w2=[backward(300, w(W2=1)), backward(300, w(), X, X + 4)],
+    huge=[backward(65537 * 32, w(W1=1))],
+    step=[step(200, 300, w(), X + 2), step(200, 300, w(), X, X + 2), step(200, 300, w(W1=1)), step(200, 300, w(W2=1))],
+    bilinear=[bilinear(300, 600, 256, X + 2), bilinear(300, 600, 256, X, X + 2), bilinear(300, 600, 256, X + 2, X + 6)])
+report(**out)
+""")
+    named = lambda r, *k: [n for n in r[2] if any(x in n for x in k)]  # noqa: E731
+    assert all(r[0] == 0 and r[1] == 0 for k in got for r in got[k]), got
+    assert len(named(got["aligned"][0], *RING)) == 2 and len(named(got["aligned"][1], *RING)) == 1 and len(named(got["aligned"][2], *RING)) == 3
+    for k in ("forward", "many", "backward", "huge"):
+        for r in got[k]:
+            assert not named(r, *RING) and named(r, "skinny"), (k, r)
+    for k in ("biases", "w2"):
+        assert all(named(r, *RING) and not named(r, "skinny") for r in got[k]), k
+    assert len(named(got["many"][0], "mlp_skinny")) == 6 and len(named(got["huge"][0], "mlp_dh_skinny")) == 2
+    xq, xp, w1, w2 = got["step"]
+    assert len(named(xq, "mlp_hidden")) == len(named(xp, "mlp_hidden")) == 1 and not named(xq, "mlp_dh_tiled") and not named(xp, "mlp_dh_tiled")
+    assert not named(w1, *RING) and not named(w2, "mlp_hidden", "mlp_output") and named(w2, "mlp_dh_tiled")
+    for r, copies, ends in zip(got["aligned"][3:] + got["bilinear"], (0, 1, 1, 2), (1, 2, 1, 2)):
+        assert len(named(r, "copy_aligned_kernel")) == copies and len(named(r, "bilinear_end_kernel")) == ends, r
+        if copies:
+            assert "copy_aligned" in r[2][0] and "bilinear_project" in r[2][copies]
