@@ -112,9 +112,10 @@ def test_unsupported_width_and_bad_positive():
 
 
 # The products around the loss at the edges of their tiles, of their slices of rows (1000 x 512: four, the last with a tail of 8 rows in
-# its last stage; 2090 x 256) and of a stage of 32 rows.  Bound as for the encoder's gradients: A as two bf16 planes is off by up to
+# its last stage; 2090 x 256) and of a stage of 32 rows; H and u in tiles of 128 x 192 (5600 and 4096 rows at d = 768).  Bound as for the encoder's gradients: A as two bf16 planes is off by up to
 # 2^-17 of itself, independently from term to term.
-@pytest.mark.parametrize("B,P,d", [(1, 3, 128), (31, 2, 256), (33, 64, 384), (129, 64, 640), (1000, 100, 512), (2090, 64, 256), (2560, 40, 768)])
+@pytest.mark.parametrize("B,P,d", [(1, 3, 128), (31, 2, 256), (33, 64, 384), (129, 64, 640), (1000, 100, 512), (2090, 64, 256), (2560, 40, 768),
+                                   (4096, 64, 768), (5600, 40, 768)])
 def test_products_at_the_edges(B, P, d):
     q, p, _ = synth.dpr_batch(B, P, d, seed=7500 + B, positive_mix=0.3)
     r = torch.from_numpy(np.random.default_rng(B + P).integers(0, P, size=B).astype(np.int32))

@@ -300,12 +300,13 @@ def test_step_with_sub_batches_that_fill_a_launch_differently(B, P, cq, cp):
 
 # The tiles of the encoder's products: 64 x 128 (few tiles), 128 x 128 (rows of 1000 at dh = 2176: 272 tiles of the first) and 128 x 192
 # (1500 rows at dh = 3200, whose last tiles of columns and rows are part empty); one and several blocks of rows of the kernel for
-# few rows and the line behind it; widths that leave half a tile of dW1 (din = 64, 192).
+# few rows and the line behind it; widths that leave half a tile of dW1 (din = 64, 192); the second layer in tiles of 128 x 128 (1024
+# rows) and 128 x 192 (2040 rows, a full launch of Step 1) in three ranges.  Which kernels each size reaches is asserted on the host.
 # The bound of the gradients: factors of two bf16 planes are off by up to 2^-17 of themselves, independently from term to term,
 # so a sum is off by about that share of its size; largest of all entries over the largest entry: 2^-14.
 @pytest.mark.parametrize("rows,din,dh,dout", [(31, 64, 128, 128), (64, 192, 384, 128), (65, 128, 256, 256), (129, 64, 128, 128),
                                               (192, 320, 256, 128), (193, 64, 384, 384), (255, 192, 1408, 256), (1000, 64, 2176, 128),
-                                              (1500, 128, 3200, 128)])
+                                              (1500, 128, 3200, 128), (1024, 64, 3072, 768), (2040, 64, 3072, 768)])
 def test_tiles_of_the_encoder(rows, din, dh, dout):
     xq, _, _, params = small_problem(B=rows, din=din, dh=dh, dout=dout)
     p64, dp = widen_params(params), dev_params(params)

@@ -239,3 +239,36 @@ report(**out)
         assert len(named(r, "copy_aligned_kernel")) == copies and len(named(r, "bilinear_end_kernel")) == ends, r
         if copies:
             assert "copy_aligned" in r[2][0] and "bilinear_project" in r[2][copies]
+
+
+# (rows, din, dh, dout): tiles in units of 64 of the hidden layer, the output layer, Act and dH, or None for the kernel for few rows; whether
+# the parameter gradients take their kernel for few rows
+TILES = [((31, 64, 128, 128), None, None, None, True), ((65, 128, 256, 256), None, None, None, True), ((129, 64, 128, 128), (1, 2), (1, 2), None, True),
+         ((192, 320, 256, 128), (1, 2), (1, 2), None, True), ((193, 64, 384, 384), (1, 2), (1, 2), None, False),
+         ((255, 192, 1408, 256), (1, 2), (1, 2), (1, 2), False), ((1000, 64, 2176, 128), (2, 2), (1, 2), (2, 2), False),
+         ((1500, 128, 3200, 128), (2, 3), (1, 2), (2, 3), False), ((1024, 64, 3072, 768), (2, 2), (2, 2), (2, 2), False),
+         ((2040, 64, 3072, 768), (2, 2), (2, 3), (2, 3), False)]
+# (B, P, d): tiles of H and of u
+BILINEAR = [((1, 3, 128), (1, 2), (1, 2)), ((1000, 100, 512), (1, 2), (1, 2)), ((2560, 40, 768), (1, 2), (2, 2)), ((4096, 64, 768), (2, 2), (2, 3)),
+            ((5600, 40, 768), (2, 3), (2, 2))]
+
+
+def test_sizes_reach_the_tiles_that_their_parity_tests_mean(stub):
+    got = run(stub, ENCODER + """
+out = []
+for rows, din, dh, dout in json.loads(%r):
+    w = Params(X, X, X, X, din, dh, dout)
+    out.append([forward(rows, w), backward(rows, w)])
+report(encoder=out, bilinear=[bilinear(*c) for c in json.loads(%r)])
+""" % (json.dumps([t[0] for t in TILES]), json.dumps([t[0] for t in BILINEAR])))
+
+    def has(r, kernel, tile):
+        return any("%sILi%dELi%dE" % ((kernel,) + tile) in n for n in r[2])
+
+    for (size, hidden, output, dh, few), (f, b) in zip(TILES, got["encoder"]):
+        for r, kernel, tile, other in ((f, "mlp_hidden_kernel", hidden, "mlp_skinny"), (f, "mlp_output_kernel", output, "mlp_skinny"),
+                                       (b, "mlp_dh_tiled_kernel", dh, "mlp_dh_skinny")):
+            assert has(r, kernel, tile) if tile else any(other in n for n in r[2]), (size, kernel, r)
+        assert any("mlp_grads_few_kernel" in n for n in b[2]) == few, (size, b)
+    for (size, h, u), r in zip(BILINEAR, got["bilinear"]):
+        assert has(r, "bilinear_project_kernel", h) and has(r, "bilinear_end_kernel", u), (size, r)
