@@ -10,7 +10,7 @@
 // Operands reach LDS in stages of SUBS k-steps, a ring of NS of them; loads are issued NS - 1 stages ahead, one barrier a stage.
 // Three layouts in memory, each written to LDS so that fragment reads are free of bank conflicts:
 //   FragOp  fragments, 1 KB each: [k-step of 16][32-wide tile][plane], lane l holding index l % 32 and 8 of the 16 k
-//   RowOp   rows with k contiguous, 128 or 256 bytes of each row a stage; 16-byte chunks XORed with bits of the row
+//   RowOp   rows with k contiguous, 128 bytes of each row a stage; 16-byte chunks XORed with bits of the row
 //   ColOp   rows of k with the index contiguous (transposing reads): the weights as they are stored, too
 // Measured at 1536 rows, 1024-3072-768 (us, with 64 x 128 tiles staged through registers in LDS before, the gradients by single
 // waves that read fragments from L2): hidden layer 33.8 -> 20.6, second layer 27.0 -> 22.3, Act and dH 62.4 -> 40.7, parameter
@@ -60,21 +60,20 @@ struct RowSource {
   const void* x[2]; size_t ld;   // bytes
   int n1, n2, first2;
 };
-// LINE bytes of each row a stage: one plane of LINE / 2 values, or (P = 2) blocks of 32 high parts and 32 low parts
-template <int ROWS, int LINE, int P = 1>
+// 128 bytes of each row a stage: one plane of 64 values, or (P = 2) 32 high parts and 32 low parts
+template <int ROWS, int P = 1>
 struct RowOp {
-  static_assert(LINE == 128 || LINE == 256, "line of a row");
-  static constexpr int SUBS = LINE / 32 / P, PIECES = ROWS * LINE / 1024, N = ring_rounds<PIECES, RG_WAVES>(), CH = LINE / 16;
+  static constexpr int LINE = 128, SUBS = LINE / 32 / P, PIECES = ROWS * LINE / 1024, N = ring_rounds<PIECES, RG_WAVES>(), CH = LINE / 16;
   const char* base[N]; unsigned voff[N];
-  __device__ __forceinline__ static int swz(int row) { return LINE == 128 ? (row >> 1) & 7 : row & 15; }
-  // row0: first row of the tile; k0: bytes from the start of a row
-  __device__ __forceinline__ RowOp(const RowSource& s, int row0, size_t k0, int w, int lane) {
+  __device__ __forceinline__ static int swz(int row) { return (row >> 1) & 7; }
+  // row0: first row of the tile
+  __device__ __forceinline__ RowOp(const RowSource& s, int row0, int w, int lane) {
 #pragma unroll
     for (int i = 0; i < N; i++) {
-      const int r = (w + RG_WAVES * i) * (64 / CH), dr = lane / CH;   // (a piece is 4 or 8 rows: never of both inputs)
+      const int r = (w + RG_WAVES * i) * (64 / CH), dr = lane / CH;   // (a piece is 8 rows: never of both inputs)
       const bool second = s.n2 && row0 + r >= s.first2;
       const int local = second ? row0 + r - s.first2 : row0 + r, last = (second ? s.n2 : s.n1) - 1, first = min(local, last);
-      base[i] = (const char*)s.x[second ? 1 : 0] + (size_t)first * s.ld + k0;
+      base[i] = (const char*)s.x[second ? 1 : 0] + (size_t)first * s.ld;
       voff[i] = (unsigned)(min(local + dr, last) - first) * (unsigned)s.ld + (unsigned)(((lane % CH) ^ swz(r + dr)) * 16);
     }
   }
@@ -84,7 +83,7 @@ struct RowOp {
   }
   __device__ __forceinline__ static bf16x8 frag(const unsigned char* st, int sub, int t, int pl, int lane) {   // plain order
     const int ln = lane & 31, h = lane >> 5;
-    const int c = P == 1 ? 2 * sub + h : 8 * (sub >> 1) + 4 * pl + 2 * (sub & 1) + h;
+    const int c = 2 * sub + h + (P == 1 ? 0 : 4 * pl);
     return *(const bf16x8*)(st + (32 * t + ln) * LINE + ((c ^ swz(ln)) * 16));
   }
 };
