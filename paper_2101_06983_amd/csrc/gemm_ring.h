@@ -185,7 +185,10 @@ __device__ __forceinline__ void ring_fill(const A& a, const B& b, int nk, unsign
 }
 // acc += this wave's share of the product over stages 0 .. nk - 1, after ring_fill.  PA, PB: planes; products of planes i and j
 // with i + j < 2.  SMALL: those with i + j = 1 add up by themselves (beside acc each of them costs acc a rounding: for contractions so
-// long that it shows).  Ends behind a barrier: LDS is free.
+// long that it shows).  Of a k-step the products of low parts come first where B has them, and last where A alone has:
+// with them first there, every product is a little too small, which a sum over many rows shows (db1 of 65536 rows, 64-128-128: error
+// 3.22e-6, of which -1.8e-6 in the mean; 2.67e-6 and -3.8e-7 so, 2.70e-6 and -4.1e-7 with products by one wave group).
+// Ends behind a barrier: LDS is free.
 // The fragments of the next k-step are read while the MFMAs of this one run, across the barrier of a stage too: it stands before the
 // last k-step of the stage before.  Every wave then has the stage before in registers, whose slot takes the loads of the stage NS
 // further on; they are spread over the MFMAs of that k-step and the next (a wave waits at a load until the unit's load path has
@@ -244,7 +247,7 @@ __device__ __forceinline__ void ring_run(const A& a, const B& b, int nk, unsigne
     }
     __builtin_amdgcn_sched_barrier(0);
     static_for<MF>([&](auto i_tag) __attribute__((always_inline)) {
-      constexpr int i = decltype(i_tag)::value, t = PRODUCTS - 1 - i / (MT * NT), mt = i % (MT * NT) / NT, nt = i % NT;   // the small products first
+      constexpr int i = decltype(i_tag)::value, n = i / (MT * NT), t = PA == 2 && PB == 1 ? n : PRODUCTS - 1 - n, mt = i % (MT * NT) / NT, nt = i % NT;
       constexpr int pa = PA == 2 && PB == 2 ? (t == 1) : PA == 2 ? t : 0, pb = PA == 2 && PB == 2 ? (t == 2) : PB == 2 ? t : 0;
       f32x16& sum = SMALL && t > 0 ? small[mt][nt] : acc[mt][nt];
       sum = mfma32(cur.a[mt][pa], cur.b[nt][pb], sum);

@@ -410,3 +410,25 @@ def test_operands_aligned_to_their_elements_only(rows, what):
     out = gc.gc_step_mlp_bf16(x, other, r.to(DEV), 32, 64, dp, 1.0, 0.2, keep=True)
     torch.cuda.synchronize()
     stagewise("shifted %s step" % what, out, xq, xp, r, params, 32, 64, 1.0, 0.2)
+
+
+def test_bias_gradient_of_many_rows():
+    """db1 sums dA over every row, so that a bias of dA far below its rounding shows.  Beside what the two bf16 planes of U leave only the
+    additions of 2048 block sums in a row: each up to 2^-24 of the sum so far off, independently, 2^-24 / sqrt 3 in the mean; 7 % for two standard
+    deviations of a norm over 384 entries."""
+    rows, din, dh, dout = 65536, 64, 384, 128
+    g = torch.Generator().manual_seed(9)
+    normal = lambda *s: torch.randn(*s, generator=g)  # noqa: E731
+    params = {k: (normal(*s) * 0.02).to(torch.bfloat16).to(DEV) for k, s in (("W1", (din, dh)), ("b1", (dh,)), ("W2", (dh, dout)), ("b2", (dout,)))}
+    x, u = normal(rows, din).to(torch.bfloat16).to(DEV), (normal(rows, dout) * 1e-3).to(DEV)
+    grads = gc.zero_mlp_grads(params)
+    gc.gc_chunk_surrogate_backward_bf16(x, params, u, grads)
+    torch.cuda.synchronize()
+    h = x.double() @ params["W1"].double() + params["b1"].double()
+    prime = 0.5 * (1.0 + torch.erf(h / math.sqrt(2.0))) + h * torch.exp(-0.5 * h * h) / math.sqrt(2.0 * math.pi)
+    db1 = lambda v: ((v @ params["W2"].double().T) * prime).sum(0)  # noqa: E731
+    hi = u.bfloat16().double()
+    two = hi + (u.double() - hi).bfloat16().double()
+    want = db1(u.double())
+    off = lambda got: float((got.double() - want).norm() / want.norm())  # noqa: E731
+    check("db1 of %d rows" % rows, off(grads["b1"]), 1.07 * math.hypot(off(db1(two)), 2.0 ** -24 / math.sqrt(3.0) * math.sqrt(rows / 32 / 2)))
