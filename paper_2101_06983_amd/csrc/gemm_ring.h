@@ -13,10 +13,10 @@
 //   RowOp   rows with k contiguous, 128 bytes of each row a stage; 16-byte chunks XORed with bits of the row
 //   ColOp   rows of k with the index contiguous (transposing reads): the weights as they are stored, too
 // Measured at 1536 rows, 1024-3072-768 (us, with 64 x 128 tiles staged through registers in LDS before, the gradients by single
-// waves that read fragments from L2): hidden layer 33.8 -> 20.6, second layer 27.0 -> 22.3, Act and dH 62.4 -> 40.7, parameter
-// gradients 72.9 -> 47.5.  Repeated over data that the L2s hold, a stage of the hidden layer takes 0.58 us, of which 0.35 are its MFMAs;
-// in a call, where every stage comes from behind the L2s, 0.79.  The rest of a launch is its start, GELU and the stores, which
-// no other workgroup of the unit covers.
+// waves that read fragments from L2): hidden layer 33.8 -> 21.0, second layer 27.0 -> 22.3, Act and dH 62.4 -> 38.5, parameter
+// gradients 72.9 -> 46.4.  No unit is near full there (counters): the matrix pipe of a unit with a workgroup is busy 33, 40, 43 and 57 % of its
+// time, LDS reads and writes take 17 to 21 %, without conflicts; waves wait a third of the time for loads or a barrier.  The start of a
+// launch, GELU and the stores have no other workgroup of the unit to cover them: the more stages a workgroup has, the less they weigh.
 // Within a k-step lane half h holds k 8 h .. 8 h + 7 ("plain") or {0..3, 8..11} + 4 h ("as an MFMA leaves it": register r of a
 // result is row 8 (r / 4) + 4 h + r % 4); any order will do as long as both operands of a product share it.
 #pragma once

@@ -70,8 +70,8 @@ struct PackArgs { PackSide side[2]; int d, KS, CT, cblocks, nb0; bool vec; };
 constexpr int PK_W = 64;   // columns per workgroup
 // One workgroup: 32 rows x 64 columns through LDS, a fragment of either copy per wave.  Bound by its loads and stores (one read, two to
 // six 16-byte stores per 8 values), in small calls by one trip through them: with 128 columns, half as many workgroups and two fragments
-// one after the other, a call takes 41.5 us for 39.4 (512 x 1024 x 1000 bf16), 53.9 for 51.6 (fp32), 41.1 for 38.6 (1024 x 1024 x 200 fp32);
-// 2220 for 2212 at 2000 x 16000 x 1000 fp32.
+// one after the other, a call takes 48.6 us for 46.9 (512 x 1024 x 1000 bf16), 72.8 for 70.1 (fp32), 49.6 for 47.2 (1024 x 1024 x 200 fp32);
+// 2221 for 2218 at 2000 x 16000 x 1000 fp32.
 template <typename T>
 __global__ void __launch_bounds__(256) planes_pack_kernel(PackArgs a) {
   constexpr int NP = sizeof(T) == 4 ? 3 : 1;
