@@ -14,8 +14,9 @@
  *   - All tensor pointers are DEVICE pointers unless marked "host".  Matrices
  *     are row-major and contiguous (leading dimension = number of columns).
  *   - x, W1, W2 of the encoder and q, omega of the bilinear distance may lie at
- *     any address of their 16-bit elements; from 128 rows on (bilinear: always) a
- *     call is faster where they lie at multiples of 16 bytes.
+ *     any address of their 16-bit elements; from 128 rows on (bilinear: always)
+ *     those that do not lie at multiples of 16 bytes are copied first, into the
+ *     workspace or (q) the output u, at 2 to 8 us a call.
  *   - The caller owns every buffer, the workspace included; the library frees
  *     nothing the caller passed.  gc_loss_and_rep_grad_bf16 / _f32 take no
  *     workspace argument: they use a per-device buffer the library allocates

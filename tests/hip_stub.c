@@ -25,7 +25,7 @@ int stub_mallocs(void) { return mallocs; }
 int stub_frees(void) { return frees; }
 int stub_last_error(void) { return last_error; }
 const char* stub_launches(void) { return names; }
-void stub_reset(void) { names[0] = 0; mallocs = frees = 0; peak = used; }
+void stub_reset(void);
 
 int hipMalloc(void** out, size_t n) {
   mallocs++;
@@ -76,12 +76,23 @@ void __hipRegisterFunction(void** m, const void* host, char* dev, const char* na
   (void)m; (void)dev; (void)tl; (void)a; (void)b; (void)c; (void)d; (void)w;
   if (fns < MAXN) { fn[fns].host = host; fn[fns++].name = name; }
 }
+static int misaligned;   /* launches of kernels whose loads take 16 bytes at a time that were given another address */
+int stub_misaligned(void) { return misaligned; }
+/* places (in words of 8 bytes of the first argument) of what such a kernel reads by these loads; those that are null or -1 it doesn't */
+static const struct { const char* name; int at[4]; } wide[] = {
+  {"mlp_hidden_kernel", {0, 1, 5, -1}}, {"mlp_output_kernel", {6, -1, -1, -1}}, {"mlp_dh_tiled_kernel", {0, 1, 4, 5}}, {"bilinear_project_kernel", {0, 1, -1, -1}},
+  {"bilinear_end_kernel", {0, 1, 2, -1}}};
 int hipLaunchKernel(const void* f, dim3_t g, dim3_t b, void** args, size_t sh, void* s) {
-  (void)args; (void)s;
+  (void)s;
   const char* name = "?";
   for (int i = 0; i < fns; i++) if (fn[i].host == f) name = fn[i].name;
+  for (int i = 0; i < (int)(sizeof wide / sizeof *wide); i++)
+    if (strstr(name, wide[i].name))
+      for (int k = 0; k < 4; k++)
+        if (wide[i].at[k] >= 0 && ((const uint64_t*)args[0])[wide[i].at[k]] % 16) misaligned++;
   size_t at = strlen(names);
   snprintf(names + at, sizeof names - at, "%s %u %u %u %u %zu\n", name, g.x, g.y, g.z, b.x, sh);
   if (g.x == 0 || g.y == 0 || g.z == 0 || b.x == 0 || b.x > 1024 || sh > 163840) { last_error = 9; return 9; }
   return 0;
 }
+void stub_reset(void) { names[0] = 0; mallocs = frees = misaligned = 0; peak = used; }

@@ -412,6 +412,29 @@ def test_operands_aligned_to_their_elements_only(rows, what):
     stagewise("shifted %s step" % what, out, xq, xp, r, params, 32, 64, 1.0, 0.2)
 
 
+@pytest.mark.parametrize("what", ["x", "W1", "W2", "all"])
+@pytest.mark.parametrize("rows,din,dh,dout", [(700, 192, 2048, 256), (3000, 2048, 512, 128), (6000, 704, 128, 128)])
+def test_copies_of_operands_that_are_not_aligned(rows, din, dh, dout, what):
+    """The kernels are those of aligned operands, so are the bits; where the copy of x leaves room for half of the rows only (the second and
+    third size), the gradients add up in another order: sums of at most `rows` terms in fp32."""
+    xq, _, _, params = small_problem(B=rows, din=din, dh=dh, dout=dout)
+    put = lambda name, t: shifted(t, 3) if what in (name, "all") else t.to(DEV)  # noqa: E731
+    u = torch.from_numpy((np.random.default_rng(rows).standard_normal((rows, dout)) * 1e-3).astype(np.float32)).to(DEV)
+    got = []
+    for x, w in ((xq.to(DEV), dev_params(params)), (put("x", xq), {k: put(k, v) for k, v in params.items()})):
+        grads = gc.zero_mlp_grads(w)
+        gc.gc_chunk_surrogate_backward_bf16(x, w, u, grads)
+        got.append((gc.gc_mlp_forward_nograd_bf16(x, w), grads))
+    torch.cuda.synchronize()
+    (y, want), (y2, grads) = got
+    assert torch.equal(y, y2)
+    for k in want:
+        if rows >= 3000 and what in ("x", "all"):
+            check("copies %s %d rows d%s" % (what, rows, k), relerr(to_np(grads[k]), to_np(want[k])), 2.0 ** -24 * math.sqrt(rows))
+        else:
+            assert torch.equal(grads[k], want[k]), k
+
+
 def test_bias_gradient_of_many_rows():
     """db1 sums dA over every row, so that a bias of dA far below its rounding shows.  Beside what the two bf16 planes of U leave only the
     additions of 2048 block sums in a row: each up to 2^-24 of the sum so far off, independently, 2^-24 / sqrt 3 in the mean; 7 % for two standard

@@ -195,7 +195,7 @@ G = Grads(X, X, X, X)
 def of(call):
     stub.stub_reset()
     rc = call()
-    return [rc, stub.stub_last_error(), [l.split()[0] for l in stub.stub_launches().decode().splitlines()]]
+    return [rc, stub.stub_last_error(), [l.split()[0] for l in stub.stub_launches().decode().splitlines()], stub.stub_misaligned()]
 def forward(rows, w, x=X):
     return of(lambda: lib.gc_mlp_forward_nograd_bf16(x, rows, ctypes.byref(w), X, X, lib.gc_mlp_workspace_bytes(rows, ctypes.byref(w)), None))
 def backward(rows, w, x=X, u=X):
@@ -209,36 +209,44 @@ def bilinear(B, P, d, q=X, om=X):
 RING = ("mlp_hidden_kernel", "mlp_output_kernel", "mlp_dh_tiled_kernel")
 
 
-def test_operands_aligned_to_their_elements_only_stay_off_the_16_byte_loads(stub):
-    """The ring's loads into LDS take 16 bytes at 16-byte addresses: an operand that they would read elsewhere goes to the kernels for few
-    rows, or (bilinear distance) is copied first."""
+def test_operands_aligned_to_their_elements_only_are_copied_for_the_16_byte_loads(stub):
+    """The ring's loads into LDS take 16 bytes at 16-byte addresses: an operand that lies elsewhere is copied once a call (rows: once a
+    launch), and the kernels are those of aligned operands."""
     got = run(stub, ENCODER + """
-w = lambda **k: Params(*[X + 2 * k.get(n, 0) for n in ("W1", "b1", "W2", "b2")], 256, 2048, 256)
+w = lambda *s, **k: Params(*[X + 2 * k.get(n, 0) for n in ("W1", "b1", "W2", "b2")], *(s or (256, 2048, 256)))
 out = dict(
-    aligned=[forward(300, w()), backward(300, w()), step(200, 300, w()), bilinear(300, 600, 256)],
-    forward=[forward(300, w(), X + 2), forward(300, w(W1=1)), forward(300, w(W2=5))], biases=[forward(300, w(b1=1, b2=3))],
-    many=[forward(5000, w(), X + 2)], backward=[backward(300, w(), X + 2), backward(300, w(W1=1))], w2=[backward(300, w(W2=1)), backward(300, w(), X, X + 4)],
-    huge=[backward(65537 * 32, w(W1=1))],
-    step=[step(200, 300, w(), X + 2), step(200, 300, w(), X, X + 2), step(200, 300, w(W1=1)), step(200, 300, w(W2=1))],
+    aligned=[forward(300, w()), backward(300, w()), step(200, 300, w()), bilinear(300, 600, 256), step(3000, 100, w())],
+    forward=[forward(300, w(), X + 2), forward(300, w(W1=1)), forward(5000, w(W2=5)), forward(300, w(W1=1, W2=1), X + 2), forward(300, w(b1=1, b2=3))],
+    backward=[backward(300, w(), X + 2), backward(300, w(W1=1)), backward(300, w(W1=1), X + 6), backward(300, w(W2=1)), backward(300, w(), X, X + 4)],
+    step=[step(200, 300, w(W1=1)), step(200, 300, w(W2=1)), step(3000, 100, w(W1=1, W2=1))],
+    inputs=[step(200, 300, w(), X + 2), step(200, 300, w(), X, X + 2), step(20, 30, w(), X + 2, X + 2), step(5000, 300, w(W1=3, W2=3), X + 2, X + 2)],
+    halves=[forward(3000, w(2048, 512, 128), X + 2), backward(3000, w(2048, 512, 128), X + 2), backward(6000, w(2048, 128, 128), X + 2)], few=[forward(3000, w(1280, 128, 128), X + 2), forward(100, w(W1=1, W2=1), X + 2)],
     bilinear=[bilinear(300, 600, 256, X + 2), bilinear(300, 600, 256, X, X + 2), bilinear(300, 600, 256, X + 2, X + 6)])
 report(**out)
 """)
     named = lambda r, *k: [n for n in r[2] if any(x in n for x in k)]  # noqa: E731
-    assert all(r[0] == 0 and r[1] == 0 for k in got for r in got[k]), got
-    assert len(named(got["aligned"][0], *RING)) == 2 and len(named(got["aligned"][1], *RING)) == 1 and len(named(got["aligned"][2], *RING)) == 3
-    for k in ("forward", "many", "backward", "huge"):
+    copies = lambda r: len(named(r, "copy_aligned_kernel"))  # noqa: E731
+    rest = lambda r: [n for n in r[2] if "copy_aligned" not in n]  # noqa: E731
+    for k in got:
         for r in got[k]:
-            assert not named(r, *RING) and named(r, "skinny"), (k, r)
-    for k in ("biases", "w2"):
-        assert all(named(r, *RING) and not named(r, "skinny") for r in got[k]), k
-    assert len(named(got["many"][0], "mlp_skinny")) == 6 and len(named(got["huge"][0], "mlp_dh_skinny")) == 2
-    xq, xp, w1, w2 = got["step"]
-    assert len(named(xq, "mlp_hidden")) == len(named(xp, "mlp_hidden")) == 1 and not named(xq, "mlp_dh_tiled") and not named(xp, "mlp_dh_tiled")
-    assert not named(w1, *RING) and not named(w2, "mlp_hidden", "mlp_output") and named(w2, "mlp_dh_tiled")
-    for r, copies, ends in zip(got["aligned"][3:] + got["bilinear"], (0, 1, 1, 2), (1, 2, 1, 2)):
-        assert len(named(r, "copy_aligned_kernel")) == copies and len(named(r, "bilinear_end_kernel")) == ends, r
-        if copies:
-            assert "copy_aligned" in r[2][0] and "bilinear_project" in r[2][copies]
+            assert r[0] == 0 and r[1] == 0 and r[3] == 0, (k, r)
+    fwd, bwd, st, bil, mixed = got["aligned"]
+    assert len(named(fwd, *RING)) == 2 and len(named(bwd, *RING)) == 1 and len(named(st, *RING)) == 3 and not copies(st)
+    assert [copies(r) for r in got["forward"]] == [1, 1, 1, 3, 0] and [copies(r) for r in got["backward"]] == [1, 1, 2, 0, 0]
+    assert all(len(named(r, *RING)) == 2 and not named(r, "skinny") for r in got["forward"])
+    assert all(rest(r) == bwd[2] for r in got["backward"])
+    # (W2: of a backward only fragments are read.  3000 x 100: the copies for the anchors are over when the targets' fragments come)
+    assert [copies(r) for r in got["step"]] == [1, 1, 3] and rest(got["step"][0]) == rest(got["step"][1]) == st[2] and rest(got["step"][2]) == mixed[2]
+    one, other, few, many = got["inputs"]
+    assert copies(one) == copies(other) == 2 and len(named(one, *RING)) == len(named(other, *RING)) == 6 and not named(one, "skinny")
+    assert not copies(few) and named(few, "mlp_dh_skinny") and not named(few, *RING)
+    assert copies(many) == 2 + 2 * 4 and len(named(many, "mlp_hidden")) == 4 and len(named(many, "mlp_dh_tiled")) == 4
+    assert [copies(r) for r in got["halves"]] == [2, 2, 2] and [len(named(r, "mlp_hidden", "mlp_dh_tiled")) for r in got["halves"]] == [2, 2, 2]
+    assert all(not copies(r) and not named(r, *RING) and named(r, "mlp_skinny") for r in got["few"])
+    for r, n, ends in zip([bil] + got["bilinear"], (0, 1, 1, 2), (1, 2, 1, 2)):
+        assert copies(r) == n and len(named(r, "bilinear_end_kernel")) == ends, r
+        if n:
+            assert "copy_aligned" in r[2][0] and "bilinear_project" in r[2][n]
 
 
 # (rows, din, dh, dout): tiles in units of 64 of the hidden layer, the output layer, Act and dH, or None for the kernel for few rows; whether
